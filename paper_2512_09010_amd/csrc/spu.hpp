@@ -6,11 +6,19 @@ namespace luvc {
 
 constexpr int kSpuMaxN = 32768;     // tokens per sample (twiddle index arithmetic stays in int32)
 
+// Which kernels serve a score call (chosen from N and sigma alone)
+enum class SpuPath {
+    Fft,        // spu_fft16q: transform decomposition, N = 16 Q N2
+    DenseFused, // spu_dense_fused: direct pass-band DFT in one launch, small N and sigma
+    Conv,       // spu_conv: M-point transforms in one workgroup, any N up to 8192
+    Dense       // direct pass-band DFT through the workspace, any N
+};
+
 // Offsets (bytes) of the score kernels' scratch inside the caller's workspace.
 struct SpuLayout {
-    size_t tw, gk, gm, Fc, Fs, partial, gpartial, arrive, bytes;
+    size_t tw, gk, gm, Fc, Fs, spec, partial, gpartial, arrive, bytes;
     int n_tiles;
-    bool fast;      // transform-decomposition FFT path instead of the direct pass-band DFT
+    SpuPath path;
 };
 SpuLayout spu_layout(int B, int N, int D, int sigma);
 
@@ -22,6 +30,14 @@ bool spu_fft_supported(int N, int sigma);
 struct TileSync;
 luvc_status spu_score_fft(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
                           float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st);
+
+// Any N (spu_conv.hip): N <= 8192, or N = 16384
+int spu_conv_rows(int N, bool* half);
+int spu_conv_tiles(int B, int N, int D);
+size_t spu_conv_spec_bytes(int N);
+inline int spu_conv_ld(int N) { return (N + 3) / 4 * 4; }
+luvc_status spu_score_conv(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
+                           float* spec, float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st);
 
 luvc_status spu_prune_run(const void* x, const float* scores, int B, int N, int D, int64_t row_stride, luvc_dtype dt,
                           int n_keep, int32_t* kept_idx, void* x_out, const int32_t* origin_in, int32_t* origin_out, hipStream_t st);

@@ -1,0 +1,447 @@
+// SPU score (paper Section 3.3, Eq. 4-8) for any number of tokens and any pass band: one transform of M = 256 R points
+// (R = 16, 32, 64) forward, one back, all of it in the registers and the LDS of a workgroup.
+//
+// Eq. 4-7 together are a circular convolution of length N with the even kernel
+//     p[j] = 1/N sum_{|f| <= sigma} M[f] e^{2 pi i f j / N}.
+// N = M: the spectrum of the kernel is the mask itself, M[f] / N.  Any other N <= M / 2: the tokens are followed by M - N
+// zeros and the kernel is laid out over the lags -(N - 1) .. N - 1, so that the M-point circular convolution equals the
+// N-point one on the N tokens; its spectrum (real and even, like the kernel's) is
+//     P[k] = 1/(N M) sum_{|f| <= sigma} M[f] sin((2 N - 1) pi u) / sin(pi u),   u = f / N - k / M,
+// evaluated in fp64 by spu_conv_spectrum.  Nothing about N has to factor.
+//
+// Two channels of a token are one complex value (the filter is real).  A workgroup holds P channel pairs at a time:
+//   A    thread (pair c, column n2): tokens n2, n2 + 256, ... straight from memory, R-point DFT in registers over them,
+//        twiddle W_M^{k1 n2}, row k1 of the exchange grid [R][256][P] gets the result;
+//   B,C  256 points of a row = 16 x 16: both passes, the spectrum and the two inverse passes run inside one wavefront, in
+//        place, so nothing but the order of one wavefront's LDS accesses stands between them;
+//   A'   thread (c, n2) again: twiddle, R-point inverse DFT, |.|^2 added to the thread's R (R/2) token energies.
+// Two barriers per P pairs; the next pairs' tokens are fetched while B and C run.  A workgroup walks the pairs in steps of
+// the number of workgroups of its sample, so that at any time neighbouring workgroups (same XCD) read neighbouring
+// 4 P-byte pieces of the same cache lines, and keeps the energies in registers until its last pairs are done.
+// With half of the inputs zero and half of the outputs unwanted (N <= M / 2) passes A and A' take half the loads and skip a
+// butterfly level each.
+//
+// Bound: fp32 vector arithmetic (about 5 M log2 M flops per direction and pair) and the LDS traffic beside it (64 bytes per
+// point and pair).
+#include "common.hpp"
+#include "spu.hpp"
+#include "spu_fftcore.hpp"
+#include "spu_tiles.hpp"
+
+namespace luvc {
+
+namespace {
+
+// R-point DFT across the registers of a thread, natural order in and out; HALF: inputs j >= R/2 are zero and not read
+// (forward), outputs j >= R/2 are not formed (inverse)
+template <int R, bool HALF> struct dft_cols;
+template <bool HALF> struct dft_cols<16, HALF> {
+    __device__ static __forceinline__ void fwd(cf (&v)[16]) { fft16<false, HALF>(v); }
+    __device__ static __forceinline__ void inv(cf (&v)[16]) { fft16<true>(v); }
+};
+template <bool HALF> struct dft_cols<32, HALF> {
+    __device__ static __forceinline__ void fwd(cf (&v)[32])
+    {
+        cf e[16], o[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const cf a = v[j], s = HALF ? a : a + v[j + 16], d = HALF ? a : a - v[j + 16];
+            e[j] = s;
+            o[j] = j ? cmul(d, w64(2 * j)) : d;
+        }
+        fft16<false>(e);
+        fft16<false>(o);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) { v[2 * q] = e[q]; v[2 * q + 1] = o[q]; }
+    }
+    __device__ static __forceinline__ void inv(cf (&v)[32])
+    {
+        cf e[16], o[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) { e[q] = v[2 * q]; o[q] = v[2 * q + 1]; }
+        fft16<true>(e);
+        fft16<true>(o);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const cf t = j ? cmulc(o[j], w64(2 * j)) : o[j];
+            v[j] = e[j] + t;
+            if (!HALF) v[j + 16] = e[j] - t;
+        }
+    }
+};
+template <bool HALF> struct dft_cols<64, HALF> {
+    __device__ static __forceinline__ void fwd(cf (&v)[64])
+    {
+        cf u[4][16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            cf a0 = v[j], a1 = v[j + 16], a2 = HALF ? cf{0.f, 0.f} : v[j + 32], a3 = HALF ? cf{0.f, 0.f} : v[j + 48];
+            if (HALF) bf4_half<false>(a0, a1, a2, a3);
+            else bf4<false>(a0, a1, a2, a3);
+            u[0][j] = a0;
+            u[1][j] = j ? cmul(a1, w64(j)) : a1;
+            u[2][j] = j ? cmul(a2, w64(2 * j)) : a2;
+            u[3][j] = j ? cmul(a3, w64(3 * j)) : a3;
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            fft16<false>(u[s]);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[4 * q + s] = u[s][q];
+        }
+    }
+    __device__ static __forceinline__ void inv(cf (&v)[64])
+    {
+        cf u[4][16];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) u[s][q] = v[4 * q + s];
+            fft16<true>(u[s]);
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            cf a0 = u[0][j];
+            cf a1 = j ? cmulc(u[1][j], w64(j)) : u[1][j];
+            cf a2 = j ? cmulc(u[2][j], w64(2 * j)) : u[2][j];
+            cf a3 = j ? cmulc(u[3][j], w64(3 * j)) : u[3][j];
+            bf4<true>(a0, a1, a2, a3);
+            v[j] = a0;
+            v[j + 16] = a1;
+            if (!HALF) { v[j + 32] = a2; v[j + 48] = a3; }
+        }
+    }
+};
+
+// one channel pair as it lies in memory: by buffer access (one instruction, bounds by the descriptor) or element by element
+template <typename T> struct raw_pair;
+template <> struct raw_pair<bf16_t> {
+    uint32_t v;
+    __device__ static __forceinline__ raw_pair load(__amdgpu_buffer_rsrc_t r, uint32_t off) { return {__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0)}; }
+    __device__ static __forceinline__ raw_pair load(const bf16_t* p, bool second)
+    {
+        const uint32_t lo = p[0].bits, hi = second ? p[1].bits : 0u;
+        return {lo | (hi << 16)};
+    }
+    __device__ __forceinline__ cf widen() const { return {__uint_as_float(v << 16), __uint_as_float(v & 0xffff0000u)}; }
+};
+typedef unsigned int u32x2 __attribute__((__vector_size__(8)));
+template <> struct raw_pair<float> {
+    u32x2 v;
+    __device__ static __forceinline__ raw_pair load(__amdgpu_buffer_rsrc_t r, uint32_t off) { return {__builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0)}; }
+    __device__ static __forceinline__ raw_pair load(const float* p, bool second)
+    {
+        raw_pair o;
+        o.v[0] = __float_as_uint(p[0]);
+        o.v[1] = second ? __float_as_uint(p[1]) : 0u;
+        return o;
+    }
+    __device__ __forceinline__ cf widen() const { return {__uint_as_float(v[0]), __uint_as_float(v[1])}; }
+};
+
+// LDS accesses of one wavefront are served in order: this only keeps the compiler from moving them
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+}  // namespace
+
+// P[k], k = 0 .. M/2.  A workgroup owns kSpecBins bins; its threads split the frequencies f >= 1 of each bin.  With
+// a = pi f / N and b = pi k / M the terms of +f and -f add to
+//     -sin(2 pi N k / M) sin 2b / (sin(a - b) sin(a + b)) - 2 cos(2 pi N k / M),
+// and to 2 N - 2 where f / N = k / M (4 N - 2 where both are 1/2: then -f / N and k / M differ by 1).
+constexpr int kSpecBins = 8, kSpecLanes = 256 / kSpecBins;
+__global__ void __launch_bounds__(256)
+spu_conv_spectrum(int N, int M, int sigma, int use_hamming, float* __restrict__ spec /* [M/2 + 1] */)
+{
+    __shared__ double sn[256], cs[256], wt[256];
+    __shared__ double part[kSpecBins][kSpecLanes];
+    const int tid = threadIdx.x, g = tid / kSpecLanes, l = tid % kSpecLanes;
+    const int k = blockIdx.x * kSpecBins + g;
+    double sb, cb, s2, c2, sk, ck;
+    sincospi((double)k / (double)M, &sb, &cb);
+    sincospi(2.0 * (double)k / (double)M, &s2, &c2);
+    sincospi(2.0 * (double)(((int64_t)N * k) % M) / (double)M, &sk, &ck);
+    double acc = 0.0;
+    for (int f0 = 1; f0 <= sigma; f0 += 256) {
+        const int f = f0 + tid;
+        __syncthreads();
+        if (f <= sigma) {
+            double s, c;
+            sincospi((double)f / (double)N, &s, &c);
+            sn[tid] = s;
+            cs[tid] = c;
+            // 2 sigma = N: the bins f = N/2 and f = -N/2 are the same one
+            wt[tid] = (2 * f == N ? 0.5 : 1.0) * (use_hamming ? 0.54 + 0.46 * cospi(2.0 * (double)f / (double)(N - 1)) : 1.0);
+        }
+        __syncthreads();
+        const int cnt = sigma - f0 + 1 < 256 ? sigma - f0 + 1 : 256;
+        for (int i = l; i < cnt; i += kSpecLanes) {
+            const double d = sn[i] * cb - cs[i] * sb, s = sn[i] * cb + cs[i] * sb;
+            const bool same = (int64_t)(f0 + i) * M == (int64_t)k * N;
+            const double t = same ? (2 * k == M ? 4.0 : 2.0) * (double)N - 2.0 : -sk * s2 / (d * s) - 2.0 * ck;
+            acc += wt[i] * t;
+        }
+    }
+    part[g][l] = acc;
+    __syncthreads();
+    if (l == 0 && k <= M / 2) {
+        double tot = k == 0 ? 2.0 * (double)N - 1.0 : sk * cb / sb - ck;            // f = 0, weight 1
+        for (int i = 0; i < kSpecLanes; ++i) tot += part[g][i];
+        spec[k] = (float)(tot / ((double)N * (double)M));
+    }
+}
+
+template <typename T, int R, int P, bool HALF /* N <= M/2: zeros behind the tokens; else N = M */, bool PAIRED /* every pair is one aligned access */>
+__global__ void __launch_bounds__(256 * P)
+spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, int use_hamming,
+         const float* __restrict__ spec /* HALF: [M/2 + 1] */, int n_groups /* of P pairs, per sample */,
+         int ld, float* __restrict__ partial /* [B, n_tiles, ld] */, float* __restrict__ gpartial, const TileSync sy,
+         float* __restrict__ scores /* [B, N] */)
+{
+    constexpr int M = 256 * R, THREADS = 256 * P, JN = HALF ? R / 2 : R;
+    constexpr int LROW = 272 * P;                // complex values per row of the exchange grid: 16 x (16 + 1 pad) x P
+    constexpr int ROWS = 4 / P, NIT = R / 16;    // rows a wavefront takes at a time, and how often
+    constexpr bool SPEC_LDS = R == 16;           // the spectrum in LDS (registers are short at 1024 threads) or in registers
+    extern __shared__ float2 sm[];               // [R][LROW]; the M-entry table while the twiddles are picked
+    float2* twb = sm + R * LROW;                 // [256] (cos, sin)(2 pi i / 256)
+    float* sp = reinterpret_cast<float*>(twb + 256);               // SPEC_LDS: [R k1][16 kb][16 ka]
+    __shared__ int flag;
+    const int tid = threadIdx.x, c = tid % P, n2 = tid / P, lane = tid & 63;
+    const int n_tiles = gridDim.x;
+    const unsigned item = xcd_contiguous(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+    const int tile = item % n_tiles, b = item / n_tiles;
+
+    const T* xs = x + (int64_t)b * N * row_stride;
+    using raw_t = raw_pair<T>;
+    raw_t raw[JN];
+    // PAIRED: a descriptor per block of 256 tokens that ends with the sample (a lane past it, or past D, reads zeros)
+    const uint32_t row_bytes = (uint32_t)row_stride * (uint32_t)sizeof(T);
+    const uint32_t lane_off = (uint32_t)n2 * row_bytes + (uint32_t)c * 2u * (uint32_t)sizeof(T);
+    auto fetch = [&](int g) {
+        const int d0 = (g * P + c) * 2;
+        if constexpr (PAIRED) {
+            const uint32_t off = d0 < D ? lane_off : 0x80000000u;
+#pragma unroll
+            for (int j = 0; j < JN; ++j) {
+                const int rows = HALF ? N - 256 * j : 256;         // rows of this block (at most 256 count: n2 < 256)
+                const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<T*>(xs) + (int64_t)(256 * j) * row_stride + 2 * P * g, 0,
+                    rows <= 0 ? 0 : (int)((uint32_t)((rows < 256 ? rows : 256) - 1) * row_bytes + (uint32_t)((D - 2 * P * g) * (int)sizeof(T))), 0x00020000);
+                raw[j] = raw_t::load(r, off);
+            }
+        } else {
+            const bool live = d0 < D, second = d0 + 1 < D;
+            const T* p = xs + (live ? d0 : 0);
+#pragma unroll
+            for (int j = 0; j < JN; ++j) {
+                const int n = 256 * j + n2;
+                const bool there = live && (!HALF || n < N);
+                raw[j] = there ? raw_t::load(p + (int64_t)n * row_stride, second) : raw_t{};
+            }
+        }
+    };
+    fetch(tile);
+
+    // ---- tables: one octant of the circle in fp64, rounded once, the rest by symmetry
+    for (int i = tid; i <= M / 8; i += THREADS) {
+        double sd, cd;
+        sincospi(2.0 * (double)i / (double)M, &sd, &cd);
+        const float cs = (float)cd, sn = (float)sd;
+        constexpr int n4 = M / 4, nh = M / 2, n34 = nh + n4;
+        sm[i] = make_float2(cs, sn);
+        sm[n4 - i] = make_float2(sn, cs);
+        sm[n4 + i] = make_float2(-sn, cs);
+        sm[nh - i] = make_float2(-cs, sn);
+        sm[nh + i] = make_float2(-cs, -sn);
+        sm[n34 - i] = make_float2(-sn, -cs);
+        sm[n34 + i] = make_float2(sn, -cs);
+        if (i) sm[M - i] = make_float2(cs, -sn);
+    }
+    auto weight = [&](int k) {                   // P[k] / mask
+        const int f = k <= M / 2 ? k : M - k;
+        if (HALF) return spec[f];
+        float w = 0.f;
+        if (f <= sigma) {
+            double v = 1.0;
+            if (use_hamming) v = 0.54 + 0.46 * cospi(2.0 * (double)f / (double)(N - 1));
+            w = (float)(v / (double)N);
+        }
+        return w;
+    };
+    const int lw = lane / P % 16;                // b of pass B, ka of pass C
+    const int wrow = (tid >> 6) * ROWS + lane / (16 * P);          // row within an iteration's 16
+    float wr[SPEC_LDS ? 1 : NIT][16];
+    if (SPEC_LDS) {
+        for (int i = tid; i < M; i += THREADS) sp[i] = weight((i >> 8) + R * ((i & 15) + 16 * ((i >> 4) & 15)));
+    } else {
+#pragma unroll
+        for (int it = 0; it < NIT; ++it)
+#pragma unroll
+            for (int kb = 0; kb < 16; ++kb) wr[it % (SPEC_LDS ? 1 : NIT)][kb] = weight(it * 16 + wrow + R * (lw + 16 * kb));
+    }
+    __syncthreads();
+    cf wa[R];                                    // W_M^{k1 n2} (conjugated on use)
+#pragma unroll
+    for (int k1 = 1; k1 < R; ++k1) { const float2 w = sm[(k1 * n2) & (M - 1)]; wa[k1] = {w.x, w.y}; }
+    if (tid < 256) twb[tid] = sm[tid * R];
+    float acc[JN];
+#pragma unroll
+    for (int j = 0; j < JN; ++j) acc[j] = 0.f;
+    __syncthreads();
+
+    float2* col = sm + (n2 + n2 / 16) * P + c;   // this thread's column of the grid
+    tile_tag_t seen = 0;
+    for (int g = tile; g < n_groups; g += n_tiles) {
+        // ---- A
+        {
+            cf v[R];
+#pragma unroll
+            for (int j = 0; j < JN; ++j) v[j] = raw[j].widen();
+            dft_cols<R, HALF>::fwd(v);
+            col[0] = make_float2(v[0].x, v[0].y);
+#pragma unroll
+            for (int k1 = 1; k1 < R; ++k1) {
+                const cf r = cmulc(v[k1], wa[k1]);
+                col[k1 * LROW] = make_float2(r.x, r.y);
+            }
+        }
+        if (g + n_tiles < n_groups) fetch(g + n_tiles);            // in flight during B and C
+        else seen = tiles_look<4>(sy, b, tile, n_tiles);
+        __syncthreads();
+        // ---- B, C, spectrum, C', B'
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int k1 = it * 16 + wrow;
+            float2* row = sm + k1 * LROW + c;
+            cf v[16];
+#pragma unroll
+            for (int a = 0; a < 16; ++a) { const float2 q = row[(17 * a + lw) * P]; v[a] = {q.x, q.y}; }
+            fft16<false>(v);
+#pragma unroll
+            for (int ka = 0; ka < 16; ++ka) {
+                const float2 w = twb[ka * lw];
+                const cf r = ka ? cmulc(v[ka], cf{w.x, w.y}) : v[ka];
+                row[(17 * ka + lw) * P] = make_float2(r.x, r.y);
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < 16; ++i) { const float2 q = row[(17 * lw + i) * P]; v[i] = {q.x, q.y}; }
+            fft16<false>(v);
+#pragma unroll
+            for (int kb = 0; kb < 16; ++kb) {
+                const float w = SPEC_LDS ? sp[(k1 * 16 + kb) * 16 + lw] : wr[it % (SPEC_LDS ? 1 : NIT)][kb];
+                v[kb] = {v[kb].x * w, v[kb].y * w};
+            }
+            fft16<true>(v);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float2 w = twb[i * lw];
+                const cf r = i ? cmul(v[i], cf{w.x, w.y}) : v[i];
+                row[(17 * lw + i) * P] = make_float2(r.x, r.y);
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int ka = 0; ka < 16; ++ka) { const float2 q = row[(17 * ka + lw) * P]; v[ka] = {q.x, q.y}; }
+            fft16<true>(v);
+#pragma unroll
+            for (int a = 0; a < 16; ++a) row[(17 * a + lw) * P] = make_float2(v[a].x, v[a].y);
+        }
+        __syncthreads();
+        // ---- A'
+        {
+            cf v[R];
+            { const float2 q = col[0]; v[0] = {q.x, q.y}; }
+#pragma unroll
+            for (int k1 = 1; k1 < R; ++k1) { const float2 q = col[k1 * LROW]; v[k1] = cmul(cf{q.x, q.y}, wa[k1]); }
+            dft_cols<R, HALF>::inv(v);
+#pragma unroll
+            for (int j = 0; j < JN; ++j) acc[j] = fmaf(v[j].x, v[j].x, fmaf(v[j].y, v[j].y, acc[j]));
+        }
+    }
+    tiles_claim<4>(sy, b, tile, n_tiles, seen);
+    // ---- Eq. 8: over the P pairs of a thread group, then across the workgroups of the sample
+    float* pout = partial + ((int64_t)b * n_tiles + tile) * ld;
+#pragma unroll
+    for (int j = 0; j < JN; ++j) {
+        float e = acc[j];
+        if (P >= 2) e += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(e), 0xB1, 0xf, 0xf, false));    // quad_perm [1,0,3,2]
+        if (P >= 4) e += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(e), 0x4E, 0xf, 0xf, false));    // quad_perm [2,3,0,1]
+        const int n = 256 * j + n2;
+        if (c == 0 && n < ld) tile_store(pout + n, n < N ? e : 0.f);
+    }
+    tiles_to_scores<THREADS, 4>(partial, gpartial, sy, scores, b, tile, n_tiles, N, ld, &flag);
+}
+
+// ------------------------------------------------------------------ host side
+// R = M / 256 for N tokens; *half: zeros behind the tokens (N <= M / 2), else N = M.  0: too long.
+int spu_conv_rows(int N, bool* half)
+{
+    for (int R : {16, 32, 64})
+        if (2 * N <= 256 * R || N == 256 * R) { *half = N != 256 * R; return R; }
+    return 0;
+}
+
+static int conv_pairs(int R) { return 64 / R; }
+
+// Workgroups per sample.  One workgroup fills a compute unit; a workgroup's time is its pair groups plus about one more
+// for tables and hand-over, and the launch takes as many rounds of that as there are multiples of 256 workgroups.
+int spu_conv_tiles(int B, int N, int D)
+{
+    bool half;
+    const int R = spu_conv_rows(N, &half), P = conv_pairs(R), ng = (D + 2 * P - 1) / (2 * P);
+    int best = ng;
+    int64_t best_cost = INT64_MAX;
+    for (int g = 1; g <= ng && g <= 64; ++g) {
+        const int t = (ng + g - 1) / g;
+        const int64_t cost = (((int64_t)B * t + 255) / 256) * (g + 1);
+        if (cost < best_cost) { best_cost = cost; best = t; }
+    }
+    return best;
+}
+
+size_t spu_conv_spec_bytes(int N)
+{
+    bool half;
+    const int R = spu_conv_rows(N, &half);
+    return half ? sizeof(float) * (size_t)(128 * R + 1) : 0;
+}
+
+template <typename T, int R, int P>
+static void conv_launch(const T* x, int B, int N, int D, int64_t row_stride, int sigma, int use_hamming, bool half, bool aligned,
+                        const float* spec, float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st)
+{
+    const int ng = (D + 2 * P - 1) / (2 * P), ld = spu_conv_ld(N);
+    const size_t lds = sizeof(float2) * (size_t)(R * 272 * P + 256) + (R == 16 ? sizeof(float) * 256 * R : 0);
+    const dim3 grid((unsigned)n_tiles, (unsigned)B), block(256 * P);
+#define LUVC_CONV(HF, AL) LUVC_LAUNCH("spu_conv", (spu_conv<T, R, P, HF, AL>), grid, block, lds, st, x, N, D, row_stride, sigma, use_hamming, spec, ng, ld, partial, gpartial, sy, scores)
+    if (half) { if (aligned) LUVC_CONV(true, true); else LUVC_CONV(true, false); }
+    else      { if (aligned) LUVC_CONV(false, true); else LUVC_CONV(false, false); }
+#undef LUVC_CONV
+}
+
+luvc_status spu_score_conv(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
+                           float* spec, float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st)
+{
+    bool half;
+    const int R = spu_conv_rows(N, &half);
+    const size_t es = dt == LUVC_F32 ? 4 : 2;
+    // 255 rows and a row's width have to stay below the offset that marks a lane without channels
+    const bool aligned = (row_stride % 2 == 0) && ((uintptr_t)x % (2 * es) == 0) && (D % 2 == 0) && row_stride * (int64_t)es < ((int64_t)1 << 22);
+    if (half) {
+        const int M = 256 * R;
+        LUVC_LAUNCH("spu_conv_spectrum", spu_conv_spectrum, dim3((unsigned)(M / 2 / kSpecBins + 1)), dim3(256), 0, st, N, M, sigma, use_hamming, spec);
+    }
+#define LUVC_CONV_R(TT) do { \
+        if (R == 16)      conv_launch<TT, 16, 4>((const TT*)x, B, N, D, row_stride, sigma, use_hamming, half, aligned, spec, partial, gpartial, sy, n_tiles, scores, st); \
+        else if (R == 32) conv_launch<TT, 32, 2>((const TT*)x, B, N, D, row_stride, sigma, use_hamming, half, aligned, spec, partial, gpartial, sy, n_tiles, scores, st); \
+        else              conv_launch<TT, 64, 1>((const TT*)x, B, N, D, row_stride, sigma, use_hamming, half, aligned, spec, partial, gpartial, sy, n_tiles, scores, st); \
+    } while (0)
+    if (dt == LUVC_F32) LUVC_CONV_R(float); else LUVC_CONV_R(bf16_t);
+#undef LUVC_CONV_R
+    return check_launch("spu score (convolution)");
+}
+
+}  // namespace luvc

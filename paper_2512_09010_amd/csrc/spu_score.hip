@@ -352,7 +352,7 @@ spu_dense_fused(const T* __restrict__ x, int N, int D, int64_t row_stride, int s
         }
         if (pb == wave) tiles_claim<1>(sy, b, tile, n_tiles, seen);    // by the end of the loop the swap has long been served
     }
-    tiles_to_scores<64 * kDfWaves, 1>(partial, gpartial, sy, scores, b, tile, n_tiles, N, &flag);
+    tiles_to_scores<64 * kDfWaves, 1>(partial, gpartial, sy, scores, b, tile, n_tiles, N, N, &flag);
 }
 
 // Tags of the arrival words (spu_tiles.hpp): one per launch, from a process-wide sequence that starts at a random
@@ -377,21 +377,31 @@ tile_tag_t spu_next_tag()
 }
 
 // ------------------------------------------------------------------ host side
+static SpuPath spu_path(int N, int sigma)
+{
+    bool half;
+    if (spu_fft_supported(N, sigma)) return SpuPath::Fft;
+    if (dense_fused_lds(N, sigma) <= dense_fused_cap()) return SpuPath::DenseFused;
+    return spu_conv_rows(N, &half) ? SpuPath::Conv : SpuPath::Dense;
+}
+
 SpuLayout spu_layout(int B, int N, int D, int sigma)
 {
     SpuLayout L;
-    L.fast = spu_fft_supported(N, sigma);
-    L.n_tiles = L.fast ? (D + 31) / 32 : (D + 63) / 64;
-    const size_t spec = L.fast ? 0 : (size_t)B * (sigma + 1) * D;   // pass-band spectra of the direct path
+    L.path = spu_path(N, sigma);
+    L.n_tiles = L.path == SpuPath::Fft ? (D + 31) / 32 : L.path == SpuPath::Conv ? spu_conv_tiles(B, N, D) : (D + 63) / 64;
+    const bool dense = L.path == SpuPath::Dense;                     // the one path whose tables and spectra do not stay in LDS
+    const size_t spec = dense ? (size_t)B * (sigma + 1) * D : 0;     // pass-band spectra
+    const size_t ld = L.path == SpuPath::Conv ? spu_conv_ld(N) : N;
     size_t off = 0;
-    // the fast path builds its tables in LDS
-    L.tw = off;      off += L.fast ? 0 : align_up(sizeof(float2) * (size_t)N);
-    L.gk = off;      off += L.fast ? 0 : align_up(sizeof(float) * (size_t)(sigma + 1));
-    L.gm = off;      off += L.fast ? 0 : align_up(sizeof(float) * (size_t)(sigma + 1));
+    L.tw = off;      off += dense ? align_up(sizeof(float2) * (size_t)N) : 0;
+    L.gk = off;      off += dense ? align_up(sizeof(float) * (size_t)(sigma + 1)) : 0;
+    L.gm = off;      off += dense ? align_up(sizeof(float) * (size_t)(sigma + 1)) : 0;
     L.Fc = off;      off += align_up(sizeof(float) * spec);
     L.Fs = off;      off += align_up(sizeof(float) * spec);
-    L.partial = off; off += align_up(sizeof(float) * (size_t)B * L.n_tiles * N);
-    L.gpartial = off; off += align_up(sizeof(float) * (size_t)B * spu_tile_groups(L.n_tiles) * N);
+    L.spec = off;    off += L.path == SpuPath::Conv ? align_up(spu_conv_spec_bytes(N)) : 0;
+    L.partial = off; off += align_up(sizeof(float) * (size_t)B * L.n_tiles * ld);
+    L.gpartial = off; off += align_up(sizeof(float) * (size_t)B * spu_tile_groups(L.n_tiles) * ld);
     L.arrive = off;  off += align_up(sizeof(tile_tag_t) * (size_t)B * (spu_tile_groups(L.n_tiles) + 1));
     L.bytes = off;
     return L;
@@ -413,8 +423,10 @@ luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stri
     TileSync sy;
     sy.arrive = (tile_tag_t*)(ws + L.arrive);
     sy.tag = spu_next_tag();
-    if (L.fast) return spu_score_fft(x, B, N, D, row_stride, dt, sigma, use_hamming, partial, gpartial, sy, L.n_tiles, scores, st);
-    if (dense_fused_lds(N, sigma) <= dense_fused_cap()) {
+    if (L.path == SpuPath::Fft) return spu_score_fft(x, B, N, D, row_stride, dt, sigma, use_hamming, partial, gpartial, sy, L.n_tiles, scores, st);
+    if (L.path == SpuPath::Conv)
+        return spu_score_conv(x, B, N, D, row_stride, dt, sigma, use_hamming, (float*)(ws + L.spec), partial, gpartial, sy, L.n_tiles, scores, st);
+    if (L.path == SpuPath::DenseFused) {
         const dim3 grid((unsigned)L.n_tiles, (unsigned)B);
         if (dt == LUVC_F32)
             LUVC_LAUNCH("spu_dense_fused", (spu_dense_fused<float>), grid, dim3(64 * kDfWaves), dense_fused_lds(N, sigma), st,

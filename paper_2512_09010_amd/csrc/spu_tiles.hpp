@@ -68,13 +68,13 @@ __device__ __forceinline__ void tile_store(__amdgpu_buffer_rsrc_t r, uint32_t by
     }
 }
 
-// out[n] = sum over `count` rows (row stride N floats) of in[row][n], added in row order in fp64; FIN: square root.
-// Up to TRIP rows per trip, all loads of a trip in flight together (a short trip re-reads its last row).
+// out[n] = sum over `count` rows (row stride ld floats) of in[row][n], n < N, added in row order in fp64; FIN: square
+// root.  W = 4 needs ld % 4 == 0.  Up to TRIP rows per trip, all loads of a trip in flight together (a short trip re-reads its last row).
 template <int THREADS, int W, bool FIN, int TRIP = kTileGroup>
-__device__ __forceinline__ void tile_rows_sum(const float* in, int count, int N, float* out)
+__device__ __forceinline__ void tile_rows_sum(const float* in, int count, int N, int ld, float* out)
 {
-    const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in), 0, count * N * 4, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, N * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in), 0, count * ld * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, ld * 4, 0x00020000);
     for (int i = threadIdx.x * W; i < N; i += THREADS * W) {
         double e[W];
 #pragma unroll
@@ -84,7 +84,7 @@ __device__ __forceinline__ void tile_rows_sum(const float* in, int count, int N,
             tile_vec<W> p[TRIP];
 #pragma unroll
             for (int r = 0; r < TRIP; ++r)
-                p[r] = tile_load<W>(rin, (uint32_t)(((r0 + (r < left ? r : left - 1)) * N + i) * 4));
+                p[r] = tile_load<W>(rin, (uint32_t)(((r0 + (r < left ? r : left - 1)) * ld + i) * 4));
 #pragma unroll
             for (int r = 0; r < TRIP; ++r)
 #pragma unroll
@@ -95,7 +95,8 @@ __device__ __forceinline__ void tile_rows_sum(const float* in, int count, int N,
         for (int c = 0; c < W; ++c) o.v[c] = FIN ? (float)sqrt(e[c]) : (float)e[c];
         if (FIN) {
 #pragma unroll
-            for (int c = 0; c < W; ++c) out[i + c] = o.v[c];       // scores: ordinary stores, no alignment assumed
+            for (int c = 0; c < W; ++c)
+                if (W == 1 || i + c < N) out[i + c] = o.v[c];      // scores: ordinary stores, no alignment assumed
         } else {
             tile_store<W>(rout, (uint32_t)(i * 4), o);
         }
@@ -162,15 +163,15 @@ __device__ __forceinline__ bool tiles_arrive(tile_tag_t* w, int total)
 }
 
 // Called by all THREADS threads of the workgroup of (sample b, tile) after they have written the tile's
-// energies to partial[(b * n_tiles + tile) * N + n] with tile_store().  `flag` is a __shared__ word.
-// W = 4 needs N % 4 == 0 (and the 256-byte alignment the workspace has anyway).  A sample of at most
+// energies to partial[(b * n_tiles + tile) * ld + n] with tile_store().  `flag` is a __shared__ word.
+// W = 4 needs ld % 4 == 0 (and the 256-byte alignment the workspace has anyway).  A sample of at most
 // kTileGroup tiles has no group level: its last workgroup adds the tiles directly.
 template <int THREADS, int W>
-__device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [B, n_tiles, N] */,
-                                                float* __restrict__ gpartial /* [B, n_groups, N] */,
+__device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [B, n_tiles, ld] */,
+                                                float* __restrict__ gpartial /* [B, n_groups, ld] */,
                                                 const TileSync sy,
                                                 float* __restrict__ scores /* [B, N] */,
-                                                int b, int tile, int n_tiles, int N, int* flag)
+                                                int b, int tile, int n_tiles, int N, int ld, int* flag)
 {
     const int tid = threadIdx.x;
     const int n_groups = spu_tile_groups(n_tiles);
@@ -184,8 +185,8 @@ __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [
         if (tid == 0) *flag = tiles_arrive(cnt + 1 + grp, t_cnt);
         __syncthreads();
         if (!*flag) return;
-        tile_rows_sum<THREADS, W, false>(partial + ((int64_t)b * n_tiles + t_first) * N, t_cnt, N,
-                                         gpartial + ((int64_t)b * n_groups + grp) * N);
+        tile_rows_sum<THREADS, W, false>(partial + ((int64_t)b * n_tiles + t_first) * ld, t_cnt, N, ld,
+                                         gpartial + ((int64_t)b * n_groups + grp) * ld);
     }
     const int last_cnt = two_level ? n_groups : n_tiles;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -194,9 +195,9 @@ __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [
     __syncthreads();
     if (!*flag) return;
     if (two_level)
-        tile_rows_sum<THREADS, W, true>(gpartial + (int64_t)b * n_groups * N, last_cnt, N, scores + (int64_t)b * N);
+        tile_rows_sum<THREADS, W, true>(gpartial + (int64_t)b * n_groups * ld, last_cnt, N, ld, scores + (int64_t)b * N);
     else
-        tile_rows_sum<THREADS, W, true, (W == 1 ? kTileGroupOneLevelMax : kTileGroup)>(partial + (int64_t)b * n_tiles * N, last_cnt, N, scores + (int64_t)b * N);
+        tile_rows_sum<THREADS, W, true, (W == 1 ? kTileGroupOneLevelMax : kTileGroup)>(partial + (int64_t)b * n_tiles * ld, last_cnt, N, ld, scores + (int64_t)b * N);
 }
 
 // Host side: 48-bit non-zero tag of the next launch (process-wide sequence, random start)

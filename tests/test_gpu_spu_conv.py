@@ -1,0 +1,38 @@
+"""GPU parity of the score on lengths that no factorisation serves (spu_conv: one M-point transform forward and back, zeros
+behind the tokens unless N is M itself) against the CPU oracle: both sides of every length limit, the smallest and widest
+pass bands (2 sigma = N included), channel counts around a workgroup's share, unaligned rows."""
+import numpy as np
+import pytest
+
+from paper_2512_09010_amd import workloads as wl
+from test_gpu_spu import score_case
+
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,N,D,sigma,pad", [
+    (2, 1999, 70, 300, 0), (1, 2048, 33, 1024, 0), (1, 2047, 9, 1023, 7),      # M = 4096
+    (1, 2049, 24, 130, 0), (2, 4095, 6, 2047, 0), (1, 3001, 130, 20, 3),       # M = 8192
+    (1, 4097, 5, 60, 0), (1, 8191, 3, 11, 1), (1, 8192, 4, 200, 0),            # M = 16384; N = M = 8192
+    (1, 4096, 70, 2048, 0), (2, 4096, 17, 128, 2), (1, 16384, 2, 40, 0),       # N = M
+    (1, 1501, 64, 0, 0), (1, 1025, 8, 512, 0),
+])
+def test_score_any_length(oracle, dtype, B, N, D, sigma, pad):
+    rng = np.random.default_rng(N * 7 + D)
+    x = wl.cast_io(rng.standard_normal((B, N, D)).astype(np.float32), dtype)
+    score_case(oracle, x, dtype, sigma, True, "random", stride_pad=pad)
+    walk = wl.cast_io((np.cumsum(rng.standard_normal((B, N, D)), axis=1) / np.sqrt(N)).astype(np.float32), dtype)
+    score_case(oracle, walk, dtype, sigma, False, "walk-rect", stride_pad=pad)
+
+
+def test_many_channel_groups_per_workgroup(oracle):
+    """More channel groups than workgroups fit the chip: a workgroup keeps its energies over several of them."""
+    rng = np.random.default_rng(5)
+    x = wl.cast_io(rng.standard_normal((6, 1026, 1100)).astype(np.float32), "bf16")
+    xd, got, _ = score_case(oracle, x, "bf16", 9, True, "groups")
+    from paper_2512_09010_amd import binding as lv
+    for _ in range(3):
+        assert torch.equal(lv.luvc_spu_score(xd, 9, True), got)
