@@ -79,9 +79,23 @@ static bool walk_schedule(int B, int H, int W, int D, const luvc_oim_pass* passe
     return true;
 }
 
+// Schedules of adjacent matching that run on grids of row ids: some pass takes fewer than all sources out of its lines,
+// so that most tokens go through the call unchanged (or every pass takes none: a copy).  Schedules of halvings keep the
+// fused kernels, which move every token anyway.
+static bool takes_few(const OimPlan& pl, const luvc_oim_pass* passes)
+{
+    bool none = true;
+    for (int i = 0; i < pl.n; ++i) {
+        const int len = passes[i].axis ? pl.w[i] : pl.h[i];
+        if (passes[i].m != 0 && passes[i].m != (len + 1) / 2) return true;
+        none = none && passes[i].m == 0;
+    }
+    return none;
+}
+
 struct OimLayout {
     size_t xbuf[2], sbuf[2], kbuf[2], maps[kMaxPasses], n2, dn, anchor, absorb, gram, srcdest, lazy_idx[2], lazy_ov, bytes;
-    int lazy_cap;      // overlay rows per image (wide matching with one launch per pass)
+    int lazy_cap;      // overlay rows per image (grids of row ids)
 };
 
 static OimLayout oim_layout(int B, int D, luvc_dtype dt, const OimPlan& pl, const luvc_oim_pass* passes = nullptr, int radius = 1)
@@ -121,15 +135,16 @@ static OimLayout oim_layout(int B, int D, luvc_dtype dt, const OimPlan& pl, cons
         }
     L.gram = off;    off += align_up(gram);
     L.srcdest = off; off += align_up(srcdest);
-    // wide matching with one launch per pass: two grids of row ids and the rows of the merged destinations
+    // one launch per pass: two grids of row ids and the rows of the merged destinations
     // (whether a call can run that way depends on the alignment of its buffers, so the space is always there)
     int64_t cap = 0;
-    if (radius != 1 && passes)
+    const bool ids = passes && (radius != 1 || takes_few(pl, passes));
+    if (ids)
         for (int i = 0; i < pl.n; ++i) cap += oim_wide_lazy_rows(pl.h[i], pl.w[i], passes[i].axis, passes[i].m);
     L.lazy_cap = (int)cap;
     for (int j = 0; j < 2; ++j) {
         L.lazy_idx[j] = off;
-        off += (radius != 1 && passes) ? align_up((size_t)B * pl.h[0] * pl.w[0] * sizeof(int32_t)) : 0;
+        off += ids ? align_up((size_t)B * pl.h[0] * pl.w[0] * sizeof(int32_t)) : 0;
     }
     L.lazy_ov = off; off += align_up((size_t)B * (size_t)cap * D * esize(dt));
     L.bytes = off;
@@ -213,27 +228,90 @@ size_t luvc_oim_workspace_bytes(int B, int H, int W, int D, luvc_dtype dtype, co
 {
     OimPlan pl;
     if (!dtype_ok(dtype) || !walk_schedule(B, H, W, D, passes, n_passes, &pl)) return 0;
-    return oim_layout(B, D, dtype, pl).bytes;
+    return oim_layout(B, D, dtype, pl, passes, 1).bytes;
+}
+
+// The passes of a schedule that take something out of their lines (a pass with m = 0 changes nothing: no token, size or
+// map), on the grids they see.  At least one pass stays.
+static OimPlan drop_empty_passes(const OimPlan& pl, const luvc_oim_pass* passes, luvc_oim_pass* kept)
+{
+    OimPlan out;
+    out.n = 0;
+    for (int i = 0; i < pl.n; ++i) {
+        if (passes[i].m == 0 && !(out.n == 0 && i + 1 == pl.n)) continue;
+        kept[out.n] = passes[i];
+        out.h[out.n] = pl.h[i];
+        out.w[out.n] = pl.w[i];
+        ++out.n;
+    }
+    out.h[out.n] = pl.h[pl.n];
+    out.w[out.n] = pl.w[pl.n];
+    return out;
+}
+
+// Can a schedule run on grids of row ids, given aligned rows?
+static bool lazy_supported(int64_t n0, const OimPlan& pl, const luvc_oim_pass* passes, int radius, int64_t cap)
+{
+    if ((radius == 1 && !takes_few(pl, passes)) || n0 + cap >= ((int64_t)1 << 31)) return false;
+    for (int i = 0; i < pl.n; ++i)
+        if ((passes[i].axis ? pl.w[i] : pl.h[i]) > kLazyMaxLen) return false;
+    return true;
+}
+
+// One launch per pass on grids of row ids, decided on `metric` (or on x); the tokens (and the metric) move once at the end.
+static luvc_status lazy_run(const void* x, const void* metric, void* metric_ov, int Dm, const int32_t* sizes_in, int B, int D, luvc_dtype dtype,
+                            const OimPlan& pl, const luvc_oim_pass* passes, int radius, const OimLayout& L, char* ws,
+                            void* x_out, void* metric_out, int32_t* sizes_out, int32_t* merged_map, int32_t* kept_map, hipStream_t st)
+{
+    const int n0 = pl.h[0] * pl.w[0];
+    const int32_t *cur_i = nullptr, *cur_sz = sizes_in, *cur_kp = nullptr;
+    PassMaps maps;
+    maps.n = 0;
+    int ov_base = 0;
+    for (int i = 0; i < pl.n; ++i) {
+        const int h = pl.h[i], w = pl.w[i], axis = passes[i].axis, m = passes[i].m;
+        if (m == 0) break;                               // the only pass, and nothing to do
+        const bool last = i + 1 == pl.n;
+        int32_t* oi = (int32_t*)(ws + L.lazy_idx[i & 1]);
+        int32_t* os = last ? sizes_out : (int32_t*)(ws + L.sbuf[i & 1]);
+        int32_t* ok = last ? kept_map : (int32_t*)(ws + L.kbuf[i & 1]);
+        int32_t* pm = merged_map ? (pl.n == 1 ? merged_map : (int32_t*)(ws + L.maps[i])) : nullptr;
+        maps.map[i] = pm;
+        maps.n_in[i] = h * w;
+        maps.n = i + 1;
+        const luvc_status rc = radius == 1
+            ? oim_adjacent_pass(x, ws + L.lazy_ov, metric, metric_ov, Dm, cur_i, cur_sz, cur_kp, B, n0, h, w, D, dtype, axis, m, L.lazy_cap, ov_base, oi, os, ok, pm, st)
+            : oim_wide_lazy_pass(x, ws + L.lazy_ov, metric, metric_ov, Dm, cur_i, cur_sz, cur_kp, B, n0, h, w, D, dtype, axis, m, radius, L.lazy_cap, ov_base, oi, os, ok, pm, st);
+        if (rc != LUVC_OK) return rc;
+        ov_base += oim_wide_lazy_rows(h, w, axis, m);
+        cur_i = oi;
+        cur_sz = os;
+        cur_kp = ok;
+    }
+    const int es = (int)esize(dtype);
+    LazyOutput outs[2] = {{x, ws + L.lazy_ov, x_out, D * es}, {metric, metric_ov, metric_out, Dm * es}};
+    return oim_lazy_finish(outs, metric_out ? 2 : 1, cur_i, B, n0, L.lazy_cap, pl.h[pl.n] * pl.w[pl.n], maps,
+                           maps.n == 1 ? nullptr : merged_map, sizes_in, sizes_out, kept_map, st);
 }
 
 static luvc_status oim_merge_impl(const void* x, const int32_t* sizes_in, int B, int H, int W, int D, luvc_dtype dtype,
-                                  const luvc_oim_pass* passes, int n_passes, int radius, int64_t target_tokens,
+                                  const luvc_oim_pass* all_passes, int n_passes, int radius, int64_t target_tokens,
                                   void* x_out, int32_t* sizes_out, int32_t* merged_map, int32_t* kept_map,
                                   void* workspace, size_t workspace_bytes, void* hip_stream)
 {
     if (!dtype_ok(dtype)) { set_error("unknown dtype %d", (int)dtype); return LUVC_ERR_INVALID_ARG; }
     if (!x || !x_out || !sizes_out) { set_error("x, x_out and sizes_out must not be NULL"); return LUVC_ERR_INVALID_ARG; }
-    OimPlan pl;
-    if (!walk_schedule(B, H, W, D, passes, n_passes, &pl)) return LUVC_ERR_INVALID_ARG;
-    const int Ho = pl.h[pl.n], Wo = pl.w[pl.n];
+    OimPlan full;
+    if (!walk_schedule(B, H, W, D, all_passes, n_passes, &full)) return LUVC_ERR_INVALID_ARG;
+    const int Ho = full.h[full.n], Wo = full.w[full.n];
     if (target_tokens != 0 && target_tokens != (int64_t)Ho * Wo) {
         set_error("schedule ends at %dx%d = %lld tokens, target is %lld", Ho, Wo, (long long)Ho * Wo, (long long)target_tokens);
         return LUVC_ERR_INVALID_ARG;
     }
     if (radius < 0) { set_error("radius must be 0 (whole line) or positive"); return LUVC_ERR_INVALID_ARG; }
     if (radius != 1)
-        for (int i = 0; i < pl.n; ++i)
-            if ((passes[i].axis ? pl.w[i] : pl.h[i]) > kMaxWideLineLen) {
+        for (int i = 0; i < full.n; ++i)
+            if ((all_passes[i].axis ? full.w[i] : full.h[i]) > kMaxWideLineLen) {
                 set_error("pass %d: wide matching supports lines of at most %d tokens", i, kMaxWideLineLen);
                 return LUVC_ERR_UNSUPPORTED;
             }
@@ -241,44 +319,18 @@ static luvc_status oim_merge_impl(const void* x, const int32_t* sizes_in, int B,
         set_error("wide matching supports grids of less than 2 GiB per image");
         return LUVC_ERR_UNSUPPORTED;
     }
-    const OimLayout L = oim_layout(B, D, dtype, pl, passes, radius);
+    const OimLayout L = oim_layout(B, D, dtype, full, all_passes, radius);
     if (!workspace_ok(workspace, workspace_bytes, L.bytes)) return LUVC_ERR_WORKSPACE;
+    luvc_oim_pass passes[kMaxPasses];
+    const OimPlan pl = drop_empty_passes(full, all_passes, passes);
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
     const size_t es = esize(dtype);
     // 16-byte accesses need aligned rows in every buffer the kernels touch
     const bool vec = ((size_t)D * es) % 16 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)x_out % 16 == 0;
 
-    bool lazy = radius != 1 && vec && (int64_t)H * W + L.lazy_cap < ((int64_t)1 << 31);
-    for (int i = 0; i < pl.n; ++i)
-        if ((passes[i].axis ? pl.w[i] : pl.h[i]) > kLazyMaxLen) lazy = false;
-    if (lazy) {
-        // one launch per pass on grids of row ids, the tokens move once at the end
-        const int32_t *cur_i = nullptr, *cur_sz = sizes_in, *cur_kp = nullptr;
-        const int32_t* lmaps[kMaxPasses];
-        int32_t ln_in[kMaxPasses];
-        int ov_base = 0;
-        for (int i = 0; i < pl.n; ++i) {
-            const bool last = i + 1 == pl.n;
-            int32_t* oi = (int32_t*)(ws + L.lazy_idx[i & 1]);
-            int32_t* os = last ? sizes_out : (int32_t*)(ws + L.sbuf[i & 1]);
-            int32_t* ok = last ? kept_map : (int32_t*)(ws + L.kbuf[i & 1]);
-            int32_t* pm = merged_map ? ((pl.n == 1) ? merged_map : (int32_t*)(ws + L.maps[i])) : nullptr;
-            lmaps[i] = pm;
-            ln_in[i] = pl.h[i] * pl.w[i];
-            const luvc_status rc = oim_wide_lazy_pass(x, ws + L.lazy_ov, nullptr, nullptr, 0, cur_i, cur_sz, cur_kp, B, H * W, pl.h[i], pl.w[i], D, dtype,
-                                                      passes[i].axis, passes[i].m, radius, L.lazy_cap, ov_base, oi, os, ok, pm, st);
-            if (rc != LUVC_OK) return rc;
-            ov_base += oim_wide_lazy_rows(pl.h[i], pl.w[i], passes[i].axis, passes[i].m);
-            cur_i = oi;
-            cur_sz = os;
-            cur_kp = ok;
-        }
-        const luvc_status rc = oim_wide_lazy_gather(x, ws + L.lazy_ov, cur_i, B, H * W, L.lazy_cap, Ho * Wo, D, dtype, x_out, st);
-        if (rc != LUVC_OK) return rc;
-        if (merged_map && pl.n > 1) return oim_compose(lmaps, ln_in, pl.n, B, H * W, merged_map, st);
-        return LUVC_OK;
-    }
+    if (vec && lazy_supported((int64_t)H * W, pl, passes, radius, L.lazy_cap))
+        return lazy_run(x, nullptr, nullptr, 0, sizes_in, B, D, dtype, pl, passes, radius, L, ws, x_out, nullptr, sizes_out, merged_map, kept_map, st);
 
     OimScratch sc;
     sc.n2 = (double*)(ws + L.n2);
@@ -299,8 +351,8 @@ static luvc_status oim_merge_impl(const void* x, const int32_t* sizes_in, int B,
         steps[n_steps++] = Step{i, pair ? 2 : 1};
         i += pair ? 2 : 1;
     }
-    const int32_t* maps[kMaxPasses];
-    int32_t n_in[kMaxPasses];
+    PassMaps maps;
+    maps.n = n_steps;
     for (int s = 0; s < n_steps; ++s) {
         const int i = steps[s].first, e = i + steps[s].count - 1;          // passes i..e
         const bool last = e + 1 == pl.n;
@@ -310,8 +362,8 @@ static luvc_status oim_merge_impl(const void* x, const int32_t* sizes_in, int B,
         int32_t* ok = last ? kept_map : (int32_t*)(ws + L.kbuf[s & 1]);
         // a call that is a single launch writes its map straight to the caller
         int32_t* pm = (n_steps == 1 && merged_map) ? merged_map : (int32_t*)(ws + L.maps[i]);
-        maps[s] = pm;
-        n_in[s] = pl.h[i] * pl.w[i];
+        maps.map[s] = pm;
+        maps.n_in[s] = pl.h[i] * pl.w[i];
         luvc_status rc;
         if (radius != 1)
             rc = oim_wide_pass(cur_x, cur_s, B, pl.h[i], pl.w[i], D, dtype, passes[i].axis, passes[i].m, radius, vec,
@@ -328,7 +380,7 @@ static luvc_status oim_merge_impl(const void* x, const int32_t* sizes_in, int B,
         cur_s = os;
         cur_k = ok;
     }
-    if (merged_map && n_steps > 1) return oim_compose(maps, n_in, n_steps, B, H * W, merged_map, st);
+    if (merged_map && n_steps > 1) return oim_compose(maps, B, H * W, merged_map, st);
     return LUVC_OK;
 }
 
@@ -399,23 +451,23 @@ size_t luvc_oim_keyed_workspace_bytes(int B, int H, int W, int D, int Dm, luvc_d
 
 luvc_status luvc_oim_merge_keyed(const void* x, const void* metric, const int32_t* sizes_in,
                                  int B, int H, int W, int D, int Dm, luvc_dtype dtype,
-                                 const luvc_oim_pass* passes, int n_passes, int radius, int64_t target_tokens,
+                                 const luvc_oim_pass* all_passes, int n_passes, int radius, int64_t target_tokens,
                                  void* x_out, void* metric_out, int32_t* sizes_out, int32_t* merged_map, int32_t* kept_map,
                                  void* workspace, size_t workspace_bytes, void* hip_stream)
 {
     if (!dtype_ok(dtype)) { set_error("unknown dtype %d", (int)dtype); return LUVC_ERR_INVALID_ARG; }
     if (!x || !metric || !x_out || !sizes_out) { set_error("x, metric, x_out and sizes_out must not be NULL"); return LUVC_ERR_INVALID_ARG; }
     if (!keyed_args_ok(radius, Dm)) return LUVC_ERR_INVALID_ARG;
-    OimPlan pl;
-    if (!walk_schedule(B, H, W, D, passes, n_passes, &pl)) return LUVC_ERR_INVALID_ARG;
-    const int Ho = pl.h[pl.n], Wo = pl.w[pl.n];
+    OimPlan full;
+    if (!walk_schedule(B, H, W, D, all_passes, n_passes, &full)) return LUVC_ERR_INVALID_ARG;
+    const int Ho = full.h[full.n], Wo = full.w[full.n];
     if (target_tokens != 0 && target_tokens != (int64_t)Ho * Wo) {
         set_error("schedule ends at %dx%d = %lld tokens, target is %lld", Ho, Wo, (long long)Ho * Wo, (long long)target_tokens);
         return LUVC_ERR_INVALID_ARG;
     }
     if (radius != 1) {
-        for (int i = 0; i < pl.n; ++i)
-            if ((passes[i].axis ? pl.w[i] : pl.h[i]) > kMaxWideLineLen) {
+        for (int i = 0; i < full.n; ++i)
+            if ((all_passes[i].axis ? full.w[i] : full.h[i]) > kMaxWideLineLen) {
                 set_error("pass %d: wide matching supports lines of at most %d tokens", i, kMaxWideLineLen);
                 return LUVC_ERR_UNSUPPORTED;
             }
@@ -424,9 +476,11 @@ luvc_status luvc_oim_merge_keyed(const void* x, const void* metric, const int32_
             return LUVC_ERR_UNSUPPORTED;
         }
     }
-    const KeyedLayout K = keyed_layout(B, D, Dm, dtype, pl, passes, radius);
+    const KeyedLayout K = keyed_layout(B, D, Dm, dtype, full, all_passes, radius);
     const OimLayout& L = K.base;
     if (!workspace_ok(workspace, workspace_bytes, K.bytes)) return LUVC_ERR_WORKSPACE;
+    luvc_oim_pass passes[kMaxPasses];
+    const OimPlan pl = drop_empty_passes(full, all_passes, passes);
     hipStream_t st = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
     const size_t es = esize(dtype);
@@ -440,40 +494,8 @@ luvc_status luvc_oim_merge_keyed(const void* x, const void* metric, const int32_
     double* G = (double*)(ws + L.gram);
     int32_t* src_dest = (int32_t*)(ws + L.srcdest);
 
-    bool lazy = radius != 1 && vec_x && vec_m && (int64_t)H * W + L.lazy_cap < ((int64_t)1 << 31);
-    for (int i = 0; i < pl.n; ++i)
-        if ((passes[i].axis ? pl.w[i] : pl.h[i]) > kLazyMaxLen) lazy = false;
-    if (lazy) {
-        // wide matching on the metric, one launch per pass on grids of row ids; tokens and metric move once at the end
-        const int32_t *cur_i = nullptr, *cur_sz = sizes_in, *cur_kp = nullptr;
-        const int32_t* lmaps[kMaxPasses];
-        int32_t ln_in[kMaxPasses];
-        int ov_base = 0;
-        for (int i = 0; i < pl.n; ++i) {
-            const bool last = i + 1 == pl.n;
-            int32_t* oi = (int32_t*)(ws + L.lazy_idx[i & 1]);
-            int32_t* os = last ? sizes_out : (int32_t*)(ws + L.sbuf[i & 1]);
-            int32_t* ok = last ? kept_map : (int32_t*)(ws + L.kbuf[i & 1]);
-            int32_t* pm = merged_map ? ((pl.n == 1) ? merged_map : (int32_t*)(ws + L.maps[i])) : nullptr;
-            lmaps[i] = pm;
-            ln_in[i] = pl.h[i] * pl.w[i];
-            const luvc_status rc = oim_wide_lazy_pass(x, ws + L.lazy_ov, metric, ws + K.mov, Dm, cur_i, cur_sz, cur_kp, B, H * W, pl.h[i], pl.w[i],
-                                                      D, dtype, passes[i].axis, passes[i].m, radius, L.lazy_cap, ov_base, oi, os, ok, pm, st);
-            if (rc != LUVC_OK) return rc;
-            ov_base += oim_wide_lazy_rows(pl.h[i], pl.w[i], passes[i].axis, passes[i].m);
-            cur_i = oi;
-            cur_sz = os;
-            cur_kp = ok;
-        }
-        luvc_status rc = oim_wide_lazy_gather(x, ws + L.lazy_ov, cur_i, B, H * W, L.lazy_cap, Ho * Wo, D, dtype, x_out, st);
-        if (rc != LUVC_OK) return rc;
-        if (metric_out) {
-            rc = oim_wide_lazy_gather(metric, ws + K.mov, cur_i, B, H * W, L.lazy_cap, Ho * Wo, Dm, dtype, metric_out, st);
-            if (rc != LUVC_OK) return rc;
-        }
-        if (merged_map && pl.n > 1) return oim_compose(lmaps, ln_in, pl.n, B, H * W, merged_map, st);
-        return LUVC_OK;
-    }
+    if (vec_x && vec_m && lazy_supported((int64_t)H * W, pl, passes, radius, L.lazy_cap))
+        return lazy_run(x, metric, ws + K.mov, Dm, sizes_in, B, D, dtype, pl, passes, radius, L, ws, x_out, metric_out, sizes_out, merged_map, kept_map, st);
 
     const void *cur_x = x, *cur_m = metric;
     const int32_t* cur_s = sizes_in;
@@ -488,8 +510,8 @@ luvc_status luvc_oim_merge_keyed(const void* x, const void* metric, const int32_
         steps[n_steps++] = Step{i, pair ? 2 : 1};
         i += pair ? 2 : 1;
     }
-    const int32_t* maps[kMaxPasses];
-    int32_t n_in[kMaxPasses];
+    PassMaps maps;
+    maps.n = n_steps;
     for (int s = 0; s < n_steps; ++s) {
         const int i = steps[s].first, e = i + steps[s].count - 1;          // passes i..e
         const bool last = e + 1 == pl.n;
@@ -499,8 +521,8 @@ luvc_status luvc_oim_merge_keyed(const void* x, const void* metric, const int32_
         int32_t* os = last ? sizes_out : (int32_t*)(ws + L.sbuf[s & 1]);
         int32_t* ok = last ? kept_map : (int32_t*)(ws + L.kbuf[s & 1]);
         int32_t* pm = (n_steps == 1 && merged_map) ? merged_map : (int32_t*)(ws + L.maps[i]);
-        maps[s] = pm;
-        n_in[s] = h * w;
+        maps.map[s] = pm;
+        maps.n_in[s] = h * w;
         luvc_status rc;
         if (steps[s].count == 2) {
             rc = oim_pair_keyed_pass(cur_x, cur_m, cur_s, B, h, w, D, Dm, dtype, axis, ox, (last && !metric_out) ? nullptr : om, os, pm, cur_k, ok, st);
@@ -523,7 +545,7 @@ luvc_status luvc_oim_merge_keyed(const void* x, const void* metric, const int32_
         cur_s = os;
         cur_k = ok;
     }
-    if (merged_map && n_steps > 1) return oim_compose(maps, n_in, n_steps, B, H * W, merged_map, st);
+    if (merged_map && n_steps > 1) return oim_compose(maps, B, H * W, merged_map, st);
     return LUVC_OK;
 }
 

@@ -220,12 +220,6 @@ oim_merge(const T* __restrict__ x, const int32_t* __restrict__ sizes_in,
 }
 
 // ------------------------------------------------------------------ map composition over the passes of a call
-struct PassMaps {
-    const int32_t* map[kMaxPasses];
-    int32_t n_in[kMaxPasses];
-    int n;
-};
-
 __global__ void __launch_bounds__(256)
 oim_compose_merged(PassMaps pm, int64_t total, int n_first, int32_t* __restrict__ merged_out)
 {
@@ -303,12 +297,8 @@ luvc_status oim_general_pass(const void* x, const int32_t* sizes_in, int B, int 
     return oim_general_apply(x, sizes_in, B, H, W, D, dt, axis, m, vec, x_out, sizes_out, kept_prev, kept_out, ws, st);
 }
 
-luvc_status oim_compose(const int32_t* const* maps, const int32_t* n_in, int n, int B, int n_first,
-                        int32_t* merged_out, hipStream_t st)
+luvc_status oim_compose(const PassMaps& pm, int B, int n_first, int32_t* merged_out, hipStream_t st)
 {
-    PassMaps pm;
-    pm.n = n;
-    for (int i = 0; i < n; ++i) { pm.map[i] = maps[i]; pm.n_in[i] = n_in[i]; }
     const int64_t total = (int64_t)B * n_first;
     LUVC_LAUNCH("oim_compose_merged", oim_compose_merged, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, pm, total, n_first,
                        merged_out);

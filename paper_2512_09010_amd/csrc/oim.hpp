@@ -36,15 +36,29 @@ luvc_status oim_wide_pass(const void* x, const int32_t* sizes_in, int B, int H, 
 
 // Wide matching with one launch per pass and the tokens moved once, at the end (oim_wide_lazy.hip): grids between the
 // passes are tensors of row ids (below n0: a token of x; from n0: a row of the overlay `ov`, which receives the merged
-// destinations).  Lines of at most kLazyMaxLen tokens, 16-byte aligned rows.
+// destinations).  Lines of at most kLazyMaxLen tokens, 16-byte aligned rows.  oim_adjacent_pass (oim_adjacent.hip): the same
+// with the adjacent destinations as candidates.
 constexpr int kLazyMaxLen = 128;
 int oim_wide_lazy_rows(int h, int w, int axis, int m);      // overlay rows per image that a pass may write
 // metric / ov_metric / Dm: the tensor the decisions are taken on and its overlay (merged like x), or NULL / NULL / 0: x itself
 luvc_status oim_wide_lazy_pass(const void* x, void* ov, const void* metric, void* ov_metric, int Dm, const int32_t* idx_in, const int32_t* sizes_in, const int32_t* kept_in,
                                int B, int n0, int h, int w, int D, luvc_dtype dt, int axis, int m, int radius, int cap, int ov_base,
                                int32_t* idx_out, int32_t* sizes_out, int32_t* kept_out, int32_t* pass_map, hipStream_t st);
-luvc_status oim_wide_lazy_gather(const void* x, const void* ov, const int32_t* idx, int B, int n0, int cap, int n_out_per, int D,
-                                 luvc_dtype dt, void* x_out, hipStream_t st);
+luvc_status oim_adjacent_pass(const void* x, void* ov, const void* metric, void* ov_metric, int Dm, const int32_t* idx_in, const int32_t* sizes_in, const int32_t* kept_in,
+                              int B, int n0, int h, int w, int D, luvc_dtype dt, int axis, int m, int cap, int ov_base,
+                              int32_t* idx_out, int32_t* sizes_out, int32_t* kept_out, int32_t* pass_map, hipStream_t st);
+
+// Maps of the launches of a call, first to last: input flat index of launch k -> output slot
+struct PassMaps {
+    const int32_t* map[kMaxPasses];
+    int32_t n_in[kMaxPasses];
+    int n;
+};
+// The end of such a call in one launch: the rows behind the final ids to the outputs (tokens, and the metric where it is
+// wanted), the composition of the pass maps.  idx NULL: no pass took anything out, and sizes and kept_map are written here too.
+struct LazyOutput { const void *x, *ov; void* out; int row_bytes; };
+luvc_status oim_lazy_finish(const LazyOutput* outs, int n_outs, const int32_t* idx, int B, int n0, int cap, int n_out_per, const PassMaps& maps,
+                            int32_t* merged_map, const int32_t* sizes_in, int32_t* sizes_out, int32_t* kept_map, hipStream_t st);
 
 // The two stages of a pass on their own: decisions on one tensor (`metric`), merge applied to another.
 luvc_status oim_general_decide(const void* metric, int B, int H, int W, int Dm, luvc_dtype dt, int axis, int m, bool vec,
@@ -82,7 +96,6 @@ luvc_status oim_pair_keyed_pass(const void* x, const void* metric, const int32_t
                                 luvc_dtype dt, int first_axis, void* x_out, void* metric_out, int32_t* sizes_out, int32_t* pair_map,
                                 const int32_t* kept_prev, int32_t* kept_out, hipStream_t st);
 
-luvc_status oim_compose(const int32_t* const* maps, const int32_t* n_in, int n, int B, int n_first,
-                        int32_t* merged_out, hipStream_t st);
+luvc_status oim_compose(const PassMaps& maps, int B, int n_first, int32_t* merged_out, hipStream_t st);
 
 }  // namespace luvc

@@ -15,62 +15,6 @@ namespace luvc {
 
 namespace {
 
-// ------------------------------------------------------------------ fp64 sums over the wavefront, eight at a time
-__device__ __forceinline__ double dpp_get64(double v, const int sel)
-{
-    const float lo = dpp_get(__int_as_float(__double2loint(v)), sel), hi = dpp_get(__int_as_float(__double2hiint(v)), sel);
-    return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
-}
-
-// v + (v of the lane 32 away), then 16 away: lane-swap instructions on both halves of the value
-__device__ __forceinline__ double add_far_lanes64(double r)
-{
-    const uint32_t lo = (uint32_t)__double2loint(r), hi = (uint32_t)__double2hiint(r);
-    const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    r = __hiloint2double((int)h32[0], (int)l32[0]) + __hiloint2double((int)h32[1], (int)l32[1]);
-    const uint32_t lo2 = (uint32_t)__double2loint(r), hi2 = (uint32_t)__double2hiint(r);
-    const auto l16 = __builtin_amdgcn_permlane16_swap(lo2, lo2, false, false), h16 = __builtin_amdgcn_permlane16_swap(hi2, hi2, false, false);
-    return __hiloint2double((int)h16[0], (int)l16[0]) + __hiloint2double((int)h16[1], (int)l16[1]);
-}
-
-// Eight wave64 sums at once, the scheme of wave_total32x8: three exchange steps (lanes 1, 2, 4 apart) after which a
-// lane keeps only the partial sum of value (lane & 7), then lanes 8, 32 and 16 apart.  Every step adds the partial sums
-// of two lane groups, so all eight values - and wave_total64b below - are summed over the same tree: a sum has the
-// same bits in whichever of these places it is formed, which two workgroups that look at one source rely on.
-__device__ __forceinline__ void wave_total64x8(double (&v)[8], int lane)
-{
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
-    double p[4], q[2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const double keep = b0 ? v[2 * i + 1] : v[2 * i], send = b0 ? v[2 * i] : v[2 * i + 1];
-        p[i] = keep + dpp_get64(send, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const double keep = b1 ? p[2 * i + 1] : p[2 * i], send = b1 ? p[2 * i] : p[2 * i + 1];
-        q[i] = keep + dpp_get64(send, 1);
-    }
-    const double keep = b2 ? q[1] : q[0], send = b2 ? q[0] : q[1];
-    double r = keep + dpp_get64(dpp_get64(send, 2), 3);             // (lane ^ 7) ^ 3 = lane ^ 4
-    r += dpp_get64(r, 4);
-    r = add_far_lanes64(r);
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        v[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(r), i), __builtin_amdgcn_readlane(__double2loint(r), i));
-}
-
-// one sum over the same tree
-__device__ __forceinline__ double wave_total64b(double v)
-{
-    v += dpp_get64(v, 0);
-    v += dpp_get64(v, 1);
-    v += dpp_get64(dpp_get64(v, 2), 3);
-    v += dpp_get64(v, 4);
-    v = add_far_lanes64(v);
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 0), __builtin_amdgcn_readlane(__double2loint(v), 0));
-}
-
 // fp64 squared norms n[p] = <P_p, P_p> and neighbour products d[p] = <P_p, P_p+1> of five metric rows that follow
 // each other on a line; n[4], the ninth sum, only with FIVE
 template <typename T, bool FIVE, int MQ, int MW>

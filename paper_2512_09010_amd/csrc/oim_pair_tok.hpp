@@ -3,6 +3,7 @@
 // the decision expressions, the size-weighted merge with one rounding, and the cut of long lines into runs.
 #pragma once
 #include "common.hpp"
+#include "oim_sum64.hpp"
 #include "oim.hpp"
 
 namespace luvc {
@@ -122,18 +123,6 @@ template <> __device__ __forceinline__ float dot_word<float>(float acc, uint32_t
 // value in every lane.  Then one add across the half rows, one across the two halves of the wave
 // and one across neighbouring rows (lane-swap instructions), and lane i holds the total of value i.
 // Six additions per term, like the one-value sum above.
-__device__ __forceinline__ float dpp_get(float v, const int sel)
-{
-    const int x = __float_as_int(v);
-    switch (sel) {
-        case 0: return __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, true));    // quad_perm [1,0,3,2]: lane ^ 1
-        case 1: return __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, true));    // quad_perm [2,3,0,1]: lane ^ 2
-        case 2: return __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, true));   // row_half_mirror: lane ^ 7
-        case 3: return __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x1B, 0xf, 0xf, true));    // quad_perm [3,2,1,0]: lane ^ 3
-        default: return __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, true));  // row_ror:8: lane ^ 8
-    }
-}
-
 __device__ __forceinline__ void wave_total32x8(float (&v)[8], int lane)
 {
     const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;

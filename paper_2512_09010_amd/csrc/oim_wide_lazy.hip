@@ -6,7 +6,7 @@
 // input, id >= n0 a row of the "overlay", the buffer that receives every token a merge produces.  A pass reads the
 // ids of its grid, fetches the tokens behind them, and writes the ids of the next grid (compacted: survivors move
 // up on their line), the sizes, the anchors and the pass map; only the merged destinations - at most m per line -
-// are written as tokens, into overlay rows of their own.  After the last pass oim_wide_gather copies the rows behind
+// are written as tokens, into overlay rows of their own.  After the last pass oim_lazy_finish copies the rows behind
 // the final ids to the output.  A pass that rewrote its whole grid would move 97 % of the tokens unchanged when two
 // of 64 leave a line.
 //
@@ -29,29 +29,15 @@
 //      ascending position, fp64, one rounding), a wavefront per destination.
 #include "common.hpp"
 #include "oim.hpp"
+#include "oim_lazy.hpp"
 #include "oim_wide_tok.hpp"
 
 namespace luvc {
 
 namespace {
 
-struct LazyGeom {
-    int n0;         // tokens per image of the call's input grid: ids below it are rows of x
-    int h, w;       // grid before this pass
-    int D, axis, m, radius;
-    int cap;        // overlay rows per image over the whole call
-    int ov_base;    // first overlay row of this pass
-    int per_line;   // overlay rows a line of this pass may write: min(m, destinations of the line)
-};
-
 // floats between the rows of the screened matrix: the smallest value of at least n_dst that is 4 mod 32
 __host__ __device__ inline int lazy_row_stride(int n_dst) { return n_dst <= 4 ? 4 : 32 * ((n_dst - 4 + 31) / 32) + 4; }
-
-template <typename T>
-__device__ __forceinline__ const T* row_of(const T* x, const T* ov, int64_t b, int id, const LazyGeom& g, int D)
-{
-    return id < g.n0 ? x + (b * g.n0 + id) * D : ov + (b * g.cap + (id - g.n0)) * D;
-}
 
 }  // namespace
 
@@ -528,54 +514,77 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     }
 }
 
-// ------------------------------------------------------------------ the rows behind the final ids
+// ------------------------------------------------------------------ the end of a call
 typedef unsigned int lazy_u32x4 __attribute__((__vector_size__(16)));
-__device__ __forceinline__ const unsigned char* lazy_row(const unsigned char* x, const unsigned char* ov, const int32_t* idx, int64_t row,
-                                                         int n0, int cap, int n_out_per, int row_bytes)
-{
-    const int64_t b = row / n_out_per;
-    int id = idx[row];
-    id = id < 0 ? 0 : (id >= n0 + cap ? n0 + cap - 1 : id);            // ids come from oim_wide_line; stay in bounds regardless
-    return id < n0 ? x + (b * n0 + id) * (int64_t)row_bytes : ov + (b * cap + (id - n0)) * (int64_t)row_bytes;
-}
 
-// one wavefront per row
+struct FinishPart {
+    const unsigned char *x, *ov;
+    unsigned char* out;
+    int row_bytes, lanes;        // lanes per row: 16 or 32 for rows of at most 256 or 512 bytes, else the wavefront
+    unsigned blocks;
+};
+struct FinishArgs {
+    FinishPart part[2];          // tokens, metric (0 blocks: not wanted)
+    const int32_t* idx;          // final ids, or null: the input grid as it is
+    int n0, cap, n_out_per;
+    int64_t n_rows, n_tok;       // output rows, input tokens of the whole call
+    PassMaps maps;
+    int32_t* merged_map;         // or null
+    const int32_t* sizes_in;     // the rest only where idx is null
+    int32_t *sizes_out, *kept_map;
+};
+
+// Three kinds of workgroup in one launch (none waits for another): rows of the tokens, rows of the metric, the composition
+// of the pass maps, 256 entries each.  Rows are copied eight 16-byte pieces per lane at a time; short rows (the keys of
+// one attention head) several to a wavefront, since a wavefront is three memory round trips long whatever it moves.
+// Bound: HBM (8 x 64 x 64 x 1280 bf16: 20.4 us for 138 MB).
 __global__ void __launch_bounds__(256)
-oim_wide_gather(const unsigned char* __restrict__ x, const unsigned char* __restrict__ ov, const int32_t* __restrict__ idx,
-                int n0, int cap, int n_out_per, int row_bytes, int64_t n_rows, unsigned char* __restrict__ x_out)
+oim_lazy_finish_k(FinishArgs a)
 {
-    const int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    unsigned blk = blockIdx.x;
     const int lane = threadIdx.x & 63;
-    if (row >= n_rows) return;
-    const unsigned char* in = lazy_row(x, ov, idx, row, n0, cap, n_out_per, row_bytes);
-    unsigned char* o = x_out + row * (int64_t)row_bytes;
-    // eight 16-byte pieces per lane in flight before the first store; the descriptors bound every piece
-    const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(in), 0, row_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(o, 0, row_bytes, 0x00020000);
-    for (int base = 0; base < row_bytes; base += 8 * 1024) {
-        lazy_u32x4 v[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(ri, base + k * 1024 + lane * 16, 0, 0);
+    for (int q = 0; q < 2; ++q) {
+        const FinishPart& f = a.part[q];
+        if (blk < f.blocks) {
+            const int per_wave = 64 / f.lanes;
+            const int64_t row = ((int64_t)blk * 4 + (threadIdx.x >> 6)) * per_wave + lane / f.lanes;
+            if (row >= a.n_rows) return;
+            const int64_t b = row / a.n_out_per;
+            int id = a.idx ? a.idx[row] : (int)(row - b * a.n_out_per);
+            id = id < 0 ? 0 : (id >= a.n0 + a.cap ? a.n0 + a.cap - 1 : id);            // ids come from the passes; stay in bounds regardless
+            const unsigned char* in = id < a.n0 ? f.x + (b * a.n0 + id) * (int64_t)f.row_bytes : f.ov + (b * a.cap + (id - a.n0)) * (int64_t)f.row_bytes;
+            unsigned char* o = f.out + row * (int64_t)f.row_bytes;
+            if (f.lanes < 64) {
+                const int off = lane % f.lanes * 16;
+                if (off < f.row_bytes) *reinterpret_cast<lazy_u32x4*>(o + off) = *reinterpret_cast<const lazy_u32x4*>(in + off);
+                return;
+            }
+            // the descriptors bound every piece
+            const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(in), 0, f.row_bytes, 0x00020000);
+            const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(o, 0, f.row_bytes, 0x00020000);
+            for (int base = 0; base < f.row_bytes; base += 8 * 1024) {
+                lazy_u32x4 v[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) __builtin_amdgcn_raw_buffer_store_b128(v[k], ro, base + k * 1024 + lane * 16, 0, 2);
+                for (int k = 0; k < 8; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(ri, base + k * 1024 + lane * 16, 0, 0);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) __builtin_amdgcn_raw_buffer_store_b128(v[k], ro, base + k * 1024 + lane * 16, 0, 2);
+            }
+            return;
+        }
+        blk -= f.blocks;
     }
-}
-
-// short rows (at most 512 bytes, e.g. the keys of one attention head): LPR = 16 or 32 lanes per row, several rows per
-// wavefront, so that a launch has a quarter or half of the wavefronts - each is three memory round trips long whatever it moves
-template <int LPR>
-__global__ void __launch_bounds__(256)
-oim_wide_gather_short(const unsigned char* __restrict__ x, const unsigned char* __restrict__ ov, const int32_t* __restrict__ idx,
-                      int n0, int cap, int n_out_per, int row_bytes, int64_t n_rows, unsigned char* __restrict__ x_out)
-{
-    constexpr int RPW = 64 / LPR;
-    const int lane = threadIdx.x & 63, sub = lane % LPR;
-    const int64_t row = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * RPW + lane / LPR;
-    if (row >= n_rows) return;
-    const unsigned char* in = lazy_row(x, ov, idx, row, n0, cap, n_out_per, row_bytes);
-    unsigned char* o = x_out + row * (int64_t)row_bytes;
-    const int off = sub * 16;
-    if (off < row_bytes) *reinterpret_cast<lazy_u32x4*>(o + off) = *reinterpret_cast<const lazy_u32x4*>(in + off);
+    const int64_t i = (int64_t)blk * 256 + threadIdx.x;
+    if (i >= a.n_tok) return;
+    const int64_t b = i / a.n0;
+    int t = (int)(i - b * a.n0);
+    if (!a.idx) {
+        a.sizes_out[i] = a.sizes_in ? a.sizes_in[i] : 1;
+        if (a.kept_map) a.kept_map[i] = t;
+    }
+    if (!a.merged_map) return;
+    for (int k = 0; k < a.maps.n; ++k) t = a.maps.map[k][b * a.maps.n_in[k] + t];
+    a.merged_map[i] = t;
 }
 
 // ------------------------------------------------------------------ host side
@@ -614,24 +623,27 @@ luvc_status oim_wide_lazy_pass(const void* x, void* ov, const void* metric, void
                                  idx_out, sizes_out, kept_out, pass_map, st);
 }
 
-luvc_status oim_wide_lazy_gather(const void* x, const void* ov, const int32_t* idx, int B, int n0, int cap, int n_out_per, int D,
-                                 luvc_dtype dt, void* x_out, hipStream_t st)
+luvc_status oim_lazy_finish(const LazyOutput* outs, int n_outs, const int32_t* idx, int B, int n0, int cap, int n_out_per, const PassMaps& maps,
+                            int32_t* merged_map, const int32_t* sizes_in, int32_t* sizes_out, int32_t* kept_map, hipStream_t st)
 {
-    const int64_t rows = (int64_t)B * n_out_per;
-    const int row_bytes = D * (dt == LUVC_F32 ? 4 : 2);
-    if (row_bytes <= 512) {
-        const int rpw = row_bytes <= 256 ? 4 : 2;
-        const unsigned grid = (unsigned)(((rows + rpw - 1) / rpw * 64 + 255) / 256);
-        if (rpw == 4) LUVC_LAUNCH("oim_wide_gather", (oim_wide_gather_short<16>), dim3(grid), dim3(256), 0, st, (const unsigned char*)x, (const unsigned char*)ov, idx,
-                                  n0, cap, n_out_per, row_bytes, rows, (unsigned char*)x_out);
-        else          LUVC_LAUNCH("oim_wide_gather", (oim_wide_gather_short<32>), dim3(grid), dim3(256), 0, st, (const unsigned char*)x, (const unsigned char*)ov, idx,
-                                  n0, cap, n_out_per, row_bytes, rows, (unsigned char*)x_out);
-        return check_launch("oim wide matching, output rows");
+    FinishArgs a{};
+    a.idx = idx; a.n0 = n0; a.cap = cap; a.n_out_per = n_out_per;
+    a.n_rows = (int64_t)B * n_out_per;
+    a.n_tok = (int64_t)B * n0;
+    a.maps = maps;
+    a.merged_map = merged_map; a.sizes_in = sizes_in; a.sizes_out = sizes_out; a.kept_map = kept_map;
+    unsigned grid = (merged_map || !idx) ? (unsigned)((a.n_tok + 255) / 256) : 0u;
+    for (int q = 0; q < n_outs; ++q) {
+        FinishPart& f = a.part[q];
+        f.x = (const unsigned char*)outs[q].x; f.ov = (const unsigned char*)outs[q].ov; f.out = (unsigned char*)outs[q].out;
+        f.row_bytes = outs[q].row_bytes;
+        f.lanes = f.row_bytes <= 256 ? 16 : f.row_bytes <= 512 ? 32 : 64;
+        const int64_t per_block = 4 * (64 / f.lanes);
+        f.blocks = (unsigned)((a.n_rows + per_block - 1) / per_block);
+        grid += f.blocks;
     }
-    const unsigned grid = (unsigned)((rows * 64 + 255) / 256);
-    LUVC_LAUNCH("oim_wide_gather", oim_wide_gather, dim3(grid), dim3(256), 0, st, (const unsigned char*)x, (const unsigned char*)ov, idx,
-                n0, cap, n_out_per, row_bytes, rows, (unsigned char*)x_out);
-    return check_launch("oim wide matching, output rows");
+    LUVC_LAUNCH("oim_lazy_finish", oim_lazy_finish_k, dim3(grid), dim3(256), 0, st, a);
+    return check_launch("oim output rows and maps");
 }
 
 }  // namespace luvc
