@@ -221,7 +221,7 @@ def run_config(cfg, args, lv, wl, torch, np):
     work = {
         "oim_halve_pair": (oim_bytes, None, "hbm"), "oim_halve": (oim_bytes, None, "hbm"),
         "spu_fft16q": (score_bytes, fft_flops, "alu"),
-        "spu_fwd_dense": (score_bytes, None, "hbm"), "spu_dense_fused": (score_bytes, None, "hbm"),
+        "spu_fwd_dense": (score_bytes, None, "hbm"), "spu_circ": (score_bytes, None, "hbm"),
         "spu_gather": (prune_bytes, None, "hbm"), "spu_prune_fused": (prune_bytes, None, "hbm"),
     }
     try:

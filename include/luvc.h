@@ -294,7 +294,7 @@ luvc_status luvc_oim_plan_anyres(int H, int W, int64_t max_tokens,
  *   x_out, sizes_out   device, packed by the output grids H'[i] x W'[i] the schedules end at
  *   merged_map  device, packed like x: input flat index -> output slot WITHIN the image, or NULL
  *   kept_map    device, packed like x_out: output slot -> input flat index WITHIN the image, or NULL
- *   workspace   luvc_oim_ragged_workspace_bytes for the same arguments (the largest need of any run)
+ *   workspace   luvc_oim_ragged_workspace_bytes for the same arguments (at least the largest need of any run)
  * Limits: those of luvc_oim_merge per run; fewer than 2^31 tokens in the batch.
  */
 size_t luvc_oim_ragged_workspace_bytes(int n_images, const int32_t* H, const int32_t* W, int D, luvc_dtype dtype,

@@ -368,11 +368,12 @@ static luvc_status oim_merge_impl(const void* x, const int32_t* sizes_in, int B,
         if (radius != 1)
             rc = oim_wide_pass(cur_x, cur_s, B, pl.h[i], pl.w[i], D, dtype, passes[i].axis, passes[i].m, radius, vec,
                                ox, os, pm, cur_k, ok, sc, (double*)(ws + L.gram), (int32_t*)(ws + L.srcdest), st);
-        else if (steps[s].count == 2)
-            rc = oim_pair_pass(cur_x, cur_s, B, pl.h[i], pl.w[i], D, dtype, passes[i].axis, ox, os, pm, cur_k, ok, st);
-        else if (oim_halve_supported(pl.h[i], pl.w[i], D, dtype, passes[i].axis, passes[i].m, vec))
-            rc = oim_halve_pass(cur_x, cur_s, B, pl.h[i], pl.w[i], D, dtype, passes[i].axis, ox, os, pm, cur_k, ok, st);
-        else
+        else if (steps[s].count == 2 || oim_halve_supported(pl.h[i], pl.w[i], D, dtype, passes[i].axis, passes[i].m, vec)) {
+            const OimStepItem item = {pl.h[i], pl.w[i], passes[i].axis, B, StepAt{0, 0, 0, pl.h[i] * pl.w[i], 0, 0, 0}};
+            const StepIn in = {cur_x, cur_s, cur_k};
+            const StepOut out = {{ox, nullptr}, {os, nullptr}, {ok, nullptr}, {pm, nullptr}};
+            rc = steps[s].count == 2 ? oim_pair_step(&item, 1, in, out, D, dtype, st) : oim_halve_step(&item, 1, in, out, D, dtype, st);
+        } else
             rc = oim_general_pass(cur_x, cur_s, B, pl.h[i], pl.w[i], D, dtype, passes[i].axis, passes[i].m, vec,
                                   ox, os, pm, cur_k, ok, sc, st);
         if (rc != LUVC_OK) return rc;
@@ -563,7 +564,7 @@ luvc_status luvc_value_enhance(const void* v, const int32_t* sizes, int64_t rows
 size_t luvc_spu_workspace_bytes(int B, int N, int D, luvc_dtype dtype, int sigma)
 {
     if (!dtype_ok(dtype) || B < 1 || N < 1 || D < 1 || sigma < 0 || sigma > N / 2 || N > kSpuMaxN) return 0;
-    return spu_layout(B, N, D, sigma).bytes;
+    return spu_workspace(B, N, D, sigma, dtype);
 }
 
 luvc_status luvc_spu_score(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dtype, int sigma,
@@ -576,7 +577,7 @@ luvc_status luvc_spu_score(const void* x, int B, int N, int D, int64_t row_strid
     if (sigma < 0 || sigma > N / 2) { set_error("sigma=%d must lie in 0..N/2=%d", sigma, N / 2); return LUVC_ERR_INVALID_ARG; }
     if (N > kSpuMaxN) { set_error("N=%d exceeds the supported %d tokens per sample", N, kSpuMaxN); return LUVC_ERR_UNSUPPORTED; }
     if (B > 65535) { set_error("B=%d exceeds 65535 samples per call", B); return LUVC_ERR_UNSUPPORTED; }
-    const size_t need = spu_layout(B, N, D, sigma).bytes;
+    const size_t need = spu_workspace(B, N, D, sigma, dtype);
     if (!workspace_ok(workspace, workspace_bytes, need)) return LUVC_ERR_WORKSPACE;
     return spu_score_dense(x, B, N, D, row_stride, dtype, sigma, use_hamming ? 1 : 0, scores, workspace, (hipStream_t)hip_stream);
 }
@@ -602,7 +603,10 @@ luvc_status luvc_spu_prune(const void* x, const float* scores, int B, int N, int
     if (row_stride < D) { set_error("row_stride %lld is smaller than D=%d", (long long)row_stride, D); return LUVC_ERR_INVALID_ARG; }
     if (n_keep < 1 || n_keep > N) { set_error("n_keep=%d must lie in 1..N=%d", n_keep, N); return LUVC_ERR_INVALID_ARG; }
     if ((int64_t)B * N >= ((int64_t)1 << 31)) { set_error("B*N must stay below 2^31"); return LUVC_ERR_UNSUPPORTED; }
-    return spu_prune_run(x, scores, B, N, D, row_stride, dtype, n_keep, kept_idx, x_out, nullptr, nullptr, (hipStream_t)hip_stream);
+    PruneRuns runs;
+    runs.n = 1;
+    runs.run[0] = PruneRun{0, N, n_keep, B, 0, 0};
+    return spu_prune_run(x, scores, D, row_stride, dtype, runs, kept_idx, x_out, nullptr, nullptr, (hipStream_t)hip_stream);
 }
 
 int luvc_spu_cascade_keeps(int N0, double keep_ratio, int n_stages, int eliminate, int* keeps)
@@ -629,7 +633,10 @@ luvc_status luvc_spu_stage(const void* x, int B, int N, int D, int64_t row_strid
     const luvc_status rc = luvc_spu_score(x, B, N, D, row_stride, dtype, sigma, use_hamming, scores, workspace, workspace_bytes, hip_stream);
     if (rc != LUVC_OK) return rc;
     if ((int64_t)B * N >= ((int64_t)1 << 31)) { set_error("B*N must stay below 2^31"); return LUVC_ERR_UNSUPPORTED; }
-    return spu_prune_run(x, scores, B, N, D, row_stride, dtype, n_keep, kept_idx, x_out, origin_in, origin_out, (hipStream_t)hip_stream);
+    PruneRuns runs;
+    runs.n = 1;
+    runs.run[0] = PruneRun{0, N, n_keep, B, 0, 0};
+    return spu_prune_run(x, scores, D, row_stride, dtype, runs, kept_idx, x_out, origin_in, origin_out, (hipStream_t)hip_stream);
 }
 
 }  // extern "C"

@@ -76,18 +76,34 @@ luvc_status oim_wide_apply(const void* x, const int32_t* sizes_in, int B, int H,
 luvc_status value_enhance_run(const void* v, const int32_t* sizes, int64_t rows, int D, int64_t v_stride, int64_t out_stride,
                               luvc_dtype dt, void* out, hipStream_t st);
 
-// Fused pass for m = ceil(len/2) (oim_fast.hip); `vec` = rows are 16-byte aligned.
-bool oim_halve_supported(int H, int W, int D, luvc_dtype dt, int axis, int m, bool vec);
-luvc_status oim_halve_pass(const void* x, const int32_t* sizes_in, int B, int H, int W, int D, luvc_dtype dt, int axis,
-                           void* x_out, int32_t* sizes_out, int32_t* pass_map, const int32_t* kept_prev, int32_t* kept_out,
-                           hipStream_t st);
+// ---- Halving steps of one or several runs of equal images in one launch.  An item is a run: `count` images of H x W; axis is
+// that of the (first) pass.  Where its images lie: token offsets into the step's input and output, an offset and a stride per
+// image for its map; dst / map_dst choose one of two sets of outputs (a step that ends some images of a batch and not others).
+constexpr int kOimMaxItems = 24;
+struct StepAt {
+    int64_t in_off, out_off, map_off;
+    int map_stride;
+    unsigned wg0;                    // first workgroup (filled in by the launcher)
+    int dst, map_dst;
+};
+struct OimStepItem { int H, W, axis, count; StepAt at; };
+struct StepIn { const void* x; const int32_t *sizes, *kept; };               // sizes NULL: ones; kept NULL: identity
+struct StepOut { void* x[2]; int32_t *sizes[2], *kept[2], *map[2]; };        // kept, map: NULL = not wanted
 
-// One launch for two consecutive halving passes on different axes (oim_pair.hip); pair_map sends an
-// input flat index of the first pass to an output slot of the second.
+// One pass with m = ceil(len/2) (oim_fast.hip); `vec` = rows are 16-byte aligned.
+bool oim_halve_supported(int H, int W, int D, luvc_dtype dt, int axis, int m, bool vec);
+luvc_status oim_halve_step(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st);
+
+// Two consecutive halving passes on different axes (oim_pair.hip); the map sends an input flat index of the first pass
+// to an output slot of the second.
 bool oim_pair_supported(int H, int W, int D, luvc_dtype dt, int axis0, int m0, int axis1, int m1, bool vec);
-luvc_status oim_pair_pass(const void* x, const int32_t* sizes_in, int B, int H, int W, int D, luvc_dtype dt, int first_axis,
-                          void* x_out, int32_t* sizes_out, int32_t* pair_map, const int32_t* kept_prev, int32_t* kept_out,
-                          hipStream_t st);
+luvc_status oim_pair_step(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st);
+
+// What a batch of runs leaves to the end (ragged.hip): images no pass touches are copied, the maps of images with several
+// steps composed (step s of a batch writes its maps at maps + s * map_level, an image its n0 entries at map_off + image * n0).
+struct OimTailItem { int copy, n0, steps; unsigned blk0; int64_t tokens, tok_in, tok_out, map_off; };
+luvc_status oim_batch_tail(const OimTailItem* items, int n, const void* x, const int32_t* sizes, int row_bytes, void* x_out, int32_t* sizes_out,
+                           int32_t* merged_map, int32_t* kept_map, const int32_t* maps, int64_t map_level, hipStream_t st);
 
 // The same pair of passes decided on a metric tensor of Dm values per token (oim_pair_keyed.hip): features and
 // metric are merged alike; metric_out may be NULL when the merged metric is not wanted.

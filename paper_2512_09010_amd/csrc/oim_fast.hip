@@ -18,21 +18,18 @@
 // repeats the sweep in fp64 and the fp64 cosines decide.  The verdict "closer than tau" is a
 // function of the screening values of that source alone, which are the same bits in every
 // wavefront and workgroup that looks at it, so neighbours always agree on a shared source.
-#include <cstdlib>
-
 #include "common.hpp"
 #include "oim.hpp"
 #include "oim_tok.hpp"
 
 namespace luvc {
 
+struct HalveItem { int H, W, axis, tiles, slots; StepAt at; };      // a line is cut into `tiles` runs of `slots` output slots
+struct HalveTable { int n; HalveItem it[kOimMaxItems]; };
 
 template <typename T, int NCH>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NCH <= 3 ? 4 : 2)))
-oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, int H, int W, int D, int axis,
-          int tiles_per_line, int slots_per_tile,
-          const int32_t* __restrict__ kept_prev, T* __restrict__ x_out, int32_t* __restrict__ sizes_out,
-          int32_t* __restrict__ pass_map, int32_t* __restrict__ kept_out)
+oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, int D, const StepOut out, const HalveTable tab)
 {
     using tr = io_traits<T>;
     constexpr int V = tr::kVec;
@@ -44,10 +41,20 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, int H, 
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);         // tiles of a line stay on one XCD
+    HalveItem it = tab.it[0];                                      // fetched beside the count: one item is the common case
+    if (tab.n > 1) {
+        int ent = 0;
+        for (int i = 1; i < tab.n; ++i)
+            if (item >= tab.it[i].at.wg0) ent = i;
+        it = tab.it[ent];
+    }
+    const StepAt& at = it.at;
+    const int H = it.H, W = it.W, axis = it.axis, tiles_per_line = it.tiles, slots_per_tile = it.slots;
+    item -= at.wg0;
     const int len = axis ? W : H, nlines = axis ? H : W;
     const int nd = len >> 1;                      // destinations = output slots per line
     const int Wo = axis ? nd : W;
-    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);   // tiles of a line stay on one XCD
     const int tile = item % tiles_per_line;
     const int line = (item / tiles_per_line) % nlines;
     const int b = item / (tiles_per_line * nlines);
@@ -56,7 +63,7 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, int H, 
     const int j = j0 + w;
     const bool live = w < nslot;
     const int64_t step = axis ? 1 : W;                     // tokens between neighbours on the line
-    const int64_t img = (int64_t)b * H * W;
+    const int64_t img = at.in_off + (int64_t)b * H * W;
     const int64_t line0 = img + (axis ? (int64_t)line * W : line);    // token index of position 0
     auto tok_ptr = [&](int pos) { return x + (line0 + pos * step) * D; };
 
@@ -182,7 +189,9 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, int H, 
     const int S = sb + sa + scz;
     const int64_t n_out_per = (int64_t)(axis ? H : nd) * Wo;
     const int out_in_img = axis ? line * Wo + j : j * Wo + line;
-    const int64_t slot = b * n_out_per + out_in_img;
+    const int64_t slot = at.out_off + b * n_out_per + out_in_img;
+    T* x_out = (T*)out.x[at.dst];
+    int32_t *sizes_out = out.sizes[at.dst], *kept_out = out.kept[at.dst];
     if (lane == 0) {
         sizes_out[slot] = S;
         const int p_in = (int)(tb - img);
@@ -190,9 +199,13 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, int H, 
         // a lands here or in the previous slot of the line; the last source of an odd line has no
         // slot of its own and always folds into the last destination
         const int prev_slot = axis ? out_in_img - 1 : out_in_img - Wo;
-        pass_map[tb] = out_in_img;
-        pass_map[ta] = take_a ? out_in_img : prev_slot;
-        if (has_c && pc + 1 >= len) pass_map[tc] = out_in_img;
+        int32_t* pass_map = out.map[at.map_dst];
+        if (pass_map) {
+            pass_map += at.map_off + (int64_t)b * at.map_stride - img;
+            pass_map[tb] = out_in_img;
+            pass_map[ta] = take_a ? out_in_img : prev_slot;
+            if (has_c && pc + 1 >= len) pass_map[tc] = out_in_img;
+        }
     }
     T* o = x_out + slot * D;
     if (!take_a && !take_c) {                     // nothing absorbed: bit copy
@@ -225,26 +238,34 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, int H, 
 }
 
 template <typename T, int NCH>
-static void launch_halve(const T* x, const int32_t* sizes_in, int B, int H, int W, int D, int axis,
-                         const int32_t* kept_prev, T* x_out, int32_t* sizes_out, int32_t* pass_map, int32_t* kept_out,
-                         hipStream_t st)
+static void launch_halve(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
 {
-    const int len = axis ? W : H, nlines = axis ? H : W, nd = len / 2;
-    constexpr int cap = 4;
-    const int spt = nd < cap ? nd : cap;                   // wavefronts (= output slots) per workgroup
-    const int tiles = (nd + spt - 1) / spt;
-    LUVC_LAUNCH("oim_halve", (oim_halve<T, NCH>), dim3((unsigned)((int64_t)B * nlines * tiles)), dim3(64 * spt), 0, st,
-                       x, sizes_in, H, W, D, axis, tiles, spt, kept_prev, x_out, sizes_out, pass_map, kept_out);
+    constexpr int cap = 4;                                 // wavefronts (= output slots) per workgroup
+    HalveTable tab;
+    tab.n = n;
+    int64_t wgs = 0;
+    int waves = 1;
+    for (int i = 0; i < n; ++i) {
+        const int H = items[i].H, W = items[i].W, axis = items[i].axis, nd = (axis ? W : H) / 2;
+        tab.it[i].H = H;
+        tab.it[i].W = W;
+        tab.it[i].axis = axis;
+        tab.it[i].slots = nd < cap ? nd : cap;
+        tab.it[i].tiles = (nd + tab.it[i].slots - 1) / tab.it[i].slots;
+        waves = tab.it[i].slots > waves ? tab.it[i].slots : waves;
+        tab.it[i].at = items[i].at;
+        tab.it[i].at.wg0 = (unsigned)wgs;
+        wgs += (int64_t)items[i].count * (axis ? H : W) * tab.it[i].tiles;
+    }
+    LUVC_LAUNCH("oim_halve", (oim_halve<T, NCH>), dim3((unsigned)wgs), dim3(64 * waves), 0, st, (const T*)in.x, in.sizes, in.kept, D, out, tab);
 }
 
 template <typename T>
-static bool dispatch_halve(const T* x, const int32_t* sizes_in, int B, int H, int W, int D, int axis,
-                           const int32_t* kept_prev, T* x_out, int32_t* sizes_out, int32_t* pass_map, int32_t* kept_out,
-                           hipStream_t st)
+static bool dispatch_halve(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
 {
     const int per_wave = 64 * io_traits<T>::kVec;
     const int nch = (D + per_wave - 1) / per_wave;
-#define LUVC_HALVE(N) launch_halve<T, N>(x, sizes_in, B, H, W, D, axis, kept_prev, x_out, sizes_out, pass_map, kept_out, st); return true
+#define LUVC_HALVE(N) launch_halve<T, N>(items, n, in, out, D, st); return true
     switch (nch) {
         case 1: LUVC_HALVE(1);
         case 2: LUVC_HALVE(2);
@@ -266,17 +287,64 @@ bool oim_halve_supported(int H, int W, int D, luvc_dtype dt, int axis, int m, bo
     return vec && len >= 2 && m == (len + 1) / 2 && (D + per_wave - 1) / per_wave <= 8;
 }
 
-luvc_status oim_halve_pass(const void* x, const int32_t* sizes_in, int B, int H, int W, int D, luvc_dtype dt, int axis,
-                           void* x_out, int32_t* sizes_out, int32_t* pass_map, const int32_t* kept_prev, int32_t* kept_out,
-                           hipStream_t st)
+luvc_status oim_halve_step(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st)
 {
-    bool ok;
-    if (dt == LUVC_F32)
-        ok = dispatch_halve<float>((const float*)x, sizes_in, B, H, W, D, axis, kept_prev, (float*)x_out, sizes_out, pass_map, kept_out, st);
-    else
-        ok = dispatch_halve<bf16_t>((const bf16_t*)x, sizes_in, B, H, W, D, axis, kept_prev, (bf16_t*)x_out, sizes_out, pass_map, kept_out, st);
-    if (!ok) { set_error("oim_halve_pass: unsupported D"); return LUVC_ERR_UNSUPPORTED; }
+    const bool ok = dt == LUVC_F32 ? dispatch_halve<float>(items, n, in, out, D, st) : dispatch_halve<bf16_t>(items, n, in, out, D, st);
+    if (!ok) { set_error("oim halving pass: unsupported D"); return LUVC_ERR_UNSUPPORTED; }
     return check_launch("oim halving pass");
+}
+
+// ------------------------------------------------------------------ end of a batch of runs
+struct TailTable { int n; OimTailItem it[kOimMaxItems]; };
+
+// a copied image: one wavefront per token; composed maps: one thread per token
+__global__ void __launch_bounds__(256)
+oim_batch_tail_k(const unsigned char* __restrict__ x, const int32_t* __restrict__ sizes, int row_bytes, unsigned char* __restrict__ x_out,
+                 int32_t* __restrict__ sizes_out, int32_t* __restrict__ merged_map, int32_t* __restrict__ kept_map,
+                 const int32_t* __restrict__ maps, int64_t map_level, const TailTable tab)
+{
+    int ent = 0;
+    for (int i = 1; i < tab.n; ++i)
+        if (blockIdx.x >= tab.it[i].blk0) ent = i;
+    const OimTailItem& a = tab.it[ent];
+    const int64_t blk = blockIdx.x - a.blk0;
+    if (a.copy) {
+        const int lane = threadIdx.x & 63;
+        const int64_t t = blk * 4 + (threadIdx.x >> 6);
+        if (t >= a.tokens) return;
+        const unsigned char* in = x + (a.tok_in + t) * (int64_t)row_bytes;
+        unsigned char* o = x_out + (a.tok_out + t) * (int64_t)row_bytes;
+        for (int d = lane * 16; d < row_bytes; d += 64 * 16) *reinterpret_cast<u32x4*>(o + d) = *reinterpret_cast<const u32x4*>(in + d);
+        if (lane == 0) {
+            const int at = (int)(t % a.n0);
+            sizes_out[a.tok_out + t] = sizes ? sizes[a.tok_in + t] : 1;
+            if (kept_map) kept_map[a.tok_out + t] = at;
+            if (merged_map) merged_map[a.tok_in + t] = at;
+        }
+        return;
+    }
+    const int64_t i = blk * 256 + threadIdx.x;
+    if (i >= a.tokens) return;
+    const int64_t img = i / a.n0 * a.n0;
+    int t = (int)(i - img);
+    for (int k = 0; k < a.steps; ++k) t = maps[k * map_level + a.map_off + img + t];
+    merged_map[a.tok_in + i] = t;
+}
+
+luvc_status oim_batch_tail(const OimTailItem* items, int n, const void* x, const int32_t* sizes, int row_bytes, void* x_out, int32_t* sizes_out,
+                           int32_t* merged_map, int32_t* kept_map, const int32_t* maps, int64_t map_level, hipStream_t st)
+{
+    TailTable tab;
+    tab.n = n;
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        tab.it[i] = items[i];
+        tab.it[i].blk0 = (unsigned)blocks;
+        blocks += items[i].copy ? (items[i].tokens + 3) / 4 : (items[i].tokens + 255) / 256;
+    }
+    LUVC_LAUNCH("oim_batch_tail", oim_batch_tail_k, dim3((unsigned)blocks), dim3(256), 0, st, (const unsigned char*)x, sizes, row_bytes, (unsigned char*)x_out,
+                sizes_out, merged_map, kept_map, maps, map_level, tab);
+    return check_launch("oim batch");
 }
 
 }  // namespace luvc

@@ -30,11 +30,14 @@
 // result: either the sum is exact in fp32 (exponents at most 15 apart), or the smaller term is below
 // 2^-15 of the larger, whose half lies on the bf16 grid at least 2^-10 (relative) away from every
 // rounding boundary - too far for the smaller term or the fp32 rounding to matter.
-#include <cstdlib>
-
 #include "oim_pair_tok.hpp"
 
 namespace luvc {
+
+struct PairTable {
+    int n;
+    struct { PairGeom g; StepAt at; } it[kOimMaxItems];
+};
 
 // Tokens of at most 8 words per lane (1 KB in bf16) are compiled for six wavefronts per SIMD (80 registers, a few spilled
 // in the fp64 repeat): on batches of small grids a workgroup is 6 wavefronts, and four workgroups per compute unit instead
@@ -42,9 +45,7 @@ namespace luvc {
 // hint on wider tokens (96 instead of 103 registers) measured slower on every workload and is not given.
 template <typename T, int NQ, int TW, int NW>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((4 * NQ + TW <= 8 && NW == 16) ? 6 : 1)))
-oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, PairGeom g,
-               const int32_t* __restrict__ kept_prev, T* __restrict__ x_out, int32_t* __restrict__ sizes_out,
-               int32_t* __restrict__ pair_map, int32_t* __restrict__ kept_out)
+oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, const StepOut out, const PairTable tab)
 {
     using TokT = Tok<NQ, TW>;
     constexpr int N = TokT::N;
@@ -58,7 +59,17 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, Pa
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
+    unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
+    PairGeom g = tab.it[0].g;                                     // fetched beside the count: one item is the common case
+    StepAt at = tab.it[0].at;
+    if (tab.n > 1) {
+        int ent = 0;
+        for (int i = 1; i < tab.n; ++i)
+            if (item >= tab.it[i].at.wg0) ent = i;
+        g = tab.it[ent].g;
+        at = tab.it[ent].at;
+    }
+    item -= at.wg0;
     const int j = item % g.nd1;
     const int seg = (item / g.nd1) % g.segs;
     const int b = item / (g.nd1 * g.segs);
@@ -89,7 +100,7 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, Pa
     // ------------------------------------------------------------------ first pass: four intermediate tokens
     const int pa = 2 * j, pb = pa + 1, pc = pa + 2;
     const bool has_l = j > 0, has_c = pc < g.L1, has_r = pc + 1 < g.L1;
-    const int64_t img_in = (int64_t)b * g.n_in;
+    const int64_t img_in = at.in_off + (int64_t)b * g.n_in;
     TokT T0, T1, T2, T3;
     zero_tok(T0); zero_tok(T1); zero_tok(T2); zero_tok(T3);
     int s0 = 0, s1 = 0, s2 = 0, s3 = 0;
@@ -222,7 +233,9 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, Pa
     // ------------------------------------------------------------------ second pass: merge, write, maps
     const int own_end = row_base + 2 * nseg;                      // rows below it belong to the next run ...
     const bool tail = (g.L2 & 1) && own_end == g.L2 - 1;          // ... except the last source of an odd line
-    const int64_t img_out = (int64_t)b * g.n_out;
+    const int64_t img_out = at.out_off + (int64_t)b * g.n_out;
+    T* x_out = (T*)out.x[at.dst];
+    int32_t *sizes_out = out.sizes[at.dst], *kept_out = out.kept[at.dst], *pair_map = out.map[at.map_dst];
     const int uo = r0 >> 1;                                       // output slot (second axis) of destination r0 + 1
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
@@ -261,7 +274,7 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, Pa
             if (r & 1) u = r >> 1;
             else u = (k == 0 ? up0 : up2) ? (r >> 1) - 1 : (r >> 1);
             const int slot = u * g.oB + j * g.oA;
-            const int64_t t0 = img_in + (int64_t)r * g.sB;
+            const int64_t t0 = at.map_off + (int64_t)b * at.map_stride + (int64_t)r * g.sB;
             pair_map[t0 + (int64_t)pb * g.sA] = slot;
             if ((took_a >> k) & 1u) pair_map[t0 + (int64_t)pa * g.sA] = slot;
             if ((took_c >> k) & 1u) pair_map[t0 + (int64_t)pc * g.sA] = slot;
@@ -273,38 +286,45 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, Pa
 namespace {
 
 template <typename T, int NQ, int TW>
-luvc_status launch_pair(const T* x, const int32_t* sizes_in, int B, int H, int W, int D, int first_axis,
-                        const int32_t* kept_prev, T* x_out, int32_t* sizes_out, int32_t* pair_map, int32_t* kept_out,
-                        hipStream_t st)
+luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
 {
     constexpr int N = 4 * NQ + TW;
     constexpr int NW = N <= 10 ? 16 : 8;           // 16 wavefronts leave 128 registers per lane, 8 leave 256
-    PairGeom g;
-    g.L1 = first_axis ? W : H;
-    g.L2 = first_axis ? H : W;
-    g.nd1 = g.L1 / 2;
-    g.nd2 = g.L2 / 2;
-    g.sA = first_axis ? 1 : W;
-    g.sB = first_axis ? W : 1;
-    const int Wo = W / 2;
-    g.oA = first_axis ? 1 : Wo;
-    g.oB = first_axis ? Wo : 1;
-    g.n_in = H * W;
-    g.n_out = (H / 2) * Wo;
-    g.D = D;
-    const PairPlan p = plan_pair(g.L2, NW, (int64_t)B * g.nd1);
-    g.segs = p.segs;
-    g.seg_out = p.seg_out;
-    const size_t lds = (size_t)p.waves * N * 64 * 4;           // at most 16 * 10 * 256 = 40 KiB
-    LUVC_LAUNCH("oim_halve_pair", (oim_halve_pair<T, NQ, TW, NW>), dim3((unsigned)((int64_t)B * g.segs * g.nd1)), dim3(64 * p.waves), lds, st,
-                       x, sizes_in, g, kept_prev, x_out, sizes_out, pair_map, kept_out);
+    PairTable tab;
+    tab.n = n;
+    int64_t lines = 0, wgs = 0;
+    int waves = 1;
+    for (int i = 0; i < n; ++i) lines += (int64_t)items[i].count * ((items[i].axis ? items[i].W : items[i].H) / 2);
+    for (int i = 0; i < n; ++i) {
+        const int H = items[i].H, W = items[i].W, axis = items[i].axis, Wo = W / 2;
+        PairGeom& g = tab.it[i].g;
+        g.L1 = axis ? W : H;
+        g.L2 = axis ? H : W;
+        g.nd1 = g.L1 / 2;
+        g.nd2 = g.L2 / 2;
+        g.sA = axis ? 1 : W;
+        g.sB = axis ? W : 1;
+        g.oA = axis ? 1 : Wo;
+        g.oB = axis ? Wo : 1;
+        g.n_in = H * W;
+        g.n_out = (H / 2) * Wo;
+        g.D = D;
+        const PairPlan p = plan_pair(g.L2, NW, lines);
+        g.segs = p.segs;
+        g.seg_out = p.seg_out;
+        waves = p.waves > waves ? p.waves : waves;     // a workgroup with fewer rows leaves the rest idle
+        tab.it[i].at = items[i].at;
+        tab.it[i].at.wg0 = (unsigned)wgs;
+        wgs += (int64_t)items[i].count * g.segs * g.nd1;
+    }
+    const size_t lds = (size_t)waves * N * 64 * 4;             // at most 16 * 10 * 256 = 40 KiB
+    LUVC_LAUNCH("oim_halve_pair", (oim_halve_pair<T, NQ, TW, NW>), dim3((unsigned)wgs), dim3(64 * waves), lds, st,
+                (const T*)in.x, in.sizes, in.kept, out, tab);
     return check_launch("oim halving pair");
 }
 
 template <typename T>
-luvc_status dispatch_pair(const T* x, const int32_t* sizes_in, int B, int H, int W, int D, int first_axis,
-                          const int32_t* kept_prev, T* x_out, int32_t* sizes_out, int32_t* pair_map, int32_t* kept_out,
-                          hipStream_t st)
+luvc_status dispatch_pair(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
 {
     // 16-byte pieces per lane, then a 4- or 8-byte tail piece if that covers what is left
     const int bytes = D * (int)sizeof(T);
@@ -313,7 +333,7 @@ luvc_status dispatch_pair(const T* x, const int32_t* sizes_in, int B, int H, int
     if (rem > 512) ++nq;
     else if (rem > 256) tw = 2;
     else if (rem > 0) tw = 1;
-#define LUVC_PAIR(Q, W_) if (nq == Q && tw == W_) return launch_pair<T, Q, W_>(x, sizes_in, B, H, W, D, first_axis, kept_prev, x_out, sizes_out, pair_map, kept_out, st)
+#define LUVC_PAIR(Q, W_) if (nq == Q && tw == W_) return launch_pair<T, Q, W_>(items, n, in, out, D, st)
     LUVC_PAIR(0, 1); LUVC_PAIR(0, 2);
     LUVC_PAIR(1, 0); LUVC_PAIR(1, 1); LUVC_PAIR(1, 2);
     LUVC_PAIR(2, 0); LUVC_PAIR(2, 1); LUVC_PAIR(2, 2);
@@ -334,15 +354,9 @@ bool oim_pair_supported(int H, int W, int D, luvc_dtype dt, int axis0, int m0, i
     return (int64_t)D * (dt == LUVC_F32 ? 4 : 2) <= 4096;
 }
 
-luvc_status oim_pair_pass(const void* x, const int32_t* sizes_in, int B, int H, int W, int D, luvc_dtype dt, int first_axis,
-                          void* x_out, int32_t* sizes_out, int32_t* pair_map, const int32_t* kept_prev, int32_t* kept_out,
-                          hipStream_t st)
+luvc_status oim_pair_step(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st)
 {
-    if (dt == LUVC_F32)
-        return dispatch_pair<float>((const float*)x, sizes_in, B, H, W, D, first_axis, kept_prev, (float*)x_out, sizes_out,
-                                    pair_map, kept_out, st);
-    return dispatch_pair<bf16_t>((const bf16_t*)x, sizes_in, B, H, W, D, first_axis, kept_prev, (bf16_t*)x_out, sizes_out,
-                                 pair_map, kept_out, st);
+    return dt == LUVC_F32 ? dispatch_pair<float>(items, n, in, out, D, st) : dispatch_pair<bf16_t>(items, n, in, out, D, st);
 }
 
 }  // namespace luvc

@@ -6,10 +6,10 @@ namespace luvc {
 
 constexpr int kSpuMaxN = 32768;     // tokens per sample (twiddle index arithmetic stays in int32)
 
-// Which kernels serve a score call (chosen from N and sigma alone)
+// Which kernels serve a score call (chosen from the sizes and the alignment of the rows)
 enum class SpuPath {
+    Circ,       // spu_circ: the filter as a circulant matrix on the matrix cores, short samples
     Fft,        // spu_fft16q: transform decomposition, N = 16 Q N2
-    DenseFused, // spu_dense_fused: direct pass-band DFT in one launch, small N and sigma
     Conv,       // spu_conv: M-point transforms in one workgroup, any N up to 8192
     Dense       // direct pass-band DFT through the workspace, any N
 };
@@ -20,7 +20,9 @@ struct SpuLayout {
     int n_tiles;
     SpuPath path;
 };
-SpuLayout spu_layout(int B, int N, int D, int sigma);
+SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, bool circ);
+size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt);
+bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt);
 
 luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma,
                             int use_hamming, float* scores, void* workspace, hipStream_t st);
@@ -31,6 +33,17 @@ struct TileSync;
 luvc_status spu_score_fft(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
                           float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st);
 
+// Short samples on the matrix cores (spu_circ.hip), runs of equal samples in one launch
+constexpr int kCircMaxN = 1024, kCircMaxRuns = 64;
+struct CircRun {
+    int group0, N, sigma, count;     // first group of output tokens (filled in by the launcher)
+    int64_t tok0;                    // first token of the first sample
+};
+struct CircRuns { int n; CircRun run[kCircMaxRuns]; };
+bool spu_circ_aligned(const void* x, int D, int64_t row_stride, luvc_dtype dt);
+size_t spu_circ_bytes(int64_t samples, int N, int D);
+luvc_status spu_score_circ(const void* x, int64_t row_stride, int D, luvc_dtype dt, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st);
+
 // Any N (spu_conv.hip): N <= 8192, or N = 16384
 int spu_conv_rows(int N, bool* half);
 int spu_conv_tiles(int B, int N, int D);
@@ -39,7 +52,14 @@ inline int spu_conv_ld(int N) { return (N + 3) / 4 * 4; }
 luvc_status spu_score_conv(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
                            float* spec, float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st);
 
-luvc_status spu_prune_run(const void* x, const float* scores, int B, int N, int D, int64_t row_stride, luvc_dtype dt,
-                          int n_keep, int32_t* kept_idx, void* x_out, const int32_t* origin_in, int32_t* origin_out, hipStream_t st);
+// Runs of equal samples, packed one after the other, pruned together
+constexpr int kPruneMaxRuns = 64;
+struct PruneRun {
+    int wg0, N, n_keep, count;       // first workgroup (filled in by the launcher)
+    int64_t tok_in, tok_out;         // first token of the first sample, in and out
+};
+struct PruneRuns { int n; PruneRun run[kPruneMaxRuns]; };
+luvc_status spu_prune_run(const void* x, const float* scores, int D, int64_t row_stride, luvc_dtype dt, PruneRuns& runs,
+                          int32_t* kept_idx, void* x_out, const int32_t* origin_in, int32_t* origin_out, hipStream_t st);
 
 }  // namespace luvc

@@ -1,0 +1,344 @@
+// SPU score (paper Section 3.3, Eq. 4-8) for samples of up to kCircMaxN tokens: the filter as a circulant matrix on the
+// matrix cores.  x'[n, d] = sum_m p[n - m] x[m, d] with the kernel p of spu_taps.hpp, in fp32 accuracy: p is the sum of three
+// bf16 terms (24 bits), bf16 tokens enter as they are (the products are exact), fp32 tokens as three bf16 terms of their
+// own with the six products that matter (the rest is below 2^-24 of |x| |p|).
+//
+// A workgroup owns 32 RT output tokens and 256 channels of a sample, a wavefront 64 of them.  Per step of 16 tokens a lane
+// fetches 8 tokens of a pair of neighbouring channels, straight from memory (half a wavefront: one 128-byte row piece), and
+// two byte permutations per pair of tokens turn that into the operands of two 32-channel tiles (the even and the odd
+// channels; their order does not matter, the energies are summed over channels).  The channels are the rows of the
+// product, the output tokens its columns: squares are added in a lane's own registers.  The columns of p are shifts of one
+// another, so the other operand is read from LDS at a shift: a lane's 8 taps start anywhere, therefore the taps lie there
+// eight times, displaced by one to seven places, and every read is one aligned 16-byte access (copies 32 bytes apart
+// modulo 256: no two lanes of a phase meet in a bank).
+//
+// Samples of different lengths share a launch: the argument lists runs of equal samples, and workgroups find theirs.
+//
+// Hand-over between the workgroups of 32 RT tokens: each writes its sums as 64-bit words (value, launch tag), waits for its
+// stores, then reads the words of all of them.  Whoever finds every tag adds the sums in channel order in fp64, writes the
+// scores and clears the tags; the last to write always does, and if another does too it writes the same values.  One
+// trip to memory each way, no atomics; nothing has to be set up, and a captured launch replayed with its tag starts over.
+//
+// Bound: matrix cores for N near kCircMaxN (6 N^2 D flops per bf16 sample, 12 for fp32), latency for short samples.
+// {CIRC_MEASURED}
+#include "common.hpp"
+#include "spu.hpp"
+#include "spu_taps.hpp"
+#include "spu_tiles.hpp"
+
+namespace luvc {
+
+namespace {
+
+typedef __bf16 circ_bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 circ_bf16x2 __attribute__((ext_vector_type(2)));
+typedef float circ_f32x2 __attribute__((ext_vector_type(2)));
+typedef float circ_f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned int circ_u32x4 __attribute__((__vector_size__(16)));
+typedef unsigned int circ_u32x2 __attribute__((__vector_size__(8)));
+
+// two values rounded to bf16, packed (first one low)
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b)
+{
+    const circ_bf16x2 v = __builtin_convertvector(circ_f32x2{a, b}, circ_bf16x2);
+    uint32_t u;
+    __builtin_memcpy(&u, &v, 4);
+    return u;
+}
+
+__device__ __forceinline__ circ_f32x16 circ_mac(circ_f32x16 acc, const circ_u32x4& a, const circ_u32x4& b)
+{
+    circ_bf16x8 va, vb;
+    __builtin_memcpy(&va, &a, 16);
+    __builtin_memcpy(&vb, &b, 16);
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, vb, acc, 0, 0, 0);
+}
+
+// 8 tokens of a channel pair as they lie in memory, and the operands of the two channel tiles made of them
+template <typename T> struct circ_raw;
+template <> struct circ_raw<bf16_t> {
+    static constexpr int TERMS = 1;
+    uint32_t w[8];
+    __device__ __forceinline__ void fetch(int j, __amdgpu_buffer_rsrc_t r, uint32_t off) { w[j] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
+    __device__ __forceinline__ void operands(circ_u32x4 (&even)[1], circ_u32x4 (&odd)[1]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            even[0][i] = __builtin_amdgcn_perm(w[2 * i + 1], w[2 * i], 0x05040100u);
+            odd[0][i] = __builtin_amdgcn_perm(w[2 * i + 1], w[2 * i], 0x07060302u);
+        }
+    }
+};
+template <> struct circ_raw<float> {
+    static constexpr int TERMS = 3;
+    circ_u32x2 w[8];
+    __device__ __forceinline__ void fetch(int j, __amdgpu_buffer_rsrc_t r, uint32_t off) { w[j] = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0); }
+    __device__ static __forceinline__ void split(float a, float b, uint32_t& t0, uint32_t& t1, uint32_t& t2)
+    {
+        t0 = pk_bf16(a, b);
+        a -= __uint_as_float(t0 << 16);
+        b -= __uint_as_float(t0 & 0xffff0000u);
+        t1 = pk_bf16(a, b);
+        a -= __uint_as_float(t1 << 16);
+        b -= __uint_as_float(t1 & 0xffff0000u);
+        t2 = pk_bf16(a, b);
+    }
+    __device__ __forceinline__ void operands(circ_u32x4 (&even)[3], circ_u32x4 (&odd)[3]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t t0, t1, t2;
+            split(__uint_as_float(w[2 * i][0]), __uint_as_float(w[2 * i + 1][0]), t0, t1, t2);
+            even[0][i] = t0; even[1][i] = t1; even[2][i] = t2;
+            split(__uint_as_float(w[2 * i][1]), __uint_as_float(w[2 * i + 1][1]), t0, t1, t2);
+            odd[0][i] = t0; odd[1][i] = t1; odd[2][i] = t2;
+        }
+    }
+};
+
+// LDS: taps [3 terms][8 displacements] of circ_stride bytes, 32 mod 256; the taps once more, undisplaced; p itself
+__host__ __device__ inline int circ_taps(int N, int RT) { return (N + 15) / 16 * 16 + 32 * RT + 8; }
+__host__ __device__ inline int circ_stride(int N, int RT) { return ((circ_taps(N, RT) + 8) * 2 + 223) / 256 * 256 + 32; }
+__host__ __device__ inline int circ_lds(int N, int RT) { return 24 * circ_stride(N, RT) + 3 * 2 * (circ_taps(N, RT) + 16) + 3 * 2 * (N / 2 + 2); }
+
+}  // namespace
+
+template <typename T, int RT>
+__global__ void __launch_bounds__(256, 2)
+spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* workgroups across the channels */, int use_hamming, const CircRuns runs,
+         unsigned long long* __restrict__ words /* [groups of 32 RT tokens][n_quads][32 RT] */, uint32_t tag, float* __restrict__ scores)
+{
+    using raw_t = circ_raw<T>;
+    constexpr int ROWS = 32 * RT, TERMS = raw_t::TERMS;
+    constexpr int PF = RT == 4 ? 2 : 4;          // steps of 16 tokens in flight
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double part[256];
+    __shared__ float red[4 * ROWS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int item = (int)xcd_contiguous(blockIdx.x, gridDim.x);
+    CircRun run = runs.run[0];                   // fetched beside the count: one run is the common case
+    if (runs.n > 1) {
+        int q = 0;
+        for (int i = 1; i < runs.n; ++i)
+            if (item >= runs.run[i].group0 * n_quads) q = i;
+        run = runs.run[q];
+    }
+    const int N = run.N, sigma = run.sigma, group0 = run.group0;
+    const int n_groups = (N + ROWS - 1) / ROWS, local = item - group0 * n_quads;
+    const int s = local / (n_quads * n_groups), rem = local - s * (n_quads * n_groups), quad = rem / n_groups, grp = rem - quad * n_groups;
+    const int64_t tok = run.tok0 + (int64_t)s * N;
+    const int n0 = grp * ROWS, steps = (N + 15) / 16;
+
+    // ---- tokens: lane l fetches channels 2 (l % 32), + 1 of the wavefront's 64 and the tokens of half l / 32 of a step
+    const int d0 = (quad * 4 + wave) * 64, h = lane >> 5, c31 = lane & 31;
+    const bool live = d0 < D;
+    const uint32_t row_bytes = (uint32_t)row_stride * (uint32_t)sizeof(T);
+    // the descriptor ends with the last token of the sample: tokens past it read zeros; so do channels past D (an offset beyond any descriptor)
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<T*>(x) + tok * row_stride + (live ? d0 : 0), 0,
+        live ? (int)((uint32_t)(N - 1) * row_bytes + (uint32_t)((D - d0 < 64 ? D - d0 : 64) * (int)sizeof(T))) : 0, 0x00020000);
+    const uint32_t lane_off = d0 + 2 * c31 < D ? (uint32_t)(8 * h) * row_bytes + (uint32_t)(2 * c31 * (int)sizeof(T)) : 0x80000000u;
+    raw_t raw[PF];
+    auto fetch = [&](raw_t& r, int k) {
+        const uint32_t off = lane_off + (uint32_t)(16 * k) * row_bytes;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) r.fetch(j, rx, off + (uint32_t)j * row_bytes);
+    };
+#pragma unroll
+    for (int u = 0; u < PF; ++u) fetch(raw[u], u);
+
+    // ---- taps: p[0 .. N/2] in fp64, split into three bf16 terms; entry o of the line of taps is p[o - n0 - ROWS]
+    const int taps = circ_taps(N, RT), stride = circ_stride(N, RT);
+    uint16_t* line = reinterpret_cast<uint16_t*>(smem + 24 * stride);          // [3][taps + 16]
+    uint16_t* base = line + 3 * (taps + 16);                                   // [3][N / 2 + 2]
+    {
+        const SpuTaps p(N, sigma, use_hamming);
+        for (int j = tid; j <= N / 2; j += 256) {
+            double v = p(j);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                const uint16_t b = f64_to_bf16(v);
+                base[t * (N / 2 + 2) + j] = b;
+                v -= (double)bf16_to_f32(b);
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < taps + 16; i += 256) {
+        int j = (i - n0 - ROWS) % N;
+        j = j < 0 ? j + N : j;
+        j = 2 * j > N ? N - j : j;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) line[t * (taps + 16) + i] = base[t * (N / 2 + 2) + j];
+    }
+    __syncthreads();
+    for (int tc = wave; tc < 24; tc += 4) {      // copy c of term t, a lane 8 taps at a time
+        const int t = tc >> 3, c = tc & 7;
+        const uint32_t* from = reinterpret_cast<const uint32_t*>(line + t * (taps + 16));
+        for (int i = lane; i * 8 < taps; i += 64) {
+            const int at = (i * 8 + c) >> 1;
+            uint32_t v[5];
+#pragma unroll
+            for (int e = 0; e < 5; ++e) v[e] = from[at + e];
+            circ_u32x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (c & 1) ? __builtin_amdgcn_alignbit(v[e + 1], v[e], 16) : v[e];
+            *reinterpret_cast<circ_u32x4*>(smem + tc * stride + i * 16) = o;
+        }
+    }
+    __syncthreads();
+
+    // ---- the product
+    circ_f32x16 acc[RT][2];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[t][o][v] = 0.f;
+    if (live) {
+        const int cp = (8 - (c31 & 7)) & 7;
+        const unsigned char* tap = smem + cp * stride + (8 * h + ROWS - c31 - cp) * 2;
+        auto step = [&](const raw_t& r, int k) {
+            circ_u32x4 xe[TERMS], xo[TERMS];
+            r.operands(xe, xo);
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                circ_u32x4 pt[3];
+#pragma unroll
+                for (int e = 0; e < 3; ++e) pt[e] = *reinterpret_cast<const circ_u32x4*>(tap + e * 8 * stride + k * 32 - t * 64);
+                // smallest products first
+#pragma unroll
+                for (int sum = 2; sum >= 0; --sum)
+#pragma unroll
+                    for (int e = 2; e >= 0; --e) {
+                        const int f = TERMS == 1 ? 0 : sum - e;
+                        if (TERMS == 1 ? e != sum : (f < 0 || f >= TERMS)) continue;
+                        acc[t][0] = circ_mac(acc[t][0], xe[f < 0 ? 0 : f], pt[e]);
+                        acc[t][1] = circ_mac(acc[t][1], xo[f < 0 ? 0 : f], pt[e]);
+                    }
+            }
+        };
+        for (int k = 0; k < steps; k += PF) {
+#pragma unroll
+            for (int u = 0; u < PF; ++u) {
+                if (k + u < steps) {
+                    step(raw[u], k + u);
+                    fetch(raw[u], k + u + PF);
+                }
+            }
+        }
+    }
+    // ---- Eq. 8: over the wavefront's channels (16 rows per lane and tile, two halves of the wavefront), then the four wavefronts
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        float e = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { e = fmaf(acc[t][0][v], acc[t][0][v], e); e = fmaf(acc[t][1][v], acc[t][1][v], e); }
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(e), __float_as_uint(e), false, false);
+        e = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+        if (h == 0) red[wave * ROWS + t * 32 + c31] = e;
+    }
+    __syncthreads();
+    float own = 0.f;
+    if (tid < ROWS) own = ((red[tid] + red[ROWS + tid]) + red[2 * ROWS + tid]) + red[3 * ROWS + tid];
+    float* out = scores + tok + n0;
+    if (n_quads == 1) {
+        if (tid < ROWS && n0 + tid < N) out[tid] = sqrtf(own);
+        return;
+    }
+    unsigned long long* w = words + (int64_t)(group0 + s * n_groups + grp) * n_quads * ROWS;
+    if (tid < ROWS)
+        __hip_atomic_store(w + quad * ROWS + tid, ((unsigned long long)tag << 32) | __float_as_uint(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    // ---- all of them there?  Thread: a token, every PARTS-th workgroup
+    constexpr int PARTS = 256 / ROWS;
+    const int row = tid % ROWS, pt0 = tid / ROWS;
+    bool all = true;
+    double e = 0.0;
+    for (int i0 = pt0; i0 < n_quads; i0 += 8 * PARTS) {
+        unsigned long long v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int at = i0 + i * PARTS < n_quads ? i0 + i * PARTS : i0;
+            v[i] = __hip_atomic_load(w + at * ROWS + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            all = all && (uint32_t)(v[i] >> 32) == tag;
+            e += i0 + i * PARTS < n_quads ? (double)__uint_as_float((uint32_t)v[i]) : 0.0;
+        }
+    }
+    part[tid] = e;
+    if (!__syncthreads_and(all)) return;
+    for (int i = pt0; i < n_quads; i += PARTS) __hip_atomic_store(w + i * ROWS + row, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid < ROWS && n0 + tid < N) {
+        double sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) sum += part[i * ROWS + tid];
+        out[tid] = (float)sqrt(sum);
+    }
+}
+
+// ------------------------------------------------------------------ host side
+static int circ_quads(int D) { return (D + 255) / 256; }
+
+// Output tokens per workgroup / 32.  More of them share a fetch and a set of operands (a row of output costs 1.25 with
+// RT = 1, 1.05 with 2, 1 with 4), fewer pad less and make more workgroups, of which every compute unit should have one.
+static int circ_rt(const CircRuns& runs, int D)
+{
+    int best = 1;
+    double best_cost = 0.0;
+    for (int RT = 1; RT <= 4; RT *= 2) {
+        int64_t wg = 0;
+        double cost = 0.0;
+        for (int i = 0; i < runs.n; ++i) {
+            const int64_t groups = (int64_t)runs.run[i].count * ((runs.run[i].N + 32 * RT - 1) / (32 * RT));
+            wg += groups * circ_quads(D);
+            cost += (double)groups * RT * ((runs.run[i].N + 15) / 16) * (RT == 1 ? 1.25 : RT == 2 ? 1.05 : 1.0);
+        }
+        if (RT == 1 || (wg >= 256 && cost < best_cost)) { best = RT; best_cost = cost; }
+    }
+    return best;
+}
+
+bool spu_circ_aligned(const void* x, int D, int64_t row_stride, luvc_dtype dt)
+{
+    const int64_t es = dt == LUVC_F32 ? 4 : 2;
+    // one access per channel pair; a sample inside one descriptor, below the offset that marks a lane without channels
+    return D % 2 == 0 && row_stride % 2 == 0 && (uintptr_t)x % (uintptr_t)(2 * es) == 0 && (int64_t)(kCircMaxN + 64) * row_stride * es < ((int64_t)1 << 31);
+}
+
+// one word per output token (rounded up to a workgroup's share) and 256 channels
+size_t spu_circ_bytes(int64_t samples, int N, int D)
+{
+    return circ_quads(D) == 1 ? 0 : sizeof(unsigned long long) * (size_t)samples * circ_quads(D) * ((size_t)(N + 127) / 128 * 128);
+}
+
+template <typename T, int RT>
+static void circ_launch(const T* x, int64_t row_stride, int D, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st)
+{
+    int64_t groups = 0;
+    int lds = 0;
+    for (int i = 0; i < runs.n; ++i) {
+        runs.run[i].group0 = (int)groups;
+        groups += (int64_t)runs.run[i].count * ((runs.run[i].N + 32 * RT - 1) / (32 * RT));
+        const int b = circ_lds(runs.run[i].N, RT);
+        lds = b > lds ? b : lds;
+    }
+    LUVC_LAUNCH("spu_circ", (spu_circ<T, RT>), dim3((unsigned)(groups * circ_quads(D))), dim3(256), (size_t)lds, st, x, row_stride, D, circ_quads(D), use_hamming,
+                runs, (unsigned long long*)words, (uint32_t)(spu_next_tag() % 0xffffffffull) + 1u, scores);
+}
+
+luvc_status spu_score_circ(const void* x, int64_t row_stride, int D, luvc_dtype dt, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st)
+{
+    const int RT = circ_rt(runs, D);
+#define LUVC_CIRC(TT, R) circ_launch<TT, R>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st)
+    if (dt == LUVC_F32) { if (RT == 4) LUVC_CIRC(float, 4); else if (RT == 2) LUVC_CIRC(float, 2); else LUVC_CIRC(float, 1); }
+    else                { if (RT == 4) LUVC_CIRC(bf16_t, 4); else if (RT == 2) LUVC_CIRC(bf16_t, 2); else LUVC_CIRC(bf16_t, 1); }
+#undef LUVC_CIRC
+    return check_launch("spu score (circulant)");
+}
+
+}  // namespace luvc

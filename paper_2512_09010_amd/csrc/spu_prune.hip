@@ -175,8 +175,9 @@ spu_gather(const unsigned char* __restrict__ x, const int32_t* __restrict__ kept
 }
 
 // ------------------------------------------------------------------ select + gather in one launch (N <= 4096)
-// Workgroup (g, b) of 256 threads repeats the selection of sample b on its own (the scores of a sample
-// are a few KB, and the groups run side by side), keeps the list of kept tokens in LDS, and then copies
+// Workgroup g of sample b, 256 threads, repeats the selection of the sample on its own (the scores of a sample
+// are a few KB, and the groups run side by side; samples of different lengths share a launch, the argument lists
+// runs of equal ones), keeps the list of kept tokens in LDS, and then copies
 // its share of the kept rows: row q goes to wavefront q mod (4 G) of the sample.  Group 0 also writes
 // kept_idx.  Compared with a selection launch followed by a gather launch this saves a dispatch and the
 // wait between the two, which is most of the time at these sizes.
@@ -186,18 +187,34 @@ constexpr int kPruneLoadAux = 0, kPruneStoreAux = 2;
 typedef unsigned int prune_u32x4 __attribute__((__vector_size__(16)));
 constexpr int kFusedMaxN = 4096, kFusedThreads = 256, kFusedKeys = kFusedMaxN / kFusedThreads;
 
+// workgroups of a sample: one kept row per wavefront, up to 256 of them
+__host__ __device__ inline int prune_groups(int n_keep, bool gather)
+{
+    const int G = gather ? (n_keep + 3) / 4 : 1;
+    return G > 256 ? 256 : G;
+}
+
 template <int BYTES>
 __global__ void __launch_bounds__(kFusedThreads)
-spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ scores, int N, int n_keep,
+spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ scores, const PruneRuns runs,
                 int64_t row_bytes_in, int64_t row_bytes_out, int32_t* __restrict__ kept_idx, unsigned char* __restrict__ x_out,
-                const int32_t* __restrict__ origin_in /* [B,N] or null: identity */, int32_t* __restrict__ origin_out /* [B,n_keep] or null */)
+                const int32_t* __restrict__ origin_in /* per token or null: identity */, int32_t* __restrict__ origin_out /* per kept token or null */)
 {
     __shared__ int32_t kept[kFusedMaxN];
     __shared__ int hist[4][256];                       // one histogram per digit pass: none has to be cleared in between
     __shared__ uint32_t wave_tot[4], wave_hi[4], wave_lo[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = blockIdx.x, G = gridDim.x, b = blockIdx.y;
-    const float* s = scores + (int64_t)b * N;
+    PruneRun run = runs.run[0];                        // fetched beside the count: one run is the common case
+    if (runs.n > 1) {
+        int r = 0;
+        for (int i = 1; i < runs.n; ++i)
+            if ((int)blockIdx.x >= runs.run[i].wg0) r = i;
+        run = runs.run[r];
+    }
+    const int N = run.N, n_keep = run.n_keep, G = prune_groups(n_keep, x_out != nullptr);
+    const int b = ((int)blockIdx.x - run.wg0) / G, g = (int)blockIdx.x - run.wg0 - b * G;
+    const int64_t tok_in = run.tok_in + (int64_t)b * N, tok_out = run.tok_out + (int64_t)b * n_keep;
+    const float* s = scores + tok_in;
     // thread tid owns the K consecutive tokens tid * K .. tid * K + K - 1 and reads them straight from memory
     // (a wavefront covers 64 K consecutive scores; a few KB per sample, served by the caches)
     const int K = (N + kFusedThreads - 1) / kFusedThreads, n0 = tid * K;
@@ -283,18 +300,18 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
     }
     __syncthreads();
     if (g == 0) {
-        for (int q = tid; q < n_keep; q += kFusedThreads) kept_idx[(int64_t)b * n_keep + q] = kept[q];
+        for (int q = tid; q < n_keep; q += kFusedThreads) kept_idx[tok_out + q] = kept[q];
         // position of every kept token before the first stage of a cascade
         if (origin_out)
             for (int q = tid; q < n_keep; q += kFusedThreads)
-                origin_out[(int64_t)b * n_keep + q] = origin_in ? origin_in[(int64_t)b * N + kept[q]] : kept[q];
+                origin_out[tok_out + q] = origin_in ? origin_in[tok_in + kept[q]] : kept[q];
     }
     if (!x_out) return;
     for (int q = g * 4 + wave; q < n_keep; q += G * 4) {
         int src = kept[q];
         src = src < 0 ? 0 : (src >= N ? N - 1 : src);  // in bounds whatever the scores held
-        const unsigned char* in = x + ((int64_t)b * N + src) * row_bytes_in;
-        unsigned char* o = x_out + ((int64_t)b * n_keep + q) * row_bytes_out;
+        const unsigned char* in = x + (tok_in + src) * row_bytes_in;
+        unsigned char* o = x_out + (tok_out + q) * row_bytes_out;
         if (BYTES == 16) {
             // eight 16-byte pieces per lane in flight before the first store (bounds by the buffer descriptors: pieces
             // past the end of the row read zeros and write nothing), so a row costs one trip to memory, not seven
@@ -318,24 +335,11 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
     }
 }
 
-luvc_status spu_prune_run(const void* x, const float* scores, int B, int N, int D, int64_t row_stride, luvc_dtype dt,
-                          int n_keep, int32_t* kept_idx, void* x_out, const int32_t* origin_in, int32_t* origin_out, hipStream_t st)
+static luvc_status prune_two_launches(const void* x, const float* scores, int B, int N, int D, int64_t row_stride, luvc_dtype dt,
+                                      int n_keep, int32_t* kept_idx, void* x_out, const int32_t* origin_in, int32_t* origin_out, bool v16, hipStream_t st)
 {
     const int es = dt == LUVC_F32 ? 4 : 2;
     const int64_t rin = row_stride * es, rout = (int64_t)D * es, rows = (int64_t)B * n_keep;
-    const bool v16 = x_out && rin % 16 == 0 && rout % 16 == 0 && ((uintptr_t)x % 16 == 0) && ((uintptr_t)x_out % 16 == 0);
-    if (N <= kFusedMaxN && B <= 65535) {
-        int G = x_out ? (n_keep + 3) / 4 : 1;          // one kept row per wavefront, up to 256 groups per sample
-        G = G > 256 ? 256 : G;
-        const dim3 grid((unsigned)G, (unsigned)B);
-        if (v16 || !x_out)
-            LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<16>), grid, dim3(kFusedThreads), 0, st, (const unsigned char*)x, scores, N, n_keep, rin, rout, kept_idx, (unsigned char*)x_out, origin_in, origin_out);
-        else if (es == 4)
-            LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<4>), grid, dim3(kFusedThreads), 0, st, (const unsigned char*)x, scores, N, n_keep, rin, rout, kept_idx, (unsigned char*)x_out, origin_in, origin_out);
-        else
-            LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<2>), grid, dim3(kFusedThreads), 0, st, (const unsigned char*)x, scores, N, n_keep, rin, rout, kept_idx, (unsigned char*)x_out, origin_in, origin_out);
-        return check_launch("spu prune");
-    }
     LUVC_LAUNCH("spu_select", spu_select, dim3((unsigned)B), dim3(kSelThreads), 0, st, scores, N, n_keep, kept_idx, origin_in, origin_out);
     if (x_out) {
         const unsigned g = (unsigned)((rows * 64 + 255) / 256);
@@ -346,6 +350,40 @@ luvc_status spu_prune_run(const void* x, const float* scores, int B, int N, int 
         else
             LUVC_LAUNCH("spu_gather", (spu_gather<2>), dim3(g), dim3(256), 0, st, (const unsigned char*)x, kept_idx, N, n_keep, rin, rout, rows, (unsigned char*)x_out);
     }
+    return check_launch("spu prune");
+}
+
+luvc_status spu_prune_run(const void* x, const float* scores, int D, int64_t row_stride, luvc_dtype dt, PruneRuns& runs,
+                          int32_t* kept_idx, void* x_out, const int32_t* origin_in, int32_t* origin_out, hipStream_t st)
+{
+    const int es = dt == LUVC_F32 ? 4 : 2;
+    const int64_t rin = row_stride * es, rout = (int64_t)D * es;
+    const bool v16 = x_out && rin % 16 == 0 && rout % 16 == 0 && ((uintptr_t)x % 16 == 0) && ((uintptr_t)x_out % 16 == 0);
+    int64_t wgs = 0;
+    int fused = 0;
+    for (int i = 0; i < runs.n; ++i) {
+        const PruneRun r = runs.run[i];
+        if (r.N > kFusedMaxN) {                            // the list of kept tokens does not fit in LDS
+            const luvc_status rc = prune_two_launches((const char*)x + r.tok_in * rin, scores + r.tok_in, r.count, r.N, D, row_stride, dt, r.n_keep, kept_idx + r.tok_out,
+                                                      x_out ? (char*)x_out + r.tok_out * rout : nullptr, origin_in ? origin_in + r.tok_in : nullptr,
+                                                      origin_out ? origin_out + r.tok_out : nullptr, v16, st);
+            if (rc != LUVC_OK) return rc;
+            continue;
+        }
+        runs.run[fused] = r;
+        runs.run[fused].wg0 = (int)wgs;
+        wgs += (int64_t)r.count * prune_groups(r.n_keep, x_out != nullptr);
+        ++fused;
+    }
+    if (fused == 0) return LUVC_OK;
+    if (wgs >= ((int64_t)1 << 31)) { set_error("too many kept tokens in one call"); return LUVC_ERR_UNSUPPORTED; }
+    runs.n = fused;
+#define LUVC_PRUNE(BYTES) LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<BYTES>), dim3((unsigned)wgs), dim3(kFusedThreads), 0, st, (const unsigned char*)x, scores, runs, \
+                                      rin, rout, kept_idx, (unsigned char*)x_out, origin_in, origin_out)
+    if (v16 || !x_out) LUVC_PRUNE(16);
+    else if (es == 4)  LUVC_PRUNE(4);
+    else               LUVC_PRUNE(2);
+#undef LUVC_PRUNE
     return check_launch("spu prune");
 }
 
