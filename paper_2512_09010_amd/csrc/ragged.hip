@@ -1,7 +1,14 @@
 // Ragged batches (appendix "Iterative Strategy and Pseudocode of OIM": with any-resolution inputs every image has
 // its own grid and its own number of merges): images / samples of different shapes packed back to back.  Host code
-// only: consecutive items of equal shape and schedule form a run, and every run is one batched call of the entry
-// points in api.hip, on slices of the packed buffers.  Every item is validated before the first launch.
+// only: consecutive items of equal shape and schedule form a run; every item is validated before the first launch.
+//
+// Runs share launches wherever a kernel takes several of them.  OIM: images whose schedules consist of halvings advance
+// together, one launch per step and kind of step (a pair of passes, a single pass), then one for the images that stay as
+// they are and the maps of those with several steps.  SPU: the short samples are scored in one launch, all samples pruned
+// in one.  What does not fit these (other merge numbers, long samples, unaligned rows) is a batched call of the entry points
+// in api.hip per run.  A launch costs 4 to 12 us whatever it does: eight images of 24x24 to 56x56 tokens took
+// {RAGGED_US}.
+#include <algorithm>
 #include <vector>
 
 #include "common.hpp"
@@ -56,6 +63,112 @@ bool oim_runs(int n_images, const int32_t* H, const int32_t* W, const luvc_oim_p
         p += n_passes[i];
     }
     return true;
+}
+
+// ---- runs that advance together
+struct BatchStep { int h, w, axis, passes; };        // grid before the step; one pass or a fused pair
+struct BatchRun {
+    const OimRun* run;
+    int n;
+    BatchStep step[kMaxPasses];
+    int64_t tokens, between;                          // of the run: entering, and the most any step but the last leaves
+    int64_t map_off, between_off;                     // its place among the runs with several steps
+};
+struct BatchPlan {
+    std::vector<BatchRun> runs;
+    std::vector<const OimRun*> others;
+    int levels = 0;
+    int64_t map_level = 0, between = 0;               // tokens of the runs with several steps: map entries per step, scratch rows
+    size_t x[2], sizes[2], kept[2], maps, bytes;
+};
+
+bool batch_run(const OimRun& r, int D, luvc_dtype dt, BatchRun* b)
+{
+    luvc_oim_pass ps[kMaxPasses];
+    int n = 0, h = r.H, w = r.W;
+    for (int i = 0; i < r.n_passes; ++i)
+        if (r.passes[i].m != 0) ps[n++] = r.passes[i];
+    b->run = &r;
+    b->n = 0;
+    b->tokens = (int64_t)r.count * h * w;
+    b->between = 0;
+    for (int i = 0; i < n;) {
+        const bool pair = i + 1 < n && oim_pair_supported(h, w, D, dt, ps[i].axis, ps[i].m, ps[i + 1].axis, ps[i + 1].m, true);
+        if (!pair && !oim_halve_supported(h, w, D, dt, ps[i].axis, ps[i].m, true)) return false;
+        if (b->n) b->between = std::max(b->between, (int64_t)r.count * h * w);
+        b->step[b->n++] = BatchStep{h, w, ps[i].axis, pair ? 2 : 1};
+        for (int k = 0; k < (pair ? 2 : 1); ++k, ++i) (ps[i].axis ? w : h) -= ps[i].m;
+    }
+    return true;
+}
+
+// vec: rows are 16-byte aligned
+void batch_plan(const std::vector<OimRun>& runs, int D, luvc_dtype dt, bool vec, BatchPlan* p)
+{
+    BatchRun b;
+    for (const OimRun& r : runs) {
+        if (runs.size() > 1 && vec && batch_run(r, D, dt, &b)) {
+            b.map_off = p->map_level;
+            b.between_off = p->between;
+            if (b.n > 1) { p->map_level += b.tokens; p->between += b.between; }
+            p->levels = std::max(p->levels, b.n);
+            p->runs.push_back(b);
+        } else {
+            p->others.push_back(&r);
+        }
+    }
+    size_t off = 0;
+    for (int j = 0; j < 2; ++j) {
+        p->x[j] = off;     off += align_up((size_t)p->between * D * (dt == LUVC_F32 ? 4 : 2));
+        p->sizes[j] = off; off += align_up((size_t)p->between * sizeof(int32_t));
+        p->kept[j] = off;  off += align_up((size_t)p->between * sizeof(int32_t));
+    }
+    p->maps = off;         off += p->levels > 1 ? align_up((size_t)p->levels * p->map_level * sizeof(int32_t)) : 0;
+    p->bytes = off;
+}
+
+luvc_status batch_run_all(const BatchPlan& p, const void* x, const int32_t* sizes_in, int D, luvc_dtype dt, void* x_out, int32_t* sizes_out,
+                          int32_t* merged_map, int32_t* kept_map, char* ws, hipStream_t st)
+{
+    int32_t* maps = (int32_t*)(ws + p.maps);
+    OimStepItem items[kOimMaxItems];
+    for (int s = 0; s < p.levels; ++s) {
+        const int i0 = (s + 1) & 1, o = s & 1;
+        const StepIn in = s == 0 ? StepIn{x, sizes_in, nullptr} : StepIn{ws + p.x[i0], (int32_t*)(ws + p.sizes[i0]), (int32_t*)(ws + p.kept[i0])};
+        const StepOut out = {{x_out, ws + p.x[o]}, {sizes_out, (int32_t*)(ws + p.sizes[o])}, {kept_map, kept_map ? (int32_t*)(ws + p.kept[o]) : nullptr},
+                             {merged_map, merged_map ? maps + s * p.map_level : nullptr}};
+        for (int passes = 2; passes >= 1; --passes) {
+            int n = 0;
+            for (size_t i = 0; i <= p.runs.size(); ++i) {
+                if (n == kOimMaxItems || (i == p.runs.size() && n)) {
+                    const luvc_status rc = passes == 2 ? oim_pair_step(items, n, in, out, D, dt, st) : oim_halve_step(items, n, in, out, D, dt, st);
+                    if (rc != LUVC_OK) return rc;
+                    n = 0;
+                }
+                if (i == p.runs.size()) break;
+                const BatchRun& b = p.runs[i];
+                if (s >= b.n || b.step[s].passes != passes) continue;
+                const bool last = s + 1 == b.n, single = b.n == 1;
+                items[n++] = OimStepItem{b.step[s].h, b.step[s].w, b.step[s].axis, b.run->count,
+                                         StepAt{s == 0 ? b.run->tok_in : b.between_off, last ? b.run->tok_out : b.between_off,
+                                                single ? b.run->tok_in : b.map_off, b.run->H * b.run->W, 0, last ? 0 : 1, single ? 0 : 1}};
+            }
+        }
+    }
+    OimTailItem tail[kOimMaxItems];
+    int n = 0;
+    for (size_t i = 0; i <= p.runs.size(); ++i) {
+        if (n == kOimMaxItems || (i == p.runs.size() && n)) {
+            const luvc_status rc = oim_batch_tail(tail, n, x, sizes_in, D * (dt == LUVC_F32 ? 4 : 2), x_out, sizes_out, merged_map, kept_map, maps, p.map_level, st);
+            if (rc != LUVC_OK) return rc;
+            n = 0;
+        }
+        if (i == p.runs.size()) break;
+        const BatchRun& b = p.runs[i];
+        if (b.n == 0 || (b.n > 1 && merged_map))
+            tail[n++] = OimTailItem{b.n == 0, b.run->H * b.run->W, b.n, 0, b.tokens, b.run->tok_in, b.run->tok_out, b.map_off};
+    }
+    return LUVC_OK;
 }
 
 struct SpuRun {
@@ -127,6 +240,9 @@ size_t luvc_oim_ragged_workspace_bytes(int n_images, const int32_t* H, const int
         if (b == 0) return 0;
         need = b > need ? b : need;
     }
+    BatchPlan plan;
+    batch_plan(runs, D, dtype, (size_t)D * esz(dtype) % 16 == 0, &plan);
+    need = plan.bytes > need ? plan.bytes : need;
     return need;
 }
 
@@ -147,7 +263,13 @@ luvc_status luvc_oim_merge_ragged(const void* x, const int32_t* sizes_in, int n_
         if (!workspace_ok(workspace, workspace_bytes, b)) return LUVC_ERR_WORKSPACE;
     }
     const size_t row = (size_t)D * esz(dtype);
-    for (const OimRun& r : runs) {
+    BatchPlan plan;
+    batch_plan(runs, D, dtype, row % 16 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)x_out % 16 == 0, &plan);
+    if (!workspace_ok(workspace, workspace_bytes, plan.bytes)) return LUVC_ERR_WORKSPACE;
+    const luvc_status rc = batch_run_all(plan, x, sizes_in, D, dtype, x_out, sizes_out, merged_map, kept_map, (char*)workspace, (hipStream_t)hip_stream);
+    if (rc != LUVC_OK) return rc;
+    for (const OimRun* q : plan.others) {
+        const OimRun& r = *q;
         const luvc_status rc = luvc_oim_merge(
             (const char*)x + (size_t)r.tok_in * row, sizes_in ? sizes_in + r.tok_in : nullptr, r.count, r.H, r.W, D, dtype,
             r.passes, r.n_passes, 0, (char*)x_out + (size_t)r.tok_out * row, sizes_out + r.tok_out,
@@ -162,13 +284,14 @@ size_t luvc_spu_ragged_workspace_bytes(int n_samples, const int32_t* N, int D, l
 {
     std::vector<SpuRun> runs;
     if (D < 1 || !spu_runs(n_samples, N, sigma, nullptr, &runs)) return 0;
-    size_t need = 0;
+    size_t need = 0, shared = 0;
     for (const SpuRun& r : runs) {
         const size_t b = luvc_spu_workspace_bytes(r.count, r.N, D, dtype, r.sigma);
         if (b == 0) return 0;
         need = b > need ? b : need;
+        if (spu_circ_in_batch(r.count, r.N, D, r.sigma, dtype)) shared += spu_circ_bytes(r.count, r.N, D);
     }
-    return need;
+    return need > align_up(shared) ? need : align_up(shared);
 }
 
 luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N, int D, int64_t row_stride, luvc_dtype dtype,
@@ -182,26 +305,50 @@ luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N
     if (n_keep && (!kept_idx || !origin_out)) { set_error("kept_idx and origin_out must be given with n_keep"); return LUVC_ERR_INVALID_ARG; }
     std::vector<SpuRun> runs;
     if (!spu_runs(n_samples, N, sigma, n_keep, &runs)) return LUVC_ERR_INVALID_ARG;
+    const bool circ = spu_circ_aligned(x, D, row_stride, dtype);
+    size_t shared = 0;
     for (const SpuRun& r : runs) {
         const size_t b = luvc_spu_workspace_bytes(r.count, r.N, D, dtype, r.sigma);
         if (b == 0) { set_error("run of %d samples with N=%d, sigma=%d is not supported", r.count, r.N, r.sigma); return LUVC_ERR_INVALID_ARG; }
         if (!workspace_ok(workspace, workspace_bytes, b)) return LUVC_ERR_WORKSPACE;
+        if (circ && spu_circ_in_batch(r.count, r.N, D, r.sigma, dtype)) shared += spu_circ_bytes(r.count, r.N, D);
     }
+    if (!workspace_ok(workspace, workspace_bytes, align_up(shared))) return LUVC_ERR_WORKSPACE;
     const size_t es = esz(dtype);
+    hipStream_t st = (hipStream_t)hip_stream;
+    // scores: the short samples share launches, every other run is a call of its own
+    CircRuns cr;
+    cr.n = 0;
+    auto flush_scores = [&]() {
+        const luvc_status rc = cr.n ? spu_score_circ(x, row_stride, D, dtype, use_hamming ? 1 : 0, cr, workspace, scores, st) : LUVC_OK;
+        cr.n = 0;
+        return rc;
+    };
     for (const SpuRun& r : runs) {
-        const char* xr = (const char*)x + (size_t)r.tok_in * (size_t)row_stride * es;
-        luvc_status rc;
-        if (!n_keep || r.keep == 0)                      // scores only (a sample that is eliminated still gets its scores)
-            rc = luvc_spu_score(xr, r.count, r.N, D, row_stride, dtype, r.sigma, use_hamming, scores + r.tok_in,
-                                workspace, workspace_bytes, hip_stream);
-        else
-            rc = luvc_spu_stage(xr, r.count, r.N, D, row_stride, dtype, r.sigma, use_hamming, r.keep,
-                                origin_in ? origin_in + r.tok_in : nullptr, scores + r.tok_in, kept_idx + r.tok_out,
-                                origin_out + r.tok_out, x_out ? (char*)x_out + (size_t)r.tok_out * D * es : nullptr,
-                                workspace, workspace_bytes, hip_stream);
+        luvc_status rc = LUVC_OK;
+        if (circ && spu_circ_in_batch(r.count, r.N, D, r.sigma, dtype)) {
+            cr.run[cr.n++] = CircRun{0, r.N, r.sigma, r.count, r.tok_in};
+            if (cr.n == kCircMaxRuns) rc = flush_scores();
+        } else {
+            rc = luvc_spu_score((const char*)x + (size_t)r.tok_in * (size_t)row_stride * es, r.count, r.N, D, row_stride, dtype, r.sigma, use_hamming,
+                                scores + r.tok_in, workspace, workspace_bytes, hip_stream);
+        }
         if (rc != LUVC_OK) return rc;
     }
-    return LUVC_OK;
+    luvc_status rc = flush_scores();
+    if (rc != LUVC_OK || !n_keep) return rc;
+    // keep and gather (a sample that is eliminated only gets its scores)
+    PruneRuns pr;
+    pr.n = 0;
+    for (const SpuRun& r : runs) {
+        if (r.keep == 0) continue;
+        pr.run[pr.n++] = PruneRun{0, r.N, r.keep, r.count, r.tok_in, r.tok_out};
+        if (pr.n < kPruneMaxRuns) continue;
+        rc = spu_prune_run(x, scores, D, row_stride, dtype, pr, kept_idx, x_out, origin_in, origin_out, st);
+        if (rc != LUVC_OK) return rc;
+        pr.n = 0;
+    }
+    return pr.n ? spu_prune_run(x, scores, D, row_stride, dtype, pr, kept_idx, x_out, origin_in, origin_out, st) : LUVC_OK;
 }
 
 }  // extern "C"

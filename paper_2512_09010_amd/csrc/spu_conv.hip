@@ -402,6 +402,16 @@ int spu_conv_tiles(int B, int N, int D)
     return best;
 }
 
+// us of one call, from measurements: a launch for the spectrum where one is needed, then what a workgroup starts with and its
+// pair groups one after the other.  8x1200x3584 bf16: 148, 1x2000x3584: 37, 4x4096x3584: 129.
+double spu_conv_us(int B, int N, int D)
+{
+    bool half;
+    const int R = spu_conv_rows(N, &half), P = conv_pairs(R), ng = (D + 2 * P - 1) / (2 * P), t = spu_conv_tiles(B, N, D);
+    const double rounds = (double)(((int64_t)B * t + 255) / 256) * ((ng + t - 1) / t);
+    return (half ? 15.0 : 14.0) + rounds * (half ? 9.6 : 16.5);
+}
+
 size_t spu_conv_spec_bytes(int N)
 {
     bool half;

@@ -172,25 +172,32 @@ tile_tag_t spu_next_tag()
 }
 
 // ------------------------------------------------------------------ host side
-// Which kernel is quickest: measured times (us, one call) of the three that take short samples, as functions of the sizes.
-//   spu_circ    6 (fp32: 9) + its products at 1.1e15 flop/s          8x205x3584 bf16: 15, 1x512x3584: 16, 4x861x1408: 36
-//   spu_fft16q  11 + 1.3 per million values                          8x256x3584 bf16: 19, 1x512x3584: 17, 16x720x4096: 71
-//   spu_conv    18 + 4.4 per thousand channels, 4096 points each     4x861x1408 bf16: 42, 8x1200x3584: 148
+// Which kernel is quickest: measured times (us, one call) as functions of the sizes; spu_circ: 6 (fp32: 9) and its products at
+// 1.1e15 flop/s (8x205x3584 bf16: 15, 1x512x3584: 16, 4x861x1408: 36), the others beside their launchers.
 static double circ_work_us(int64_t B, int N, int D, luvc_dtype dt) { return (dt == LUVC_F32 ? 12.0 : 6.0) * N * N * (double)D * (double)B / 1.1e9; }
-static double other_us(int64_t B, int N, int D, int sigma)
+static SpuPath long_path(int B, int N, int D, int sigma, double* us)
 {
-    return spu_fft_supported(N, sigma) ? 11.0 + 1.3e-6 * (double)B * N * D : 18.0 + 4.4e-3 * (double)B * D;
+    bool half;
+    const bool conv = spu_conv_rows(N, &half) != 0, fft = spu_fft_supported(N, sigma);
+    const double f = fft ? spu_fft_us(B, N, D, sigma) : 0.0, c = conv ? spu_conv_us(B, N, D) : 0.0;
+    if (fft && (!conv || f <= c)) { *us = f; return SpuPath::Fft; }
+    *us = c;
+    return conv ? SpuPath::Conv : SpuPath::Dense;
 }
 // circ: the call's rows let spu_circ take them (spu_circ_aligned)
 static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, bool circ)
 {
-    bool half;
-    if (circ && N <= kCircMaxN && circ_work_us(B, N, D, dt) + (dt == LUVC_F32 ? 9.0 : 6.0) <= other_us(B, N, D, sigma)) return SpuPath::Circ;
-    if (spu_fft_supported(N, sigma)) return SpuPath::Fft;
-    return spu_conv_rows(N, &half) ? SpuPath::Conv : SpuPath::Dense;
+    double us;
+    const SpuPath other = long_path(B, N, D, sigma, &us);
+    return circ && N <= kCircMaxN && circ_work_us(B, N, D, dt) + (dt == LUVC_F32 ? 9.0 : 6.0) <= us ? SpuPath::Circ : other;
 }
 // in a launch that several runs share, a run adds its products and nothing else
-bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt) { return N <= kCircMaxN && circ_work_us(B, N, D, dt) <= other_us(B, N, D, sigma); }
+bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt)
+{
+    double us;
+    (void)long_path(B, N, D, sigma, &us);
+    return N <= kCircMaxN && circ_work_us(B, N, D, dt) <= us;
+}
 
 SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, bool circ)
 {

@@ -1,15 +1,18 @@
 // Value enhancement (paper Section 3.2, Eq. 3): the values that enter attention are V + log(s), where s is
 // the number of tokens merged into each token; the logarithm is added to every channel of the token's row.
 //
-// One wavefront owns kRows consecutive rows: the first kRows lanes take the fp64 logarithms of their rows'
-// sizes (one pass through the log code for all of them), every row is then streamed with 16-byte accesses,
-// the sum formed in fp64 and rounded once to the storage type.  Bound: HBM, 2 * rows * D * e bytes.
+// A wavefront owns two consecutive rows and goes through their 16-byte pieces as one list, four per lane in flight; the
+// first four are requested before the fp64 logarithms of the two sizes are taken.  The sum is formed in fp64 and rounded
+// once.  Bound: HBM, 2 * rows * D * e bytes; short inputs are bound by the latency of one wavefront, so a wavefront has
+// little to do one after the other (eight rows per wavefront: {VE_US}).
+#include <type_traits>
+
 #include "common.hpp"
 #include "oim.hpp"
 
 namespace luvc {
 
-constexpr int kVeRows = 8;
+constexpr int kVeRows = 2, kVePieces = 4;
 
 template <typename T, bool VECTOR>
 __global__ void __launch_bounds__(256)
@@ -21,26 +24,45 @@ value_enhance(const T* __restrict__ v, const int32_t* __restrict__ sizes, int64_
     const int lane = threadIdx.x & 63;
     const int64_t row0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * kVeRows;
     if (row0 >= rows) return;
-    const int64_t mine = row0 + (lane < kVeRows ? lane : 0);
-    const int s_mine = mine < rows ? sizes[mine] : 1;
-    const double ls_mine = log((double)(s_mine < 1 ? 1 : s_mine));
-    for (int r = 0; r < kVeRows; ++r) {
-        const int64_t row = row0 + r;
-        if (row >= rows) break;
-        const double ls = __shfl(ls_mine, r, kWave);
-        const T* in = v + row * v_stride;
-        T* o = out + row * out_stride;
-        if (VECTOR) {
-            for (int d = lane * V; d < D; d += 64 * V) {
+    const int64_t row1 = row0 + 1 < rows ? row0 + 1 : row0;
+    const int s0 = sizes[row0], s1 = sizes[row1];
+    const int per_row = VECTOR ? D / V : D, total = row1 > row0 ? 2 * per_row : per_row;
+    using piece_t = typename std::conditional<VECTOR, typename tr::vec_t, T>::type;
+    const int width = VECTOR ? V : 1;
+    auto in_at = [&](int i) { return reinterpret_cast<const piece_t*>(i < per_row ? v + row0 * v_stride + (int64_t)i * width : v + row1 * v_stride + (int64_t)(i - per_row) * width); };
+    auto out_at = [&](int i) { return reinterpret_cast<piece_t*>(i < per_row ? out + row0 * out_stride + (int64_t)i * width : out + row1 * out_stride + (int64_t)(i - per_row) * width); };
+    piece_t p[kVePieces];
+    auto fetch = [&](int base) {
+#pragma unroll
+        for (int u = 0; u < kVePieces; ++u) {
+            const int i = base + u * 64 + lane;
+            p[u] = *in_at(i < total ? i : total - 1);
+        }
+    };
+    fetch(0);
+    const double l = log((double)((lane & 1 ? s1 : s0) < 1 ? 1 : (lane & 1 ? s1 : s0)));
+    const double l0 = __shfl(l, 0, kWave), l1 = __shfl(l, 1, kWave);
+    for (int base = 0; base < total; base += 64 * kVePieces) {
+        if (base) fetch(base);
+#pragma unroll
+        for (int u = 0; u < kVePieces; ++u) {
+            const int i = base + u * 64 + lane;
+            if (i >= total) continue;
+            const double ls = i < per_row ? l0 : l1;
+            if constexpr (VECTOR) {
                 float f[V];
-                tr::unpack(*reinterpret_cast<const typename tr::vec_t*>(in + d), f);
+                tr::unpack(p[u], f);
                 T q[V];
 #pragma unroll
-                for (int i = 0; i < V; ++i) tr::store(&q[i], (double)f[i] + ls);
-                *reinterpret_cast<typename tr::vec_t*>(o + d) = *reinterpret_cast<const typename tr::vec_t*>(q);
+                for (int e = 0; e < V; ++e) tr::store(&q[e], (double)f[e] + ls);
+                piece_t o;
+                __builtin_memcpy(&o, q, sizeof(o));
+                *out_at(i) = o;
+            } else {
+                T q;
+                tr::store(&q, (double)tr::load(&p[u]) + ls);
+                *out_at(i) = q;
             }
-        } else {
-            for (int d = lane; d < D; d += 64) tr::store(o + d, (double)tr::load(in + d) + ls);
         }
     }
 }
