@@ -19,32 +19,7 @@
 
 namespace luvc {
 
-namespace {
-
-typedef unsigned int adj_u32x4 __attribute__((__vector_size__(16)));
-
-template <typename T> struct adj_io;
-template <> struct adj_io<bf16_t> {
-    static constexpr int V = 8;
-    __device__ static __forceinline__ double at(const adj_u32x4& v, int e) { return (double)__uint_as_float((e & 1) ? v[e >> 1] & 0xffff0000u : v[e >> 1] << 16); }
-};
-template <> struct adj_io<float> {
-    static constexpr int V = 4;
-    __device__ static __forceinline__ double at(const adj_u32x4& v, int e) { return (double)__uint_as_float(v[e]); }
-};
-
-// 16 bytes per lane of a row of `bytes` bytes; zeros past its end
-__device__ __forceinline__ adj_u32x4 adj_load(__amdgpu_buffer_rsrc_t r, int off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
-template <typename T>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t adj_row(const T* p, int D, bool present)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, present ? D * (int)sizeof(T) : 0, 0x00020000);
-}
-
-}  // namespace
-
 constexpr int kAdjTok = 4;                       // consecutive tokens of a wavefront
-constexpr int kAdjPieces = 3;                    // 16-byte pieces of a token per lane in flight (bf16: 1536 channels)
 
 template <typename T>
 __global__ void __launch_bounds__(1024)
@@ -54,7 +29,7 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
                   LazyGeom g, int32_t* __restrict__ idx_out, int32_t* __restrict__ sizes_out, int32_t* __restrict__ kept_out /* or null */,
                   int32_t* __restrict__ pass_map /* or null */)
 {
-    using io = adj_io<T>;
+    using io = lz_io<T>;
     constexpr int V = io::V;
     __shared__ double nrm2[kLazyMaxLen + 4], dnx[kLazyMaxLen + 4];     // squared norm; product with the next token of the line
     __shared__ double score[64];
@@ -86,19 +61,19 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
 #pragma unroll
         for (int i = 0; i <= kAdjTok; ++i) {
             const int p = p0 + i < len ? p0 + i : len - 1, f = in_flat(p);
-            r[i] = adj_row(row_of<T>(dx, dov, b, idx_in ? idx_in[img + f] : f, g, dD), dD, p0 + i < len);
+            r[i] = lz_row(row_of<T>(dx, dov, b, idx_in ? idx_in[img + f] : f, g, dD), dD, p0 + i < len);
         }
         double s[2 * kAdjTok];
 #pragma unroll
         for (int i = 0; i < 2 * kAdjTok; ++i) s[i] = 0.0;
-        for (int d0 = 0; d0 < dD; d0 += 64 * V * kAdjPieces) {
-            adj_u32x4 t[kAdjTok + 1][kAdjPieces];
+        for (int d0 = 0; d0 < dD; d0 += 64 * V * kLzPieces) {
+            lz_u32x4 t[kAdjTok + 1][kLzPieces];
 #pragma unroll
             for (int i = 0; i <= kAdjTok; ++i)
 #pragma unroll
-                for (int u = 0; u < kAdjPieces; ++u) t[i][u] = adj_load(r[i], (d0 + (u * 64 + lane) * V) * (int)sizeof(T));
+                for (int u = 0; u < kLzPieces; ++u) t[i][u] = lz_load(r[i], (d0 + (u * 64 + lane) * V) * (int)sizeof(T));
 #pragma unroll
-            for (int u = 0; u < kAdjPieces; ++u)
+            for (int u = 0; u < kLzPieces; ++u)
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
                     double a = io::at(t[0][u], e);
@@ -147,12 +122,8 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
     const int sside = lane < n_src ? side[lane] : -1;
     const unsigned long long m_gone = __ballot(sgone), m_right = __ballot(sgone && sside == 1), m_left = __ballot(sgone && sside == 0);
     const unsigned long long from_prev = m_right, from_next = m_left >> 1;       // destinations that take in source 2 k, source 2 k + 2
-    const unsigned long long takes = from_prev | from_next;
-    auto slot = [&](int p) {                     // output slot of the surviving position p: the survivors before it
-        const int k = p >> 1;                    // sources before p: k (+ 1 when p is odd), destinations before p: k
-        const unsigned long long before = (p & 1) ? (2ull << k) - 1ull : (1ull << k) - 1ull;
-        return out_flat(p - __popcll(m_gone & before));
-    };
+    const LazyLine ln = {m_gone, from_prev | from_next};
+    auto slot = [&](int p) { return out_flat(lazy_slot(ln, p)); };
     auto taken = [&](int k) {                    // size of destination 2 k + 1 after the pass
         int S = sz[2 * k + 1];
         if ((from_prev >> k) & 1ull) S += sz[2 * k];
@@ -173,55 +144,23 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
     }
     if (wave == NW - 1 && lane < n_dst) {        // destinations
         const int p = 2 * lane + 1, f = in_flat(p), of = slot(p);
-        idx_out[img_out + of] = ((takes >> lane) & 1ull) ? g.n0 + g.ov_base + line * g.per_line + __popcll(takes & below) : rid[p];
+        idx_out[img_out + of] = ((ln.takes >> lane) & 1ull) ? g.n0 + g.ov_base + line * g.per_line + __popcll(ln.takes & below) : rid[p];
         sizes_out[img_out + of] = taken(lane);
         if (kept_out) kept_out[img_out + of] = kept_in ? kept_in[img + f] : f;
         if (pass_map) pass_map[img + f] = of;
     }
-    // ---- the destinations that take sources in: size-weighted mean in fp64 (destination first, then the sources in
-    // ascending position), rounded once; a wavefront per destination and tensor
-    const int n_abs = __popcll(takes);
+    // ---- the destinations that take sources in, a wavefront per destination and tensor
+    const int n_abs = __popcll(ln.takes);
     for (int kk = wave; kk < (xk ? 2 : 1) * n_abs; kk += NW) {
         const bool on_metric = kk >= n_abs;
         const int at = on_metric ? kk - n_abs : kk;
-        unsigned long long left = takes;
+        unsigned long long left = ln.takes;
         for (int i = 0; i < at; ++i) left &= left - 1;
-        const int k = (int)__builtin_ctzll(left), p = 2 * k + 1;
-        const T* mx = on_metric ? xk : x;
+        const int k = (int)__builtin_ctzll(left);
+        const unsigned long long hits = ((from_prev >> k) & 1ull) << k | (((from_next >> k) & 1ull) << k) << 1;
         T* mov = on_metric ? ovk : ov;
         const int mD = on_metric ? Dk : g.D;
-        const bool fa = (from_prev >> k) & 1ull, fc = (from_next >> k) & 1ull;
-        const __amdgpu_buffer_rsrc_t rp = adj_row(row_of<T>(mx, mov, b, rid[p], g, mD), mD, true),
-                                     ra = adj_row(row_of<T>(mx, mov, b, rid[p - 1], g, mD), mD, fa),
-                                     rc = adj_row(row_of<T>(mx, mov, b, rid[fc ? p + 1 : p], g, mD), mD, fc);
-        T* o = mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD;
-        const double sp = sz[p], sa = fa ? sz[p - 1] : 0, s2 = fc ? sz[p + 1] : 0, S = (sp + sa) + s2, inv = 1.0 / S;
-        for (int d0 = 0; d0 < mD; d0 += 64 * V * kAdjPieces) {
-            adj_u32x4 vp[kAdjPieces], va[kAdjPieces], vc[kAdjPieces];
-#pragma unroll
-            for (int u = 0; u < kAdjPieces; ++u) {
-                const int off = (d0 + (u * 64 + lane) * V) * (int)sizeof(T);
-                vp[u] = adj_load(rp, off);
-                va[u] = adj_load(ra, off);
-                vc[u] = adj_load(rc, off);
-            }
-#pragma unroll
-            for (int u = 0; u < kAdjPieces; ++u) {
-                const int d = d0 + (u * 64 + lane) * V;
-                if (d >= mD) continue;
-                T q[V];
-#pragma unroll
-                for (int e = 0; e < V; ++e) {
-                    double acc = sp * io::at(vp[u], e);
-                    if (fa) acc += sa * io::at(va[u], e);
-                    if (fc) acc += s2 * io::at(vc[u], e);
-                    // acc / S, correctly rounded: the reciprocal is, and one step on the exact remainder corrects the product
-                    const double h = acc * inv, rem = fma(-h, S, acc);
-                    io_traits<T>::store(&q[e], rem == 0.0 ? h : fma(rem, inv, h));       // (a zero keeps its sign)
-                }
-                *reinterpret_cast<adj_u32x4*>(o + d) = *reinterpret_cast<const adj_u32x4*>(q);
-            }
-        }
+        lazy_merge<T>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, hits, mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane);
     }
 }
 

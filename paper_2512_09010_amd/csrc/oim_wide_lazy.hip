@@ -13,20 +13,26 @@
 // oim_wide_line, one workgroup per line (lines of at most 128 tokens).  The decisions are the fp64 decisions of the
 // method, reached in two steps:
 //   1. SCREENING.  The source x destination dot products of the line on the matrix cores in the storage precision
-//      (v_mfma_f32_32x32x16_bf16, or four v_mfma_f32_32x32x2_f32 for fp32 tokens): a 32 x 32 tile at a time, the four
+//      (v_mfma_f32_32x32x16_bf16, or four v_mfma_f32_32x32x2_f32 for fp32 tokens): a 32 x 32 tile at a time, eight
 //      wavefronts split the channels, every token byte is fetched once per tile.  The squared norms are summed in fp64
-//      on the way.  A screened cosine is taken to be within eps = (D + 2) 2^-22 of the fp64 cosine: the products of
+//      on the way.  A screened cosine is taken to be within eps = (D + 4) 2^-22 of the fp64 cosine: the products of
 //      bf16 values are exact in fp32, and D accumulation steps of at most 2^-23 each (relative to the sum of the
-//      magnitudes of the products, which is at most the product of the norms) plus the rounding of fp32 products
-//      stay below half of that; tests/test_gpu_oim_wide.py pins the contraction against fp64 on adversarial rows.
-//   2. EXACT.  A source whose best screened cosine is within 2 eps of the m-th best of the line may be among the m
-//      best of the line, nobody else can; for each such source, the destinations within 2 eps of its best screened
-//      cosine may be its best destination, no other can.  Their dot products are repeated in fp64 (a wavefront per
-//      pair), and the rules of the method - higher cosine wins, ties go to the lower position - are applied to the
-//      fp64 values.  With a merge number of 2 that is a handful of pairs per line instead of 1024.
-//   3. Survivor layout by ballot counts; ids / sizes / anchors / maps of the next grid.
-//   4. Size-weighted mean of every destination that absorbs sources (destination first, then the sources in
-//      ascending position, fp64, one rounding), a wavefront per destination.
+//      magnitudes of the products, which is at most the product of the norms) plus the rounding of fp32 products, of
+//      the reciprocal norms and of two products stay below half of that; tests/test_gpu_oim_wide.py pins the
+//      contraction against fp64 on adversarial rows.
+//   2. EXACT.  A source may be among the m best of the line only if fewer than m screened best cosines exceed its own by
+//      more than 2 eps; for each such contender, the destinations within 2 eps of its best screened cosine may be its
+//      best destination, no other can.  Their dot products are repeated in fp64 (a wavefront per contender, two
+//      destinations at a time), and the rules of the method - higher cosine wins, ties go to the lower position - are
+//      applied to the fp64 values.  Nothing is repeated for a contender with one candidate where there are no more
+//      than m contenders.
+//   3. Layout of the next grid from two 64-bit masks, sources gone and destinations taking sources in, which every
+//      wavefront works out for itself; ids / sizes / anchors / maps of the next grid.
+//   4. Size-weighted mean of every destination that takes sources in, a wavefront per destination.
+// All lines of a grid start together, so what follows the screening is serial time of the launch: no lists or
+// flags are handed through LDS where a ballot does, and each step after the screening is one barrier.
+// Bound: the screening, by the rate at which the tokens arrive (8 x 64 x 64 x 1280 bf16: 84 MB a pass), then latency:
+// {WIDE_US}.
 #include "common.hpp"
 #include "oim.hpp"
 #include "oim_lazy.hpp"
@@ -130,37 +136,43 @@ __device__ __forceinline__ double wave_total64(double v)
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63), __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
-// <a1, c1> and <a2, c2> in fp64 by one wavefront, all fetches of both in flight together
+// <a, c1> and <a, c2> in fp64 by one wavefront, all fetches in flight together
 template <typename T>
-__device__ __forceinline__ void dot64_wave2(const T* a1, const T* c1, const T* a2, const T* c2, int D, int lane, double& d1, double& d2)
+__device__ __forceinline__ void dot64_wave2(const T* a, const T* c1, const T* c2, int D, int lane, double& d1, double& d2)
 {
     constexpr int V = 16 / (int)sizeof(T);
     double acc1 = 0.0, acc2 = 0.0;
-    for (int d0 = 0; d0 < D; d0 += 64 * V * 4) {
-        u32x4 ra1[4], rc1[4], ra2[4], rc2[4];
+    for (int d0 = 0; d0 < D; d0 += 64 * V * 3) {
+        u32x4 ra[3], rc1[3], rc2[3];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < 3; ++u) {
             const int d = d0 + (u * 64 + lane) * V;
-            ra1[u] = piece(a1, D, d, true);
+            ra[u] = piece(a, D, d, true);
             rc1[u] = piece(c1, D, d, true);
-            ra2[u] = piece(a2, D, d, true);
             rc2[u] = piece(c2, D, d, true);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            acc1 = screen<T>::dot(ra1[u], rc1[u], acc1);
-            acc2 = screen<T>::dot(ra2[u], rc2[u], acc2);
+        for (int u = 0; u < 3; ++u) {
+            acc1 = screen<T>::dot(ra[u], rc1[u], acc1);
+            acc2 = screen<T>::dot(ra[u], rc2[u], acc2);
         }
     }
     d1 = wave_total64(acc1);
     d2 = wave_total64(acc2);
 }
 
-__device__ __forceinline__ float quad_max(float v)
+// largest value over groups of eight lanes, in every lane
+__device__ __forceinline__ float oct_max(float v)
 {
     v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true)));    // lane ^ 1
     v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true)));    // lane ^ 2
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true)));   // lane ^ 7
     return v;
+}
+
+__device__ __forceinline__ double lane_f64(double v, int i)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i), __builtin_amdgcn_readlane(__double2loint(v), i));
 }
 
 }  // namespace
@@ -182,9 +194,10 @@ selftest_screen_tile(const T* __restrict__ a, const T* __restrict__ c, int D, fl
     for (int v = 0; v < 16; ++v) out[(8 * (v >> 2) + 4 * kh + (v & 3)) * 32 + r] = acc[v];
 }
 
-constexpr int kLazyLoads = 8;                    // steps of the screening contraction fetched before the first is used
+constexpr int kLazyLoads = 5;                    // steps of the screening contraction in flight
+constexpr int kScreenWaves = 8;                  // wavefronts that split its channels
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric [.., Dk] the decisions are taken on, or null: x */,
               T* ovk /* its overlay */, int Dk, const int32_t* __restrict__ idx_in /* null: identity */,
               const int32_t* __restrict__ sizes_in /* null: ones */, const int32_t* __restrict__ kept_in /* null: identity */,
@@ -192,58 +205,41 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
               int32_t* __restrict__ pass_map /* or null */)
 {
     using sc = screen<T>;
-    using tr = io_traits<T>;
-    constexpr int V = tr::kVec;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int len = g.axis ? g.w : g.h, nlines = g.axis ? g.h : g.w;
     const int n_src = (len + 1) / 2, n_dst = len / 2;
     const int Wo = g.axis ? g.w - g.m : g.w, Ho = g.axis ? g.h : g.h - g.m;
-    double* pn = reinterpret_cast<double*>(smem_raw);    // [4][len] squared norms, the part of each wavefront
-    double* nrm = pn + 4 * len;                          // [len] max(norm, 1e-12)
-    float* P = reinterpret_cast<float*>(nrm + len);      // [4][32 * 32] a tile, the part of each wavefront; later the list of pairs
-    // [n_src][sd] screened dot products, then cosines; later [pairs] fp64 cosines.  Rows are sd = 4 mod 32 floats apart, so
-    // that the four lanes per source of the cosine step fall into different banks
-    float* S = P + 4 * 1024;
+    double* pn = reinterpret_cast<double*>(smem_raw);    // [kScreenWaves][len] squared norms, the part of each wavefront
+    double* nrm = pn + kScreenWaves * len;               // [len] max(norm, 1e-12)
+    double* escore = nrm + len;                          // [64] fp64 cosine of a contender with its best destination
+    float* P = reinterpret_cast<float*>(escore + 64);    // [kScreenWaves][32 * 32] a tile, the part of each wavefront
+    // [n_src][sd] screened dot products, then cosines.  Rows are sd = 4 mod 32 floats apart: lanes on neighbouring sources
+    // fall into different banks
+    float* S = P + kScreenWaves * 1024;
     const int sd = lazy_row_stride(n_dst);
-    float* b32 = S + n_src * max(2 * n_dst, sd);         // [n_src] best screened cosine
-    float* inv32 = b32 + n_src;                          // [len] 1 / nrm
-    int* rid = reinterpret_cast<int*>(inv32 + len);      // [len] row id of the token at position p
+    float* inv32 = S + n_src * sd;                       // [len] 1 / norm
+    float* b32 = inv32 + len;                            // [64] best screened cosine of a source
+    int* rid = reinterpret_cast<int*>(b32 + 64);         // [len] row id of the token at position p
     int* sz = rid + len;                                 // [len] its size
-    int* snew = sz + len;                                // [len] its size after the pass (survivors)
-    int* addsz = snew + len;                             // [len] sizes of the sources a destination takes in
-    int* best = addsz + len;                             // [n_src] position of the best destination, -1: not looked at
-    int* pstart = best + n_src;                          // [n_src] first pair of the source in the list
-    int* pcount = pstart + n_src;                        // [n_src] its number of pairs
-    int* slot_of = pcount + n_src;                       // [len]
-    int* dlist = slot_of + len;                          // [len] destinations that absorb sources, ascending
-    int* tot = dlist + len;                              // [4] counts handed between the wavefronts
-    int* npairs = tot + 4;                               // [1]
-    float* thr = reinterpret_cast<float*>(npairs + 1);   // [1] m-th best screened cosine of the line
-    unsigned char* merged = reinterpret_cast<unsigned char*>(thr + 1);   // [len]
-    unsigned char* absorb = merged + len;                // [len]
+    int* ebest = sz + len;                               // [64] best destination of a contender
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t b = blockIdx.x / nlines;
-    const int line = blockIdx.x % nlines;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), NW = blockDim.x >> 6;
+    const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);       // lines of one image meet in one L2
+    const int64_t b = item / nlines;
+    const int line = item % nlines;
     const int64_t img = b * g.h * g.w, img_out = b * Ho * Wo;
     auto in_flat = [&](int p) -> int { return g.axis ? line * g.w + p : p * g.w + line; };
     auto out_flat = [&](int q) -> int { return g.axis ? line * Wo + q : q * Wo + line; };
-    // eps: bound of |screened cosine - fp64 cosine| (head of this file); both selections use 2 eps
     // the tensor the decisions are taken on
     const T* dx = xk ? xk : x;
     const T* dov = xk ? ovk : ov;
     const int dD = xk ? Dk : g.D;
-    const float tau = 2.f * (float)(dD + 2) * 2.3841858e-7f;
+    const float tau = 2.f * (float)(dD + 4) * 2.3841858e-7f;           // 2 eps
 
     for (int p = tid; p < len; p += blockDim.x) {
         const int f = in_flat(p);
         rid[p] = idx_in ? idx_in[img + f] : f;
         sz[p] = sizes_in ? sizes_in[img + f] : 1;
-        merged[p] = 0;
-    }
-    if (tid == 0) {
-        *thr = -INFINITY;                                // stays there only if the cosines do not order (NaN): then every source is looked at
-        *npairs = 0;
     }
     __syncthreads();
 
@@ -254,263 +250,194 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
         const int r = lane & 31, kh = lane >> 5;
         for (int t = 0; t < tiles_s * tiles_d; ++t) {
             const int ts = t / tiles_d, td = t % tiles_d;
-            const int js = ts * 32 + r, jd = td * 32 + r;
-            const bool has_s = js < n_src, has_d = jd < n_dst;
-            const T* tok_s = row_of<T>(dx, dov, b, has_s ? rid[2 * js] : rid[0], g, dD);
-            const T* tok_d = row_of<T>(dx, dov, b, has_d ? rid[2 * jd + 1] : rid[0], g, dD);
-            f32x16 acc;
+            if (wave < kScreenWaves) {
+                const int js = ts * 32 + r, jd = td * 32 + r;
+                const bool has_s = js < n_src, has_d = jd < n_dst;
+                const T* tok_s = row_of<T>(dx, dov, b, has_s ? rid[2 * js] : rid[0], g, dD);
+                const T* tok_d = row_of<T>(dx, dov, b, has_d ? rid[2 * jd + 1] : rid[0], g, dD);
+                f32x16 acc;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-            double na = 0.0, nc = 0.0;
-            // wavefront w takes steps w, w + 4, ... of KS channels, a lane its half of each; the trip count is the same in
-            // every lane (the matrix instructions want the whole wavefront), pieces past the end of the token are zeros
-            for (int d0 = wave * sc::KS; d0 < dD; d0 += 4 * sc::KS * kLazyLoads) {
+                for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+                double na = 0.0, nc = 0.0;
+                // wavefront w takes steps w, w + kScreenWaves, ... of KS channels, a lane its half of each; the trip count is the
+                // same in every lane (the matrix instructions want the whole wavefront), pieces past the end of the token
+                // are zeros.  kLazyLoads steps stay in flight: a slot is fetched again as soon as it is used up.
+                constexpr int STEP = kScreenWaves * sc::KS;
+                const int first = wave * sc::KS + kh * sc::KL;
                 u32x4 ra[kLazyLoads], rc[kLazyLoads];
 #pragma unroll
                 for (int u = 0; u < kLazyLoads; ++u) {
-                    ra[u] = piece(tok_s, dD, d0 + 4 * sc::KS * u + kh * sc::KL, has_s);
-                    rc[u] = piece(tok_d, dD, d0 + 4 * sc::KS * u + kh * sc::KL, has_d);
+                    ra[u] = piece(tok_s, dD, first + STEP * u, has_s);
+                    rc[u] = piece(tok_d, dD, first + STEP * u, has_d);
+                }
+                for (int d0 = wave * sc::KS; d0 < dD; d0 += STEP * kLazyLoads) {
+#pragma unroll
+                    for (int u = 0; u < kLazyLoads; ++u) {
+                        acc = sc::mac(acc, ra[u], rc[u]);
+                        if (td == 0) na = sc::sq(ra[u], na);
+                        if (ts == 0) nc = sc::sq(rc[u], nc);
+                        const int next = d0 + kh * sc::KL + STEP * (u + kLazyLoads);
+                        ra[u] = piece(tok_s, dD, next, has_s);
+                        rc[u] = piece(tok_d, dD, next, has_d);
+                    }
                 }
 #pragma unroll
-                for (int u = 0; u < kLazyLoads; ++u) {
-                    acc = sc::mac(acc, ra[u], rc[u]);
-                    if (td == 0) na = sc::sq(ra[u], na);
-                    if (ts == 0) nc = sc::sq(rc[u], nc);
+                for (int v = 0; v < 16; ++v) P[wave * 1024 + (8 * (v >> 2) + 4 * kh + (v & 3)) * 32 + r] = acc[v];
+                na += __shfl_xor(na, 32, kWave);                              // the two channel halves of a step
+                nc += __shfl_xor(nc, 32, kWave);
+                if (kh == 0) {
+                    if (td == 0 && has_s) pn[wave * len + 2 * js] = na;
+                    if (ts == 0 && has_d) pn[wave * len + 2 * jd + 1] = nc;
                 }
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) P[wave * 1024 + (8 * (v >> 2) + 4 * kh + (v & 3)) * 32 + r] = acc[v];
-            na += __shfl_xor(na, 32, kWave);                              // the two channel halves of a step
-            nc += __shfl_xor(nc, 32, kWave);
-            if (kh == 0) {
-                if (td == 0 && has_s) pn[wave * len + 2 * js] = na;
-                if (ts == 0 && has_d) pn[wave * len + 2 * jd + 1] = nc;
             }
             __syncthreads();
-            for (int e = tid; e < 1024; e += 256) {
+            for (int e = tid; e < 1024; e += blockDim.x) {
                 const int row = ts * 32 + (e >> 5), col = td * 32 + (e & 31);
-                if (row < n_src && col < n_dst) S[row * sd + col] = ((P[e] + P[1024 + e]) + P[2048 + e]) + P[3072 + e];
+                float sum = P[e];
+#pragma unroll
+                for (int w = 1; w < kScreenWaves; ++w) sum += P[w * 1024 + e];
+                if (row < n_src && col < n_dst) S[row * sd + col] = sum;
             }
-            __syncthreads();
+            if (t + 1 < tiles_s * tiles_d) __syncthreads();
         }
     }
     for (int p = tid; p < len; p += blockDim.x) {
         double v = 1.0;                                  // a line of one token has no products and no decisions
-        if (n_dst > 0) v = sqrt(((pn[p] + pn[len + p]) + pn[2 * len + p]) + pn[3 * len + p]);
+        if (n_dst > 0) {
+            v = pn[p];
+#pragma unroll
+            for (int w = 1; w < kScreenWaves; ++w) v += pn[w * len + p];
+            v = sqrt(v);
+        }
         v = v < 1e-12 ? 1e-12 : v;
         nrm[p] = v;
-        inv32[p] = (float)(1.0 / v);
-        addsz[p] = 0;
-        absorb[p] = 0;
+        inv32[p] = 1.0f / (float)v;
     }
     __syncthreads();
-    // screened cosines (fp32 from here: four more roundings, inside the "+ 2" of eps) and the best of each source:
-    // four lanes per source
-    {
-        const int j = tid >> 2, part = tid & 3;
+    // screened cosines and the best of each source: eight lanes per source.  A cosine that is no number counts as the
+    // lowest, so that exactly m sources leave the line whatever the tokens hold.
+    if (wave < 8) {
+        const int j = tid >> 3, part = tid & 7;
         float mx = -INFINITY;
         if (j < n_src) {
             const int a = 2 * j;
             const float ia = inv32[a];
-            for (int k = part; k < n_dst; k += 4) {
+            for (int k = part; k < n_dst; k += 8) {
                 const int c = 2 * k + 1;
                 const int dist = c > a ? c - a : a - c;
                 float s = -INFINITY;                     // outside the radius: never a candidate
-                if (g.radius <= 0 || dist <= 2 * g.radius - 1) s = (S[j * sd + k] * ia) * inv32[c];
+                if (g.radius <= 0 || dist <= 2 * g.radius - 1) {
+                    s = (S[j * sd + k] * ia) * inv32[c];
+                    s = s >= -2.f ? s : -2.f;
+                }
                 S[j * sd + k] = s;
                 mx = fmaxf(mx, s);
             }
         }
-        mx = quad_max(mx);
+        mx = oct_max(mx);
         if (j < n_src && part == 0) b32[j] = mx;
-    }
-    __syncthreads();
-    // the m-th best of them: the value v with fewer than m values above it and at least m values not below it
-    // (wavefront 0, a source per lane, the values passed around in registers)
-    if (wave == 0 && g.m > 0 && g.m < n_src) {
-        const float v = lane < n_src ? b32[lane] : -INFINITY;
-        int gt = 0, ge = 0;
-        for (int i = 0; i < n_src; ++i) {
-            const float t = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
-            gt += t > v ? 1 : 0;
-            ge += t >= v ? 1 : 0;
-        }
-        if (lane < n_src && gt < g.m && g.m <= ge) *thr = v;
     }
     __syncthreads();
 
     // ------------------------------------------------------------------ 2. exact: fp64 cosines where the screening cannot tell
-    // the (source, destination) pairs to repeat: a wavefront scans every fourth source, its lanes one destination each
-    int* pairs = reinterpret_cast<int*>(P);              // the tile buffer is free: up to n_src * n_dst <= 4096 pairs
-    const unsigned long long below = (1ull << lane) - 1ull;
-    for (int j = wave; j < n_src; j += 4) {
-        const float bj = b32[j];
-        const bool contender = g.m > 0 && bj > -INFINITY && (g.m == n_src || bj >= *thr - tau);
-        int start = 0, cnt = 0;
-        if (contender) {                                 // wave-uniform
-            const unsigned long long cand = __ballot(lane < n_dst && S[j * sd + lane] >= bj - tau);
-            cnt = __popcll(cand);
-            if (lane == 0) start = atomicAdd(npairs, cnt);
-            start = __builtin_amdgcn_readfirstlane(start);
-            if ((cand >> lane) & 1ull) pairs[start + __popcll(cand & below)] = (j << 8) | lane;   // ascending destination
-        }
-        if (lane == 0) { pstart[j] = start; pcount[j] = cnt; }
+    const bool is_src = lane < n_src;
+    const float vbest = is_src ? b32[lane] : -INFINITY;
+    bool contender = is_src && g.m > 0 && vbest > -INFINITY;
+    if (g.m < n_src) {
+        int above = 0;
+        for (int i = 0; i < n_src; ++i) above += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vbest), i)) > vbest + tau ? 1 : 0;
+        contender = contender && above < g.m;
     }
-    __syncthreads();
-    // their fp64 cosines, a wavefront per pair, two pairs in flight; S is dead from here and the values take its place
-    double* E = reinterpret_cast<double*>(S);
+    const unsigned long long con = __ballot(contender), below = (1ull << lane) - 1ull;
+    const int n_con = __popcll(con);
+    const bool ranked = n_con > g.m;                     // some contender stays
     {
-        const int np = *npairs;
-        for (int i = wave; i < np; i += 8) {
-            const bool two = i + 4 < np;
-            const int pr1 = pairs[i], pr2 = pairs[two ? i + 4 : i];
-            const int a1 = 2 * (pr1 >> 8), c1 = 2 * (pr1 & 255) + 1, a2 = 2 * (pr2 >> 8), c2 = 2 * (pr2 & 255) + 1;
-            double d1, d2;
-            dot64_wave2<T>(row_of<T>(dx, dov, b, rid[a1], g, dD), row_of<T>(dx, dov, b, rid[c1], g, dD), row_of<T>(dx, dov, b, rid[a2], g, dD),
-                           row_of<T>(dx, dov, b, rid[c2], g, dD), dD, lane, d1, d2);
-            if (lane == 0) {
-                E[i] = d1 / (nrm[a1] * nrm[c1]);
-                if (two) E[i + 4] = d2 / (nrm[a2] * nrm[c2]);
+        unsigned long long left = con;
+        for (int q = 0; q < n_con; ++q, left &= left - 1) {
+            if (q % NW != wave) continue;
+            const int j = (int)__builtin_ctzll(left), a = 2 * j;
+            const float bj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vbest), j));
+            unsigned long long cand = __ballot(lane < n_dst && S[j * sd + (lane < n_dst ? lane : 0)] >= bj - tau);
+            double bs = -INFINITY;
+            int bk = (int)__builtin_ctzll(cand);
+            if (ranked || (cand & (cand - 1))) {
+                const T* ta = row_of<T>(dx, dov, b, rid[a], g, dD);
+                while (cand) {                           // ascending, two at a time
+                    const int k1 = (int)__builtin_ctzll(cand);
+                    cand &= cand - 1;
+                    const int k2 = cand ? (int)__builtin_ctzll(cand) : k1;
+                    cand &= cand - 1;
+                    double d1, d2;
+                    dot64_wave2<T>(ta, row_of<T>(dx, dov, b, rid[2 * k1 + 1], g, dD), row_of<T>(dx, dov, b, rid[2 * k2 + 1], g, dD), dD, lane, d1, d2);
+                    const double c1 = d1 / (nrm[a] * nrm[2 * k1 + 1]), c2 = d2 / (nrm[a] * nrm[2 * k2 + 1]);
+                    if (c1 > bs) { bs = c1; bk = k1; }
+                    if (c2 > bs) { bs = c2; bk = k2; }
+                }
             }
+            if (lane == 0) { escore[j] = bs; ebest[j] = bk; }
         }
     }
     __syncthreads();
-    // best destination of every source looked at (higher cosine wins, equal cosines keep the lower position), then the m
-    // best sources (higher cosine, equal cosines: lower position): wavefront 0, a source per lane; the sources not looked
-    // at are below all of these
-    if (wave == 0) {
-        const int j = lane;
-        double bs = -INFINITY;
-        int bc = -1;
-        if (j < n_src) {
-            const int st = pstart[j], cn = pcount[j];
-            for (int i = 0; i < cn; ++i) {
-                const double s = E[st + i];
-                const int c = 2 * (pairs[st + i] & 255) + 1;
-                if (bc < 0 || s > bs || (s == bs && c < bc)) { bs = s; bc = c; }
-            }
-            best[j] = bc;
+    // the m best contenders (higher cosine, equal cosines: lower position), a source per lane, in every wavefront
+    const double es = contender ? escore[lane] : 0.0;
+    const int bk = contender ? ebest[lane] : -1;
+    bool leaves = contender;
+    if (ranked) {
+        int rank = 0;
+        for (unsigned long long left = con; left; left &= left - 1) {
+            const int i = (int)__builtin_ctzll(left);
+            const double t = lane_f64(es, i);
+            rank += (t > es || (t == es && i < lane)) ? 1 : 0;
         }
-        bool mg = false;
-        if (g.m == n_src) {
-            mg = bc >= 0;
-        } else if (g.m > 0) {
-            unsigned long long looked = __ballot(bc >= 0);
-            int rank = 0;
-            while (looked) {                             // wave-uniform
-                const int i = (int)__builtin_ctzll(looked);
-                looked &= looked - 1;
-                const double t = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(bs), i), __builtin_amdgcn_readlane(__double2loint(bs), i));
-                rank += (t > bs || (t == bs && i < j)) ? 1 : 0;
-            }
-            mg = bc >= 0 && rank < g.m;
-        }
-        if (mg) {
-            merged[2 * j] = 1;
-            atomicAdd(&addsz[bc], sz[2 * j]);
-            absorb[bc] = 1;
-        }
+        leaves = contender && rank < g.m;
     }
-    __syncthreads();
+    LazyLine ln = {__ballot(leaves), 0ull};
+    for (unsigned long long left = ln.gone; left; left &= left - 1)
+        ln.takes |= 1ull << __builtin_amdgcn_readlane(bk, (int)__builtin_ctzll(left));
 
     // ------------------------------------------------------------------ 3. layout of the next grid
-    // thread p looks at position p (len <= 128: wavefronts 0 and 1); counts before a position by ballot
-    {
-        const int p = tid;
-        const bool alive = p < len && !merged[p];
-        const bool absorbs = alive && absorb[p];         // a destination that takes in sources (destinations are never merged)
-        const int Sz = p < len ? sz[p] + addsz[p] : 0;
-        const unsigned long long bal_a = __ballot(alive), bal_d = __ballot(absorbs);
-        int q = __popcll(bal_a & below), k = __popcll(bal_d & below);
-        if (wave == 0 && lane == 0) { tot[0] = __popcll(bal_a); tot[1] = __popcll(bal_d); }
-        if (wave == 1 && lane == 0) tot[2] = __popcll(bal_d);
-        __syncthreads();
-        if (wave == 1) { q += tot[0]; k += tot[1]; }
-        if (alive) {
-            const int of = out_flat(q), f = in_flat(p);
-            slot_of[p] = of;
-            snew[p] = Sz;
-            if (absorbs) dlist[k] = p;
-            idx_out[img_out + of] = absorbs ? g.n0 + g.ov_base + line * g.per_line + k : rid[p];
-            sizes_out[img_out + of] = Sz;
+    auto slot = [&](int p) { return out_flat(lazy_slot(ln, p)); };
+    if (wave == 0 && is_src) {                           // sources
+        const int p = 2 * lane, f = in_flat(p);
+        if (!leaves) {
+            const int of = slot(p);
+            idx_out[img_out + of] = rid[p];
+            sizes_out[img_out + of] = sz[p];
+            if (kept_out) kept_out[img_out + of] = kept_in ? kept_in[img + f] : f;
+            if (pass_map) pass_map[img + f] = of;
+        } else if (pass_map) {
+            pass_map[img + f] = slot(2 * bk + 1);        // a merged source lands in its destination's slot
+        }
+    }
+    if (wave == NW - 1) {                                // destinations
+        const int ssz = is_src ? sz[2 * lane] : 0;
+        int S1 = lane < n_dst ? sz[2 * lane + 1] : 0;
+        for (unsigned long long left = ln.gone; left; left &= left - 1) {
+            const int i = (int)__builtin_ctzll(left);
+            S1 += __builtin_amdgcn_readlane(bk, i) == lane ? __builtin_amdgcn_readlane(ssz, i) : 0;
+        }
+        if (lane < n_dst) {
+            const int p = 2 * lane + 1, f = in_flat(p), of = slot(p);
+            idx_out[img_out + of] = ((ln.takes >> lane) & 1ull) ? g.n0 + g.ov_base + line * g.per_line + __popcll(ln.takes & below) : rid[p];
+            sizes_out[img_out + of] = S1;
             if (kept_out) kept_out[img_out + of] = kept_in ? kept_in[img + f] : f;
             if (pass_map) pass_map[img + f] = of;
         }
     }
-    __syncthreads();
-    if (pass_map)
-        for (int j = tid; j < n_src; j += blockDim.x)
-            if (merged[2 * j]) pass_map[img + in_flat(2 * j)] = slot_of[best[j]];    // a merged source lands in its destination's slot
 
     // ------------------------------------------------------------------ 4. the merged destinations
-    // the destination's pieces and those of the first two sources are in flight together
     // (features, and the metric too when the decisions were taken on one: it follows its own decisions)
-    const int n_abs = tot[1] + tot[2];
-    for (int kk = wave; kk < (xk ? 2 : 1) * n_abs; kk += 4) {
+    const int n_abs = __popcll(ln.takes);
+    for (int kk = wave; kk < (xk ? 2 : 1) * n_abs; kk += NW) {
         const bool on_metric = kk >= n_abs;
-        const int k = on_metric ? kk - n_abs : kk;
-        const T* mx = on_metric ? xk : x;
+        const int at = on_metric ? kk - n_abs : kk;
+        unsigned long long left = ln.takes;
+        for (int i = 0; i < at; ++i) left &= left - 1;
+        const int k = (int)__builtin_ctzll(left);
         T* mov = on_metric ? ovk : ov;
         const int mD = on_metric ? Dk : g.D;
-        const int c = dlist[k];
-        const T* xp = row_of<T>(mx, mov, b, rid[c], g, mD);
-        T* o = mov + (b * g.cap + g.ov_base + line * g.per_line + k) * mD;
-        const double sp = (double)sz[c], dS = (double)snew[c];
-        const unsigned long long hits = __ballot(lane < n_src && merged[2 * lane] && best[lane] == c);   // n_src <= 64
-        for (int d0 = 0; d0 < mD; d0 += 64 * V * 4) {
-            double acc[4][V];
-            {
-                u32x4 rp[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) rp[u] = piece(xp, mD, d0 + (u * 64 + lane) * V, true);
-                unsigned long long h = hits;
-                bool first = true;
-                do {
-                    const int j1 = h ? (int)__builtin_ctzll(h) : -1;
-                    h &= h - 1;
-                    const int j2 = h ? (int)__builtin_ctzll(h) : -1;
-                    h &= h - 1;
-                    const T* x1 = row_of<T>(mx, mov, b, rid[j1 >= 0 ? 2 * j1 : 0], g, mD);
-                    const T* x2 = row_of<T>(mx, mov, b, rid[j2 >= 0 ? 2 * j2 : 0], g, mD);
-                    u32x4 r1[4], r2[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        r1[u] = piece(x1, mD, d0 + (u * 64 + lane) * V, j1 >= 0);
-                        r2[u] = piece(x2, mD, d0 + (u * 64 + lane) * V, j2 >= 0);
-                    }
-                    const double s1 = j1 >= 0 ? (double)sz[2 * j1] : 0.0, s2 = j2 >= 0 ? (double)sz[2 * j2] : 0.0;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        float f[V];
-                        if (first) {
-                            tr::unpack(*reinterpret_cast<const typename tr::vec_t*>(&rp[u]), f);
-#pragma unroll
-                            for (int i = 0; i < V; ++i) acc[u][i] = sp * (double)f[i];
-                        }
-                        if (j1 >= 0) {
-                            tr::unpack(*reinterpret_cast<const typename tr::vec_t*>(&r1[u]), f);
-#pragma unroll
-                            for (int i = 0; i < V; ++i) acc[u][i] += s1 * (double)f[i];
-                        }
-                        if (j2 >= 0) {
-                            tr::unpack(*reinterpret_cast<const typename tr::vec_t*>(&r2[u]), f);
-#pragma unroll
-                            for (int i = 0; i < V; ++i) acc[u][i] += s2 * (double)f[i];
-                        }
-                    }
-                    first = false;
-                } while (h);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int d = d0 + (u * 64 + lane) * V;
-                if (d >= mD) continue;
-                T r[V];
-#pragma unroll
-                for (int i = 0; i < V; ++i) tr::store(&r[i], acc[u][i] / dS);
-                *reinterpret_cast<typename tr::vec_t*>(o + d) = *reinterpret_cast<const typename tr::vec_t*>(r);
-            }
-        }
+        lazy_merge<T>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, __ballot(leaves && bk == k),
+                      mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane);
     }
 }
 
@@ -605,9 +532,11 @@ static luvc_status run_lazy_pass(const T* x, T* ov, const T* xk, T* ovk, int Dk,
     g.n0 = n0; g.h = h; g.w = w; g.D = D; g.axis = axis; g.m = m; g.radius = radius; g.cap = cap; g.ov_base = ov_base;
     g.per_line = m < n_dst ? m : n_dst;
     const int sd = lazy_row_stride(n_dst);
-    const size_t lds = sizeof(double) * ((size_t)5 * len) + sizeof(float) * ((size_t)n_src * (2 * n_dst > sd ? 2 * n_dst : sd) + 4096 + n_src + len) +
-                       sizeof(int) * ((size_t)6 * len + 3 * n_src + 6) + (size_t)2 * len + 16;
-    LUVC_LAUNCH("oim_wide_line", (oim_wide_line<T>), dim3((unsigned)(B * nlines)), dim3(256), lds, st, x, ov, xk, ovk, Dk, idx_in, sizes_in, kept_in, g,
+    const size_t lds = sizeof(double) * ((size_t)(kScreenWaves + 1) * len + 64) + sizeof(float) * ((size_t)kScreenWaves * 1024 + (size_t)n_src * sd + len + 64) +
+                       sizeof(int) * ((size_t)2 * len + 64);
+    // eight wavefronts; sixteen where so many destinations are merged that eight would take several rounds
+    const int waves = g.per_line * (xk ? 2 : 1) > 8 ? 16 : 8;
+    LUVC_LAUNCH("oim_wide_line", (oim_wide_line<T>), dim3((unsigned)(B * nlines)), dim3(64 * waves), lds, st, x, ov, xk, ovk, Dk, idx_in, sizes_in, kept_in, g,
                 idx_out, sizes_out, kept_out, pass_map);
     return check_launch("oim pass (wide matching, one launch)");
 }
