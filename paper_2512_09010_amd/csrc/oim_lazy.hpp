@@ -71,6 +71,7 @@ __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGe
     const double sp = (double)sz[2 * k + 1];
     for (int d0 = 0; d0 < D; d0 += 64 * V * kLzPieces) {
         double acc[kLzPieces][V], S = sp;
+        const int pieces = (D - d0 + 64 * V - 1) / (64 * V);           // of this block that hold anything, the same in every lane
         unsigned long long h = hits;
         bool first = true;
         do {
@@ -83,20 +84,23 @@ __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGe
             lz_u32x4 vp[kLzPieces], v1[kLzPieces], v2[kLzPieces];
 #pragma unroll
             for (int u = 0; u < kLzPieces; ++u) {
+                if (u >= pieces) continue;
                 const int off = (d0 + (u * 64 + lane) * V) * (int)sizeof(T);
                 if (first) vp[u] = lz_load(rp, off);
                 v1[u] = lz_load(r1, off);
-                v2[u] = lz_load(r2, off);
+                if (j2 >= 0) v2[u] = lz_load(r2, off);
             }
             const double s1 = j1 >= 0 ? (double)sz[2 * j1] : 0.0, s2 = j2 >= 0 ? (double)sz[2 * j2] : 0.0;
 #pragma unroll
-            for (int u = 0; u < kLzPieces; ++u)
+            for (int u = 0; u < kLzPieces; ++u) {
+                if (u >= pieces) continue;
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
                     if (first) acc[u][e] = sp * io::at(vp[u], e);
                     if (j1 >= 0) acc[u][e] += s1 * io::at(v1[u], e);
                     if (j2 >= 0) acc[u][e] += s2 * io::at(v2[u], e);
                 }
+            }
             S = (S + s1) + s2;
             first = false;
         } while (h);

@@ -534,8 +534,9 @@ static luvc_status run_lazy_pass(const T* x, T* ov, const T* xk, T* ovk, int Dk,
     const int sd = lazy_row_stride(n_dst);
     const size_t lds = sizeof(double) * ((size_t)(kScreenWaves + 1) * len + 64) + sizeof(float) * ((size_t)kScreenWaves * 1024 + (size_t)n_src * sd + len + 64) +
                        sizeof(int) * ((size_t)2 * len + 64);
-    // eight wavefronts; sixteen where so many destinations are merged that eight would take several rounds
-    const int waves = g.per_line * (xk ? 2 : 1) > 8 ? 16 : 8;
+    // eight wavefronts; sixteen where so many destinations are merged that eight would take several rounds and a compute
+    // unit has no second line to work on
+    const int waves = g.per_line * (xk ? 2 : 1) > 8 && B * nlines <= 256 ? 16 : 8;
     LUVC_LAUNCH("oim_wide_line", (oim_wide_line<T>), dim3((unsigned)(B * nlines)), dim3(64 * waves), lds, st, x, ov, xk, ovk, Dk, idx_in, sizes_in, kept_in, g,
                 idx_out, sizes_out, kept_out, pass_map);
     return check_launch("oim pass (wide matching, one launch)");
