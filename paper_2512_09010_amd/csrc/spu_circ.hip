@@ -110,7 +110,7 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
 {
     using raw_t = circ_raw<T>;
     constexpr int ROWS = 32 * RT, TERMS = raw_t::TERMS;
-    constexpr int PF = RT == 4 ? 2 : 4;          // steps of 16 tokens in flight
+    constexpr int PF = TERMS == 1 ? (RT == 4 ? 3 : RT == 2 ? 4 : 6) : (RT == 4 ? 2 : RT == 2 ? 3 : 4);      // steps of 16 tokens in flight
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double part[256];
     __shared__ float red[4 * ROWS];
@@ -199,14 +199,21 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
     if (live) {
         const int cp = (8 - (c31 & 7)) & 7;
         const unsigned char* tap = smem + cp * stride + (8 * h + ROWS - c31 - cp) * 2;
+        // the taps of the next tile (of this step, or the first of the next) are read ahead of a tile's products
+        circ_u32x4 next[3];
+        auto read_taps = [&](int k, int t) {
+#pragma unroll
+            for (int e = 0; e < 3; ++e) next[e] = *reinterpret_cast<const circ_u32x4*>(tap + e * 8 * stride + k * 32 - t * 64);
+        };
+        read_taps(0, 0);
         auto step = [&](const raw_t& r, int k) {
             circ_u32x4 xe[TERMS], xo[TERMS];
             r.operands(xe, xo);
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
-                circ_u32x4 pt[3];
-#pragma unroll
-                for (int e = 0; e < 3; ++e) pt[e] = *reinterpret_cast<const circ_u32x4*>(tap + e * 8 * stride + k * 32 - t * 64);
+                const circ_u32x4 pt[3] = {next[0], next[1], next[2]};
+                read_taps(t + 1 < RT ? k : k + 1, t + 1 < RT ? t + 1 : 0);
+                __builtin_amdgcn_sched_barrier(0);
                 // smallest products first
 #pragma unroll
                 for (int sum = 2; sum >= 0; --sum)
@@ -219,15 +226,19 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
                     }
             }
         };
-        for (int k = 0; k < steps; k += PF) {
+        // whole rounds of PF steps without a branch inside: at a join the compiler waits for everything in flight
+        int k = 0;
+        for (; k + PF <= steps; k += PF) {
 #pragma unroll
             for (int u = 0; u < PF; ++u) {
-                if (k + u < steps) {
-                    step(raw[u], k + u);
-                    fetch(raw[u], k + u + PF);
-                }
+                step(raw[u], k + u);
+                fetch(raw[u], k + u + PF);
+                __builtin_amdgcn_sched_barrier(0);       // fetches, and the permutations that wait for them, stay in this order
             }
         }
+#pragma unroll
+        for (int u = 0; u < PF - 1; ++u)
+            if (k + u < steps) step(raw[u], k + u);
     }
     // ---- Eq. 8: over the wavefront's channels (16 rows per lane and tile, two halves of the wavefront), then the four wavefronts
 #pragma unroll

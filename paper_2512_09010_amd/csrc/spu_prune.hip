@@ -175,7 +175,7 @@ spu_gather(const unsigned char* __restrict__ x, const int32_t* __restrict__ kept
 }
 
 // ------------------------------------------------------------------ select + gather in one launch (N <= 4096)
-// Workgroup g of sample b, 256 threads, repeats the selection of the sample on its own (the scores of a sample
+// Workgroup g of sample b repeats the selection of the sample on its own (the scores of a sample
 // are a few KB, and the groups run side by side; samples of different lengths share a launch, the argument lists
 // runs of equal ones), keeps the list of kept tokens in LDS, and then copies
 // its share of the kept rows: row q goes to wavefront q mod (4 G) of the sample.  Group 0 also writes
@@ -185,16 +185,18 @@ spu_gather(const unsigned char* __restrict__ x, const int32_t* __restrict__ kept
 // carry the non-temporal hint (2) and leave less dirty data in L2 for the end of the kernel (measured: -0.3 us)
 constexpr int kPruneLoadAux = 0, kPruneStoreAux = 2;
 typedef unsigned int prune_u32x4 __attribute__((__vector_size__(16)));
-constexpr int kFusedMaxN = 4096, kFusedThreads = 256, kFusedKeys = kFusedMaxN / kFusedThreads;
+// Threads: 256 for samples of up to 1024 tokens, four keys each; longer ones take 1024, so that the selection stays four
+// keys per thread and fewer workgroups repeat it (4 x 4096 tokens, 819 kept: {PRUNE_US}).
+constexpr int kFusedMaxN = 4096, kFusedKeys = 4;
 
 // workgroups of a sample: one kept row per wavefront, up to 256 of them
-__host__ __device__ inline int prune_groups(int n_keep, bool gather)
+__host__ __device__ inline int prune_groups(int n_keep, int waves, bool gather)
 {
-    const int G = gather ? (n_keep + 3) / 4 : 1;
+    const int G = gather ? (n_keep + waves - 1) / waves : 1;
     return G > 256 ? 256 : G;
 }
 
-template <int BYTES>
+template <int BYTES, int kFusedThreads>
 __global__ void __launch_bounds__(kFusedThreads)
 spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ scores, const PruneRuns runs,
                 int64_t row_bytes_in, int64_t row_bytes_out, int32_t* __restrict__ kept_idx, unsigned char* __restrict__ x_out,
@@ -202,7 +204,8 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
 {
     __shared__ int32_t kept[kFusedMaxN];
     __shared__ int hist[4][256];                       // one histogram per digit pass: none has to be cleared in between
-    __shared__ uint32_t wave_tot[4], wave_hi[4], wave_lo[4];
+    constexpr int WAVES = kFusedThreads / 64;
+    __shared__ uint32_t wave_tot[WAVES], wave_hi[WAVES], wave_lo[WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     PruneRun run = runs.run[0];                        // fetched beside the count: one run is the common case
     if (runs.n > 1) {
@@ -211,7 +214,7 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
             if ((int)blockIdx.x >= runs.run[i].wg0) r = i;
         run = runs.run[r];
     }
-    const int N = run.N, n_keep = run.n_keep, G = prune_groups(n_keep, x_out != nullptr);
+    const int N = run.N, n_keep = run.n_keep, G = prune_groups(n_keep, WAVES, x_out != nullptr);
     const int b = ((int)blockIdx.x - run.wg0) / G, g = (int)blockIdx.x - run.wg0 - b * G;
     const int64_t tok_in = run.tok_in + (int64_t)b * N, tok_out = run.tok_out + (int64_t)b * n_keep;
     const float* s = scores + tok_in;
@@ -221,7 +224,7 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
     uint32_t key[kFusedKeys];
 #pragma unroll
     for (int i = 0; i < kFusedKeys; ++i) key[i] = (i < K && n0 + i < N) ? score_key(s[n0 + i]) : 0u;
-    hist[0][tid] = 0; hist[1][tid] = 0; hist[2][tid] = 0; hist[3][tid] = 0;
+    for (int i = tid; i < 4 * 256; i += kFusedThreads) hist[i >> 8][i & 255] = 0;
     // Largest and smallest key of the sample: the bits above the highest one in which they differ are common to all
     // keys and need no digit pass (scores of one sample share sign and most of the exponent, so the first of four
     // 8-bit passes would pile every key onto one or two counters - same-address LDS atomics, one after the other).
@@ -234,7 +237,7 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
     if (lane == 0) { wave_hi[wave] = hi; wave_lo[wave] = lo; }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < 4; ++w) { hi = wave_hi[w] > hi ? wave_hi[w] : hi; lo = wave_lo[w] < lo ? wave_lo[w] : lo; }
+    for (int w = 0; w < WAVES; ++w) { hi = wave_hi[w] > hi ? wave_hi[w] : hi; lo = wave_lo[w] < lo ? wave_lo[w] : lo; }
     const int nb = 32 - __clz((int)(hi ^ lo));         // the keys differ in their low nb bits only (0: all equal)
 
     // MSD radix select on those bits, 8 at a time (the last pass takes what is left).  Every wavefront scans the
@@ -242,7 +245,8 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
     // handed from wavefront to wavefront.
     uint32_t prefix = nb >= 32 ? 0u : (hi >> nb) << nb, mask = nb >= 32 ? 0u : ~((1u << nb) - 1u);
     int remaining = n_keep;                            // still to pick among keys matching the prefix
-    for (int top = nb, pass = 0; top > 0; top -= 8, ++pass) {
+    bool whole = false;                                // ... which is all of them: no further digit matters
+    for (int top = nb, pass = 0; top > 0 && !whole; top -= 8, ++pass) {
         const int shift = top > 8 ? top - 8 : 0, width = top - shift;
         const uint32_t dmask = (1u << width) - 1u;
         int* h_pass = hist[pass];
@@ -256,11 +260,11 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
         for (int j = 0; j < 4; ++j) { h[j] = h_pass[255 - 4 * lane - j]; sum += h[j]; }
         const int incl = (int)wave_scan_incl((uint32_t)sum);
         int above = incl - sum;                        // tokens with a larger digit
-        int digit = 0, left = 0;
+        int digit = 0, left = 0, in_digit = 0;
         bool found = false;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if (above < remaining && remaining <= above + h[j]) { digit = 255 - 4 * lane - j; left = remaining - above; found = true; }
+            if (above < remaining && remaining <= above + h[j]) { digit = 255 - 4 * lane - j; left = remaining - above; in_digit = h[j]; found = true; }
             above += h[j];
         }
         const unsigned long long who = __ballot(found);
@@ -268,18 +272,21 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
             const int src = (int)__builtin_ctzll(who);
             digit = __builtin_amdgcn_readlane(digit, src);
             remaining = __builtin_amdgcn_readlane(left, src);
+            whole = remaining == __builtin_amdgcn_readlane(in_digit, src);
         }
         prefix |= (uint32_t)digit << shift;
         mask |= dmask << shift;
     }
-    const uint32_t T = prefix;                         // key of the n_keep-th largest score
-    const int take_eq = remaining;                     // tokens with key == T that are kept (lowest indices)
+    // Kept: the keys whose bits under the mask exceed the prefix, and the first `remaining` of those that equal it - once every
+    // bit is under the mask, the n_keep-th largest key and the lowest indices among its equals.
+    const uint32_t T = prefix;
+    const int take_eq = remaining;
 
     // one scan for both counts: tokens above T in the low half, tokens equal to T in the high half
     uint32_t cnt = 0;
 #pragma unroll
     for (int i = 0; i < kFusedKeys; ++i)
-        if (i < K && n0 + i < N) cnt += (key[i] > T ? 1u : 0u) + (key[i] == T ? 0x10000u : 0u);
+        if (i < K && n0 + i < N) cnt += ((key[i] & mask) > T ? 1u : 0u) + ((key[i] & mask) == T ? 0x10000u : 0u);
     const uint32_t incl = wave_scan_incl(cnt);
     if (lane == 63) wave_tot[wave] = incl;
     __syncthreads();
@@ -290,8 +297,8 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
 #pragma unroll
     for (int i = 0; i < kFusedKeys; ++i) {
         if (i < K && n0 + i < N) {
-            const bool eq = key[i] == T;
-            if (key[i] > T || (eq && eq_rank < take_eq)) {
+            const bool eq = (key[i] & mask) == T;
+            if ((key[i] & mask) > T || (eq && eq_rank < take_eq)) {
                 if (pos < n_keep) kept[pos] = n0 + i;
                 ++pos;
             }
@@ -307,7 +314,7 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
                 origin_out[tok_out + q] = origin_in ? origin_in[tok_in + kept[q]] : kept[q];
     }
     if (!x_out) return;
-    for (int q = g * 4 + wave; q < n_keep; q += G * 4) {
+    for (int q = g * WAVES + wave; q < n_keep; q += G * WAVES) {
         int src = kept[q];
         src = src < 0 ? 0 : (src >= N ? N - 1 : src);  // in bounds whatever the scores held
         const unsigned char* in = x + (tok_in + src) * row_bytes_in;
@@ -361,6 +368,8 @@ luvc_status spu_prune_run(const void* x, const float* scores, int D, int64_t row
     const bool v16 = x_out && rin % 16 == 0 && rout % 16 == 0 && ((uintptr_t)x % 16 == 0) && ((uintptr_t)x_out % 16 == 0);
     int64_t wgs = 0;
     int fused = 0;
+    bool wide = false;
+    for (int i = 0; i < runs.n; ++i) wide = wide || (runs.run[i].N > 256 * kFusedKeys && runs.run[i].N <= kFusedMaxN);
     for (int i = 0; i < runs.n; ++i) {
         const PruneRun r = runs.run[i];
         if (r.N > kFusedMaxN) {                            // the list of kept tokens does not fit in LDS
@@ -372,18 +381,20 @@ luvc_status spu_prune_run(const void* x, const float* scores, int D, int64_t row
         }
         runs.run[fused] = r;
         runs.run[fused].wg0 = (int)wgs;
-        wgs += (int64_t)r.count * prune_groups(r.n_keep, x_out != nullptr);
+        wgs += (int64_t)r.count * prune_groups(r.n_keep, wide ? 16 : 4, x_out != nullptr);
         ++fused;
     }
     if (fused == 0) return LUVC_OK;
     if (wgs >= ((int64_t)1 << 31)) { set_error("too many kept tokens in one call"); return LUVC_ERR_UNSUPPORTED; }
     runs.n = fused;
-#define LUVC_PRUNE(BYTES) LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<BYTES>), dim3((unsigned)wgs), dim3(kFusedThreads), 0, st, (const unsigned char*)x, scores, runs, \
-                                      rin, rout, kept_idx, (unsigned char*)x_out, origin_in, origin_out)
+#define LUVC_PRUNE_T(BYTES, THREADS) LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<BYTES, THREADS>), dim3((unsigned)wgs), dim3(THREADS), 0, st, (const unsigned char*)x, \
+                                                 scores, runs, rin, rout, kept_idx, (unsigned char*)x_out, origin_in, origin_out)
+#define LUVC_PRUNE(BYTES) do { if (wide) LUVC_PRUNE_T(BYTES, 1024); else LUVC_PRUNE_T(BYTES, 256); } while (0)
     if (v16 || !x_out) LUVC_PRUNE(16);
     else if (es == 4)  LUVC_PRUNE(4);
     else               LUVC_PRUNE(2);
 #undef LUVC_PRUNE
+#undef LUVC_PRUNE_T
     return check_launch("spu prune");
 }
 
