@@ -3,6 +3,10 @@
 Argument marshalling only: every step of OIM and SPU runs in the HIP kernels.  PyTorch is used
 for device memory (tensors own the buffers) and for the current stream handle.  There is no
 CPU fallback: if the library is missing or cannot be loaded, importing callers get an error.
+
+The calls that enqueue work go through ``_luvc_call`` (csrc/pycall.c), not ctypes, and ask for a workspace size only where
+they allocate one: on small inputs a call is bound by what the host does before the launch (one 24x24 image through merge, score
+and prune: {HOST_US}).
 """
 from __future__ import annotations
 
@@ -107,6 +111,38 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+class _Native:
+    """What a call needs at hand: torch, the caller, the addresses of the entry points."""
+
+    def __init__(self):
+        import torch
+        L = lib()
+        try:
+            from . import _luvc_call
+        except ImportError as e:
+            raise FileNotFoundError("_luvc_call.so is not built; run `python -m paper_2512_09010_amd.build`") from e
+        self.torch, self.call = torch, _luvc_call.call
+        self.code = {torch.float32: LUVC_F32, torch.bfloat16: LUVC_BF16}
+        self.i32, self.f32 = torch.int32, torch.float32
+        self.raw_stream, self.device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+        for name in ("luvc_oim_merge", "luvc_oim_merge_wide", "luvc_oim_merge_keyed", "luvc_value_enhance", "luvc_spu_score", "luvc_spu_score_static",
+                     "luvc_spu_prune", "luvc_spu_stage", "luvc_oim_merge_ragged", "luvc_spu_stage_ragged"):
+            setattr(self, name, ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
+
+    def stream(self, stream) -> int:
+        return self.raw_stream(self.device()) if stream is None else int(stream.cuda_stream)
+
+
+_native_state = None
+
+
+def _native() -> _Native:
+    global _native_state
+    if _native_state is None:
+        _native_state = _Native()
+    return _native_state
+
+
 def last_error() -> str:
     return lib().luvc_last_error().decode()
 
@@ -123,23 +159,43 @@ def _passes(passes: Sequence[Tuple[int, int]]):
     return arr
 
 
+class _Bounded(dict):
+    """Marshalled argument lists by what they were made from; emptied when full."""
+
+    def keep(self, key, value, most=128):
+        if len(self) >= most:
+            self.clear()
+        self[key] = value
+        return value
+
+
+_schedules = _Bounded()
+
+
+def _schedule(passes):
+    """(ctypes array, its address, length) of a schedule."""
+    try:
+        key = tuple(passes)
+        hit = _schedules.get(key)
+    except TypeError:                                   # passes that do not hash: lists, arrays
+        key, hit = None, None
+    if hit is None:
+        arr = _passes(passes)
+        hit = (arr, ctypes.addressof(arr), len(passes))
+        if key is not None:
+            _schedules.keep(key, hit)
+    return hit
+
+
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.float32:
-        return LUVC_F32
-    if t.dtype == torch.bfloat16:
-        return LUVC_BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
-
-
-def _stream(stream) -> int:
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    code = _native().code.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _ptr(t) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def luvc_version() -> str:
@@ -170,30 +226,38 @@ def out_grid(H: int, W: int, passes) -> Tuple[int, int]:
     return H, W
 
 
+def _merge_outputs(t, x, Ho, Wo, want_maps):
+    B, H, W, D = x.shape
+    Ho, Wo = max(Ho, 0), max(Wo, 0)
+    i32 = dict(dtype=t.int32, device=x.device)
+    return dict(x=t.empty((B, Ho, Wo, D), dtype=x.dtype, device=x.device), sizes=t.empty((B, Ho, Wo), **i32),
+                merged_map=t.empty((B, H * W), **i32) if want_maps else None, kept_map=t.empty((B, Ho * Wo), **i32) if want_maps else None)
+
+
+def _map_ptrs(out):
+    m, k = out.get("merged_map"), out.get("kept_map")
+    return None if m is None else m.data_ptr(), None if k is None else k.data_ptr()
+
+
 def luvc_oim_merge(x, passes, sizes=None, target_tokens: int = 0, want_maps: bool = True, workspace=None, stream=None,
                    out=None):
     """x: CUDA tensor [B,H,W,D] (fp32 or bf16, contiguous).  Returns dict(x, sizes, merged_map, kept_map)."""
-    import torch
+    nat = _native()
     assert x.is_cuda and x.is_contiguous() and x.dim() == 4
     B, H, W, D = x.shape
     code = _dtype_code(x)
-    parr = _passes(passes)
-    Ho, Wo = out_grid(H, W, passes)
-    need = lib().luvc_oim_workspace_bytes(B, H, W, D, code, parr, len(passes))
+    arr, addr, n = _schedule(passes)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
+        need = lib().luvc_oim_workspace_bytes(B, H, W, D, code, arr, n)
+        workspace = nat.torch.empty(max(need, 256), dtype=nat.torch.uint8, device=x.device)
     if out is None:
-        out = dict(
-            x=torch.empty((B, max(Ho, 0), max(Wo, 0), D), dtype=x.dtype, device=x.device),
-            sizes=torch.empty((B, max(Ho, 0), max(Wo, 0)), dtype=torch.int32, device=x.device),
-            merged_map=torch.empty((B, H * W), dtype=torch.int32, device=x.device) if want_maps else None,
-            kept_map=torch.empty((B, max(Ho, 0) * max(Wo, 0)), dtype=torch.int32, device=x.device) if want_maps else None,
-        )
+        out = _merge_outputs(nat.torch, x, *out_grid(H, W, passes), want_maps)
     if sizes is not None:
-        assert sizes.is_cuda and sizes.dtype == torch.int32 and sizes.is_contiguous() and sizes.numel() == B * H * W
-    _check(lib().luvc_oim_merge(_ptr(x), _ptr(sizes), B, H, W, D, code, parr, len(passes), int(target_tokens),
-                                _ptr(out["x"]), _ptr(out["sizes"]), _ptr(out.get("merged_map")), _ptr(out.get("kept_map")),
-                                _ptr(workspace), workspace.numel(), _stream(stream)))
+        assert sizes.is_cuda and sizes.dtype == nat.i32 and sizes.is_contiguous() and sizes.numel() == B * H * W
+        sizes = sizes.data_ptr()
+    merged, kept = _map_ptrs(out)
+    _check(nat.call(nat.luvc_oim_merge, x.data_ptr(), sizes, B, H, W, D, code, addr, n, int(target_tokens),
+                    out["x"].data_ptr(), out["sizes"].data_ptr(), merged, kept, workspace.data_ptr(), workspace.numel(), nat.stream(stream)))
     return out
 
 
@@ -204,27 +268,22 @@ def luvc_oim_wide_workspace_bytes(B, H, W, D, dtype_code, passes, radius) -> int
 def luvc_oim_merge_wide(x, passes, radius: int, sizes=None, target_tokens: int = 0, want_maps: bool = True, workspace=None,
                         stream=None, out=None):
     """As luvc_oim_merge with candidates within `radius` (0 = the whole line).  Returns dict(x, sizes, merged_map, kept_map)."""
-    import torch
+    nat = _native()
     assert x.is_cuda and x.is_contiguous() and x.dim() == 4
     B, H, W, D = x.shape
     code = _dtype_code(x)
-    parr = _passes(passes)
-    Ho, Wo = out_grid(H, W, passes)
-    need = lib().luvc_oim_wide_workspace_bytes(B, H, W, D, code, parr, len(passes), int(radius))
+    arr, addr, n = _schedule(passes)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
+        need = lib().luvc_oim_wide_workspace_bytes(B, H, W, D, code, arr, n, int(radius))
+        workspace = nat.torch.empty(max(need, 256), dtype=nat.torch.uint8, device=x.device)
     if out is None:
-        out = dict(
-            x=torch.empty((B, max(Ho, 0), max(Wo, 0), D), dtype=x.dtype, device=x.device),
-            sizes=torch.empty((B, max(Ho, 0), max(Wo, 0)), dtype=torch.int32, device=x.device),
-            merged_map=torch.empty((B, H * W), dtype=torch.int32, device=x.device) if want_maps else None,
-            kept_map=torch.empty((B, max(Ho, 0) * max(Wo, 0)), dtype=torch.int32, device=x.device) if want_maps else None,
-        )
+        out = _merge_outputs(nat.torch, x, *out_grid(H, W, passes), want_maps)
     if sizes is not None:
-        assert sizes.is_cuda and sizes.dtype == torch.int32 and sizes.is_contiguous() and sizes.numel() == B * H * W
-    _check(lib().luvc_oim_merge_wide(_ptr(x), _ptr(sizes), B, H, W, D, code, parr, len(passes), int(radius), int(target_tokens),
-                                     _ptr(out["x"]), _ptr(out["sizes"]), _ptr(out.get("merged_map")), _ptr(out.get("kept_map")),
-                                     _ptr(workspace), workspace.numel(), _stream(stream)))
+        assert sizes.is_cuda and sizes.dtype == nat.i32 and sizes.is_contiguous() and sizes.numel() == B * H * W
+        sizes = sizes.data_ptr()
+    merged, kept = _map_ptrs(out)
+    _check(nat.call(nat.luvc_oim_merge_wide, x.data_ptr(), sizes, B, H, W, D, code, addr, n, int(radius), int(target_tokens),
+                    out["x"].data_ptr(), out["sizes"].data_ptr(), merged, kept, workspace.data_ptr(), workspace.numel(), nat.stream(stream)))
     return out
 
 
@@ -235,44 +294,40 @@ def luvc_oim_keyed_workspace_bytes(B, H, W, D, Dm, dtype_code, passes, radius) -
 def luvc_oim_merge_keyed(x, metric, passes, radius: int = 1, sizes=None, target_tokens: int = 0, want_maps: bool = True,
                          want_metric: bool = True, workspace=None, stream=None, out=None):
     """Decisions on metric [B,H,W,Dm], merge applied to x [B,H,W,D].  Returns dict(x, metric, sizes, merged_map, kept_map)."""
-    import torch
+    nat = _native()
     assert x.is_cuda and x.is_contiguous() and x.dim() == 4 and metric.is_cuda and metric.is_contiguous() and metric.dim() == 4
     assert metric.shape[:3] == x.shape[:3] and metric.dtype == x.dtype
     B, H, W, D = x.shape
     Dm = metric.shape[3]
     code = _dtype_code(x)
-    parr = _passes(passes)
-    Ho, Wo = out_grid(H, W, passes)
-    need = lib().luvc_oim_keyed_workspace_bytes(B, H, W, D, Dm, code, parr, len(passes), int(radius))
+    arr, addr, n = _schedule(passes)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
+        need = lib().luvc_oim_keyed_workspace_bytes(B, H, W, D, Dm, code, arr, n, int(radius))
+        workspace = nat.torch.empty(max(need, 256), dtype=nat.torch.uint8, device=x.device)
     if out is None:
-        out = dict(
-            x=torch.empty((B, max(Ho, 0), max(Wo, 0), D), dtype=x.dtype, device=x.device),
-            metric=torch.empty((B, max(Ho, 0), max(Wo, 0), Dm), dtype=x.dtype, device=x.device) if want_metric else None,
-            sizes=torch.empty((B, max(Ho, 0), max(Wo, 0)), dtype=torch.int32, device=x.device),
-            merged_map=torch.empty((B, H * W), dtype=torch.int32, device=x.device) if want_maps else None,
-            kept_map=torch.empty((B, max(Ho, 0) * max(Wo, 0)), dtype=torch.int32, device=x.device) if want_maps else None,
-        )
+        Ho, Wo = out_grid(H, W, passes)
+        out = _merge_outputs(nat.torch, x, Ho, Wo, want_maps)
+        out["metric"] = nat.torch.empty((B, max(Ho, 0), max(Wo, 0), Dm), dtype=x.dtype, device=x.device) if want_metric else None
     if sizes is not None:
-        assert sizes.is_cuda and sizes.dtype == torch.int32 and sizes.is_contiguous() and sizes.numel() == B * H * W
-    _check(lib().luvc_oim_merge_keyed(_ptr(x), _ptr(metric), _ptr(sizes), B, H, W, D, Dm, code, parr, len(passes), int(radius),
-                                      int(target_tokens), _ptr(out["x"]), _ptr(out.get("metric")), _ptr(out["sizes"]),
-                                      _ptr(out.get("merged_map")), _ptr(out.get("kept_map")),
-                                      _ptr(workspace), workspace.numel(), _stream(stream)))
+        assert sizes.is_cuda and sizes.dtype == nat.i32 and sizes.is_contiguous() and sizes.numel() == B * H * W
+        sizes = sizes.data_ptr()
+    merged, kept = _map_ptrs(out)
+    _check(nat.call(nat.luvc_oim_merge_keyed, x.data_ptr(), metric.data_ptr(), sizes, B, H, W, D, Dm, code, addr, n, int(radius),
+                    int(target_tokens), out["x"].data_ptr(), _ptr(out.get("metric")), out["sizes"].data_ptr(), merged, kept,
+                    workspace.data_ptr(), workspace.numel(), nat.stream(stream)))
     return out
 
 
 def luvc_value_enhance(v, sizes, stream=None, out=None):
     """v: CUDA tensor [..., D] (last dim contiguous, rows evenly strided), sizes int32 [...]: returns v + log(sizes)."""
-    import torch
-    assert v.is_cuda and v.stride(-1) == 1 and sizes.is_cuda and sizes.dtype == torch.int32 and sizes.is_contiguous()
+    nat = _native()
+    assert v.is_cuda and v.stride(-1) == 1 and sizes.is_cuda and sizes.dtype == nat.i32 and sizes.is_contiguous()
     D = v.shape[-1]
     rows = sizes.numel()
     assert v.numel() == rows * D and v.is_contiguous()
     if out is None:
-        out = torch.empty_like(v)
-    _check(lib().luvc_value_enhance(_ptr(v), _ptr(sizes), rows, D, D, _dtype_code(v), _ptr(out), D, _stream(stream)))
+        out = nat.torch.empty_like(v)
+    _check(nat.call(nat.luvc_value_enhance, v.data_ptr(), sizes.data_ptr(), rows, D, D, _dtype_code(v), out.data_ptr(), D, nat.stream(stream)))
     return out
 
 
@@ -282,17 +337,18 @@ def luvc_spu_workspace_bytes(B, N, D, dtype_code, sigma) -> int:
 
 def luvc_spu_score(x, sigma: int, use_hamming: bool = True, workspace=None, stream=None, out=None):
     """x: CUDA tensor [B,N,D] (last dim contiguous; token stride may exceed D).  Returns scores [B,N] fp32."""
-    import torch
-    assert x.is_cuda and x.dim() == 3 and x.stride(2) == 1 and x.stride(0) == x.shape[1] * x.stride(1)
+    nat = _native()
     B, N, D = x.shape
+    sb, sn, sd = x.stride()
+    assert x.is_cuda and sd == 1 and sb == N * sn
     code = _dtype_code(x)
-    need = lib().luvc_spu_workspace_bytes(B, N, D, code, int(sigma))
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
+        need = lib().luvc_spu_workspace_bytes(B, N, D, code, int(sigma))
+        workspace = nat.torch.empty(max(need, 256), dtype=nat.torch.uint8, device=x.device)
     if out is None:
-        out = torch.empty((B, N), dtype=torch.float32, device=x.device)
-    _check(lib().luvc_spu_score(_ptr(x), B, N, D, x.stride(1), code, int(sigma), int(bool(use_hamming)), _ptr(out),
-                                _ptr(workspace), workspace.numel(), _stream(stream)))
+        out = nat.torch.empty((B, N), dtype=nat.f32, device=x.device)
+    _check(nat.call(nat.luvc_spu_score, x.data_ptr(), B, N, D, sn, code, int(sigma), int(bool(use_hamming)), out.data_ptr(),
+                    workspace.data_ptr(), workspace.numel(), nat.stream(stream)))
     return out
 
 
@@ -301,30 +357,30 @@ SPU_STATIC_SCRATCH_BYTES = 8 << 20
 
 def luvc_spu_score_static(x, sigma: int, use_hamming: bool = True, stream=None, out=None):
     """luvc_spu_score on the library's static scratch (no workspace; pass `out` to keep the call free of allocations)."""
-    import torch
+    nat = _native()
     assert x.is_cuda and x.dim() == 3 and x.stride(2) == 1 and x.stride(0) == x.shape[1] * x.stride(1)
     B, N, D = x.shape
     if out is None:
-        out = torch.empty((B, N), dtype=torch.float32, device=x.device)
-    _check(lib().luvc_spu_score_static(_ptr(x), B, N, D, x.stride(1), _dtype_code(x), int(sigma), int(bool(use_hamming)),
-                                       _ptr(out), _stream(stream)))
+        out = nat.torch.empty((B, N), dtype=nat.f32, device=x.device)
+    _check(nat.call(nat.luvc_spu_score_static, x.data_ptr(), B, N, D, x.stride(1), _dtype_code(x), int(sigma), int(bool(use_hamming)),
+                    out.data_ptr(), nat.stream(stream)))
     return out
 
 
 def luvc_spu_prune(x, scores, n_keep: int, gather: bool = True, stream=None, out=None):
     """Returns dict(kept_idx [B,n_keep] int32 ascending, x [B,n_keep,D] or None)."""
-    import torch
-    assert scores.is_cuda and scores.dtype == torch.float32 and scores.is_contiguous() and scores.dim() == 2
+    nat = _native()
+    assert scores.is_cuda and scores.dtype == nat.f32 and scores.is_contiguous() and scores.dim() == 2
     B, N = scores.shape
     D, stride, code, xp = 1, 1, LUVC_F32, None
     if x is not None:
         assert x.is_cuda and x.dim() == 3 and x.stride(2) == 1 and x.shape[:2] == scores.shape
-        D, stride, code, xp = x.shape[2], x.stride(1), _dtype_code(x), _ptr(x)
+        D, stride, code, xp = x.shape[2], x.stride(1), _dtype_code(x), x.data_ptr()
     if out is None:
-        out = dict(kept_idx=torch.empty((B, max(n_keep, 0)), dtype=torch.int32, device=scores.device),
-                   x=torch.empty((B, max(n_keep, 0), D), dtype=x.dtype, device=x.device) if (gather and x is not None) else None)
-    _check(lib().luvc_spu_prune(xp, _ptr(scores), B, N, D, stride, code, int(n_keep), _ptr(out["kept_idx"]),
-                                _ptr(out.get("x")), None, 0, _stream(stream)))
+        out = dict(kept_idx=nat.torch.empty((B, max(n_keep, 0)), dtype=nat.i32, device=scores.device),
+                   x=nat.torch.empty((B, max(n_keep, 0), D), dtype=x.dtype, device=x.device) if (gather and x is not None) else None)
+    _check(nat.call(nat.luvc_spu_prune, xp, scores.data_ptr(), B, N, D, stride, code, int(n_keep), out["kept_idx"].data_ptr(),
+                    _ptr(out.get("x")), None, 0, nat.stream(stream)))
     return out
 
 
@@ -341,24 +397,26 @@ def luvc_spu_stage(x, sigma: int, n_keep: int, use_hamming: bool = True, origin=
                    workspace=None, stream=None, out=None):
     """One cascade stage on x [B,N,D].  Returns dict(scores [B,N] fp32, kept_idx, origin [B,n_keep] int32,
     x [B,n_keep,D] or None); with n_keep = 0 nothing is launched and the tensors are empty."""
-    import torch
-    assert x.is_cuda and x.dim() == 3 and x.stride(2) == 1 and x.stride(0) == x.shape[1] * x.stride(1)
+    nat = _native()
     B, N, D = x.shape
+    sb, sn, sd = x.stride()
+    assert x.is_cuda and sd == 1 and sb == N * sn
     code = _dtype_code(x)
     if origin is not None:
-        assert origin.is_cuda and origin.dtype == torch.int32 and origin.is_contiguous() and tuple(origin.shape) == (B, N)
+        assert origin.is_cuda and origin.dtype == nat.i32 and origin.is_contiguous() and tuple(origin.shape) == (B, N)
+        origin = origin.data_ptr()
     k = max(int(n_keep), 0)
     if workspace is None:
         need = lib().luvc_spu_workspace_bytes(B, N, D, code, int(sigma)) if k else 0
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
+        workspace = nat.torch.empty(max(need, 256), dtype=nat.torch.uint8, device=x.device)
     if out is None:
-        out = dict(scores=torch.empty((B, N), dtype=torch.float32, device=x.device),
-                   kept_idx=torch.empty((B, k), dtype=torch.int32, device=x.device),
-                   origin=torch.empty((B, k), dtype=torch.int32, device=x.device),
-                   x=torch.empty((B, k, D), dtype=x.dtype, device=x.device) if gather else None)
-    _check(lib().luvc_spu_stage(_ptr(x), B, N, D, x.stride(1), code, int(sigma), int(bool(use_hamming)), int(n_keep),
-                                _ptr(origin), _ptr(out["scores"]), _ptr(out["kept_idx"]), _ptr(out["origin"]),
-                                _ptr(out.get("x")), _ptr(workspace), workspace.numel(), _stream(stream)))
+        out = dict(scores=nat.torch.empty((B, N), dtype=nat.f32, device=x.device),
+                   kept_idx=nat.torch.empty((B, k), dtype=nat.i32, device=x.device),
+                   origin=nat.torch.empty((B, k), dtype=nat.i32, device=x.device),
+                   x=nat.torch.empty((B, k, D), dtype=x.dtype, device=x.device) if gather else None)
+    _check(nat.call(nat.luvc_spu_stage, x.data_ptr(), B, N, D, sn, code, int(sigma), int(bool(use_hamming)), int(n_keep),
+                    origin, out["scores"].data_ptr(), out["kept_idx"].data_ptr(), out["origin"].data_ptr(),
+                    _ptr(out.get("x")), workspace.data_ptr(), workspace.numel(), nat.stream(stream)))
     return out
 
 
@@ -373,64 +431,108 @@ def luvc_oim_plan_anyres(H: int, W: int, max_tokens: int, max_passes: int = 16) 
     return [(arr[k].axis, arr[k].m) for k in range(n.value)]
 
 
+_ragged_merges, _ragged_stages = _Bounded(), _Bounded()
+
+
+class _RaggedMerge:
+    """The host arrays of a ragged merge and what follows from them."""
+
+    def __init__(self, shapes, schedules, D, code):
+        flat = [p for sch in schedules for p in sch]
+        self.H, self.W = _i32([h for h, _ in shapes]), _i32([w for _, w in shapes])
+        self.passes, self.n_passes = _passes(flat), _i32([len(sch) for sch in schedules])
+        self.n = len(shapes)
+        self.out_shapes = [out_grid(h, w, sch) for (h, w), sch in zip(shapes, schedules)]
+        self.tokens_in = sum(h * w for h, w in shapes)
+        self.tokens_out = sum(max(h, 0) * max(w, 0) for h, w in self.out_shapes)
+        self.need = lib().luvc_oim_ragged_workspace_bytes(self.n, self.H, self.W, D, code, self.passes, self.n_passes)
+        self.addr = [ctypes.addressof(a) for a in (self.H, self.W, self.passes, self.n_passes)]
+
+
 def luvc_oim_merge_ragged(x, shapes, schedules, sizes=None, want_maps: bool = True, workspace=None, stream=None):
     """x: CUDA tensor [sum H_i*W_i, D], image after image; shapes [(H_i, W_i)]; schedules: one pass list per image.
     Returns dict(x [sum H'_i*W'_i, D], sizes, merged_map, kept_map, out_shapes)."""
-    import torch
+    nat = _native()
+    torch = nat.torch
     assert x.is_cuda and x.is_contiguous() and x.dim() == 2 and len(shapes) == len(schedules)
     T, D = x.shape
-    assert T == sum(h * w for h, w in shapes)
     code = _dtype_code(x)
-    Hs, Ws = _i32([h for h, _ in shapes]), _i32([w for _, w in shapes])
-    flat = [p for sch in schedules for p in sch]
-    parr, nps = _passes(flat), _i32([len(sch) for sch in schedules])
-    out_shapes = [out_grid(h, w, sch) for (h, w), sch in zip(shapes, schedules)]
-    To = sum(max(h, 0) * max(w, 0) for h, w in out_shapes)
+    try:
+        key = (D, code, tuple(shapes), tuple(map(tuple, schedules)))
+        plan = _ragged_merges.get(key)
+    except TypeError:                                   # shapes or passes that do not hash
+        key, plan = None, None
+    if plan is None:
+        plan = _RaggedMerge(shapes, schedules, D, code)
+        if key is not None:
+            _ragged_merges.keep(key, plan)
+    assert T == plan.tokens_in
+    To = plan.tokens_out
     if workspace is None:
-        need = lib().luvc_oim_ragged_workspace_bytes(len(shapes), Hs, Ws, D, code, parr, nps)
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
+        workspace = torch.empty(max(plan.need, 256), dtype=torch.uint8, device=x.device)
     if sizes is not None:
-        assert sizes.is_cuda and sizes.dtype == torch.int32 and sizes.is_contiguous() and sizes.numel() == T
-    out = dict(x=torch.empty((To, D), dtype=x.dtype, device=x.device),
-               sizes=torch.empty((To,), dtype=torch.int32, device=x.device),
-               merged_map=torch.empty((T,), dtype=torch.int32, device=x.device) if want_maps else None,
-               kept_map=torch.empty((To,), dtype=torch.int32, device=x.device) if want_maps else None,
-               out_shapes=out_shapes)
-    _check(lib().luvc_oim_merge_ragged(_ptr(x), _ptr(sizes), len(shapes), Hs, Ws, D, code, parr, nps, _ptr(out["x"]),
-                                       _ptr(out["sizes"]), _ptr(out["merged_map"]), _ptr(out["kept_map"]),
-                                       _ptr(workspace), workspace.numel(), _stream(stream)))
-    return out
+        assert sizes.is_cuda and sizes.dtype == nat.i32 and sizes.is_contiguous() and sizes.numel() == T
+        sizes = sizes.data_ptr()
+    xo = torch.empty((To, D), dtype=x.dtype, device=x.device)
+    merged = kept = None
+    if want_maps:                                       # one allocation for the three of them
+        so, merged, kept = torch.empty((2 * To + T,), dtype=nat.i32, device=x.device).split_with_sizes((To, T, To))
+    else:
+        so = torch.empty((To,), dtype=nat.i32, device=x.device)
+    H, W, passes, n_passes = plan.addr
+    _check(nat.call(nat.luvc_oim_merge_ragged, x.data_ptr(), sizes, plan.n, H, W, D, code, passes, n_passes, xo.data_ptr(), so.data_ptr(),
+                    _ptr(merged), _ptr(kept), workspace.data_ptr(), workspace.numel(), nat.stream(stream)))
+    return dict(x=xo, sizes=so, merged_map=merged, kept_map=kept, out_shapes=list(plan.out_shapes))
+
+
+class _RaggedStage:
+    """The host arrays of a ragged stage and what follows from them."""
+
+    def __init__(self, lengths, sigmas, keeps, D, code):
+        self.N, self.sigma = _i32(lengths), _i32(sigmas)
+        self.keep = _i32(keeps) if keeps is not None else None
+        self.n = len(lengths)
+        self.tokens = sum(lengths)
+        self.kept = sum(max(int(k), 0) for k in keeps) if keeps is not None else 0
+        self.need = lib().luvc_spu_ragged_workspace_bytes(self.n, self.N, D, code, self.sigma)
+        self.addr = [None if a is None else ctypes.addressof(a) for a in (self.N, self.sigma, self.keep)]
 
 
 def luvc_spu_stage_ragged(x, lengths, sigmas, keeps=None, use_hamming: bool = True, origin=None, gather: bool = True,
                           workspace=None, stream=None):
     """x: CUDA tensor [sum N_i, D] (rows evenly strided), sample after sample; lengths, sigmas, keeps: per sample.
     Returns dict(scores [sum N_i] fp32, kept_idx, origin [sum keep_i] int32, x [sum keep_i, D] or None)."""
-    import torch
+    nat = _native()
+    torch = nat.torch
     assert x.is_cuda and x.dim() == 2 and x.stride(1) == 1 and len(lengths) == len(sigmas)
     T, D = x.shape
-    assert T == sum(lengths)
     code = _dtype_code(x)
-    Ns, Sg = _i32(lengths), _i32(sigmas)
-    Kp = _i32(keeps) if keeps is not None else None
-    K = sum(max(int(k), 0) for k in keeps) if keeps is not None else 0
+    try:
+        key = (D, code, tuple(lengths), tuple(sigmas), None if keeps is None else tuple(keeps))
+        plan = _ragged_stages.get(key)
+    except TypeError:
+        key, plan = None, None
+    if plan is None:
+        plan = _RaggedStage(lengths, sigmas, keeps, D, code)
+        if key is not None:
+            _ragged_stages.keep(key, plan)
+    assert T == plan.tokens
+    K = plan.kept
     if origin is not None:
-        assert origin.is_cuda and origin.dtype == torch.int32 and origin.is_contiguous() and origin.numel() == T
+        assert origin.is_cuda and origin.dtype == nat.i32 and origin.is_contiguous() and origin.numel() == T
+        origin = origin.data_ptr()
     if workspace is None:
-        need = lib().luvc_spu_ragged_workspace_bytes(len(lengths), Ns, D, code, Sg)
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
-    out = dict(scores=torch.empty((T,), dtype=torch.float32, device=x.device),
-               kept_idx=torch.empty((K,), dtype=torch.int32, device=x.device),
-               origin=torch.empty((K,), dtype=torch.int32, device=x.device),
-               x=torch.empty((K, D), dtype=x.dtype, device=x.device) if (gather and keeps is not None) else None)
-    # a tensor without elements has no address: hand the library a one-element stand-in it will not touch
-    pad = torch.empty((1,), dtype=torch.int32, device=x.device)
-    ki = out["kept_idx"] if K else pad
-    og = out["origin"] if K else pad
-    _check(lib().luvc_spu_stage_ragged(_ptr(x), len(lengths), Ns, D, x.stride(0), code, Sg, int(bool(use_hamming)), Kp,
-                                       _ptr(origin), _ptr(out["scores"]), _ptr(ki), _ptr(og), _ptr(out["x"]) if K else None,
-                                       _ptr(workspace), workspace.numel(), _stream(stream)))
-    return out
+        workspace = torch.empty(max(plan.need, 256), dtype=torch.uint8, device=x.device)
+    scores = torch.empty((T,), dtype=nat.f32, device=x.device)
+    kept_idx, kept_origin = torch.empty((2 * K,), dtype=nat.i32, device=x.device).split_with_sizes((K, K))
+    xo = torch.empty((K, D), dtype=x.dtype, device=x.device) if (gather and keeps is not None) else None
+    # a tensor without elements has no address: hand the library one it will not touch
+    ki = kept_idx.data_ptr() if K else scores.data_ptr()
+    og = kept_origin.data_ptr() if K else scores.data_ptr()
+    N, sigma, keep = plan.addr
+    _check(nat.call(nat.luvc_spu_stage_ragged, x.data_ptr(), plan.n, N, D, x.stride(0), code, sigma, int(bool(use_hamming)), keep,
+                    origin, scores.data_ptr(), ki, og, _ptr(xo) if K else None, workspace.data_ptr(), workspace.numel(), nat.stream(stream)))
+    return dict(scores=scores, kept_idx=kept_idx, origin=kept_origin, x=xo)
 
 
 class LaunchProfile:
@@ -484,7 +586,7 @@ def luvc_selftest_fdot2(x, y, stream=None):
     assert x.is_cuda and x.dtype == torch.bfloat16 and x.shape == y.shape and x.dim() == 2 and x.shape[1] % 2 == 0
     assert x.is_contiguous() and y.is_contiguous()
     out = torch.empty((x.shape[0],), dtype=torch.float32, device=x.device)
-    _check(lib().luvc_selftest_fdot2(_ptr(x), _ptr(y), x.shape[0], x.shape[1] // 2, _ptr(out), _stream(stream)))
+    _check(lib().luvc_selftest_fdot2(_ptr(x), _ptr(y), x.shape[0], x.shape[1] // 2, _ptr(out), _native().stream(stream)))
     return out
 
 
@@ -494,5 +596,5 @@ def luvc_selftest_screen_tile(a, c, stream=None):
     assert a.is_cuda and a.shape == c.shape and a.dim() == 2 and a.shape[0] == 32 and a.dtype == c.dtype
     assert a.is_contiguous() and c.is_contiguous()
     out = torch.empty((32, 32), dtype=torch.float32, device=a.device)
-    _check(lib().luvc_selftest_screen_tile(_ptr(a), _ptr(c), a.shape[1], _dtype_code(a), _ptr(out), _stream(stream)))
+    _check(lib().luvc_selftest_screen_tile(_ptr(a), _ptr(c), a.shape[1], _dtype_code(a), _ptr(out), _native().stream(stream)))
     return out

@@ -1,10 +1,11 @@
-"""Builds libluvc.so (the gfx950 kernels + C ABI) in-tree with hipcc."""
+"""Builds libluvc.so (the gfx950 kernels + C ABI) in-tree with hipcc, and _luvc_call.so (the caller of its entry points)."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -16,6 +17,8 @@ SANITIZE = os.environ.get("LUVC_HOST_SANITIZE", "") not in ("", "0")
 LIB = os.path.join(HERE, "libluvc_san.so" if SANITIZE else "libluvc.so")
 OBJ = os.path.join(HERE, "_build_san" if SANITIZE else "_build")
 SAN_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
+
+CALL_SRC, CALL_LIB = os.path.join(CSRC, "pycall.c"), os.path.join(HERE, "_luvc_call.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -30,7 +33,7 @@ def sources():
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(CALL_LIB) or os.path.getmtime(CALL_SRC) > os.path.getmtime(CALL_LIB):
         return True
     t = os.path.getmtime(LIB)
     deps = sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + [os.path.join(HERE, "..", "include", "luvc.h")]
@@ -60,6 +63,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
         objs = list(ex.map(compile_one, srcs))
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *(["-fsanitize=address", "-fsanitize=undefined", "-shared-libsan"] if SANITIZE else []), *objs, "-o", LIB])
+    subprocess.check_call(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], CALL_SRC, "-o", CALL_LIB])
     return LIB
 
 
