@@ -14,12 +14,16 @@
 // method, reached in two steps:
 //   1. SCREENING.  The source x destination dot products of the line on the matrix cores in the storage precision
 //      (v_mfma_f32_32x32x16_bf16, or four v_mfma_f32_32x32x2_f32 for fp32 tokens): a 32 x 32 tile at a time, eight
-//      wavefronts split the channels, every token byte is fetched once per tile.  The squared norms are summed in fp64
-//      on the way.  A screened cosine is taken to be within eps = (D + 4) 2^-22 of the fp64 cosine: the products of
-//      bf16 values are exact in fp32, and D accumulation steps of at most 2^-23 each (relative to the sum of the
-//      magnitudes of the products, which is at most the product of the norms) plus the rounding of fp32 products, of
-//      the reciprocal norms and of two products stay below half of that; tests/test_gpu_oim_wide.py pins the
-//      contraction against fp64 on adversarial rows.
+//      wavefronts split the channels, every token byte is fetched once per tile.  The squared norms are summed in fp32
+//      on the way (in fp64, they took as long as everything else of the screening).  A screened cosine is taken to be
+//      within eps = (D + 24) 2^-22 of the fp64 cosine: the products of bf16 values are exact in fp32, and D
+//      accumulation steps of at most 2^-23 each (relative to the sum of the magnitudes of the products, which is at
+//      most the product of the norms) stay below half of that - tests/test_gpu_oim_wide.py pins the contraction against
+//      fp64 on adversarial rows; the other half covers the norms (a lane adds a sixteenth of the squares, D / 16 + 24
+//      steps of at most 2^-23 on each, halved by the root), the rounding of fp32 products, of the reciprocals and of
+//      two products.  Sums of squares beyond 2^100 end the screening of their line: everything is repeated then.  Small
+//      values need no such care: what flushed products lose is below 2^-116, far below a norm of 1e-12, which is where
+//      the method clamps.
 //   2. EXACT.  A source may be among the m best of the line only if fewer than m screened best cosines exceed its own by
 //      more than 2 eps; for each such contender, the destinations within 2 eps of its best screened cosine may be its
 //      best destination, no other can.  Their dot products are repeated in fp64 (a wavefront per contender, two
@@ -36,6 +40,7 @@
 #include "common.hpp"
 #include "oim.hpp"
 #include "oim_lazy.hpp"
+#include "oim_sum64.hpp"
 #include "oim_wide_tok.hpp"
 
 namespace luvc {
@@ -50,6 +55,7 @@ __host__ __device__ inline int lazy_row_stride(int n_dst) { return n_dst <= 4 ? 
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_lz __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // What a lane feeds to the matrix cores per step of the screening contraction: 16 bytes of a token.  Lane l belongs
@@ -58,6 +64,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 template <typename T> struct screen;
 template <> struct screen<bf16_t> {
     static constexpr int KS = 16, KL = 8;      // channels per step, per lane
+    static constexpr int LOADS = 5;            // steps in flight
     __device__ static __forceinline__ f32x16 mac(f32x16 acc, const u32x4& a, const u32x4& c)
     {
         bf16x8_t va, vc;
@@ -65,13 +72,14 @@ template <> struct screen<bf16_t> {
         __builtin_memcpy(&vc, &c, 16);
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, vc, acc, 0, 0, 0);
     }
-    __device__ static __forceinline__ double sq(const u32x4& a, double acc)
+    __device__ static __forceinline__ float sq(const u32x4& a, float acc)
     {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const double lo = (double)__uint_as_float(a[i] << 16), hi = (double)__uint_as_float(a[i] & 0xffff0000u);
-            acc = fma(lo, lo, acc);
-            acc = fma(hi, hi, acc);
+            bf16x2_lz w;
+            const uint32_t bits = a[i];
+            __builtin_memcpy(&w, &bits, 4);
+            acc = __builtin_amdgcn_fdot2_f32_bf16(w, w, acc, false);
         }
         return acc;
     }
@@ -86,7 +94,7 @@ template <> struct screen<bf16_t> {
     }
 };
 template <> struct screen<float> {
-    static constexpr int KS = 8, KL = 4;
+    static constexpr int KS = 8, KL = 4, LOADS = 4;
     // instruction e contracts channels {e, 4 + e} of the step: the same pairing on both sides
     __device__ static __forceinline__ f32x16 mac(f32x16 acc, const u32x4& a, const u32x4& c)
     {
@@ -94,10 +102,10 @@ template <> struct screen<float> {
         for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(c[e]), acc, 0, 0, 0);
         return acc;
     }
-    __device__ static __forceinline__ double sq(const u32x4& a, double acc)
+    __device__ static __forceinline__ float sq(const u32x4& a, float acc)
     {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { const double v = (double)__uint_as_float(a[i]); acc = fma(v, v, acc); }
+        for (int i = 0; i < 4; ++i) acc = fmaf(__uint_as_float(a[i]), __uint_as_float(a[i]), acc);
         return acc;
     }
     __device__ static __forceinline__ double dot(const u32x4& a, const u32x4& c, double acc)
@@ -117,48 +125,36 @@ __device__ __forceinline__ u32x4 piece(const T* tok, int D, int d, bool present)
     return v;
 }
 
-// wave64 sum of fp64 values without the LDS crossbar: DPP adds inside each row of 16 lanes on both halves of the value,
-// two row broadcasts, the total read back from lane 63
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_mov64(double v)
-{
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false));
-}
-__device__ __forceinline__ double wave_total64(double v)
-{
-    v += dpp_mov64<0xB1, 0xf>(v);        // quad_perm [1,0,3,2]
-    v += dpp_mov64<0x4E, 0xf>(v);        // quad_perm [2,3,0,1]
-    v += dpp_mov64<0x141, 0xf>(v);       // row_half_mirror
-    v += dpp_mov64<0x140, 0xf>(v);       // row_mirror
-    v += dpp_mov64<0x142, 0xa>(v);       // row_bcast:15 -> rows 1, 3 (the other rows add the zero of the disabled lanes)
-    v += dpp_mov64<0x143, 0xc>(v);       // row_bcast:31 -> rows 2, 3
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63), __builtin_amdgcn_readlane(__double2loint(v), 63));
-}
-
-// <a, c1> and <a, c2> in fp64 by one wavefront, all fetches in flight together
+// fp64 cosines of a with c1 and c2 by one wavefront, all fetches in flight together
 template <typename T>
-__device__ __forceinline__ void dot64_wave2(const T* a, const T* c1, const T* c2, int D, int lane, double& d1, double& d2)
+__device__ __forceinline__ void cos64_wave2(const T* a, const T* c1, const T* c2, int D, int lane, double& s1, double& s2)
 {
     constexpr int V = 16 / (int)sizeof(T);
-    double acc1 = 0.0, acc2 = 0.0;
+    double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};            // aa, c1 c1, c2 c2, a c1, a c2
+    const __amdgpu_buffer_rsrc_t ba = lz_row(a, D, true), b1 = lz_row(c1, D, true), b2 = lz_row(c2, D, true);
     for (int d0 = 0; d0 < D; d0 += 64 * V * 3) {
-        u32x4 ra[3], rc1[3], rc2[3];
+        u32x4 ra[3], r1[3], r2[3];
 #pragma unroll
         for (int u = 0; u < 3; ++u) {
-            const int d = d0 + (u * 64 + lane) * V;
-            ra[u] = piece(a, D, d, true);
-            rc1[u] = piece(c1, D, d, true);
-            rc2[u] = piece(c2, D, d, true);
+            const int off = (d0 + (u * 64 + lane) * V) * (int)sizeof(T);
+            ra[u] = lz_load(ba, off);
+            r1[u] = lz_load(b1, off);
+            r2[u] = lz_load(b2, off);
         }
 #pragma unroll
         for (int u = 0; u < 3; ++u) {
-            acc1 = screen<T>::dot(ra[u], rc1[u], acc1);
-            acc2 = screen<T>::dot(ra[u], rc2[u], acc2);
+            v[0] = screen<T>::dot(ra[u], ra[u], v[0]);
+            v[1] = screen<T>::dot(r1[u], r1[u], v[1]);
+            v[2] = screen<T>::dot(r2[u], r2[u], v[2]);
+            v[3] = screen<T>::dot(ra[u], r1[u], v[3]);
+            v[4] = screen<T>::dot(ra[u], r2[u], v[4]);
         }
     }
-    d1 = wave_total64(acc1);
-    d2 = wave_total64(acc2);
+    wave_total64x8(v, lane);
+    auto norm = [](double n2) { const double n = sqrt(n2); return n < 1e-12 ? 1e-12 : n; };
+    const double na = norm(v[0]);
+    s1 = v[3] / (na * norm(v[1]));
+    s2 = v[4] / (na * norm(v[2]));
 }
 
 // largest value over groups of eight lanes, in every lane
@@ -194,7 +190,6 @@ selftest_screen_tile(const T* __restrict__ a, const T* __restrict__ c, int D, fl
     for (int v = 0; v < 16; ++v) out[(8 * (v >> 2) + 4 * kh + (v & 3)) * 32 + r] = acc[v];
 }
 
-constexpr int kLazyLoads = 5;                    // steps of the screening contraction in flight
 constexpr int kScreenWaves = 8;                  // wavefronts that split its channels
 template <typename T>
 __global__ void __launch_bounds__(1024)
@@ -209,19 +204,19 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     const int len = g.axis ? g.w : g.h, nlines = g.axis ? g.h : g.w;
     const int n_src = (len + 1) / 2, n_dst = len / 2;
     const int Wo = g.axis ? g.w - g.m : g.w, Ho = g.axis ? g.h : g.h - g.m;
-    double* pn = reinterpret_cast<double*>(smem_raw);    // [kScreenWaves][len] squared norms, the part of each wavefront
-    double* nrm = pn + kScreenWaves * len;               // [len] max(norm, 1e-12)
-    double* escore = nrm + len;                          // [64] fp64 cosine of a contender with its best destination
+    double* escore = reinterpret_cast<double*>(smem_raw);              // [64] fp64 cosine of a contender with its best destination
     float* P = reinterpret_cast<float*>(escore + 64);    // [kScreenWaves][32 * 32] a tile, the part of each wavefront
     // [n_src][sd] screened dot products, then cosines.  Rows are sd = 4 mod 32 floats apart: lanes on neighbouring sources
     // fall into different banks
     float* S = P + kScreenWaves * 1024;
     const int sd = lazy_row_stride(n_dst);
-    float* inv32 = S + n_src * sd;                       // [len] 1 / norm
+    float* pn = S + n_src * sd;                          // [kScreenWaves][len] squared norms, the part of each wavefront
+    float* inv32 = pn + kScreenWaves * len;              // [len] 1 / norm
     float* b32 = inv32 + len;                            // [64] best screened cosine of a source
     int* rid = reinterpret_cast<int*>(b32 + 64);         // [len] row id of the token at position p
     int* sz = rid + len;                                 // [len] its size
     int* ebest = sz + len;                               // [64] best destination of a contender
+    int* wild = ebest + 64;                              // [1] a norm that fp32 does not hold
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), NW = blockDim.x >> 6;
     const unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);       // lines of one image meet in one L2
@@ -234,60 +229,84 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     const T* dx = xk ? xk : x;
     const T* dov = xk ? ovk : ov;
     const int dD = xk ? Dk : g.D;
-    const float tau = 2.f * (float)(dD + 4) * 2.3841858e-7f;           // 2 eps
+    float tau = 2.f * (float)(dD + 24) * 2.3841858e-7f;                // 2 eps
 
     for (int p = tid; p < len; p += blockDim.x) {
         const int f = in_flat(p);
         rid[p] = idx_in ? idx_in[img + f] : f;
         sz[p] = sizes_in ? sizes_in[img + f] : 1;
     }
+    if (tid == 0) *wild = 0;
     __syncthreads();
 
     // ------------------------------------------------------------------ 1. screening: dot products and squared norms
     // Result layout of the 32 x 32 instructions: lane l, register v holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.
     {
-        const int tiles_s = (n_src + 31) / 32, tiles_d = (n_dst + 31) / 32;
+        constexpr int LOADS = sc::LOADS, STEP = kScreenWaves * sc::KS;
+        const int tiles_s = (n_src + 31) / 32, tiles_d = (n_dst + 31) / 32, tiles = tiles_s * tiles_d;
         const int r = lane & 31, kh = lane >> 5;
-        for (int t = 0; t < tiles_s * tiles_d; ++t) {
+        const bool screens = wave < kScreenWaves;
+        // Wavefront w takes steps w, w + kScreenWaves, ... of KS channels, a lane its half of each; the trip count is the
+        // same in every lane (the matrix instructions want the whole wavefront).  Rows and channels that are not there are
+        // read from where some are, without a branch - the compiler waits for everything in flight at a join - and
+        // such channels are masked.  LOADS steps stay in flight, across the tiles of a long line too.
+        const int first = wave * sc::KS + kh * sc::KL, steps = wave * sc::KS < dD ? (dD - wave * sc::KS + STEP - 1) / STEP : 0;
+        const T *tok_s = dx, *tok_d = dx;
+        u32x4 ra[LOADS], rc[LOADS];
+        auto fetch = [&](int u, int d) {
+            const int at = d < dD ? d : dD - sc::KL;
+            ra[u] = *reinterpret_cast<const u32x4*>(tok_s + at);
+            rc[u] = *reinterpret_cast<const u32x4*>(tok_d + at);
+        };
+        auto begin_tile = [&](int t) {
+            const int js = t / tiles_d * 32 + r, jd = t % tiles_d * 32 + r;
+            tok_s = row_of<T>(dx, dov, b, rid[js < n_src ? 2 * js : 0], g, dD);
+            tok_d = row_of<T>(dx, dov, b, rid[jd < n_dst ? 2 * jd + 1 : 0], g, dD);
+            if (steps >= LOADS) {
+#pragma unroll
+                for (int u = 0; u < LOADS; ++u) fetch(u, first + STEP * u);
+            } else {
+#pragma unroll
+                for (int u = 0; u < LOADS; ++u)
+                    if (u < steps) fetch(u, first + STEP * u);
+            }
+        };
+        if (screens && tiles > 0) begin_tile(0);
+        for (int t = 0; t < tiles; ++t) {
             const int ts = t / tiles_d, td = t % tiles_d;
-            if (wave < kScreenWaves) {
-                const int js = ts * 32 + r, jd = td * 32 + r;
-                const bool has_s = js < n_src, has_d = jd < n_dst;
-                const T* tok_s = row_of<T>(dx, dov, b, has_s ? rid[2 * js] : rid[0], g, dD);
-                const T* tok_d = row_of<T>(dx, dov, b, has_d ? rid[2 * jd + 1] : rid[0], g, dD);
+            if (screens) {
                 f32x16 acc;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-                double na = 0.0, nc = 0.0;
-                // wavefront w takes steps w, w + kScreenWaves, ... of KS channels, a lane its half of each; the trip count is the
-                // same in every lane (the matrix instructions want the whole wavefront), pieces past the end of the token
-                // are zeros.  kLazyLoads steps stay in flight: a slot is fetched again as soon as it is used up.
-                constexpr int STEP = kScreenWaves * sc::KS;
-                const int first = wave * sc::KS + kh * sc::KL;
-                u32x4 ra[kLazyLoads], rc[kLazyLoads];
+                float na = 0.f, nc = 0.f;
+                auto use = [&](int u, int d) {
+                    const uint32_t there = d < dD ? 0xffffffffu : 0u;
+                    const u32x4 a = ra[u] & there, c = rc[u] & there;
+                    acc = sc::mac(acc, a, c);
+                    na = sc::sq(a, na);
+                    nc = sc::sq(c, nc);
+                };
+                int d = first, left = steps;
+                for (; left > LOADS; d += STEP * LOADS, left -= LOADS) {
 #pragma unroll
-                for (int u = 0; u < kLazyLoads; ++u) {
-                    ra[u] = piece(tok_s, dD, first + STEP * u, has_s);
-                    rc[u] = piece(tok_d, dD, first + STEP * u, has_d);
-                }
-                for (int d0 = wave * sc::KS; d0 < dD; d0 += STEP * kLazyLoads) {
-#pragma unroll
-                    for (int u = 0; u < kLazyLoads; ++u) {
-                        acc = sc::mac(acc, ra[u], rc[u]);
-                        if (td == 0) na = sc::sq(ra[u], na);
-                        if (ts == 0) nc = sc::sq(rc[u], nc);
-                        const int next = d0 + kh * sc::KL + STEP * (u + kLazyLoads);
-                        ra[u] = piece(tok_s, dD, next, has_s);
-                        rc[u] = piece(tok_d, dD, next, has_d);
+                    for (int u = 0; u < LOADS; ++u) {
+                        use(u, d + STEP * u);
+                        fetch(u, d + STEP * (u + LOADS));
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                 }
+#pragma unroll
+                for (int u = 0; u < LOADS; ++u)
+                    if (u < left) use(u, d + STEP * u);
+                if (t + 1 < tiles) begin_tile(t + 1);
 #pragma unroll
                 for (int v = 0; v < 16; ++v) P[wave * 1024 + (8 * (v >> 2) + 4 * kh + (v & 3)) * 32 + r] = acc[v];
                 na += __shfl_xor(na, 32, kWave);                              // the two channel halves of a step
                 nc += __shfl_xor(nc, 32, kWave);
+                const int js = ts * 32 + r, jd = td * 32 + r;
                 if (kh == 0) {
-                    if (td == 0 && has_s) pn[wave * len + 2 * js] = na;
-                    if (ts == 0 && has_d) pn[wave * len + 2 * jd + 1] = nc;
+                    if (td == 0 && js < n_src) pn[wave * len + 2 * js] = na;
+                    if (ts == 0 && jd < n_dst) pn[wave * len + 2 * jd + 1] = nc;
                 }
             }
             __syncthreads();
@@ -298,22 +317,20 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
                 for (int w = 1; w < kScreenWaves; ++w) sum += P[w * 1024 + e];
                 if (row < n_src && col < n_dst) S[row * sd + col] = sum;
             }
-            if (t + 1 < tiles_s * tiles_d) __syncthreads();
+            if (t + 1 < tiles) __syncthreads();
         }
     }
-    for (int p = tid; p < len; p += blockDim.x) {
-        double v = 1.0;                                  // a line of one token has no products and no decisions
-        if (n_dst > 0) {
-            v = pn[p];
+    if (n_dst > 0)                                       // a line of one token has no products and no decisions
+        for (int p = tid; p < len; p += blockDim.x) {
+            float v = pn[p];
 #pragma unroll
             for (int w = 1; w < kScreenWaves; ++w) v += pn[w * len + p];
-            v = sqrt(v);
+            if (!(v <= 1.2676506e30f)) *wild = 1;
+            v = sqrtf(v);
+            inv32[p] = 1.0f / (v < 1e-12f ? 1e-12f : v);
         }
-        v = v < 1e-12 ? 1e-12 : v;
-        nrm[p] = v;
-        inv32[p] = 1.0f / (float)v;
-    }
     __syncthreads();
+    if (*wild) tau = INFINITY;
     // screened cosines and the best of each source: eight lanes per source.  A cosine that is no number counts as the
     // lowest, so that exactly m sources leave the line whatever the tokens hold.
     if (wave < 8) {
@@ -357,7 +374,7 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
             if (q % NW != wave) continue;
             const int j = (int)__builtin_ctzll(left), a = 2 * j;
             const float bj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vbest), j));
-            unsigned long long cand = __ballot(lane < n_dst && S[j * sd + (lane < n_dst ? lane : 0)] >= bj - tau);
+            unsigned long long cand = __ballot(lane < n_dst && S[j * sd + (lane < n_dst ? lane : 0)] >= fmaxf(bj - tau, -3.f));
             double bs = -INFINITY;
             int bk = (int)__builtin_ctzll(cand);
             if (ranked || (cand & (cand - 1))) {
@@ -367,9 +384,8 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
                     cand &= cand - 1;
                     const int k2 = cand ? (int)__builtin_ctzll(cand) : k1;
                     cand &= cand - 1;
-                    double d1, d2;
-                    dot64_wave2<T>(ta, row_of<T>(dx, dov, b, rid[2 * k1 + 1], g, dD), row_of<T>(dx, dov, b, rid[2 * k2 + 1], g, dD), dD, lane, d1, d2);
-                    const double c1 = d1 / (nrm[a] * nrm[2 * k1 + 1]), c2 = d2 / (nrm[a] * nrm[2 * k2 + 1]);
+                    double c1, c2;
+                    cos64_wave2<T>(ta, row_of<T>(dx, dov, b, rid[2 * k1 + 1], g, dD), row_of<T>(dx, dov, b, rid[2 * k2 + 1], g, dD), dD, lane, c1, c2);
                     if (c1 > bs) { bs = c1; bk = k1; }
                     if (c2 > bs) { bs = c2; bk = k2; }
                 }
@@ -532,8 +548,7 @@ static luvc_status run_lazy_pass(const T* x, T* ov, const T* xk, T* ovk, int Dk,
     g.n0 = n0; g.h = h; g.w = w; g.D = D; g.axis = axis; g.m = m; g.radius = radius; g.cap = cap; g.ov_base = ov_base;
     g.per_line = m < n_dst ? m : n_dst;
     const int sd = lazy_row_stride(n_dst);
-    const size_t lds = sizeof(double) * ((size_t)(kScreenWaves + 1) * len + 64) + sizeof(float) * ((size_t)kScreenWaves * 1024 + (size_t)n_src * sd + len + 64) +
-                       sizeof(int) * ((size_t)2 * len + 64);
+    const size_t lds = sizeof(double) * 64 + sizeof(float) * ((size_t)kScreenWaves * (1024 + len) + (size_t)n_src * sd + len + 64) + sizeof(int) * ((size_t)2 * len + 65);
     // eight wavefronts; sixteen where so many destinations are merged that eight would take several rounds and a compute
     // unit has no second line to work on
     const int waves = g.per_line * (xk ? 2 : 1) > 8 && B * nlines <= 256 ? 16 : 8;
