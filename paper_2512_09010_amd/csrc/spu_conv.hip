@@ -139,6 +139,26 @@ template <> struct raw_pair<float> {
     __device__ __forceinline__ cf widen() const { return {__uint_as_float(v[0]), __uint_as_float(v[1])}; }
 };
 
+// The values of a 16-point DFT times W_256^{i lw} (INV: its conjugate's inverse), handed to `put` one by one.  The twiddles come
+// from LDS in groups: read one at a time, each would wait for the write before it (the compiler cannot tell the table from
+// the exchange grid), all at once they would not fit beside the values.
+template <bool INV, int GROUP, typename F>
+__device__ __forceinline__ void twiddled(const cf (&v)[16], const float2* twb, int lw, F put)
+{
+#pragma unroll
+    for (int i0 = 0; i0 < 16; i0 += GROUP) {
+        __builtin_amdgcn_sched_barrier(0);
+        float2 w[GROUP];
+#pragma unroll
+        for (int i = 0; i < GROUP; ++i) w[i] = twb[(i0 + i) * lw];
+#pragma unroll
+        for (int i = 0; i < GROUP; ++i) {
+            const cf t{w[i].x, w[i].y};
+            put(i0 + i, i0 + i == 0 ? v[0] : INV ? cmul(v[i0 + i], t) : cmulc(v[i0 + i], t));
+        }
+    }
+}
+
 // LDS accesses of one wavefront are served in order: this only keeps the compiler from moving them
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -217,20 +237,19 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
     const T* xs = x + (int64_t)b * N * row_stride;
     using raw_t = raw_pair<T>;
     raw_t raw[JN];
-    // PAIRED: a descriptor per block of 256 tokens that ends with the sample (a lane past it, or past D, reads zeros)
+    // PAIRED: the descriptor ends with the sample's last token (a lane past it, or past D, reads zeros)
     const uint32_t row_bytes = (uint32_t)row_stride * (uint32_t)sizeof(T);
     const uint32_t lane_off = (uint32_t)n2 * row_bytes + (uint32_t)c * 2u * (uint32_t)sizeof(T);
     auto fetch = [&](int g) {
         const int d0 = (g * P + c) * 2;
         if constexpr (PAIRED) {
-            const uint32_t off = d0 < D ? lane_off : 0x80000000u;
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<T*>(xs) + 2 * P * g, 0, (int)((uint32_t)(N - 1) * row_bytes + (uint32_t)((D - 2 * P * g) * (int)sizeof(T))), 0x00020000);
+            uint32_t off = d0 < D ? lane_off : 0x80000000u;
 #pragma unroll
             for (int j = 0; j < JN; ++j) {
-                const int rows = HALF ? N - 256 * j : 256;         // rows of this block (at most 256 count: n2 < 256)
-                const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-                    const_cast<T*>(xs) + (int64_t)(256 * j) * row_stride + 2 * P * g, 0,
-                    rows <= 0 ? 0 : (int)((uint32_t)((rows < 256 ? rows : 256) - 1) * row_bytes + (uint32_t)((D - 2 * P * g) * (int)sizeof(T))), 0x00020000);
                 raw[j] = raw_t::load(r, off);
+                off += 256u * row_bytes;
             }
         } else {
             const bool live = d0 < D, second = d0 + 1 < D;
@@ -283,9 +302,17 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
             for (int kb = 0; kb < 16; ++kb) wr[it % (SPEC_LDS ? 1 : NIT)][kb] = weight(it * 16 + wrow + R * (lw + 16 * kb));
     }
     __syncthreads();
-    cf wa[R];                                    // W_M^{k1 n2} (conjugated on use)
+    // W_M^{k1 n2} (conjugated on use).  N = M, where a thread holds R tokens and R sums, or fp32 tokens: the upper half as
+    // W_256^{n2} conj(W_M^{(R - k1) n2}), so that the rest stays in registers - what spills goes through L2, and the cache
+    // lines of the tokens, which neighbouring workgroups share, have left it when the next one asks (4x4096x3584 bf16 out of
+    // HBM: 313 MB fetched for 117, {CONV_SPILL_US}).
+    constexpr bool FOLD = !HALF || sizeof(T) == 4;
+    constexpr int KEPT = FOLD ? R / 2 + 1 : R;
+    cf wa[KEPT], wtop{0.f, 0.f};
 #pragma unroll
-    for (int k1 = 1; k1 < R; ++k1) { const float2 w = sm[(k1 * n2) & (M - 1)]; wa[k1] = {w.x, w.y}; }
+    for (int k1 = 1; k1 < KEPT; ++k1) { const float2 w = sm[(k1 * n2) & (M - 1)]; wa[k1] = {w.x, w.y}; }
+    if (FOLD) { const float2 w = sm[(R * n2) & (M - 1)]; wtop = {w.x, w.y}; }
+    auto tw_a = [&](int k1) { return k1 < KEPT ? wa[k1 < KEPT ? k1 : 0] : cmulc(wtop, wa[k1 < KEPT ? 0 : R - k1]); };
     if (tid < 256) twb[tid] = sm[tid * R];
     float acc[JN];
 #pragma unroll
@@ -296,6 +323,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
     tile_tag_t seen = 0;
     for (int g = tile; g < n_groups; g += n_tiles) {
         // ---- A
+        if (FOLD) asm volatile("" : "+v"(wtop.x), "+v"(wtop.y));         // the products with it are formed where they are used, not kept
         {
             cf v[R];
 #pragma unroll
@@ -304,7 +332,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
             col[0] = make_float2(v[0].x, v[0].y);
 #pragma unroll
             for (int k1 = 1; k1 < R; ++k1) {
-                const cf r = cmulc(v[k1], wa[k1]);
+                const cf r = cmulc(v[k1], tw_a(k1));
                 col[k1 * LROW] = make_float2(r.x, r.y);
             }
         }
@@ -320,12 +348,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
 #pragma unroll
             for (int a = 0; a < 16; ++a) { const float2 q = row[(17 * a + lw) * P]; v[a] = {q.x, q.y}; }
             fft16<false>(v);
-#pragma unroll
-            for (int ka = 0; ka < 16; ++ka) {
-                const float2 w = twb[ka * lw];
-                const cf r = ka ? cmulc(v[ka], cf{w.x, w.y}) : v[ka];
-                row[(17 * ka + lw) * P] = make_float2(r.x, r.y);
-            }
+            twiddled<false, R == 16 ? 4 : 8>(v, twb, lw, [&](int ka, cf r) { row[(17 * ka + lw) * P] = make_float2(r.x, r.y); });
             wave_lds_fence();
 #pragma unroll
             for (int i = 0; i < 16; ++i) { const float2 q = row[(17 * lw + i) * P]; v[i] = {q.x, q.y}; }
@@ -336,12 +359,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
                 v[kb] = {v[kb].x * w, v[kb].y * w};
             }
             fft16<true>(v);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float2 w = twb[i * lw];
-                const cf r = i ? cmul(v[i], cf{w.x, w.y}) : v[i];
-                row[(17 * lw + i) * P] = make_float2(r.x, r.y);
-            }
+            twiddled<true, R == 16 ? 4 : 8>(v, twb, lw, [&](int i, cf r) { row[(17 * lw + i) * P] = make_float2(r.x, r.y); });
             wave_lds_fence();
 #pragma unroll
             for (int ka = 0; ka < 16; ++ka) { const float2 q = row[(17 * ka + lw) * P]; v[ka] = {q.x, q.y}; }
@@ -351,11 +369,12 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
         }
         __syncthreads();
         // ---- A'
+        if (FOLD) asm volatile("" : "+v"(wtop.x), "+v"(wtop.y));
         {
             cf v[R];
             { const float2 q = col[0]; v[0] = {q.x, q.y}; }
 #pragma unroll
-            for (int k1 = 1; k1 < R; ++k1) { const float2 q = col[k1 * LROW]; v[k1] = cmul(cf{q.x, q.y}, wa[k1]); }
+            for (int k1 = 1; k1 < R; ++k1) { const float2 q = col[k1 * LROW]; v[k1] = cmul(cf{q.x, q.y}, tw_a(k1)); }
             dft_cols<R, HALF>::inv(v);
 #pragma unroll
             for (int j = 0; j < JN; ++j) acc[j] = fmaf(v[j].x, v[j].x, fmaf(v[j].y, v[j].y, acc[j]));
@@ -438,8 +457,8 @@ luvc_status spu_score_conv(const void* x, int B, int N, int D, int64_t row_strid
     bool half;
     const int R = spu_conv_rows(N, &half);
     const size_t es = dt == LUVC_F32 ? 4 : 2;
-    // 255 rows and a row's width have to stay below the offset that marks a lane without channels
-    const bool aligned = (row_stride % 2 == 0) && ((uintptr_t)x % (2 * es) == 0) && (D % 2 == 0) && row_stride * (int64_t)es < ((int64_t)1 << 22);
+    // a sample, rounded up to M tokens, has to stay below the offset that marks a lane without channels
+    const bool aligned = (row_stride % 2 == 0) && ((uintptr_t)x % (2 * es) == 0) && (D % 2 == 0) && (int64_t)256 * R * row_stride * (int64_t)es < ((int64_t)1 << 31);
     if (half) {
         const int M = 256 * R;
         LUVC_LAUNCH("spu_conv_spectrum", spu_conv_spectrum, dim3((unsigned)(M / 2 / kSpecBins + 1)), dim3(256), 0, st, N, M, sigma, use_hamming, spec);
