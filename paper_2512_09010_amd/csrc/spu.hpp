@@ -46,9 +46,9 @@ size_t spu_circ_bytes(int64_t samples, int N, int D);
 luvc_status spu_score_circ(const void* x, int64_t row_stride, int D, luvc_dtype dt, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st);
 
 // Any N (spu_conv.hip): N <= 8192, or N = 16384
-int spu_conv_rows(int N, bool* half);
+int spu_conv_points(int N, bool* half);
 int spu_conv_tiles(int B, int N, int D);
-double spu_conv_us(int B, int N, int D);
+double spu_conv_us(int B, int N, int D, luvc_dtype dt);
 size_t spu_conv_spec_bytes(int N);
 inline int spu_conv_ld(int N) { return (N + 3) / 4 * 4; }
 luvc_status spu_score_conv(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,

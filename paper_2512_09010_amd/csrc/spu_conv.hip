@@ -1,5 +1,5 @@
-// SPU score (paper Section 3.3, Eq. 4-8) for any number of tokens and any pass band: one transform of M = 256 R points
-// (R = 16, 32, 64) forward, one back, all of it in the registers and the LDS of a workgroup.
+// SPU score (paper Section 3.3, Eq. 4-8) for any number of tokens and any pass band: one transform of M = 2048, 4096, 8192 or
+// 16384 points forward, one back, all of it in the registers and the LDS of a workgroup.
 //
 // Eq. 4-7 together are a circular convolution of length N with the even kernel
 //     p[j] = 1/N sum_{|f| <= sigma} M[f] e^{2 pi i f j / N}.
@@ -10,9 +10,9 @@
 // evaluated in fp64 by spu_conv_spectrum.  Nothing about N has to factor.
 //
 // Two channels of a token are one complex value (the filter is real).  A workgroup holds P channel pairs at a time:
-//   A    thread (pair c, column n2): tokens n2, n2 + 256, ... straight from memory, R-point DFT in registers over them,
-//        twiddle W_M^{k1 n2}, row k1 of the exchange grid [R][256][P] gets the result;
-//   B,C  256 points of a row = 16 x 16: both passes, the spectrum and the two inverse passes run inside one wavefront, in
+//   A    thread (pair c, column n2 of C = 256, or 128 for M = 2048): tokens n2, n2 + C, ... straight from memory, R-point DFT
+//        (M = R C) in registers over them, twiddle W_M^{k1 n2}, row k1 of the exchange grid [R][C][P] gets the result;
+//   B,C  the points of a row = 16 x 16 (16 x 8): both passes, the spectrum and the two inverse passes run inside one wavefront, in
 //        place, so nothing but the order of one wavefront's LDS accesses stands between them;
 //   A'   thread (c, n2) again: twiddle, R-point inverse DFT, |.|^2 added to the thread's R (R/2) token energies.
 // Two barriers per P pairs; the next pairs' tokens are fetched while B and C run.  A workgroup walks the pairs in steps of
@@ -20,9 +20,13 @@
 // 4 P-byte pieces of the same cache lines, and keeps the energies in registers until its last pairs are done.
 // With half of the inputs zero and half of the outputs unwanted (N <= M / 2) passes A and A' take half the loads and skip a
 // butterfly level each.
+// M is the smallest that fits: the longer transform costs its zeros (8x1000x3584 bf16: 152 us on 4096 points, 77 on 2048;
+// 8x2048x3584: 208 and 88).
 //
 // Bound: fp32 vector arithmetic (about 5 M log2 M flops per direction and pair) and the LDS traffic beside it (64 bytes per
 // point and pair).
+#include <type_traits>
+
 #include "common.hpp"
 #include "spu.hpp"
 #include "spu_fftcore.hpp"
@@ -139,18 +143,18 @@ template <> struct raw_pair<float> {
     __device__ __forceinline__ cf widen() const { return {__uint_as_float(v[0]), __uint_as_float(v[1])}; }
 };
 
-// The values of a 16-point DFT times W_256^{i lw} (INV: its conjugate's inverse), handed to `put` one by one.  The twiddles come
-// from LDS in groups: read one at a time, each would wait for the write before it (the compiler cannot tell the table from
-// the exchange grid), all at once they would not fit beside the values.
-template <bool INV, int GROUP, typename F>
-__device__ __forceinline__ void twiddled(const cf (&v)[16], const float2* twb, int lw, F put)
+// Sixteen values times W^{exponent(i)}, exponent(0) = 0, out of the table twb, forward or inverse, handed to `put` one by
+// one.  The twiddles come from LDS in groups: read one at a time, each would wait for the write before it (the compiler
+// cannot tell the table from the exchange grid), all at once they would not fit beside the values.
+template <bool INV, int GROUP, typename E, typename F>
+__device__ __forceinline__ void twiddled(const cf (&v)[16], const float2* twb, E exponent, F put)
 {
 #pragma unroll
     for (int i0 = 0; i0 < 16; i0 += GROUP) {
         __builtin_amdgcn_sched_barrier(0);
         float2 w[GROUP];
 #pragma unroll
-        for (int i = 0; i < GROUP; ++i) w[i] = twb[(i0 + i) * lw];
+        for (int i = 0; i < GROUP; ++i) w[i] = twb[exponent(i0 + i)];
 #pragma unroll
         for (int i = 0; i < GROUP; ++i) {
             const cf t{w[i].x, w[i].y};
@@ -214,20 +218,20 @@ spu_conv_spectrum(int N, int M, int sigma, int use_hamming, float* __restrict__ 
     }
 }
 
-template <typename T, int R, int P, bool HALF /* N <= M/2: zeros behind the tokens; else N = M */, bool PAIRED /* every pair is one aligned access */>
-__global__ void __launch_bounds__(256 * P)
+template <typename T, int R, int LB, int P, bool HALF /* N <= M/2: zeros behind the tokens; else N = M */, bool PAIRED /* every pair is one aligned access */>
+__global__ void __launch_bounds__(16 * LB * P)
 spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, int use_hamming,
          const float* __restrict__ spec /* HALF: [M/2 + 1] */, int n_groups /* of P pairs, per sample */,
          int ld, float* __restrict__ partial /* [B, n_tiles, ld] */, float* __restrict__ gpartial, const TileSync sy,
          float* __restrict__ scores /* [B, N] */)
 {
-    constexpr int M = 256 * R, THREADS = 256 * P, JN = HALF ? R / 2 : R;
-    constexpr int LROW = 272 * P;                // complex values per row of the exchange grid: 16 x (16 + 1 pad) x P
-    constexpr int ROWS = 4 / P, NIT = R / 16;    // rows a wavefront takes at a time, and how often
+    constexpr int COLS = 16 * LB, M = COLS * R, THREADS = COLS * P, JN = HALF ? R / 2 : R;
+    constexpr int LROW = (COLS + LB) * P;        // complex values per row of the exchange grid: a pad of P after every 16 columns
+    constexpr int ROWS = 64 / (LB * P), NIT = R / 16;              // rows a wavefront takes at a time, and how often
     constexpr bool SPEC_LDS = R == 16;           // the spectrum in LDS (registers are short at 1024 threads) or in registers
     extern __shared__ float2 sm[];               // [R][LROW]; the M-entry table while the twiddles are picked
-    float2* twb = sm + R * LROW;                 // [256] (cos, sin)(2 pi i / 256)
-    float* sp = reinterpret_cast<float*>(twb + 256);               // SPEC_LDS: [R k1][16 kb][16 ka]
+    float2* twb = sm + R * LROW;                 // [COLS] (cos, sin)(2 pi i / COLS)
+    float* sp = reinterpret_cast<float*>(twb + COLS);              // SPEC_LDS: [R k1][16 i][LB lw]
     __shared__ int flag;
     const int tid = threadIdx.x, c = tid % P, n2 = tid / P, lane = tid & 63;
     const int n_tiles = gridDim.x;
@@ -240,29 +244,36 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
     // PAIRED: the descriptor ends with the sample's last token (a lane past it, or past D, reads zeros)
     const uint32_t row_bytes = (uint32_t)row_stride * (uint32_t)sizeof(T);
     const uint32_t lane_off = (uint32_t)n2 * row_bytes + (uint32_t)c * 2u * (uint32_t)sizeof(T);
-    auto fetch = [&](int g) {
+    auto fetch = [&](int g, auto from, auto to) {
+        constexpr int J0 = decltype(from)::value, J1 = decltype(to)::value;
         const int d0 = (g * P + c) * 2;
         if constexpr (PAIRED) {
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<T*>(xs) + 2 * P * g, 0, (int)((uint32_t)(N - 1) * row_bytes + (uint32_t)((D - 2 * P * g) * (int)sizeof(T))), 0x00020000);
-            uint32_t off = d0 < D ? lane_off : 0x80000000u;
+            uint32_t off = (d0 < D ? lane_off : 0x80000000u) + (uint32_t)(J0 * COLS) * row_bytes;
 #pragma unroll
-            for (int j = 0; j < JN; ++j) {
+            for (int j = J0; j < J1; ++j) {
                 raw[j] = raw_t::load(r, off);
-                off += 256u * row_bytes;
+                off += (uint32_t)COLS * row_bytes;
             }
         } else {
             const bool live = d0 < D, second = d0 + 1 < D;
             const T* p = xs + (live ? d0 : 0);
 #pragma unroll
-            for (int j = 0; j < JN; ++j) {
-                const int n = 256 * j + n2;
+            for (int j = J0; j < J1; ++j) {
+                const int n = COLS * j + n2;
                 const bool there = live && (!HALF || n < N);
                 raw[j] = there ? raw_t::load(p + (int64_t)n * row_stride, second) : raw_t{};
             }
         }
     };
-    fetch(tile);
+    // fp32 tokens, N = M: all of the next group's beside the values of B and C do not fit, the second half follows them
+    // (4x4096x3584: 174 us with spills, 137)
+    constexpr int EARLY = !HALF && sizeof(T) == 4 ? JN / 2 : JN;
+    using first_t = std::integral_constant<int, 0>;
+    using early_t = std::integral_constant<int, EARLY>;
+    using last_t = std::integral_constant<int, JN>;
+    fetch(tile, first_t{}, last_t{});
 
     // ---- tables: one octant of the circle in fp64, rounded once, the rest by symmetry
     for (int i = tid; i <= M / 8; i += THREADS) {
@@ -290,30 +301,31 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
         }
         return w;
     };
-    const int lw = lane / P % 16;                // b of pass B, ka of pass C
-    const int wrow = (tid >> 6) * ROWS + lane / (16 * P);          // row within an iteration's 16
+    const int lw = lane / P % LB;                // b of pass B; in pass C, a lane holds ka = lw (LB = 16) or ka = 2 lw and 2 lw + 1 (LB = 8)
+    const int wrow = (tid >> 6) * ROWS + lane / (LB * P);          // row within an iteration's 16
+    auto bin = [&](int k1, int i, int l) { return k1 + R * (LB == 16 ? l + 16 * i : 2 * l + (i >> 3) + 16 * (i & 7)); };      // of pass C's value i
     float wr[SPEC_LDS ? 1 : NIT][16];
     if (SPEC_LDS) {
-        for (int i = tid; i < M; i += THREADS) sp[i] = weight((i >> 8) + R * ((i & 15) + 16 * ((i >> 4) & 15)));
+        for (int i = tid; i < M; i += THREADS) sp[i] = weight(bin(i / COLS, i / LB % 16, i % LB));
     } else {
 #pragma unroll
         for (int it = 0; it < NIT; ++it)
 #pragma unroll
-            for (int kb = 0; kb < 16; ++kb) wr[it % (SPEC_LDS ? 1 : NIT)][kb] = weight(it * 16 + wrow + R * (lw + 16 * kb));
+            for (int kb = 0; kb < 16; ++kb) wr[it % (SPEC_LDS ? 1 : NIT)][kb] = weight(bin(it * 16 + wrow, kb, lw));
     }
     __syncthreads();
-    // W_M^{k1 n2} (conjugated on use).  N = M, where a thread holds R tokens and R sums, or fp32 tokens: the upper half as
-    // W_256^{n2} conj(W_M^{(R - k1) n2}), so that the rest stays in registers - what spills goes through L2, and the cache
-    // lines of the tokens, which neighbouring workgroups share, have left it when the next one asks (4x4096x3584 bf16 out of
-    // HBM: 313 MB fetched for 117, {CONV_SPILL_US}).
-    constexpr bool FOLD = !HALF || sizeof(T) == 4;
+    // W_M^{k1 n2} (conjugated on use).  N = M, where a thread holds R tokens and R sums, or fp32 tokens, or eight pairs: the
+    // upper half as W_C^{n2} conj(W_M^{(R - k1) n2}), so that the rest stays in registers - what spills goes through L2, and
+    // the cache lines of the tokens, which neighbouring workgroups share, have left it when the next one asks (4x4096x3584
+    // bf16 out of HBM with all of them kept and spilled: 313 MB fetched for 117, 172 us against 109).
+    constexpr bool FOLD = !HALF || sizeof(T) == 4 || LB == 8;
     constexpr int KEPT = FOLD ? R / 2 + 1 : R;
     cf wa[KEPT], wtop{0.f, 0.f};
 #pragma unroll
     for (int k1 = 1; k1 < KEPT; ++k1) { const float2 w = sm[(k1 * n2) & (M - 1)]; wa[k1] = {w.x, w.y}; }
     if (FOLD) { const float2 w = sm[(R * n2) & (M - 1)]; wtop = {w.x, w.y}; }
     auto tw_a = [&](int k1) { return k1 < KEPT ? wa[k1 < KEPT ? k1 : 0] : cmulc(wtop, wa[k1 < KEPT ? 0 : R - k1]); };
-    if (tid < 256) twb[tid] = sm[tid * R];
+    if (tid < COLS) twb[tid] = sm[tid * R];
     float acc[JN];
 #pragma unroll
     for (int j = 0; j < JN; ++j) acc[j] = 0.f;
@@ -336,7 +348,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
                 col[k1 * LROW] = make_float2(r.x, r.y);
             }
         }
-        if (g + n_tiles < n_groups) fetch(g + n_tiles);            // in flight during B and C
+        if (g + n_tiles < n_groups) fetch(g + n_tiles, first_t{}, early_t{});          // in flight during B and C
         else seen = tiles_look<4>(sy, b, tile, n_tiles);
         __syncthreads();
         // ---- B, C, spectrum, C', B'
@@ -344,30 +356,35 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
         for (int it = 0; it < NIT; ++it) {
             const int k1 = it * 16 + wrow;
             float2* row = sm + k1 * LROW + c;
+            int lt = lw;
+            asm volatile("" : "+v"(lt));         // the places of the twiddles are formed here, not kept
             cf v[16];
 #pragma unroll
-            for (int a = 0; a < 16; ++a) { const float2 q = row[(17 * a + lw) * P]; v[a] = {q.x, q.y}; }
+            for (int a = 0; a < 16; ++a) { const float2 q = row[(a * LB + a * LB / 16 + lw) * P]; v[a] = {q.x, q.y}; }
             fft16<false>(v);
-            twiddled<false, R == 16 ? 4 : 8>(v, twb, lw, [&](int ka, cf r) { row[(17 * ka + lw) * P] = make_float2(r.x, r.y); });
+            twiddled<false, R == 16 ? 4 : 8>(v, twb, [&](int ka) { return ka * lt; }, [&](int ka, cf r) { row[(ka * LB + ka * LB / 16 + lw) * P] = make_float2(r.x, r.y); });
             wave_lds_fence();
 #pragma unroll
             for (int i = 0; i < 16; ++i) { const float2 q = row[(17 * lw + i) * P]; v[i] = {q.x, q.y}; }
-            fft16<false>(v);
+            if constexpr (LB == 16) fft16<false>(v);
+            else { fft8<false>(v); fft8<false>(v + 8); }
 #pragma unroll
             for (int kb = 0; kb < 16; ++kb) {
-                const float w = SPEC_LDS ? sp[(k1 * 16 + kb) * 16 + lw] : wr[it % (SPEC_LDS ? 1 : NIT)][kb];
+                const float w = SPEC_LDS ? sp[(k1 * 16 + kb) * LB + lw] : wr[it % (SPEC_LDS ? 1 : NIT)][kb];
                 v[kb] = {v[kb].x * w, v[kb].y * w};
             }
-            fft16<true>(v);
-            twiddled<true, R == 16 ? 4 : 8>(v, twb, lw, [&](int i, cf r) { row[(17 * lw + i) * P] = make_float2(r.x, r.y); });
+            if constexpr (LB == 16) fft16<true>(v);
+            else { fft8<true>(v); fft8<true>(v + 8); }
+            twiddled<true, R == 16 ? 4 : 8>(v, twb, [&](int i) { return LB == 16 ? i * lt : (i & 7) * (2 * lt + (i >> 3)); }, [&](int i, cf r) { row[(17 * lw + i) * P] = make_float2(r.x, r.y); });
             wave_lds_fence();
 #pragma unroll
-            for (int ka = 0; ka < 16; ++ka) { const float2 q = row[(17 * ka + lw) * P]; v[ka] = {q.x, q.y}; }
+            for (int ka = 0; ka < 16; ++ka) { const float2 q = row[(ka * LB + ka * LB / 16 + lw) * P]; v[ka] = {q.x, q.y}; }
             fft16<true>(v);
 #pragma unroll
-            for (int a = 0; a < 16; ++a) row[(17 * a + lw) * P] = make_float2(v[a].x, v[a].y);
+            for (int a = 0; a < 16; ++a) row[(a * LB + a * LB / 16 + lw) * P] = make_float2(v[a].x, v[a].y);
         }
         __syncthreads();
+        if (EARLY < JN && g + n_tiles < n_groups) fetch(g + n_tiles, early_t{}, last_t{});
         // ---- A'
         if (FOLD) asm volatile("" : "+v"(wtop.x), "+v"(wtop.y));
         {
@@ -388,29 +405,30 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
         float e = acc[j];
         if (P >= 2) e += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(e), 0xB1, 0xf, 0xf, false));    // quad_perm [1,0,3,2]
         if (P >= 4) e += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(e), 0x4E, 0xf, 0xf, false));    // quad_perm [2,3,0,1]
-        const int n = 256 * j + n2;
+        if (P >= 8) e += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(e), 0x141, 0xf, 0xf, false));   // row_half_mirror
+        const int n = COLS * j + n2;
         if (c == 0 && n < ld) tile_store(pout + n, n < N ? e : 0.f);
     }
     tiles_to_scores<THREADS, 4>(partial, gpartial, sy, scores, b, tile, n_tiles, N, ld, &flag);
 }
 
 // ------------------------------------------------------------------ host side
-// R = M / 256 for N tokens; *half: zeros behind the tokens (N <= M / 2), else N = M.  0: too long.
-int spu_conv_rows(int N, bool* half)
+// Points M of the transform for N tokens; *half: zeros behind the tokens (N <= M / 2), else N = M.  0: too long.
+int spu_conv_points(int N, bool* half)
 {
-    for (int R : {16, 32, 64})
-        if (2 * N <= 256 * R || N == 256 * R) { *half = N != 256 * R; return R; }
+    for (int M : {2048, 4096, 8192, 16384})
+        if (2 * N <= M || N == M) { *half = N != M; return M; }
     return 0;
 }
 
-static int conv_pairs(int R) { return 64 / R; }
+static int conv_pairs(int M) { return 16384 / M; }
 
 // Workgroups per sample.  One workgroup fills a compute unit; a workgroup's time is its pair groups plus about one more
 // for tables and hand-over, and the launch takes as many rounds of that as there are multiples of 256 workgroups.
 int spu_conv_tiles(int B, int N, int D)
 {
     bool half;
-    const int R = spu_conv_rows(N, &half), P = conv_pairs(R), ng = (D + 2 * P - 1) / (2 * P);
+    const int P = conv_pairs(spu_conv_points(N, &half)), ng = (D + 2 * P - 1) / (2 * P);
     int best = ng;
     int64_t best_cost = INT64_MAX;
     for (int g = 1; g <= ng && g <= 64; ++g) {
@@ -422,30 +440,31 @@ int spu_conv_tiles(int B, int N, int D)
 }
 
 // us of one call, from measurements: a launch for the spectrum where one is needed, then what a workgroup starts with and its
-// pair groups one after the other.  8x1200x3584 bf16: 148, 1x2000x3584: 37, 4x4096x3584: 129.
-double spu_conv_us(int B, int N, int D)
+// pair groups one after the other.  8x1200x3584 bf16: 143, 1x2000x3584: 35, 4x4096x3584: 101 (fp32: 137), 8x2048x3584: 87
+// (fp32: 110).
+double spu_conv_us(int B, int N, int D, luvc_dtype dt)
 {
     bool half;
-    const int R = spu_conv_rows(N, &half), P = conv_pairs(R), ng = (D + 2 * P - 1) / (2 * P), t = spu_conv_tiles(B, N, D);
+    const int M = spu_conv_points(N, &half), P = conv_pairs(M), ng = (D + 2 * P - 1) / (2 * P), t = spu_conv_tiles(B, N, D);
     const double rounds = (double)(((int64_t)B * t + 255) / 256) * ((ng + t - 1) / t);
-    return (half ? 15.0 : 14.0) + rounds * (half ? 9.6 : 16.5);
+    return half ? 15.0 + rounds * 9.1 : 14.0 + rounds * (M == 2048 ? 10.5 : 12.4) * (dt == LUVC_F32 && M <= 4096 ? 1.35 : 1.0);
 }
 
 size_t spu_conv_spec_bytes(int N)
 {
     bool half;
-    const int R = spu_conv_rows(N, &half);
-    return half ? sizeof(float) * (size_t)(128 * R + 1) : 0;
+    const int M = spu_conv_points(N, &half);
+    return half ? sizeof(float) * (size_t)(M / 2 + 1) : 0;
 }
 
-template <typename T, int R, int P>
+template <typename T, int R, int LB, int P>
 static void conv_launch(const T* x, int B, int N, int D, int64_t row_stride, int sigma, int use_hamming, bool half, bool aligned,
                         const float* spec, float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st)
 {
     const int ng = (D + 2 * P - 1) / (2 * P), ld = spu_conv_ld(N);
-    const size_t lds = sizeof(float2) * (size_t)(R * 272 * P + 256) + (R == 16 ? sizeof(float) * 256 * R : 0);
-    const dim3 grid((unsigned)n_tiles, (unsigned)B), block(256 * P);
-#define LUVC_CONV(HF, AL) LUVC_LAUNCH("spu_conv", (spu_conv<T, R, P, HF, AL>), grid, block, lds, st, x, N, D, row_stride, sigma, use_hamming, spec, ng, ld, partial, gpartial, sy, scores)
+    const size_t lds = sizeof(float2) * (size_t)(R * 17 * LB * P + 16 * LB) + (R == 16 ? sizeof(float) * 16 * LB * R : 0);
+    const dim3 grid((unsigned)n_tiles, (unsigned)B), block(16 * LB * P);
+#define LUVC_CONV(HF, AL) LUVC_LAUNCH("spu_conv", (spu_conv<T, R, LB, P, HF, AL>), grid, block, lds, st, x, N, D, row_stride, sigma, use_hamming, spec, ng, ld, partial, gpartial, sy, scores)
     if (half) { if (aligned) LUVC_CONV(true, true); else LUVC_CONV(true, false); }
     else      { if (aligned) LUVC_CONV(false, true); else LUVC_CONV(false, false); }
 #undef LUVC_CONV
@@ -455,21 +474,23 @@ luvc_status spu_score_conv(const void* x, int B, int N, int D, int64_t row_strid
                            float* spec, float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st)
 {
     bool half;
-    const int R = spu_conv_rows(N, &half);
+    const int M = spu_conv_points(N, &half);
     const size_t es = dt == LUVC_F32 ? 4 : 2;
     // a sample, rounded up to M tokens, has to stay below the offset that marks a lane without channels
-    const bool aligned = (row_stride % 2 == 0) && ((uintptr_t)x % (2 * es) == 0) && (D % 2 == 0) && (int64_t)256 * R * row_stride * (int64_t)es < ((int64_t)1 << 31);
+    const bool aligned = (row_stride % 2 == 0) && ((uintptr_t)x % (2 * es) == 0) && (D % 2 == 0) && (int64_t)M * row_stride * (int64_t)es < ((int64_t)1 << 31);
     if (half) {
-        const int M = 256 * R;
         LUVC_LAUNCH("spu_conv_spectrum", spu_conv_spectrum, dim3((unsigned)(M / 2 / kSpecBins + 1)), dim3(256), 0, st, N, M, sigma, use_hamming, spec);
     }
+#define LUVC_CONV_S(TT, R, LB, P) conv_launch<TT, R, LB, P>((const TT*)x, B, N, D, row_stride, sigma, use_hamming, half, aligned, spec, partial, gpartial, sy, n_tiles, scores, st)
 #define LUVC_CONV_R(TT) do { \
-        if (R == 16)      conv_launch<TT, 16, 4>((const TT*)x, B, N, D, row_stride, sigma, use_hamming, half, aligned, spec, partial, gpartial, sy, n_tiles, scores, st); \
-        else if (R == 32) conv_launch<TT, 32, 2>((const TT*)x, B, N, D, row_stride, sigma, use_hamming, half, aligned, spec, partial, gpartial, sy, n_tiles, scores, st); \
-        else              conv_launch<TT, 64, 1>((const TT*)x, B, N, D, row_stride, sigma, use_hamming, half, aligned, spec, partial, gpartial, sy, n_tiles, scores, st); \
+        if (M == 2048)      LUVC_CONV_S(TT, 16, 8, 8); \
+        else if (M == 4096) LUVC_CONV_S(TT, 16, 16, 4); \
+        else if (M == 8192) LUVC_CONV_S(TT, 32, 16, 2); \
+        else                LUVC_CONV_S(TT, 64, 16, 1); \
     } while (0)
     if (dt == LUVC_F32) LUVC_CONV_R(float); else LUVC_CONV_R(bf16_t);
 #undef LUVC_CONV_R
+#undef LUVC_CONV_S
     return check_launch("spu score (convolution)");
 }
 

@@ -1,5 +1,5 @@
 // Register-level pieces shared by the transform kernels of the SPU score (paper Section 3.3): complex arithmetic, the
-// radix-4 butterfly and the 16-point DFT.
+// radix-4 butterfly, the 8- and the 16-point DFT.
 #pragma once
 #include "common.hpp"
 
@@ -54,6 +54,22 @@ __device__ __forceinline__ void fft16(cf (&v)[16])
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int p = q + 1; p < 4; ++p) { const cf s = v[4 * q + p]; v[4 * q + p] = v[4 * p + q]; v[4 * p + q] = s; }
+}
+
+// 8-point DFT of v[0], v[1], ... in registers, natural order in, natural order out
+template <bool INV>
+__device__ __forceinline__ void fft8(cf* v)
+{
+    constexpr float r = 0.7071067811865476f;
+    cf e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    bf4<INV>(e[0], e[1], e[2], e[3]);
+    bf4<INV>(o[0], o[1], o[2], o[3]);
+    auto tw = [](cf a, cf w) { return INV ? cmulc(a, w) : cmul(a, w); };
+    o[1] = tw(o[1], cf{r, -r});
+    o[2] = INV ? cf{-o[2].y, o[2].x} : cf{o[2].y, -o[2].x};        // W8^2 = -i
+    o[3] = tw(o[3], cf{-r, -r});
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { v[k] = e[k] + o[k]; v[k + 4] = e[k] - o[k]; }
 }
 
 // cos(2 pi i / 64)

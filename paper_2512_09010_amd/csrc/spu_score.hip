@@ -175,11 +175,11 @@ tile_tag_t spu_next_tag()
 // Which kernel is quickest: measured times (us, one call) as functions of the sizes; spu_circ: 6 (fp32: 9) and its products at
 // 1.1e15 flop/s (8x205x3584 bf16: 15, 1x512x3584: 16, 4x861x1408: 36), the others beside their launchers.
 static double circ_work_us(int64_t B, int N, int D, luvc_dtype dt) { return (dt == LUVC_F32 ? 12.0 : 6.0) * N * N * (double)D * (double)B / 1.1e9; }
-static SpuPath long_path(int B, int N, int D, int sigma, double* us)
+static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, double* us)
 {
     bool half;
-    const bool conv = spu_conv_rows(N, &half) != 0, fft = spu_fft_supported(N, sigma);
-    const double f = fft ? spu_fft_us(B, N, D, sigma) : 0.0, c = conv ? spu_conv_us(B, N, D) : 0.0;
+    const bool conv = spu_conv_points(N, &half) != 0, fft = spu_fft_supported(N, sigma);
+    const double f = fft ? spu_fft_us(B, N, D, sigma) : 0.0, c = conv ? spu_conv_us(B, N, D, dt) : 0.0;
     if (fft && (!conv || f <= c)) { *us = f; return SpuPath::Fft; }
     *us = c;
     return conv ? SpuPath::Conv : SpuPath::Dense;
@@ -188,14 +188,14 @@ static SpuPath long_path(int B, int N, int D, int sigma, double* us)
 static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, bool circ)
 {
     double us;
-    const SpuPath other = long_path(B, N, D, sigma, &us);
+    const SpuPath other = long_path(B, N, D, sigma, dt, &us);
     return circ && N <= kCircMaxN && circ_work_us(B, N, D, dt) + (dt == LUVC_F32 ? 9.0 : 6.0) <= us ? SpuPath::Circ : other;
 }
 // in a launch that several runs share, a run adds its products and nothing else
 bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt)
 {
     double us;
-    (void)long_path(B, N, D, sigma, &us);
+    (void)long_path(B, N, D, sigma, dt, &us);
     return N <= kCircMaxN && circ_work_us(B, N, D, dt) <= us;
 }
 
