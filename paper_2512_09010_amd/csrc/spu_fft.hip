@@ -262,14 +262,32 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
         if (tid < N1) tw1[tid] = tw[tid * N2];
         __syncthreads();
     }
-    // without the register copy: walk the N1 table, i = 0, 1, 2, ... in order (o1 = t i mod N1)
-    int o1 = 0;
-    auto tw1_next = [&](int i) {
-        if (kHoist) return w1[i];
-        const float2 w = tw1[o1];
-        o1 += t;
-        if (o1 >= N1) o1 -= N1;
-        return cf{w.x, w.y};
+    // v[i] times W_N1^{-+ t i} to its place in the exchange buffer.  Without the register copy the twiddles come out of
+    // the N1 table eight at a time: the compiler has to assume that a table read and a write into the buffer meet, so
+    // read one by one each of them would wait for its own trip to LDS.
+    auto to_exchange = [&](auto& v, auto count, auto inv) {
+        constexpr int n = decltype(count)::value, G = kHoist ? n : sizeof(T) == 4 ? 8 : 1;
+        int o1 = 0;                                              // t i mod N1
+#pragma unroll
+        for (int i0 = 0; i0 < n; i0 += G) {
+            cf w[G];
+#pragma unroll
+            for (int i = 0; i < G && i0 + i < n; ++i) {
+                if (kHoist) w[i] = w1[i0 + i];
+                else {
+                    const float2 q = tw1[o1];
+                    w[i] = {q.x, q.y};
+                    o1 += t;
+                    if (o1 >= N1) o1 -= N1;
+                }
+            }
+            if (!kHoist && G > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < G && i0 + i < n; ++i) {
+                const cf r = decltype(inv)::value ? cmul(v[i0 + i], w[i]) : cmulc(v[i0 + i], w[i]);
+                xbuf[(i0 + i) * kRowPad + t * kPairs + c] = make_float2(r.x, r.y);
+            }
+        }
     };
 
     // ------------------------------------------------------------------ forward (Eq. 4 on the pass band)
@@ -282,12 +300,7 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
         if (n2 + 1 < N2) load_sub(n2 + 1);       // next subsequence in flight while this one is transformed
         if (rdx) {
             fft16<false>(v);                     // over j -> ka
-            o1 = 0;
-#pragma unroll
-            for (int ka = 0; ka < 16; ++ka) {
-                const cf r = cmulc(v[ka], tw1_next(ka));         // * W_N1^{t ka}
-                xbuf[ka * kRowPad + t * kPairs + c] = make_float2(r.x, r.y);
-            }
+            to_exchange(v, std::integral_constant<int, 16>{}, std::false_type{});      // * W_N1^{t ka}
         }
         __syncthreads();
         cf u[Q];
@@ -334,12 +347,7 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
             }
         }
         dftq<Q, true>::run(u);                   // over kb -> residue s
-        o1 = 0;
-#pragma unroll
-        for (int s = 0; s < Q; ++s) {
-            const cf r = cmul(u[s], tw1_next(s));               // * W_N1^{-s ka}
-            xbuf[s * kRowPad + t * kPairs + c] = make_float2(r.x, r.y);
-        }
+        to_exchange(u, std::integral_constant<int, Q>{}, std::true_type{});            // * W_N1^{-s ka}
         __syncthreads();
         if (rdx) {
             cf v[16];
