@@ -11,7 +11,7 @@
 // Bound: latency.  A pass reads its tokens once, but a line is a chain of memory trips - ids, tokens, merged rows - with
 // the decisions between them; as many wavefronts as a line has groups of four tokens share it, so that each trip is made once.
 // 12 x 32 x 32 x 1024 bf16, three operations of (W,2),(H,2): 157 us as three launches per pass (norms and products,
-// decisions, a merge that rewrote the whole grid), {ADJ_US} us as one.
+// decisions, a merge that rewrote the whole grid), 75 us as one.
 #include "common.hpp"
 #include "oim.hpp"
 #include "oim_lazy.hpp"

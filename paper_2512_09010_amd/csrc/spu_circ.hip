@@ -20,7 +20,7 @@
 // trip to memory each way, no atomics; nothing has to be set up, and a captured launch replayed with its tag starts over.
 //
 // Bound: matrix cores for N near kCircMaxN (6 N^2 D flops per bf16 sample, 12 for fp32), latency for short samples.
-// {CIRC_MEASURED}
+// 1x729x3584 bf16: 25 us (4096-point transform: 39), 8x205x3584: 15, 8x143x3584: 12, 4x861x1408: 36.
 #include "common.hpp"
 #include "spu.hpp"
 #include "spu_taps.hpp"
