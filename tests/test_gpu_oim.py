@@ -303,3 +303,28 @@ def test_packed_bf16_dot_rounds_like_the_screening_bound_assumes():
         bound = 2 * words * 2.0 ** -24 * mag
         assert (np.abs(got - exact) <= bound).all(), float((np.abs(got - exact) / bound).max())
         print(f"[fdot2] worst error / bound = {float((np.abs(got - exact) / bound).max()):.3f}", flush=True)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,W,D,passes", [
+    (1, 2, 3, 8, [(W_AX, 1)]), (1, 3, 5, 16, [(W_AX, 2), (H_AX, 1)]),            # two and three sources, the last without a right neighbour
+    (2, 3, 64, 24, [(W_AX, 31)]), (2, 2, 65, 24, [(W_AX, 1), (W_AX, 31)]),       # around 32 sources
+    (1, 127, 2, 16, [(H_AX, 63)]), (1, 128, 3, 16, [(H_AX, 2), (H_AX, 62)]),     # the longest lines of one launch per pass
+    (1, 2, 129, 16, [(W_AX, 2)]),                                                # and one token more
+    (1, 4, 13, 1544, [(W_AX, 2), (H_AX, 1)]),                                    # rows that take several rounds of loads
+])
+def test_few_tokens_out_of_a_line(oracle, dtype, B, H, W, D, passes):
+    """Adjacent matching that leaves some sources of a line: one launch per pass up to 128 tokens.  Aligned tokens and a copy
+    8 bytes off (three launches per pass) give the same."""
+    rng = np.random.default_rng(H * 1000 + W * 10 + D)
+    x = wl.cast_io((wl.smooth_field(rng, B, H, W, D, 1.5) + 0.5 * rng.standard_normal((B, H, W, D))).astype(np.float32), dtype)
+    sizes = rng.integers(1, 6, (B, H, W))
+    out, _ = run_case(oracle, x, dtype, passes, sizes=sizes, tag="few")
+    xd = to_dev(x, dtype)
+    off = 8 // xd.element_size()
+    flat = torch.empty(xd.numel() + off, dtype=xd.dtype, device="cuda")
+    flat[off:] = xd.reshape(-1)
+    other = lv.luvc_oim_merge(flat[off:].view(B, H, W, D), passes, sizes=torch.from_numpy(sizes.astype(np.int32)).cuda())
+    torch.cuda.synchronize()
+    for k in ("x", "sizes", "merged_map", "kept_map"):
+        assert torch.equal(out[k], other[k]), k

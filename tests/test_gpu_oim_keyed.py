@@ -242,3 +242,15 @@ def test_keyed_and_wide_calls_on_seeded_random_cases(oracle, block):
         keys = wl.smooth_field(rng, B, H, W, Dm, 2.0) * (0.0 if kind == 2 else 1.0) + 1.0 + [0.3, 1e-3, 0.0][kind] * rng.standard_normal((B, H, W, Dm)).astype(np.float32)
         sizes = rng.integers(1, 4, (B, H, W)) if seed % 3 == 0 else None
         run_keyed(oracle, x, wl.cast_io(keys.astype(np.float32), dtype), dtype, passes, radius, sizes=sizes, tag=f"fuzz{seed} kind{kind}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,W,D,Dm,passes", [
+    (2, 3, 65, 24, 8, [(W_AX, 2), (H_AX, 1), (W_AX, 30)]), (1, 5, 9, 16, 1544, [(W_AX, 2), (H_AX, 2)]), (1, 9, 4, 1544, 16, [(H_AX, 4), (W_AX, 1)]),
+])
+def test_keyed_few_tokens_out_of_a_line(oracle, dtype, B, H, W, D, Dm, passes):
+    """Adjacent matching on keys, one launch per pass: lines around a wavefront, rows that take several rounds of loads."""
+    rng = np.random.default_rng(H * 1000 + W * 10 + D + Dm)
+    x = wl.cast_io(rng.standard_normal((B, H, W, D)).astype(np.float32), dtype)
+    keys = wl.cast_io(rng.standard_normal((B, H, W, Dm)).astype(np.float32), dtype)
+    run_keyed(oracle, x, keys, dtype, passes, 1, sizes=rng.integers(1, 6, (B, H, W)), tag="few")

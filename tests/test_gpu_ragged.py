@@ -129,3 +129,20 @@ def test_ragged_errors():
         lv.luvc_oim_merge_ragged(x, [(2, 5), (2, 5)], [[(1, 2)], [(1, 4)]])    # m too large for the second image
     with pytest.raises(lv.LuvcError):
         lv.luvc_oim_plan_anyres(0, 4, 10)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_oim_more_runs_than_a_launch_takes(oracle, dtype):
+    """Runs that share launches: more of them than one argument list holds, images that stay as they are, take one pass, a pair
+    of passes or several steps, and rows that no such launch takes."""
+    shapes = [(1 + i % 9, 3 + (5 * i) % 23) for i in range(40)] + [(31, 18), (18, 31), (26, 26)]
+    oim_ragged_case(oracle, shapes, 40, dtype, 36, 11, with_sizes=True)
+    oim_ragged_case(oracle, shapes[30:], 33, dtype, 36, 12, with_sizes=False)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_spu_more_runs_than_a_launch_takes(oracle, dtype):
+    """More runs of short samples than one argument list holds, with samples of other kernels between them."""
+    lengths = list(range(1, 71)) + [1030, 1030] + list(range(130, 70, -7)) + [4100, 5, 5, 1024]
+    spu_ragged_case(oracle, lengths, 34, dtype, 0.2, 21, origin_shift=3)
+    spu_ragged_case(oracle, lengths[60:80], 33, dtype, 0.3, 22)

@@ -325,3 +325,35 @@ def test_score_fuzz_on_lengths_with_a_thinned_inverse(oracle, seed):
             x = np.cumsum(x, axis=1) / np.sqrt(N)
         pad = int(rng.choice([0, 0, 3, 8]))
         score_case(oracle, wl.cast_io(x.astype(np.float32), dtype), dtype, sigma, True, f"thin-fuzz{seed}.{it} kind={kind}", stride_pad=pad)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,N,D,sigma", [
+    (1, 1, 2, 0), (1, 2, 8, 1), (3, 3, 6, 1), (2, 15, 64, 7), (1, 16, 254, 8), (3, 17, 258, 2),      # one step of 16 tokens and one more
+    (2, 31, 256, 15), (1, 33, 512, 16), (5, 65, 34, 32), (1, 127, 1026, 9), (2, 129, 258, 64),       # around a workgroup's tokens and channels
+    (1, 1022, 130, 511), (1, 1023, 34, 0), (1, 1024, 66, 512),                                       # the longest samples
+])
+def test_score_as_a_circulant_product(oracle, dtype, B, N, D, sigma):
+    """Samples of up to 1024 tokens on the matrix cores: edges of its tiles, of the pass band (2 sigma = N included), of the
+    channels a wavefront takes; large token norms beside small ones."""
+    rng = np.random.default_rng(N * 13 + D)
+    x = rng.standard_normal((B, N, D)) * np.exp(2.0 * rng.standard_normal((B, N, 1)))
+    x = wl.cast_io(x.astype(np.float32), dtype)
+    xd, got, _ = score_case(oracle, x, dtype, sigma, True, "circulant")
+    for _ in range(3):                                                           # same bits whichever workgroup adds up
+        assert torch.equal(lv.luvc_spu_score(xd, sigma, True), got)
+    score_case(oracle, x, dtype, sigma, False, "circulant-rect", stride_pad=10)
+
+
+@pytest.mark.parametrize("N,k", [(1024, 1024), (1025, 1), (1025, 1025), (2049, 700), (4095, 3), (4096, 2049)])
+def test_prune_around_the_sizes_of_its_workgroups(oracle, N, k):
+    """256 threads up to 1024 tokens, 1024 beyond: selection (ties, signed zeros, infinities) and the rows that follow it."""
+    rng = np.random.default_rng(N * 5 + k)
+    sc = adversarial_scores(N, rng)
+    x = torch.from_numpy(rng.standard_normal((sc.shape[0], N, 24)).astype(np.float32)).to(torch.bfloat16).cuda()
+    print(f"[prune] N={N} k={k}", flush=True)
+    pr = lv.luvc_spu_prune(x, torch.from_numpy(sc).cuda(), k)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(pr["kept_idx"].cpu().numpy(), oracle.spu_prune(sc.astype(np.float64), k)["kept_idx"])
+    idx = pr["kept_idx"].long()
+    assert torch.equal(pr["x"], torch.gather(x, 1, idx[:, :, None].expand(-1, -1, 24)))

@@ -36,3 +36,16 @@ def test_many_channel_groups_per_workgroup(oracle):
     from paper_2512_09010_amd import binding as lv
     for _ in range(3):
         assert torch.equal(lv.luvc_spu_score(xd, 9, True), got)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,N,D,sigma,pad", [
+    (1, 1024, 33, 512, 0), (2, 1023, 15, 511, 1), (1, 513, 17, 3, 0), (3, 1, 3, 0, 0), (1, 9, 5, 4, 0),      # zeros behind the tokens, single elements
+    (8, 1000, 514, 100, 0), (8, 1021, 500, 1, 4),                                                            # pairs, several groups of eight
+    (1, 2048, 34, 1024, 0), (3, 2048, 30, 200, 0), (1, 2048, 15, 300, 1),                                    # N = M
+])
+def test_score_on_2048_points(oracle, dtype, B, N, D, sigma, pad):
+    rng = np.random.default_rng(N * 11 + D)
+    x = wl.cast_io(rng.standard_normal((B, N, D)).astype(np.float32), dtype)
+    score_case(oracle, x, dtype, sigma, True, "2048", stride_pad=pad)
+    score_case(oracle, x, dtype, sigma, False, "2048-rect", stride_pad=pad)
