@@ -5,19 +5,24 @@
 // Eq. 5 is real and symmetric in k, so the filter is a real linear operator and Re / Im of the
 // filtered z are the two filtered channels: no unpacking is ever needed.
 //
-// Transform decomposition along the token index, n = N2 * n1 + n2 (n1 < N1, n2 < N2):
-//   Eq. 4 on the pass band:  F[k] = sum_{n2} W_N^{k n2} Y_{n2}[k mod N1],  |k| <= sigma,
-//                            Y_{n2} = N1-point DFT of the stride-N2 subsequence n2;
-//   Eq. 6:                   F[k] *= M[|k|] / N;
-//   Eq. 7:                   z'[N2 n1 + n2] = N1-point inverse DFT over k1 of F[k] W_N^{-k n2};
-//   Eq. 8:                   |z'|^2 summed over the channel pairs of the tile.
-// Each N1-point transform is 16 x Q (n1 = Q j + t, k1 = ka + 16 kb): a radix-16 butterfly over j held
-// in registers, the twiddle W_N1^{t ka}, one exchange through LDS, and a Q-point transform over t
-// (radix-16 again, or 3 x 5 by the prime-factor map, or 3 x 3).  A workgroup owns 16 channel pairs
-// (32 channels, 64-byte row segments for bf16); thread (c, t) = (pair, residue): Q of the 16 residue
-// threads hold 16 points each for the radix-16 side, all 16 hold Q points each for the other side.
-// The pass-band accumulators F stay in registers across the N2 subsequences, so x is read exactly
-// once and nothing but N floats per tile is written.
+// Transform decomposition along the token index, n = N2 (16 j + t) + n2 (n2 < N2, j < Q, t < 16), bins k1 = a + Q b of an
+// N1-point transform (a < Q, b < 16):
+//   Eq. 4 on the pass band:  A[a] = Q-point DFT over j of the tokens of residue t, subsequence n2;
+//                            Y[a + Q b] = 16-point DFT over t of A_t[a] W_N1^{t a};
+//                            F <- F W_N^k + Y, n2 falling (Horner), k = a + Q b, for b >= 8 less N1: |k| <= sigma;
+//   Eq. 6:                   F *= M[|k|] / N;
+//   Eq. 7:                   16-point DFT over b of F W_N^{-(k - a) n2}, then Q-point DFT over a of its outputs t times
+//                            W_N^{-a (n2 + N2 t)}: the filtered tokens of residue t, subsequence n2;
+//   Eq. 8:                   |.|^2 summed over the channel pairs of the tile.
+// A workgroup owns 16 channel pairs (32 channels, 64-byte row segments for bf16).  Thread (c, r) = (pair, 0 .. 15) is residue
+// t = r on the token side, Q points, and (if r < Q) output a = r on the bin side, 16 points; one exchange through LDS in
+// between.  The twiddles of a 16-point transform (and of a 16-point Q) are geometric in its index, so they split into
+// those of its two radix-4 levels and go into the additions there (fft16_tw); those over b depend on n2 only.
+// The pass-band accumulators F stay in registers across the N2 subsequences, so x is read exactly once and nothing but
+// N floats per tile is written.
+// Bound: fp32 vector arithmetic, about 900 instructions per wavefront and subsequence.  With the twiddles between the sides
+// as multiplications of their own, and the accumulation's looked up per subsequence, it was 1160: 8x1024x3584 bf16 49 us
+// (42 now), 16x720x4096 72 (60), 4x2048x3584 47 (42), 8x1440x3584 fp32 76 (67).
 //
 // (An inverse on every second or fourth subsequence, with the energies between interpolated from the band limit, needs
 // tokens of even energy to stay within fp32 error and otherwise has to run in full after all: on tokens whose norms
@@ -39,9 +44,8 @@ __device__ __forceinline__ void dft3(cf& a, cf& b, cf& c)
 {
     constexpr float s3 = 0.8660254037844386f;
     const cf t = b + c, m{a.x - 0.5f * t.x, a.y - 0.5f * t.y};
-    const cf d{(b.x - c.x) * s3, (b.y - c.y) * s3};
-    const cf r = INV ? cf{-d.y, d.x} : cf{d.y, -d.x};          // d * (+i) or d * (-i)
-    a = a + t; b = m + r; c = m - r;
+    const cf d = b - c, r = INV ? cf{-d.y, d.x} : cf{d.y, -d.x};       // d * (+i) or d * (-i)
+    a = a + t; b = axpy(s3, r, m); c = axpy(-s3, r, m);
 }
 
 // 5-point DFT
@@ -144,19 +148,28 @@ template <> struct pair_io<float> {
 constexpr int kPairs = 16;                       // channel pairs per workgroup
 constexpr int kRowPad = 16 * kPairs + kPairs;    // float2 per exchange row: 16 x 16 pairs + one pad group
 
-// sum over the 16 lanes of a DPP row; every lane of the row ends up with the total, fixed order
-__device__ __forceinline__ float row16_sum(float v)
+// Lane c of a DPP row of 16 gets the sum of e[c] over the 16 lanes, fixed order: halves, then quarters of the list go with
+// the halves and quarters of the row, so that 16 sums take 45 instructions (64 one by one, into every lane).
+__device__ __forceinline__ float row16_scatter(const float (&e)[16], bool odd, bool upper /* bits 0 and 1 of the lane */)
 {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, false));    // quad_perm [1,0,3,2]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, false));    // quad_perm [2,3,0,1]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false));   // row_half_mirror
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, false));   // row_mirror
-    return v;
+    auto dpp = [](float v, auto ctrl) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false)); };
+    auto banks = [](float lo, float hi, auto mask) { return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(lo), __float_as_int(hi), 0xE4, 0xf, decltype(mask)::value, false)); };
+    using mirror = std::integral_constant<int, 0x140>;
+    using half_mirror = std::integral_constant<int, 0x141>;
+    using swap1 = std::integral_constant<int, 0xB1>;             // quad_perm [1,0,3,2]
+    using swap2 = std::integral_constant<int, 0x4E>;             // quad_perm [2,3,0,1]
+    float r[8], q[4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = banks(e[i] + dpp(e[i], mirror{}), e[i + 8] + dpp(e[i + 8], mirror{}), std::integral_constant<int, 0xc>{});
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i] = banks(r[i] + dpp(r[i], half_mirror{}), r[i + 4] + dpp(r[i + 4], half_mirror{}), std::integral_constant<int, 0xa>{});
+    const float a = (odd ? q[1] : q[0]) + dpp(odd ? q[0] : q[1], swap1{}), b = (odd ? q[3] : q[2]) + dpp(odd ? q[2] : q[3], swap1{});
+    return (upper ? b : a) + dpp(upper ? a : b, swap2{});
 }
 
 }  // namespace
 
-template <typename T, int Q, bool POW2, bool ALIGNED>
+template <typename T, int Q, bool ALIGNED>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((Q == 9 || (Q == 15 && sizeof(T) == 2)) ? 3 : 2)))
 spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, int use_hamming,
            float* __restrict__ partial /* [B, n_tiles, N] */, float* __restrict__ gpartial /* [B, n_groups, N] */,
@@ -165,22 +178,21 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
     using pio = pair_io<T>;
     constexpr int N1 = 16 * Q;
     extern __shared__ float2 smem[];
-    float2* xbuf = smem;                         // [16][kRowPad]  exchange between the two passes
+    float2* xbuf = smem;                         // [16][kRowPad]  exchange between the two sides
     float2* tw = smem + 16 * kRowPad;            // [N]    (cos, sin)(2 pi i / N)
-    float2* tw1 = tw + N;                        // [N1]   (cos, sin)(2 pi i / N1)
-    float* eperm = reinterpret_cast<float*>(tw1 + N1);      // [N2][Q t][16 j] energies of this tile
-    float* gm = eperm + N;                       // [sigma + 1]  M[f] / N  (Eq. 5 with the 1/N of Eq. 7)
+    float* eperm = reinterpret_cast<float*>(tw + N);        // [N2][16 t][16 j] energies of this tile
+    float* gm = eperm + N / Q * 16;              // [sigma + 1]  M[f] / N  (Eq. 5 with the 1/N of Eq. 7)
     __shared__ int is_last;
-    const int tid = threadIdx.x, c = tid & 15, t = tid >> 4;
+    const int tid = threadIdx.x, c = tid & 15, r = tid >> 4;
     // neighbouring channel tiles share 128-byte lines of every token row: keep them on one XCD
     const int n_tiles = gridDim.x;
     const unsigned item = xcd_contiguous(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
     const int tile = item % n_tiles, b = item / n_tiles;
-    const int N2 = N / N1;
+    const int N2 = N / N1, n16 = N / 16;
 
     const int d0 = tile * 32 + 2 * c;
-    const bool rdx = Q == 16 || t < Q;           // this thread takes part in the radix-16 side
-    const bool live = d0 < D && rdx, second = d0 + 1 < D;
+    const bool bins = Q == 16 || r < Q;          // this thread takes part on the bin side
+    const bool live = d0 < D, second = d0 + 1 < D;
     const uint32_t es = (uint32_t)sizeof(T);
     const uint32_t row_bytes = (uint32_t)row_stride * es;
     // resource over sample b (N rows); lanes without a channel pair point past its end
@@ -189,36 +201,13 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
         const_cast<T*>(x) + (int64_t)b * N * row_stride, 0, (int)(span > 0x7fffffffull ? 0x7fffffffull : span), 0x00020000);
     const uint32_t lane_off = live ? (uint32_t)d0 * es : 0x80000000u;
 
-    // this thread's output bins of every N1-point transform: k1 = t + 16 kb (t doubles as ka)
-    int kpos[Q], ph[Q];
-    cf F[Q];
-#pragma unroll
-    for (int kb = 0; kb < Q; ++kb) {
-        const int k1 = t + 16 * kb;
-        kpos[kb] = 8 * (k1 <= sigma ? k1 : N - N1 + k1);  // k mod N (bins outside the band are masked later), as a byte offset into tw
-        ph[kb] = 0;                                        // (k * n2) mod N, likewise
-        F[kb] = {0.f, 0.f};
-    }
-    // W_N^{+-k n2} for bin kb of this thread: a power-of-two N takes the product modulo N directly, any other N
-    // keeps a running sum
-    auto tw_k = [&](int kb, int n2) {
-        int off;
-        if (POW2) off = (int)__umul24((unsigned)kpos[kb], (unsigned)n2) & (8 * N - 1);
-        else {
-            off = ph[kb];
-            ph[kb] += kpos[kb];
-            if (ph[kb] >= 8 * N) ph[kb] -= 8 * N;
-        }
-        return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(tw) + off);
-    };
-
-    typename pio::raw_t raw[16];
+    typename pio::raw_t raw[Q];
     auto load_sub = [&](int n2) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
-            raw[j] = pio::load(rsrc, lane_off + (uint32_t)(N2 * (Q * j + t) + n2) * row_bytes, second, ALIGNED);
+        for (int j = 0; j < Q; ++j)
+            raw[j] = pio::load(rsrc, lane_off + (uint32_t)(N2 * (16 * j + r) + n2) * row_bytes, second, ALIGNED);
     };
-    load_sub(0);
+    load_sub(N2 - 1);
     // Tables, built while the first loads are in flight.  One octant of the circle is evaluated in fp64
     // and rounded once; the other seven follow by symmetry (8 divides N).
     {
@@ -245,136 +234,118 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
         }
     }
     __syncthreads();
-    // W_N1^{t i}, i < 16: the twiddles between the two passes of every N1-point transform, both directions
-    constexpr bool kHoist = Q == 16;
-    cf w1[16];
-    if (kHoist) {
-        int e1 = 0;
+    auto table = [&](int i) { const float2 q = tw[i]; return cf{q.x, q.y}; };
+    // h^j = W_N^{j p}, j < 16, as fft16_tw takes them; p < N / Q: none of the places reaches N
+    auto powers = [&](int p, cf (&lo)[3], cf (&hi)[4][3]) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float2 w = tw[e1 * N2];
-            w1[i] = {w.x, w.y};
-            e1 += t;
-            if (e1 >= N1) e1 -= N1;
-        }
-    }
-    else {
-        if (tid < N1) tw1[tid] = tw[tid * N2];
-        __syncthreads();
-    }
-    // v[i] times W_N1^{-+ t i} to its place in the exchange buffer.  Without the register copy the twiddles come out of
-    // the N1 table eight at a time: the compiler has to assume that a table read and a write into the buffer meet, so
-    // read one by one each of them would wait for its own trip to LDS (8x1440x3584 fp32: 83 us, 75 in eights).  With bf16
-    // tokens the three wavefronts per SIMD hide that, and have no registers for eight more (16x720x4096: 72 and 78 us).
-    auto to_exchange = [&](auto& v, auto count, auto inv) {
-        constexpr int n = decltype(count)::value, G = kHoist ? n : sizeof(T) == 4 ? 8 : 1;
-        int o1 = 0;                                              // t i mod N1
+        for (int i = 1; i < 4; ++i) lo[i - 1] = table(4 * i * p);
 #pragma unroll
-        for (int i0 = 0; i0 < n; i0 += G) {
-            cf w[G];
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int i = 0; i < G && i0 + i < n; ++i) {
-                if (kHoist) w[i] = w1[i0 + i];
-                else {
-                    const float2 q = tw1[o1];
-                    w[i] = {q.x, q.y};
-                    o1 += t;
-                    if (o1 >= N1) o1 -= N1;
-                }
-            }
-            if (!kHoist && G > 1) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < G && i0 + i < n; ++i) {
-                const cf r = decltype(inv)::value ? cmul(v[i0 + i], w[i]) : cmulc(v[i0 + i], w[i]);
-                xbuf[(i0 + i) * kRowPad + t * kPairs + c] = make_float2(r.x, r.y);
-            }
-        }
+            for (int i = 1; i < 4; ++i) hi[q][i - 1] = table(i * (p + q * n16));
     };
 
     // ------------------------------------------------------------------ forward (Eq. 4 on the pass band)
-    // The subsequence n2 = 0 carries the twiddle W_N^0 = 1: its pass is a copy of the loop body without the
-    // pass-band multiplications (the same holds for the inverse below).
-    auto forward = [&](int n2, auto first) {
-        cf v[16];
+    cf F[16];
+    {
+        // W_N1^{t a}, and W_N^k of this thread's bins: in registers for Q = 16, from the table in every pass where that
+        // keeps a third wavefront per SIMD
+        constexpr bool kHold = Q == 16;
+        cf lo[3], hi[4][3], wk[16];
+        const int a = bins ? r : 0;
+        powers(N2 * a, lo, hi);
+        auto bin_turn = [&](int kb) { return table(a + Q * kb + (kb < 8 ? 0 : N - N1)); };
+        if (kHold) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = pio::widen(raw[j]);
-        if (n2 + 1 < N2) load_sub(n2 + 1);       // next subsequence in flight while this one is transformed
-        if (rdx) {
-            fft16<false>(v);                     // over j -> ka
-            to_exchange(v, std::integral_constant<int, 16>{}, std::false_type{});      // * W_N1^{t ka}
+            for (int kb = 0; kb < 16; ++kb) wk[kb] = bin_turn(kb);
         }
-        __syncthreads();
-        cf u[Q];
+        // The last subsequence comes first and starts the sums: its pass is a copy of the loop body without them.
+        auto forward = [&](int n2, auto first) {
+            cf u[Q];
 #pragma unroll
-        for (int s = 0; s < Q; ++s) { const float2 q = xbuf[t * kRowPad + s * kPairs + c]; u[s] = {q.x, q.y}; }
-        __syncthreads();
-        dftq<Q, false>::run(u);                  // over the residue -> kb ; u[kb] = Y[t + 16 kb]
+            for (int j = 0; j < Q; ++j) u[j] = pio::widen(raw[j]);
+            if (n2 > 0) load_sub(n2 - 1);        // next subsequence in flight while this one is transformed
+            dftq<Q, false>::run(u);              // over j -> a
 #pragma unroll
-        for (int kb = 0; kb < Q; ++kb) {
-            if constexpr (decltype(first)::value) {
-                F[kb] = u[kb];
-                ph[kb] = kpos[kb];               // (k * 1) mod N for the next subsequence
+            for (int i = 0; i < Q; ++i) xbuf[i * kRowPad + r * kPairs + c] = make_float2(u[i].x, u[i].y);
+            __syncthreads();
+            cf v[16];
+            if (bins) {
+#pragma unroll
+                for (int t = 0; t < 16; ++t) { const float2 q = xbuf[r * kRowPad + t * kPairs + c]; v[t] = {q.x, q.y}; }
             }
-            else {
-                const float2 w = tw_k(kb, n2);
-                F[kb] = F[kb] + cmulc(u[kb], cf{w.x, w.y});    // * W_N^{k n2}
+            __syncthreads();
+            if (bins) {
+                fft16_tw<false>(v, lo, hi);      // over t -> b
+#pragma unroll
+                for (int kb = 0; kb < 16; ++kb) F[kb] = decltype(first)::value ? v[kb] : cmac<false>(v[kb], F[kb], kHold ? wk[kb] : bin_turn(kb));
             }
-        }
-    };
-    forward(0, std::true_type{});
-    for (int n2 = 1; n2 < N2; ++n2) forward(n2, std::false_type{});
+        };
+        forward(N2 - 1, std::true_type{});
+        for (int n2 = N2 - 2; n2 >= 0; --n2) forward(n2, std::false_type{});
+    }
     const tile_tag_t seen = tiles_look<4>(sy, b, tile, n_tiles);     // no loads follow: nothing waits behind this one
     // ------------------------------------------------------------------ mask (Eq. 5-6) with the 1/N of Eq. 7
 #pragma unroll
-    for (int kb = 0; kb < Q; ++kb) {
-        const int k1 = t + 16 * kb;
-        const bool lo = k1 <= sigma, hi = k1 >= N1 - sigma;
-        const float g = (lo || hi) ? gm[lo ? k1 : N1 - k1] : 0.f;
+    for (int kb = 0; kb < 16; ++kb) {
+        const int f = kb < 8 ? r + Q * kb : N1 - (r + Q * kb);       // |k|
+        const float g = bins && f <= sigma ? gm[f] : 0.f;
         F[kb] = {F[kb].x * g, F[kb].y * g};
-        ph[kb] = 0;
     }
     // ------------------------------------------------------------------ inverse (Eq. 7) and energy (Eq. 8)
+    const bool odd = (tid & 1) != 0, upper = (tid & 2) != 0;
     auto inverse = [&](int n2, auto first) {
-        cf u[Q];
-#pragma unroll
-        for (int kb = 0; kb < Q; ++kb) {
-            if constexpr (decltype(first)::value) {
-                u[kb] = F[kb];
-                ph[kb] = kpos[kb];
-            }
-            else {
-                const float2 w = tw_k(kb, n2);
-                u[kb] = cmul(F[kb], cf{w.x, w.y});   // F[k] W_N^{-k n2}
-            }
-        }
-        dftq<Q, true>::run(u);                   // over kb -> residue s
-        to_exchange(u, std::integral_constant<int, Q>{}, std::true_type{});            // * W_N1^{-s ka}
-        __syncthreads();
-        if (rdx) {
+        if (bins) {
             cf v[16];
 #pragma unroll
-            for (int ka = 0; ka < 16; ++ka) { const float2 q = xbuf[t * kRowPad + ka * kPairs + c]; v[ka] = {q.x, q.y}; }
-            fft16<true>(v);                      // over ka -> j ; v[j] = z'[N2 (Q j + t) + n2]
-            float e[16];
+            for (int kb = 0; kb < 16; ++kb) v[kb] = F[kb];
+            if constexpr (decltype(first)::value) fft16<true>(v);    // over b -> t
+            else {
+                // W_N^{-Q b n2}, b >= 8: W_N^{-Q (b - 16) n2}
+                const int p = Q * n2;
+                const cf w1 = table(4 * p), w2 = table(8 * p);
+                const cf lo[3] = {w1, {w2.x, -w2.y}, {w1.x, -w1.y}};
+                cf hi[4][3];
 #pragma unroll
-            for (int j = 0; j < 16; ++j) e[j] = row16_sum(fmaf(v[j].x, v[j].x, v[j].y * v[j].y));   // over the 16 pairs
-            if (c == 0) {
-                float4* dst = reinterpret_cast<float4*>(eperm + (n2 * Q + t) * 16);
+                for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) dst[q] = make_float4(e[4 * q], e[4 * q + 1], e[4 * q + 2], e[4 * q + 3]);
+                    for (int i = 1; i < 4; ++i) hi[q][i - 1] = table(i * (p + q * n16));
+                fft16_tw<true>(v, lo, hi);
             }
+#pragma unroll
+            for (int t = 0; t < 16; ++t) xbuf[t * kRowPad + r * kPairs + c] = make_float2(v[t].x, v[t].y);
         }
+        const int p = n2 + N2 * r;
+        cf lo[3], hi[4][3], wa[Q];
+        if constexpr (Q == 16) powers(p, lo, hi);
+        else {
+#pragma unroll
+            for (int i = 1; i < Q; ++i) wa[i] = table(i * p);
+        }
+        __syncthreads();
+        cf u[Q];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) { const float2 q = xbuf[r * kRowPad + i * kPairs + c]; u[i] = {q.x, q.y}; }
+        if constexpr (Q == 16) fft16_tw<true>(u, lo, hi);            // over a -> j ; u[j] = z'[N2 (16 j + t) + n2]
+        else {
+#pragma unroll
+            for (int i = 1; i < Q; ++i) u[i] = cmul(u[i], wa[i]);
+            dftq<Q, true>::run(u);
+        }
+        float e[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) e[j] = j < Q ? fmaf(u[j < Q ? j : 0].x, u[j < Q ? j : 0].x, u[j < Q ? j : 0].y * u[j < Q ? j : 0].y) : 0.f;
+        eperm[(n2 * 16 + r) * 16 + c] = row16_scatter(e, odd, upper);                    // over the 16 pairs
         __syncthreads();
     };
     inverse(0, std::true_type{});
     tiles_claim<4>(sy, b, tile, n_tiles, seen);
     for (int n2 = 1; n2 < N2; ++n2) inverse(n2, std::false_type{});
     float* pout = partial + ((int64_t)b * n_tiles + tile) * N;
-    for (int n = tid; n < N; n += 256) {         // n = N2 (Q j + t') + n2
-        const int n2 = POW2 ? (n & (N2 - 1)) : n % N2;
-        const int q = (n - n2) / N2;
-        const int tq = Q == 16 ? (q & 15) : q % Q, j = Q == 16 ? (q >> 4) : q / Q;
-        tile_store(pout + n, eperm[(n2 * Q + tq) * 16 + j]);
+    const float inv_n2 = 1.f / (float)N2;
+    for (int n = tid; n < N; n += 256) {         // n = N2 (16 j + t) + n2
+        const int q = (int)(((float)n + 0.5f) * inv_n2), n2 = n - q * N2;                // exact: n < 4097
+        tile_store(pout + n, eperm[(n2 * 16 + (q & 15)) * 16 + (q >> 4)]);
     }
     // ------------------------------------------------------------------ Eq. 8 across the channel tiles
     tiles_to_scores<256, 4>(partial, gpartial, sy, scores, b, tile, n_tiles, N, N, &is_last);
@@ -382,7 +353,7 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
 
 static size_t fft_lds_bytes(int N, int Q, int sigma)
 {
-    return sizeof(float2) * (size_t)(16 * kRowPad + N + 16 * Q) + sizeof(float) * (size_t)(N + sigma + 1);
+    return sizeof(float2) * (size_t)(16 * kRowPad + N) + sizeof(float) * (size_t)(N / Q * 16 + sigma + 1);
 }
 
 // the residue-side length Q of the 16 x Q transform that serves (N, sigma); 0 if none does
@@ -399,12 +370,16 @@ static int fft_pick_q(int N, int sigma)
 bool spu_fft_supported(int N, int sigma) { return fft_pick_q(N, sigma) != 0; }
 
 // us of one call, from measurements: a workgroup's share of a subsequence, both ways, and the rounds the workgroups take on
-// the chip (two per compute unit for Q = 16, three otherwise).  8x1024x3584 bf16: 46, 2x4096x1792: 74, 16x720x4096: 69.
+// the chip (two per compute unit for Q = 16, three otherwise; a last round that is half empty costs less than a full one).
+// 8x1024x3584 bf16: 42, 4x2048x3584: 42, 16x720x4096: 60, 8x1440x3584: 61, 32x1152x2048: 105, fp32 1x576x4096: 18.
 double spu_fft_us(int B, int N, int D, int sigma)
 {
     const int Q = fft_pick_q(N, sigma);
     const int64_t wgs = (int64_t)B * ((D + 31) / 32), slots = Q == 16 ? 512 : 768;
-    return 5.0 + (double)((wgs + slots - 1) / slots) * (N / (16 * Q)) * (wgs <= slots ? 4.4 : Q == 16 ? 5.1 : 7.1);
+    const double n2 = N / (16 * Q);
+    if (wgs <= slots) return 7.0 + n2 * (wgs <= 256 ? 2.9 : 4.4);
+    const double rounds = 0.5 * ((double)((wgs + slots - 1) / slots) + (double)wgs / (double)slots);
+    return 5.0 + rounds * n2 * (Q == 16 ? 5.0 : Q == 15 ? 6.2 : 4.35);
 }
 
 luvc_status spu_score_fft(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
@@ -412,16 +387,14 @@ luvc_status spu_score_fft(const void* x, int B, int N, int D, int64_t row_stride
 {
     const int Q = fft_pick_q(N, sigma);
     const size_t lds = fft_lds_bytes(N, Q, sigma);
-    const bool pow2 = (N & (N - 1)) == 0;
     // channel pairs are fetched with one access when every pair is naturally aligned
     const size_t es = dt == LUVC_F32 ? 4 : 2;
     const bool aligned = (row_stride % 2 == 0) && ((uintptr_t)x % (2 * es) == 0) && (D % 2 == 0);
     if (n_tiles > 65535) { set_error("D=%d exceeds the supported width of the fft path", D); return LUVC_ERR_UNSUPPORTED; }
     const dim3 grid((unsigned)n_tiles, (unsigned)B);
-#define LUVC_FFT(TT, QQ, P2, AL) LUVC_LAUNCH("spu_fft16q", (spu_fft16q<TT, QQ, P2, AL>), grid, dim3(256), lds, st, (const TT*)x, N, D, row_stride, sigma, use_hamming, partial, gpartial, sy, scores)
-#define LUVC_FFT_A(TT, QQ, P2) do { if (aligned) LUVC_FFT(TT, QQ, P2, true); else LUVC_FFT(TT, QQ, P2, false); } while (0)
-#define LUVC_FFT_T(TT) do { if (Q == 16) { if (pow2) LUVC_FFT_A(TT, 16, true); else LUVC_FFT_A(TT, 16, false); } \
-                            else if (Q == 15) LUVC_FFT_A(TT, 15, false); else LUVC_FFT_A(TT, 9, false); } while (0)
+#define LUVC_FFT(TT, QQ, AL) LUVC_LAUNCH("spu_fft16q", (spu_fft16q<TT, QQ, AL>), grid, dim3(256), lds, st, (const TT*)x, N, D, row_stride, sigma, use_hamming, partial, gpartial, sy, scores)
+#define LUVC_FFT_A(TT, QQ) do { if (aligned) LUVC_FFT(TT, QQ, true); else LUVC_FFT(TT, QQ, false); } while (0)
+#define LUVC_FFT_T(TT) do { if (Q == 16) LUVC_FFT_A(TT, 16); else if (Q == 15) LUVC_FFT_A(TT, 15); else LUVC_FFT_A(TT, 9); } while (0)
     if (dt == LUVC_F32) LUVC_FFT_T(float); else LUVC_FFT_T(bf16_t);
 #undef LUVC_FFT_T
 #undef LUVC_FFT_A

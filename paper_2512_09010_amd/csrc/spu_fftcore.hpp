@@ -28,32 +28,85 @@ __device__ __forceinline__ void bf4_half(cf& a0, cf& a1, cf& a2, cf& a3)
     a0 = a + b; a1 = a + t3; a2 = a - b; a3 = a - t3;
 }
 
+// acc + a w (INV) or acc + a conj(w)
+template <bool INV>
+__device__ __forceinline__ cf cmac(cf acc, cf a, cf w)
+{
+    return INV ? cf{fmaf(a.x, w.x, fmaf(-a.y, w.y, acc.x)), fmaf(a.x, w.y, fmaf(a.y, w.x, acc.y))}
+               : cf{fmaf(a.x, w.x, fmaf(a.y, w.y, acc.x)), fmaf(a.y, w.x, fmaf(-a.x, w.y, acc.y))};
+}
+
+// Radix-4 butterfly of a0, a1 w1, a2 w2, a3 w3 (INV = false: of the conjugate factors).  Every factor goes into the additions
+// that follow it: a0 - a2 w2 is 2 a0 - (a0 + a2 w2), likewise for the other pair, 24 instructions for 28.
+template <bool INV>
+__device__ __forceinline__ void bf4_tw(cf& a0, cf& a1, cf& a2, cf& a3, cf w1, cf w2, cf w3)
+{
+    const cf t0 = cmac<INV>(a0, a2, w2), t1{fmaf(2.f, a0.x, -t0.x), fmaf(2.f, a0.y, -t0.y)};
+    const cf p = INV ? cmul(a1, w1) : cmulc(a1, w1);
+    const cf t2 = cmac<INV>(p, a3, w3), d{fmaf(2.f, p.x, -t2.x), fmaf(2.f, p.y, -t2.y)};
+    const cf t3 = INV ? cf{-d.y, d.x} : cf{d.y, -d.x};
+    a0 = t0 + t2; a1 = t1 + t3; a2 = t0 - t2; a3 = t1 - t3;
+}
+
+// a + k u, a - k u
+__device__ __forceinline__ cf axpy(float k, cf u, cf a) { return {fmaf(k, u.x, a.x), fmaf(k, u.y, a.y)}; }
+// u = a (1 + i t) or its conjugate form, the direction of a twiddle whose real part is left to the caller; u = a (t + i) likewise
+template <bool INV> __device__ __forceinline__ cf rot(cf a, float t) { return INV ? cf{fmaf(-t, a.y, a.x), fmaf(t, a.x, a.y)} : cf{fmaf(t, a.y, a.x), fmaf(-t, a.x, a.y)}; }
+template <bool INV> __device__ __forceinline__ cf rotq(cf a, float t) { return INV ? cf{fmaf(t, a.x, -a.y), fmaf(t, a.y, a.x)} : cf{fmaf(t, a.x, a.y), fmaf(t, a.y, -a.x)}; }
+
+__device__ __forceinline__ void transpose4x4(cf (&v)[16])
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int p = q + 1; p < 4; ++p) { const cf s = v[4 * q + p]; v[4 * q + p] = v[4 * p + q]; v[4 * p + q] = s; }
+}
+
 // 16-point DFT in registers: X[k] = sum_j v[j] e^{-+ 2 pi i jk/16}; natural order in, natural order out
-// HALF: v[8..15] are taken to be zero and not read
+// HALF: v[8..15] are taken to be zero and not read.  The constant twiddles between the two radix-4 levels are split into
+// a direction and a length; the lengths go into the additions of the second level: 144 instructions for 160.
 template <bool INV, bool HALF = false>
 __device__ __forceinline__ void fft16(cf (&v)[16])
 {
-    constexpr float c1 = 0.9238795325112867f, s1 = 0.3826834323650898f, r = 0.7071067811865476f;
+    constexpr float c1 = 0.9238795325112867f, s1 = 0.3826834323650898f, r = 0.7071067811865476f, tn = 0.41421356237309503f;   // tn = s1 / c1
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if (HALF) bf4_half<INV>(v[i], v[i + 4], v[i + 8], v[i + 12]);
         else bf4<INV>(v[i], v[i + 4], v[i + 8], v[i + 12]);
     }
-    // v[i + 4q] now holds the q-th output of column i; twiddle by W16^{i q}
-    const cf w1{c1, -s1}, w2{r, -r}, w3{s1, -c1}, w6{-r, -r}, w9{-c1, s1};
-    auto tw = [](cf a, cf w) { return INV ? cmulc(a, w) : cmul(a, w); };
-    v[1 + 4] = tw(v[1 + 4], w1);  v[1 + 8] = tw(v[1 + 8], w2);  v[1 + 12] = tw(v[1 + 12], w3);
-    v[2 + 4] = tw(v[2 + 4], w2);
-    v[2 + 8] = INV ? cf{-v[2 + 8].y, v[2 + 8].x} : cf{v[2 + 8].y, -v[2 + 8].x};     // W16^4 = -i
-    v[2 + 12] = tw(v[2 + 12], w6);
-    v[3 + 4] = tw(v[3 + 4], w3);  v[3 + 8] = tw(v[3 + 8], w6);  v[3 + 12] = tw(v[3 + 12], w9);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) bf4<INV>(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    // v[i + 4q] now holds the q-th output of column i; its twiddle is W16^{i q}, q = 0: none
+    bf4<INV>(v[0], v[1], v[2], v[3]);
+    auto quarter = [](cf d) { return INV ? cf{-d.y, d.x} : cf{d.y, -d.x}; };
+    // the second level with a1 = l1 u1, a3 = l1 u3, l1 and u1 +- u3 given: outputs t0 +- l1 (u1 + u3), t1 +- quarter(l1 (u1 - u3))
+    auto finish = [&](int q, cf t0, cf t1, float l1, cf s, cf d) {
+        const cf e = quarter(d);
+        v[4 * q] = axpy(l1, s, t0); v[4 * q + 1] = axpy(l1, e, t1); v[4 * q + 2] = axpy(-l1, s, t0); v[4 * q + 3] = axpy(-l1, e, t1);
+    };
+    {                                            // q = 1: W^1 = c1 (1, tn), W^2 = r (1, 1), W^3 = c1 (tn, 1)
+        const cf u1 = rot<INV>(v[5], tn), u2 = rot<INV>(v[6], 1.f), u3 = rotq<INV>(v[7], tn);
+        finish(1, axpy(r, u2, v[4]), axpy(-r, u2, v[4]), c1, u1 + u3, u1 - u3);
+    }
+    {                                            // q = 2: W^2 = r (1, 1), W^4 = -+ i, W^6 = r (-1, 1)
+        const cf u1 = rot<INV>(v[9], 1.f), u2 = quarter(v[10]), u3 = rotq<INV>(v[11], -1.f);
+        finish(2, v[8] + u2, v[8] - u2, r, u1 + u3, u1 - u3);
+    }
+    {                                            // q = 3: W^3 = c1 (tn, 1), W^6 = r (-1, 1), W^9 = c1 (-1, -tn)
+        const cf u1 = rotq<INV>(v[13], tn), u2 = rotq<INV>(v[14], -1.f), u3 = rot<INV>(v[15], tn);
+        finish(3, axpy(r, u2, v[12]), axpy(-r, u2, v[12]), c1, u1 - u3, u1 + u3);
+    }
     // v[4q + p] holds X[q + 4p]: transpose the 4x4 index back to natural order
+    transpose4x4(v);
+}
+
+// the same of v[j] h^j (INV = false: conjugate), h^j = lo[j / 4 - 1] hi[0][j mod 4 - 1], with hi[q][i - 1] = h^i e^{2 pi i q i / 16}
+template <bool INV>
+__device__ __forceinline__ void fft16_tw(cf (&v)[16], const cf (&lo)[3], const cf (&hi)[4][3])
+{
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int i = 0; i < 4; ++i) bf4_tw<INV>(v[i], v[i + 4], v[i + 8], v[i + 12], lo[0], lo[1], lo[2]);
 #pragma unroll
-        for (int p = q + 1; p < 4; ++p) { const cf s = v[4 * q + p]; v[4 * q + p] = v[4 * p + q]; v[4 * p + q] = s; }
+    for (int q = 0; q < 4; ++q) bf4_tw<INV>(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3], hi[q][0], hi[q][1], hi[q][2]);
+    transpose4x4(v);
 }
 
 // 8-point DFT of v[0], v[1], ... in registers, natural order in, natural order out
