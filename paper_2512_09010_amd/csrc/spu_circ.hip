@@ -20,7 +20,8 @@
 // trip to memory each way, no atomics; nothing has to be set up, and a captured launch replayed with its tag starts over.
 //
 // Bound: matrix cores for N near kCircMaxN (6 N^2 D flops per bf16 sample, 12 for fp32), latency for short samples.
-// 1x729x3584 bf16: 25 us (4096-point transform: 39), 8x205x3584: 15, 8x143x3584: 12, 4x861x1408: 36.
+// 1x729x3584 bf16: 20.5 us (2048-point transform: 24), 8x205x3584: 13.9, 4x144x4096: 9.2, 4x861x1408: 33.6.  Laying out the
+// taps costs about 1 us less than with a division per angle and a copy at a time: 1x512x3584 13.9 -> 12.6.
 #include "common.hpp"
 #include "spu.hpp"
 #include "spu_taps.hpp"
@@ -103,16 +104,18 @@ __host__ __device__ inline int circ_lds(int N, int RT) { return 24 * circ_stride
 
 }  // namespace
 
-template <typename T, int RT>
-__global__ void __launch_bounds__(256, 2)
+// KS: wavefronts that share the steps of a product, each an equal run of them (RT = 1)
+template <typename T, int RT, int KS>
+__global__ void __launch_bounds__(256 * KS, KS == 1 || sizeof(T) == 4 ? 2 : 4)
 spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* workgroups across the channels */, int use_hamming, const CircRuns runs,
          unsigned long long* __restrict__ words /* [groups of 32 RT tokens][n_quads][32 RT] */, uint32_t tag, float* __restrict__ scores)
 {
     using raw_t = circ_raw<T>;
-    constexpr int ROWS = 32 * RT, TERMS = raw_t::TERMS;
+    constexpr int ROWS = 32 * RT, TERMS = raw_t::TERMS, THREADS = 256 * KS;
+    static_assert(KS == 1 || RT == 1, "");
     constexpr int PF = TERMS == 1 ? (RT == 4 ? 3 : RT == 2 ? 4 : 6) : (RT == 4 ? 2 : RT == 2 ? 3 : 4);      // steps of 16 tokens in flight
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double part[256];
+    __shared__ double part[THREADS];
     __shared__ float red[4 * ROWS];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int item = (int)xcd_contiguous(blockIdx.x, gridDim.x);
@@ -127,10 +130,11 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
     const int n_groups = (N + ROWS - 1) / ROWS, local = item - group0 * n_quads;
     const int s = local / (n_quads * n_groups), rem = local - s * (n_quads * n_groups), quad = rem / n_groups, grp = rem - quad * n_groups;
     const int64_t tok = run.tok0 + (int64_t)s * N;
-    const int n0 = grp * ROWS, steps = (N + 15) / 16;
+    const int n0 = grp * ROWS, all_steps = (N + 15) / 16, share = (all_steps + KS - 1) / KS;
+    const int k0 = (wave >> 2) * share, steps = k0 + share < all_steps ? k0 + share : all_steps;      // this wavefront's: k0 .. steps - 1
 
     // ---- tokens: lane l fetches channels 2 (l % 32), + 1 of the wavefront's 64 and the tokens of half l / 32 of a step
-    const int d0 = (quad * 4 + wave) * 64, h = lane >> 5, c31 = lane & 31;
+    const int d0 = (quad * 4 + (wave & 3)) * 64, h = lane >> 5, c31 = lane & 31;
     const bool live = d0 < D;
     const uint32_t row_bytes = (uint32_t)row_stride * (uint32_t)sizeof(T);
     // the descriptor ends with the last token of the sample: tokens past it read zeros; so do channels past D (an offset beyond any descriptor)
@@ -145,7 +149,7 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
         for (int j = 0; j < 8; ++j) r.fetch(j, rx, off + (uint32_t)j * row_bytes);
     };
 #pragma unroll
-    for (int u = 0; u < PF; ++u) fetch(raw[u], u);
+    for (int u = 0; u < PF; ++u) fetch(raw[u], k0 + u);
 
     // ---- taps: p[0 .. N/2] in fp64, split into three bf16 terms; entry o of the line of taps is p[o - n0 - ROWS]
     const int taps = circ_taps(N, RT), stride = circ_stride(N, RT);
@@ -153,7 +157,7 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
     uint16_t* base = line + 3 * (taps + 16);                                   // [3][N / 2 + 2]
     {
         const SpuTaps p(N, sigma, use_hamming);
-        for (int j = tid; j <= N / 2; j += 256) {
+        for (int j = tid; j <= N / 2; j += THREADS) {
             double v = p(j);
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
@@ -164,26 +168,30 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
         }
     }
     __syncthreads();
-    for (int i = tid; i < taps + 16; i += 256) {
-        int j = (i - n0 - ROWS) % N;
-        j = j < 0 ? j + N : j;
+    const float inv_n = 1.f / (float)N;
+    for (int i = tid; i < taps + 16; i += THREADS) {
+        const int at = i - n0 - ROWS;
+        int j = at - (int)floorf((float)at * inv_n) * N;           // modulo N, the quotient off by one at most
+        j += j < 0 ? N : 0;
+        j -= j >= N ? N : 0;
         j = 2 * j > N ? N - j : j;
 #pragma unroll
         for (int t = 0; t < 3; ++t) line[t * (taps + 16) + i] = base[t * (N / 2 + 2) + j];
     }
     __syncthreads();
-    for (int tc = wave; tc < 24; tc += 4) {      // copy c of term t, a lane 8 taps at a time
-        const int t = tc >> 3, c = tc & 7;
-        const uint32_t* from = reinterpret_cast<const uint32_t*>(line + t * (taps + 16));
-        for (int i = lane; i * 8 < taps; i += 64) {
-            const int at = (i * 8 + c) >> 1;
-            uint32_t v[5];
+    // a thread: 16 taps of a term, out of which 8 of every displaced copy
+    const int eights = taps / 8;
+    for (int at = tid; at < 3 * eights; at += THREADS) {
+        const int t = at / eights, i = at - t * eights;
+        const circ_u32x4* from = reinterpret_cast<const circ_u32x4*>(line + t * (taps + 16)) + i;
+        const circ_u32x4 lo = from[0], hi = from[1];
+        const uint32_t v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 #pragma unroll
-            for (int e = 0; e < 5; ++e) v[e] = from[at + e];
+        for (int c = 0; c < 8; ++c) {
             circ_u32x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (c & 1) ? __builtin_amdgcn_alignbit(v[e + 1], v[e], 16) : v[e];
-            *reinterpret_cast<circ_u32x4*>(smem + tc * stride + i * 16) = o;
+            for (int e = 0; e < 4; ++e) o[e] = (c & 1) ? __builtin_amdgcn_alignbit(v[c / 2 + e + 1], v[c / 2 + e], 16) : v[c / 2 + e];
+            *reinterpret_cast<circ_u32x4*>(smem + (8 * t + c) * stride + i * 16) = o;
         }
     }
     __syncthreads();
@@ -205,7 +213,7 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
 #pragma unroll
             for (int e = 0; e < 3; ++e) next[e] = *reinterpret_cast<const circ_u32x4*>(tap + e * 8 * stride + k * 32 - t * 64);
         };
-        read_taps(0, 0);
+        read_taps(k0, 0);
         auto step = [&](const raw_t& r, int k) {
             circ_u32x4 xe[TERMS], xo[TERMS];
             r.operands(xe, xo);
@@ -227,7 +235,7 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
             }
         };
         // whole rounds of PF steps without a branch inside: at a join the compiler waits for everything in flight
-        int k = 0;
+        int k = k0;
         for (; k + PF <= steps; k += PF) {
 #pragma unroll
             for (int u = 0; u < PF; ++u) {
@@ -240,6 +248,29 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
         for (int u = 0; u < PF - 1; ++u)
             if (k + u < steps) step(raw[u], k + u);
     }
+    // ---- the shares of a product, the first one's wavefronts add the others' in order
+    if constexpr (KS > 1) {
+        float4* grid = reinterpret_cast<float4*>(smem);          // [KS - 1][4 wavefronts][8][64 lanes], where the taps were
+        __syncthreads();
+        if (wave >= 4) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const circ_f32x16& a = acc[0][q >> 2];
+                grid[((wave - 4) * 8 + q) * 64 + lane] = make_float4(a[4 * (q & 3)], a[4 * (q & 3) + 1], a[4 * (q & 3) + 2], a[4 * (q & 3) + 3]);
+            }
+        }
+        __syncthreads();
+        if (wave < 4) {
+#pragma unroll
+            for (int u = 0; u < KS - 1; ++u)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    circ_f32x16& a = acc[0][q >> 2];
+                    const float4 o = grid[((4 * u + wave) * 8 + q) * 64 + lane];
+                    a[4 * (q & 3)] += o.x; a[4 * (q & 3) + 1] += o.y; a[4 * (q & 3) + 2] += o.z; a[4 * (q & 3) + 3] += o.w;
+                }
+        }
+    }
     // ---- Eq. 8: over the wavefront's channels (16 rows per lane and tile, two halves of the wavefront), then the four wavefronts
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
@@ -248,7 +279,7 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
         for (int v = 0; v < 16; ++v) { e = fmaf(acc[t][0][v], acc[t][0][v], e); e = fmaf(acc[t][1][v], acc[t][1][v], e); }
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(e), __float_as_uint(e), false, false);
         e = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-        if (h == 0) red[wave * ROWS + t * 32 + c31] = e;
+        if (h == 0 && wave < 4) red[wave * ROWS + t * 32 + c31] = e;
     }
     __syncthreads();
     float own = 0.f;
@@ -264,7 +295,7 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     // ---- all of them there?  Thread: a token, every PARTS-th workgroup
-    constexpr int PARTS = 256 / ROWS;
+    constexpr int PARTS = THREADS / ROWS;
     const int row = tid % ROWS, pt0 = tid / ROWS;
     bool all = true;
     double e = 0.0;
@@ -318,7 +349,7 @@ bool spu_circ_aligned(const void* x, int D, int64_t row_stride, luvc_dtype dt)
 {
     const int64_t es = dt == LUVC_F32 ? 4 : 2;
     // one access per channel pair; a sample inside one descriptor, below the offset that marks a lane without channels
-    return D % 2 == 0 && row_stride % 2 == 0 && (uintptr_t)x % (uintptr_t)(2 * es) == 0 && (int64_t)(kCircMaxN + 64) * row_stride * es < ((int64_t)1 << 31);
+    return D % 2 == 0 && row_stride % 2 == 0 && (uintptr_t)x % (uintptr_t)(2 * es) == 0 && (int64_t)(kCircMaxN + 256) * row_stride * es < ((int64_t)1 << 31);
 }
 
 // one word per output token (rounded up to a workgroup's share) and 256 channels
@@ -327,27 +358,42 @@ size_t spu_circ_bytes(int64_t samples, int N, int D)
     return circ_quads(D) == 1 ? 0 : sizeof(unsigned long long) * (size_t)samples * circ_quads(D) * ((size_t)(N + 127) / 128 * 128);
 }
 
-template <typename T, int RT>
+// Wavefronts per product.  Its steps come one after the other; where the workgroups do not fill the chip and the samples are
+// long enough to pay for a last addition, two wavefronts take half of them each (1x1000x1024 bf16 17.3 -> 16.1 us, fp32
+// 32.5 -> 28.6, 1x300x2048 fp32 13.4 -> 12.9; 1x144x4096 bf16 would go from 7.2 to 7.6, and four wavefronts gain nothing more).
+static int circ_shares(const CircRuns& runs, int D, luvc_dtype dt)
+{
+    int64_t wg = 0;
+    int longest = 0;
+    for (int i = 0; i < runs.n; ++i) {
+        wg += (int64_t)runs.run[i].count * ((runs.run[i].N + 31) / 32) * circ_quads(D);
+        longest = runs.run[i].N > longest ? runs.run[i].N : longest;
+    }
+    return wg <= 256 && longest >= (dt == LUVC_F32 ? 256 : 512) ? 2 : 1;
+}
+
+template <typename T, int RT, int KS>
 static void circ_launch(const T* x, int64_t row_stride, int D, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st)
 {
     int64_t groups = 0;
-    int lds = 0;
+    int lds = (KS - 1) * 32768;
     for (int i = 0; i < runs.n; ++i) {
         runs.run[i].group0 = (int)groups;
         groups += (int64_t)runs.run[i].count * ((runs.run[i].N + 32 * RT - 1) / (32 * RT));
         const int b = circ_lds(runs.run[i].N, RT);
         lds = b > lds ? b : lds;
     }
-    LUVC_LAUNCH("spu_circ", (spu_circ<T, RT>), dim3((unsigned)(groups * circ_quads(D))), dim3(256), (size_t)lds, st, x, row_stride, D, circ_quads(D), use_hamming,
+    LUVC_LAUNCH("spu_circ", (spu_circ<T, RT, KS>), dim3((unsigned)(groups * circ_quads(D))), dim3(256 * KS), (size_t)lds, st, x, row_stride, D, circ_quads(D), use_hamming,
                 runs, (unsigned long long*)words, (uint32_t)(spu_next_tag() % 0xffffffffull) + 1u, scores);
 }
 
 luvc_status spu_score_circ(const void* x, int64_t row_stride, int D, luvc_dtype dt, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st)
 {
-    const int RT = circ_rt(runs, D);
-#define LUVC_CIRC(TT, R) circ_launch<TT, R>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st)
-    if (dt == LUVC_F32) { if (RT == 4) LUVC_CIRC(float, 4); else if (RT == 2) LUVC_CIRC(float, 2); else LUVC_CIRC(float, 1); }
-    else                { if (RT == 4) LUVC_CIRC(bf16_t, 4); else if (RT == 2) LUVC_CIRC(bf16_t, 2); else LUVC_CIRC(bf16_t, 1); }
+    const int RT = circ_rt(runs, D), KS = RT == 1 ? circ_shares(runs, D, dt) : 1;
+#define LUVC_CIRC(TT, R, K) circ_launch<TT, R, K>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st)
+#define LUVC_CIRC_T(TT) do { if (RT == 4) LUVC_CIRC(TT, 4, 1); else if (RT == 2) LUVC_CIRC(TT, 2, 1); else if (KS == 2) LUVC_CIRC(TT, 1, 2); else LUVC_CIRC(TT, 1, 1); } while (0)
+    if (dt == LUVC_F32) LUVC_CIRC_T(float); else LUVC_CIRC_T(bf16_t);
+#undef LUVC_CIRC_T
 #undef LUVC_CIRC
     return check_launch("spu score (circulant)");
 }

@@ -14,6 +14,7 @@
 //   spu_finish      fixed-order sum over channel tiles, square root (Eq. 8)
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <random>
 
 #include "common.hpp"
@@ -172,9 +173,15 @@ tile_tag_t spu_next_tag()
 }
 
 // ------------------------------------------------------------------ host side
-// Which kernel is quickest: measured times (us, one call) as functions of the sizes; spu_circ: 6 (fp32: 9) and its products at
-// 1.1e15 flop/s (8x205x3584 bf16: 15, 1x512x3584: 16, 4x861x1408: 36), the others beside their launchers.
+// Which kernel is quickest: measured times (us, one call) as functions of the sizes.  spu_circ: its products at 1.1e15 flop/s,
+// and a chain of steps that grows with N, which overlap in part (bf16 8x205x3584: 14, 1x729x3584: 20, 1x1000x1024: 16,
+// 4x861x1408: 34; fp32 1x300x2048: 13, 1x1000x1024: 29); the others beside their launchers.
 static double circ_work_us(int64_t B, int N, int D, luvc_dtype dt) { return (dt == LUVC_F32 ? 12.0 : 6.0) * N * N * (double)D * (double)B / 1.1e9; }
+static double circ_us(int64_t B, int N, int D, luvc_dtype dt)
+{
+    const double work = 1.15 * circ_work_us(B, N, D, dt), chain = (dt == LUVC_F32 ? 0.0218 : 0.0105) * N;
+    return (dt == LUVC_F32 ? 6.3 : 5.5) + std::sqrt(work * work + chain * chain);
+}
 static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, double* us)
 {
     bool half;
@@ -189,7 +196,7 @@ static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, bool circ
 {
     double us;
     const SpuPath other = long_path(B, N, D, sigma, dt, &us);
-    return circ && N <= kCircMaxN && circ_work_us(B, N, D, dt) + (dt == LUVC_F32 ? 9.0 : 6.0) <= us ? SpuPath::Circ : other;
+    return circ && N <= kCircMaxN && circ_us(B, N, D, dt) <= us ? SpuPath::Circ : other;
 }
 // in a launch that several runs share, a run adds its products and nothing else
 bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt)

@@ -331,6 +331,7 @@ def test_score_fuzz_on_lengths_with_a_thinned_inverse(oracle, seed):
 @pytest.mark.parametrize("B,N,D,sigma", [
     (1, 1, 2, 0), (1, 2, 8, 1), (3, 3, 6, 1), (2, 15, 64, 7), (1, 16, 254, 8), (3, 17, 258, 2),      # one step of 16 tokens and one more
     (2, 31, 256, 15), (1, 33, 512, 16), (5, 65, 34, 32), (1, 127, 1026, 9), (2, 129, 258, 64),       # around a workgroup's tokens and channels
+    (1, 257, 18, 20), (1, 513, 34, 30), (1, 545, 300, 99), (2, 512, 66, 256),                        # steps shared by two wavefronts, evenly or not
     (1, 1022, 130, 511), (1, 1023, 34, 0), (1, 1024, 66, 512),                                       # the longest samples
 ])
 def test_score_as_a_circulant_product(oracle, dtype, B, N, D, sigma):
