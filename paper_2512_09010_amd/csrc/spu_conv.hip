@@ -187,7 +187,7 @@ spu_conv_spectrum(int N, int M, int sigma, int use_hamming, float* __restrict__ 
     double sb, cb, s2, c2, sk, ck;
     sincospi((double)k / (double)M, &sb, &cb);
     sincospi(2.0 * (double)k / (double)M, &s2, &c2);
-    sincospi(2.0 * (double)(((int64_t)N * k) % M) / (double)M, &sk, &ck);
+    sincospi(2.0 * (double)((N * k) & (M - 1)) / (double)M, &sk, &ck);       // M is a power of two, all products stay below 2^28
     double acc = 0.0;
     for (int f0 = 1; f0 <= sigma; f0 += 256) {
         const int f = f0 + tid;
@@ -204,8 +204,13 @@ spu_conv_spectrum(int N, int M, int sigma, int use_hamming, float* __restrict__ 
         const int cnt = sigma - f0 + 1 < 256 ? sigma - f0 + 1 : 256;
         for (int i = l; i < cnt; i += kSpecLanes) {
             const double d = sn[i] * cb - cs[i] * sb, s = sn[i] * cb + cs[i] * sb;
-            const bool same = (int64_t)(f0 + i) * M == (int64_t)k * N;
-            const double t = same ? (2 * k == M ? 4.0 : 2.0) * (double)N - 2.0 : -sk * s2 / (d * s) - 2.0 * ck;
+            const bool same = (f0 + i) * M == k * N;
+            // 1 / (d s): the hardware's estimate and two Newton steps
+            const double q = d * s;
+            double inv = __builtin_amdgcn_rcp(q);
+            inv = fma(fma(-q, inv, 1.0), inv, inv);
+            inv = fma(fma(-q, inv, 1.0), inv, inv);
+            const double t = same ? (2 * k == M ? 4.0 : 2.0) * (double)N - 2.0 : fma(-sk * s2, inv, -2.0 * ck);
             acc += wt[i] * t;
         }
     }

@@ -174,7 +174,7 @@ spu_gather(const unsigned char* __restrict__ x, const int32_t* __restrict__ kept
     }
 }
 
-// ------------------------------------------------------------------ select + gather in one launch (N <= 4096)
+// ------------------------------------------------------------------ select + gather in one launch (N <= kFusedMaxN)
 // Workgroup g of sample b repeats the selection of the sample on its own (the scores of a sample
 // are a few KB, and the groups run side by side; samples of different lengths share a launch, the argument lists
 // runs of equal ones), keeps the list of kept tokens in LDS, and then copies
@@ -188,7 +188,9 @@ typedef unsigned int prune_u32x4 __attribute__((__vector_size__(16)));
 // Threads: 256 for samples of up to 1024 tokens, four keys each; longer ones take 1024, so that the selection stays four
 // keys per thread and fewer workgroups repeat it (4 x 4096 tokens, 819 kept, 3584 channels bf16:
 // 19 us with 256 threads, 12 with 1024).
-constexpr int kFusedMaxN = 4096, kFusedKeys = 4;
+// Above 4096 tokens it is eight keys per thread: 1 x 5245 tokens, 545 kept, 21 us as a selection and a
+// gather launch, 8.6 like this.
+constexpr int kFusedMaxN = 8192;
 
 // workgroups of a sample: one kept row per wavefront, up to 256 of them
 __host__ __device__ inline int prune_groups(int n_keep, int waves, bool gather)
@@ -197,13 +199,13 @@ __host__ __device__ inline int prune_groups(int n_keep, int waves, bool gather)
     return G > 256 ? 256 : G;
 }
 
-template <int BYTES, int kFusedThreads>
+template <int BYTES, int kFusedThreads, int kFusedKeys>
 __global__ void __launch_bounds__(kFusedThreads)
 spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ scores, const PruneRuns runs,
                 int64_t row_bytes_in, int64_t row_bytes_out, int32_t* __restrict__ kept_idx, unsigned char* __restrict__ x_out,
                 const int32_t* __restrict__ origin_in /* per token or null: identity */, int32_t* __restrict__ origin_out /* per kept token or null */)
 {
-    __shared__ int32_t kept[kFusedMaxN];
+    __shared__ int32_t kept[kFusedThreads * kFusedKeys];
     __shared__ int hist[4][256];                       // one histogram per digit pass: none has to be cleared in between
     constexpr int WAVES = kFusedThreads / 64;
     __shared__ uint32_t wave_tot[WAVES], wave_hi[WAVES], wave_lo[WAVES];
@@ -369,8 +371,10 @@ luvc_status spu_prune_run(const void* x, const float* scores, int D, int64_t row
     const bool v16 = x_out && rin % 16 == 0 && rout % 16 == 0 && ((uintptr_t)x % 16 == 0) && ((uintptr_t)x_out % 16 == 0);
     int64_t wgs = 0;
     int fused = 0;
-    bool wide = false;
-    for (int i = 0; i < runs.n; ++i) wide = wide || (runs.run[i].N > 256 * kFusedKeys && runs.run[i].N <= kFusedMaxN);
+    int longest = 0;                                       // of the samples of the shared launch
+    for (int i = 0; i < runs.n; ++i)
+        if (runs.run[i].N <= kFusedMaxN && runs.run[i].N > longest) longest = runs.run[i].N;
+    const bool wide = longest > 1024;
     for (int i = 0; i < runs.n; ++i) {
         const PruneRun r = runs.run[i];
         if (r.N > kFusedMaxN) {                            // the list of kept tokens does not fit in LDS
@@ -388,9 +392,9 @@ luvc_status spu_prune_run(const void* x, const float* scores, int D, int64_t row
     if (fused == 0) return LUVC_OK;
     if (wgs >= ((int64_t)1 << 31)) { set_error("too many kept tokens in one call"); return LUVC_ERR_UNSUPPORTED; }
     runs.n = fused;
-#define LUVC_PRUNE_T(BYTES, THREADS) LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<BYTES, THREADS>), dim3((unsigned)wgs), dim3(THREADS), 0, st, (const unsigned char*)x, \
+#define LUVC_PRUNE_T(BYTES, THREADS, KEYS) LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<BYTES, THREADS, KEYS>), dim3((unsigned)wgs), dim3(THREADS), 0, st, (const unsigned char*)x, \
                                                  scores, runs, rin, rout, kept_idx, (unsigned char*)x_out, origin_in, origin_out)
-#define LUVC_PRUNE(BYTES) do { if (wide) LUVC_PRUNE_T(BYTES, 1024); else LUVC_PRUNE_T(BYTES, 256); } while (0)
+#define LUVC_PRUNE(BYTES) do { if (longest > 4096) LUVC_PRUNE_T(BYTES, 1024, 8); else if (wide) LUVC_PRUNE_T(BYTES, 1024, 4); else LUVC_PRUNE_T(BYTES, 256, 4); } while (0)
     if (v16 || !x_out) LUVC_PRUNE(16);
     else if (es == 4)  LUVC_PRUNE(4);
     else               LUVC_PRUNE(2);

@@ -346,9 +346,10 @@ def test_score_as_a_circulant_product(oracle, dtype, B, N, D, sigma):
     score_case(oracle, x, dtype, sigma, False, "circulant-rect", stride_pad=10)
 
 
-@pytest.mark.parametrize("N,k", [(1024, 1024), (1025, 1), (1025, 1025), (2049, 700), (4095, 3), (4096, 2049)])
+@pytest.mark.parametrize("N,k", [(1024, 1024), (1025, 1), (1025, 1025), (2049, 700), (4095, 3), (4096, 2049),
+                                 (4097, 4097), (5000, 1), (8191, 1700), (8192, 8192), (8193, 40)])
 def test_prune_around_the_sizes_of_its_workgroups(oracle, N, k):
-    """256 threads up to 1024 tokens, 1024 beyond: selection (ties, signed zeros, infinities) and the rows that follow it."""
+    """256 threads up to 1024 tokens, 1024 beyond, eight keys each above 4096, two launches above 8192: selection (ties, signed zeros, infinities) and the rows that follow it."""
     rng = np.random.default_rng(N * 5 + k)
     sc = adversarial_scores(N, rng)
     x = torch.from_numpy(rng.standard_normal((sc.shape[0], N, 24)).astype(np.float32)).to(torch.bfloat16).cuda()
