@@ -1,5 +1,5 @@
-// SPU score (paper Section 3.3, Eq. 4-8) for any number of tokens and any pass band: one transform of M = 2048, 4096, 8192 or
-// 16384 points forward, one back, all of it in the registers and the LDS of a workgroup.
+// SPU score (paper Section 3.3, Eq. 4-8) for any number of tokens and any pass band: one transform of M = 1536 to 16384
+// points forward, one back, all of it in the registers and the LDS of a workgroup.
 //
 // Eq. 4-7 together are a circular convolution of length N with the even kernel
 //     p[j] = 1/N sum_{|f| <= sigma} M[f] e^{2 pi i f j / N}.
@@ -10,7 +10,7 @@
 // evaluated in fp64 by spu_conv_spectrum.  Nothing about N has to factor.
 //
 // Two channels of a token are one complex value (the filter is real).  A workgroup holds P channel pairs at a time:
-//   A    thread (pair c, column n2 of C = 256, or 128 for M = 2048): tokens n2, n2 + C, ... straight from memory, R-point DFT
+//   A    thread (pair c, column n2 of C = 256, or 128 for M <= 2048): tokens n2, n2 + C, ... straight from memory, R-point DFT
 //        (M = R C) in registers over them, twiddle W_M^{k1 n2}, row k1 of the exchange grid [R][C][P] gets the result;
 //   B,C  the points of a row = 16 x 16 (16 x 8): both passes, the spectrum and the two inverse passes run inside one wavefront, in
 //        place, so nothing but the order of one wavefront's LDS accesses stands between them;
@@ -20,8 +20,9 @@
 // 4 P-byte pieces of the same cache lines, and keeps the energies in registers until its last pairs are done.
 // With half of the inputs zero and half of the outputs unwanted (N <= M / 2) passes A and A' take half the loads and skip a
 // butterfly level each.
-// M is the smallest that fits: the longer transform costs its zeros (8x1000x3584 bf16: 152 us on 4096 points, 77 on 2048;
-// 8x2048x3584: 208 and 88).
+// M is the smallest that fits, a power of two or three times one: the longer transform costs its zeros (8x1000x3584 bf16: 152
+// us on 4096 points, 77 on 2048; 8x2048x3584: 208 and 88; 8x700x3584: 76 on 2048, 62 on 1536; 8x1200x3584: 138 on 4096, 110
+// on 3072; 1x5245x3328: 190 on 16384, 160 on 12288).
 //
 // Bound: fp32 vector arithmetic (about 5 M log2 M flops per direction and pair) and the LDS traffic beside it (64 bytes per
 // point and pair).
@@ -38,12 +39,12 @@ namespace {
 
 // R-point DFT across the registers of a thread, natural order in and out; HALF: inputs j >= R/2 are zero and not read
 // (forward), outputs j >= R/2 are not formed (inverse)
-template <int R, bool HALF> struct dft_cols;
-template <bool HALF> struct dft_cols<16, HALF> {
+template <int R, bool HALF> struct dft_cols_pow2;
+template <bool HALF> struct dft_cols_pow2<16, HALF> {
     __device__ static __forceinline__ void fwd(cf (&v)[16]) { fft16<false, HALF>(v); }
     __device__ static __forceinline__ void inv(cf (&v)[16]) { fft16<true>(v); }
 };
-template <bool HALF> struct dft_cols<32, HALF> {
+template <bool HALF> struct dft_cols_pow2<32, HALF> {
     __device__ static __forceinline__ void fwd(cf (&v)[32])
     {
         cf e[16], o[16];
@@ -73,7 +74,7 @@ template <bool HALF> struct dft_cols<32, HALF> {
         }
     }
 };
-template <bool HALF> struct dft_cols<64, HALF> {
+template <bool HALF> struct dft_cols_pow2<64, HALF> {
     __device__ static __forceinline__ void fwd(cf (&v)[64])
     {
         cf u[4][16];
@@ -116,6 +117,34 @@ template <bool HALF> struct dft_cols<64, HALF> {
         }
     }
 };
+
+// R = 12, 24, 48, zeros in the upper half
+template <int R> struct dft_cols_three {
+    static_assert(R % 12 == 0 && 48 % R == 0, "");
+    static constexpr int S = 48 / R;
+    __device__ static __forceinline__ void fwd(cf (&v)[R])
+    {
+        cf e[R / 2], o[R / 2];
+#pragma unroll
+        for (int j = 0; j < R / 2; ++j) { e[j] = v[j]; o[j] = j ? cmul(v[j], w48(S * j)) : v[j]; }
+        dft3c<R / 6, false>(e);
+        dft3c<R / 6, false>(o);
+#pragma unroll
+        for (int q = 0; q < R / 2; ++q) { v[2 * q] = e[q]; v[2 * q + 1] = o[q]; }
+    }
+    __device__ static __forceinline__ void inv(cf (&v)[R])
+    {
+        cf e[R / 2], o[R / 2];
+#pragma unroll
+        for (int q = 0; q < R / 2; ++q) { e[q] = v[2 * q]; o[q] = v[2 * q + 1]; }
+        dft3c<R / 6, true>(e);
+        dft3c<R / 6, true>(o);
+#pragma unroll
+        for (int j = 0; j < R / 2; ++j) v[j] = e[j] + (j ? cmulc(o[j], w48(S * j)) : o[j]);
+    }
+};
+
+template <int R, bool HALF> using dft_cols = std::conditional_t<R % 3 == 0, dft_cols_three<R % 3 == 0 ? R : 12>, dft_cols_pow2<R % 3 == 0 ? 16 : R, HALF>>;
 
 // one channel pair as it lies in memory: by buffer access (one instruction, bounds by the descriptor) or element by element
 template <typename T> struct raw_pair;
@@ -187,7 +216,7 @@ spu_conv_spectrum(int N, int M, int sigma, int use_hamming, float* __restrict__ 
     double sb, cb, s2, c2, sk, ck;
     sincospi((double)k / (double)M, &sb, &cb);
     sincospi(2.0 * (double)k / (double)M, &s2, &c2);
-    sincospi(2.0 * (double)((N * k) & (M - 1)) / (double)M, &sk, &ck);       // M is a power of two, all products stay below 2^28
+    sincospi(2.0 * (double)((N * k) % M) / (double)M, &sk, &ck);       // all products stay below 2^28
     double acc = 0.0;
     for (int f0 = 1; f0 <= sigma; f0 += 256) {
         const int f = f0 + tid;
@@ -232,8 +261,8 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
 {
     constexpr int COLS = 16 * LB, M = COLS * R, THREADS = COLS * P, JN = HALF ? R / 2 : R;
     constexpr int LROW = (COLS + LB) * P;        // complex values per row of the exchange grid: a pad of P after every 16 columns
-    constexpr int ROWS = 64 / (LB * P), NIT = R / 16;              // rows a wavefront takes at a time, and how often
-    constexpr bool SPEC_LDS = R == 16;           // the spectrum in LDS (registers are short at 1024 threads) or in registers
+    constexpr int ROWS = 64 / (LB * P), NIT = (R + 15) / 16;       // rows a wavefront takes at a time, and how often
+    constexpr bool SPEC_LDS = R <= 16;           // the spectrum in LDS (registers are short at 1024 threads) or in registers
     extern __shared__ float2 sm[];               // [R][LROW]; the M-entry table while the twiddles are picked
     float2* twb = sm + R * LROW;                 // [COLS] (cos, sin)(2 pi i / COLS)
     float* sp = reinterpret_cast<float*>(twb + COLS);              // SPEC_LDS: [R k1][16 i][LB lw]
@@ -316,7 +345,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
 #pragma unroll
         for (int it = 0; it < NIT; ++it)
 #pragma unroll
-            for (int kb = 0; kb < 16; ++kb) wr[it % (SPEC_LDS ? 1 : NIT)][kb] = weight(bin(it * 16 + wrow, kb, lw));
+            for (int kb = 0; kb < 16; ++kb) wr[it % (SPEC_LDS ? 1 : NIT)][kb] = weight(bin(it * 16 + wrow < R ? it * 16 + wrow : 0, kb, lw));
     }
     __syncthreads();
     // W_M^{k1 n2} (conjugated on use).  N = M, where a thread holds R tokens and R sums, or fp32 tokens, or eight pairs: the
@@ -327,8 +356,8 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
     constexpr int KEPT = FOLD ? R / 2 + 1 : R;
     cf wa[KEPT], wtop{0.f, 0.f};
 #pragma unroll
-    for (int k1 = 1; k1 < KEPT; ++k1) { const float2 w = sm[(k1 * n2) & (M - 1)]; wa[k1] = {w.x, w.y}; }
-    if (FOLD) { const float2 w = sm[(R * n2) & (M - 1)]; wtop = {w.x, w.y}; }
+    for (int k1 = 1; k1 < KEPT; ++k1) { const float2 w = sm[k1 * n2]; wa[k1] = {w.x, w.y}; }
+    if (FOLD) { const float2 w = sm[R * n2]; wtop = {w.x, w.y}; }
     auto tw_a = [&](int k1) { return k1 < KEPT ? wa[k1 < KEPT ? k1 : 0] : cmulc(wtop, wa[k1 < KEPT ? 0 : R - k1]); };
     if (tid < COLS) twb[tid] = sm[tid * R];
     float acc[JN];
@@ -360,6 +389,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int k1 = it * 16 + wrow;
+            if (R % 16 != 0 && (it * 16 + (tid >> 6) * ROWS >= R)) break;          // a whole wavefront: R is a multiple of ROWS
             float2* row = sm + k1 * LROW + c;
             int lt = lw;
             asm volatile("" : "+v"(lt));         // the places of the twiddles are formed here, not kept
@@ -367,7 +397,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
 #pragma unroll
             for (int a = 0; a < 16; ++a) { const float2 q = row[(a * LB + a * LB / 16 + lw) * P]; v[a] = {q.x, q.y}; }
             fft16<false>(v);
-            twiddled<false, R == 16 ? 4 : 8>(v, twb, [&](int ka) { return ka * lt; }, [&](int ka, cf r) { row[(ka * LB + ka * LB / 16 + lw) * P] = make_float2(r.x, r.y); });
+            twiddled<false, R <= 16 ? 4 : 8>(v, twb, [&](int ka) { return ka * lt; }, [&](int ka, cf r) { row[(ka * LB + ka * LB / 16 + lw) * P] = make_float2(r.x, r.y); });
             wave_lds_fence();
 #pragma unroll
             for (int i = 0; i < 16; ++i) { const float2 q = row[(17 * lw + i) * P]; v[i] = {q.x, q.y}; }
@@ -380,7 +410,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
             }
             if constexpr (LB == 16) fft16<true>(v);
             else { fft8<true>(v); fft8<true>(v + 8); }
-            twiddled<true, R == 16 ? 4 : 8>(v, twb, [&](int i) { return LB == 16 ? i * lt : (i & 7) * (2 * lt + (i >> 3)); }, [&](int i, cf r) { row[(17 * lw + i) * P] = make_float2(r.x, r.y); });
+            twiddled<true, R <= 16 ? 4 : 8>(v, twb, [&](int i) { return LB == 16 ? i * lt : (i & 7) * (2 * lt + (i >> 3)); }, [&](int i, cf r) { row[(17 * lw + i) * P] = make_float2(r.x, r.y); });
             wave_lds_fence();
 #pragma unroll
             for (int ka = 0; ka < 16; ++ka) { const float2 q = row[(ka * LB + ka * LB / 16 + lw) * P]; v[ka] = {q.x, q.y}; }
@@ -421,12 +451,12 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
 // Points M of the transform for N tokens; *half: zeros behind the tokens (N <= M / 2), else N = M.  0: too long.
 int spu_conv_points(int N, bool* half)
 {
-    for (int M : {2048, 4096, 8192, 16384})
-        if (2 * N <= M || N == M) { *half = N != M; return M; }
+    for (int M : {1536, 2048, 3072, 4096, 6144, 8192, 12288, 16384})
+        if (2 * N <= M || (N == M && (M & (M - 1)) == 0)) { *half = N != M; return M; }
     return 0;
 }
 
-static int conv_pairs(int M) { return 16384 / M; }
+static int conv_pairs(int M) { return M <= 2048 ? 8 : M <= 4096 ? 4 : M <= 8192 ? 2 : 1; }
 
 // Workgroups per sample.  One workgroup fills a compute unit; a workgroup's time is its pair groups plus about one more
 // for tables and hand-over, and the launch takes as many rounds of that as there are multiples of 256 workgroups.
@@ -445,14 +475,16 @@ int spu_conv_tiles(int B, int N, int D)
 }
 
 // us of one call, from measurements: a launch for the spectrum where one is needed, then what a workgroup starts with and its
-// pair groups one after the other.  8x1200x3584 bf16: 143, 1x2000x3584: 35, 4x4096x3584: 101 (fp32: 137), 8x2048x3584: 87
-// (fp32: 110).
+// pair groups one after the other.  8x700x3584 bf16: 62, 8x1000x3584: 77, 8x1200x3584: 110, 2x3000x3584: 95, 1x5245x3328: 160,
+// 4x4096x3584: 101 (fp32: 137), 8x2048x3584: 87 (fp32: 110).
 double spu_conv_us(int B, int N, int D, luvc_dtype dt)
 {
     bool half;
     const int M = spu_conv_points(N, &half), P = conv_pairs(M), ng = (D + 2 * P - 1) / (2 * P), t = spu_conv_tiles(B, N, D);
     const double rounds = (double)(((int64_t)B * t + 255) / 256) * ((ng + t - 1) / t);
-    return half ? 15.0 + rounds * 9.1 : 14.0 + rounds * (M == 2048 ? 10.5 : 12.4) * (dt == LUVC_F32 && M <= 4096 ? 1.35 : 1.0);
+    const bool three = M % 3 == 0;
+    if (half) return 15.0 + rounds * (M <= 4096 ? (three ? 6.8 : 9.1) : M <= 8192 ? (three ? 11.4 : 14.0) : (three ? 20.7 : 25.0));
+    return 14.0 + rounds * (M == 2048 ? 10.5 : 12.4) * (dt == LUVC_F32 && M <= 4096 ? 1.35 : 1.0);
 }
 
 size_t spu_conv_spec_bytes(int N)
@@ -467,11 +499,11 @@ static void conv_launch(const T* x, int B, int N, int D, int64_t row_stride, int
                         const float* spec, float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st)
 {
     const int ng = (D + 2 * P - 1) / (2 * P), ld = spu_conv_ld(N);
-    const size_t lds = sizeof(float2) * (size_t)(R * 17 * LB * P + 16 * LB) + (R == 16 ? sizeof(float) * 16 * LB * R : 0);
+    const size_t lds = sizeof(float2) * (size_t)(R * 17 * LB * P + 16 * LB) + (R <= 16 ? sizeof(float) * 16 * LB * R : 0);
     const dim3 grid((unsigned)n_tiles, (unsigned)B), block(16 * LB * P);
 #define LUVC_CONV(HF, AL) LUVC_LAUNCH("spu_conv", (spu_conv<T, R, LB, P, HF, AL>), grid, block, lds, st, x, N, D, row_stride, sigma, use_hamming, spec, ng, ld, partial, gpartial, sy, scores)
     if (half) { if (aligned) LUVC_CONV(true, true); else LUVC_CONV(true, false); }
-    else      { if (aligned) LUVC_CONV(false, true); else LUVC_CONV(false, false); }
+    else if constexpr (R % 3 != 0) { if (aligned) LUVC_CONV(false, true); else LUVC_CONV(false, false); }
 #undef LUVC_CONV
 }
 
@@ -488,10 +520,14 @@ luvc_status spu_score_conv(const void* x, int B, int N, int D, int64_t row_strid
     }
 #define LUVC_CONV_S(TT, R, LB, P) conv_launch<TT, R, LB, P>((const TT*)x, B, N, D, row_stride, sigma, use_hamming, half, aligned, spec, partial, gpartial, sy, n_tiles, scores, st)
 #define LUVC_CONV_R(TT) do { \
-        if (M == 2048)      LUVC_CONV_S(TT, 16, 8, 8); \
-        else if (M == 4096) LUVC_CONV_S(TT, 16, 16, 4); \
-        else if (M == 8192) LUVC_CONV_S(TT, 32, 16, 2); \
-        else                LUVC_CONV_S(TT, 64, 16, 1); \
+        if (M == 1536)       LUVC_CONV_S(TT, 12, 8, 8); \
+        else if (M == 2048)  LUVC_CONV_S(TT, 16, 8, 8); \
+        else if (M == 3072)  LUVC_CONV_S(TT, 12, 16, 4); \
+        else if (M == 4096)  LUVC_CONV_S(TT, 16, 16, 4); \
+        else if (M == 6144)  LUVC_CONV_S(TT, 24, 16, 2); \
+        else if (M == 8192)  LUVC_CONV_S(TT, 32, 16, 2); \
+        else if (M == 12288) LUVC_CONV_S(TT, 48, 16, 1); \
+        else                 LUVC_CONV_S(TT, 64, 16, 1); \
     } while (0)
     if (dt == LUVC_F32) LUVC_CONV_R(float); else LUVC_CONV_R(bf16_t);
 #undef LUVC_CONV_R

@@ -38,16 +38,6 @@ namespace luvc {
 
 namespace {
 
-// 3-point DFT (INV: conjugate twiddles)
-template <bool INV>
-__device__ __forceinline__ void dft3(cf& a, cf& b, cf& c)
-{
-    constexpr float s3 = 0.8660254037844386f;
-    const cf t = b + c, m{a.x - 0.5f * t.x, a.y - 0.5f * t.y};
-    const cf d = b - c, r = INV ? cf{-d.y, d.x} : cf{d.y, -d.x};       // d * (+i) or d * (-i)
-    a = a + t; b = axpy(s3, r, m); c = axpy(-s3, r, m);
-}
-
 // 5-point DFT
 template <bool INV>
 __device__ __forceinline__ void dft5(cf& x0, cf& x1, cf& x2, cf& x3, cf& x4)

@@ -125,6 +125,49 @@ __device__ __forceinline__ void fft8(cf* v)
     for (int k = 0; k < 4; ++k) { v[k] = e[k] + o[k]; v[k + 4] = e[k] - o[k]; }
 }
 
+// 3-point DFT (INV: conjugate twiddles)
+template <bool INV>
+__device__ __forceinline__ void dft3(cf& a, cf& b, cf& c)
+{
+    constexpr float s3 = 0.8660254037844386f;
+    const cf t = b + c, m{a.x - 0.5f * t.x, a.y - 0.5f * t.y};
+    const cf d = b - c, r = INV ? cf{-d.y, d.x} : cf{d.y, -d.x};       // d * (+i) or d * (-i)
+    a = a + t; b = axpy(s3, r, m); c = axpy(-s3, r, m);
+}
+
+// DFT of 3 C points, C = 2, 4 or 8 (no twiddles: C and 3 are coprime), natural order in, natural order out
+template <int C, bool INV>
+__device__ __forceinline__ void dft3c(cf (&v)[3 * C])
+{
+    constexpr int N = 3 * C, K1 = C * (C % 3), K2 = 3 * (C == 2 ? 1 : 3);       // C (1 / C mod 3), 3 (1 / 3 mod C)
+    cf u[3][C];
+#pragma unroll
+    for (int n2 = 0; n2 < C; ++n2) {
+        cf a = v[(3 * n2) % N], b = v[(C + 3 * n2) % N], c = v[(2 * C + 3 * n2) % N];
+        dft3<INV>(a, b, c);
+        u[0][n2] = a; u[1][n2] = b; u[2][n2] = c;
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) {
+        if constexpr (C == 8) fft8<INV>(u[k1]);
+        else if constexpr (C == 4) bf4<INV>(u[k1][0], u[k1][1], u[k1][2], u[k1][3]);
+        else { const cf t = u[k1][0]; u[k1][0] = t + u[k1][1]; u[k1][1] = t - u[k1][1]; }
+#pragma unroll
+        for (int k2 = 0; k2 < C; ++k2) v[(K1 * k1 + K2 * k2) % N] = u[k1][k2];
+    }
+}
+
+// cos(2 pi i / 48)
+constexpr float kCos48[48] = {
+    1.0f, 0.991444861f, 0.965925826f, 0.923879533f, 0.866025404f, 0.79335334f, 0.707106781f, 0.608761429f,
+    0.5f, 0.382683432f, 0.258819045f, 0.130526192f, 0.0f, -0.130526192f, -0.258819045f, -0.382683432f,
+    -0.5f, -0.608761429f, -0.707106781f, -0.79335334f, -0.866025404f, -0.923879533f, -0.965925826f, -0.991444861f,
+    -1.0f, -0.991444861f, -0.965925826f, -0.923879533f, -0.866025404f, -0.79335334f, -0.707106781f, -0.608761429f,
+    -0.5f, -0.382683432f, -0.258819045f, -0.130526192f, 0.0f, 0.130526192f, 0.258819045f, 0.382683432f,
+    0.5f, 0.608761429f, 0.707106781f, 0.79335334f, 0.866025404f, 0.923879533f, 0.965925826f, 0.991444861f};
+// e^{-2 pi i e / 48}
+__device__ __forceinline__ constexpr cf w48(int e) { return {kCos48[e % 48], -kCos48[(e + 36) % 48]}; }
+
 // cos(2 pi i / 64)
 constexpr float kCos64[64] = {
     1.0f, 0.995184727f, 0.98078528f, 0.956940336f, 0.923879533f, 0.881921264f, 0.831469612f, 0.773010453f,

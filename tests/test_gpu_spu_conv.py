@@ -49,3 +49,17 @@ def test_score_on_2048_points(oracle, dtype, B, N, D, sigma, pad):
     x = wl.cast_io(rng.standard_normal((B, N, D)).astype(np.float32), dtype)
     score_case(oracle, x, dtype, sigma, True, "2048", stride_pad=pad)
     score_case(oracle, x, dtype, sigma, False, "2048-rect", stride_pad=pad)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,N,D,sigma,pad", [
+    (1, 767, 17, 380, 0), (1, 768, 9, 384, 1), (1, 769, 15, 0, 0), (13, 700, 514, 70, 0),      # 1536 points
+    (1, 1535, 6, 100, 0), (2, 1536, 19, 768, 0), (1, 1537, 10, 3, 0), (2, 1100, 266, 150, 2),  # 3072
+    (1, 3071, 6, 1500, 0), (1, 3072, 34, 200, 1), (1, 3073, 4, 60, 0),                         # 6144
+    (1, 6143, 4, 2000, 0), (1, 6144, 5, 30, 0), (1, 6145, 3, 700, 0), (2, 4500, 34, 450, 0),   # 12288
+])
+def test_score_on_three_times_a_power_of_two_points(oracle, dtype, B, N, D, sigma, pad):
+    rng = np.random.default_rng(N * 3 + D)
+    x = wl.cast_io(rng.standard_normal((B, N, D)).astype(np.float32), dtype)
+    score_case(oracle, x, dtype, sigma, True, "3 * 2^n", stride_pad=pad)
+    score_case(oracle, x, dtype, sigma, False, "3 * 2^n-rect", stride_pad=pad)
