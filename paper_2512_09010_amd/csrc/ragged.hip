@@ -176,6 +176,7 @@ struct SpuRun {
     int64_t tok_in, tok_out;
 };
 
+// n_keep NULL: the runs that are scored together, which keep counts do not split
 bool spu_runs(int n_samples, const int32_t* N, const int32_t* sigma, const int32_t* n_keep, std::vector<SpuRun>* runs)
 {
     if (n_samples < 1 || !N || !sigma) { set_error("n_samples, N and sigma must be given"); return false; }
@@ -197,6 +198,20 @@ bool spu_runs(int n_samples, const int32_t* N, const int32_t* sigma, const int32
 }
 
 size_t esz(luvc_dtype dt) { return dt == LUVC_F32 ? 4 : 2; }
+
+// Workspace of the scores of a ragged batch: the largest need of a run that is a call of its own, or the words of all runs that
+// share a launch (circ: the rows let them).  0 (with an error message) when a run is not supported.
+size_t spu_runs_workspace(const std::vector<SpuRun>& runs, int D, luvc_dtype dt, bool circ)
+{
+    size_t need = 0, shared = 0;
+    for (const SpuRun& r : runs) {
+        const size_t b = luvc_spu_workspace_bytes(r.count, r.N, D, dt, r.sigma);
+        if (b == 0) { set_error("run of %d samples with N=%d, sigma=%d is not supported", r.count, r.N, r.sigma); return 0; }
+        need = std::max(need, b);
+        if (circ && spu_circ_in_batch(r.count, r.N, D, r.sigma, dt)) shared += spu_circ_bytes(r.count, r.N, D);
+    }
+    return std::max(need, align_up(shared));
+}
 
 }  // namespace
 
@@ -284,14 +299,7 @@ size_t luvc_spu_ragged_workspace_bytes(int n_samples, const int32_t* N, int D, l
 {
     std::vector<SpuRun> runs;
     if (D < 1 || !spu_runs(n_samples, N, sigma, nullptr, &runs)) return 0;
-    size_t need = 0, shared = 0;
-    for (const SpuRun& r : runs) {
-        const size_t b = luvc_spu_workspace_bytes(r.count, r.N, D, dtype, r.sigma);
-        if (b == 0) return 0;
-        need = b > need ? b : need;
-        if (spu_circ_in_batch(r.count, r.N, D, r.sigma, dtype)) shared += spu_circ_bytes(r.count, r.N, D);
-    }
-    return need > align_up(shared) ? need : align_up(shared);
+    return spu_runs_workspace(runs, D, dtype, true);
 }
 
 luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N, int D, int64_t row_stride, luvc_dtype dtype,
@@ -303,17 +311,14 @@ luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N
     if (!x || !scores) { set_error("x and scores must not be NULL"); return LUVC_ERR_INVALID_ARG; }
     if (D < 1 || row_stride < D) { set_error("need D >= 1 and row_stride >= D (got %d, %lld)", D, (long long)row_stride); return LUVC_ERR_INVALID_ARG; }
     if (n_keep && (!kept_idx || !origin_out)) { set_error("kept_idx and origin_out must be given with n_keep"); return LUVC_ERR_INVALID_ARG; }
-    std::vector<SpuRun> runs;
-    if (!spu_runs(n_samples, N, sigma, n_keep, &runs)) return LUVC_ERR_INVALID_ARG;
+    // What is scored together and what is pruned together are runs of their own: which kernel scores a sample, and with it the
+    // workspace, follows from lengths and cut-offs alone, as in the query, which has no keep counts.
+    std::vector<SpuRun> runs, kept;
+    if (!spu_runs(n_samples, N, sigma, nullptr, &runs) || (n_keep && !spu_runs(n_samples, N, sigma, n_keep, &kept))) return LUVC_ERR_INVALID_ARG;
     const bool circ = spu_circ_aligned(x, D, row_stride, dtype);
-    size_t shared = 0;
-    for (const SpuRun& r : runs) {
-        const size_t b = luvc_spu_workspace_bytes(r.count, r.N, D, dtype, r.sigma);
-        if (b == 0) { set_error("run of %d samples with N=%d, sigma=%d is not supported", r.count, r.N, r.sigma); return LUVC_ERR_INVALID_ARG; }
-        if (!workspace_ok(workspace, workspace_bytes, b)) return LUVC_ERR_WORKSPACE;
-        if (circ && spu_circ_in_batch(r.count, r.N, D, r.sigma, dtype)) shared += spu_circ_bytes(r.count, r.N, D);
-    }
-    if (!workspace_ok(workspace, workspace_bytes, align_up(shared))) return LUVC_ERR_WORKSPACE;
+    const size_t need = spu_runs_workspace(runs, D, dtype, circ);
+    if (need == 0) return LUVC_ERR_INVALID_ARG;
+    if (!workspace_ok(workspace, workspace_bytes, need)) return LUVC_ERR_WORKSPACE;
     const size_t es = esz(dtype);
     hipStream_t st = (hipStream_t)hip_stream;
     // scores: the short samples share launches, every other run is a call of its own
@@ -340,7 +345,7 @@ luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N
     // keep and gather (a sample that is eliminated only gets its scores)
     PruneRuns pr;
     pr.n = 0;
-    for (const SpuRun& r : runs) {
+    for (const SpuRun& r : kept) {
         if (r.keep == 0) continue;
         pr.run[pr.n++] = PruneRun{0, r.N, r.keep, r.count, r.tok_in, r.tok_out};
         if (pr.n < kPruneMaxRuns) continue;

@@ -232,6 +232,27 @@ def test_ragged_queries_and_arguments(L):
     assert rc == lv.LUVC_ERR_INVALID_ARG and b"axis" in L.luvc_last_error()
 
 
+@pytest.mark.parametrize("dt", [lv.LUVC_F32, lv.LUVC_BF16])
+@pytest.mark.parametrize("D", [96, 1024, 3584, 3585])
+def test_spu_ragged_workspace_does_not_depend_on_keep_counts(L, dt, D):
+    """The query has no keep counts, so a call may not need more for any of them: equal samples with distinct counts, with
+    equal ones, and with runs of other lengths between them.  Without a workspace a call names its need."""
+    i32 = lambda v: (ctypes.c_int32 * len(v))(*v)
+    one = ctypes.c_void_p(256)
+    lengths = [[729] * 12, [64] * 40, [1000] * 40, [500] * 40, [700] * 64, [729] * 6 + [300] * 3 + [729] * 6, [2048] * 3 + [196] * 9]
+    for ns in lengths:
+        sg = [max(1, n // 10) for n in ns]
+        need = L.luvc_spu_ragged_workspace_bytes(len(ns), i32(ns), D, dt, i32(sg))
+        assert need > 0
+        for keeps in (None, [n // 10 for n in ns], [n // 10 + i % 3 for i, n in enumerate(ns)], [n // 10 + i for i, n in enumerate(ns)]):
+            rc = L.luvc_spu_stage_ragged(one, len(ns), i32(ns), D, D, dt, i32(sg), 1, None if keeps is None else i32(keeps), None,
+                                         one, one, one, one, None, 0, None)
+            assert rc == lv.LUVC_ERR_WORKSPACE
+            called = int(re.search(r"(\d+) bytes are needed", lv.last_error()).group(1))
+            assert called <= need, (ns[0], len(ns), keeps)
+            assert D % 2 or called == need, (ns[0], len(ns), keeps)        # odd rows may need less: they share no launch
+
+
 def test_header_is_plain_c(tmp_path):
     """include/luvc.h must be usable from C (and C++) without any HIP or torch header."""
     import shutil

@@ -76,10 +76,12 @@ def test_oim_ragged_explicit_schedules(oracle):
     assert to == gx.shape[0]
 
 
-def spu_ragged_case(oracle, lengths, D, dtype, ratio, seed, origin_shift=None):
+def spu_ragged_case(oracle, lengths, D, dtype, ratio, seed, origin_shift=None, sigmas=None, keeps=None):
     rng = np.random.default_rng(seed)
-    sigmas = [max(1, int(ratio * n / 2)) if n > 1 else 0 for n in lengths]
-    keeps = [lv.luvc_keep_count(n, ratio) for n in lengths]
+    if sigmas is None:
+        sigmas = [max(1, int(ratio * n / 2)) if n > 1 else 0 for n in lengths]
+    if keeps is None:
+        keeps = [lv.luvc_keep_count(n, ratio) for n in lengths]
     xs = [wl.cast_io((rng.standard_normal((1, n, D)) + np.sin(np.arange(n) / 5.0)[None, :, None] * rng.standard_normal((1, 1, D))).astype(np.float32), dtype)
           for n in lengths]
     print(f"[ragged spu] lengths={lengths} D={D} dtype={dtype} keeps={keeps}", flush=True)
@@ -117,6 +119,13 @@ def test_spu_ragged_batch(oracle, dtype):
     lengths = [1024, 1024, 720, 196, 196, 300, 64, 97, 256, 1]
     spu_ragged_case(oracle, lengths, 96, dtype, 0.25, 4)
     spu_ragged_case(oracle, lengths[2:], 70, dtype, 0.1, 5, origin_shift=7)
+
+
+@pytest.mark.parametrize("n, count, D, dtype", [(729, 12, 3584, "bf16"), (500, 12, 3584, "f32"), (24, 9, 64, "bf16")])
+def test_spu_equal_samples_with_keep_counts_of_their_own(oracle, n, count, D, dtype):
+    """Equal samples are scored together whatever they keep: the first two batches score on another kernel together than one
+    by one, whose need the workspace query would not have covered."""
+    spu_ragged_case(oracle, [n] * count, D, dtype, 0.1, 31, sigmas=[4] * count, keeps=[n // 10 + i for i in range(count)])
 
 
 def test_ragged_errors():
