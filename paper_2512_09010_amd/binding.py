@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from itertools import chain
 from typing import List, Optional, Sequence, Tuple
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -169,6 +170,12 @@ class _Bounded(dict):
         return value
 
 
+def _ints(*lists) -> bool:
+    """Only tuples of plain ints become a key: an entry that may be changed in place (a 0-d tensor hashes by identity) would
+    be found again with another value.  Looking up needs no such care: what equals a tuple of ints holds these values now."""
+    return set(map(type, lists)) <= {tuple} and set(map(type, chain.from_iterable(lists))) <= {int}
+
+
 _schedules = _Bounded()
 
 
@@ -177,12 +184,12 @@ def _schedule(passes):
     try:
         key = tuple(passes)
         hit = _schedules.get(key)
-    except TypeError:                                   # passes that do not hash: lists, arrays
+    except TypeError:                                   # entries that do not hash
         key, hit = None, None
     if hit is None:
         arr = _passes(passes)
         hit = (arr, ctypes.addressof(arr), len(passes))
-        if key is not None:
+        if key is not None and _ints(*key):
             _schedules.keep(key, hit)
     return hit
 
@@ -218,11 +225,11 @@ def luvc_oim_workspace_bytes(B, H, W, D, dtype_code, passes) -> int:
 
 
 def out_grid(H: int, W: int, passes) -> Tuple[int, int]:
-    for axis, m in passes:
+    for axis, m in passes:                              # not in place: H and W may be the caller's 0-d tensors
         if axis == 1:
-            W -= m
+            W = W - m
         else:
-            H -= m
+            H = H - m
     return H, W
 
 
@@ -449,6 +456,19 @@ class _RaggedMerge:
         self.addr = [ctypes.addressof(a) for a in (self.H, self.W, self.passes, self.n_passes)]
 
 
+def _merge_plan(shapes, schedules, D, code) -> _RaggedMerge:
+    try:
+        key = (D, code, tuple(shapes), tuple(map(tuple, schedules)))
+        plan = _ragged_merges.get(key)
+    except TypeError:                                   # entries that do not hash
+        key, plan = None, None
+    if plan is None:
+        plan = _RaggedMerge(shapes, schedules, D, code)
+        if key is not None and _ints(*key[2], *chain.from_iterable(key[3])):
+            _ragged_merges.keep(key, plan)
+    return plan
+
+
 def luvc_oim_merge_ragged(x, shapes, schedules, sizes=None, want_maps: bool = True, workspace=None, stream=None):
     """x: CUDA tensor [sum H_i*W_i, D], image after image; shapes [(H_i, W_i)]; schedules: one pass list per image.
     Returns dict(x [sum H'_i*W'_i, D], sizes, merged_map, kept_map, out_shapes)."""
@@ -457,15 +477,7 @@ def luvc_oim_merge_ragged(x, shapes, schedules, sizes=None, want_maps: bool = Tr
     assert x.is_cuda and x.is_contiguous() and x.dim() == 2 and len(shapes) == len(schedules)
     T, D = x.shape
     code = _dtype_code(x)
-    try:
-        key = (D, code, tuple(shapes), tuple(map(tuple, schedules)))
-        plan = _ragged_merges.get(key)
-    except TypeError:                                   # shapes or passes that do not hash
-        key, plan = None, None
-    if plan is None:
-        plan = _RaggedMerge(shapes, schedules, D, code)
-        if key is not None:
-            _ragged_merges.keep(key, plan)
+    plan = _merge_plan(shapes, schedules, D, code)
     assert T == plan.tokens_in
     To = plan.tokens_out
     if workspace is None:
@@ -498,6 +510,19 @@ class _RaggedStage:
         self.addr = [None if a is None else ctypes.addressof(a) for a in (self.N, self.sigma, self.keep)]
 
 
+def _stage_plan(lengths, sigmas, keeps, D, code) -> _RaggedStage:
+    try:
+        key = (D, code, tuple(lengths), tuple(sigmas), None if keeps is None else tuple(keeps))
+        plan = _ragged_stages.get(key)
+    except TypeError:
+        key, plan = None, None
+    if plan is None:
+        plan = _RaggedStage(lengths, sigmas, keeps, D, code)
+        if key is not None and _ints(*key[2:4], key[4] or ()):
+            _ragged_stages.keep(key, plan)
+    return plan
+
+
 def luvc_spu_stage_ragged(x, lengths, sigmas, keeps=None, use_hamming: bool = True, origin=None, gather: bool = True,
                           workspace=None, stream=None):
     """x: CUDA tensor [sum N_i, D] (rows evenly strided), sample after sample; lengths, sigmas, keeps: per sample.
@@ -507,15 +532,7 @@ def luvc_spu_stage_ragged(x, lengths, sigmas, keeps=None, use_hamming: bool = Tr
     assert x.is_cuda and x.dim() == 2 and x.stride(1) == 1 and len(lengths) == len(sigmas)
     T, D = x.shape
     code = _dtype_code(x)
-    try:
-        key = (D, code, tuple(lengths), tuple(sigmas), None if keeps is None else tuple(keeps))
-        plan = _ragged_stages.get(key)
-    except TypeError:
-        key, plan = None, None
-    if plan is None:
-        plan = _RaggedStage(lengths, sigmas, keeps, D, code)
-        if key is not None:
-            _ragged_stages.keep(key, plan)
+    plan = _stage_plan(lengths, sigmas, keeps, D, code)
     assert T == plan.tokens
     K = plan.kept
     if origin is not None:

@@ -4,7 +4,9 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
+import torch
 
 from paper_2512_09010_amd import binding as lv
 from paper_2512_09010_amd import build as lvbuild
@@ -251,6 +253,31 @@ def test_spu_ragged_workspace_does_not_depend_on_keep_counts(L, dt, D):
             called = int(re.search(r"(\d+) bytes are needed", lv.last_error()).group(1))
             assert called <= need, (ns[0], len(ns), keeps)
             assert D % 2 or called == need, (ns[0], len(ns), keeps)        # odd rows may need less: they share no launch
+
+
+@pytest.mark.parametrize("make", [torch.tensor, lambda v: np.array(v, dtype=np.int64)], ids=["tensor", "array"])
+def test_argument_lists_follow_entries_changed_in_place(L, make):
+    """0-d tensors pass for integers and hash by identity; what was marshalled from them may not be taken for later values."""
+    m, h, keep, sigma = make(2), make(12), make(3), make(4)
+    passes, shapes = [(1, m), (0, 2)], [(h, 8)]
+    for step in range(3):
+        arr, addr, n = lv._schedule(passes)
+        assert addr == ctypes.addressof(arr) and [(arr[i].axis, arr[i].m) for i in range(n)] == [(1, 2 + step), (0, 2)]
+        plan = lv._merge_plan(shapes, [passes], 16, lv.LUVC_BF16)
+        assert (plan.H[0], plan.passes[0].m, plan.tokens_in) == (12 + step, 2 + step, (12 + step) * 8)
+        assert tuple(map(int, plan.out_shapes[0])) == (10 + step, 6 - step)
+        st = lv._stage_plan([16, 16], [sigma, 4], [keep, 3], 16, lv.LUVC_BF16)
+        assert (st.sigma[0], st.keep[0], st.kept) == (4 + step, 3 + step, 6 + step)
+        for v in (m, h, keep, sigma):
+            v += 1
+
+
+def test_argument_lists_of_plain_integers_are_kept(L):
+    assert lv._schedule([(1, 2), (0, 2)])[1] == lv._schedule(((1, 2), (0, 2)))[1]
+    assert lv._merge_plan([(8, 8)], [[(1, 2)]], 16, 1) is lv._merge_plan(((8, 8),), (((1, 2),),), 16, 1)
+    assert lv._stage_plan([8], [2], [3], 16, 1) is lv._stage_plan((8,), (2,), (3,), 16, 1)
+    assert lv._stage_plan([8], [2], None, 16, 1) is not lv._stage_plan([8], [2], [], 16, 1)
+    assert lv._schedule([(1, 1.0)])[0][0].m == lv._schedule([(1, True)])[0][0].m == lv._schedule([[1, 1]])[0][0].m == 1
 
 
 def test_header_is_plain_c(tmp_path):
