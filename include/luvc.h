@@ -198,12 +198,14 @@ luvc_status luvc_spu_score(const void* x, int B, int N, int D, int64_t row_strid
 
 /*
  * luvc_spu_score for callers that cannot allocate device memory and so have no workspace to pass: code that runs
- * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same arithmetic and
- * the same bits in `scores` as luvc_spu_score; the scratch lives in a static device array of
+ * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels and same arithmetic as
+ * luvc_spu_score; the scratch lives in a static device array of
  * LUVC_SPU_STATIC_SCRATCH_BYTES inside the library (one copy per GPU, held until the process ends).  The call
- * allocates and frees no device memory and calls no library routine that does.
+ * allocates and frees no device memory and calls no library routine that does.  Where luvc_spu_workspace_bytes fits the
+ * array the scores have the same bits as those of luvc_spu_score; a call that wants more but can do with less (long
+ * samples split over fewer workgroups) runs with less, and its sums over channels are then formed in other parts.
  *   x, B, N, D, row_stride, dtype, sigma, use_hamming, scores, hip_stream   as for luvc_spu_score
- * Returns LUVC_ERR_WORKSPACE (nothing enqueued) when luvc_spu_workspace_bytes(B, N, D, dtype, sigma) exceeds
+ * Returns LUVC_ERR_WORKSPACE (nothing enqueued) when the least the call can do with exceeds
  * LUVC_SPU_STATIC_SCRATCH_BYTES; the message carries both figures.
  * Every call on a GPU uses that GPU's one array: two calls that overlap in time on one GPU (different streams, or a
  * captured graph replayed while another call runs) race on it and give wrong scores.  Calls on one stream, one

@@ -160,6 +160,21 @@ bool workspace_ok(const void* ws, size_t have, size_t need)
     return true;
 }
 
+luvc_status spu_score_call(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dtype, int sigma, int use_hamming,
+                           float* scores, void* workspace, size_t workspace_bytes, size_t most, void* hip_stream)
+{
+    if (!dtype_ok(dtype)) { set_error("unknown dtype %d", (int)dtype); return LUVC_ERR_INVALID_ARG; }
+    if (!x || !scores) { set_error("x and scores must not be NULL"); return LUVC_ERR_INVALID_ARG; }
+    if (B < 1 || N < 1 || D < 1) { set_error("B, N, D must be positive (got %d,%d,%d)", B, N, D); return LUVC_ERR_INVALID_ARG; }
+    if (row_stride < D) { set_error("row_stride %lld is smaller than D=%d", (long long)row_stride, D); return LUVC_ERR_INVALID_ARG; }
+    if (sigma < 0 || sigma > N / 2) { set_error("sigma=%d must lie in 0..N/2=%d", sigma, N / 2); return LUVC_ERR_INVALID_ARG; }
+    if (N > kSpuMaxN) { set_error("N=%d exceeds the supported %d tokens per sample", N, kSpuMaxN); return LUVC_ERR_UNSUPPORTED; }
+    if (B > 65535) { set_error("B=%d exceeds 65535 samples per call", B); return LUVC_ERR_UNSUPPORTED; }
+    const size_t need = spu_workspace(B, N, D, sigma, dtype, most);
+    if (!workspace_ok(workspace, workspace_bytes, need)) return LUVC_ERR_WORKSPACE;
+    return spu_score_dense(x, B, N, D, row_stride, dtype, sigma, use_hamming ? 1 : 0, scores, workspace, most, (hipStream_t)hip_stream);
+}
+
 }  // namespace luvc
 
 using namespace luvc;
@@ -570,16 +585,7 @@ size_t luvc_spu_workspace_bytes(int B, int N, int D, luvc_dtype dtype, int sigma
 luvc_status luvc_spu_score(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dtype, int sigma,
                            int use_hamming, float* scores, void* workspace, size_t workspace_bytes, void* hip_stream)
 {
-    if (!dtype_ok(dtype)) { set_error("unknown dtype %d", (int)dtype); return LUVC_ERR_INVALID_ARG; }
-    if (!x || !scores) { set_error("x and scores must not be NULL"); return LUVC_ERR_INVALID_ARG; }
-    if (B < 1 || N < 1 || D < 1) { set_error("B, N, D must be positive (got %d,%d,%d)", B, N, D); return LUVC_ERR_INVALID_ARG; }
-    if (row_stride < D) { set_error("row_stride %lld is smaller than D=%d", (long long)row_stride, D); return LUVC_ERR_INVALID_ARG; }
-    if (sigma < 0 || sigma > N / 2) { set_error("sigma=%d must lie in 0..N/2=%d", sigma, N / 2); return LUVC_ERR_INVALID_ARG; }
-    if (N > kSpuMaxN) { set_error("N=%d exceeds the supported %d tokens per sample", N, kSpuMaxN); return LUVC_ERR_UNSUPPORTED; }
-    if (B > 65535) { set_error("B=%d exceeds 65535 samples per call", B); return LUVC_ERR_UNSUPPORTED; }
-    const size_t need = spu_workspace(B, N, D, sigma, dtype);
-    if (!workspace_ok(workspace, workspace_bytes, need)) return LUVC_ERR_WORKSPACE;
-    return spu_score_dense(x, B, N, D, row_stride, dtype, sigma, use_hamming ? 1 : 0, scores, workspace, (hipStream_t)hip_stream);
+    return spu_score_call(x, B, N, D, row_stride, dtype, sigma, use_hamming, scores, workspace, workspace_bytes, SIZE_MAX, hip_stream);
 }
 
 int luvc_keep_count(int N, double keep_ratio)

@@ -20,12 +20,15 @@ struct SpuLayout {
     int n_tiles;
     SpuPath path;
 };
-SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, bool circ);
-size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt);
+SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, bool circ, size_t most);
+size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most = SIZE_MAX);
 bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt);
 
 luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma,
-                            int use_hamming, float* scores, void* workspace, hipStream_t st);
+                            int use_hamming, float* scores, void* workspace, size_t most, hipStream_t st);
+// luvc_spu_score behind its entry points; most: the layout has to fit so much scratch (SIZE_MAX: the quickest one)
+luvc_status spu_score_call(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dtype, int sigma, int use_hamming,
+                           float* scores, void* workspace, size_t workspace_bytes, size_t most, void* hip_stream);
 
 // Fast path (spu_fft.hip): N = 16 * Q * N2 with Q in {16, 15, 9}, 2 * sigma + 1 <= 16 * Q, N <= 4096.
 bool spu_fft_supported(int N, int sigma);
@@ -47,7 +50,7 @@ luvc_status spu_score_circ(const void* x, int64_t row_stride, int D, luvc_dtype 
 
 // Any N (spu_conv.hip): N <= 8192, or N = 16384
 int spu_conv_points(int N, bool* half);
-int spu_conv_tiles(int B, int N, int D);
+int spu_conv_tiles(int B, int N, int D, int most = INT32_MAX);
 double spu_conv_us(int B, int N, int D, luvc_dtype dt);
 size_t spu_conv_spec_bytes(int N);
 inline int spu_conv_ld(int N) { return (N + 3) / 4 * 4; }

@@ -459,15 +459,17 @@ int spu_conv_points(int N, bool* half)
 static int conv_pairs(int M) { return M <= 2048 ? 8 : M <= 4096 ? 4 : M <= 8192 ? 2 : 1; }
 
 // Workgroups per sample.  One workgroup fills a compute unit; a workgroup's time is its pair groups plus about one more
-// for tables and hand-over, and the launch takes as many rounds of that as there are multiples of 256 workgroups.
-int spu_conv_tiles(int B, int N, int D)
+// for tables and hand-over, and the launch takes as many rounds of that as there are multiples of 256 workgroups.  At most
+// `most` of them.
+int spu_conv_tiles(int B, int N, int D, int most)
 {
     bool half;
     const int P = conv_pairs(spu_conv_points(N, &half)), ng = (D + 2 * P - 1) / (2 * P);
-    int best = ng;
+    int best = ng < most ? ng : most;
     int64_t best_cost = INT64_MAX;
     for (int g = 1; g <= ng && g <= 64; ++g) {
         const int t = (ng + g - 1) / g;
+        if (t > most) continue;
         const int64_t cost = (((int64_t)B * t + 255) / 256) * (g + 1);
         if (cost < best_cost) { best_cost = cost; best = t; }
     }

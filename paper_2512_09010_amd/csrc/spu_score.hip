@@ -206,44 +206,63 @@ bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt)
     return N <= kCircMaxN && circ_work_us(B, N, D, dt) <= us;
 }
 
-SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, bool circ)
+// Energies per tile and group of tiles, arrival words.  Up to kTileGroup tiles have no group level.
+static size_t tile_bytes(int B, int n_tiles, size_t ld, SpuLayout* L, size_t off)
+{
+    const int groups = spu_tile_groups(n_tiles);
+    L->partial = off;  off += align_up(sizeof(float) * (size_t)B * n_tiles * ld);
+    L->gpartial = off; off += groups > 1 ? align_up(sizeof(float) * (size_t)B * groups * ld) : 0;
+    L->arrive = off;   off += align_up(sizeof(tile_tag_t) * (size_t)B * (groups + 1));
+    return off;
+}
+
+// most: scratch the call has to do with; a layout that needs more is returned where nothing smaller serves the call.  Short
+// samples then go to the kernels of long ones; spu_conv takes fewer workgroups per sample, down to one per 64 channels,
+// which is what the direct path's energies take (1 x 8192 x 2048: 256 of them want 8.9 MB, 205 want 7.2).
+SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, bool circ, size_t most)
 {
     SpuLayout L{};
     L.path = spu_path(B, N, D, sigma, dt, circ);
     if (L.path == SpuPath::Circ) {
         L.n_tiles = 1;
         L.bytes = align_up(spu_circ_bytes(B, N, D));
-        return L;
+        return L.bytes > most ? spu_layout(B, N, D, sigma, dt, false, most) : L;
     }
-    L.n_tiles = L.path == SpuPath::Fft ? (D + 31) / 32 : L.path == SpuPath::Conv ? spu_conv_tiles(B, N, D) : (D + 63) / 64;
+    L.n_tiles = L.path == SpuPath::Fft ? (D + 31) / 32 : (D + 63) / 64;
     const bool dense = L.path == SpuPath::Dense;                     // the one path whose tables and spectra do not stay in LDS
     const size_t spec = dense ? (size_t)B * (sigma + 1) * D : 0;     // pass-band spectra
-    const size_t ld = L.path == SpuPath::Conv ? spu_conv_ld(N) : N;
     size_t off = 0;
     L.tw = off;      off += dense ? align_up(sizeof(float2) * (size_t)N) : 0;
     L.gk = off;      off += dense ? align_up(sizeof(float) * (size_t)(sigma + 1)) : 0;
     L.gm = off;      off += dense ? align_up(sizeof(float) * (size_t)(sigma + 1)) : 0;
     L.Fc = off;      off += align_up(sizeof(float) * spec);
     L.Fs = off;      off += align_up(sizeof(float) * spec);
-    L.spec = off;    off += L.path == SpuPath::Conv ? align_up(spu_conv_spec_bytes(N)) : 0;
-    L.partial = off; off += align_up(sizeof(float) * (size_t)B * L.n_tiles * ld);
-    L.gpartial = off; off += align_up(sizeof(float) * (size_t)B * spu_tile_groups(L.n_tiles) * ld);
-    L.arrive = off;  off += align_up(sizeof(tile_tag_t) * (size_t)B * (spu_tile_groups(L.n_tiles) + 1));
-    L.bytes = off;
-    return L;
+    L.spec = off;
+    if (L.path != SpuPath::Conv) {
+        L.bytes = tile_bytes(B, L.n_tiles, N, &L, off);
+        return L;
+    }
+    off += align_up(spu_conv_spec_bytes(N));
+    const int fewest = L.n_tiles;
+    for (int limit = INT32_MAX;;) {
+        L.n_tiles = spu_conv_tiles(B, N, D, limit);
+        L.bytes = tile_bytes(B, L.n_tiles, spu_conv_ld(N), &L, off);
+        if (L.bytes <= most || L.n_tiles <= fewest) return L;
+        limit = L.n_tiles - 1;
+    }
 }
 
 // what a call needs whichever way its rows lie
-size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt)
+size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most)
 {
-    const size_t a = spu_layout(B, N, D, sigma, dt, true).bytes, b = spu_layout(B, N, D, sigma, dt, false).bytes;
+    const size_t a = spu_layout(B, N, D, sigma, dt, true, most).bytes, b = spu_layout(B, N, D, sigma, dt, false, most).bytes;
     return a > b ? a : b;
 }
 
 luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma,
-                            int use_hamming, float* scores, void* workspace, hipStream_t st)
+                            int use_hamming, float* scores, void* workspace, size_t most, hipStream_t st)
 {
-    const SpuLayout L = spu_layout(B, N, D, sigma, dt, spu_circ_aligned(x, D, row_stride, dt));
+    const SpuLayout L = spu_layout(B, N, D, sigma, dt, spu_circ_aligned(x, D, row_stride, dt), most);
     char* ws = (char*)workspace;
     if (L.path == SpuPath::Circ) {
         CircRuns runs;

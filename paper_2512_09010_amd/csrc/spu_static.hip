@@ -51,14 +51,17 @@ extern "C" luvc_status luvc_spu_score_static(const void* x, int B, int N, int D,
     const size_t need = luvc_spu_workspace_bytes(B, N, D, dtype, sigma);
     // invalid arguments (need == 0): the checks of luvc_spu_score name the problem; no workspace is looked at before they fail
     if (need == 0) return luvc_spu_score(x, B, N, D, row_stride, dtype, sigma, use_hamming, scores, nullptr, 0, hip_stream);
-    if (need > kStaticScratchBytes) {
+    // a long sample asks for as many tiles as there are compute units, but does with fewer where the array is too small for them
+    const size_t most = need > kStaticScratchBytes ? kStaticScratchBytes : SIZE_MAX;
+    const size_t least = most == SIZE_MAX ? need : spu_workspace(B, N, D, sigma, dtype, most);
+    if (least > kStaticScratchBytes) {
         set_error("luvc_spu_score_static: B=%d N=%d D=%d sigma=%d needs %zu bytes of scratch, the static buffer holds %zu; "
-                  "use luvc_spu_score with a workspace", B, N, D, sigma, need, kStaticScratchBytes);
+                  "use luvc_spu_score with a workspace", B, N, D, sigma, least, kStaticScratchBytes);
         return LUVC_ERR_WORKSPACE;
     }
     void* ws = static_scratch();
     if (!ws) return LUVC_ERR_HIP;
     // nothing in the scratch has to start at zero: tile energies and group sums are written before they are read, and
     // the arrival words recognise what an earlier call left behind by its tag
-    return luvc_spu_score(x, B, N, D, row_stride, dtype, sigma, use_hamming, scores, ws, kStaticScratchBytes, hip_stream);
+    return spu_score_call(x, B, N, D, row_stride, dtype, sigma, use_hamming, scores, ws, kStaticScratchBytes, most, hip_stream);
 }

@@ -114,6 +114,18 @@ def test_oim_merge_rejects_bad_arguments(L):
     assert lv.last_error() != ""
 
 
+# sizes, and the scratch that the direct path (tables, spectra, energies per 64 channels) takes for them
+@pytest.mark.parametrize("B, N, D, dt, sigma", [(1, 8192, 2048, 1, 204), (1, 7800, 2048, 1, 195), (1, 8000, 3584, 0, 200), (2, 7800, 1280, 1, 195),
+                                                (4, 8000, 896, 0, 200), (1, 16384, 896, 0, 0), (16, 8192, 64, 0, 819), (5000, 205, 1, 0, 0)])
+def test_static_scratch_takes_long_samples(L, B, N, D, dt, sigma):
+    """Calls whose quickest layout is larger than the static array but which can do with less: refused only for want of a GPU."""
+    if torch.cuda.device_count():
+        pytest.skip("the pointers are dummies: nothing may be launched")
+    assert lv.luvc_spu_workspace_bytes(B, N, D, dt, sigma) > (4 << 20)
+    assert L.luvc_spu_score_static(FAKE, B, N, D, D, dt, sigma, 1, FAKE, None) == lv.LUVC_ERR_HIP, lv.last_error()
+    assert L.luvc_spu_score_static(FAKE, 8 * B, N, 2 * D + 64, 2 * D + 64, dt, sigma, 1, FAKE, None) == lv.LUVC_ERR_WORKSPACE
+
+
 def test_spu_rejects_bad_arguments(L):
     sc = lambda **kw: [kw.get("x", FAKE), kw.get("B", 2), kw.get("N", 64), kw.get("D", 128), kw.get("rs", 128),
                        kw.get("dt", lv.LUVC_BF16), kw.get("sigma", 6), 1, kw.get("out", FAKE), kw.get("ws", None),

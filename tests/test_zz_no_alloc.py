@@ -35,6 +35,20 @@ def test_static_scratch_matches_the_workspace_call():
         assert bool((got >= 0).all())
 
 
+@pytest.mark.parametrize("B, N, D, dtype, sigma", [(1, 8192, 2048, "bf16", 204), (2, 7800, 1280, "bf16", 195), (1, 16384, 896, "f32", 5)])
+def test_static_scratch_with_fewer_workgroups_per_sample(B, N, D, dtype, sigma):
+    """Long samples whose energies do not fit the array at the usual number of workgroups: other partial sums of the same
+    squares.  A workgroup adds up to 64 groups of pairs, two roundings of 2^-24 each: 2^-17 on its sum, 2^-18 on the root,
+    on either side."""
+    code = lv.LUVC_BF16 if dtype == "bf16" else lv.LUVC_F32
+    assert lv.luvc_spu_workspace_bytes(B, N, D, code, sigma) > lv.SPU_STATIC_SCRATCH_BYTES
+    x = _x(50, B, N, D, dtype)
+    got = lv.luvc_spu_score_static(x, sigma, True)
+    want = lv.luvc_spu_score(x, sigma, True)
+    torch.cuda.synchronize()
+    torch.testing.assert_close(got, want, rtol=2.0 ** -17, atol=0)
+
+
 def test_static_scratch_rejects_what_does_not_fit():
     B, N, D, sigma = 40, 2048, 4096, 102
     assert lv.luvc_spu_workspace_bytes(B, N, D, lv.LUVC_BF16, sigma) > lv.SPU_STATIC_SCRATCH_BYTES
