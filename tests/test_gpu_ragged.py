@@ -121,11 +121,12 @@ def test_spu_ragged_batch(oracle, dtype):
     spu_ragged_case(oracle, lengths[2:], 70, dtype, 0.1, 5, origin_shift=7)
 
 
-@pytest.mark.parametrize("n, count, D, dtype", [(729, 12, 3584, "bf16"), (500, 12, 3584, "f32"), (24, 9, 64, "bf16")])
-def test_spu_equal_samples_with_keep_counts_of_their_own(oracle, n, count, D, dtype):
+# seeds: the first from 31 on whose keep sets are all decided by more than the margin of the scores
+@pytest.mark.parametrize("n, count, D, dtype, seed", [(729, 12, 3584, "bf16", 31), (500, 12, 3584, "f32", 35), (24, 9, 64, "bf16", 31)])
+def test_spu_equal_samples_with_keep_counts_of_their_own(oracle, n, count, D, dtype, seed):
     """Equal samples are scored together whatever they keep: the first two batches score on another kernel together than one
     by one, whose need the workspace query would not have covered."""
-    spu_ragged_case(oracle, [n] * count, D, dtype, 0.1, 31, sigmas=[4] * count, keeps=[n // 10 + i for i in range(count)])
+    spu_ragged_case(oracle, [n] * count, D, dtype, 0.1, seed, sigmas=[4] * count, keeps=[n // 10 + i for i in range(count)])
 
 
 def test_ragged_errors():
