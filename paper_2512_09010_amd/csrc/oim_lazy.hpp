@@ -113,9 +113,9 @@ __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGe
 #pragma unroll
             for (int e = 0; e < V; ++e) {
                 // acc / S, correctly rounded: the reciprocal is, and one step on the exact remainder corrects the product
-                // (a zero keeps its sign)
+                // (a zero keeps its sign, an infinity, whose remainder is no number, stays one)
                 const double w = acc[u][e] * inv, rem = fma(-w, S, acc[u][e]);
-                io_traits<T>::store(&q[e], rem == 0.0 ? w : fma(rem, inv, w));
+                io_traits<T>::store(&q[e], __builtin_islessgreater(rem, 0.0) ? fma(rem, inv, w) : w);
             }
             *reinterpret_cast<lz_u32x4*>(o + d) = *reinterpret_cast<const lz_u32x4*>(q);
         }

@@ -232,3 +232,34 @@ def test_wide_determinism():
         torch.cuda.synchronize()
         for k in ("x", "sizes", "merged_map", "kept_map"):
             assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("radius", [0, 1])
+def test_infinite_channels_stay_infinite_in_the_means(dtype, radius):
+    """Which tokens merge is unspecified beside an infinity, what a merge makes of its tokens is not: the size-weighted mean of
+    the group that the maps state, an infinite channel infinite with its sign, opposite ones no number."""
+    rng = np.random.default_rng(77)
+    B, H, W, D = 2, 12, 20, 64
+    x = wl.widen(wl.cast_io(rng.standard_normal((B, H, W, D)).astype(np.float32), dtype), dtype)
+    x[rng.random(x.shape) < 0.01] = np.inf
+    x[rng.random(x.shape) < 0.01] = -np.inf
+    sizes = rng.integers(1, 4, (B, H, W)).astype(np.int32)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    xd, sd = torch.from_numpy(x).to(tdt).cuda(), torch.from_numpy(sizes).cuda()
+    passes = [(W_AX, 7)]
+    out = lv.luvc_oim_merge(xd, passes, sizes=sd) if radius else lv.luvc_oim_merge_wide(xd, passes, 0, sizes=sd)
+    torch.cuda.synchronize()
+    n_out = H * (W - 7)
+    merged = out["merged_map"].cpu().numpy()
+    want, total = np.zeros((B, n_out, D)), np.zeros((B, n_out))
+    with np.errstate(invalid="ignore"):
+        for b in range(B):
+            np.add.at(want[b], merged[b], x[b].reshape(-1, D) * sizes[b].reshape(-1, 1))
+            np.add.at(total[b], merged[b], sizes[b].reshape(-1))
+        want /= total[:, :, None]
+    got = to_host_f64(out["x"]).reshape(B, n_out, D)
+    np.testing.assert_array_equal(out["sizes"].cpu().numpy().reshape(B, n_out), total)
+    assert (np.isinf(want) & (total[:, :, None] > sizes.max())).sum() > 20          # in groups of several tokens
+    # one rounding to the storage type on either side of the mean: 2^-8 (bf16), 2^-23 (f32)
+    np.testing.assert_allclose(got, want, rtol=2.0 ** (-8 if dtype == "bf16" else -23), atol=1e-30)
