@@ -315,7 +315,7 @@ luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N
     // workspace, follows from lengths and cut-offs alone, as in the query, which has no keep counts.
     std::vector<SpuRun> runs, kept;
     if (!spu_runs(n_samples, N, sigma, nullptr, &runs) || (n_keep && !spu_runs(n_samples, N, sigma, n_keep, &kept))) return LUVC_ERR_INVALID_ARG;
-    const bool circ = spu_circ_aligned(x, D, row_stride, dtype);
+    const bool circ = spu_circ_rows(x, D, row_stride, dtype) != CircRows::None;
     const size_t need = spu_runs_workspace(runs, D, dtype, circ);
     if (need == 0) return LUVC_ERR_INVALID_ARG;
     if (!workspace_ok(workspace, workspace_bytes, need)) return LUVC_ERR_WORKSPACE;

@@ -14,13 +14,16 @@ enum class SpuPath {
     Dense       // direct pass-band DFT through the workspace, any N
 };
 
+// How spu_circ reads the rows of a call: channel pairs in one access, channel by channel, or not at all (strides too large)
+enum class CircRows { None, Single, Paired };
+
 // Offsets (bytes) of the score kernels' scratch inside the caller's workspace.
 struct SpuLayout {
     size_t tw, gk, gm, Fc, Fs, spec, partial, gpartial, arrive, bytes;
     int n_tiles;
     SpuPath path;
 };
-SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, bool circ, size_t most);
+SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, CircRows circ, size_t most);
 size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most = SIZE_MAX);
 bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt);
 
@@ -44,7 +47,7 @@ struct CircRun {
     int64_t tok0;                    // first token of the first sample
 };
 struct CircRuns { int n; CircRun run[kCircMaxRuns]; };
-bool spu_circ_aligned(const void* x, int D, int64_t row_stride, luvc_dtype dt);
+CircRows spu_circ_rows(const void* x, int D, int64_t row_stride, luvc_dtype dt);
 size_t spu_circ_bytes(int64_t samples, int N, int D);
 luvc_status spu_score_circ(const void* x, int64_t row_stride, int D, luvc_dtype dt, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st);
 

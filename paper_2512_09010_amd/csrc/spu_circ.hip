@@ -20,7 +20,9 @@
 // trip to memory each way, no atomics; nothing has to be set up, and a captured launch replayed with its tag starts over.
 //
 // Bound: matrix cores for N near kCircMaxN (6 N^2 D flops per bf16 sample, 12 for fp32), latency for short samples.
-// 1x729x3584 bf16: 20.5 us (2048-point transform: 24), 8x205x3584: 13.9, 4x144x4096: 9.2, 4x861x1408: 33.6.  Laying out the
+// 1x729x3584 bf16: 20.5 us (2048-point transform: 24), 8x205x3584: 13.9, 4x144x4096: 9.2, 4x861x1408: 33.6.  Rows of odd width,
+// stride or start, channel by channel: 16x64x3585 bf16 11.6 us (1536-point transform: 102), 8x205x3585 15.8 (62), fp32 24
+// (64), 1x64x65 5.0 (14.8), but 1x729x3585 26.7 (22.3).  Laying out the
 // taps costs about 1 us less than with a division per angle and a copy at a time: 1x512x3584 13.9 -> 12.6.
 #include "common.hpp"
 #include "spu.hpp"
@@ -55,12 +57,13 @@ __device__ __forceinline__ circ_f32x16 circ_mac(circ_f32x16 acc, const circ_u32x
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, vb, acc, 0, 0, 0);
 }
 
-// 8 tokens of a channel pair as they lie in memory, and the operands of the two channel tiles made of them
-template <typename T> struct circ_raw;
-template <> struct circ_raw<bf16_t> {
+// 8 tokens of two channels as they lie in memory, and the operands of the two channel tiles made of them.  PAIRED: neighbouring
+// channels, one access; else the channels are 32 apart and fetched one by one (at `off` and `off1`), wherever they start.
+template <typename T, bool PAIRED> struct circ_raw;
+template <> struct circ_raw<bf16_t, true> {
     static constexpr int TERMS = 1;
     uint32_t w[8];
-    __device__ __forceinline__ void fetch(int j, __amdgpu_buffer_rsrc_t r, uint32_t off) { w[j] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
+    __device__ __forceinline__ void fetch(int j, __amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t) { w[j] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
     __device__ __forceinline__ void operands(circ_u32x4 (&even)[1], circ_u32x4 (&odd)[1]) const
     {
 #pragma unroll
@@ -70,10 +73,34 @@ template <> struct circ_raw<bf16_t> {
         }
     }
 };
-template <> struct circ_raw<float> {
+template <> struct circ_raw<bf16_t, false> {
+    static constexpr int TERMS = 1;
+    uint32_t w[8], w1[8];
+    __device__ __forceinline__ void fetch(int j, __amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t off1)
+    {
+        w[j] = __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0);
+        w1[j] = __builtin_amdgcn_raw_buffer_load_b16(r, off1, 0, 0);
+    }
+    __device__ __forceinline__ void operands(circ_u32x4 (&even)[1], circ_u32x4 (&odd)[1]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            even[0][i] = __builtin_amdgcn_perm(w[2 * i + 1], w[2 * i], 0x05040100u);
+            odd[0][i] = __builtin_amdgcn_perm(w1[2 * i + 1], w1[2 * i], 0x05040100u);
+        }
+    }
+};
+template <bool PAIRED> struct circ_raw<float, PAIRED> {
     static constexpr int TERMS = 3;
     circ_u32x2 w[8];
-    __device__ __forceinline__ void fetch(int j, __amdgpu_buffer_rsrc_t r, uint32_t off) { w[j] = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0); }
+    __device__ __forceinline__ void fetch(int j, __amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t off1)
+    {
+        if constexpr (PAIRED) w[j] = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+        else {
+            w[j][0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+            w[j][1] = __builtin_amdgcn_raw_buffer_load_b32(r, off1, 0, 0);
+        }
+    }
     __device__ static __forceinline__ void split(float a, float b, uint32_t& t0, uint32_t& t1, uint32_t& t2)
     {
         t0 = pk_bf16(a, b);
@@ -105,15 +132,16 @@ __host__ __device__ inline int circ_lds(int N, int RT) { return 24 * circ_stride
 }  // namespace
 
 // KS: wavefronts that share the steps of a product, each an equal run of them (RT = 1)
-template <typename T, int RT, int KS>
+template <typename T, int RT, int KS, bool PAIRED /* every channel pair is one aligned access */>
 __global__ void __launch_bounds__(256 * KS, KS == 1 || sizeof(T) == 4 ? 2 : 4)
 spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* workgroups across the channels */, int use_hamming, const CircRuns runs,
          unsigned long long* __restrict__ words /* [groups of 32 RT tokens][n_quads][32 RT] */, uint32_t tag, float* __restrict__ scores)
 {
-    using raw_t = circ_raw<T>;
+    using raw_t = circ_raw<T, PAIRED>;
     constexpr int ROWS = 32 * RT, TERMS = raw_t::TERMS, THREADS = 256 * KS;
     static_assert(KS == 1 || RT == 1, "");
-    constexpr int PF = TERMS == 1 ? (RT == 4 ? 3 : RT == 2 ? 4 : 6) : (RT == 4 ? 2 : RT == 2 ? 3 : 4);      // steps of 16 tokens in flight
+    // steps of 16 tokens in flight; a bf16 channel fetched by itself takes a register, as a pair does
+    constexpr int PF = TERMS == 3 ? (RT == 4 ? 2 : RT == 2 ? 3 : 4) : PAIRED ? (RT == 4 ? 3 : RT == 2 ? 4 : 6) : (RT == 4 || KS == 2 ? 2 : 3);
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double part[THREADS];
     __shared__ float red[4 * ROWS];
@@ -133,7 +161,7 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
     const int n0 = grp * ROWS, all_steps = (N + 15) / 16, share = (all_steps + KS - 1) / KS;
     const int k0 = (wave >> 2) * share, steps = k0 + share < all_steps ? k0 + share : all_steps;      // this wavefront's: k0 .. steps - 1
 
-    // ---- tokens: lane l fetches channels 2 (l % 32), + 1 of the wavefront's 64 and the tokens of half l / 32 of a step
+    // ---- tokens: lane l fetches channels 2 (l % 32), + 1 (or l % 32, + 32) of the wavefront's 64 and the tokens of half l / 32 of a step
     const int d0 = (quad * 4 + (wave & 3)) * 64, h = lane >> 5, c31 = lane & 31;
     const bool live = d0 < D;
     const uint32_t row_bytes = (uint32_t)row_stride * (uint32_t)sizeof(T);
@@ -141,12 +169,15 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(x) + tok * row_stride + (live ? d0 : 0), 0,
         live ? (int)((uint32_t)(N - 1) * row_bytes + (uint32_t)((D - d0 < 64 ? D - d0 : 64) * (int)sizeof(T))) : 0, 0x00020000);
-    const uint32_t lane_off = d0 + 2 * c31 < D ? (uint32_t)(8 * h) * row_bytes + (uint32_t)(2 * c31 * (int)sizeof(T)) : 0x80000000u;
+    const int c0 = PAIRED ? 2 * c31 : c31, c1 = c31 + 32;
+    const uint32_t half_off = (uint32_t)(8 * h) * row_bytes;
+    const uint32_t lane_off = d0 + c0 < D ? half_off + (uint32_t)(c0 * (int)sizeof(T)) : 0x80000000u;
+    const uint32_t lane_off1 = d0 + c1 < D ? half_off + (uint32_t)(c1 * (int)sizeof(T)) : 0x80000000u;         // not PAIRED
     raw_t raw[PF];
     auto fetch = [&](raw_t& r, int k) {
-        const uint32_t off = lane_off + (uint32_t)(16 * k) * row_bytes;
+        const uint32_t at = (uint32_t)(16 * k) * row_bytes;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) r.fetch(j, rx, off + (uint32_t)j * row_bytes);
+        for (int j = 0; j < 8; ++j) r.fetch(j, rx, lane_off + at + (uint32_t)j * row_bytes, lane_off1 + at + (uint32_t)j * row_bytes);
     };
 #pragma unroll
     for (int u = 0; u < PF; ++u) fetch(raw[u], k0 + u);
@@ -345,11 +376,12 @@ static int circ_rt(const CircRuns& runs, int D)
     return best;
 }
 
-bool spu_circ_aligned(const void* x, int D, int64_t row_stride, luvc_dtype dt)
+CircRows spu_circ_rows(const void* x, int D, int64_t row_stride, luvc_dtype dt)
 {
     const int64_t es = dt == LUVC_F32 ? 4 : 2;
-    // one access per channel pair; a sample inside one descriptor, below the offset that marks a lane without channels
-    return D % 2 == 0 && row_stride % 2 == 0 && (uintptr_t)x % (uintptr_t)(2 * es) == 0 && (int64_t)(kCircMaxN + 256) * row_stride * es < ((int64_t)1 << 31);
+    // a sample inside one descriptor, below the offset that marks a lane without channels
+    if ((int64_t)(kCircMaxN + 256) * row_stride * es >= ((int64_t)1 << 31)) return CircRows::None;
+    return D % 2 == 0 && row_stride % 2 == 0 && (uintptr_t)x % (uintptr_t)(2 * es) == 0 ? CircRows::Paired : CircRows::Single;
 }
 
 // one word per output token (rounded up to a workgroup's share) and 256 channels
@@ -372,7 +404,7 @@ static int circ_shares(const CircRuns& runs, int D, luvc_dtype dt)
     return wg <= 256 && longest >= (dt == LUVC_F32 ? 256 : 512) ? 2 : 1;
 }
 
-template <typename T, int RT, int KS>
+template <typename T, int RT, int KS, bool PAIRED>
 static void circ_launch(const T* x, int64_t row_stride, int D, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st)
 {
     int64_t groups = 0;
@@ -383,14 +415,18 @@ static void circ_launch(const T* x, int64_t row_stride, int D, int use_hamming, 
         const int b = circ_lds(runs.run[i].N, RT);
         lds = b > lds ? b : lds;
     }
-    LUVC_LAUNCH("spu_circ", (spu_circ<T, RT, KS>), dim3((unsigned)(groups * circ_quads(D))), dim3(256 * KS), (size_t)lds, st, x, row_stride, D, circ_quads(D), use_hamming,
+    LUVC_LAUNCH("spu_circ", (spu_circ<T, RT, KS, PAIRED>), dim3((unsigned)(groups * circ_quads(D))), dim3(256 * KS), (size_t)lds, st, x, row_stride, D, circ_quads(D), use_hamming,
                 runs, (unsigned long long*)words, (uint32_t)(spu_next_tag() % 0xffffffffull) + 1u, scores);
 }
 
 luvc_status spu_score_circ(const void* x, int64_t row_stride, int D, luvc_dtype dt, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st)
 {
     const int RT = circ_rt(runs, D), KS = RT == 1 ? circ_shares(runs, D, dt) : 1;
-#define LUVC_CIRC(TT, R, K) circ_launch<TT, R, K>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st)
+    const bool paired = spu_circ_rows(x, D, row_stride, dt) == CircRows::Paired;
+#define LUVC_CIRC(TT, R, K) do { \
+        if (paired) circ_launch<TT, R, K, true>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st); \
+        else circ_launch<TT, R, K, false>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st); \
+    } while (0)
 #define LUVC_CIRC_T(TT) do { if (RT == 4) LUVC_CIRC(TT, 4, 1); else if (RT == 2) LUVC_CIRC(TT, 2, 1); else if (KS == 2) LUVC_CIRC(TT, 1, 2); else LUVC_CIRC(TT, 1, 1); } while (0)
     if (dt == LUVC_F32) LUVC_CIRC_T(float); else LUVC_CIRC_T(bf16_t);
 #undef LUVC_CIRC_T

@@ -175,12 +175,13 @@ tile_tag_t spu_next_tag()
 // ------------------------------------------------------------------ host side
 // Which kernel is quickest: measured times (us, one call) as functions of the sizes.  spu_circ: its products at 1.1e15 flop/s,
 // and a chain of steps that grows with N, which overlap in part (bf16 8x205x3584: 14, 1x729x3584: 20, 1x1000x1024: 16,
-// 4x861x1408: 34; fp32 1x300x2048: 13, 1x1000x1024: 29); the others beside their launchers.
+// 4x861x1408: 34; fp32 1x300x2048: 13, 1x1000x1024: 29; channel by channel 8x205x3585: 16, 1x729x3585: 27); the others beside
+// their launchers.
 static double circ_work_us(int64_t B, int N, int D, luvc_dtype dt) { return (dt == LUVC_F32 ? 12.0 : 6.0) * N * N * (double)D * (double)B / 1.1e9; }
-static double circ_us(int64_t B, int N, int D, luvc_dtype dt)
+static double circ_us(int64_t B, int N, int D, luvc_dtype dt, CircRows rows)
 {
     const double work = 1.15 * circ_work_us(B, N, D, dt), chain = (dt == LUVC_F32 ? 0.0218 : 0.0105) * N;
-    return (dt == LUVC_F32 ? 6.3 : 5.5) + std::sqrt(work * work + chain * chain);
+    return (dt == LUVC_F32 ? 6.3 : 5.5) + (rows == CircRows::Single ? 1.35 : 1.0) * std::sqrt(work * work + chain * chain);
 }
 static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, double* us)
 {
@@ -191,12 +192,11 @@ static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, double* 
     *us = c;
     return conv ? SpuPath::Conv : SpuPath::Dense;
 }
-// circ: the call's rows let spu_circ take them (spu_circ_aligned)
-static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, bool circ)
+static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, CircRows circ)
 {
     double us;
     const SpuPath other = long_path(B, N, D, sigma, dt, &us);
-    return circ && N <= kCircMaxN && circ_us(B, N, D, dt) <= us ? SpuPath::Circ : other;
+    return circ != CircRows::None && N <= kCircMaxN && circ_us(B, N, D, dt, circ) <= us ? SpuPath::Circ : other;
 }
 // in a launch that several runs share, a run adds its products and nothing else
 bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt)
@@ -219,14 +219,14 @@ static size_t tile_bytes(int B, int n_tiles, size_t ld, SpuLayout* L, size_t off
 // most: scratch the call has to do with; a layout that needs more is returned where nothing smaller serves the call.  Short
 // samples then go to the kernels of long ones; spu_conv takes fewer workgroups per sample, down to one per 64 channels,
 // which is what the direct path's energies take (1 x 8192 x 2048: 256 of them want 8.9 MB, 205 want 7.2).
-SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, bool circ, size_t most)
+SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, CircRows circ, size_t most)
 {
     SpuLayout L{};
     L.path = spu_path(B, N, D, sigma, dt, circ);
     if (L.path == SpuPath::Circ) {
         L.n_tiles = 1;
         L.bytes = align_up(spu_circ_bytes(B, N, D));
-        return L.bytes > most ? spu_layout(B, N, D, sigma, dt, false, most) : L;
+        return L.bytes > most ? spu_layout(B, N, D, sigma, dt, CircRows::None, most) : L;
     }
     L.n_tiles = L.path == SpuPath::Fft ? (D + 31) / 32 : (D + 63) / 64;
     const bool dense = L.path == SpuPath::Dense;                     // the one path whose tables and spectra do not stay in LDS
@@ -255,14 +255,18 @@ SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, bool circ, s
 // what a call needs whichever way its rows lie
 size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most)
 {
-    const size_t a = spu_layout(B, N, D, sigma, dt, true, most).bytes, b = spu_layout(B, N, D, sigma, dt, false, most).bytes;
-    return a > b ? a : b;
+    size_t need = 0;
+    for (CircRows rows : {CircRows::None, CircRows::Single, CircRows::Paired}) {
+        const size_t b = spu_layout(B, N, D, sigma, dt, rows, most).bytes;
+        need = b > need ? b : need;
+    }
+    return need;
 }
 
 luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma,
                             int use_hamming, float* scores, void* workspace, size_t most, hipStream_t st)
 {
-    const SpuLayout L = spu_layout(B, N, D, sigma, dt, spu_circ_aligned(x, D, row_stride, dt), most);
+    const SpuLayout L = spu_layout(B, N, D, sigma, dt, spu_circ_rows(x, D, row_stride, dt), most);
     char* ws = (char*)workspace;
     if (L.path == SpuPath::Circ) {
         CircRuns runs;

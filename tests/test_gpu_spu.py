@@ -346,6 +346,30 @@ def test_score_as_a_circulant_product(oracle, dtype, B, N, D, sigma):
     score_case(oracle, x, dtype, sigma, False, "circulant-rect", stride_pad=10)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,N,D,sigma,pad,start", [
+    (1, 1, 1, 0, 0, 0), (2, 16, 31, 8, 0, 0), (2, 15, 33, 3, 1, 0), (3, 17, 63, 2, 0, 1), (2, 64, 64, 7, 1, 1), (2, 40, 65, 6, 0, 0),
+    (1, 33, 255, 5, 2, 1), (16, 64, 257, 8, 0, 0), (1, 31, 1153, 10, 0, 1),       # around a wavefront's and a workgroup's channels
+    (1, 513, 97, 30, 0, 0), (1, 530, 64, 99, 3, 1), (1, 1000, 129, 50, 0, 0),     # steps shared by two wavefronts
+    (4, 900, 897, 99, 0, 0), (16, 100, 1025, 9, 0, 0),                            # two and four tiles of output tokens per workgroup
+])
+def test_score_of_rows_without_aligned_pairs(oracle, dtype, B, N, D, sigma, pad, start):
+    """Odd widths, strides and first elements: the circulant kernel fetches channel by channel; nothing beside the rows may count."""
+    rng = np.random.default_rng(N * 17 + D)
+    x = wl.cast_io((rng.standard_normal((B, N, D)) * np.exp(rng.standard_normal((B, N, 1)))).astype(np.float32), dtype)
+    print(f"[spu] rows {B}x{N}x{D} sigma={sigma} pad={pad} start={start} {dtype}", flush=True)
+    xd = to_dev(x, dtype)
+    buf = torch.full((start + B * N * (D + pad),), float("nan"), dtype=xd.dtype, device="cuda")
+    rows = buf[start:].view(B, N, D + pad)[:, :, :D]
+    rows.copy_(xd)
+    got = lv.luvc_spu_score(rows, sigma, True)
+    torch.cuda.synchronize()
+    ref = oracle.spu_score(wl.widen(x, dtype), sigma, True)
+    err = np.abs(got.cpu().numpy() - ref)
+    assert (err <= SCORE_RTOL * np.abs(ref) + 1e-6 * np.abs(ref).max()).all(), float((err / np.abs(ref)).max())
+    assert torch.equal(lv.luvc_spu_score(rows, sigma, True), got)
+
+
 @pytest.mark.parametrize("N,k", [(1024, 1024), (1025, 1), (1025, 1025), (2049, 700), (4095, 3), (4096, 2049),
                                  (4097, 4097), (5000, 1), (8191, 1700), (8192, 8192), (8193, 40)])
 def test_prune_around_the_sizes_of_its_workgroups(oracle, N, k):
