@@ -305,21 +305,26 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
     // ---- Eq. 8: over the wavefront's channels (16 rows per lane and tile, two halves of the wavefront), then the four wavefronts
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-        float e = 0.f;
+        // in four parts: fewer roundings on the way to a sum, and a shorter chain
+        float p[4];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { e = fmaf(acc[t][0][v], acc[t][0][v], e); e = fmaf(acc[t][1][v], acc[t][1][v], e); }
+        for (int v = 0; v < 4; ++v) p[v] = acc[t][v & 1][v >> 1] * acc[t][v & 1][v >> 1];
+#pragma unroll
+        for (int v = 4; v < 32; ++v) p[v & 3] = fmaf(acc[t][v & 1][v >> 1], acc[t][v & 1][v >> 1], p[v & 3]);
+        float e = (p[0] + p[1]) + (p[2] + p[3]);
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(e), __float_as_uint(e), false, false);
         e = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
         if (h == 0 && wave < 4) red[wave * ROWS + t * 32 + c31] = e;
     }
     __syncthreads();
-    float own = 0.f;
-    if (tid < ROWS) own = ((red[tid] + red[ROWS + tid]) + red[2 * ROWS + tid]) + red[3 * ROWS + tid];
+    double sum4 = 0.0;
+    if (tid < ROWS) sum4 = (((double)red[tid] + (double)red[ROWS + tid]) + (double)red[2 * ROWS + tid]) + (double)red[3 * ROWS + tid];
     float* out = scores + tok + n0;
     if (n_quads == 1) {
-        if (tid < ROWS && n0 + tid < N) out[tid] = sqrtf(own);
+        if (tid < ROWS && n0 + tid < N) out[tid] = (float)sqrt(sum4);
         return;
     }
+    const float own = (float)sum4;
     unsigned long long* w = words + (int64_t)(group0 + s * n_groups + grp) * n_quads * ROWS;
     if (tid < ROWS)
         __hip_atomic_store(w + quad * ROWS + tid, ((unsigned long long)tag << 32) | __float_as_uint(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

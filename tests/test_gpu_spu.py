@@ -347,6 +347,22 @@ def test_score_as_a_circulant_product(oracle, dtype, B, N, D, sigma):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,D", [(64, 256), (130, 256), (130, 200), (300, 256)])
+def test_circulant_scores_of_narrow_rows_round_little(oracle, dtype, N, D):
+    """Up to 256 channels one workgroup adds all squares; they are not added one after the other.  Error (rms): the score's own
+    rounding, at most 2^-24 / sqrt(3), and the 3 N / 16 additions behind a filtered value, as much each (squared, doubled for
+    partial sums above the last one), independent over D channels."""
+    rng = np.random.default_rng(N + D)
+    x = rng.standard_normal((16, N, D)) * np.exp(0.5 * rng.standard_normal((16, N, 1)))
+    x = wl.cast_io(x.astype(np.float32), dtype)
+    got = lv.luvc_spu_score(to_dev(x, dtype), N // 10, True).cpu().numpy().astype(np.float64)
+    err = got / oracle.spu_score(wl.widen(x, dtype), N // 10, True) - 1.0
+    rms = np.sqrt((err * err).mean())
+    print(f"[spu] {N}x{D} {dtype} error rms={rms:.2e} mean={err.mean():.2e}", flush=True)
+    assert rms <= 2.0 ** -24 * np.sqrt(1.0 / 3.0 + N / (8.0 * D))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("B,N,D,sigma,pad,start", [
     (1, 1, 1, 0, 0, 0), (2, 16, 31, 8, 0, 0), (2, 15, 33, 3, 1, 0), (3, 17, 63, 2, 0, 1), (2, 64, 64, 7, 1, 1), (2, 40, 65, 6, 0, 0),
     (1, 33, 255, 5, 2, 1), (16, 64, 257, 8, 0, 0), (1, 31, 1153, 10, 0, 1),       # around a wavefront's and a workgroup's channels
