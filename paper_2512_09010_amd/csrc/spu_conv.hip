@@ -201,6 +201,12 @@ __device__ __forceinline__ void wave_lds_fence()
 
 }  // namespace
 
+// The constants of the transforms as fp32 values are short: cos(pi / 8) by 2.9e-8, 1 / sqrt 2 by 1.7e-8, and a token passes four
+// to six transforms there and back.  All scores came out too small by this share (mean over the tokens against fp64,
+// white and smooth tokens of 700 to 16384: 6.7e-8 .. 8.2e-8 up to 4096 points, 7.6e-8 .. 9.8e-8 beyond, beside 3e-8 of noise);
+// the weights, which are worked out in fp64, give it back.
+__host__ __device__ constexpr double conv_length(int M) { return M <= 4096 ? 1.0 + 7.4e-8 : 1.0 + 8.9e-8; }
+
 // P[k], k = 0 .. M/2.  A workgroup owns kSpecBins bins; its threads split the frequencies f >= 1 of each bin.  With
 // a = pi f / N and b = pi k / M the terms of +f and -f add to
 //     -sin(2 pi N k / M) sin 2b / (sin(a - b) sin(a + b)) - 2 cos(2 pi N k / M),
@@ -248,7 +254,7 @@ spu_conv_spectrum(int N, int M, int sigma, int use_hamming, float* __restrict__ 
     if (l == 0 && k <= M / 2) {
         double tot = k == 0 ? 2.0 * (double)N - 1.0 : sk * cb / sb - ck;            // f = 0, weight 1
         for (int i = 0; i < kSpecLanes; ++i) tot += part[g][i];
-        spec[k] = (float)(tot / ((double)N * (double)M));
+        spec[k] = (float)(tot / ((double)N * (double)M) * conv_length(M));
     }
 }
 
@@ -331,7 +337,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
         if (f <= sigma) {
             double v = 1.0;
             if (use_hamming) v = 0.54 + 0.46 * cospi(2.0 * (double)f / (double)(N - 1));
-            w = (float)(v / (double)N);
+            w = (float)(v / (double)N * conv_length(M));
         }
         return w;
     };

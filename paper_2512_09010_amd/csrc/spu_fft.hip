@@ -167,6 +167,9 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
 {
     using pio = pair_io<T>;
     constexpr int N1 = 16 * Q;
+    // the constants of a 16-point transform as fp32 values are short (see spu_conv.hip): with Q = 16 scores came out
+    // 4.6e-8 .. 5.1e-8 too small on the mean, 256 to 1024 tokens, white and smooth; with Q = 15 0.3e-8
+    constexpr double kLength = Q == 16 ? 1.0 + 4.8e-8 : 1.0;
     extern __shared__ float2 smem[];
     float2* xbuf = smem;                         // [16][kRowPad]  exchange between the two sides
     float2* tw = smem + 16 * kRowPad;            // [N]    (cos, sin)(2 pi i / N)
@@ -220,7 +223,7 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
             const int f = tid - 128;
             double w = 1.0;
             if (use_hamming) w = 0.54 + 0.46 * cospi(2.0 * (double)f / (double)(N - 1));
-            gm[f] = (float)(w / (double)N);
+            gm[f] = (float)(w / (double)N * kLength);
         }
     }
     __syncthreads();

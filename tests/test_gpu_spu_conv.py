@@ -4,7 +4,9 @@ pass bands (2 sigma = N included), channel counts around a workgroup's share, un
 import numpy as np
 import pytest
 
+from paper_2512_09010_amd import binding as lv
 from paper_2512_09010_amd import workloads as wl
+from gpu_util import to_dev
 from test_gpu_spu import score_case
 
 import torch
@@ -63,3 +65,16 @@ def test_score_on_three_times_a_power_of_two_points(oracle, dtype, B, N, D, sigm
     x = wl.cast_io(rng.standard_normal((B, N, D)).astype(np.float32), dtype)
     score_case(oracle, x, dtype, sigma, True, "3 * 2^n", stride_pad=pad)
     score_case(oracle, x, dtype, sigma, False, "3 * 2^n-rect", stride_pad=pad)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,sigma", [(256, 25), (1024, 102), (1500, 150), (2000, 200), (2048, 300), (3000, 300), (4000, 400), (4096, 409), (6000, 150), (8000, 200)])
+def test_scores_are_not_short_on_the_mean(oracle, dtype, N, sigma):
+    """The fp32 constants of the transforms are all rounded down; what that takes off every score is given back by the weights.
+    Left: at most half a unit of the score's own rounding, 2^-25 (5e-8 .. 1e-7 was missing before)."""
+    rng = np.random.default_rng(N)
+    x = wl.cast_io(rng.standard_normal((1, N, 256)).astype(np.float32), dtype)
+    got = lv.luvc_spu_score(to_dev(x, dtype), sigma, True).cpu().numpy().astype(np.float64)
+    err = got / oracle.spu_score(wl.widen(x, dtype), sigma, True) - 1.0
+    print(f"[spu] N={N} sigma={sigma} {dtype} error mean={err.mean():.2e} rms={np.sqrt((err * err).mean()):.2e}", flush=True)
+    assert abs(err.mean()) <= 2.0 ** -25
