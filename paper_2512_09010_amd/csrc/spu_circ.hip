@@ -18,6 +18,8 @@
 // stores, then reads the words of all of them.  Whoever finds every tag adds the sums in channel order in fp64, writes the
 // scores and clears the tags; the last to write always does, and if another does too it writes the same values.  One
 // trip to memory each way, no atomics; nothing has to be set up, and a captured launch replayed with its tag starts over.
+// A tag has 32 bits and depends on the token's row (circ_tag), so memory that another call left behind passes for the
+// words of a workgroup only if it holds 32 RT different right values in a row: a constant fill never does.
 //
 // Bound: matrix cores for N near kCircMaxN (6 N^2 D flops per bf16 sample, 12 for fp32), latency for short samples.
 // 1x729x3584 bf16: 20.5 us (2048-point transform: 24), 8x205x3584: 13.9, 4x144x4096: 9.2, 4x861x1408: 33.6.  Rows of odd width,
@@ -123,6 +125,9 @@ template <bool PAIRED> struct circ_raw<float, PAIRED> {
         }
     }
 };
+
+// the tag of the words of a group's token `row`
+__device__ __forceinline__ uint32_t circ_tag(uint32_t tag, int row) { return tag + (uint32_t)row * 0x9E3779B1u; }
 
 // LDS: taps [3 terms][8 displacements] of circ_stride bytes, 32 mod 256; the taps once more, undisplaced; p itself
 __host__ __device__ inline int circ_taps(int N, int RT) { return (N + 15) / 16 * 16 + 32 * RT + 8; }
@@ -325,14 +330,16 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
         return;
     }
     const float own = (float)sum4;
+    const int row = tid % ROWS;
+    const uint32_t row_tag = circ_tag(tag, row);
     unsigned long long* w = words + (int64_t)(group0 + s * n_groups + grp) * n_quads * ROWS;
     if (tid < ROWS)
-        __hip_atomic_store(w + quad * ROWS + tid, ((unsigned long long)tag << 32) | __float_as_uint(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(w + quad * ROWS + tid, ((unsigned long long)row_tag << 32) | __float_as_uint(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     // ---- all of them there?  Thread: a token, every PARTS-th workgroup
     constexpr int PARTS = THREADS / ROWS;
-    const int row = tid % ROWS, pt0 = tid / ROWS;
+    const int pt0 = tid / ROWS;
     bool all = true;
     double e = 0.0;
     for (int i0 = pt0; i0 < n_quads; i0 += 8 * PARTS) {
@@ -344,7 +351,7 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            all = all && (uint32_t)(v[i] >> 32) == tag;
+            all = all && (uint32_t)(v[i] >> 32) == row_tag;
             e += i0 + i * PARTS < n_quads ? (double)__uint_as_float((uint32_t)v[i]) : 0.0;
         }
     }
