@@ -89,6 +89,11 @@ struct StepAt {
 struct OimStepItem { int H, W, axis, count; StepAt at; };
 struct StepIn { const void* x; const int32_t *sizes, *kept; };               // sizes NULL: ones; kept NULL: identity
 struct StepOut { void* x[2]; int32_t *sizes[2], *kept[2], *map[2]; };        // kept, map: NULL = not wanted
+// the outputs of a launch of one item, as number 0
+inline StepOut step_out_of(const StepOut& o, const StepAt& at)
+{
+    return StepOut{{o.x[at.dst], nullptr}, {o.sizes[at.dst], nullptr}, {o.kept[at.dst], nullptr}, {o.map[at.map_dst], nullptr}};
+}
 
 // One pass with m = ceil(len/2) (oim_fast.hip); `vec` = rows are 16-byte aligned.
 bool oim_halve_supported(int H, int W, int D, luvc_dtype dt, int axis, int m, bool vec);

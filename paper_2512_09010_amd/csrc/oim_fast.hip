@@ -25,11 +25,11 @@
 namespace luvc {
 
 struct HalveItem { int H, W, axis, tiles, slots; StepAt at; };      // a line is cut into `tiles` runs of `slots` output slots
-struct HalveTable { int n; HalveItem it[kOimMaxItems]; };
+template <int MOST> struct HalveTable { int n; HalveItem it[MOST]; };        // one item: a kernel of its own, as in oim_pair.hip (8 x 64 x 64 x 1280 bf16 36.7 -> 35.1 us)
 
-template <typename T, int NCH>
+template <typename T, int NCH, int MOST>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NCH <= 3 ? 4 : 2)))
-oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, int D, const StepOut out, const HalveTable tab)
+oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, int D, const StepOut out, const HalveTable<MOST> tab)
 {
     using tr = io_traits<T>;
     constexpr int V = tr::kVec;
@@ -42,8 +42,8 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const i
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);         // tiles of a line stay on one XCD
-    HalveItem it = tab.it[0];                                      // fetched beside the count: one item is the common case
-    if (tab.n > 1) {
+    HalveItem it = tab.it[0];
+    if (MOST > 1) {
         int ent = 0;
         for (int i = 1; i < tab.n; ++i)
             if (item >= tab.it[i].at.wg0) ent = i;
@@ -190,8 +190,9 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const i
     const int64_t n_out_per = (int64_t)(axis ? H : nd) * Wo;
     const int out_in_img = axis ? line * Wo + j : j * Wo + line;
     const int64_t slot = at.out_off + b * n_out_per + out_in_img;
-    T* x_out = (T*)out.x[at.dst];
-    int32_t *sizes_out = out.sizes[at.dst], *kept_out = out.kept[at.dst];
+    const int dst = MOST > 1 ? at.dst : 0;
+    T* x_out = (T*)out.x[dst];
+    int32_t *sizes_out = out.sizes[dst], *kept_out = out.kept[dst];
     if (lane == 0) {
         sizes_out[slot] = S;
         const int p_in = (int)(tb - img);
@@ -199,7 +200,7 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const i
         // a lands here or in the previous slot of the line; the last source of an odd line has no
         // slot of its own and always folds into the last destination
         const int prev_slot = axis ? out_in_img - 1 : out_in_img - Wo;
-        int32_t* pass_map = out.map[at.map_dst];
+        int32_t* pass_map = out.map[MOST > 1 ? at.map_dst : 0];
         if (pass_map) {
             pass_map += at.map_off + (int64_t)b * at.map_stride - img;
             pass_map[tb] = out_in_img;
@@ -237,11 +238,11 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const i
     }
 }
 
-template <typename T, int NCH>
+template <typename T, int NCH, int MOST>
 static void launch_halve(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
 {
     constexpr int cap = 4;                                 // wavefronts (= output slots) per workgroup
-    HalveTable tab;
+    HalveTable<MOST> tab;
     tab.n = n;
     int64_t wgs = 0;
     int waves = 1;
@@ -257,7 +258,7 @@ static void launch_halve(const OimStepItem* items, int n, const StepIn& in, cons
         tab.it[i].at.wg0 = (unsigned)wgs;
         wgs += (int64_t)items[i].count * (axis ? H : W) * tab.it[i].tiles;
     }
-    LUVC_LAUNCH("oim_halve", (oim_halve<T, NCH>), dim3((unsigned)wgs), dim3(64 * waves), 0, st, (const T*)in.x, in.sizes, in.kept, D, out, tab);
+    LUVC_LAUNCH("oim_halve", (oim_halve<T, NCH, MOST>), dim3((unsigned)wgs), dim3(64 * waves), 0, st, (const T*)in.x, in.sizes, in.kept, D, MOST > 1 ? out : step_out_of(out, items[0].at), tab);
 }
 
 template <typename T>
@@ -265,7 +266,7 @@ static bool dispatch_halve(const OimStepItem* items, int n, const StepIn& in, co
 {
     const int per_wave = 64 * io_traits<T>::kVec;
     const int nch = (D + per_wave - 1) / per_wave;
-#define LUVC_HALVE(N) launch_halve<T, N>(items, n, in, out, D, st); return true
+#define LUVC_HALVE(N) if (n == 1) launch_halve<T, N, 1>(items, n, in, out, D, st); else launch_halve<T, N, kOimMaxItems>(items, n, in, out, D, st); return true
     switch (nch) {
         case 1: LUVC_HALVE(1);
         case 2: LUVC_HALVE(2);

@@ -34,18 +34,22 @@
 
 namespace luvc {
 
+// The items of a launch.  One item, the common case, has a kernel of its own: an argument list with room for all of them is
+// 2 KB and costs a launch 0.3 .. 0.7 us (8 x 64 x 64 x 1280 bf16 34.7 -> 34.0, 2 x 112 x 112 x 1280 and its two smaller
+// grids 59.8 -> 58.3).
+template <int MOST>
 struct PairTable {
     int n;
-    struct { PairGeom g; StepAt at; } it[kOimMaxItems];
+    struct { PairGeom g; StepAt at; } it[MOST];
 };
 
 // Tokens of at most 8 words per lane (1 KB in bf16) are compiled for six wavefronts per SIMD (80 registers, a few spilled
 // in the fp64 repeat): on batches of small grids a workgroup is 6 wavefronts, and four workgroups per compute unit instead
 // of three put 80 x 24 x 24 grids (960 workgroups) on the chip in one round - measured 36.8 -> 33.9 us.  The same
 // hint on wider tokens (96 instead of 103 registers) measured slower on every workload and is not given.
-template <typename T, int NQ, int TW, int NW>
+template <typename T, int NQ, int TW, int NW, int MOST>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((4 * NQ + TW <= 8 && NW == 16) ? 6 : 1)))
-oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, const StepOut out, const PairTable tab)
+oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, const StepOut out, const PairTable<MOST> tab)
 {
     using TokT = Tok<NQ, TW>;
     constexpr int N = TokT::N;
@@ -60,9 +64,9 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
-    PairGeom g = tab.it[0].g;                                     // fetched beside the count: one item is the common case
+    PairGeom g = tab.it[0].g;
     StepAt at = tab.it[0].at;
-    if (tab.n > 1) {
+    if (MOST > 1) {
         int ent = 0;
         for (int i = 1; i < tab.n; ++i)
             if (item >= tab.it[i].at.wg0) ent = i;
@@ -234,8 +238,9 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     const int own_end = row_base + 2 * nseg;                      // rows below it belong to the next run ...
     const bool tail = (g.L2 & 1) && own_end == g.L2 - 1;          // ... except the last source of an odd line
     const int64_t img_out = at.out_off + (int64_t)b * g.n_out;
-    T* x_out = (T*)out.x[at.dst];
-    int32_t *sizes_out = out.sizes[at.dst], *kept_out = out.kept[at.dst], *pair_map = out.map[at.map_dst];
+    const int dst = MOST > 1 ? at.dst : 0;
+    T* x_out = (T*)out.x[dst];
+    int32_t *sizes_out = out.sizes[dst], *kept_out = out.kept[dst], *pair_map = out.map[MOST > 1 ? at.map_dst : 0];
     const int uo = r0 >> 1;                                       // output slot (second axis) of destination r0 + 1
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
@@ -285,12 +290,12 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
 // ------------------------------------------------------------------ host side
 namespace {
 
-template <typename T, int NQ, int TW>
+template <typename T, int NQ, int TW, int MOST>
 luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
 {
     constexpr int N = 4 * NQ + TW;
     constexpr int NW = N <= 10 ? 16 : 8;           // 16 wavefronts leave 128 registers per lane, 8 leave 256
-    PairTable tab;
+    PairTable<MOST> tab;
     tab.n = n;
     int64_t lines = 0, wgs = 0;
     int waves = 1;
@@ -318,8 +323,8 @@ luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const
         wgs += (int64_t)items[i].count * g.segs * g.nd1;
     }
     const size_t lds = (size_t)waves * N * 64 * 4;             // at most 16 * 10 * 256 = 40 KiB
-    LUVC_LAUNCH("oim_halve_pair", (oim_halve_pair<T, NQ, TW, NW>), dim3((unsigned)wgs), dim3(64 * waves), lds, st,
-                (const T*)in.x, in.sizes, in.kept, out, tab);
+    LUVC_LAUNCH("oim_halve_pair", (oim_halve_pair<T, NQ, TW, NW, MOST>), dim3((unsigned)wgs), dim3(64 * waves), lds, st,
+                (const T*)in.x, in.sizes, in.kept, MOST > 1 ? out : step_out_of(out, items[0].at), tab);
     return check_launch("oim halving pair");
 }
 
@@ -333,7 +338,7 @@ luvc_status dispatch_pair(const OimStepItem* items, int n, const StepIn& in, con
     if (rem > 512) ++nq;
     else if (rem > 256) tw = 2;
     else if (rem > 0) tw = 1;
-#define LUVC_PAIR(Q, W_) if (nq == Q && tw == W_) return launch_pair<T, Q, W_>(items, n, in, out, D, st)
+#define LUVC_PAIR(Q, W_) if (nq == Q && tw == W_) return n == 1 ? launch_pair<T, Q, W_, 1>(items, n, in, out, D, st) : launch_pair<T, Q, W_, kOimMaxItems>(items, n, in, out, D, st)
     LUVC_PAIR(0, 1); LUVC_PAIR(0, 2);
     LUVC_PAIR(1, 0); LUVC_PAIR(1, 1); LUVC_PAIR(1, 2);
     LUVC_PAIR(2, 0); LUVC_PAIR(2, 1); LUVC_PAIR(2, 2);
