@@ -22,11 +22,14 @@
 // N floats per tile is written.
 // Bound: fp32 vector arithmetic, about 900 instructions per wavefront and subsequence.  With the twiddles between the sides
 // as multiplications of their own, and the accumulation's looked up per subsequence, it was 1160: 8x1024x3584 bf16 49 us
-// (42 now), 16x720x4096 72 (60), 4x2048x3584 47 (42), 8x1440x3584 fp32 76 (67).
+// (42 now), 16x720x4096 72 (60), 4x2048x3584 47 (45), 8x1440x3584 fp32 76 (70), on tokens whose norms vary by region.
 //
-// (An inverse on every second or fourth subsequence, with the energies between interpolated from the band limit, needs
-// tokens of even energy to stay within fp32 error and otherwise has to run in full after all: on tokens whose norms
-// vary by region it did so nearly always, at 52 us for 8 x 1024 x 3584 bf16 against 46 for this kernel.)
+// What it gave up: an inverse on every second or fourth subsequence, with the energies between interpolated from the band
+// limit.  On tokens of even energy, merged tokens through a random projection, it took 42.8 us for 8x1024x3584 bf16
+// (this kernel: 39.8), 67.7 for 16x720x4096 (57.2), but 39.1 for 4x2048x3584 (44.4): eight subsequences, of which six were
+// interpolated.  On tokens whose norms vary by region it ran in full after all, nearly always: 52 us for 8x1024x3584 against
+// 46 for this kernel of then.  Interpolated scores were only known to 3e-6 of their value (the taps' stop band); these
+// are fp32 transforms throughout, 3e-8 off (rms).
 #include <type_traits>
 
 #include "common.hpp"
