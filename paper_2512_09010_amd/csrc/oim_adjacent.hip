@@ -11,7 +11,9 @@
 // Bound: latency.  A pass reads its tokens once, but a line is a chain of memory trips - ids, tokens, merged rows - with
 // the decisions between them; as many wavefronts as a line has groups of four tokens share it, so that each trip is made once.
 // 12 x 32 x 32 x 1024 bf16, three operations of (W,2),(H,2): 157 us as three launches per pass (norms and products,
-// decisions, a merge that rewrote the whole grid), 75 us as one.
+// decisions, a merge that rewrote the whole grid), 75 us as one, 68 with two pieces of a row per lane where a row has no more.
+// Narrow rows were slower than the three launches while every row took three pieces: 32 x 64 x 64 x 384 bf16, (W,2): 92 us by
+// pass, 130, 78 now, of which the copy of the output rows went from 63 to 31.
 #include "common.hpp"
 #include "oim.hpp"
 #include "oim_lazy.hpp"
@@ -21,7 +23,9 @@ namespace luvc {
 
 constexpr int kAdjTok = 4;                       // consecutive tokens of a wavefront
 
-template <typename T>
+// P, PM: 16-byte pieces of a row per lane at a time, for the decisions and for the merged rows.  A piece past the row's end
+// costs its fp64 products all the same, and the registers of fewer pieces leave room for a second line on a compute unit.
+template <typename T, int P, int PM>
 __global__ void __launch_bounds__(1024)
 oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric [.., Dk] the decisions are taken on, or null: x */,
                   T* ovk /* its overlay */, int Dk, const int32_t* __restrict__ idx_in /* null: identity */,
@@ -66,14 +70,14 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
         double s[2 * kAdjTok];
 #pragma unroll
         for (int i = 0; i < 2 * kAdjTok; ++i) s[i] = 0.0;
-        for (int d0 = 0; d0 < dD; d0 += 64 * V * kLzPieces) {
-            lz_u32x4 t[kAdjTok + 1][kLzPieces];
+        for (int d0 = 0; d0 < dD; d0 += 64 * V * P) {
+            lz_u32x4 t[kAdjTok + 1][P];
 #pragma unroll
             for (int i = 0; i <= kAdjTok; ++i)
 #pragma unroll
-                for (int u = 0; u < kLzPieces; ++u) t[i][u] = lz_load(r[i], (d0 + (u * 64 + lane) * V) * (int)sizeof(T));
+                for (int u = 0; u < P; ++u) t[i][u] = lz_load(r[i], (d0 + (u * 64 + lane) * V) * (int)sizeof(T));
 #pragma unroll
-            for (int u = 0; u < kLzPieces; ++u)
+            for (int u = 0; u < P; ++u)
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
                     double a = io::at(t[0][u], e);
@@ -160,20 +164,33 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
         const unsigned long long hits = ((from_prev >> k) & 1ull) << k | (((from_next >> k) & 1ull) << k) << 1;
         T* mov = on_metric ? ovk : ov;
         const int mD = on_metric ? Dk : g.D;
-        lazy_merge<T>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, hits, mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane);
+        lazy_merge<T, PM>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, hits, mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane);
     }
 }
 
 // ------------------------------------------------------------------ host side
+static int adjacent_waves(int len)
+{
+    const int waves = (len + kAdjTok - 1) / kAdjTok;
+    return waves > 16 ? 16 : waves;
+}
+
 template <typename T>
 static luvc_status run_adjacent(const T* x, T* ov, const T* xk, T* ovk, int Dk, const int32_t* idx_in, const int32_t* sizes_in, const int32_t* kept_in,
                                 int B, const LazyGeom& g, int32_t* idx_out, int32_t* sizes_out, int32_t* kept_out, int32_t* pass_map, hipStream_t st)
 {
     const int len = g.axis ? g.w : g.h, nlines = g.axis ? g.h : g.w;
-    int waves = (len + kAdjTok - 1) / kAdjTok;
-    waves = waves > 16 ? 16 : waves;
-    LUVC_LAUNCH("oim_adjacent_line", (oim_adjacent_line<T>), dim3((unsigned)(B * nlines)), dim3(64 * waves), 0, st, x, ov, xk, ovk, Dk,
-                idx_in, sizes_in, kept_in, g, idx_out, sizes_out, kept_out, pass_map);
+    const int waves = adjacent_waves(len);
+    auto pieces = [](int D) { return (D + 64 * lz_io<T>::V - 1) / (64 * lz_io<T>::V); };
+    const int p = pieces(xk ? Dk : g.D), pm = pieces(xk && Dk > g.D ? Dk : g.D);
+#define LUVC_ADJ(P, PM) LUVC_LAUNCH("oim_adjacent_line", (oim_adjacent_line<T, P, PM>), dim3((unsigned)(B * nlines)), dim3(64 * waves), 0, st, x, ov, xk, ovk, Dk, \
+                                idx_in, sizes_in, kept_in, g, idx_out, sizes_out, kept_out, pass_map)
+    if (p == 1 && pm == 1) LUVC_ADJ(1, 1);
+    else if (p == 1) LUVC_ADJ(1, kLzPieces);
+    else if (p == 2 && pm == 2) LUVC_ADJ(2, 2);
+    else if (p == 2) LUVC_ADJ(2, kLzPieces);
+    else LUVC_ADJ(kLzPieces, kLzPieces);
+#undef LUVC_ADJ
     return check_launch("oim pass (adjacent matching, one launch)");
 }
 

@@ -60,8 +60,9 @@ __device__ __forceinline__ int lazy_slot(const LazyLine& l, int p)
 }
 
 // Size-weighted mean of destination k and the sources `hits` (bit j: source 2 j) of the line, to row o: fp64, destination
-// first, then the sources in ascending position, rounded once.  The destination and two sources are fetched together.
-template <typename T>
+// first, then the sources in ascending position, rounded once.  The destination and two sources are fetched together, P pieces
+// of each at a time.
+template <typename T, int P = kLzPieces>
 __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGeom& g, int D, int64_t b, const int* rid, const int* sz, int k,
                                            unsigned long long hits, T* o, int lane)
 {
@@ -69,8 +70,8 @@ __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGe
     constexpr int V = io::V;
     const __amdgpu_buffer_rsrc_t rp = lz_row(row_of<T>(x, ov, b, rid[2 * k + 1], g, D), D, true);
     const double sp = (double)sz[2 * k + 1];
-    for (int d0 = 0; d0 < D; d0 += 64 * V * kLzPieces) {
-        double acc[kLzPieces][V], S = sp;
+    for (int d0 = 0; d0 < D; d0 += 64 * V * P) {
+        double acc[P][V], S = sp;
         const int pieces = (D - d0 + 64 * V - 1) / (64 * V);           // of this block that hold anything, the same in every lane
         unsigned long long h = hits;
         bool first = true;
@@ -81,9 +82,9 @@ __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGe
             h &= h - 1;
             const __amdgpu_buffer_rsrc_t r1 = lz_row(row_of<T>(x, ov, b, rid[j1 < 0 ? 0 : 2 * j1], g, D), D, j1 >= 0),
                                          r2 = lz_row(row_of<T>(x, ov, b, rid[j2 < 0 ? 0 : 2 * j2], g, D), D, j2 >= 0);
-            lz_u32x4 vp[kLzPieces], v1[kLzPieces], v2[kLzPieces];
+            lz_u32x4 vp[P], v1[P], v2[P];
 #pragma unroll
-            for (int u = 0; u < kLzPieces; ++u) {
+            for (int u = 0; u < P; ++u) {
                 if (u >= pieces) continue;
                 const int off = (d0 + (u * 64 + lane) * V) * (int)sizeof(T);
                 if (first) vp[u] = lz_load(rp, off);
@@ -92,7 +93,7 @@ __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGe
             }
             const double s1 = j1 >= 0 ? (double)sz[2 * j1] : 0.0, s2 = j2 >= 0 ? (double)sz[2 * j2] : 0.0;
 #pragma unroll
-            for (int u = 0; u < kLzPieces; ++u) {
+            for (int u = 0; u < P; ++u) {
                 if (u >= pieces) continue;
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
@@ -106,7 +107,7 @@ __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGe
         } while (h);
         const double inv = 1.0 / S;
 #pragma unroll
-        for (int u = 0; u < kLzPieces; ++u) {
+        for (int u = 0; u < P; ++u) {
             const int d = d0 + (u * 64 + lane) * V;
             if (d >= D) continue;
             T q[V];

@@ -38,6 +38,8 @@
 // Bound: the screening, by the rate at which the tokens arrive (8 x 64 x 64 x 1280 bf16: 84 MB a pass), then latency
 // (three operations of merge number 2 on that grid, 25 passes and the last copy: 212 us, 175 with eight wavefronts per line
 // where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening).
+#include <type_traits>
+
 #include "common.hpp"
 #include "oim.hpp"
 #include "oim_lazy.hpp"
@@ -465,6 +467,7 @@ struct FinishPart {
     const unsigned char *x, *ov;
     unsigned char* out;
     int row_bytes, lanes;        // lanes per row: 16 or 32 for rows of at most 256 or 512 bytes, else the wavefront
+    int rows;                    // rows per wavefront where a row takes all of its lanes
     unsigned blocks;
 };
 struct FinishArgs {
@@ -479,8 +482,8 @@ struct FinishArgs {
 };
 
 // Three kinds of workgroup in one launch (none waits for another): rows of the tokens, rows of the metric, the composition
-// of the pass maps, 256 entries each.  Rows are copied eight 16-byte pieces per lane at a time; short rows (the keys of
-// one attention head) several to a wavefront, since a wavefront is three memory round trips long whatever it moves.
+// of the pass maps, 256 entries each.  Rows are copied eight 16-byte pieces per lane at a time; short rows several to a
+// wavefront, since a wavefront is three memory round trips long whatever it moves.
 // Bound: HBM (8 x 64 x 64 x 1280 bf16: 20.4 us for 138 MB).
 __global__ void __launch_bounds__(256)
 oim_lazy_finish_k(FinishArgs a)
@@ -491,29 +494,48 @@ oim_lazy_finish_k(FinishArgs a)
     for (int q = 0; q < 2; ++q) {
         const FinishPart& f = a.part[q];
         if (blk < f.blocks) {
-            const int per_wave = 64 / f.lanes;
-            const int64_t row = ((int64_t)blk * 4 + (threadIdx.x >> 6)) * per_wave + lane / f.lanes;
-            if (row >= a.n_rows) return;
-            const int64_t b = row / a.n_out_per;
-            int id = a.idx ? a.idx[row] : (int)(row - b * a.n_out_per);
-            id = id < 0 ? 0 : (id >= a.n0 + a.cap ? a.n0 + a.cap - 1 : id);            // ids come from the passes; stay in bounds regardless
-            const unsigned char* in = id < a.n0 ? f.x + (b * a.n0 + id) * (int64_t)f.row_bytes : f.ov + (b * a.cap + (id - a.n0)) * (int64_t)f.row_bytes;
-            unsigned char* o = f.out + row * (int64_t)f.row_bytes;
+            auto row_in = [&](int64_t row) {
+                const int64_t b = row / a.n_out_per;
+                int id = a.idx ? a.idx[row] : (int)(row - b * a.n_out_per);
+                id = id < 0 ? 0 : (id >= a.n0 + a.cap ? a.n0 + a.cap - 1 : id);        // ids come from the passes; stay in bounds regardless
+                return id < a.n0 ? f.x + (b * a.n0 + id) * (int64_t)f.row_bytes : f.ov + (b * a.cap + (id - a.n0)) * (int64_t)f.row_bytes;
+            };
+            const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
             if (f.lanes < 64) {
+                const int per_wave = 64 / f.lanes;
+                const int64_t row = ((int64_t)blk * 4 + wave) * per_wave + lane / f.lanes;
+                if (row >= a.n_rows) return;
                 const int off = lane % f.lanes * 16;
+                const unsigned char* in = row_in(row);
+                unsigned char* o = f.out + row * (int64_t)f.row_bytes;
                 if (off < f.row_bytes) *reinterpret_cast<lazy_u32x4*>(o + off) = *reinterpret_cast<const lazy_u32x4*>(in + off);
                 return;
             }
-            // the descriptors bound every piece
-            const __amdgpu_buffer_rsrc_t ri = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(in), 0, f.row_bytes, 0x00020000);
-            const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(o, 0, f.row_bytes, 0x00020000);
-            for (int base = 0; base < f.row_bytes; base += 8 * 1024) {
-                lazy_u32x4 v[8];
+            // R rows of up to 8 / R pieces, all in flight together; the descriptors bound every piece, a row past the last has none
+            auto copy = [&](auto rows) {
+                constexpr int R = decltype(rows)::value, P = 8 / R;
+                const int64_t row0 = ((int64_t)blk * 4 + wave) * R;
+                if (row0 >= a.n_rows) return;
+                __amdgpu_buffer_rsrc_t ri[R], ro[R];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(ri, base + k * 1024 + lane * 16, 0, 0);
+                for (int r = 0; r < R; ++r) {
+                    const bool there = row0 + r < a.n_rows;
+                    const int64_t row = there ? row0 + r : row0;
+                    ri[r] = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(row_in(row)), 0, there ? f.row_bytes : 0, 0x00020000);
+                    ro[r] = __builtin_amdgcn_make_buffer_rsrc(f.out + row * (int64_t)f.row_bytes, 0, there ? f.row_bytes : 0, 0x00020000);
+                }
+                for (int base = 0; base < f.row_bytes; base += P * 1024) {
+                    lazy_u32x4 v[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) __builtin_amdgcn_raw_buffer_store_b128(v[k], ro, base + k * 1024 + lane * 16, 0, 2);
-            }
+                    for (int k = 0; k < 8; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(ri[k / P], base + k % P * 1024 + lane * 16, 0, 0);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) __builtin_amdgcn_raw_buffer_store_b128(v[k], ro[k / P], base + k % P * 1024 + lane * 16, 0, 2);
+                }
+            };
+            if (f.rows == 8) copy(std::integral_constant<int, 8>{});
+            else if (f.rows == 4) copy(std::integral_constant<int, 4>{});
+            else if (f.rows == 2) copy(std::integral_constant<int, 2>{});
+            else copy(std::integral_constant<int, 1>{});
             return;
         }
         blk -= f.blocks;
@@ -584,7 +606,10 @@ luvc_status oim_lazy_finish(const LazyOutput* outs, int n_outs, const int32_t* i
         f.x = (const unsigned char*)outs[q].x; f.ov = (const unsigned char*)outs[q].ov; f.out = (unsigned char*)outs[q].out;
         f.row_bytes = outs[q].row_bytes;
         f.lanes = f.row_bytes <= 256 ? 16 : f.row_bytes <= 512 ? 32 : 64;
-        const int64_t per_block = 4 * (64 / f.lanes);
+        // rows of a wavefront: as many as have eight pieces together, as long as there are 8192 wavefronts
+        f.rows = 1;
+        while (f.lanes == 64 && f.rows < 8 && 2 * f.rows * ((f.row_bytes + 1023) / 1024) <= 8 && a.n_rows >= (int64_t)8192 * 2 * f.rows) f.rows *= 2;
+        const int64_t per_block = 4 * (64 / f.lanes) * f.rows;
         f.blocks = (unsigned)((a.n_rows + per_block - 1) / per_block);
         grid += f.blocks;
     }

@@ -328,3 +328,17 @@ def test_few_tokens_out_of_a_line(oracle, dtype, B, H, W, D, passes):
     torch.cuda.synchronize()
     for k in ("x", "sizes", "merged_map", "kept_map"):
         assert torch.equal(out[k], other[k]), k
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,W,D,passes", [
+    (2, 5, 9, 256, [(W_AX, 2), (H_AX, 1)]), (2, 5, 9, 264, [(W_AX, 2), (H_AX, 1)]), (2, 5, 9, 512, [(W_AX, 2), (H_AX, 1)]),
+    (2, 5, 9, 520, [(W_AX, 2), (H_AX, 1)]), (2, 5, 9, 1024, [(W_AX, 2), (H_AX, 1)]), (2, 5, 9, 1032, [(W_AX, 2), (H_AX, 1)]),
+    (1, 5, 9, 1544, [(W_AX, 2), (H_AX, 1)]),                                     # around one, two and three pieces of a row per lane
+    (5, 107, 126, 264, [(W_AX, 2)]), (3, 95, 127, 520, [(W_AX, 2)]), (3, 95, 63, 1032, [(H_AX, 1)]),   # several output rows to a wavefront, the last one short
+])
+def test_few_tokens_row_widths(oracle, dtype, B, H, W, D, passes):
+    """The widths at which the one-launch passes and the copy of the output rows change how many pieces and rows a wavefront holds."""
+    rng = np.random.default_rng(H * 1000 + W * 10 + D)
+    x = wl.cast_io((wl.smooth_field(rng, B, H, W, D, 1.5) + 0.5 * rng.standard_normal((B, H, W, D))).astype(np.float32), dtype)
+    run_case(oracle, x, dtype, passes, sizes=rng.integers(1, 6, (B, H, W)), tag="widths")
