@@ -80,17 +80,17 @@ static bool walk_schedule(int B, int H, int W, int D, const luvc_oim_pass* passe
 }
 
 // Schedules of adjacent matching that run on grids of row ids: some pass takes fewer than all sources out of its lines,
-// so that most tokens go through the call unchanged (or every pass takes none: a copy).  Schedules of halvings keep the
-// fused kernels, which move every token anyway.
-static bool takes_few(const OimPlan& pl, const luvc_oim_pass* passes)
+// so that tokens go through the call unchanged, and it is quicker that way (or every pass takes none: a copy).  Schedules of
+// halvings keep the fused kernels, which move every token anyway.  Passes that take none do not count.
+static bool takes_few(const OimPlan& pl, const luvc_oim_pass* passes, bool keyed, int B, int D, luvc_dtype dt)
 {
-    bool none = true;
+    bool none = true, few = false;
     for (int i = 0; i < pl.n; ++i) {
         const int len = passes[i].axis ? pl.w[i] : pl.h[i];
-        if (passes[i].m != 0 && passes[i].m != (len + 1) / 2) return true;
+        few = few || (passes[i].m != 0 && passes[i].m != (len + 1) / 2);
         none = none && passes[i].m == 0;
     }
-    return none;
+    return none || (few && (keyed || oim_adjacent_pays(pl.h, pl.w, passes, pl.n, B, D, dt)));
 }
 
 struct OimLayout {
@@ -98,7 +98,7 @@ struct OimLayout {
     int lazy_cap;      // overlay rows per image (grids of row ids)
 };
 
-static OimLayout oim_layout(int B, int D, luvc_dtype dt, const OimPlan& pl, const luvc_oim_pass* passes = nullptr, int radius = 1)
+static OimLayout oim_layout(int B, int D, luvc_dtype dt, const OimPlan& pl, const luvc_oim_pass* passes, int radius, bool keyed)
 {
     OimLayout L{};
     size_t off = 0;
@@ -127,7 +127,7 @@ static OimLayout oim_layout(int B, int D, luvc_dtype dt, const OimPlan& pl, cons
     L.absorb = off; off += align_up(max_out * sizeof(int32_t));
     // wide matching: the largest source x destination matrix set and merge list of any pass
     size_t gram = 0, srcdest = 0;
-    if (radius != 1 && passes)
+    if (radius != 1)
         for (int i = 0; i < pl.n; ++i) {
             const size_t gb = oim_wide_gram_bytes(B, pl.h[i], pl.w[i], passes[i].axis), sb = oim_wide_srcdest_bytes(B, pl.h[i], pl.w[i], passes[i].axis);
             if (gb > gram) gram = gb;
@@ -138,7 +138,7 @@ static OimLayout oim_layout(int B, int D, luvc_dtype dt, const OimPlan& pl, cons
     // one launch per pass: two grids of row ids and the rows of the merged destinations
     // (whether a call can run that way depends on the alignment of its buffers, so the space is always there)
     int64_t cap = 0;
-    const bool ids = passes && (radius != 1 || takes_few(pl, passes));
+    const bool ids = radius != 1 || takes_few(pl, passes, keyed, B, D, dt);
     if (ids)
         for (int i = 0; i < pl.n; ++i) cap += oim_wide_lazy_rows(pl.h[i], pl.w[i], passes[i].axis, passes[i].m);
     L.lazy_cap = (int)cap;
@@ -243,7 +243,7 @@ size_t luvc_oim_workspace_bytes(int B, int H, int W, int D, luvc_dtype dtype, co
 {
     OimPlan pl;
     if (!dtype_ok(dtype) || !walk_schedule(B, H, W, D, passes, n_passes, &pl)) return 0;
-    return oim_layout(B, D, dtype, pl, passes, 1).bytes;
+    return oim_layout(B, D, dtype, pl, passes, 1, false).bytes;
 }
 
 // The passes of a schedule that take something out of their lines (a pass with m = 0 changes nothing: no token, size or
@@ -265,9 +265,9 @@ static OimPlan drop_empty_passes(const OimPlan& pl, const luvc_oim_pass* passes,
 }
 
 // Can a schedule run on grids of row ids, given aligned rows?
-static bool lazy_supported(int64_t n0, const OimPlan& pl, const luvc_oim_pass* passes, int radius, int64_t cap)
+static bool lazy_supported(int64_t n0, const OimPlan& pl, const luvc_oim_pass* passes, int radius, bool keyed, int B, int D, luvc_dtype dt, int64_t cap)
 {
-    if ((radius == 1 && !takes_few(pl, passes)) || n0 + cap >= ((int64_t)1 << 31)) return false;
+    if ((radius == 1 && !takes_few(pl, passes, keyed, B, D, dt)) || n0 + cap >= ((int64_t)1 << 31)) return false;
     for (int i = 0; i < pl.n; ++i)
         if ((passes[i].axis ? pl.w[i] : pl.h[i]) > kLazyMaxLen) return false;
     return true;
@@ -334,7 +334,7 @@ static luvc_status oim_merge_impl(const void* x, const int32_t* sizes_in, int B,
         set_error("wide matching supports grids of less than 2 GiB per image");
         return LUVC_ERR_UNSUPPORTED;
     }
-    const OimLayout L = oim_layout(B, D, dtype, full, all_passes, radius);
+    const OimLayout L = oim_layout(B, D, dtype, full, all_passes, radius, false);
     if (!workspace_ok(workspace, workspace_bytes, L.bytes)) return LUVC_ERR_WORKSPACE;
     luvc_oim_pass passes[kMaxPasses];
     const OimPlan pl = drop_empty_passes(full, all_passes, passes);
@@ -344,7 +344,7 @@ static luvc_status oim_merge_impl(const void* x, const int32_t* sizes_in, int B,
     // 16-byte accesses need aligned rows in every buffer the kernels touch
     const bool vec = ((size_t)D * es) % 16 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)x_out % 16 == 0;
 
-    if (vec && lazy_supported((int64_t)H * W, pl, passes, radius, L.lazy_cap))
+    if (vec && lazy_supported((int64_t)H * W, pl, passes, radius, false, B, D, dtype, L.lazy_cap))
         return lazy_run(x, nullptr, nullptr, 0, sizes_in, B, D, dtype, pl, passes, radius, L, ws, x_out, nullptr, sizes_out, merged_map, kept_map, st);
 
     OimScratch sc;
@@ -413,7 +413,7 @@ size_t luvc_oim_wide_workspace_bytes(int B, int H, int W, int D, luvc_dtype dtyp
 {
     OimPlan pl;
     if (!dtype_ok(dtype) || radius < 0 || !walk_schedule(B, H, W, D, passes, n_passes, &pl)) return 0;
-    return oim_layout(B, D, dtype, pl, passes, radius).bytes;
+    return oim_layout(B, D, dtype, pl, passes, radius, false).bytes;
 }
 
 luvc_status luvc_oim_merge_wide(const void* x, const int32_t* sizes_in, int B, int H, int W, int D, luvc_dtype dtype,
@@ -436,7 +436,7 @@ static KeyedLayout keyed_layout(int B, int D, int Dm, luvc_dtype dt, const OimPl
 {
     KeyedLayout K;
     // the wide-matching scratch is sized by oim_layout when radius != 1; a radius of 1 needs none
-    K.base = oim_layout(B, D, dt, pl, passes, radius);
+    K.base = oim_layout(B, D, dt, pl, passes, radius, true);
     size_t off = K.base.bytes;
     size_t tok[2] = {0, 0};
     // launch s (one pass, or two passes fused) writes buffer s & 1; which passes fuse depends on the alignment of the
@@ -510,7 +510,7 @@ luvc_status luvc_oim_merge_keyed(const void* x, const void* metric, const int32_
     double* G = (double*)(ws + L.gram);
     int32_t* src_dest = (int32_t*)(ws + L.srcdest);
 
-    if (vec_x && vec_m && lazy_supported((int64_t)H * W, pl, passes, radius, L.lazy_cap))
+    if (vec_x && vec_m && lazy_supported((int64_t)H * W, pl, passes, radius, true, B, D, dtype, L.lazy_cap))
         return lazy_run(x, metric, ws + K.mov, Dm, sizes_in, B, D, dtype, pl, passes, radius, L, ws, x_out, metric_out, sizes_out, merged_map, kept_map, st);
 
     const void *cur_x = x, *cur_m = metric;

@@ -39,6 +39,8 @@ luvc_status oim_wide_pass(const void* x, const int32_t* sizes_in, int B, int H, 
 // destinations).  Lines of at most kLazyMaxLen tokens, 16-byte aligned rows.  oim_adjacent_pass (oim_adjacent.hip): the same
 // with the adjacent destinations as candidates.
 constexpr int kLazyMaxLen = 128;
+// h, w: n + 1 grids along the schedule
+bool oim_adjacent_pays(const int* h, const int* w, const luvc_oim_pass* passes, int n, int B, int D, luvc_dtype dt);
 int oim_wide_lazy_rows(int h, int w, int axis, int m);      // overlay rows per image that a pass may write
 // metric / ov_metric / Dm: the tensor the decisions are taken on and its overlay (merged like x), or NULL / NULL / 0: x itself
 luvc_status oim_wide_lazy_pass(const void* x, void* ov, const void* metric, void* ov_metric, int Dm, const int32_t* idx_in, const int32_t* sizes_in, const int32_t* kept_in,

@@ -175,6 +175,39 @@ static int adjacent_waves(int len)
     return waves > 16 ? 16 : waves;
 }
 
+// Is a schedule of adjacent matching quicker on grids of row ids than pass by pass (halving kernels, or norms, decisions and a
+// merge that moves the whole grid)?  us of either way, fitted to 190 schedules on twelve grids of 2 to 430 MB, one to six
+// passes of m = 2 up to every source (off by 15 %, rms).  What counts is bytes (MB of a grid) and, where the lines leave
+// compute units idle, the rounds in which the wavefronts of a line sum its tokens and merge its destinations.  Both ways
+// measured: 8x64x64x1280 bf16 (W,2),(H,2) three times 339 us pass by pass, 170 on ids; (W,31) 61, 59; 32x64x64x384 (W,2) 92, 78;
+// (W,32),(H,16) 112, 119; 2x30x120x1152 (W,2) 24, 22; (W,59) 26, 38; (W,60),(H,7) 40, 48; 1x12x100x640 (W,50),(H,3) 24, 31.
+// Decided on keys, pass by pass is two more launches and ids always win: (W,31) 65 and 63, (W,32),(H,16) 109 and 80.
+bool oim_adjacent_pays(const int* h, const int* w, const luvc_oim_pass* passes, int n, int B, int D, luvc_dtype dt)
+{
+    const double mb = (double)B * D * (dt == LUVC_F32 ? 4 : 2) * 1e-6;
+    auto halves = [&](int i) { return passes[i].m == ((passes[i].axis ? w[i] : h[i]) + 1) / 2; };
+    auto size = [&](int i) { return mb * h[i] * w[i]; };                        // MB before pass i
+    double by_pass = 0.0, by_ids = 2.5 + 0.30 * size(n);
+    int steps = 0, last_axis = -1;                                              // axis of a halving that may still find a partner
+    for (int i = 0; i < n; ++i) {
+        const int axis = passes[i].axis, m = passes[i].m, len = axis ? w[i] : h[i], n_src = (len + 1) / 2, n_dst = len / 2;
+        if (m == 0) continue;
+        const int64_t lines = (int64_t)B * (axis ? h[i] : w[i]);
+        const int waves = adjacent_waves(len), sums = (len + kAdjTok * waves - 1) / (kAdjTok * waves);
+        const int rounds = ((m < n_dst ? m : n_dst) + waves - 1) / waves;
+        by_ids += 3.9 + 0.18 * size(i) + 0.24 * size(i) * m / n_src + 2.8 * sums + (lines <= 192 ? 3.6 * (rounds - 1) : 0.0);
+        if (halves(i) && last_axis >= 0 && last_axis != axis) {                 // the second of a pair: one launch for both
+            by_pass += 0.20 * (size(i + 1) - size(i));
+            last_axis = -1;
+            continue;
+        }
+        by_pass += halves(i) ? 6.3 + 0.20 * (size(i) + size(i + 1)) : 15.7 + 0.54 * size(i);
+        last_axis = halves(i) ? axis : -1;
+        ++steps;
+    }
+    return by_ids <= by_pass + (steps > 1 ? 3.9 : 0.0);
+}
+
 template <typename T>
 static luvc_status run_adjacent(const T* x, T* ov, const T* xk, T* ovk, int Dk, const int32_t* idx_in, const int32_t* sizes_in, const int32_t* kept_in,
                                 int B, const LazyGeom& g, int32_t* idx_out, int32_t* sizes_out, int32_t* kept_out, int32_t* pass_map, hipStream_t st)

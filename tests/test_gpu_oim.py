@@ -342,3 +342,23 @@ def test_few_tokens_row_widths(oracle, dtype, B, H, W, D, passes):
     rng = np.random.default_rng(H * 1000 + W * 10 + D)
     x = wl.cast_io((wl.smooth_field(rng, B, H, W, D, 1.5) + 0.5 * rng.standard_normal((B, H, W, D))).astype(np.float32), dtype)
     run_case(oracle, x, dtype, passes, sizes=rng.integers(1, 6, (B, H, W)), tag="widths")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,W,D,passes", [
+    (1, 12, 100, 640, [(W_AX, 50), (H_AX, 3)]), (1, 12, 100, 640, [(W_AX, 25), (H_AX, 3)]), (1, 12, 100, 640, [(W_AX, 49)]),
+    (1, 12, 100, 640, [(W_AX, 2)]), (1, 6, 120, 64, [(W_AX, 60), (W_AX, 0), (H_AX, 3), (W_AX, 2)]), (2, 24, 24, 64, [(W_AX, 12), (H_AX, 6)]),
+    (2, 24, 24, 64, [(W_AX, 6), (H_AX, 12)]), (1, 96, 96, 72, [(W_AX, 47), (H_AX, 48)]), (3, 9, 17, 40, [(H_AX, 0), (W_AX, 3), (H_AX, 0)]),
+])
+def test_schedules_by_pass_or_on_row_ids(oracle, dtype, B, H, W, D, passes):
+    """Schedules on both sides of the rule that runs them pass by pass or on grids of row ids, halvings and empty passes among
+    them; the keyed call with the tokens as their own keys always takes the ids."""
+    rng = np.random.default_rng(H * 1000 + W * 10 + D + len(passes))
+    x = wl.cast_io((wl.smooth_field(rng, B, H, W, D, 1.5) + 0.5 * rng.standard_normal((B, H, W, D))).astype(np.float32), dtype)
+    out, _ = run_case(oracle, x, dtype, passes, sizes=None, tag="route")
+    xd = to_dev(x, dtype)
+    keyed = lv.luvc_oim_merge_keyed(xd, xd.clone(), passes, 1)
+    torch.cuda.synchronize()
+    for k in ("x", "sizes", "merged_map", "kept_map"):
+        assert torch.equal(out[k], keyed[k]), k
+    assert torch.equal(keyed["x"], keyed["metric"])
