@@ -486,11 +486,9 @@ def luvc_oim_merge_ragged(x, shapes, schedules, sizes=None, want_maps: bool = Tr
         assert sizes.is_cuda and sizes.dtype == nat.i32 and sizes.is_contiguous() and sizes.numel() == T
         sizes = sizes.data_ptr()
     xo = torch.empty((To, D), dtype=x.dtype, device=x.device)
-    merged = kept = None
-    if want_maps:                                       # one allocation for the three of them
-        so, merged, kept = torch.empty((2 * To + T,), dtype=nat.i32, device=x.device).split_with_sizes((To, T, To))
-    else:
-        so = torch.empty((To,), dtype=nat.i32, device=x.device)
+    so = torch.empty((To,), dtype=nat.i32, device=x.device)
+    merged = torch.empty((T,), dtype=nat.i32, device=x.device) if want_maps else None
+    kept = torch.empty((To,), dtype=nat.i32, device=x.device) if want_maps else None
     H, W, passes, n_passes = plan.addr
     _check(nat.call(nat.luvc_oim_merge_ragged, x.data_ptr(), sizes, plan.n, H, W, D, code, passes, n_passes, xo.data_ptr(), so.data_ptr(),
                     _ptr(merged), _ptr(kept), workspace.data_ptr(), workspace.numel(), nat.stream(stream)))
@@ -541,7 +539,7 @@ def luvc_spu_stage_ragged(x, lengths, sigmas, keeps=None, use_hamming: bool = Tr
     if workspace is None:
         workspace = torch.empty(max(plan.need, 256), dtype=torch.uint8, device=x.device)
     scores = torch.empty((T,), dtype=nat.f32, device=x.device)
-    kept_idx, kept_origin = torch.empty((2 * K,), dtype=nat.i32, device=x.device).split_with_sizes((K, K))
+    kept_idx, kept_origin = torch.empty((K,), dtype=nat.i32, device=x.device), torch.empty((K,), dtype=nat.i32, device=x.device)
     xo = torch.empty((K, D), dtype=x.dtype, device=x.device) if (gather and keeps is not None) else None
     # a tensor without elements has no address: hand the library one it will not touch
     ki = kept_idx.data_ptr() if K else scores.data_ptr()

@@ -129,6 +129,16 @@ def test_spu_equal_samples_with_keep_counts_of_their_own(oracle, n, count, D, dt
     spu_ragged_case(oracle, [n] * count, D, dtype, 0.1, seed, sigmas=[4] * count, keeps=[n // 10 + i for i in range(count)])
 
 
+def test_results_own_their_memory():
+    """Every result is a tensor of its own: kept, resized or saved without the others, and aligned like any allocation."""
+    merged = lv.luvc_oim_merge_ragged(torch.randn((3 * 5 + 4 * 4, 16), device="cuda"), [(3, 5), (4, 4)], [[(1, 2)], [(0, 1)]])
+    stage = lv.luvc_spu_stage_ragged(torch.randn((9 + 7, 16), device="cuda"), [9, 7], [2, 1], [3, 2])
+    torch.cuda.synchronize()
+    results = [merged[k] for k in ("x", "sizes", "merged_map", "kept_map")] + [stage[k] for k in ("scores", "kept_idx", "origin", "x")]
+    assert len({t.untyped_storage().data_ptr() for t in results}) == len(results)
+    assert all(t.storage_offset() == 0 and t.untyped_storage().nbytes() == t.numel() * t.element_size() for t in results)
+
+
 def test_ragged_errors():
     x = torch.zeros((20, 8), device="cuda")
     with pytest.raises(lv.LuvcError):
