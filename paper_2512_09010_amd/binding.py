@@ -4,9 +4,10 @@ Argument marshalling only: every step of OIM and SPU runs in the HIP kernels.  P
 for device memory (tensors own the buffers) and for the current stream handle.  There is no
 CPU fallback: if the library is missing or cannot be loaded, importing callers get an error.
 
-The calls that enqueue work go through ``_luvc_call`` (csrc/pycall.c), not ctypes, and ask for a workspace size only where
+The calls that enqueue work go through ``_luvc_call`` (csrc/pycall.c) and ask for a workspace size only where
 they allocate one: on small inputs a call is bound by what the host does before the launch (one 24x24 image through merge, score
-and prune: 30 us of host time through ctypes, 14 like this).
+and prune: 30 us of host time through ctypes, 14 like this).  Where ``_luvc_call`` is not built - it needs x86-64, gcc and the
+Python headers - ctypes makes the same calls.
 """
 from __future__ import annotations
 
@@ -119,16 +120,20 @@ class _Native:
         import torch
         L = lib()
         try:
-            from . import _luvc_call
-        except ImportError as e:
-            raise FileNotFoundError("_luvc_call.so is not built; run `python -m paper_2512_09010_amd.build`") from e
-        self.torch, self.call = torch, _luvc_call.call
+            from ._luvc_call import call
+        except ImportError:                             # hosts it is not built for: the same calls through ctypes
+            call = None
+        self.torch, self.call = torch, call or (lambda entry, *args: entry(*args))
         self.code = {torch.float32: LUVC_F32, torch.bfloat16: LUVC_BF16}
         self.i32, self.f32 = torch.int32, torch.float32
         self.raw_stream, self.device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
         for name in ("luvc_oim_merge", "luvc_oim_merge_wide", "luvc_oim_merge_keyed", "luvc_value_enhance", "luvc_spu_score", "luvc_spu_score_static",
                      "luvc_spu_prune", "luvc_spu_stage", "luvc_oim_merge_ragged", "luvc_spu_stage_ragged"):
-            setattr(self, name, ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
+            f = getattr(L, name)
+            entry = ctypes.cast(f, ctypes.c_void_p).value
+            if call is None:                            # host arrays are handed over as addresses here too
+                entry = ctypes.CFUNCTYPE(f.restype, *(ctypes.c_void_p if issubclass(t, ctypes._Pointer) else t for t in f.argtypes))(entry)
+            setattr(self, name, entry)
 
     def stream(self, stream) -> int:
         return self.raw_stream(self.device()) if stream is None else int(stream.cuda_stream)

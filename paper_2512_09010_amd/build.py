@@ -3,6 +3,8 @@ from __future__ import annotations
 
 import glob
 import os
+import platform
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -32,8 +34,17 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def _builds_call() -> bool:
+    """_luvc_call.so relies on the x86-64 calling convention and is compiled with gcc against the Python headers; without it
+    the binding calls through ctypes."""
+    return (platform.machine() in ("x86_64", "AMD64") and shutil.which("gcc") is not None
+            and os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")))
+
+
 def stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(CALL_LIB) or os.path.getmtime(CALL_SRC) > os.path.getmtime(CALL_LIB):
+    if not os.path.exists(LIB):
+        return True
+    if _builds_call() and (not os.path.exists(CALL_LIB) or os.path.getmtime(CALL_SRC) > os.path.getmtime(CALL_LIB)):
         return True
     t = os.path.getmtime(LIB)
     deps = sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + [os.path.join(HERE, "..", "include", "luvc.h")]
@@ -63,6 +74,9 @@ def build(force: bool = True, verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
         objs = list(ex.map(compile_one, srcs))
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *(["-fsanitize=address", "-fsanitize=undefined", "-shared-libsan"] if SANITIZE else []), *objs, "-o", LIB])
+    if not _builds_call():
+        print("_luvc_call.so is not built (needs x86-64, gcc and the Python headers): calls go through ctypes", file=sys.stderr)
+        return LIB
     subprocess.check_call(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], CALL_SRC, "-o", CALL_LIB])
     return LIB
 

@@ -283,6 +283,23 @@ def test_argument_lists_follow_entries_changed_in_place(L, make):
             v += 1
 
 
+def test_calls_without_the_native_caller(L, monkeypatch):
+    """Hosts that cannot build _luvc_call.so make the same calls through ctypes: same entry points, pointers as integers or None."""
+    import sys
+    native = lv._Native()
+    monkeypatch.setitem(sys.modules, "paper_2512_09010_amd._luvc_call", None)
+    plain = lv._Native()
+    assert isinstance(native.luvc_value_enhance, int) and not isinstance(plain.luvc_value_enhance, int)
+    for nat in (native, plain):
+        rc = nat.call(nat.luvc_value_enhance, None, 4096, 4, 8, 8, lv.LUVC_F32, 8192, 8, 0)
+        assert rc == lv.LUVC_ERR_INVALID_ARG and "v, sizes and out" in lv.last_error()
+        rc = nat.call(nat.luvc_value_enhance, 4096, 4096, 4, 8, 7, lv.LUVC_F32, 8192, 8, 0)
+        assert rc == lv.LUVC_ERR_INVALID_ARG and "strides" in lv.last_error()
+        arr, addr, n = lv._schedule([(1, 9)])
+        rc = nat.call(nat.luvc_oim_merge, 4096, None, 1, 4, 4, 8, lv.LUVC_F32, addr, n, 0, 4096, 4096, None, None, 0, 0, 0)
+        assert rc == lv.LUVC_ERR_INVALID_ARG and "m=9" in lv.last_error()
+
+
 def test_argument_lists_of_plain_integers_are_kept(L):
     assert lv._schedule([(1, 2), (0, 2)])[1] == lv._schedule(((1, 2), (0, 2)))[1]
     assert lv._merge_plan([(8, 8)], [[(1, 2)]], 16, 1) is lv._merge_plan(((8, 8),), (((1, 2),),), 16, 1)
