@@ -389,7 +389,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
             }
         }
         if (g + n_tiles < n_groups) fetch(g + n_tiles, first_t{}, early_t{});          // in flight during B and C
-        else seen = tiles_look<4>(sy, b, tile, n_tiles);
+        else seen = tiles_look(sy, b, tile, n_tiles);
         __syncthreads();
         // ---- B, C, spectrum, C', B'
 #pragma unroll
@@ -438,7 +438,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
             for (int j = 0; j < JN; ++j) acc[j] = fmaf(v[j].x, v[j].x, fmaf(v[j].y, v[j].y, acc[j]));
         }
     }
-    tiles_claim<4>(sy, b, tile, n_tiles, seen);
+    tiles_claim(sy, b, tile, n_tiles, seen);
     // ---- Eq. 8: over the P pairs of a thread group, then across the workgroups of the sample
     float* pout = partial + ((int64_t)b * n_tiles + tile) * ld;
 #pragma unroll
@@ -450,7 +450,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
         const int n = COLS * j + n2;
         if (c == 0 && n < ld) tile_store(pout + n, n < N ? e : 0.f);
     }
-    tiles_to_scores<THREADS, 4>(partial, gpartial, sy, scores, b, tile, n_tiles, N, ld, &flag);
+    tiles_to_scores<THREADS>(partial, gpartial, sy, scores, b, tile, n_tiles, N, ld, &flag);
 }
 
 // ------------------------------------------------------------------ host side

@@ -280,7 +280,7 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
         forward(N2 - 1, std::true_type{});
         for (int n2 = N2 - 2; n2 >= 0; --n2) forward(n2, std::false_type{});
     }
-    const tile_tag_t seen = tiles_look<4>(sy, b, tile, n_tiles);     // no loads follow: nothing waits behind this one
+    const tile_tag_t seen = tiles_look(sy, b, tile, n_tiles);     // no loads follow: nothing waits behind this one
     // ------------------------------------------------------------------ mask (Eq. 5-6) with the 1/N of Eq. 7
 #pragma unroll
     for (int kb = 0; kb < 16; ++kb) {
@@ -335,7 +335,7 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
         __syncthreads();
     };
     inverse(0, std::true_type{});
-    tiles_claim<4>(sy, b, tile, n_tiles, seen);
+    tiles_claim(sy, b, tile, n_tiles, seen);
     for (int n2 = 1; n2 < N2; ++n2) inverse(n2, std::false_type{});
     float* pout = partial + ((int64_t)b * n_tiles + tile) * N;
     const float inv_n2 = 1.f / (float)N2;
@@ -344,7 +344,7 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
         tile_store(pout + n, eperm[(n2 * 16 + (q & 15)) * 16 + (q >> 4)]);
     }
     // ------------------------------------------------------------------ Eq. 8 across the channel tiles
-    tiles_to_scores<256, 4>(partial, gpartial, sy, scores, b, tile, n_tiles, N, N, &is_last);
+    tiles_to_scores<256>(partial, gpartial, sy, scores, b, tile, n_tiles, N, N, &is_last);
 }
 
 static size_t fft_lds_bytes(int N, int Q, int sigma)

@@ -1,6 +1,6 @@
 // SPU prune (paper Algorithm 2, last two steps): order-preserving top-k keep and gather.
 //
-//   spu_select   one workgroup per sample.  Scores are mapped to unsigned keys whose integer order
+//   spu_select   samples of more than 8192 tokens, one workgroup each.  Scores are mapped to unsigned keys whose integer order
 //                is the float order; a most-significant-digit radix select (4 passes of 8 bits,
 //                histogram in LDS) finds the key T of the n_keep-th largest score and how many
 //                tokens with key == T still belong to the keep set; a stable block-wide compaction
@@ -67,8 +67,6 @@ __device__ __forceinline__ int block_scan_incl(int v, int* wave_tot /*[16]*/, in
     return s + base;
 }
 
-constexpr int kSelMaxRegKeys = 8;                     // keys cached in registers per thread (N <= 8 * 1024)
-
 __global__ void __launch_bounds__(kSelThreads)
 spu_select(const float* __restrict__ scores, int N, int n_keep, int32_t* __restrict__ kept_idx,
            const int32_t* __restrict__ origin_in /* [B,N] or null: identity */, int32_t* __restrict__ origin_out /* [B,n_keep] or null */)
@@ -81,29 +79,14 @@ spu_select(const float* __restrict__ scores, int N, int n_keep, int32_t* __restr
     const float* s = scores + (int64_t)b * N;
     int32_t* out = kept_idx + (int64_t)b * n_keep;
 
-    // keys of tokens tid, tid + 1024, ... stay in registers when the sample is small enough
-    const bool cached = N <= kSelMaxRegKeys * kSelThreads;
-    uint32_t key[kSelMaxRegKeys];
-#pragma unroll
-    for (int i = 0; i < kSelMaxRegKeys; ++i) {
-        const int n = tid + i * kSelThreads;
-        key[i] = (cached && n < N) ? score_key(s[n]) : 0u;
-    }
-
     uint32_t prefix = 0, mask = 0;
     int remaining = n_keep;                            // still to pick among keys matching the prefix
     for (int shift = 24; shift >= 0; shift -= 8) {
         if (tid < 256) hist[tid] = 0;
         __syncthreads();
-        if (cached) {
-#pragma unroll
-            for (int i = 0; i < kSelMaxRegKeys; ++i)
-                if (tid + i * kSelThreads < N && (key[i] & mask) == prefix) atomicAdd(&hist[(key[i] >> shift) & 255u], 1);
-        } else {
-            for (int n = tid; n < N; n += kSelThreads) {
-                const uint32_t k = score_key(s[n]);
-                if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1);
-            }
+        for (int n = tid; n < N; n += kSelThreads) {
+            const uint32_t k = score_key(s[n]);
+            if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1);
         }
         __syncthreads();
         // digit d is the one where (tokens with a larger digit) < remaining <= (those plus hist[d]);
@@ -129,7 +112,7 @@ spu_select(const float* __restrict__ scores, int N, int n_keep, int32_t* __restr
         uint32_t k = 0;
         bool eq = false, gt = false;
         if (n < N) {
-            k = score_key(s[n]);                       // L1/L2-resident re-read; keeps the loop free of dynamic register indexing
+            k = score_key(s[n]);
             eq = (k == T);
             gt = (k > T);
         }

@@ -39,66 +39,40 @@ __device__ __forceinline__ void tile_store(float* p, float v)
     __hip_atomic_store(reinterpret_cast<unsigned int*>(p), __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// W consecutive floats (W = 4: one 16-byte access, needs 16-byte alignment) with device scope
-template <int W> struct tile_vec { float v[W]; };
+// four consecutive floats with device scope: one 16-byte access, 16-byte aligned
 typedef unsigned int tile_u32x4 __attribute__((__vector_size__(16)));
+constexpr int kTileVec = 4;
 constexpr int kAuxSc1 = 16;                      // cache-policy bit of the buffer instructions: device scope
 
-template <int W>
-__device__ __forceinline__ tile_vec<W> tile_load(__amdgpu_buffer_rsrc_t r, uint32_t byte_off)
-{
-    tile_vec<W> o;
-    if (W == 4) {
-        const tile_u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, kAuxSc1);
-        o.v[0] = __uint_as_float(q[0]); o.v[1 % W] = __uint_as_float(q[1]); o.v[2 % W] = __uint_as_float(q[2]); o.v[3 % W] = __uint_as_float(q[3]);
-    } else {
-        o.v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, byte_off, 0, kAuxSc1));
-    }
-    return o;
-}
-template <int W>
-__device__ __forceinline__ void tile_store(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, const tile_vec<W>& o)
-{
-    if (W == 4) {
-        tile_u32x4 q;
-        q[0] = __float_as_uint(o.v[0]); q[1] = __float_as_uint(o.v[1 % W]); q[2] = __float_as_uint(o.v[2 % W]); q[3] = __float_as_uint(o.v[3 % W]);
-        __builtin_amdgcn_raw_buffer_store_b128(q, r, byte_off, 0, kAuxSc1);
-    } else {
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o.v[0]), r, byte_off, 0, kAuxSc1);
-    }
-}
-
-// out[n] = sum over `count` rows (row stride ld floats) of in[row][n], n < N, added in row order in fp64; FIN: square
-// root.  W = 4 needs ld % 4 == 0.  Up to TRIP rows per trip, all loads of a trip in flight together (a short trip re-reads its last row).
-template <int THREADS, int W, bool FIN, int TRIP = kTileGroup>
+// out[n] = sum over `count` rows (row stride ld floats, ld % 4 == 0) of in[row][n], n < N, added in row order in fp64; FIN: square
+// root.  Up to kTileGroup rows per trip, all loads of a trip in flight together (a short trip re-reads its last row).
+template <int THREADS, bool FIN>
 __device__ __forceinline__ void tile_rows_sum(const float* in, int count, int N, int ld, float* out)
 {
     const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in), 0, count * ld * 4, 0x00020000);
     const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, ld * 4, 0x00020000);
-    for (int i = threadIdx.x * W; i < N; i += THREADS * W) {
-        double e[W];
-#pragma unroll
-        for (int c = 0; c < W; ++c) e[c] = 0.0;
-        for (int r0 = 0; r0 < count; r0 += TRIP) {
+    for (int i = threadIdx.x * kTileVec; i < N; i += THREADS * kTileVec) {
+        double e[kTileVec] = {0.0, 0.0, 0.0, 0.0};
+        for (int r0 = 0; r0 < count; r0 += kTileGroup) {
             const int left = count - r0;
-            tile_vec<W> p[TRIP];
+            tile_u32x4 p[kTileGroup];
 #pragma unroll
-            for (int r = 0; r < TRIP; ++r)
-                p[r] = tile_load<W>(rin, (uint32_t)(((r0 + (r < left ? r : left - 1)) * ld + i) * 4));
+            for (int r = 0; r < kTileGroup; ++r)
+                p[r] = __builtin_amdgcn_raw_buffer_load_b128(rin, (uint32_t)(((r0 + (r < left ? r : left - 1)) * ld + i) * 4), 0, kAuxSc1);
 #pragma unroll
-            for (int r = 0; r < TRIP; ++r)
+            for (int r = 0; r < kTileGroup; ++r)
 #pragma unroll
-                for (int c = 0; c < W; ++c) e[c] += r < left ? (double)p[r].v[c] : 0.0;
+                for (int c = 0; c < kTileVec; ++c) e[c] += r < left ? (double)__uint_as_float(p[r][c]) : 0.0;
         }
-        tile_vec<W> o;
+        tile_u32x4 o;
 #pragma unroll
-        for (int c = 0; c < W; ++c) o.v[c] = FIN ? (float)sqrt(e[c]) : (float)e[c];
+        for (int c = 0; c < kTileVec; ++c) o[c] = __float_as_uint(FIN ? (float)sqrt(e[c]) : (float)e[c]);
         if (FIN) {
 #pragma unroll
-            for (int c = 0; c < W; ++c)
-                if (W == 1 || i + c < N) out[i + c] = o.v[c];      // scores: ordinary stores, no alignment assumed
+            for (int c = 0; c < kTileVec; ++c)
+                if (i + c < N) out[i + c] = __uint_as_float(o[c]);             // scores: ordinary stores, no alignment assumed
         } else {
-            tile_store<W>(rout, (uint32_t)(i * 4), o);
+            __builtin_amdgcn_raw_buffer_store_b128(o, rout, (uint32_t)(i * 4), 0, kAuxSc1);
         }
     }
 }
@@ -111,14 +85,8 @@ struct TileSync {
     tile_tag_t tag;              // 48 bits, non-zero
 };
 
-constexpr int kTileGroupOneLevelMax = 64;        // W = 1: up to this many tiles are added in one level
 inline __host__ __device__ int spu_tile_groups(int n_tiles) { return (n_tiles + kTileGroup - 1) / kTileGroup; }
-template <int W>
-__device__ __forceinline__ bool tiles_two_level(int n_tiles)
-{
-    // scalar accesses (W = 1) leave room for 64 loads in flight per thread
-    return spu_tile_groups(n_tiles) > 1 && !(W == 1 && n_tiles <= kTileGroupOneLevelMax);
-}
+__device__ __forceinline__ bool tiles_two_level(int n_tiles) { return spu_tile_groups(n_tiles) > 1; }
 
 __device__ __forceinline__ tile_tag_t tag_load(const tile_tag_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void tag_store(tile_tag_t* p, tile_tag_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -127,26 +95,23 @@ __device__ __forceinline__ void tag_store(tile_tag_t* p, tile_tag_t v) { __hip_a
 // itself (its group's, or the sample's where there is no group level); lane 1 of the first workgroup of every
 // group handles the sample's word, which the workgroup that completes the group bumps - after every workgroup of
 // the group has arrived, the first one with its claim behind it.
-template <int W>
 __device__ __forceinline__ tile_tag_t* tiles_word(const TileSync& sy, int b, int tile, int n_tiles)
 {
     const int n_groups = spu_tile_groups(n_tiles);
     tile_tag_t* w = sy.arrive + (int64_t)b * (n_groups + 1);
-    const bool two_level = tiles_two_level<W>(n_tiles);
+    const bool two_level = tiles_two_level(n_tiles);
     if (threadIdx.x == 0) return two_level ? w + 1 + tile / kTileGroup : w;
     if (threadIdx.x == 1 && two_level && tile % kTileGroup == 0) return w;
     return nullptr;
 }
-template <int W>
 __device__ __forceinline__ tile_tag_t tiles_look(const TileSync& sy, int b, int tile, int n_tiles)
 {
-    const tile_tag_t* w = tiles_word<W>(sy, b, tile, n_tiles);
+    const tile_tag_t* w = tiles_word(sy, b, tile, n_tiles);
     return w ? tag_load(w) : 0;
 }
-template <int W>
 __device__ __forceinline__ void tiles_claim(const TileSync& sy, int b, int tile, int n_tiles, tile_tag_t seen)
 {
-    tile_tag_t* w = tiles_word<W>(sy, b, tile, n_tiles);
+    tile_tag_t* w = tiles_word(sy, b, tile, n_tiles);
     if (w && (seen >> 16) != sy.tag) {
         tile_tag_t expect = seen;
         (void)__hip_atomic_compare_exchange_strong(w, &expect, sy.tag << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -164,9 +129,9 @@ __device__ __forceinline__ bool tiles_arrive(tile_tag_t* w, int total)
 
 // Called by all THREADS threads of the workgroup of (sample b, tile) after they have written the tile's
 // energies to partial[(b * n_tiles + tile) * ld + n] with tile_store().  `flag` is a __shared__ word.
-// W = 4 needs ld % 4 == 0 (and the 256-byte alignment the workspace has anyway).  A sample of at most
+// ld % 4 == 0 (and the 256-byte alignment the workspace has anyway).  A sample of at most
 // kTileGroup tiles has no group level: its last workgroup adds the tiles directly.
-template <int THREADS, int W>
+template <int THREADS>
 __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [B, n_tiles, ld] */,
                                                 float* __restrict__ gpartial /* [B, n_groups, ld] */,
                                                 const TileSync sy,
@@ -176,7 +141,7 @@ __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [
     const int tid = threadIdx.x;
     const int n_groups = spu_tile_groups(n_tiles);
     tile_tag_t* cnt = sy.arrive + (int64_t)b * (n_groups + 1);
-    const bool two_level = tiles_two_level<W>(n_tiles);
+    const bool two_level = tiles_two_level(n_tiles);
     if (two_level) {
         const int grp = tile / kTileGroup, t_first = grp * kTileGroup;
         const int t_cnt = n_tiles - t_first < kTileGroup ? n_tiles - t_first : kTileGroup;
@@ -185,7 +150,7 @@ __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [
         if (tid == 0) *flag = tiles_arrive(cnt + 1 + grp, t_cnt);
         __syncthreads();
         if (!*flag) return;
-        tile_rows_sum<THREADS, W, false>(partial + ((int64_t)b * n_tiles + t_first) * ld, t_cnt, N, ld,
+        tile_rows_sum<THREADS, false>(partial + ((int64_t)b * n_tiles + t_first) * ld, t_cnt, N, ld,
                                          gpartial + ((int64_t)b * n_groups + grp) * ld);
     }
     const int last_cnt = two_level ? n_groups : n_tiles;
@@ -195,9 +160,9 @@ __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [
     __syncthreads();
     if (!*flag) return;
     if (two_level)
-        tile_rows_sum<THREADS, W, true>(gpartial + (int64_t)b * n_groups * ld, last_cnt, N, ld, scores + (int64_t)b * N);
+        tile_rows_sum<THREADS, true>(gpartial + (int64_t)b * n_groups * ld, last_cnt, N, ld, scores + (int64_t)b * N);
     else
-        tile_rows_sum<THREADS, W, true, (W == 1 ? kTileGroupOneLevelMax : kTileGroup)>(partial + (int64_t)b * n_tiles * ld, last_cnt, N, ld, scores + (int64_t)b * N);
+        tile_rows_sum<THREADS, true>(partial + (int64_t)b * n_tiles * ld, last_cnt, N, ld, scores + (int64_t)b * N);
 }
 
 // Host side: 48-bit non-zero tag of the next launch (process-wide sequence, random start)

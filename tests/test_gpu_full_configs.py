@@ -132,7 +132,7 @@ def test_step_replayed_from_a_hip_graph():
         assert torch.equal(pr["kept_idx"], eager_p["kept_idx"]) and torch.equal(pr["x"].view(torch.int16), eager_p["x"].view(torch.int16)), rep
 
 
-@pytest.mark.parametrize("B,N,D,sigma", [(2, 1024, 544, 102), (2, 196, 320, 4)])      # fft path (two tile groups), one-launch direct path
+@pytest.mark.parametrize("B,N,D,sigma", [(2, 1024, 544, 102), (2, 196, 320, 4)])      # fft path (two tile groups), circulant path (two workgroups across the channels)
 def test_graph_replays_beside_eager_score_calls(B, N, D, sigma):
     """A captured score launch replayed on one stream while more than 64 eager score calls run on another: every call
     owns its workspace (completion counters included), so nothing is shared between calls in flight and every result

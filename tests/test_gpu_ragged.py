@@ -115,7 +115,7 @@ def spu_ragged_case(oracle, lengths, D, dtype, ratio, seed, origin_shift=None, s
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_spu_ragged_batch(oracle, dtype):
-    # lengths on the fft path (1024, 720, 256), the fused direct path (196, 64) and the general path (300, 97, 1); runs of 2
+    # lengths with convenient factors (1024, 720, 256) and without, long and short; runs of 2
     lengths = [1024, 1024, 720, 196, 196, 300, 64, 97, 256, 1]
     spu_ragged_case(oracle, lengths, 96, dtype, 0.25, 4)
     spu_ragged_case(oracle, lengths[2:], 70, dtype, 0.1, 5, origin_shift=7)

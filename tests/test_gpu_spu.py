@@ -40,7 +40,7 @@ def score_case(oracle, x_io, dtype, sigma, ham=True, tag="", stride_pad=0):
     (1, 1280, 31, 64),
     (2, 240, 64, 119), (1, 240, 33, 0), (2, 720, 70, 54), (1, 480, 40, 60), (1, 1200, 34, 100),      # Q = 15
     (2, 144, 64, 71), (1, 144, 200, 18), (1, 288, 37, 30), (1, 432, 64, 72), (1, 1008, 32, 7),       # Q = 9
-    # one-launch direct path beyond a single batch of token pairs per wavefront, odd and even lengths, up to its LDS limit
+    # narrow bands on lengths without convenient factors, odd and even
     (2, 600, 70, 3), (1, 601, 33, 5), (1, 1500, 33, 2), (1, 3000, 64, 1), (1, 4000, 40, 1), (1, 513, 64, 11),
 ])
 def test_score_small_random(oracle, dtype, B, N, D, sigma):
@@ -297,8 +297,8 @@ def test_score_where_token_energies_vanish(oracle, dtype, B, N, D, sigma):
 
 
 @pytest.mark.parametrize("seed", range(4))
-def test_score_fuzz_on_lengths_with_a_thinned_inverse(oracle, seed):
-    """Seeded random cases on the lengths the fft path serves, mostly with bands narrow enough for the thinned inverse:
+def test_score_fuzz_on_token_energies(oracle, seed):
+    """Seeded random cases on the lengths the fft path serves (and whatever else takes them at these sizes), mostly with narrow bands:
     white noise, tones that cross zero in every channel, spans of zero tokens, a few dominant channels, token norms
     that swing over orders of magnitude, random walks (large energies next to small ones across the wrap-around)."""
     rng = np.random.default_rng(900 + seed)
@@ -324,7 +324,7 @@ def test_score_fuzz_on_lengths_with_a_thinned_inverse(oracle, seed):
         if kind == 5:
             x = np.cumsum(x, axis=1) / np.sqrt(N)
         pad = int(rng.choice([0, 0, 3, 8]))
-        score_case(oracle, wl.cast_io(x.astype(np.float32), dtype), dtype, sigma, True, f"thin-fuzz{seed}.{it} kind={kind}", stride_pad=pad)
+        score_case(oracle, wl.cast_io(x.astype(np.float32), dtype), dtype, sigma, True, f"energy-fuzz{seed}.{it} kind={kind}", stride_pad=pad)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

@@ -45,7 +45,7 @@ def run_cascade(oracle, x0, dtype, keeps, sigmas, ham, tag):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("B,N,D,ratio,stages", [
     (2, 1024, 96, 0.5, 4),        # 1024 -> 512 -> 256 (fft path) -> 128 -> 0
-    (3, 720, 70, 0.3, 3),         # 720 (Q = 15) -> 216 -> 65 (direct path) -> 0
+    (3, 720, 70, 0.3, 3),         # 720 (Q = 15) -> 216 -> 65 -> 0
     (1, 5000, 40, 0.25, 3),       # above the single-launch prune limit: select + gather launches
     (2, 37, 9, 0.6, 3),
 ])

@@ -19,8 +19,9 @@ def _x(seed, B, N, D, dtype):
 def test_static_scratch_matches_the_workspace_call():
     cases = [(4, 1024, 512, "bf16", 102),      # fft path: 16 channel tiles per sample, two tile groups
              (2, 720, 200, "f32", 54),         # smaller, right after it, on the same array: 16 x 15 transform, ragged last tile
-             (3, 196, 256, "bf16", 4),         # direct pass-band transform in one launch
-             (2, 50, 96, "f32", 25),           # three-launch path (tables and spectra in the scratch as well)
+             (3, 196, 512, "bf16", 4),         # circulant product, two workgroups across the channels
+             (1, 8200, 70, "f32", 25),         # three-launch path (tables and spectra in the scratch as well)
+             (2, 1500, 96, "f32", 25),         # transform of 3072 points (a spectrum in the scratch)
              (4, 1024, 512, "bf16", 102)]      # the first shape again, after the others have left their traces
     for i, (B, N, D, dtype, sigma) in enumerate(cases):
         print(f"[static] call {i}: B={B} N={N} D={D} {dtype} sigma={sigma}", flush=True)
