@@ -36,7 +36,7 @@
 // All lines of a grid start together, so what follows the screening is serial time of the launch: no lists or
 // flags are handed through LDS where a ballot does, and each step after the screening is one barrier.
 // Bound: the screening, by the rate at which the tokens arrive (8 x 64 x 64 x 1280 bf16: 84 MB a pass), then latency
-// (three operations of merge number 2 on that grid, 25 passes and the last copy: 212 us, 175 with eight wavefronts per line
+// (three operations of merge number 2 on that grid, six passes and the last copy: 212 us, 182 with eight wavefronts per line
 // where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening).
 #include <type_traits>
 
