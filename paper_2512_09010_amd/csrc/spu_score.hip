@@ -252,15 +252,13 @@ SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, CircRows cir
     }
 }
 
-// what a call needs whichever way its rows lie
+// What a call needs whichever way its rows lie: the long kernels' scratch, or spu_circ's words where those are more and it is
+// taken for rows in pairs (where it is taken for single rows, it is for pairs too).
 size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most)
 {
-    size_t need = 0;
-    for (CircRows rows : {CircRows::None, CircRows::Single, CircRows::Paired}) {
-        const size_t b = spu_layout(B, N, D, sigma, dt, rows, most).bytes;
-        need = b > need ? b : need;
-    }
-    return need;
+    const size_t need = spu_layout(B, N, D, sigma, dt, CircRows::None, most).bytes;
+    const size_t circ = N <= kCircMaxN ? align_up(spu_circ_bytes(B, N, D)) : 0;
+    return circ > need && circ <= most && spu_path(B, N, D, sigma, dt, CircRows::Paired) == SpuPath::Circ ? circ : need;
 }
 
 luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma,
