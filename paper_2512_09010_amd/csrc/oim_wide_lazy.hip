@@ -16,12 +16,15 @@
 //      (v_mfma_f32_32x32x16_bf16, or four v_mfma_f32_32x32x2_f32 for fp32 tokens): a 32 x 32 tile at a time, eight
 //      wavefronts split the channels, every token byte is fetched once per tile.  The squared norms are summed in fp32
 //      on the way (in fp64, they took as long as everything else of the screening).  A screened cosine is taken to be
-//      within eps = (D + 24) 2^-22 of the fp64 cosine: the products of bf16 values are exact in fp32, and D
-//      accumulation steps of at most 2^-23 each (relative to the sum of the magnitudes of the products, which is at
-//      most the product of the norms) stay below half of that - tests/test_gpu_oim_wide.py pins the contraction against
-//      fp64 on adversarial rows; the other half covers the norms (a lane adds a sixteenth of the squares, D / 16 + 24
-//      steps of at most 2^-23 on each, halved by the root), the rounding of fp32 products, of the reciprocals and of
-//      two products.  Sums of squares beyond 2^100 end the screening of their line: everything is repeated then.  Small
+//      within eps = (5 D / 32 + 48) 2^-23 of the fp64 cosine.  A wavefront contracts c <= D / 8 + 16 channels, which is
+//      at most c accumulation steps of 2^-23 each (relative to the sum of the magnitudes of the products, which is at
+//      most the product of the norms; the products of bf16 values are exact in fp32) - tests/test_gpu_oim_wide.py pins
+//      the contraction at that rate against fp64 on adversarial rows - and adding the eight parts is 4 more.  A squared
+//      norm is the sum of c / 2 roundings of 2^-24 in a lane and 8 behind it, halved by the root, twice; root,
+//      reciprocal and the two products of a cosine are 5: 5 c / 4 + 13 together.  The roundings count along the
+//      longest chain of additions, an eighth of the channels, not over all of them.  With (D + 24) 2^-22, ten times as
+//      much at 1280 channels, more sources and destinations had to be repeated in fp64, a memory trip behind the
+//      screening (8 x 64 x 64 x 1280 bf16, six passes of merge number 2: 185.7 us, 173.0 now).  Sums of squares beyond 2^100 end the screening of their line: everything is repeated then.  Small
 //      values need no such care: what flushed products lose is below 2^-116, far below a norm of 1e-12, which is where
 //      the method clamps.
 //   2. EXACT.  A source may be among the m best of the line only if fewer than m screened best cosines exceed its own by
@@ -36,8 +39,8 @@
 // All lines of a grid start together, so what follows the screening is serial time of the launch: no lists or
 // flags are handed through LDS where a ballot does, and each step after the screening is one barrier.
 // Bound: the screening, by the rate at which the tokens arrive (8 x 64 x 64 x 1280 bf16: 84 MB a pass), then latency
-// (three operations of merge number 2 on that grid, six passes and the last copy: 212 us, 182 with eight wavefronts per line
-// where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening).
+// (three operations of merge number 2 on that grid, six passes and the last copy: 212 us; 185 with eight wavefronts per line
+// where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening; 173 now).
 #include <type_traits>
 
 #include "common.hpp"
@@ -232,7 +235,7 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     const T* dx = xk ? xk : x;
     const T* dov = xk ? ovk : ov;
     const int dD = xk ? Dk : g.D;
-    float tau = 2.f * (float)(dD + 24) * 2.3841858e-7f;                // 2 eps
+    float tau = 2.f * (0.15625f * (float)dD + 48.f) * 1.1920929e-7f;  // 2 eps
 
     for (int p = tid; p < len; p += blockDim.x) {
         const int f = in_flat(p);

@@ -183,8 +183,8 @@ def test_wide_without_maps(oracle):
 @pytest.mark.parametrize("D", [8, 16, 24, 72, 520, 1280, 2048])
 def test_screening_tile_error_stays_inside_the_bound_the_decisions_assume(dtype, D):
     """The 32 x 32 tile of dot products formed on the matrix cores in the storage precision against exact sums, on rows
-    chosen to provoke accumulation error: the screening of the wide matching assumes an error of at most D 2^-23 times
-    the sum of the magnitudes of the products (it budgets twice that, relative to the product of the norms)."""
+    chosen to provoke accumulation error: the screening of the wide matching assumes that a wavefront that contracts D
+    channels is off by at most D 2^-23 times the sum of the magnitudes of the products."""
     rng = np.random.default_rng(D)
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
     cases = {
@@ -220,6 +220,17 @@ def test_wide_decisions_the_screening_cannot_tell(oracle, dtype):
         sizes = rng.integers(1, 4, (2, H, W))
         run_wide(oracle, wl.cast_io(x, dtype), dtype, passes, radius, tag="close calls")
         run_wide(oracle, wl.cast_io(x, dtype), dtype, passes, radius, sizes=sizes, tag="close calls+sizes")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,apart", [(8, 2e-3), (136, 4e-3), (1280, 2e-3), (1280, 8e-3), (1408, 4e-3)])
+def test_wide_decisions_around_the_screening_bound(oracle, dtype, D, apart):
+    """Cosines of a line about apart^2 = 4e-6 .. 6e-5 from each other, where the screening's allowance (6e-6 at 8 channels, 3e-5 at
+    1408) takes some decisions and leaves others to fp64; long lines have several tiles."""
+    rng = np.random.default_rng(int(D + 1e4 * apart))
+    for (H, W, passes, radius) in ((5, 30, [(W_AX, 2), (H_AX, 1)], 0), (2, 128, [(W_AX, 3)], 0), (3, 66, [(W_AX, 20)], 4)):
+        x = rng.standard_normal((2, 1, 1, D)) + apart * rng.standard_normal((2, H, W, D))
+        run_wide(oracle, wl.cast_io(x.astype(np.float32), dtype), dtype, passes, radius, tag=f"{apart} apart")
 
 
 def test_wide_determinism():
