@@ -164,7 +164,7 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
         const unsigned long long hits = ((from_prev >> k) & 1ull) << k | (((from_next >> k) & 1ull) << k) << 1;
         T* mov = on_metric ? ovk : ov;
         const int mD = on_metric ? Dk : g.D;
-        lazy_merge<T, PM>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, hits, mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane);
+        lazy_merge<T, PM>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, hits, mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane, 0, mD);
     }
 }
 

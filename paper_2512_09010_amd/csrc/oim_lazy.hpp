@@ -59,20 +59,34 @@ __device__ __forceinline__ int lazy_slot(const LazyLine& l, int p)
     return p - __popcll(l.gone & ((p & 1) ? (2ull << k) - 1ull : (1ull << k) - 1ull));
 }
 
+// acc / S, correctly rounded, once to the storage type: the reciprocal is, and one step on the exact remainder corrects the
+// product (a zero keeps its sign, an infinity, whose remainder is no number, stays one)
+template <typename T>
+__device__ __forceinline__ void lazy_round_store(const double (&acc)[lz_io<T>::V], double S, double inv, T* to)
+{
+    T q[lz_io<T>::V];
+#pragma unroll
+    for (int e = 0; e < lz_io<T>::V; ++e) {
+        const double w = acc[e] * inv, rem = fma(-w, S, acc[e]);
+        io_traits<T>::store(&q[e], __builtin_islessgreater(rem, 0.0) ? fma(rem, inv, w) : w);
+    }
+    *reinterpret_cast<lz_u32x4*>(to) = *reinterpret_cast<const lz_u32x4*>(q);
+}
+
 // Size-weighted mean of destination k and the sources `hits` (bit j: source 2 j) of the line, to row o: fp64, destination
 // first, then the sources in ascending position, rounded once.  The destination and two sources are fetched together, P pieces
-// of each at a time.
+// of each at a time.  The wavefront's share of the row: channels `from` .. `to` - 1.
 template <typename T, int P = kLzPieces>
 __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGeom& g, int D, int64_t b, const int* rid, const int* sz, int k,
-                                           unsigned long long hits, T* o, int lane)
+                                           unsigned long long hits, T* o, int lane, int from, int to)
 {
     using io = lz_io<T>;
     constexpr int V = io::V;
     const __amdgpu_buffer_rsrc_t rp = lz_row(row_of<T>(x, ov, b, rid[2 * k + 1], g, D), D, true);
     const double sp = (double)sz[2 * k + 1];
-    for (int d0 = 0; d0 < D; d0 += 64 * V * P) {
+    for (int d0 = from; d0 < to; d0 += 64 * V * P) {
         double acc[P][V], S = sp;
-        const int pieces = (D - d0 + 64 * V - 1) / (64 * V);           // of this block that hold anything, the same in every lane
+        const int pieces = (to - d0 + 64 * V - 1) / (64 * V);           // of this block that hold anything, the same in every lane
         unsigned long long h = hits;
         bool first = true;
         do {
@@ -109,16 +123,8 @@ __device__ __forceinline__ void lazy_merge(const T* x, const T* ov, const LazyGe
 #pragma unroll
         for (int u = 0; u < P; ++u) {
             const int d = d0 + (u * 64 + lane) * V;
-            if (d >= D) continue;
-            T q[V];
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                // acc / S, correctly rounded: the reciprocal is, and one step on the exact remainder corrects the product
-                // (a zero keeps its sign, an infinity, whose remainder is no number, stays one)
-                const double w = acc[u][e] * inv, rem = fma(-w, S, acc[u][e]);
-                io_traits<T>::store(&q[e], __builtin_islessgreater(rem, 0.0) ? fma(rem, inv, w) : w);
-            }
-            *reinterpret_cast<lz_u32x4*>(o + d) = *reinterpret_cast<const lz_u32x4*>(q);
+            if (d >= to) continue;
+            lazy_round_store<T>(acc[u], S, inv, o + d);
         }
     }
 }

@@ -40,7 +40,7 @@
 // flags are handed through LDS where a ballot does, and each step after the screening is one barrier.
 // Bound: the screening, by the rate at which the tokens arrive (8 x 64 x 64 x 1280 bf16: 84 MB a pass), then latency
 // (three operations of merge number 2 on that grid, six passes and the last copy: 212 us; 185 with eight wavefronts per line
-// where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening; 173 now).
+// where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening; 170 now).
 #include <type_traits>
 
 #include "common.hpp"
@@ -450,16 +450,22 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     // ------------------------------------------------------------------ 4. the merged destinations
     // (features, and the metric too when the decisions were taken on one: it follows its own decisions)
     const int n_abs = __popcll(ln.takes);
-    for (int kk = wave; kk < (xk ? 2 : 1) * n_abs; kk += NW) {
-        const bool on_metric = kk >= n_abs;
-        const int at = on_metric ? kk - n_abs : kk;
+    // One or two rows to merge: wavefronts without one of their own take a share of its channels (8x64x64x1280 bf16, merge
+    // number 2, six passes: 173.0 us, 170.0; 12x32x32x1024: 99.9, 97.3; four rows in halves: 37.5, 39.2, so not those).
+    constexpr int kPiece = 64 * lz_io<T>::V;
+    const int n_merges = (xk ? 2 : 1) * n_abs, pieces = (g.D + kPiece - 1) / kPiece;
+    const int parts = n_merges > 0 && 4 * n_merges <= NW ? min(NW / n_merges, pieces) : 1, share = (pieces + parts - 1) / parts * kPiece;
+    for (int kk = wave; kk < n_merges * parts; kk += NW) {
+        const int merge = kk / parts, from = (kk - merge * parts) * share;
+        const bool on_metric = merge >= n_abs;
+        const int at = on_metric ? merge - n_abs : merge;
         unsigned long long left = ln.takes;
         for (int i = 0; i < at; ++i) left &= left - 1;
         const int k = (int)__builtin_ctzll(left);
         T* mov = on_metric ? ovk : ov;
         const int mD = on_metric ? Dk : g.D;
         lazy_merge<T>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, __ballot(leaves && bk == k),
-                      mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane);
+                      mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane, from, min(mD, from + share));
     }
 }
 
