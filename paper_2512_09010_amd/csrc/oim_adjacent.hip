@@ -4,16 +4,18 @@
 //
 // One workgroup per line of at most 128 tokens.  A wavefront fetches four consecutive tokens and the one after them, all
 // in flight together, and forms their squared norms and neighbour products in fp64 at once: with two candidates per
-// source there is little to save by screening, and a pass needs no second look at the tokens.  Then the cosines of the
-// sources (one wavefront, a source per lane), the m best of them (a source per ballot), the layout of the next grid and
-// the size-weighted means of the destinations that take sources in, written to overlay rows.
+// source there is little to save by screening, and a pass needs no second look at the tokens (screened in fp32, a line in a
+// hundred had to be repeated in fp64, which is a line in nearly every launch: no quicker).  Then the cosines of the
+// sources (one wavefront, a source per lane), the m best of them (few: picked one by one by that wavefront; else a source
+// per ballot), the layout of the next grid and the size-weighted means of the destinations that take sources in, written
+// to overlay rows.
 //
 // Bound: latency.  A pass reads its tokens once, but a line is a chain of memory trips - ids, tokens, merged rows - with
 // the decisions between them; as many wavefronts as a line has groups of four tokens share it, so that each trip is made once.
 // 12 x 32 x 32 x 1024 bf16, three operations of (W,2),(H,2): 157 us as three launches per pass (norms and products,
 // decisions, a merge that rewrote the whole grid), 75 us as one, 68 with two pieces of a row per lane where a row has no more.
 // Narrow rows were slower than the three launches while every row took three pieces: 32 x 64 x 64 x 384 bf16, (W,2): 92 us by
-// pass, 130, 78 now, of which the copy of the output rows went from 63 to 31.
+// pass, 130, 78 then, of which the copy of the output rows went from 63 to 31.
 #include "common.hpp"
 #include "oim.hpp"
 #include "oim_lazy.hpp"
@@ -24,8 +26,13 @@ namespace luvc {
 constexpr int kAdjTok = 4;                       // consecutive tokens of a wavefront
 
 // P, PM: 16-byte pieces of a row per lane at a time, for the decisions and for the merged rows.  A piece past the row's end
-// costs its fp64 products all the same, and the registers of fewer pieces leave room for a second line on a compute unit.
-template <typename T, int P, int PM>
+// costs its products all the same, and the registers of fewer pieces leave room for a second line on a compute unit.
+// HOLD: a line has at most four tokens per wavefront, a row at most P pieces, and the decisions are taken on the tokens:
+// they stay in registers until the end of the pass, and a wavefront merges the two destinations among its own.  Taken where
+// the lines come in several rounds: 8 x 64 x 64 x 1280 bf16, merge number 2 three times, 167.2 us a call without, 163.0 with
+// (169.1 before m sources were picked by one wavefront); 32 x 64 x 64 x 384, once, 122.4, 118.7 (124.1).  A launch that
+// is one round long is no quicker for the trip it saves: 12 x 32 x 32 x 1024 68.1, 69.6; 1 x 100 x 24 x 1408 68.7, 70.7.
+template <typename T, int P, int PM, bool HOLD>
 __global__ void __launch_bounds__(1024)
 oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric [.., Dk] the decisions are taken on, or null: x */,
                   T* ovk /* its overlay */, int Dk, const int32_t* __restrict__ idx_in /* null: identity */,
@@ -60,6 +67,7 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
         sz[p] = sizes_in ? sizes_in[img + f] : 1;
     }
     // ---- squared norms and neighbour products
+    lz_u32x4 tok[kAdjTok + 1][P];                // tokens p0 .. p0 + 4 of the line, P pieces of each
     for (int p0 = wave * kAdjTok; p0 < len; p0 += NW * kAdjTok) {
         __amdgpu_buffer_rsrc_t r[kAdjTok + 1];
 #pragma unroll
@@ -70,20 +78,19 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
         double s[2 * kAdjTok];
 #pragma unroll
         for (int i = 0; i < 2 * kAdjTok; ++i) s[i] = 0.0;
-        for (int d0 = 0; d0 < dD; d0 += 64 * V * P) {
-            lz_u32x4 t[kAdjTok + 1][P];
+        for (int d0 = 0; d0 < (HOLD ? 1 : dD); d0 += 64 * V * P) {
 #pragma unroll
             for (int i = 0; i <= kAdjTok; ++i)
 #pragma unroll
-                for (int u = 0; u < P; ++u) t[i][u] = lz_load(r[i], (d0 + (u * 64 + lane) * V) * (int)sizeof(T));
+                for (int u = 0; u < P; ++u) tok[i][u] = lz_load(r[i], (d0 + (u * 64 + lane) * V) * (int)sizeof(T));
 #pragma unroll
             for (int u = 0; u < P; ++u)
 #pragma unroll
                 for (int e = 0; e < V; ++e) {
-                    double a = io::at(t[0][u], e);
+                    double a = io::at(tok[0][u], e);
 #pragma unroll
                     for (int i = 0; i < kAdjTok; ++i) {
-                        const double c = io::at(t[i + 1][u], e);
+                        const double c = io::at(tok[i + 1][u], e);
                         s[i] = fma(a, a, s[i]);
                         s[kAdjTok + i] = fma(a, c, s[kAdjTok + i]);
                         a = c;
@@ -98,28 +105,39 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
     }
     __syncthreads();
     // ---- cosine of every source with its two neighbours (equal: the lower position)
-    if (wave == 0 && lane < n_src) {
-        const int a = 2 * lane;
+    const bool few = 3 * g.m < n_src;            // then this wavefront picks them one by one; else all wavefronts rank the sources
+    if (wave == 0) {
+        const bool is_src = lane < n_src;
+        const int a = is_src ? 2 * lane : 0;
         const bool hl = a >= 1, hr = a + 1 < len;
         auto norm = [&](int p) { const double n = sqrt(nrm2[p]); return n < 1e-12 ? 1e-12 : n; };
         const double na = norm(a);
         const double sl = hl ? dnx[a - 1] / (na * norm(a - 1)) : 0.0, sr = hr ? dnx[a] / (na * norm(a + 1)) : 0.0;
         const bool left = hl && (!hr || !(sr > sl));
-        const double best = left ? sl : sr;
-        score[lane] = best == best ? best : -INFINITY;       // NaN: last, so that exactly m sources leave the line whatever the tokens hold
-        side[lane] = hl || hr ? (left ? 0 : 1) : -1;
+        double best = left ? sl : sr;
+        best = best == best ? best : -INFINITY;              // NaN: last, so that exactly m sources leave the line whatever the tokens hold
+        if (few) {
+            // m times the highest of those left (equal: the lower position)
+            unsigned long long out = 0ull;
+            for (int i = 0; i < g.m; ++i) {
+                const bool in = is_src && !((out >> lane) & 1ull);
+                const double top = wave_max64(in ? best : -INFINITY);
+                out |= 1ull << __builtin_ctzll(__ballot(in && best == top));
+            }
+            if (is_src) gone[lane] = (int)((out >> lane) & 1ull);
+        } else if (is_src) score[lane] = best;
+        if (is_src) side[lane] = hl || hr ? (left ? 0 : 1) : -1;
     }
     __syncthreads();
-    // ---- the m best (equal: the lower position): a source per ballot of those that beat it
-    {
+    if (!few) {                                  // the m best (equal: the lower position): a source per ballot of those that beat it
         const double mine = lane < n_src ? score[lane] : 0.0;
         for (int j = wave; j < n_src; j += NW) {
             const double s = score[j];
             const int rank = __popcll(__ballot(lane < n_src && (mine > s || (mine == s && lane < j))));
             if (lane == 0) gone[j] = g.m == n_src || rank < g.m;
         }
+        __syncthreads();
     }
-    __syncthreads();
     // ---- layout of the next grid: lane k of every wavefront looks at source 2 k and destination 2 k + 1
     const unsigned long long below = (1ull << lane) - 1ull;
     const bool sgone = lane < n_src && gone[lane];
@@ -153,18 +171,50 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
         if (kept_out) kept_out[img_out + of] = kept_in ? kept_in[img + f] : f;
         if (pass_map) pass_map[img + f] = of;
     }
-    // ---- the destinations that take sources in, a wavefront per destination and tensor
-    const int n_abs = __popcll(ln.takes);
-    for (int kk = wave; kk < (xk ? 2 : 1) * n_abs; kk += NW) {
-        const bool on_metric = kk >= n_abs;
-        const int at = on_metric ? kk - n_abs : kk;
-        unsigned long long left = ln.takes;
-        for (int i = 0; i < at; ++i) left &= left - 1;
-        const int k = (int)__builtin_ctzll(left);
-        const unsigned long long hits = ((from_prev >> k) & 1ull) << k | (((from_next >> k) & 1ull) << k) << 1;
-        T* mov = on_metric ? ovk : ov;
-        const int mD = on_metric ? Dk : g.D;
-        lazy_merge<T, PM>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, hits, mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane, 0, mD);
+    if constexpr (HOLD) {
+        // ---- the destinations that take sources in: size-weighted mean in fp64, destination first, rounded once
+        // (the widened tokens of the sums are not kept for it: fp64 copies of whole tokens do not fit)
+#pragma unroll
+        for (int i = 0; i <= kAdjTok; ++i)
+#pragma unroll
+            for (int u = 0; u < P; ++u) asm volatile("" : "+v"(tok[i][u]));
+#pragma unroll
+        for (int o = 0; o < kAdjTok / 2; ++o) {
+            const int p = wave * kAdjTok + 2 * o + 1, k = p >> 1;
+            if (p >= len || !((ln.takes >> k) & 1ull)) continue;
+            const bool prev = (from_prev >> k) & 1ull, next = (from_next >> k) & 1ull;
+            const double sp = (double)sz[p], s1 = prev ? (double)sz[p - 1] : 0.0, s2 = next ? (double)sz[p + 1] : 0.0;
+            T* to = ov + (b * g.cap + g.ov_base + line * g.per_line + __popcll(ln.takes & ((1ull << k) - 1ull))) * g.D;
+            const double S = (sp + s1) + s2, inv = 1.0 / S;
+#pragma unroll
+            for (int u = 0; u < P; ++u) {
+                const int d = (u * 64 + lane) * V;
+                if (d >= g.D) continue;
+                double acc[V];
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    acc[e] = sp * io::at(tok[2 * o + 1][u], e);
+                    if (prev) acc[e] += s1 * io::at(tok[2 * o][u], e);
+                    if (next) acc[e] += s2 * io::at(tok[2 * o + 2][u], e);
+                }
+                lazy_round_store<T>(acc, S, inv, to + d);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    } else {
+        // ---- the same, a wavefront per destination and tensor
+        const int n_abs = __popcll(ln.takes);
+        for (int kk = wave; kk < (xk ? 2 : 1) * n_abs; kk += NW) {
+            const bool on_metric = kk >= n_abs;
+            const int at = on_metric ? kk - n_abs : kk;
+            unsigned long long left = ln.takes;
+            for (int i = 0; i < at; ++i) left &= left - 1;
+            const int k = (int)__builtin_ctzll(left);
+            const unsigned long long hits = ((from_prev >> k) & 1ull) << k | (((from_next >> k) & 1ull) << k) << 1;
+            T* mov = on_metric ? ovk : ov;
+            const int mD = on_metric ? Dk : g.D;
+            lazy_merge<T, PM>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, hits, mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane, 0, mD);
+        }
     }
 }
 
@@ -216,13 +266,19 @@ static luvc_status run_adjacent(const T* x, T* ov, const T* xk, T* ovk, int Dk, 
     const int waves = adjacent_waves(len);
     auto pieces = [](int D) { return (D + 64 * lz_io<T>::V - 1) / (64 * lz_io<T>::V); };
     const int p = pieces(xk ? Dk : g.D), pm = pieces(xk && Dk > g.D ? Dk : g.D);
-#define LUVC_ADJ(P, PM) LUVC_LAUNCH("oim_adjacent_line", (oim_adjacent_line<T, P, PM>), dim3((unsigned)(B * nlines)), dim3(64 * waves), 0, st, x, ov, xk, ovk, Dk, \
-                                idx_in, sizes_in, kept_in, g, idx_out, sizes_out, kept_out, pass_map)
-    if (p == 1 && pm == 1) LUVC_ADJ(1, 1);
-    else if (p == 1) LUVC_ADJ(1, kLzPieces);
-    else if (p == 2 && pm == 2) LUVC_ADJ(2, 2);
-    else if (p == 2) LUVC_ADJ(2, kLzPieces);
-    else LUVC_ADJ(kLzPieces, kLzPieces);
+#define LUVC_ADJ(P, PM, HOLD) LUVC_LAUNCH("oim_adjacent_line", (oim_adjacent_line<T, P, PM, HOLD>), dim3((unsigned)(B * nlines)), dim3(64 * waves), 0, st, x, ov, xk, ovk, Dk, \
+                                      idx_in, sizes_in, kept_in, g, idx_out, sizes_out, kept_out, pass_map)
+    // more wavefronts than 16 per compute unit: several rounds of lines
+    if (!xk && len <= kAdjTok * waves && p <= 3 && (int64_t)B * nlines * waves > 4096) {
+        if (p == 1) LUVC_ADJ(1, 1, true);
+        else if (p == 2) LUVC_ADJ(2, 2, true);
+        else LUVC_ADJ(3, 3, true);
+    }
+    else if (p == 1 && pm == 1) LUVC_ADJ(1, 1, false);
+    else if (p == 1) LUVC_ADJ(1, kLzPieces, false);
+    else if (p == 2 && pm == 2) LUVC_ADJ(2, 2, false);
+    else if (p == 2) LUVC_ADJ(2, kLzPieces, false);
+    else LUVC_ADJ(kLzPieces, kLzPieces, false);
 #undef LUVC_ADJ
     return check_launch("oim pass (adjacent matching, one launch)");
 }

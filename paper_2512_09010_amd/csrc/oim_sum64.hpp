@@ -74,6 +74,21 @@ __device__ __forceinline__ double wave_total64b(double v)
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 0), __builtin_amdgcn_readlane(__double2loint(v), 0));
 }
 
+// the largest value of the wavefront, in every lane (all 64 lanes take part, no NaN)
+__device__ __forceinline__ double wave_max64(double v)
+{
+    v = fmax(v, dpp_get64(v, 0));
+    v = fmax(v, dpp_get64(v, 1));
+    v = fmax(v, dpp_get64(v, 2));                // lane ^ 7: every quad holds its largest by now
+    v = fmax(v, dpp_get64(v, 4));
+    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    v = fmax(__hiloint2double((int)h32[0], (int)l32[0]), __hiloint2double((int)h32[1], (int)l32[1]));
+    const uint32_t lo2 = (uint32_t)__double2loint(v), hi2 = (uint32_t)__double2hiint(v);
+    const auto l16 = __builtin_amdgcn_permlane16_swap(lo2, lo2, false, false), h16 = __builtin_amdgcn_permlane16_swap(hi2, hi2, false, false);
+    return fmax(__hiloint2double((int)h16[0], (int)l16[0]), __hiloint2double((int)h16[1], (int)l16[1]));
+}
+
 }  // namespace
 
 }  // namespace luvc

@@ -346,6 +346,22 @@ def test_few_tokens_row_widths(oracle, dtype, B, H, W, D, passes):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("B,H,W,D,passes", [
+    (43, 25, 24, 16, [(W_AX, 2), (H_AX, 2)]),              # lines of 24 and of an odd 25, last wavefront with one token
+    (36, 21, 30, 520, [(W_AX, 1), (H_AX, 3)]),             # two or three pieces of a row, m at which sources are picked one by one
+    (80, 9, 33, 1032, [(W_AX, 7), (W_AX, 2)]),             # three pieces in bf16, more in fp32; sources ranked by all wavefronts
+    (5, 60, 64, 8, [(W_AX, 2), (H_AX, 2)]),                # sixteen full wavefronts
+])
+def test_few_tokens_in_several_rounds_of_lines(oracle, dtype, B, H, W, D, passes):
+    """More lines than the chip takes at once: tokens stay in registers between the decisions and the merges."""
+    rng = np.random.default_rng(B + H + W + D)
+    x = rng.standard_normal((B, H, W, D)).astype(np.float32)
+    x[0, 1] = x[0, 1, 0]                                   # a row of identical tokens: every choice is a tie
+    x[1, :, 2] = 0.0
+    run_case(oracle, wl.cast_io(x, dtype), dtype, passes, sizes=rng.integers(1, 5, (B, H, W)), tag="several rounds")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,W,D,passes", [
     (1, 12, 100, 640, [(W_AX, 50), (H_AX, 3)]), (1, 12, 100, 640, [(W_AX, 25), (H_AX, 3)]), (1, 12, 100, 640, [(W_AX, 49)]),
     (1, 12, 100, 640, [(W_AX, 2)]), (1, 6, 120, 64, [(W_AX, 60), (W_AX, 0), (H_AX, 3), (W_AX, 2)]), (2, 24, 24, 64, [(W_AX, 12), (H_AX, 6)]),
     (2, 24, 24, 64, [(W_AX, 6), (H_AX, 12)]), (1, 96, 96, 72, [(W_AX, 47), (H_AX, 48)]), (3, 9, 17, 40, [(H_AX, 0), (W_AX, 3), (H_AX, 0)]),
