@@ -18,11 +18,19 @@
 // Two barriers per P pairs; the next pairs' tokens are fetched while B and C run.  A workgroup walks the pairs in steps of
 // the number of workgroups of its sample, so that at any time neighbouring workgroups (same XCD) read neighbouring
 // 4 P-byte pieces of the same cache lines, and keeps the energies in registers until its last pairs are done.
+// An access of a wavefront touches up to 64 / P cache lines and takes the memory path as many cycles and more, so that
+// the next tokens, asked for all at once, fill its queue and the wavefronts stand still before the barrier until it has
+// taken them.  They are asked for a few at a time between the transforms of B and C.  And one cache line in eight is
+// slow (bytes 384 .. 511 of every 1024, wherever a sample starts, seen with row strides of 4, 7 and 8 KB: workgroups that read only
+// those end a fifth later), so a workgroup moves on by kConvTurn places with every step.  us of a call, before, with the
+// turn, and with the parts: bf16 8x700x3584 57, 55, 54; 8x1000x3584 73, 70, 67; 8x1200x3584 106, 106, 98; 4x2000x3584 80, 77, 74;
+// 2x3000x3584 94, 90, 77; 1x5245x3328 149, 149, 122; 1x8000x2048 147, -, 117; 8x2048x3584 91, 84, 75; 4x4096x3584 107, 103, 84; fp32
+// 2x3000x3584 109, -, 79; 4x4096x3584 155, 139, 140.
 // With half of the inputs zero and half of the outputs unwanted (N <= M / 2) passes A and A' take half the loads and skip a
 // butterfly level each.
-// M is the smallest that fits, a power of two or three times one: the longer transform costs its zeros (8x1000x3584 bf16: 152
-// us on 4096 points, 77 on 2048; 8x2048x3584: 208 and 88; 8x700x3584: 76 on 2048, 62 on 1536; 8x1200x3584: 138 on 4096, 110
-// on 3072; 1x5245x3328: 190 on 16384, 160 on 12288).
+// M is the smallest that fits, a power of two or three times one: the longer transform costs its zeros (measured before the tokens
+// were asked for in parts: 8x1000x3584 bf16: 152 us on 4096 points, 77 on 2048; 8x2048x3584: 208 and 88; 8x700x3584: 76 on
+// 2048, 62 on 1536; 8x1200x3584: 138 on 4096, 110 on 3072; 1x5245x3328: 190 on 16384, 160 on 12288).
 //
 // Bound: fp32 vector arithmetic (about 5 M log2 M flops per direction and pair) and the LDS traffic beside it (64 bytes per
 // point and pair).
@@ -192,6 +200,16 @@ __device__ __forceinline__ void twiddled(const cf (&v)[16], const float2* twb, E
     }
 }
 
+// The lane, formed anew in every step of the kernel: the places derived from it are worked out where they are used instead of being
+// kept.  (The step is an operand for the sake of the compiler, which would form the lane once; ID tells the uses of a step apart.)
+template <int ID>
+__device__ __forceinline__ int fresh_lane(int step)
+{
+    int l;
+    asm("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(l) : "s"(step), "n"(ID));
+    return l;
+}
+
 // LDS accesses of one wavefront are served in order: this only keeps the compiler from moving them
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -258,6 +276,16 @@ spu_conv_spectrum(int N, int M, int sigma, int use_hamming, float* __restrict__ 
     }
 }
 
+// Tokens of the next group, of JN, that have been asked for behind a point of a step.  fp32, N = M: from the second point on, there are
+// no registers for them before.
+template <typename T, bool HALF>
+constexpr int conv_part(int point, int points, int JN)
+{
+    if (point == points - 1) return JN;
+    return HALF || sizeof(T) == 2 ? (point + 1) * JN / (points - 1) : point * JN / (points - 1);
+}
+constexpr int kConvTurn = 8;                     // places: a cache line of pairs (P = 4, bf16)
+
 template <typename T, int R, int LB, int P, bool HALF /* N <= M/2: zeros behind the tokens; else N = M */, bool PAIRED /* every pair is one aligned access */>
 __global__ void __launch_bounds__(16 * LB * P)
 spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, int use_hamming,
@@ -273,7 +301,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
     float2* twb = sm + R * LROW;                 // [COLS] (cos, sin)(2 pi i / COLS)
     float* sp = reinterpret_cast<float*>(twb + COLS);              // SPEC_LDS: [R k1][16 i][LB lw]
     __shared__ int flag;
-    const int tid = threadIdx.x, c = tid % P, n2 = tid / P, lane = tid & 63;
+    const int tid = threadIdx.x, c = tid % P, n2 = tid / P, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_tiles = gridDim.x;
     const unsigned item = xcd_contiguous(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
     const int tile = item % n_tiles, b = item / n_tiles;
@@ -281,39 +309,37 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
     const T* xs = x + (int64_t)b * N * row_stride;
     using raw_t = raw_pair<T>;
     raw_t raw[JN];
+    // FRESH: the registers of 1024 threads do not hold the places of a thread in memory and in the grid beside R points.  A place that
+    // is spilled and read back behind a fetch is a wait for the tokens.
+    constexpr bool FRESH = R <= 16 && (!PAIRED || (R == 16 && (LB == 16 || !HALF)));
     // PAIRED: the descriptor ends with the sample's last token (a lane past it, or past D, reads zeros)
     const uint32_t row_bytes = (uint32_t)row_stride * (uint32_t)sizeof(T);
     const uint32_t lane_off = (uint32_t)n2 * row_bytes + (uint32_t)c * 2u * (uint32_t)sizeof(T);
-    auto fetch = [&](int g, auto from, auto to) {
-        constexpr int J0 = decltype(from)::value, J1 = decltype(to)::value;
-        const int d0 = (g * P + c) * 2;
+    auto fetch = [&](auto id, int g, int from, int to) {           // tokens from .. to - 1 of this thread
+        const int l = FRESH ? fresh_lane<decltype(id)::value>(g) : 0, fc = FRESH ? l % P : c, fn2 = FRESH ? wave * (64 / P) + l / P : n2, d0 = (g * P + fc) * 2;
         if constexpr (PAIRED) {
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<T*>(xs) + 2 * P * g, 0, (int)((uint32_t)(N - 1) * row_bytes + (uint32_t)((D - 2 * P * g) * (int)sizeof(T))), 0x00020000);
-            uint32_t off = (d0 < D ? lane_off : 0x80000000u) + (uint32_t)(J0 * COLS) * row_bytes;
+            const uint32_t own = FRESH ? (uint32_t)fn2 * row_bytes + (uint32_t)fc * 2u * (uint32_t)sizeof(T) : lane_off, off = d0 < D ? own : 0x80000000u;
 #pragma unroll
-            for (int j = J0; j < J1; ++j) {
-                raw[j] = raw_t::load(r, off);
-                off += (uint32_t)COLS * row_bytes;
-            }
+            for (int j = 0; j < JN; ++j)
+                if (j >= from && j < to) raw[j] = raw_t::load(r, off + (uint32_t)(j * COLS) * row_bytes);
         } else {
             const bool live = d0 < D, second = d0 + 1 < D;
             const T* p = xs + (live ? d0 : 0);
 #pragma unroll
-            for (int j = J0; j < J1; ++j) {
-                const int n = COLS * j + n2;
+            for (int j = 0; j < JN; ++j) {
+                const int n = COLS * j + fn2;
                 const bool there = live && (!HALF || n < N);
-                raw[j] = there ? raw_t::load(p + (int64_t)n * row_stride, second) : raw_t{};
+                if (j >= from && j < to) raw[j] = there ? raw_t::load(p + (int64_t)n * row_stride, second) : raw_t{};
             }
         }
     };
-    // fp32 tokens, N = M: all of the next group's beside the values of B and C do not fit, the second half follows them
-    // (4x4096x3584: 174 us with spills, 137)
-    constexpr int EARLY = !HALF && sizeof(T) == 4 ? JN / 2 : JN;
-    using first_t = std::integral_constant<int, 0>;
-    using early_t = std::integral_constant<int, EARLY>;
-    using last_t = std::integral_constant<int, JN>;
-    fetch(tile, first_t{}, last_t{});
+    // The next group's tokens are asked for in parts, point by point of a step: 0 after A, three in every iteration of B and C, the
+    // last behind them.
+    constexpr int POINTS = 3 * NIT + 2;
+    auto upto = [&](int point) { return conv_part<T, HALF>(point, POINTS, JN); };
+    fetch(std::integral_constant<int, 10>{}, tile, 0, JN);
 
     // ---- tables: one octant of the circle in fp64, rounded once, the rest by symmetry
     for (int i = tid; i <= M / 8; i += THREADS) {
@@ -371,12 +397,23 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
     for (int j = 0; j < JN; ++j) acc[j] = 0.f;
     __syncthreads();
 
-    float2* col = sm + (n2 + n2 / 16) * P + c;   // this thread's column of the grid
+    float2* kept_col = sm + (n2 + n2 / 16) * P + c;
+    auto column = [&](auto id, int step) {       // this thread's column of the grid
+        if (!FRESH) return kept_col;
+        const int l = fresh_lane<decltype(id)::value>(step), n2 = wave * (64 / P) + l / P;
+        return sm + (n2 + n2 / 16) * P + l % P;
+    };
     tile_tag_t seen = 0;
-    for (int g = tile; g < n_groups; g += n_tiles) {
+    for (int g = tile, round = 0, turned = tile; g < n_groups;) {
+        round += n_tiles;
+        turned = (turned + kConvTurn) % n_tiles;
+        const int next = round + turned;
+        const bool fetches = next < n_groups;
+        auto fetch_part = [&](auto id, int point) { if (fetches) fetch(id, next, point ? upto(point - 1) : 0, upto(point)); };
         // ---- A
-        if (FOLD) asm volatile("" : "+v"(wtop.x), "+v"(wtop.y));         // the products with it are formed where they are used, not kept
+        if (FOLD) asm("" : "+v"(wtop.x), "+v"(wtop.y) : "s"(g), "n"(5));         // the products with it are formed where they are used, not kept
         {
+            float2* col = column(std::integral_constant<int, 1>{}, g);
             cf v[R];
 #pragma unroll
             for (int j = 0; j < JN; ++j) v[j] = raw[j].widen();
@@ -388,48 +425,56 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
                 col[k1 * LROW] = make_float2(r.x, r.y);
             }
         }
-        if (g + n_tiles < n_groups) fetch(g + n_tiles, first_t{}, early_t{});          // in flight during B and C
-        else seen = tiles_look(sy, b, tile, n_tiles);
+        if (!fetches) seen = tiles_look(sy, b, tile, n_tiles);
+        fetch_part(std::integral_constant<int, 11>{}, 0);
         __syncthreads();
         // ---- B, C, spectrum, C', B'
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
-            const int k1 = it * 16 + wrow;
-            if (R % 16 != 0 && (it * 16 + (tid >> 6) * ROWS >= R)) break;          // a whole wavefront: R is a multiple of ROWS
-            float2* row = sm + k1 * LROW + c;
-            int lt = lw;
-            asm volatile("" : "+v"(lt));         // the places of the twiddles are formed here, not kept
+            if (R % 16 != 0 && (it * 16 + wave * ROWS >= R)) {                     // a whole wavefront: R is a multiple of ROWS
+                if (fetches) fetch(std::integral_constant<int, 12>{}, next, upto(3 * it), upto(POINTS - 2));
+                break;
+            }
+            const int l = FRESH ? fresh_lane<3>(g + it) : lane, k1 = FRESH ? it * 16 + wave * ROWS + l / (LB * P) : it * 16 + wrow;
+            int lt = FRESH ? l / P % LB : lw;
+            if (!FRESH) asm volatile("" : "+v"(lt));                     // the places of the twiddles are formed here, not kept
+            const int rl = FRESH ? lt : lw;
+            float2* row = sm + k1 * LROW + (FRESH ? l % P : c);
             cf v[16];
 #pragma unroll
-            for (int a = 0; a < 16; ++a) { const float2 q = row[(a * LB + a * LB / 16 + lw) * P]; v[a] = {q.x, q.y}; }
+            for (int a = 0; a < 16; ++a) { const float2 q = row[(a * LB + a * LB / 16 + rl) * P]; v[a] = {q.x, q.y}; }
             fft16<false>(v);
-            twiddled<false, R <= 16 ? 4 : 8>(v, twb, [&](int ka) { return ka * lt; }, [&](int ka, cf r) { row[(ka * LB + ka * LB / 16 + lw) * P] = make_float2(r.x, r.y); });
+            twiddled<false, R <= 16 ? 4 : 8>(v, twb, [&](int ka) { return ka * lt; }, [&](int ka, cf r) { row[(ka * LB + ka * LB / 16 + rl) * P] = make_float2(r.x, r.y); });
             wave_lds_fence();
+            fetch_part(std::integral_constant<int, 13>{}, 3 * it + 1);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) { const float2 q = row[(17 * lw + i) * P]; v[i] = {q.x, q.y}; }
+            for (int i = 0; i < 16; ++i) { const float2 q = row[(17 * rl + i) * P]; v[i] = {q.x, q.y}; }
             if constexpr (LB == 16) fft16<false>(v);
             else { fft8<false>(v); fft8<false>(v + 8); }
 #pragma unroll
             for (int kb = 0; kb < 16; ++kb) {
-                const float w = SPEC_LDS ? sp[(k1 * 16 + kb) * LB + lw] : wr[it % (SPEC_LDS ? 1 : NIT)][kb];
+                const float w = SPEC_LDS ? sp[(k1 * 16 + kb) * LB + rl] : wr[it % (SPEC_LDS ? 1 : NIT)][kb];
                 v[kb] = {v[kb].x * w, v[kb].y * w};
             }
+            fetch_part(std::integral_constant<int, 14>{}, 3 * it + 2);
             if constexpr (LB == 16) fft16<true>(v);
             else { fft8<true>(v); fft8<true>(v + 8); }
-            twiddled<true, R <= 16 ? 4 : 8>(v, twb, [&](int i) { return LB == 16 ? i * lt : (i & 7) * (2 * lt + (i >> 3)); }, [&](int i, cf r) { row[(17 * lw + i) * P] = make_float2(r.x, r.y); });
+            twiddled<true, R <= 16 ? 4 : 8>(v, twb, [&](int i) { return LB == 16 ? i * lt : (i & 7) * (2 * lt + (i >> 3)); }, [&](int i, cf r) { row[(17 * rl + i) * P] = make_float2(r.x, r.y); });
             wave_lds_fence();
+            fetch_part(std::integral_constant<int, 15>{}, 3 * it + 3);
 #pragma unroll
-            for (int ka = 0; ka < 16; ++ka) { const float2 q = row[(ka * LB + ka * LB / 16 + lw) * P]; v[ka] = {q.x, q.y}; }
+            for (int ka = 0; ka < 16; ++ka) { const float2 q = row[(ka * LB + ka * LB / 16 + rl) * P]; v[ka] = {q.x, q.y}; }
             fft16<true>(v);
 #pragma unroll
-            for (int a = 0; a < 16; ++a) row[(a * LB + a * LB / 16 + lw) * P] = make_float2(v[a].x, v[a].y);
+            for (int a = 0; a < 16; ++a) row[(a * LB + a * LB / 16 + rl) * P] = make_float2(v[a].x, v[a].y);
         }
         __syncthreads();
-        if (EARLY < JN && g + n_tiles < n_groups) fetch(g + n_tiles, early_t{}, last_t{});
+        fetch_part(std::integral_constant<int, 16>{}, POINTS - 1);
         // ---- A'
-        if (FOLD) asm volatile("" : "+v"(wtop.x), "+v"(wtop.y));
+        if (FOLD) asm("" : "+v"(wtop.x), "+v"(wtop.y) : "s"(g), "n"(6));
         {
             cf v[R];
+            const float2* col = column(std::integral_constant<int, 2>{}, g);
             { const float2 q = col[0]; v[0] = {q.x, q.y}; }
 #pragma unroll
             for (int k1 = 1; k1 < R; ++k1) { const float2 q = col[k1 * LROW]; v[k1] = cmul(cf{q.x, q.y}, tw_a(k1)); }
@@ -437,6 +482,7 @@ spu_conv(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma, i
 #pragma unroll
             for (int j = 0; j < JN; ++j) acc[j] = fmaf(v[j].x, v[j].x, fmaf(v[j].y, v[j].y, acc[j]));
         }
+        g = next;
     }
     tiles_claim(sy, b, tile, n_tiles, seen);
     // ---- Eq. 8: over the P pairs of a thread group, then across the workgroups of the sample
