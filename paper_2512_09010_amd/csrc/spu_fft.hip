@@ -22,7 +22,7 @@
 // N floats per tile is written.
 // Bound: fp32 vector arithmetic, about 900 instructions per wavefront and subsequence.  With the twiddles between the sides
 // as multiplications of their own, and the accumulation's looked up per subsequence, it was 1160: 8x1024x3584 bf16 49 us
-// (42 now), 16x720x4096 72 (60), 4x2048x3584 47 (45), 8x1440x3584 fp32 76 (70), on tokens whose norms vary by region.
+// (40 now), 16x720x4096 72 (57), 4x2048x3584 47 (43), 8x1440x3584 fp32 76 (65), on tokens whose norms vary by region.
 //
 // What it gave up: an inverse on every second or fourth subsequence, with the energies between interpolated from the band
 // limit.  On tokens of even energy, merged tokens through a random projection, it took 42.8 us for 8x1024x3584 bf16
@@ -255,15 +255,22 @@ spu_fft16q(const T* __restrict__ x, int N, int D, int64_t row_stride, int sigma,
 #pragma unroll
             for (int kb = 0; kb < 16; ++kb) wk[kb] = bin_turn(kb);
         }
+        // The next subsequence is in flight while the bin side works on this one.  Asked for before the token side's transform, its
+        // Q requests stood in the way of that side's start: 32x1152x1152 bf16 59.5 us (58.5 here), 4x2048x3584 43.8 (42.7),
+        // 2x2880x2048 52.4 (51.6), 8x1440x3584 55.7 (55.2), 8x1024x3584 39.7 (39.6); and with fp32 tokens and Q = 15 it took the
+        // registers of the third wavefront per SIMD: 8x1440x3584 69.1 (64.5), 16x720x4096 74.0 (68.0).  The other fp32 kernels,
+        // whose tokens take twice the time, want them early: late, 32x1152x1152 took 68.0 (66.7), 8x1024x3584 49.0 (47.2).
+        constexpr bool kEarly = sizeof(T) == 4 && Q != 15;
         // The last subsequence comes first and starts the sums: its pass is a copy of the loop body without them.
         auto forward = [&](int n2, auto first) {
             cf u[Q];
 #pragma unroll
             for (int j = 0; j < Q; ++j) u[j] = pio::widen(raw[j]);
-            if (n2 > 0) load_sub(n2 - 1);        // next subsequence in flight while this one is transformed
+            if (kEarly && n2 > 0) load_sub(n2 - 1);
             dftq<Q, false>::run(u);              // over j -> a
 #pragma unroll
             for (int i = 0; i < Q; ++i) xbuf[i * kRowPad + r * kPairs + c] = make_float2(u[i].x, u[i].y);
+            if (!kEarly && n2 > 0) load_sub(n2 - 1);
             __syncthreads();
             cf v[16];
             if (bins) {
