@@ -22,10 +22,13 @@
 // words of a workgroup only if it holds 32 RT different right values in a row: a constant fill never does.
 //
 // Bound: matrix cores for N near kCircMaxN (6 N^2 D flops per bf16 sample, 12 for fp32), latency for short samples.
-// 1x729x3584 bf16: 20.5 us (2048-point transform: 24), 8x205x3584: 13.9, 4x144x4096: 9.2, 4x861x1408: 33.6.  Rows of odd width,
+// 1x729x3584 bf16: 18.1 us (2048-point transform: 22), 8x205x3584: 12.8, 4x144x4096: 8.4, 4x861x1408: 31.3.  Rows of odd width,
 // stride or start, channel by channel: 16x64x3585 bf16 11.6 us (1536-point transform: 102), 8x205x3585 15.8 (62), fp32 24
 // (64), 1x64x65 5.0 (14.8), but 1x729x3585 26.7 (22.3).  Laying out the
-// taps costs about 1 us less than with a division per angle and a copy at a time: 1x512x3584 13.9 -> 12.6.
+// taps costs about 1 us less than with a division per angle and a copy at a time: 1x512x3584 13.9 -> 12.6; and another .5 to 1 us
+// less with the angles put together (spu_taps.hpp), every tap written straight to its places in the line instead of by way
+// of a list of p, and the first fetches spread over these phases: 1x729x3584 19.1 -> 18.1, 1x1000x1024 14.8 -> 13.8,
+// 4x144x4096 9.0 -> 8.4, fp32 1x144x4096 9.6 -> 9.1.  The start, until the first product, is 3 us of those.
 #include "common.hpp"
 #include "spu.hpp"
 #include "spu_taps.hpp"
@@ -129,10 +132,10 @@ template <bool PAIRED> struct circ_raw<float, PAIRED> {
 // the tag of the words of a group's token `row`
 __device__ __forceinline__ uint32_t circ_tag(uint32_t tag, int row) { return tag + (uint32_t)row * 0x9E3779B1u; }
 
-// LDS: taps [3 terms][8 displacements] of circ_stride bytes, 32 mod 256; the taps once more, undisplaced; p itself
+// LDS: taps [3 terms][8 displacements] of circ_stride bytes, 32 mod 256; the taps once more, undisplaced
 __host__ __device__ inline int circ_taps(int N, int RT) { return (N + 15) / 16 * 16 + 32 * RT + 8; }
 __host__ __device__ inline int circ_stride(int N, int RT) { return ((circ_taps(N, RT) + 8) * 2 + 223) / 256 * 256 + 32; }
-__host__ __device__ inline int circ_lds(int N, int RT) { return 24 * circ_stride(N, RT) + 3 * 2 * (circ_taps(N, RT) + 16) + 3 * 2 * (N / 2 + 2); }
+__host__ __device__ inline int circ_lds(int N, int RT) { return 24 * circ_stride(N, RT) + 3 * 2 * (circ_taps(N, RT) + 16); }
 
 }  // namespace
 
@@ -184,36 +187,49 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
 #pragma unroll
         for (int j = 0; j < 8; ++j) r.fetch(j, rx, lane_off + at + (uint32_t)j * row_bytes, lane_off1 + at + (uint32_t)j * row_bytes);
     };
+    // asked for in three parts, between the phases of the taps: all at once they are .6 us in which nothing else starts
+    constexpr int PF1 = (PF + 2) / 3, PF2 = (2 * PF + 2) / 3;
 #pragma unroll
-    for (int u = 0; u < PF; ++u) fetch(raw[u], k0 + u);
+    for (int u = 0; u < PF1; ++u) fetch(raw[u], k0 + u);
 
-    // ---- taps: p[0 .. N/2] in fp64, split into three bf16 terms; entry o of the line of taps is p[o - n0 - ROWS]
+    // ---- taps: p[0 .. N/2] in fp64, split into three bf16 terms, to every place of the line of taps where they belong: entry o of
+    // the line is p[o - n0 - ROWS].  p is even and repeats after N, so also after `turn`, N or a multiple of it that is 64 at least
+    // and leaves a thread few places.
     const int taps = circ_taps(N, RT), stride = circ_stride(N, RT);
     uint16_t* line = reinterpret_cast<uint16_t*>(smem + 24 * stride);          // [3][taps + 16]
-    uint16_t* base = line + 3 * (taps + 16);                                   // [3][N / 2 + 2]
+    double2* angles = reinterpret_cast<double2*>(smem);                        // where the displaced taps will lie
+    SpuTaps::fill_angles<THREADS>(angles, N, sigma);
+#pragma unroll
+    for (int u = PF1; u < PF2; ++u) fetch(raw[u], k0 + u);
+    __syncthreads();
     {
-        const SpuTaps p(N, sigma, use_hamming);
-        for (int j = tid; j <= N / 2; j += THREADS) {
-            double v = p(j);
+        const SpuTaps p(N, sigma, use_hamming, angles);
+        const int turn = N >= 64 ? N : N * (63 / N + 1), zero = (n0 + ROWS) % turn;
+        for (int jj = tid; jj <= turn / 2; jj += THREADS) {
+            int j = jj;
+            if (N < 64) {
+                j = jj % N;
+                j = 2 * j > N ? N - j : j;
+            }
+            double v = p(j, angles);
+            uint16_t b[3];
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
-                const uint16_t b = f64_to_bf16(v);
-                base[t * (N / 2 + 2) + j] = b;
-                v -= (double)bf16_to_f32(b);
+                b[t] = f64_to_bf16(v);
+                v -= (double)bf16_to_f32(b[t]);
             }
+            const int up = zero + jj, down = zero - jj;
+            auto put = [&](int at) {
+                for (; at < taps + 16; at += turn)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) line[t * (taps + 16) + at] = b[t];
+            };
+            put(up >= turn ? up - turn : up);
+            put(down < 0 ? down + turn : down);
         }
     }
-    __syncthreads();
-    const float inv_n = 1.f / (float)N;
-    for (int i = tid; i < taps + 16; i += THREADS) {
-        const int at = i - n0 - ROWS;
-        int j = at - (int)floorf((float)at * inv_n) * N;           // modulo N, the quotient off by one at most
-        j += j < 0 ? N : 0;
-        j -= j >= N ? N : 0;
-        j = 2 * j > N ? N - j : j;
 #pragma unroll
-        for (int t = 0; t < 3; ++t) line[t * (taps + 16) + i] = base[t * (N / 2 + 2) + j];
-    }
+    for (int u = PF2; u < PF; ++u) fetch(raw[u], k0 + u);
     __syncthreads();
     // a thread: 16 taps of a term, out of which 8 of every displaced copy
     const int eights = taps / 8;

@@ -4,6 +4,10 @@
 // The window is a sum of three exponentials in f, so p is a sum of three Dirichlet kernels and needs no sum over f:
 //     N p[j] = 0.54 D(u) + 0.23 D(u + d) + 0.23 D(u - d),   u = j / N,  d = 1 / (N - 1),  D(v) = sin((2 sigma + 1) pi v) / sin(pi v),
 // less M[sigma] (-1)^j where 2 sigma = N: the bins sigma and -sigma are then one bin, which D counts twice.
+//
+// The angles of j = 16 a + b are put together from those of 16 a and of b: some hundred angles, one evaluation per thread of
+// a workgroup, and a few products per p[j].  With two evaluations per p[j], one after the other, and one more for the
+// constants, the taps were ready .6 us later.  The sums of angles are good to a few 2^-53, taps are used to 24 bits.
 #pragma once
 #include "common.hpp"
 
@@ -11,43 +15,62 @@ namespace luvc {
 
 namespace {
 
-// for 1 <= N <= 4096, built and called by whole wavefronts
+// for 1 <= N <= 4096
 struct SpuTaps {
     int N, sigma;
     bool hamming;
-    double sd, cd, sKd, cKd;         // sin, cos of pi d and of (2 sigma + 1) pi d
-    double sv, sKv;                  // sin of pi v and of (2 sigma + 1) pi v, v = d - 1 / N = 1 / (N (N - 1))
+    double sd, cd, sKd, cKd;         // sin, cos of pi d and of K pi d, K = 2 sigma + 1
+    double sv, sKv;                  // sin of pi v and of K pi v, v = d - 1 / N = 1 / (N (N - 1))
     double inv;                      // 1 / N
 
-    // Four angles, one evaluation: a lane takes one of them.
-    __device__ __forceinline__ SpuTaps(int N_, int sigma_, int use_hamming) : N(N_), sigma(sigma_), hamming(use_hamming && N_ > 2)
+    // (sin, cos) of pi times: d, v, K d, K v; then j / N and K j / N in turn for j = 0 .. 15, then for j = 0, 16, ..., N / 2
+    static constexpr int kHead = 4;
+    static __host__ __device__ constexpr int angles_count(int N) { return kHead + 32 + 2 * (N / 32 + 1); }
+    template <int THREADS>
+    static __device__ __forceinline__ void fill_angles(double2* angles, int N, int sigma)
+    {
+        const int K = 2 * sigma + 1, turn = 2 * N;
+        for (int i = threadIdx.x; i < angles_count(N); i += THREADS) {
+            double a;
+            if (i < kHead) {
+                a = (double)((i & 2) ? K : 1) / (N > 1 ? (double)((i & 1) ? N * (N - 1) : N - 1) : 1.0);
+            } else {
+                const int q = i - kHead, j = q < 32 ? q >> 1 : 16 * ((q - 32) >> 1);
+                int r = j;
+                if (q & 1) {                     // K j mod 2 N: K j is below 2^24, the quotient off by one at most
+                    r = K * j - (int)((float)(K * j) / (float)turn) * turn;
+                    r += r < 0 ? turn : 0;
+                    r -= r >= turn ? turn : 0;
+                }
+                a = (double)r / (double)N;
+            }
+            double s, c;
+            sincospi(a, &s, &c);
+            angles[i] = make_double2(s, c);
+        }
+    }
+
+    // angles: filled, and a barrier passed
+    __device__ __forceinline__ SpuTaps(int N_, int sigma_, int use_hamming, const double2* angles) : N(N_), sigma(sigma_), hamming(use_hamming && N_ > 2)
     {
         // N <= 2: the window is 1 at every bin
         sd = sKd = sv = sKv = 0.0;
         cd = cKd = 1.0;
         inv = 1.0 / (double)N;
         if (hamming) {
-            const int lane = threadIdx.x & 63;
-            double s, c, a = 1.0 / (double)(N - 1);
-            if (lane & 1) a *= inv;
-            if (lane & 2) a *= (double)(2 * sigma + 1);
-            sincospi(a, &s, &c);
-            sd = of_lane(s, 0); cd = of_lane(c, 0); sv = of_lane(s, 1);
-            sKd = of_lane(s, 2); cKd = of_lane(c, 2); sKv = of_lane(s, 3);
+            const double2 d1 = angles[0], v1 = angles[1], dK = angles[2], vK = angles[3];
+            sd = d1.x; cd = d1.y; sv = v1.x;
+            sKd = dK.x; cKd = dK.y; sKv = vK.x;
         }
     }
     // p[j], 0 <= j <= N / 2
-    __device__ __forceinline__ double operator()(int j) const
+    __device__ __forceinline__ double operator()(int j, const double2* angles) const
     {
-        const int K = 2 * sigma + 1, turn = 2 * N;
-        // K j mod 2 N: below 2^24, the quotient is off by one at most
-        int r = K * j - (int)((float)(K * j) * (0.5f * (float)inv)) * turn;
-        r += r < 0 ? turn : 0;
-        r -= r >= turn ? turn : 0;
-        double s1, c1, sK, cK;
-        sincospi((double)j * inv, &s1, &c1);
-        sincospi((double)r * inv, &sK, &cK);
-        const double num = j == 0 ? (double)K : sK, den = j == 0 ? 1.0 : s1;        // D(u)
+        const double2* t = angles + kHead;
+        const double2 b1 = t[2 * (j & 15)], bK = t[2 * (j & 15) + 1], a1 = t[32 + 2 * (j >> 4)], aK = t[32 + 2 * (j >> 4) + 1];
+        const double s1 = a1.x * b1.y + a1.y * b1.x, c1 = a1.y * b1.y - a1.x * b1.x;
+        const double sK = aK.x * bK.y + aK.y * bK.x, cK = aK.y * bK.y - aK.x * bK.x;
+        const double num = j == 0 ? (double)(2 * sigma + 1) : sK, den = j == 0 ? 1.0 : s1;        // D(u)
         double p;
         if (hamming) {
             const double np = sK * cKd + cK * sKd, dp = s1 * cd + c1 * sd;
@@ -60,13 +83,6 @@ struct SpuTaps {
             p -= (j & 1) ? -w : w;
         }
         return p * inv;
-    }
-
-private:
-    __device__ static __forceinline__ double of_lane(double v, int lane)
-    {
-        const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane), hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-        return __hiloint2double(hi, lo);
     }
 };
 

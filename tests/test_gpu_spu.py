@@ -346,6 +346,17 @@ def test_score_as_a_circulant_product(oracle, dtype, B, N, D, sigma):
     score_case(oracle, x, dtype, sigma, False, "circulant-rect", stride_pad=10)
 
 
+@pytest.mark.parametrize("lengths", [range(1, 24), range(24, 48), range(48, 70), (95, 96, 97, 159, 160, 161, 511, 512, 993, 1007, 1008, 1009)])
+def test_circulant_taps_of_every_short_length(oracle, lengths):
+    """Taps are written to all their places in a line that is longer than the sample; below 64 tokens it repeats after a multiple of
+    them.  Angles are put together from those of 16 a and b: lengths around multiples of 16."""
+    for N in lengths:
+        rng = np.random.default_rng(N)
+        x = wl.cast_io(rng.standard_normal((2, N, 10)).astype(np.float32), "f32")
+        for sigma in {0, N // 5, N // 2}:
+            score_case(oracle, x, "f32", sigma, True, "circulant-taps")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,D", [(64, 256), (130, 256), (130, 200), (300, 256)])
 def test_circulant_scores_of_narrow_rows_round_little(oracle, dtype, N, D):
