@@ -20,9 +20,15 @@
 //
 // Decisions are fp64 decisions reached in two steps, as in the single-pass kernel: a screening
 // sweep in fp32 with a rigorous error bound, and a repeat in fp64 of whatever is closer than the
-// bound.  In the first pass the repeat is local to a wavefront; in the second pass it is taken by
-// the whole workgroup, because the sums of a decision live in two wavefronts.  A source shared by
+// bound.  In the first pass the repeat is local to a wavefront; in the second pass the sums of a
+// decision may live in two wavefronts, which then both put theirs in LDS.  A source shared by
 // two workgroups is decided from the same bits by the same expressions in both.
+//
+// Bound: memory, while tokens come in (8 x 64 x 64 x 1280 bf16: 84 MB in 20 us), and then the wait for the last of them.  The
+// older wavefronts of a workgroup get their tokens first, the youngest as they come to 20 us.  A wavefront therefore
+// waits only for its two neighbours (`stage`), not at barriers for all: the merges and stores of the older ones run
+// while the younger ones' tokens are on their way: a call of 34.5 us takes 30.5 (32 x 64 x 64 x 384 61.5 -> 54.8; 80 x 24 x 24 x
+// 1024, workgroups of 6 wavefronts, 35.9 -> 34.7; 128 x 16 x 16 x 1152, of 4, the same).
 //
 // The merge is the size-weighted mean evaluated in fp64 in position order and rounded once.  One
 // case needs no fp64: bf16 storage, one absorbed source, equal sizes.  Then the mean is (b + x) / 2
@@ -59,7 +65,7 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     __shared__ float inv32[kRows], dt32[kRows];                   // 1/|T[r]|, <T[r], T[r+1]> of the intermediate tokens
     __shared__ double inv64[kRows], dt64[kRows];
     __shared__ int szl[kRows];
-    __shared__ int redo;
+    __shared__ int stage[NW];                                     // what a wavefront has written: 1 its first token, 2 inv32, dt32 and szl, 3 inv64 and dt64
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -99,7 +105,15 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     constexpr int kE = N * (words<T>::per == 2 ? 2 : 1) + 6;
     const float tau = (float)(6 * kE + 20) * 5.9604645e-8f;
     const int tok_bytes = g.D * (int)sizeof(T);
-    if (threadIdx.x == 0) redo = 0;
+    if (threadIdx.x < NW) stage[threadIdx.x] = 0;
+    auto reached = [&](int v) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0) __hip_atomic_store(stage + w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto wait_for = [&](int other, int v) {
+        while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(stage + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < v) {}
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
 
     // ------------------------------------------------------------------ first pass: four intermediate tokens
     const int pa = 2 * j, pb = pa + 1, pc = pa + 2;
@@ -114,20 +128,27 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
 #pragma unroll 4
     for (int k = 0; k < 4; ++k) {
         const int r = r0 + k;
-        TokT Tn;
-        int sn = 0;
-        if (active && r >= row_lo && r <= row_end) {
+        TokT Tn, A, Bt, C, Lt, Rt;
+        int sn = 0, sa_in = 1, sb = 1, sc_in = 1;
+        const bool there = active && r >= row_lo && r <= row_end;
+        if (there) {
             const int64_t t0 = img_in + (int64_t)r * g.sB;        // token of position 0 on this line
             const int64_t ta = t0 + (int64_t)pa * g.sA, tb = t0 + (int64_t)pb * g.sA, tc = t0 + (int64_t)pc * g.sA;
-            TokT A, Bt, C, Lt, Rt;
             load_tok(A, x + ta * g.D, tok_bytes, lane);
             load_tok(Bt, x + tb * g.D, tok_bytes, lane);
             load_tok(C, x + (has_c ? tc : tb) * g.D, tok_bytes, lane, has_c);
             load_tok(Lt, x + (has_l ? ta - g.sA : tb) * g.D, tok_bytes, lane, has_l);
             load_tok(Rt, x + (has_r ? tc + g.sA : tb) * g.D, tok_bytes, lane, has_r);
-            const int sb = sizes_in ? sizes_in[tb] : 1;
-            const int sa_in = sizes_in ? sizes_in[ta] : 1;
-            const int sc_in = (sizes_in && has_c) ? sizes_in[tc] : 1;
+            sb = sizes_in ? sizes_in[tb] : 1;
+            sa_in = sizes_in ? sizes_in[ta] : 1;
+            sc_in = (sizes_in && has_c) ? sizes_in[tc] : 1;
+        }
+        if (k == 0) {                                             // `stage` is cleared for everyone before it is used; the first tokens are on their way
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        }
+        if (there) {
             // screening: every sum is formed lower position first, so the sum two workgroups share has the same bits
             // (tokens that are not there were loaded as zeros: their sums are zero and never looked at)
             float sm[8] = {dot32_lane<T>(A, A), dot32_lane<T>(Bt, Bt), dot32_lane<T>(A, Bt), dot32_lane<T>(Lt, A),
@@ -162,22 +183,24 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         s0 = s1; s1 = s2; s2 = s3; s3 = sn;
     }
 
+    if (!active) return;
+
     // ------------------------------------------------------------------ second pass: exchange
     if (is_main) {
 #pragma unroll
         for (int i = 0; i < N; ++i) lds_tok[(w * N + i) * 64 + lane] = T0.w[i];
     }
-    __syncthreads();
+    reached(1);
+    const int above = is_halo ? -1 : w > 0 ? w - 1 : u0 > 0 ? nwm : -1, below = is_halo ? 0 : w + 1;
     TokT Tx;                                                      // the token after T3: first token of the next wavefront
-    const bool has_x = active && r0 + 4 <= row_end;
-    if (has_x) {
-        const int nxt = is_halo ? 0 : w + 1;
+    if (r0 + 4 <= row_end) {
+        wait_for(below, 1);
 #pragma unroll
-        for (int i = 0; i < N; ++i) Tx.w[i] = lds_tok[(nxt * N + i) * 64 + lane];
+        for (int i = 0; i < N; ++i) Tx.w[i] = lds_tok[(below * N + i) * 64 + lane];
     } else {
         zero_tok(Tx);
     }
-    if (active) {
+    {
         float sm[8] = {dot32_lane<T>(T0, T0), dot32_lane<T>(T1, T1), dot32_lane<T>(T2, T2), dot32_lane<T>(T3, T3),
                        dot32_lane<T>(T0, T1), dot32_lane<T>(T1, T2), dot32_lane<T>(T2, T3), dot32_lane<T>(T3, Tx)};
         wave_total32x8(sm, lane);
@@ -191,48 +214,38 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
             }
         }
     }
-    __syncthreads();
+    reached(2);
+    const bool e2 = is_main && r0 + 2 <= row_end, e4 = r0 + 4 <= row_end;
+    if (above >= 0) wait_for(above, 2);
+    if (e4) wait_for(below, 2);
     // a source at intermediate row r (LDS index q) goes UP (to the lower position) unless the row below is strictly more similar
     auto verdict32 = [&](int r, int q) -> int {
         const bool has_up = r >= 1, has_dn = r + 1 < g.L2;
         const int qm = q > 0 ? q - 1 : 0;
         return screen_source(has_up, has_dn, inv32[q], dt32[qm], inv32[qm], dt32[q], inv32[q + 1], tau);
     };
-    auto decide64 = [&](int r, int q) -> bool {
-        const bool has_up = r >= 1, has_dn = r + 1 < g.L2;
-        const int qm = q > 0 ? q - 1 : 0;
-        return source_goes_left(has_up, has_dn, inv64[q], dt64[qm], inv64[qm], dt64[q], inv64[q + 1]);
-    };
-    const bool e2 = r0 + 2 <= row_end, e4 = r0 + 4 <= row_end;
-    int v0 = -1, v2 = -1, v4 = -1;
-    if (is_main) {
-        v0 = verdict32(r0, rr0);
-        if (e2) v2 = verdict32(r0 + 2, rr0 + 2);
-        if (e4) v4 = verdict32(r0 + 4, rr0 + 4);
-        if ((v0 == 0 || v2 == 0 || v4 == 0) && lane == 0) redo = 1;
-    }
-    __syncthreads();
+    const int v0 = is_main ? verdict32(r0, rr0) : -1, v2 = e2 ? verdict32(r0 + 2, rr0 + 2) : -1, v4 = e4 ? verdict32(r0 + 4, rr0 + 4) : -1;
     bool up0 = v0 > 0, up2 = v2 > 0, up4 = v4 > 0;
-    if (redo) {                                                   // uniform over the workgroup
-        if (active) {
-            double n[5], d[4];
-            chain_sums64<T>(T0, T1, T2, T3, Tx, n, d);
-            if (lane < 4) {
-                const int k = lane, r = r0 + k;
-                if (r >= row_lo && r <= row_end) {
-                    inv64[rr0 + k] = inv_norm64(k == 0 ? n[0] : k == 1 ? n[1] : k == 2 ? n[2] : n[3]);
-                    dt64[rr0 + k] = k == 0 ? d[0] : k == 1 ? d[1] : k == 2 ? d[2] : d[3];
-                }
+    if (v0 == 0 || v2 == 0 || v4 == 0) {                          // too close for fp32: fp64 decides
+        double n[5], d[4];
+        chain_sums64<T>(T0, T1, T2, T3, Tx, n, d);
+        if (lane < 4) {
+            const int k = lane, r = r0 + k;
+            if (r >= row_lo && r <= row_end) {
+                inv64[rr0 + k] = inv_norm64(k == 0 ? n[0] : k == 1 ? n[1] : k == 2 ? n[2] : n[3]);
+                dt64[rr0 + k] = k == 0 ? d[0] : k == 1 ? d[1] : k == 2 ? d[2] : d[3];
             }
         }
-        __syncthreads();
-        if (is_main) {
-            up0 = decide64(r0, rr0);
-            up2 = e2 && decide64(r0 + 2, rr0 + 2);
-            up4 = e4 && decide64(r0 + 4, rr0 + 4);
-        }
+        reached(3);
+        auto decide64 = [&](int q) { return source_goes_left(true, true, inv64[q], dt64[q - 1], inv64[q - 1], dt64[q], inv64[q + 1]); };
+        // the wavefront on the other side of the line has the same verdict of v0, of v4 from the same bits, and comes here as well
+        if (v0 == 0) wait_for(above, 3);
+        if (v4 == 0) wait_for(below, 3);
+        if (v0 == 0) up0 = decide64(rr0);
+        if (v2 == 0) up2 = decide64(rr0 + 2);
+        if (v4 == 0) up4 = decide64(rr0 + 4);
     }
-    if (!is_main) return;
+    if (is_halo) return;
 
     // ------------------------------------------------------------------ second pass: merge, write, maps
     const int own_end = row_base + 2 * nseg;                      // rows below it belong to the next run ...

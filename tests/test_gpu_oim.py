@@ -136,6 +136,25 @@ def test_pair_close_calls(oracle):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,W,D", [
+    (1, 64, 6, 40), (3, 61, 10, 24), (1, 24, 24, 32), (1, 64, 64, 16),      # short runs, with a wavefront for the row above
+    (4, 64, 64, 16), (2, 112, 112, 16), (6, 40, 72, 16),                    # as many runs as compute units, or one per line
+    (5, 64, 104, 16), (33, 16, 16, 16), (1, 12, 80, 1032),                  # uncut lines of 16 and 4 wavefronts, wide tokens
+])
+def test_pair_decisions_shared_by_wavefronts(oracle, dtype, B, H, W, D):
+    """A source between two wavefronts is decided by both; where fp32 cannot tell they exchange fp64 sums.  Lines of which some
+    pieces are near-duplicates, equal or zero and others clear make some wavefronts go that way beside others that do not."""
+    rng = np.random.default_rng(H * 131 + W)
+    x = rng.standard_normal((B, H, W, D)).astype(np.float32)
+    base = rng.standard_normal((1, 1, 1, D)).astype(np.float32)
+    rows = np.repeat(rng.integers(0, 4, (B, (H + 2) // 3, 1, 1)), 3, axis=1)[:, :H]
+    x = np.where(rows == 1, base + 1e-3 * x, np.where(rows == 2, np.broadcast_to(base, x.shape), np.where(rows == 3, x * (rng.random((B, H, W, 1)) < 0.5), x)))
+    x = wl.cast_io(x.astype(np.float32), dtype)
+    for order in ("WH", "HW"):
+        run_case(oracle, x, dtype, _halving(H, W, order), tag="shared decisions " + order)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_smooth_field_general_m(oracle, dtype):
     rng = np.random.default_rng(77)
     x = wl.cast_io(wl.smooth_field(rng, 2, 12, 14, 96, 2.0), dtype)
