@@ -373,27 +373,39 @@ struct PairPlan { int segs, seg_out, waves; };
 // two rows below (one more wavefront at most) and the single-row wavefront above.
 PairPlan plan_pair(int L2, int nw, int64_t lines)
 {
-    const int nd2 = L2 / 2;
-    PairPlan p;
-    // A grid with fewer line positions than the chip has CUs would leave most of it idle with one workgroup
-    // per position: cut the lines into runs of 8 outputs then (measured on 2 x 112 x 112, 56 x 56 and
-    // 28 x 28 grids: 64 us for the three calls against 78; runs of 2, 6 or 14 gain less).
-    const int forced = (lines < 256 && nd2 > 8) ? 8 : 0;
-    if ((L2 + 3) / 4 <= nw && forced <= 0) {
-        p.segs = 1;
-        p.seg_out = nd2;
-        p.waves = (L2 + 3) / 4;
-        return p;
-    }
+    const int nd2 = L2 / 2, uncut = (L2 + 3) / 4;
     int cap = 2 * (nw - 1) - 1;                    // (2 * seg_out + 2 + 3) / 4 + 1 <= nw
     if (cap & 1) --cap;                            // even: workgroups start on a multiple of four rows
     if (cap < 2) cap = 2;
-    if (forced > 0 && forced < cap) cap = forced + (forced & 1);
+    // A grid with fewer line positions than the chip has CUs would leave most of it idle with one workgroup per position.
+    // The best cut is the finest that leaves a CU one workgroup: 2 x 112 x 112 x 1280 bf16 in runs of 28 26.1 us (8: 30.2,
+    // 14: 30.8), 4 x 64 x 64 x 1024 in 16s 16.8 (8: 18.1, uncut 22.7), 1 x 64 x 64 x 1280 in 4s 13.8 (8: 14.3, 2: 16.2),
+    // 2 x 28 x 28 in 2s 11.7 (8: 12.3), fp32 1 x 24 x 24 x 1024 in 2s 10.4 (6: 10.9); lines of up to
+    // 8 outputs gain nothing (1 x 16 x 16 x 1024 9.5, in 2s 9.7).  Where that would leave more than a
+    // quarter of the CUs without one, or is not to be had, runs of 8: 5 x 56 x 56 x 1152 21.9 (uncut, 140 workgroups, 23.5),
+    // 3 x 112 x 112 x 1280 42.9 (50.6), fp32 1 x 112 x 112 x 768 16.3 (12: 19.8).
+    int want = nd2;
+    if (lines < 256 && lines > 0 && nd2 > 8) {
+        const int parts = (int)(256 / lines);
+        want = (nd2 + parts - 1) / parts;
+        if (parts > 1) want += want & 1;
+        const int64_t wgs = lines * ((nd2 + want - 1) / want);
+        const bool fits = want < nd2 ? want <= cap : uncut <= nw;
+        if (!fits || (want >= 8 && wgs < 192)) want = 8;
+    }
+    PairPlan p;
+    if (uncut <= nw && want >= nd2) {
+        p.segs = 1;
+        p.seg_out = nd2;
+        p.waves = uncut;
+        return p;
+    }
+    if (want < cap) cap = want;
     p.segs = (nd2 + cap - 1) / cap;
     p.seg_out = (nd2 + p.segs - 1) / p.segs;
     if (p.seg_out & 1) ++p.seg_out;
     p.segs = (nd2 + p.seg_out - 1) / p.seg_out;
-    p.waves = p.segs == 1 ? (L2 + 3) / 4 : (2 * p.seg_out + 2 + 3) / 4 + 1;
+    p.waves = p.segs == 1 ? uncut : (2 * p.seg_out + 2 + 3) / 4 + 1;
     if (p.waves > nw) p.waves = nw;
     return p;
 }

@@ -114,6 +114,14 @@ def test_keyed_halving_pairs(oracle, dtype, B, H, W, D, Dm, order):
     run_keyed(oracle, x, kr, dtype, passes, 1, sizes=sizes, tag="pair random keys+sizes")
 
 
+@pytest.mark.parametrize("B,H,W", [(1, 24, 24), (1, 64, 64), (4, 64, 64), (2, 112, 112), (6, 40, 72)])
+def test_keyed_pair_in_runs_of_every_length(oracle, B, H, W):
+    rng = np.random.default_rng(H + W)
+    x = wl.cast_io(rng.standard_normal((B, H, W, 16)).astype(np.float32), "bf16")
+    keys = wl.cast_io(rng.standard_normal((B, H, W, 8)).astype(np.float32), "bf16")
+    run_keyed(oracle, x, keys, "bf16", _halving(H, W, "WH"), 1, tag="runs")
+
+
 def test_keyed_pair_with_the_tokens_as_keys_is_the_plain_call():
     # both kernels decide on fp64 cosines (the plain one wherever its fp32 screening is unsure); their sums run in
     # different orders, which only a decision closer than 1e-15 could notice - these inputs have none
