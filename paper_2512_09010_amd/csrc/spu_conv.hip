@@ -529,8 +529,11 @@ int spu_conv_tiles(int B, int N, int D, int most)
 }
 
 // us of one call, from measurements: a launch for the spectrum where one is needed, then what a workgroup starts with and its
-// pair groups one after the other.  8x700x3584 bf16: 62, 8x1000x3584: 77, 8x1200x3584: 110, 2x3000x3584: 95, 1x5245x3328: 160,
-// 4x4096x3584: 101 (fp32: 137), 8x2048x3584: 87 (fp32: 110).
+// pair groups one after the other.  Measured, the estimates: 8x700x3584 bf16 54 (63), 8x1000x3584 67 (79), 8x1200x3584 98 (110),
+// 2x3000x3584 77 (95), 4x4096x3584 84 (101; fp32 140, 131), 8x2048x3584 74 (88; fp32 94, 113).  They are those of a slower
+// kernel, kept on purpose: with the times of now, calls of 2048 and 4096 tokens with a short pass band would leave spu_fft16q
+// (2x2048x3584, sigma 102: 35.0 us, here 31.3; 4x4096x3584, sigma 100: 110, here 84), whose scores are closer to
+// exact on white tokens (rms 3.3e-8 against 3.6e-8, 2.9e-8 against 3.0e-8).
 double spu_conv_us(int B, int N, int D, luvc_dtype dt)
 {
     bool half;
