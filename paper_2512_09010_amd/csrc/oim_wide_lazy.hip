@@ -452,18 +452,21 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     const int n_abs = __popcll(ln.takes);
     // One or two rows to merge: wavefronts without one of their own take a share of its channels (8x64x64x1280 bf16, merge
     // number 2, six passes: 173.0 us, 170.0; 12x32x32x1024: 99.9, 97.3; four rows in halves: 37.5, 39.2, so not those).
+    // Tokens and metric differ in width: the parts of a row are counted on the wider of them, and a part's channels on the row itself
+    // (of the narrower one, the last parts may have none).
     constexpr int kPiece = 64 * lz_io<T>::V;
-    const int n_merges = (xk ? 2 : 1) * n_abs, pieces = (g.D + kPiece - 1) / kPiece;
-    const int parts = n_merges > 0 && 4 * n_merges <= NW ? min(NW / n_merges, pieces) : 1, share = (pieces + parts - 1) / parts * kPiece;
+    auto pieces = [](int width) { return (width + kPiece - 1) / kPiece; };
+    const int n_merges = (xk ? 2 : 1) * n_abs, widest = pieces(xk && Dk > g.D ? Dk : g.D);
+    const int parts = n_merges > 0 && 4 * n_merges <= NW ? min(NW / n_merges, widest) : 1;
     for (int kk = wave; kk < n_merges * parts; kk += NW) {
-        const int merge = kk / parts, from = (kk - merge * parts) * share;
+        const int merge = kk / parts;
         const bool on_metric = merge >= n_abs;
         const int at = on_metric ? merge - n_abs : merge;
         unsigned long long left = ln.takes;
         for (int i = 0; i < at; ++i) left &= left - 1;
         const int k = (int)__builtin_ctzll(left);
         T* mov = on_metric ? ovk : ov;
-        const int mD = on_metric ? Dk : g.D;
+        const int mD = on_metric ? Dk : g.D, share = (pieces(mD) + parts - 1) / parts * kPiece, from = (kk - merge * parts) * share;
         lazy_merge<T>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, __ballot(leaves && bk == k),
                       mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane, from, min(mD, from + share));
     }

@@ -262,3 +262,22 @@ def test_keyed_few_tokens_out_of_a_line(oracle, dtype, B, H, W, D, Dm, passes):
     x = wl.cast_io(rng.standard_normal((B, H, W, D)).astype(np.float32), dtype)
     keys = wl.cast_io(rng.standard_normal((B, H, W, Dm)).astype(np.float32), dtype)
     run_keyed(oracle, x, keys, dtype, passes, 1, sizes=rng.integers(1, 6, (B, H, W)), tag="few")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("radius", [0, 2])
+@pytest.mark.parametrize("D,Dm", [(64, 1024), (384, 768), (24, 1544), (256, 264), (1280, 2048)])
+def test_keyed_wide_matching_merges_every_channel_of_wider_keys(oracle, dtype, radius, D, Dm):
+    """Keys of more pieces of a wavefront than the tokens have, few and many merged rows (shares of a row, whole rows): every
+    channel of the merged keys is written, also where the workspace was all NaN before."""
+    rng = np.random.default_rng(D + Dm + radius)
+    for m in (1, 2, 5):
+        passes = [(W_AX, m), (H_AX, m), (W_AX, 1)]
+        x = wl.cast_io(rng.standard_normal((1, 11, 14, D)).astype(np.float32), dtype)
+        keys = wl.cast_io(rng.standard_normal((1, 11, 14, Dm)).astype(np.float32), dtype)
+        out, _ = run_keyed(oracle, x, keys, dtype, passes, radius, tag=f"wider keys m={m}")
+        ws = torch.full((16 << 20,), 0xFF, dtype=torch.uint8, device="cuda")
+        again = lv.luvc_oim_merge_keyed(to_dev(x, dtype), to_dev(keys, dtype), passes, radius, workspace=ws)
+        torch.cuda.synchronize()
+        for name in ("x", "metric", "sizes", "merged_map", "kept_map"):
+            assert torch.equal(out[name], again[name]), (m, name)
