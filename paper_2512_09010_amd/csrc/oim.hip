@@ -101,7 +101,8 @@ oim_decide(const double* __restrict__ n2, const double* __restrict__ dn,
         }
         const bool left = hl && (!hr || !(sr > sl));      // tie -> lower position
         best[j] = (hl || hr) ? (left ? a - 1 : a + 1) : -1;
-        score[j] = left ? sl : sr;
+        const double sb = left ? sl : sr;
+        score[j] = sb == sb ? sb : -INFINITY;             // NaN: last, so that exactly m sources leave the line whatever the tokens hold
     }
     for (int p = tid; p < len; p += blockDim.x) merged[p] = 0;
     __syncthreads();

@@ -135,7 +135,8 @@ oim_decide_wide(const double* __restrict__ n2, const double* __restrict__ G,
                 const int c = 2 * k + 1;
                 const int dist = c > a ? c - a : a - c;
                 if (radius > 0 && dist > 2 * radius - 1) continue;
-                const double s = Gl[(int64_t)j * n_dst + k] / (nrm[a] * nrm[c]);
+                double s = Gl[(int64_t)j * n_dst + k] / (nrm[a] * nrm[c]);
+                s = s == s ? s : -INFINITY;                              // NaN: last, so that exactly m sources leave the line whatever the tokens hold
                 if (bc < 0 || s > bs) { bs = s; bc = c; }
             }
 #pragma unroll

@@ -92,3 +92,36 @@ def test_spu_degenerate_and_extreme_band(oracle, B, N, D, sigma, k):
     own = oracle.spu_prune(g, k, x.astype(np.float64))
     np.testing.assert_array_equal(pr["kept_idx"].cpu().numpy(), own["kept_idx"])
     np.testing.assert_array_equal(to_host_f64(pr["x"]), own["x"])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [32, 33])                     # aligned rows (one launch per pass or pair), and rows of any alignment
+@pytest.mark.parametrize("radius", [1, 0, 2])
+@pytest.mark.parametrize("H,W,passes", [
+    (12, 20, [(W_AX, 7), (H_AX, 2)]), (12, 20, [(W_AX, 10), (H_AX, 6)]), (3, 200, [(W_AX, 3), (H_AX, 1)]),
+])
+def test_oim_maps_stay_well_formed_beside_nan(dtype, D, radius, H, W, passes):
+    """Tokens that are no numbers have cosines that are none: exactly m sources leave every line all the same, every output slot has
+    its anchor and every input token a slot."""
+    print(f"[oim nan] {H}x{W}x{D} {dtype} radius {radius} {passes}", flush=True)
+    rng = np.random.default_rng(H * W + D + radius)
+    B = 2
+    x = rng.standard_normal((B, H, W, D)).astype(np.float32)
+    x[rng.random((B, H, W)) < 0.2] = np.nan
+    x[0, 1] = np.nan                                         # a whole line
+    x[rng.random((B, H, W)) < 0.05, 0] = np.inf
+    xd = torch.from_numpy(x).to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda()
+    outs = [lv.luvc_oim_merge(xd, passes) if radius == 1 else lv.luvc_oim_merge_wide(xd, passes, radius),
+            lv.luvc_oim_merge_keyed(torch.ones_like(xd), xd, passes, radius)]
+    torch.cuda.synchronize()
+    for out in outs:
+        merged = out["merged_map"].cpu().numpy().reshape(B, -1)
+        kept = out["kept_map"].cpu().numpy().reshape(B, -1)
+        sizes = out["sizes"].cpu().numpy().reshape(B, -1)
+        n_out = kept.shape[1]
+        for b in range(B):
+            assert merged[b].min() >= 0 and merged[b].max() < n_out
+            np.testing.assert_array_equal(np.bincount(merged[b], minlength=n_out), sizes[b])
+            assert kept[b].min() >= 0 and kept[b].max() < H * W
+            np.testing.assert_array_equal(merged[b][kept[b]], np.arange(n_out))
+    assert torch.equal(outs[1]["x"], torch.ones_like(outs[1]["x"]))        # the mean of ones, whoever was merged
