@@ -65,7 +65,11 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     __shared__ float inv32[kRows], dt32[kRows];                   // 1/|T[r]|, <T[r], T[r+1]> of the intermediate tokens
     __shared__ double inv64[kRows], dt64[kRows];
     __shared__ int szl[kRows];
-    __shared__ int stage[NW];                                     // what a wavefront has written: 1 its first token, 2 inv32, dt32 and szl, 3 inv64 and dt64
+    // What a wavefront has written: 1 its first token, 2 inv32, dt32 and szl, 3 (kSums) inv64 and dt64; or, where it needs no fp64,
+    // kSettled and its verdicts (kFirstUp: of its first source, kNextUp: of the one after its last row).  Every wavefront with rows gets
+    // to 3 or beyond and waits for no more than a 2 before, so every wait ends, whatever the verdicts.
+    __shared__ int stage[NW];
+    constexpr int kSums = 3, kSettled = 16, kFirstUp = 4, kNextUp = 8;
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -111,8 +115,11 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         if (lane == 0) __hip_atomic_store(stage + w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     auto wait_for = [&](int other, int v) {
-        while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(stage + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < v) {}
+        int word;
+        do word = __builtin_amdgcn_readfirstlane(__hip_atomic_load(stage + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+        while (word < v);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        return word;
     };
 
     // ------------------------------------------------------------------ first pass: four intermediate tokens
@@ -236,14 +243,15 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
                 dt64[rr0 + k] = k == 0 ? d[0] : k == 1 ? d[1] : k == 2 ? d[2] : d[3];
             }
         }
-        reached(3);
+        reached(kSums);
         auto decide64 = [&](int q) { return source_goes_left(true, true, inv64[q], dt64[q - 1], inv64[q - 1], dt64[q], inv64[q + 1]); };
-        // the wavefront on the other side of the line has the same verdict of v0, of v4 from the same bits, and comes here as well
-        if (v0 == 0) wait_for(above, 3);
-        if (v4 == 0) wait_for(below, 3);
-        if (v0 == 0) up0 = decide64(rr0);
+        // The wavefront that shares a source looks at the same bits and comes here as well; had it not, its verdict would be the one.
+        const int wa = v0 == 0 ? wait_for(above, kSums) : 0, wb = v4 == 0 ? wait_for(below, kSums) : 0;
+        if (v0 == 0) up0 = wa & kSettled ? (wa & kNextUp) != 0 : decide64(rr0);
         if (v2 == 0) up2 = decide64(rr0 + 2);
-        if (v4 == 0) up4 = decide64(rr0 + 4);
+        if (v4 == 0) up4 = wb & kSettled ? (wb & kFirstUp) != 0 : decide64(rr0 + 4);
+    } else {
+        reached(kSettled | (up0 ? kFirstUp : 0) | (up4 ? kNextUp : 0));
     }
     if (is_halo) return;
 

@@ -260,8 +260,7 @@ __device__ __forceinline__ double inv_norm64(double n2)
 
 // Screening verdict for one source between its lower-position ("left") and higher-position
 // ("right") destination: +1 = left for certain, -1 = right for certain, 0 = too close to call.
-// Every operation rounds on its own: wherever this is inlined, the same sums give the same verdict, and two wavefronts that
-// look at one source agree on whether it is too close (in oim_halve_pair each then waits for the other's fp64 sums).
+// Every operation rounds on its own: wherever this is inlined, the same sums give the same verdict.
 __device__ __forceinline__ int screen_source(bool has_left, bool has_right, float inv_src,
                                              float dot_l, float inv_l, float dot_r, float inv_r, float tau)
 {
