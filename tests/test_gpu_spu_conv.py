@@ -7,7 +7,7 @@ import pytest
 from paper_2512_09010_amd import binding as lv
 from paper_2512_09010_amd import workloads as wl
 from gpu_util import to_dev
-from test_gpu_spu import score_case
+from test_gpu_spu import SCORE_RTOL, score_case
 
 import torch
 
@@ -78,3 +78,29 @@ def test_scores_are_not_short_on_the_mean(oracle, dtype, N, sigma):
     err = got / oracle.spu_score(wl.widen(x, dtype), sigma, True) - 1.0
     print(f"[spu] N={N} sigma={sigma} {dtype} error mean={err.mean():.2e} rms={np.sqrt((err * err).mean()):.2e}", flush=True)
     assert abs(err.mean()) <= 2.0 ** -25
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("paired", [True, False])           # a channel pair in one access, or channel by channel
+@pytest.mark.parametrize("N,sigma,P", [
+    (1500, 20, 4), (2000, 20, 4), (3000, 12, 2), (4000, 12, 2), (6000, 8, 1), (8000, 6, 1),      # zeros behind the tokens: 3072 .. 16384 points
+    (2048, 200, 8), (4096, 150, 4), (8192, 9, 2), (16384, 5, 1),                                 # N = M, beyond the bands of spu_fft16q
+])
+def test_workgroups_that_take_several_steps(oracle, dtype, paired, N, sigma, P):
+    """Seven samples of 109 or 110 groups of P pairs: 28 workgroups each, which take four steps, the last one with a part of them.
+    The channels are 37 different ones, each with scales of its own per channel: a group left out moves the scores of its sample by
+    6e-4 or more (the lowest scale, 1 of 110 groups), one taken in another's place by as much unless all scales agree."""
+    rng = np.random.default_rng(N + sigma)
+    B, D, K = 7, 220 * P - (2 if paired else 1), 37
+    base = wl.cast_io(rng.standard_normal((B, N, K)).astype(np.float32), dtype)
+    scale = rng.choice([0.5, 1.0, 2.0], (B, D))              # exact in either type
+    x = (to_dev(base, dtype)[:, :, torch.arange(D, device="cuda") % K] * torch.from_numpy(scale).to("cuda", torch.bfloat16 if dtype == "bf16" else torch.float32)[:, None, :]).contiguous()
+    print(f"[spu] several steps {tuple(x.shape)} {dtype} sigma={sigma}", flush=True)
+    got = lv.luvc_spu_score(x, sigma, True)
+    torch.cuda.synchronize()
+    _, filtered, _ = oracle.spu_score(wl.widen(base, dtype), sigma, True, want_filtered=True)
+    weight = np.stack([np.bincount(np.arange(D) % K, scale[b] ** 2, K) for b in range(B)])
+    ref = np.sqrt((filtered * filtered * weight[:, None, :]).sum(axis=2))
+    err = np.abs(got.cpu().numpy().astype(np.float64) / ref - 1.0)
+    assert err.max() <= SCORE_RTOL, (err.max(), np.unravel_index(err.argmax(), err.shape))
+    assert torch.equal(lv.luvc_spu_score(x, sigma, True), got)
