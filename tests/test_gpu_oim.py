@@ -367,6 +367,7 @@ def test_few_tokens_row_widths(oracle, dtype, B, H, W, D, passes):
 @pytest.mark.parametrize("B,H,W,D,passes", [
     (43, 25, 24, 16, [(W_AX, 2), (H_AX, 2)]),              # lines of 24 and of an odd 25, last wavefront with one token
     (36, 21, 30, 520, [(W_AX, 1), (H_AX, 3)]),             # two or three pieces of a row, m at which sources are picked one by one
+    (36, 21, 30, 520, [(W_AX, 4), (H_AX, 4)]),             # ... and the smallest m at which they are ranked by all wavefronts
     (80, 9, 33, 1032, [(W_AX, 7), (W_AX, 2)]),             # three pieces in bf16, more in fp32; sources ranked by all wavefronts
     (5, 60, 64, 8, [(W_AX, 2), (H_AX, 2)]),                # sixteen full wavefronts
 ])
