@@ -270,8 +270,11 @@ static luvc_status run_adjacent(const T* x, T* ov, const T* xk, T* ovk, int Dk, 
     const int p = pieces(xk ? Dk : g.D), pm = pieces(xk && Dk > g.D ? Dk : g.D);
 #define LUVC_ADJ(P, PM, HOLD) LUVC_LAUNCH("oim_adjacent_line", (oim_adjacent_line<T, P, PM, HOLD>), dim3((unsigned)(B * nlines)), dim3(64 * waves), 0, st, x, ov, xk, ovk, Dk, \
                                       idx_in, sizes_in, kept_in, g, idx_out, sizes_out, kept_out, pass_map)
-    // more wavefronts than 16 per compute unit: several rounds of lines
-    if (!xk && len <= kAdjTok * waves && p <= 3 && (int64_t)B * nlines * waves > 4096) {
+    // More wavefronts than 16 per compute unit: several rounds of lines.  bf16 rows of two or three pieces on lines of many wavefronts
+    // only where a line merges one or two: the merges of a wavefront wait for one another there (64 tokens of 1280, m = 4 out of
+    // both axes of 8 x 64 x 64: 77.5 us held, 75 not; 640, 5 x 62 x 63, m = 8: 48.2, 46.7; but 48 of 1024, 15 x 48 x 48, m = 8: 64.8, 71).
+    const bool merges_wait = sizeof(T) == 2 && p * waves > 24 && g.m > 2;
+    if (!xk && len <= kAdjTok * waves && p <= 3 && (int64_t)B * nlines * waves > 4096 && !merges_wait) {
         if (p == 1) LUVC_ADJ(1, 1, true);
         else if (p == 2) LUVC_ADJ(2, 2, true);
         else LUVC_ADJ(3, 3, true);

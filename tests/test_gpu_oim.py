@@ -370,6 +370,7 @@ def test_few_tokens_row_widths(oracle, dtype, B, H, W, D, passes):
     (36, 21, 30, 520, [(W_AX, 4), (H_AX, 4)]),             # ... and the smallest m at which they are ranked by all wavefronts
     (80, 9, 33, 1032, [(W_AX, 7), (W_AX, 2)]),             # three pieces in bf16, more in fp32; sources ranked by all wavefronts
     (5, 60, 64, 8, [(W_AX, 2), (H_AX, 2)]),                # sixteen full wavefronts
+    (5, 62, 54, 520, [(W_AX, 3), (H_AX, 2)]),              # bf16 rows of two pieces on long lines: merged from memory, from registers
 ])
 def test_few_tokens_in_several_rounds_of_lines(oracle, dtype, B, H, W, D, passes):
     """More lines than the chip takes at once: tokens stay in registers between the decisions and the merges."""
