@@ -28,7 +28,8 @@
 // older wavefronts of a workgroup get their tokens first, the youngest as they come to 20 us.  A wavefront therefore
 // waits only for its two neighbours (`stage`), not at barriers for all: the merges and stores of the older ones run
 // while the younger ones' tokens are on their way: a call of 34.5 us takes 30.5 (32 x 64 x 64 x 384 61.5 -> 54.8; 80 x 24 x 24 x
-// 1024, workgroups of 6 wavefronts, 35.9 -> 34.7; 128 x 16 x 16 x 1152, of 4, the same).
+// 1024, workgroups of 6 wavefronts, 35.9 -> 34.7; 128 x 16 x 16 x 1152, of 4, the same).  Tokens of a few hundred bytes, which come in
+// together, pay for the words: 16 x 17 x 15 x 128 bf16 6.9 -> 7.4, 80 x 24 x 24 x 256 19.5 -> 20.1.
 //
 // The merge is the size-weighted mean evaluated in fp64 in position order and rounded once.  One
 // case needs no fp64: bf16 storage, one absorbed source, equal sizes.  Then the mean is (b + x) / 2

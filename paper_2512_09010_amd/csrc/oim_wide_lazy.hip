@@ -24,9 +24,9 @@
 //      reciprocal and the two products of a cosine are 5: 5 c / 4 + 13 together.  The roundings count along the
 //      longest chain of additions, an eighth of the channels, not over all of them.  With (D + 24) 2^-22, ten times as
 //      much at 1280 channels, more sources and destinations had to be repeated in fp64, a memory trip behind the
-//      screening (8 x 64 x 64 x 1280 bf16, six passes of merge number 2: 185.7 us, 173.0 now).  Sums of squares beyond 2^100 end the screening of their line: everything is repeated then.  Small
-//      values need no such care: what flushed products lose is below 2^-116, far below a norm of 1e-12, which is where
-//      the method clamps.
+//      screening (8 x 64 x 64 x 1280 bf16, six passes of merge number 2: 185.7 us, 173.0 with this bound).  Sums of squares
+//      beyond 2^100 end the screening of their line: everything is repeated then.  Small values need no such care: what
+//      flushed products lose is below 2^-116, far below a norm of 1e-12, which is where the method clamps.
 //   2. EXACT.  A source may be among the m best of the line only if fewer than m screened best cosines exceed its own by
 //      more than 2 eps; for each such contender, the destinations within 2 eps of its best screened cosine may be its
 //      best destination, no other can.  Their dot products are repeated in fp64 (a wavefront per contender, two
@@ -35,12 +35,14 @@
 //      than m contenders.
 //   3. Layout of the next grid from two 64-bit masks, sources gone and destinations taking sources in, which every
 //      wavefront works out for itself; ids / sizes / anchors / maps of the next grid.
-//   4. Size-weighted mean of every destination that takes sources in, a wavefront per destination.
+//   4. Size-weighted mean of every destination that takes sources in: a wavefront per destination, or, where a line has one or two
+//      rows to merge, the wavefronts share the channels of each.
 // All lines of a grid start together, so what follows the screening is serial time of the launch: no lists or
 // flags are handed through LDS where a ballot does, and each step after the screening is one barrier.
 // Bound: the screening, by the rate at which the tokens arrive (8 x 64 x 64 x 1280 bf16: 84 MB a pass), then latency
 // (three operations of merge number 2 on that grid, six passes and the last copy: 212 us; 185 with eight wavefronts per line
-// where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening; 170 now).
+// where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening; with the bound of step 1 and
+// the shared merges of step 4 168).
 #include <type_traits>
 
 #include "common.hpp"

@@ -20,12 +20,13 @@
 // 4 P-byte pieces of the same cache lines, and keeps the energies in registers until its last pairs are done.
 // An access of a wavefront touches up to 64 / P cache lines and takes the memory path as many cycles and more, so that
 // the next tokens, asked for all at once, fill its queue and the wavefronts stand still before the barrier until it has
-// taken them.  They are asked for a few at a time between the transforms of B and C.  And one cache line in eight is
-// slow (bytes 384 .. 511 of every 1024, wherever a sample starts, seen with row strides of 4, 7 and 8 KB: workgroups that read only
-// those end a fifth later), so a workgroup moves on by kConvTurn places with every step.  us of a call, before, with the
-// turn, and with the parts: bf16 8x700x3584 57, 55, 54; 8x1000x3584 73, 70, 67; 8x1200x3584 106, 106, 98; 4x2000x3584 80, 77, 74;
-// 2x3000x3584 94, 90, 77; 1x5245x3328 149, 149, 122; 1x8000x2048 147, -, 117; 8x2048x3584 91, 84, 75; 4x4096x3584 107, 103, 84; fp32
-// 2x3000x3584 109, -, 79; 4x4096x3584 155, 139, 140.
+// taken them.  They are asked for a few at a time between the transforms of B and C.  And where N = M, workgroups that read
+// nothing but one cache line in eight, bytes 384 .. 511 of every 1024, end later than the others (4x4096x3584 bf16, seven steps: 81 us
+// after the start of the first step, the others 71 to 72; the same with rows 8 KB apart; with the four steps of 2048 channels all end
+// together), so a workgroup moves on by kConvTurn places with every step.  us of a call on tokens that no cache holds, asked for all at
+// once, in parts, and in parts with the turn: bf16 8x700x3584 57, 54, 54; 8x1000x3584 74, 67, 67; 8x1200x3584 107, 98, 98; 2x3000x3584 96,
+// 82, 79; 1x5245x3328 157, 130, 130; 1x8000x2048 164, 140, 135; 8x2048x3584 91, 75, 73; 4x4096x3584 108, 96, 84; 2x8192x2048 110, 98, 88;
+// fp32 8x1200x3584 125, 102, 102; 2x3000x3584 112, 88, 82; 8x2048x3584 122, 101, 94; 4x4096x3584 155, 159, 141.
 // With half of the inputs zero and half of the outputs unwanted (N <= M / 2) passes A and A' take half the loads and skip a
 // butterfly level each.
 // M is the smallest that fits, a power of two or three times one: the longer transform costs its zeros (measured before the tokens
@@ -284,7 +285,10 @@ constexpr int conv_part(int point, int points, int JN)
     if (point == points - 1) return JN;
     return HALF || sizeof(T) == 2 ? (point + 1) * JN / (points - 1) : point * JN / (points - 1);
 }
-constexpr int kConvTurn = 8;                     // places: a cache line of pairs (P = 4, bf16)
+// Places a workgroup moves on by with every step: for bf16 and P = 4 (4096 points) a cache line of them; with fp32 tokens or another P it
+// is another part of a line or several, and was not chosen for those.  Where N = M it gains 2 to 13 %, behind zeros up to 7 % on 6144 and
+// 16384 points, nothing on up to 4096 or where a sample has 8 workgroups (nothing turns); fp32 1x5245x3328 loses, 140 us against 136.
+constexpr int kConvTurn = 8;
 
 template <typename T, int R, int LB, int P, bool HALF /* N <= M/2: zeros behind the tokens; else N = M */, bool PAIRED /* every pair is one aligned access */>
 __global__ void __launch_bounds__(16 * LB * P)
@@ -528,12 +532,13 @@ int spu_conv_tiles(int B, int N, int D, int most)
     return best;
 }
 
-// us of one call, from measurements: a launch for the spectrum where one is needed, then what a workgroup starts with and its
-// pair groups one after the other.  Measured, the estimates: 8x700x3584 bf16 54 (63), 8x1000x3584 67 (79), 8x1200x3584 98 (110),
-// 2x3000x3584 77 (95), 4x4096x3584 84 (101; fp32 140, 131), 8x2048x3584 74 (88; fp32 94, 113).  They are those of a slower
-// kernel, kept on purpose: with the times of now, calls of 2048 and 4096 tokens with a short pass band would leave spu_fft16q
-// (2x2048x3584, sigma 102: 35.0 us, here 31.3; 4x4096x3584, sigma 100: 110, here 84), whose scores are closer to
-// exact on white tokens (rms 3.3e-8 against 3.6e-8, 2.9e-8 against 3.0e-8).
+// us of one call as the paths are weighed with: a launch for the spectrum where one is needed, then what a workgroup starts with and its
+// pair groups one after the other.  Fitted to a form of the kernel that asked for all tokens at once; most calls now take less.  Measured,
+// the estimates: 8x700x3584 bf16 54 (63), 8x1000x3584 67 (79), 8x1200x3584 98 (110), 2x3000x3584 79 (95), 4x4096x3584 84 (101; fp32 141,
+// 131), 8x2048x3584 73 (88; fp32 94, 113).  They keep calls of 2048 and 4096 tokens with a short pass band on spu_fft16q
+// (2x2048x3584, sigma 102: 34.8 us, here 31.3; 4x4096x3584, sigma 100: 110, here 84), whose scores are closer to exact on white
+// tokens (rms 3.3e-8 against 3.6e-8, 2.9e-8 against 3.0e-8).  Up to 1024 tokens they are compared with spu_circ's, which are an
+// earlier form's too.
 double spu_conv_us(int B, int N, int D, luvc_dtype dt)
 {
     bool half;

@@ -174,9 +174,9 @@ tile_tag_t spu_next_tag()
 
 // ------------------------------------------------------------------ host side
 // Which kernel is quickest: measured times (us, one call) as functions of the sizes.  spu_circ: its products at 1.1e15 flop/s,
-// and a chain of steps that grows with N, which overlap in part (bf16 8x205x3584: 14, 1x729x3584: 20, 1x1000x1024: 16,
-// 4x861x1408: 34; fp32 1x300x2048: 13, 1x1000x1024: 29; channel by channel 8x205x3585: 16, 1x729x3585: 27); the others beside
-// their launchers.
+// and a chain of steps that grows with N, which overlap in part (fitted to bf16 8x205x3584: 14, 1x729x3584: 20, 1x1000x1024: 16,
+// 4x861x1408: 34; fp32 1x300x2048: 13, 1x1000x1024: 29; channel by channel 8x205x3585: 16, 1x729x3585: 27; since its taps are ready
+// earlier it takes .5 to 2 us less); the others beside their launchers.
 static double circ_work_us(int64_t B, int N, int D, luvc_dtype dt) { return (dt == LUVC_F32 ? 12.0 : 6.0) * N * N * (double)D * (double)B / 1.1e9; }
 static double circ_us(int64_t B, int N, int D, luvc_dtype dt, CircRows rows)
 {
