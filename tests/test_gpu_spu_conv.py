@@ -83,7 +83,7 @@ def test_scores_are_not_short_on_the_mean(oracle, dtype, N, sigma):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("paired", [True, False])           # a channel pair in one access, or channel by channel
 @pytest.mark.parametrize("N,sigma,P", [
-    (1500, 20, 4), (2000, 20, 4), (3000, 12, 2), (4000, 12, 2), (6000, 8, 1), (8000, 6, 1),      # zeros behind the tokens: 3072 .. 16384 points
+    (700, 40, 8), (1000, 50, 8), (1500, 20, 4), (2000, 20, 4), (3000, 12, 2), (4000, 12, 2), (6000, 8, 1), (8000, 6, 1),      # zeros behind the tokens: 1536 .. 16384 points
     (2048, 200, 8), (4096, 150, 4), (8192, 9, 2), (16384, 5, 1),                                 # N = M, beyond the bands of spu_fft16q
 ])
 def test_workgroups_that_take_several_steps(oracle, dtype, paired, N, sigma, P):
