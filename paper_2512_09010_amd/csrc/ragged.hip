@@ -200,15 +200,15 @@ bool spu_runs(int n_samples, const int32_t* N, const int32_t* sigma, const int32
 size_t esz(luvc_dtype dt) { return dt == LUVC_F32 ? 4 : 2; }
 
 // Workspace of the scores of a ragged batch: the largest need of a run that is a call of its own, or the words of all runs that
-// share a launch (circ: the rows let them).  0 (with an error message) when a run is not supported.
-size_t spu_runs_workspace(const std::vector<SpuRun>& runs, int D, luvc_dtype dt, bool circ)
+// share a launch (rows: what lets them, and what lets others be quicker on their own).  0 (with an error message) when a run is not supported.
+size_t spu_runs_workspace(const std::vector<SpuRun>& runs, int D, luvc_dtype dt, SpuRows rows)
 {
     size_t need = 0, shared = 0;
     for (const SpuRun& r : runs) {
         const size_t b = luvc_spu_workspace_bytes(r.count, r.N, D, dt, r.sigma);
         if (b == 0) { set_error("run of %d samples with N=%d, sigma=%d is not supported", r.count, r.N, r.sigma); return 0; }
         need = std::max(need, b);
-        if (circ && spu_circ_in_batch(r.count, r.N, D, r.sigma, dt)) shared += spu_circ_bytes(r.count, r.N, D);
+        if (rows.circ != CircRows::None && spu_circ_in_batch(r.count, r.N, D, r.sigma, dt, rows.pieces)) shared += spu_circ_bytes(r.count, r.N, D);
     }
     return std::max(need, align_up(shared));
 }
@@ -299,7 +299,7 @@ size_t luvc_spu_ragged_workspace_bytes(int n_samples, const int32_t* N, int D, l
 {
     std::vector<SpuRun> runs;
     if (D < 1 || !spu_runs(n_samples, N, sigma, nullptr, &runs)) return 0;
-    return spu_runs_workspace(runs, D, dtype, true);
+    return spu_runs_workspace(runs, D, dtype, SpuRows{CircRows::Paired, false});         // without pieces, more runs share a launch
 }
 
 luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N, int D, int64_t row_stride, luvc_dtype dtype,
@@ -315,8 +315,8 @@ luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N
     // workspace, follows from lengths and cut-offs alone, as in the query, which has no keep counts.
     std::vector<SpuRun> runs, kept;
     if (!spu_runs(n_samples, N, sigma, nullptr, &runs) || (n_keep && !spu_runs(n_samples, N, sigma, n_keep, &kept))) return LUVC_ERR_INVALID_ARG;
-    const bool circ = spu_circ_rows(x, D, row_stride, dtype) != CircRows::None;
-    const size_t need = spu_runs_workspace(runs, D, dtype, circ);
+    const SpuRows rows = spu_rows(x, D, row_stride, dtype);
+    const size_t need = spu_runs_workspace(runs, D, dtype, rows);
     if (need == 0) return LUVC_ERR_INVALID_ARG;
     if (!workspace_ok(workspace, workspace_bytes, need)) return LUVC_ERR_WORKSPACE;
     const size_t es = esz(dtype);
@@ -331,7 +331,7 @@ luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N
     };
     for (const SpuRun& r : runs) {
         luvc_status rc = LUVC_OK;
-        if (circ && spu_circ_in_batch(r.count, r.N, D, r.sigma, dtype)) {
+        if (rows.circ != CircRows::None && spu_circ_in_batch(r.count, r.N, D, r.sigma, dtype, rows.pieces)) {
             cr.run[cr.n++] = CircRun{0, r.N, r.sigma, r.count, r.tok_in};
             if (cr.n == kCircMaxRuns) rc = flush_scores();
         } else {

@@ -10,12 +10,19 @@ constexpr int kSpuMaxN = 32768;     // tokens per sample (twiddle index arithmet
 enum class SpuPath {
     Circ,       // spu_circ: the filter as a circulant matrix on the matrix cores, short samples
     Fft,        // spu_fft16q: transform decomposition, N = 16 Q N2
+    Mat,        // spu_mat: two transforms on the matrix cores, N = N1 N2 with a factor N1 in 9 .. 16
     Conv,       // spu_conv: M-point transforms in one workgroup, any N up to 8192
     Dense       // direct pass-band DFT through the workspace, any N
 };
 
 // How spu_circ reads the rows of a call: channel pairs in one access, channel by channel, or not at all (strides too large)
 enum class CircRows { None, Single, Paired };
+// What the rows of a call allow: the kernels that need more than single elements
+struct SpuRows {
+    CircRows circ;
+    bool pieces;                     // bf16 rows in aligned 16-byte pieces
+};
+SpuRows spu_rows(const void* x, int D, int64_t row_stride, luvc_dtype dt);
 
 // Offsets (bytes) of the score kernels' scratch inside the caller's workspace.
 struct SpuLayout {
@@ -23,9 +30,9 @@ struct SpuLayout {
     int n_tiles;
     SpuPath path;
 };
-SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, CircRows circ, size_t most);
+SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows, size_t most);
 size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most = SIZE_MAX);
-bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt);
+bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces);
 
 luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma,
                             int use_hamming, float* scores, void* workspace, size_t most, hipStream_t st);
@@ -39,6 +46,13 @@ double spu_fft_us(int B, int N, int D, int sigma);
 struct TileSync;
 luvc_status spu_score_fft(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
                           float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st);
+
+// Samples of N = N1 N2 tokens on the matrix cores (spu_mat.hip)
+bool spu_mat_supported(int N, int sigma);
+int spu_mat_tiles(int B, int N, int D, int sigma);
+double spu_mat_us(int B, int N, int D, int sigma);
+luvc_status spu_score_mat(const void* x, int B, int N, int D, int64_t row_stride, int sigma, int use_hamming,
+                          float* partial, float* gpartial, const TileSync& sy, int n_tiles, int ld, float* scores, hipStream_t st);
 
 // Short samples on the matrix cores (spu_circ.hip), runs of equal samples in one launch
 constexpr int kCircMaxN = 1024, kCircMaxRuns = 64;

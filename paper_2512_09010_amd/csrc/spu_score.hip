@@ -12,6 +12,7 @@
 //   spu_fwd_dense   C_k, S_k for a tile of 64 channels and a group of bins
 //   spu_inv_dense   x'[n] for a tile of 64 channels and a chunk of tokens, squared and summed over the tile
 //   spu_finish      fixed-order sum over channel tiles, square root (Eq. 8)
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cmath>
@@ -183,26 +184,34 @@ static double circ_us(int64_t B, int N, int D, luvc_dtype dt, CircRows rows)
     const double work = 1.15 * circ_work_us(B, N, D, dt), chain = (dt == LUVC_F32 ? 0.0218 : 0.0105) * N;
     return (dt == LUVC_F32 ? 6.3 : 5.5) + (rows == CircRows::Single ? 1.35 : 1.0) * std::sqrt(work * work + chain * chain);
 }
-static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, double* us)
+static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces, double* us)
 {
     bool half;
-    const bool conv = spu_conv_points(N, &half) != 0, fft = spu_fft_supported(N, sigma);
-    const double f = fft ? spu_fft_us(B, N, D, sigma) : 0.0, c = conv ? spu_conv_us(B, N, D, dt) : 0.0;
-    if (fft && (!conv || f <= c)) { *us = f; return SpuPath::Fft; }
-    *us = c;
-    return conv ? SpuPath::Conv : SpuPath::Dense;
+    SpuPath path = SpuPath::Dense;
+    *us = 0.0;
+    auto offer = [&](SpuPath p, double t) {
+        if (path == SpuPath::Dense || t < *us) { path = p; *us = t; }
+    };
+    if (pieces && spu_mat_supported(N, sigma)) offer(SpuPath::Mat, spu_mat_us(B, N, D, sigma));
+    if (spu_fft_supported(N, sigma)) offer(SpuPath::Fft, spu_fft_us(B, N, D, sigma));
+    if (spu_conv_points(N, &half) != 0) offer(SpuPath::Conv, spu_conv_us(B, N, D, dt));
+    return path;
 }
-static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, CircRows circ)
+static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows)
 {
     double us;
-    const SpuPath other = long_path(B, N, D, sigma, dt, &us);
-    return circ != CircRows::None && N <= kCircMaxN && circ_us(B, N, D, dt, circ) <= us ? SpuPath::Circ : other;
+    const SpuPath other = long_path(B, N, D, sigma, dt, rows.pieces, &us);
+    return rows.circ != CircRows::None && N <= kCircMaxN && circ_us(B, N, D, dt, rows.circ) <= us ? SpuPath::Circ : other;
+}
+SpuRows spu_rows(const void* x, int D, int64_t row_stride, luvc_dtype dt)
+{
+    return SpuRows{spu_circ_rows(x, D, row_stride, dt), dt == LUVC_BF16 && D % 8 == 0 && row_stride % 8 == 0 && row_stride < (1 << 19) && (uintptr_t)x % 16 == 0};
 }
 // in a launch that several runs share, a run adds its products and nothing else
-bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt)
+bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces)
 {
     double us;
-    (void)long_path(B, N, D, sigma, dt, &us);
+    (void)long_path(B, N, D, sigma, dt, pieces, &us);
     return N <= kCircMaxN && circ_work_us(B, N, D, dt) <= us;
 }
 
@@ -219,14 +228,19 @@ static size_t tile_bytes(int B, int n_tiles, size_t ld, SpuLayout* L, size_t off
 // most: scratch the call has to do with; a layout that needs more is returned where nothing smaller serves the call.  Short
 // samples then go to the kernels of long ones; spu_conv takes fewer workgroups per sample, down to one per 64 channels,
 // which is what the direct path's energies take (1 x 8192 x 2048: 256 of them want 8.9 MB, 205 want 7.2).
-SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, CircRows circ, size_t most)
+SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows, size_t most)
 {
     SpuLayout L{};
-    L.path = spu_path(B, N, D, sigma, dt, circ);
+    L.path = spu_path(B, N, D, sigma, dt, rows);
     if (L.path == SpuPath::Circ) {
         L.n_tiles = 1;
         L.bytes = align_up(spu_circ_bytes(B, N, D));
-        return L.bytes > most ? spu_layout(B, N, D, sigma, dt, CircRows::None, most) : L;
+        return L.bytes > most ? spu_layout(B, N, D, sigma, dt, SpuRows{CircRows::None, rows.pieces}, most) : L;
+    }
+    if (L.path == SpuPath::Mat) {
+        L.n_tiles = spu_mat_tiles(B, N, D, sigma);
+        L.bytes = tile_bytes(B, L.n_tiles, (N + 3) / 4 * 4, &L, 0);
+        return L.bytes > most ? spu_layout(B, N, D, sigma, dt, SpuRows{rows.circ, false}, most) : L;
     }
     L.n_tiles = L.path == SpuPath::Fft ? (D + 31) / 32 : (D + 63) / 64;
     const bool dense = L.path == SpuPath::Dense;                     // the one path whose tables and spectra do not stay in LDS
@@ -256,15 +270,16 @@ SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, CircRows cir
 // taken for rows in pairs (where it is taken for single rows, it is for pairs too).
 size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most)
 {
-    const size_t need = spu_layout(B, N, D, sigma, dt, CircRows::None, most).bytes;
+    size_t need = spu_layout(B, N, D, sigma, dt, SpuRows{CircRows::None, false}, most).bytes;
+    if (dt == LUVC_BF16) need = std::max(need, spu_layout(B, N, D, sigma, dt, SpuRows{CircRows::None, true}, most).bytes);
     const size_t circ = N <= kCircMaxN ? align_up(spu_circ_bytes(B, N, D)) : 0;
-    return circ > need && circ <= most && spu_path(B, N, D, sigma, dt, CircRows::Paired) == SpuPath::Circ ? circ : need;
+    return circ > need && circ <= most && spu_path(B, N, D, sigma, dt, SpuRows{CircRows::Paired, false}) == SpuPath::Circ ? circ : need;
 }
 
 luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma,
                             int use_hamming, float* scores, void* workspace, size_t most, hipStream_t st)
 {
-    const SpuLayout L = spu_layout(B, N, D, sigma, dt, spu_circ_rows(x, D, row_stride, dt), most);
+    const SpuLayout L = spu_layout(B, N, D, sigma, dt, spu_rows(x, D, row_stride, dt), most);
     char* ws = (char*)workspace;
     if (L.path == SpuPath::Circ) {
         CircRuns runs;
@@ -284,6 +299,8 @@ luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stri
     sy.arrive = (tile_tag_t*)(ws + L.arrive);
     sy.tag = spu_next_tag();
     if (L.path == SpuPath::Fft) return spu_score_fft(x, B, N, D, row_stride, dt, sigma, use_hamming, partial, gpartial, sy, L.n_tiles, scores, st);
+    if (L.path == SpuPath::Mat)
+        return spu_score_mat(x, B, N, D, row_stride, sigma, use_hamming, partial, gpartial, sy, L.n_tiles, (N + 3) / 4 * 4, scores, st);
     if (L.path == SpuPath::Conv)
         return spu_score_conv(x, B, N, D, row_stride, dt, sigma, use_hamming, (float*)(ws + L.spec), partial, gpartial, sy, L.n_tiles, scores, st);
     LUVC_LAUNCH("spu_tables", spu_tables, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, N, sigma, use_hamming, tw, gk, gm);

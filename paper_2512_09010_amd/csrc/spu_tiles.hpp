@@ -86,7 +86,9 @@ struct TileSync {
 };
 
 inline __host__ __device__ int spu_tile_groups(int n_tiles) { return (n_tiles + kTileGroup - 1) / kTileGroup; }
-__device__ __forceinline__ bool tiles_two_level(int n_tiles) { return spu_tile_groups(n_tiles) > 1; }
+// DIRECT: tiles of a sample that are added in one go, without a level of groups in between
+template <int DIRECT = kTileGroup>
+__device__ __forceinline__ bool tiles_two_level(int n_tiles) { return n_tiles > DIRECT; }
 
 __device__ __forceinline__ tile_tag_t tag_load(const tile_tag_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void tag_store(tile_tag_t* p, tile_tag_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -95,23 +97,26 @@ __device__ __forceinline__ void tag_store(tile_tag_t* p, tile_tag_t v) { __hip_a
 // itself (its group's, or the sample's where there is no group level); lane 1 of the first workgroup of every
 // group handles the sample's word, which the workgroup that completes the group bumps - after every workgroup of
 // the group has arrived, the first one with its claim behind it.
+template <int DIRECT = kTileGroup>
 __device__ __forceinline__ tile_tag_t* tiles_word(const TileSync& sy, int b, int tile, int n_tiles)
 {
     const int n_groups = spu_tile_groups(n_tiles);
     tile_tag_t* w = sy.arrive + (int64_t)b * (n_groups + 1);
-    const bool two_level = tiles_two_level(n_tiles);
+    const bool two_level = tiles_two_level<DIRECT>(n_tiles);
     if (threadIdx.x == 0) return two_level ? w + 1 + tile / kTileGroup : w;
     if (threadIdx.x == 1 && two_level && tile % kTileGroup == 0) return w;
     return nullptr;
 }
+template <int DIRECT = kTileGroup>
 __device__ __forceinline__ tile_tag_t tiles_look(const TileSync& sy, int b, int tile, int n_tiles)
 {
-    const tile_tag_t* w = tiles_word(sy, b, tile, n_tiles);
+    const tile_tag_t* w = tiles_word<DIRECT>(sy, b, tile, n_tiles);
     return w ? tag_load(w) : 0;
 }
+template <int DIRECT = kTileGroup>
 __device__ __forceinline__ void tiles_claim(const TileSync& sy, int b, int tile, int n_tiles, tile_tag_t seen)
 {
-    tile_tag_t* w = tiles_word(sy, b, tile, n_tiles);
+    tile_tag_t* w = tiles_word<DIRECT>(sy, b, tile, n_tiles);
     if (w && (seen >> 16) != sy.tag) {
         tile_tag_t expect = seen;
         (void)__hip_atomic_compare_exchange_strong(w, &expect, sy.tag << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -130,8 +135,8 @@ __device__ __forceinline__ bool tiles_arrive(tile_tag_t* w, int total)
 // Called by all THREADS threads of the workgroup of (sample b, tile) after they have written the tile's
 // energies to partial[(b * n_tiles + tile) * ld + n] with tile_store().  `flag` is a __shared__ word.
 // ld % 4 == 0 (and the 256-byte alignment the workspace has anyway).  A sample of at most
-// kTileGroup tiles has no group level: its last workgroup adds the tiles directly.
-template <int THREADS>
+// DIRECT tiles has no group level: its last workgroup adds the tiles directly.
+template <int THREADS, int DIRECT = kTileGroup>
 __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [B, n_tiles, ld] */,
                                                 float* __restrict__ gpartial /* [B, n_groups, ld] */,
                                                 const TileSync sy,
@@ -141,7 +146,7 @@ __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [
     const int tid = threadIdx.x;
     const int n_groups = spu_tile_groups(n_tiles);
     tile_tag_t* cnt = sy.arrive + (int64_t)b * (n_groups + 1);
-    const bool two_level = tiles_two_level(n_tiles);
+    const bool two_level = tiles_two_level<DIRECT>(n_tiles);
     if (two_level) {
         const int grp = tile / kTileGroup, t_first = grp * kTileGroup;
         const int t_cnt = n_tiles - t_first < kTileGroup ? n_tiles - t_first : kTileGroup;
