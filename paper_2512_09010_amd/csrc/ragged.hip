@@ -199,17 +199,58 @@ bool spu_runs(int n_samples, const int32_t* N, const int32_t* sigma, const int32
 
 size_t esz(luvc_dtype dt) { return dt == LUVC_F32 ? 4 : 2; }
 
-// Workspace of the scores of a ragged batch: the largest need of a run that is a call of its own, or the words of all runs that
-// share a launch (rows: what lets them, and what lets others be quicker on their own).  0 (with an error message) when a run is not supported.
+// How the runs of a ragged batch are scored: on their own, or in a launch that several share, spu_circ's or spu_mat's.  In such a
+// launch a run adds its products and nothing else.  spu_circ takes short samples of any length; a second kind of launch is made
+// where it saves more than the 9 us it takes (eight samples of 312 to 576 tokens, 3584 channels: 45 -> 30 us with all in spu_mat,
+// which has N log N work for lengths with a factor in 9 .. 16).
+enum class SpuKind : char { Own, Circ, Mat };
+std::vector<SpuKind> spu_kinds(const std::vector<SpuRun>& runs, int D, luvc_dtype dt, SpuRows rows)
+{
+    std::vector<SpuKind> kinds(runs.size(), SpuKind::Own), with_mat;
+    double saved = 0.0;
+    bool circ = false, circ_left = false;
+    with_mat = kinds;
+    for (size_t i = 0; i < runs.size(); ++i) {
+        const SpuRun& r = runs[i];
+        double us = spu_alone_us(r.count, r.N, D, r.sigma, dt, rows.pieces);
+        const double c = spu_circ_work_us(r.count, r.N, D, dt), m = rows.pieces ? spu_mat_work_us(r.count, r.N, D, r.sigma) : 0.0;
+        if (rows.circ != CircRows::None && r.N <= kCircMaxN && c <= us) {
+            kinds[i] = with_mat[i] = SpuKind::Circ;
+            us = c;
+            circ = true;
+        }
+        if (m > 0.0 && m < us) {
+            with_mat[i] = SpuKind::Mat;
+            saved += us - m;
+        }
+        circ_left |= with_mat[i] == SpuKind::Circ;
+    }
+    return saved > (circ && !circ_left ? 1.0 : 9.0) ? with_mat : kinds;
+}
+
+std::vector<MatRun> mat_runs(const std::vector<SpuRun>& runs, const std::vector<SpuKind>& kinds)
+{
+    std::vector<MatRun> out;
+    for (size_t i = 0; i < runs.size(); ++i)
+        if (kinds[i] == SpuKind::Mat) out.push_back(MatRun{runs[i].N, runs[i].sigma, runs[i].count, runs[i].tok_in});
+    return out;
+}
+
+// Workspace of the scores of a ragged batch: the largest need of a run that is a call of its own, or of a launch that several
+// share.  0 (with an error message) when a run is not supported.
 size_t spu_runs_workspace(const std::vector<SpuRun>& runs, int D, luvc_dtype dt, SpuRows rows)
 {
+    const std::vector<SpuKind> kinds = spu_kinds(runs, D, dt, rows);
     size_t need = 0, shared = 0;
-    for (const SpuRun& r : runs) {
+    for (size_t i = 0; i < runs.size(); ++i) {
+        const SpuRun& r = runs[i];
         const size_t b = luvc_spu_workspace_bytes(r.count, r.N, D, dt, r.sigma);
         if (b == 0) { set_error("run of %d samples with N=%d, sigma=%d is not supported", r.count, r.N, r.sigma); return 0; }
         need = std::max(need, b);
-        if (rows.circ != CircRows::None && spu_circ_in_batch(r.count, r.N, D, r.sigma, dt, rows.pieces)) shared += spu_circ_bytes(r.count, r.N, D);
+        if (kinds[i] == SpuKind::Circ) shared += spu_circ_bytes(r.count, r.N, D);
     }
+    const std::vector<MatRun> mat = mat_runs(runs, kinds);
+    for (size_t i = 0; i < mat.size(); i += kMatMaxRuns) need = std::max(need, spu_mat_bytes(&mat[i], (int)std::min<size_t>(kMatMaxRuns, mat.size() - i), D));
     return std::max(need, align_up(shared));
 }
 
@@ -299,7 +340,9 @@ size_t luvc_spu_ragged_workspace_bytes(int n_samples, const int32_t* N, int D, l
 {
     std::vector<SpuRun> runs;
     if (D < 1 || !spu_runs(n_samples, N, sigma, nullptr, &runs)) return 0;
-    return spu_runs_workspace(runs, D, dtype, SpuRows{CircRows::Paired, false});         // without pieces, more runs share a launch
+    // whichever way the rows will lie
+    const size_t a = spu_runs_workspace(runs, D, dtype, SpuRows{CircRows::Paired, false}), b = spu_runs_workspace(runs, D, dtype, SpuRows{CircRows::Paired, dtype == LUVC_BF16 && D % 8 == 0});
+    return a && b ? std::max(a, b) : 0;
 }
 
 luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N, int D, int64_t row_stride, luvc_dtype dtype,
@@ -329,15 +372,22 @@ luvc_status luvc_spu_stage_ragged(const void* x, int n_samples, const int32_t* N
         cr.n = 0;
         return rc;
     };
-    for (const SpuRun& r : runs) {
+    const std::vector<SpuKind> kinds = spu_kinds(runs, D, dtype, rows);
+    for (size_t i = 0; i < runs.size(); ++i) {
+        const SpuRun& r = runs[i];
         luvc_status rc = LUVC_OK;
-        if (rows.circ != CircRows::None && spu_circ_in_batch(r.count, r.N, D, r.sigma, dtype, rows.pieces)) {
+        if (kinds[i] == SpuKind::Circ) {
             cr.run[cr.n++] = CircRun{0, r.N, r.sigma, r.count, r.tok_in};
             if (cr.n == kCircMaxRuns) rc = flush_scores();
-        } else {
+        } else if (kinds[i] == SpuKind::Own) {
             rc = luvc_spu_score((const char*)x + (size_t)r.tok_in * (size_t)row_stride * es, r.count, r.N, D, row_stride, dtype, r.sigma, use_hamming,
                                 scores + r.tok_in, workspace, workspace_bytes, hip_stream);
         }
+        if (rc != LUVC_OK) return rc;
+    }
+    const std::vector<MatRun> mat = mat_runs(runs, kinds);
+    for (size_t i = 0; i < mat.size(); i += kMatMaxRuns) {
+        const luvc_status rc = spu_score_mat_runs(x, &mat[i], (int)std::min<size_t>(kMatMaxRuns, mat.size() - i), D, row_stride, use_hamming ? 1 : 0, scores, workspace, st);
         if (rc != LUVC_OK) return rc;
     }
     luvc_status rc = flush_scores();

@@ -32,7 +32,9 @@ struct SpuLayout {
 };
 SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows, size_t most);
 size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most = SIZE_MAX);
-bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces);
+// us of a run: on its own, and what its products add to a spu_circ launch that several share
+double spu_alone_us(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces);
+double spu_circ_work_us(int64_t B, int N, int D, luvc_dtype dt);
 
 luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma,
                             int use_hamming, float* scores, void* workspace, size_t most, hipStream_t st);
@@ -47,12 +49,26 @@ struct TileSync;
 luvc_status spu_score_fft(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
                           float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st);
 
-// Samples of N = N1 N2 tokens on the matrix cores (spu_mat.hip)
+// Samples of N = N1 N2 tokens on the matrix cores (spu_mat.hip), runs of equal samples in one launch
+constexpr int kMatMaxRuns = 16;
+struct MatRun {
+    int N, sigma, count;
+    int64_t tok0;                    // first token of the first sample
+};
+struct MatPlan {
+    int rb, gpw, n_tiles, ld;
+    int64_t samples;
+    size_t lds;
+};
 bool spu_mat_supported(int N, int sigma);
-int spu_mat_tiles(int B, int N, int D, int sigma);
+MatPlan spu_mat_plan(const MatRun* runs, int n, int D);
 double spu_mat_us(int B, int N, int D, int sigma);
-luvc_status spu_score_mat(const void* x, int B, int N, int D, int64_t row_stride, int sigma, int use_hamming,
-                          float* partial, float* gpartial, const TileSync& sy, int n_tiles, int ld, float* scores, hipStream_t st);
+double spu_mat_work_us(int B, int N, int D, int sigma);
+luvc_status spu_score_mat(const void* x, const MatRun* runs, int n, const MatPlan& p, int D, int64_t row_stride, int use_hamming,
+                          float* partial, float* gpartial, const TileSync& sy, float* scores, hipStream_t st);
+// a launch that several runs share: scratch, and the launch on it
+size_t spu_mat_bytes(const MatRun* runs, int n, int D);
+luvc_status spu_score_mat_runs(const void* x, const MatRun* runs, int n, int D, int64_t row_stride, int use_hamming, float* scores, void* workspace, hipStream_t st);
 
 // Short samples on the matrix cores (spu_circ.hip), runs of equal samples in one launch
 constexpr int kCircMaxN = 1024, kCircMaxRuns = 64;

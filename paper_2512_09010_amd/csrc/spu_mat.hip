@@ -31,6 +31,7 @@
 // Tried and not kept: two wavefronts that fetch for the other eight (40 us for 38 at that time); two pairs per wavefront and
 // four wavefronts per SIMD (16x720x4096 71 for 51); products and vector instructions put in turns by hand; tokens through registers
 // (one chunk on its way: 42).
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <numeric>
@@ -158,11 +159,27 @@ struct MatShape {
     int N, N1, N2, NT /* tiles of 16 subsequences */, sigma, dn /* lowest multiple of N1 in the band, negated */, nb /* multiples */;
 };
 
-template <int RB /* blocks of 16 rows of the band */>
+// runs of equal samples that share a launch
+struct MatLaunchRun {
+    MatShape sh;
+    int wg0, sample0;                            // first workgroup, first sample of the launch
+    int64_t tok0;                                // first token
+};
+template <int RUNS> struct MatLaunch { int n; MatLaunchRun run[RUNS]; };
+
+template <int RB /* blocks of 16 rows of the band */, int RUNS>
 __global__ void __launch_bounds__(64 * kMatWaves, 2)
-spu_mat(const bf16_t* __restrict__ x, const MatShape sh, int D, int64_t row_stride, int use_hamming, int gpw /* groups of channels per workgroup */,
-        float* __restrict__ partial, float* __restrict__ gpartial, const TileSync sy, int ld, float* __restrict__ scores)
+spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t row_stride, int use_hamming, int gpw /* groups of channels per workgroup */,
+        int n_tiles /* workgroups per sample */, float* __restrict__ partial /* [samples, n_tiles, ld] */, float* __restrict__ gpartial, const TileSync sy, int ld,
+        float* __restrict__ scores)
 {
+    const int item = (int)xcd_contiguous(blockIdx.x, gridDim.x);
+    int at_run = 0;
+    if (RUNS > 1)
+        for (int i = 1; i < runs.n; ++i)
+            if (item >= runs.run[i].wg0) at_run = i;
+    const MatLaunchRun& run = runs.run[at_run];
+    const MatShape& sh = run.sh;
     constexpr int P = kMatPairs, WAVES = kMatWaves, THREADS = 64 * WAVES;
     constexpr int KS = (RB + 1) / 2;             // steps of a product over the band
     constexpr int kBuf = 256 * 8;                // 16-byte pieces of a buffer: 256 rows of 8, which are 64 channels
@@ -184,11 +201,10 @@ spu_mat(const bf16_t* __restrict__ x, const MatShape sh, int D, int64_t row_stri
     __shared__ uint32_t look[2][64];
     __shared__ int is_last;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 15, g = lane >> 4;
-    const int n_tiles = gridDim.x;
-    const unsigned item = xcd_contiguous(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
-    const int tile = item % n_tiles, b = item / n_tiles;
+    const int local = (item - run.wg0) / n_tiles, tile = item - run.wg0 - local * n_tiles, b = run.sample0 + local;
+    const int64_t tok = run.tok0 + (int64_t)local * N;
     const int groups_all = (D + kMatWidth - 1) / kMatWidth, grp0 = tile * gpw, groups = groups_all - grp0 < gpw ? groups_all - grp0 : gpw;
-    const bf16_t* xb = x + (int64_t)b * N * row_stride;
+    const bf16_t* xb = x + tok * row_stride;
 
     // ---- tokens
     const uint32_t lds0 = lds_address(data);
@@ -534,7 +550,7 @@ spu_mat(const bf16_t* __restrict__ x, const MatShape sh, int D, int64_t row_stri
         for (int w = 0; w < WAVES; ++w) q += (double)at[w * NT * 256];
         tile_store(pout + n, (float)q);
     }
-    tiles_to_scores<THREADS, kMatDirect>(partial, gpartial, sy, scores, b, tile, n_tiles, N, ld, &is_last);
+    tiles_to_scores<THREADS, kMatDirect>(partial, gpartial, sy, scores + (tok - (int64_t)b * N), b, tile, n_tiles, N, ld, &is_last);
 }
 
 namespace {
@@ -611,48 +627,91 @@ bool spu_mat_supported(int N, int sigma)
     return mat_shape(N, sigma, &sh, &rb) && mat_lds(sh, rb, 1) <= kMatLds;
 }
 
-static int mat_gpw(int B, int D, const MatShape& sh, int rb)
+static int mat_groups(int D) { return (D + kMatWidth - 1) / kMatWidth; }
+
+// How the samples of a launch are split: as few groups of channels to a workgroup as leave each compute unit one workgroup, or one
+// group where the energies of several do not fit beside the tokens
+MatPlan spu_mat_plan(const MatRun* runs, int n, int D)
 {
-    const int groups = (D + kMatWidth - 1) / kMatWidth;
-    return mat_lds(sh, rb, 2) > kMatLds ? 1 : (int)(((int64_t)B * groups + 255) / 256);
-}
-int spu_mat_tiles(int B, int N, int D, int sigma)
-{
-    MatShape sh;
-    int rb;
-    mat_shape(N, sigma, &sh, &rb);
-    const int groups = (D + kMatWidth - 1) / kMatWidth, gpw = mat_gpw(B, D, sh, rb);
-    return (groups + gpw - 1) / gpw;
+    MatPlan p{};
+    int lds_groups = 0;
+    for (int i = 0; i < n; ++i) {
+        MatShape sh;
+        int rb;
+        mat_shape(runs[i].N, runs[i].sigma, &sh, &rb);
+        p.rb = std::max(p.rb, rb);
+        p.samples += runs[i].count;
+        p.ld = std::max(p.ld, (runs[i].N + 3) / 4 * 4);
+    }
+    for (int i = 0; i < n; ++i) {
+        MatShape sh;
+        int rb;
+        mat_shape(runs[i].N, runs[i].sigma, &sh, &rb);
+        p.lds = std::max(p.lds, mat_lds(sh, p.rb, 1));
+        lds_groups = std::max(lds_groups, (int)mat_lds(sh, p.rb, 2));
+    }
+    const int groups = mat_groups(D);
+    p.gpw = (int)((p.samples * groups + 255) / 256);
+    if (p.gpw > 1 && (size_t)lds_groups > kMatLds) p.gpw = 1;
+    if (p.gpw > 1) p.lds = (size_t)lds_groups;
+    p.n_tiles = (groups + p.gpw - 1) / p.gpw;
+    return p;
 }
 
 // us of one call, from measurements: the rounds that the workgroups take on the chip, one per compute unit, each with its tables
 // and its hand-over.  bf16 8x1024x3584, sigma = 102: 35.6, 32x390x3584, 58: 48, 32x576x896, 57: 24, 16x1536x1536, 153: 61,
 // 4x234x1536, 17: 13, 1x1280x896, 32: 21.
+static double mat_tile_us(const MatShape& sh, int rb) { return sh.NT * (2.5 + 0.5 * rb); }
 double spu_mat_us(int B, int N, int D, int sigma)
 {
     MatShape sh;
     int rb;
     mat_shape(N, sigma, &sh, &rb);
-    const int gpw = mat_gpw(B, D, sh, rb);
-    const int64_t wgs = (int64_t)B * (((D + kMatWidth - 1) / kMatWidth + gpw - 1) / gpw);
-    return 3.0 + (wgs > (int64_t)B * kMatDirect ? 2.0 : 0.0) + (double)((wgs + 255) / 256) * (4.5 + gpw * sh.NT * (2.5 + 0.5 * rb));
+    const MatRun run{N, sigma, B, 0};
+    const MatPlan p = spu_mat_plan(&run, 1, D);
+    return 3.0 + (p.n_tiles > kMatDirect ? 2.0 : 0.0) + (double)(((int64_t)B * p.n_tiles + 255) / 256) * (4.5 + p.gpw * mat_tile_us(sh, rb));
 }
-
-luvc_status spu_score_mat(const void* x, int B, int N, int D, int64_t row_stride, int sigma, int use_hamming,
-                          float* partial, float* gpartial, const TileSync& sy, int n_tiles, int ld, float* scores, hipStream_t st)
+// what a run adds to a launch that several share; 0: it does not go there
+double spu_mat_work_us(int B, int N, int D, int sigma)
 {
     MatShape sh;
     int rb;
-    mat_shape(N, sigma, &sh, &rb);
-    sh.length = mat_length(sh);
-    const int gpw = mat_gpw(B, D, sh, rb);
-    const size_t lds = mat_lds(sh, rb, gpw);
-    const dim3 grid((unsigned)n_tiles, (unsigned)B);
-#define LUVC_MAT(RB) LUVC_LAUNCH("spu_mat", (spu_mat<RB>), grid, dim3(64 * kMatWaves), lds, st, (const bf16_t*)x, sh, D, row_stride, use_hamming, gpw, partial, gpartial, sy, ld, scores)
-    if (rb == 1) LUVC_MAT(1);
-    else if (rb == 2) LUVC_MAT(2);
-    else if (rb == 3) LUVC_MAT(3);
-    else LUVC_MAT(4);
+    if (!mat_shape(N, sigma, &sh, &rb) || rb > 2 || mat_lds(sh, 2, 1) > kMatLds) return 0.0;
+    return (double)B * mat_groups(D) / 256.0 * mat_tile_us(sh, 2);
+}
+
+template <int RB, int RUNS>
+static void mat_launch(const void* x, const MatRun* runs, int n, const MatPlan& p, int D, int64_t row_stride, int use_hamming,
+                       float* partial, float* gpartial, const TileSync& sy, float* scores, hipStream_t st)
+{
+    MatLaunch<RUNS> l;
+    l.n = n;
+    int64_t samples = 0;
+    for (int i = 0; i < n; ++i) {
+        int rb;
+        mat_shape(runs[i].N, runs[i].sigma, &l.run[i].sh, &rb);
+        l.run[i].sh.length = mat_length(l.run[i].sh);
+        l.run[i].wg0 = (int)(samples * p.n_tiles);
+        l.run[i].sample0 = (int)samples;
+        l.run[i].tok0 = runs[i].tok0;
+        samples += runs[i].count;
+    }
+    LUVC_LAUNCH("spu_mat", (spu_mat<RB, RUNS>), dim3((unsigned)(samples * p.n_tiles)), dim3(64 * kMatWaves), p.lds, st, (const bf16_t*)x, l, D, row_stride, use_hamming,
+                p.gpw, p.n_tiles, partial, gpartial, sy, p.ld, scores);
+}
+
+luvc_status spu_score_mat(const void* x, const MatRun* runs, int n, const MatPlan& p, int D, int64_t row_stride, int use_hamming,
+                          float* partial, float* gpartial, const TileSync& sy, float* scores, hipStream_t st)
+{
+#define LUVC_MAT(RB, RUNS) mat_launch<RB, RUNS>(x, runs, n, p, D, row_stride, use_hamming, partial, gpartial, sy, scores, st)
+    if (n > 1) {
+        if (p.rb == 1) LUVC_MAT(1, kMatMaxRuns);
+        else LUVC_MAT(2, kMatMaxRuns);
+    }
+    else if (p.rb == 1) LUVC_MAT(1, 1);
+    else if (p.rb == 2) LUVC_MAT(2, 1);
+    else if (p.rb == 3) LUVC_MAT(3, 1);
+    else LUVC_MAT(4, 1);
 #undef LUVC_MAT
     return check_launch("spu score (mat)");
 }

@@ -178,10 +178,10 @@ tile_tag_t spu_next_tag()
 // and a chain of steps that grows with N, which overlap in part (fitted to bf16 8x205x3584: 14, 1x729x3584: 20, 1x1000x1024: 16,
 // 4x861x1408: 34; fp32 1x300x2048: 13, 1x1000x1024: 29; channel by channel 8x205x3585: 16, 1x729x3585: 27; since its taps are ready
 // earlier it takes .5 to 2 us less); the others beside their launchers.
-static double circ_work_us(int64_t B, int N, int D, luvc_dtype dt) { return (dt == LUVC_F32 ? 12.0 : 6.0) * N * N * (double)D * (double)B / 1.1e9; }
+double spu_circ_work_us(int64_t B, int N, int D, luvc_dtype dt) { return (dt == LUVC_F32 ? 12.0 : 6.0) * N * N * (double)D * (double)B / 1.1e9; }
 static double circ_us(int64_t B, int N, int D, luvc_dtype dt, CircRows rows)
 {
-    const double work = 1.15 * circ_work_us(B, N, D, dt), chain = (dt == LUVC_F32 ? 0.0218 : 0.0105) * N;
+    const double work = 1.15 * spu_circ_work_us(B, N, D, dt), chain = (dt == LUVC_F32 ? 0.0218 : 0.0105) * N;
     return (dt == LUVC_F32 ? 6.3 : 5.5) + (rows == CircRows::Single ? 1.35 : 1.0) * std::sqrt(work * work + chain * chain);
 }
 static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces, double* us)
@@ -207,12 +207,11 @@ SpuRows spu_rows(const void* x, int D, int64_t row_stride, luvc_dtype dt)
 {
     return SpuRows{spu_circ_rows(x, D, row_stride, dt), dt == LUVC_BF16 && D % 8 == 0 && row_stride % 8 == 0 && row_stride < (1 << 19) && (uintptr_t)x % 16 == 0};
 }
-// in a launch that several runs share, a run adds its products and nothing else
-bool spu_circ_in_batch(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces)
+double spu_alone_us(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces)
 {
     double us;
     (void)long_path(B, N, D, sigma, dt, pieces, &us);
-    return N <= kCircMaxN && circ_work_us(B, N, D, dt) <= us;
+    return us;
 }
 
 // Energies per tile and group of tiles, arrival words.  Up to kTileGroup tiles have no group level.
@@ -238,7 +237,8 @@ SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows
         return L.bytes > most ? spu_layout(B, N, D, sigma, dt, SpuRows{CircRows::None, rows.pieces}, most) : L;
     }
     if (L.path == SpuPath::Mat) {
-        L.n_tiles = spu_mat_tiles(B, N, D, sigma);
+        const MatRun run{N, sigma, B, 0};
+        L.n_tiles = spu_mat_plan(&run, 1, D).n_tiles;
         L.bytes = tile_bytes(B, L.n_tiles, (N + 3) / 4 * 4, &L, 0);
         return L.bytes > most ? spu_layout(B, N, D, sigma, dt, SpuRows{rows.circ, false}, most) : L;
     }
@@ -276,6 +276,24 @@ size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most)
     return circ > need && circ <= most && spu_path(B, N, D, sigma, dt, SpuRows{CircRows::Paired, false}) == SpuPath::Circ ? circ : need;
 }
 
+size_t spu_mat_bytes(const MatRun* runs, int n, int D)
+{
+    const MatPlan p = spu_mat_plan(runs, n, D);
+    SpuLayout L{};
+    return tile_bytes((int)p.samples, p.n_tiles, p.ld, &L, 0);
+}
+luvc_status spu_score_mat_runs(const void* x, const MatRun* runs, int n, int D, int64_t row_stride, int use_hamming, float* scores, void* workspace, hipStream_t st)
+{
+    const MatPlan p = spu_mat_plan(runs, n, D);
+    SpuLayout L{};
+    tile_bytes((int)p.samples, p.n_tiles, p.ld, &L, 0);
+    char* ws = (char*)workspace;
+    TileSync sy;
+    sy.arrive = (tile_tag_t*)(ws + L.arrive);
+    sy.tag = spu_next_tag();
+    return spu_score_mat(x, runs, n, p, D, row_stride, use_hamming, (float*)(ws + L.partial), (float*)(ws + L.gpartial), sy, scores, st);
+}
+
 luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma,
                             int use_hamming, float* scores, void* workspace, size_t most, hipStream_t st)
 {
@@ -299,8 +317,10 @@ luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stri
     sy.arrive = (tile_tag_t*)(ws + L.arrive);
     sy.tag = spu_next_tag();
     if (L.path == SpuPath::Fft) return spu_score_fft(x, B, N, D, row_stride, dt, sigma, use_hamming, partial, gpartial, sy, L.n_tiles, scores, st);
-    if (L.path == SpuPath::Mat)
-        return spu_score_mat(x, B, N, D, row_stride, sigma, use_hamming, partial, gpartial, sy, L.n_tiles, (N + 3) / 4 * 4, scores, st);
+    if (L.path == SpuPath::Mat) {
+        const MatRun run{N, sigma, B, 0};
+        return spu_score_mat(x, &run, 1, spu_mat_plan(&run, 1, D), D, row_stride, use_hamming, partial, gpartial, sy, scores, st);
+    }
     if (L.path == SpuPath::Conv)
         return spu_score_conv(x, B, N, D, row_stride, dt, sigma, use_hamming, (float*)(ws + L.spec), partial, gpartial, sy, L.n_tiles, scores, st);
     LUVC_LAUNCH("spu_tables", spu_tables, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, N, sigma, use_hamming, tw, gk, gm);

@@ -8,7 +8,7 @@ import torch
 from paper_2512_09010_amd import binding as lv
 from paper_2512_09010_amd import workloads as wl
 from gpu_util import to_dev
-from test_gpu_spu import score_case
+from test_gpu_spu import SCORE_RTOL, score_case
 
 pytestmark = pytest.mark.gpu
 
@@ -91,3 +91,24 @@ def test_error_against_fp64(oracle, B, N, D, sigma):
     rms, mean = np.sqrt((err * err).mean()), err.mean()
     print(f"[spu] {N}x{D} error rms={rms:.2e} mean={mean:.2e}", flush=True)
     assert rms <= 2.0 ** -24 * np.sqrt(1.0 / 3.0 + 24.0 ** 2 / D + 0.8 ** 2)
+
+
+@pytest.mark.parametrize("lengths,D,names", [
+    ([520, 576, 576, 448, 312, 570, 392], 2056, ["spu_mat"]),                    # one launch; the last group of channels holds one piece
+    ([400 + 16 * i for i in range(18)] + [390, 390], 1032, ["spu_mat", "spu_mat"]),        # more runs than a launch takes
+    ([523, 576, 520, 448, 560, 570, 523, 40], 4104, ["spu_mat", "spu_circ"]),    # prime and short ones among them
+])
+def test_ragged_samples_in_one_launch(oracle, lengths, D, names):
+    rng = np.random.default_rng(D)
+    x = wl.cast_io((rng.standard_normal((sum(lengths), D)) * np.exp(rng.standard_normal((sum(lengths), 1)))).astype(np.float32), "bf16")
+    sigmas = [n // 10 for n in lengths]
+    print(f"[spu] ragged {lengths} D={D}", flush=True)
+    xd, out = to_dev(x, "bf16"), {}
+    got = kernels(lambda: out.update(lv.luvc_spu_stage_ragged(xd, lengths, sigmas, [max(1, n // 5) for n in lengths])))
+    assert sorted(got) == sorted(names + ["spu_prune_fused"])
+    scores, at = out["scores"].cpu().numpy().astype(np.float64), 0
+    for n, s in zip(lengths, sigmas):
+        ref = oracle.spu_score(wl.widen(x[None, at:at + n], "bf16"), s, True)[0]
+        err = np.abs(scores[at:at + n] - ref)
+        assert (err <= SCORE_RTOL * ref + 1e-6 * ref.max()).all(), (n, float((err / ref).max()))
+        at += n
