@@ -3,13 +3,13 @@
 // intermediate grid ever leaving the chip.
 //
 // Work split.  A workgroup owns one line position j of the first pass (output column j for a
-// row-then-column pair) and a run of output slots of the second pass.  Each wavefront owns four
-// consecutive lines of the first pass: for each of them it loads destination b = 2j+1, its two
+// row-then-column pair) and a run of output slots of the second pass.  Each wavefront owns four (on small
+// grids two) consecutive lines of the first pass: for each of them it loads destination b = 2j+1, its two
 // sources a = 2j, c = 2j+2 and the two destinations beyond them (l = 2j-1, r = 2j+3, needed only
 // to decide where a and c go), forms the first-pass token, rounds it to the storage type - the
 // second pass must read what a separate launch would have read from memory - and keeps it packed
 // in registers.  The four intermediate tokens of a wavefront are two destinations of the second
-// pass with the sources between them; the one token a wavefront needs from its neighbour (the
+// pass with the sources between them (two: one destination and the source above it); the one token a wavefront needs from its neighbour (the
 // first token of the next wavefront) goes through LDS, as do the norms and neighbour dot
 // products every wavefront needs from the tokens around its own.  A workgroup that owns only
 // part of a long line recomputes the three intermediate tokens just outside its run.
@@ -54,13 +54,13 @@ struct PairTable {
 // in the fp64 repeat): on batches of small grids a workgroup is 6 wavefronts, and four workgroups per compute unit instead
 // of three put 80 x 24 x 24 grids (960 workgroups) on the chip in one round - measured 36.8 -> 33.9 us.  The same
 // hint on wider tokens (96 instead of 103 registers) measured slower on every workload and is not given.
-template <typename T, int NQ, int TW, int NW, int MOST>
+template <typename T, int NQ, int TW, int NW, int R /* first-pass lines of a wavefront */, int MOST>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((4 * NQ + TW <= 8 && NW == 16) ? 6 : 1)))
 oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, const StepOut out, const PairTable<MOST> tab)
 {
     using TokT = Tok<NQ, TW>;
     constexpr int N = TokT::N;
-    constexpr int kRows = 4 * NW + 8;
+    constexpr int kRows = R * NW + 8;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     uint32_t* lds_tok = reinterpret_cast<uint32_t*>(lds_raw);     // [live waves][N][64]: first token of each wave
     __shared__ float inv32[kRows], dt32[kRows];                   // 1/|T[r]|, <T[r], T[r+1]> of the intermediate tokens
@@ -93,11 +93,11 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     const int row_base = 2 * u0;
     const int row_lo = u0 > 0 ? row_base - 1 : row_base;          // one intermediate row above the run decides its first source
     const int row_end = min(g.L2 - 1, row_base + 2 * nseg + 1);   // two below decide its last source (or close an odd line)
-    const int nwm = (row_end - row_base + 1 + 3) >> 2;            // wavefronts with rows of the run
+    const int nwm = (row_end - row_base + R) / R;                 // wavefronts with rows of the run
     const bool is_main = w < nwm;
     const bool is_halo = u0 > 0 && w == nwm;                      // holds row_base - 1 as ITS LAST row
     const bool active = is_main || is_halo;
-    const int r0 = is_halo ? row_base - 4 : row_base + 4 * w;
+    const int r0 = is_halo ? row_base - R : row_base + R * w;
     const int rr0 = r0 - row_base + 1;                            // LDS index of row r0 (negative only for the halo wave's unused rows)
     // Error bound of the screening, in units of u = 2^-24.  A sum takes at most E = R + 6 roundings of
     // relative size u on partial sums bounded by the sum of the magnitudes of its terms (R per lane: two
@@ -123,20 +123,20 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         return word;
     };
 
-    // ------------------------------------------------------------------ first pass: four intermediate tokens
+    // ------------------------------------------------------------------ first pass: R intermediate tokens
     const int pa = 2 * j, pb = pa + 1, pc = pa + 2;
     const bool has_l = j > 0, has_c = pc < g.L1, has_r = pc + 1 < g.L1;
     const int64_t img_in = at.in_off + (int64_t)b * g.n_in;
-    TokT T0, T1, T2, T3;
-    zero_tok(T0); zero_tok(T1); zero_tok(T2); zero_tok(T3);
-    int s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+    TokT Tk[R];
+    int sk[R];
     unsigned took_a = 0, took_c = 0;                              // bit k: row k absorbed its a / its c
-    // the four rows unrolled: the compiler renames T0..T3 instead of moving 10 registers per token and row
+    // the rows unrolled: the compiler renames tokens instead of moving 10 registers per token and row
     // (measured: 35.3 -> 34.2 us on 8 x 64 x 64 x 1280 bf16)
-#pragma unroll 4
-    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
         const int r = r0 + k;
-        TokT Tn, A, Bt, C, Lt, Rt;
+        TokT& Tn = Tk[k];
+        TokT A, Bt, C, Lt, Rt;
         int sn = 0, sa_in = 1, sb = 1, sc_in = 1;
         const bool there = active && r >= row_lo && r <= row_end;
         if (there) {
@@ -187,8 +187,7 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         } else {
             zero_tok(Tn);
         }
-        T0 = T1; T1 = T2; T2 = T3; T3 = Tn;
-        s0 = s1; s1 = s2; s2 = s3; s3 = sn;
+        sk[k] = sn;
     }
 
     if (!active) return;
@@ -196,12 +195,12 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     // ------------------------------------------------------------------ second pass: exchange
     if (is_main) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) lds_tok[(w * N + i) * 64 + lane] = T0.w[i];
+        for (int i = 0; i < N; ++i) lds_tok[(w * N + i) * 64 + lane] = Tk[0].w[i];
     }
     reached(1);
     const int above = is_halo ? -1 : w > 0 ? w - 1 : u0 > 0 ? nwm : -1, below = is_halo ? 0 : w + 1;
-    TokT Tx;                                                      // the token after T3: first token of the next wavefront
-    if (r0 + 4 <= row_end) {
+    TokT Tx;                                                      // the token after the last: first token of the next wavefront
+    if (r0 + R <= row_end) {
         wait_for(below, 1);
 #pragma unroll
         for (int i = 0; i < N; ++i) Tx.w[i] = lds_tok[(below * N + i) * 64 + lane];
@@ -209,21 +208,29 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         zero_tok(Tx);
     }
     {
-        float sm[8] = {dot32_lane<T>(T0, T0), dot32_lane<T>(T1, T1), dot32_lane<T>(T2, T2), dot32_lane<T>(T3, T3),
-                       dot32_lane<T>(T0, T1), dot32_lane<T>(T1, T2), dot32_lane<T>(T2, T3), dot32_lane<T>(T3, Tx)};
+        float sm[8];                                              // squared norms, products with the token below
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            sm[k] = k < R ? dot32_lane<T>(Tk[k < R ? k : 0], Tk[k < R ? k : 0]) : 0.f;
+            sm[4 + k] = k < R ? dot32_lane<T>(Tk[k < R ? k : 0], k + 1 < R ? Tk[k + 1 < R ? k + 1 : 0] : Tx) : 0.f;
+        }
         wave_total32x8(sm, lane);
-        const float n0 = sm[0], n1 = sm[1], n2 = sm[2], n3 = sm[3], d0 = sm[4], d1 = sm[5], d2 = sm[6], d3 = sm[7];
-        if (lane < 4) {
+        if (lane < R) {
             const int k = lane, r = r0 + k;
             if (r >= row_lo && r <= row_end) {
-                inv32[rr0 + k] = inv_norm32(k == 0 ? n0 : k == 1 ? n1 : k == 2 ? n2 : n3);
-                dt32[rr0 + k] = k == 0 ? d0 : k == 1 ? d1 : k == 2 ? d2 : d3;
-                szl[rr0 + k] = k == 0 ? s0 : k == 1 ? s1 : k == 2 ? s2 : s3;
+                float n2 = sm[0], dn = sm[4];
+                int sz = sk[0];
+#pragma unroll
+                for (int i = 1; i < R; ++i)
+                    if (k == i) { n2 = sm[i]; dn = sm[4 + i]; sz = sk[i]; }
+                inv32[rr0 + k] = inv_norm32(n2);
+                dt32[rr0 + k] = dn;
+                szl[rr0 + k] = sz;
             }
         }
     }
     reached(2);
-    const bool e2 = is_main && r0 + 2 <= row_end, e4 = r0 + 4 <= row_end;
+    const bool e2 = R > 2 && is_main && r0 + 2 <= row_end, e4 = r0 + R <= row_end;
     if (above >= 0) wait_for(above, 2);
     if (e4) wait_for(below, 2);
     // a source at intermediate row r (LDS index q) goes UP (to the lower position) unless the row below is strictly more similar
@@ -232,16 +239,23 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         const int qm = q > 0 ? q - 1 : 0;
         return screen_source(has_up, has_dn, inv32[q], dt32[qm], inv32[qm], dt32[q], inv32[q + 1], tau);
     };
-    const int v0 = is_main ? verdict32(r0, rr0) : -1, v2 = e2 ? verdict32(r0 + 2, rr0 + 2) : -1, v4 = e4 ? verdict32(r0 + 4, rr0 + 4) : -1;
+    const int v0 = is_main ? verdict32(r0, rr0) : -1, v2 = e2 ? verdict32(r0 + 2, rr0 + 2) : -1, v4 = e4 ? verdict32(r0 + R, rr0 + R) : -1;
     bool up0 = v0 > 0, up2 = v2 > 0, up4 = v4 > 0;
     if (v0 == 0 || v2 == 0 || v4 == 0) {                          // too close for fp32: fp64 decides
-        double n[5], d[4];
-        chain_sums64<T>(T0, T1, T2, T3, Tx, n, d);
-        if (lane < 4) {
+        double n[R], d[R];
+#pragma unroll
+        for (int k = 0; k < R; ++k) n[k] = norm64<T>(Tk[k]);
+#pragma unroll
+        for (int k = 0; k < R; ++k) d[k] = dot64<T>(Tk[k], k + 1 < R ? Tk[k + 1 < R ? k + 1 : 0] : Tx);
+        if (lane < R) {
             const int k = lane, r = r0 + k;
             if (r >= row_lo && r <= row_end) {
-                inv64[rr0 + k] = inv_norm64(k == 0 ? n[0] : k == 1 ? n[1] : k == 2 ? n[2] : n[3]);
-                dt64[rr0 + k] = k == 0 ? d[0] : k == 1 ? d[1] : k == 2 ? d[2] : d[3];
+                double n2 = n[0], dn = d[0];
+#pragma unroll
+                for (int i = 1; i < R; ++i)
+                    if (k == i) { n2 = n[i]; dn = d[i]; }
+                inv64[rr0 + k] = inv_norm64(n2);
+                dt64[rr0 + k] = dn;
             }
         }
         reached(kSums);
@@ -250,7 +264,7 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         const int wa = v0 == 0 ? wait_for(above, kSums) : 0, wb = v4 == 0 ? wait_for(below, kSums) : 0;
         if (v0 == 0) up0 = wa & kSettled ? (wa & kNextUp) != 0 : decide64(rr0);
         if (v2 == 0) up2 = decide64(rr0 + 2);
-        if (v4 == 0) up4 = wb & kSettled ? (wb & kFirstUp) != 0 : decide64(rr0 + 4);
+        if (v4 == 0) up4 = wb & kSettled ? (wb & kFirstUp) != 0 : decide64(rr0 + R);
     } else {
         reached(kSettled | (up0 ? kFirstUp : 0) | (up4 ? kNextUp : 0));
     }
@@ -265,17 +279,16 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     int32_t *sizes_out = out.sizes[dst], *kept_out = out.kept[dst], *pair_map = out.map[MOST > 1 ? at.map_dst : 0];
     const int uo = r0 >> 1;                                       // output slot (second axis) of destination r0 + 1
 #pragma unroll
-    for (int o = 0; o < 2; ++o) {
+    for (int o = 0; o < R / 2; ++o) {
         const int dest = r0 + 1 + 2 * o;
         if (dest >= own_end) break;
+        constexpr int kLast = R / 2 - 1;
         const bool take_a = o == 0 ? !up0 : !up2;                 // the source above comes down
-        const bool take_c = o == 0 ? (e2 && up2) : (e4 && up4);   // the source below goes up
-        const TokT& Bt = o == 0 ? T1 : T3;
-        const TokT& A = o == 0 ? T0 : T2;
-        const TokT& C = o == 0 ? T2 : Tx;
-        const int sb = o == 0 ? s1 : s3;
-        const int sa = take_a ? (o == 0 ? s0 : s2) : 0;
-        const int sc = take_c ? (o == 0 ? s2 : szl[rr0 + 4]) : 0;
+        const bool take_c = o < kLast ? (e2 && up2) : (e4 && up4);      // the source below goes up
+        const TokT &Bt = Tk[2 * o + 1], &A = Tk[2 * o], &C = o < kLast ? Tk[o < kLast ? 2 * o + 2 : 0] : Tx;
+        const int sb = sk[2 * o + 1];
+        const int sa = take_a ? sk[2 * o] : 0;
+        const int sc = take_c ? (o < kLast ? sk[o < kLast ? 2 * o + 2 : 0] : szl[rr0 + R]) : 0;
         const int slot = (uo + o) * g.oB + j * g.oA;
         T* op = x_out + (img_out + slot) * g.D;
         if (lane == 0) {
@@ -288,12 +301,12 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         if (!take_a && !take_c) {
             store_tok(op, tok_bytes, Bt, lane);
         } else {
-            TokT R;
-            merge_tok<T>(R, Bt, A, C, sb, sa, sc);
-            store_tok(op, tok_bytes, R, lane);
+            TokT merged;
+            merge_tok<T>(merged, Bt, A, C, sb, sa, sc);
+            store_tok(op, tok_bytes, merged, lane);
         }
     }
-    if (pair_map && lane < 4) {
+    if (pair_map && lane < R) {
         const int k = lane, r = r0 + k;
         if (r <= row_end && (r < own_end || (tail && r == own_end))) {
             // intermediate row r lands in output slot: odd rows are destinations; an even row goes up or down
@@ -312,16 +325,16 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
 // ------------------------------------------------------------------ host side
 namespace {
 
-template <typename T, int NQ, int TW, int MOST>
-luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
+constexpr int pair_waves(int words) { return words <= 10 ? 16 : 8; }      // 16 wavefronts leave 128 registers per lane, 8 leave 256
+
+template <typename T, int NQ, int TW, int R, int MOST>
+luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, int64_t lines, hipStream_t st)
 {
-    constexpr int N = 4 * NQ + TW;
-    constexpr int NW = N <= 10 ? 16 : 8;           // 16 wavefronts leave 128 registers per lane, 8 leave 256
+    constexpr int N = 4 * NQ + TW, NW = pair_waves(N);
     PairTable<MOST> tab;
     tab.n = n;
-    int64_t lines = 0, wgs = 0;
+    int64_t wgs = 0;
     int waves = 1;
-    for (int i = 0; i < n; ++i) lines += (int64_t)items[i].count * ((items[i].axis ? items[i].W : items[i].H) / 2);
     for (int i = 0; i < n; ++i) {
         const int H = items[i].H, W = items[i].W, axis = items[i].axis, Wo = W / 2;
         PairGeom& g = tab.it[i].g;
@@ -336,7 +349,7 @@ luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const
         g.n_in = H * W;
         g.n_out = (H / 2) * Wo;
         g.D = D;
-        const PairPlan p = plan_pair(g.L2, NW, lines);
+        const PairPlan p = plan_pair(g.L2, NW, lines, R);
         g.segs = p.segs;
         g.seg_out = p.seg_out;
         waves = p.waves > waves ? p.waves : waves;     // a workgroup with fewer rows leaves the rest idle
@@ -345,9 +358,30 @@ luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const
         wgs += (int64_t)items[i].count * g.segs * g.nd1;
     }
     const size_t lds = (size_t)waves * N * 64 * 4;             // at most 16 * 10 * 256 = 40 KiB
-    LUVC_LAUNCH("oim_halve_pair", (oim_halve_pair<T, NQ, TW, NW, MOST>), dim3((unsigned)wgs), dim3(64 * waves), lds, st,
+    LUVC_LAUNCH("oim_halve_pair", (oim_halve_pair<T, NQ, TW, NW, R, MOST>), dim3((unsigned)wgs), dim3(64 * waves), lds, st,
                 (const T*)in.x, in.sizes, in.kept, MOST > 1 ? out : step_out_of(out, items[0].at), tab);
     return check_launch("oim halving pair");
+}
+
+// Two rows per wavefront instead of four where all those wavefronts fit the chip at once: a small grid takes the time of one
+// wavefront's rows, one after the other.  us with four and with two rows, and the wavefronts of two: bf16 2x28x28x1280 10.8, 7.6 (630),
+// 1x40x24x1024 10.0, 7.2, 5x21x16x896 10.0, 7.1, fp32 1x24x24x1024 10.1, 7.3, 1x64x64x1280 11.8, 9.9, 2x56x56x1280 13.0, 12.8 (2240),
+// 11x24x38x1216 16.8, 14.7 (2508), 3x43x85x576 12.4, 10.7 (3528); beyond it 12x32x32x1024 15.5, 15.8 (3840), 2x67x107x896
+// 18.4, 21.8 (5300), 2x112x112x1280 28, 38, 8x64x64x1280 29, 39.
+constexpr int64_t kTwoRowWaves = 3600;
+template <typename T, int NQ, int TW>
+luvc_status launch_pair_rows(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
+{
+    int64_t lines = 0, waves2 = 0;
+    for (int i = 0; i < n; ++i) lines += (int64_t)items[i].count * ((items[i].axis ? items[i].W : items[i].H) / 2);
+    for (int i = 0; i < n; ++i) {
+        const PairPlan p = plan_pair(items[i].axis ? items[i].H : items[i].W, pair_waves(4 * NQ + TW), lines, 2);
+        waves2 += (int64_t)items[i].count * ((items[i].axis ? items[i].W : items[i].H) / 2) * p.segs * p.waves;
+    }
+    const bool two = waves2 <= kTwoRowWaves;
+#define LUVC_PAIR_ROWS(R) (n == 1 ? launch_pair<T, NQ, TW, R, 1>(items, n, in, out, D, lines, st) : launch_pair<T, NQ, TW, R, kOimMaxItems>(items, n, in, out, D, lines, st))
+    return two ? LUVC_PAIR_ROWS(2) : LUVC_PAIR_ROWS(4);
+#undef LUVC_PAIR_ROWS
 }
 
 template <typename T>
@@ -360,7 +394,7 @@ luvc_status dispatch_pair(const OimStepItem* items, int n, const StepIn& in, con
     if (rem > 512) ++nq;
     else if (rem > 256) tw = 2;
     else if (rem > 0) tw = 1;
-#define LUVC_PAIR(Q, W_) if (nq == Q && tw == W_) return n == 1 ? launch_pair<T, Q, W_, 1>(items, n, in, out, D, st) : launch_pair<T, Q, W_, kOimMaxItems>(items, n, in, out, D, st)
+#define LUVC_PAIR(Q, W_) if (nq == Q && tw == W_) return launch_pair_rows<T, Q, W_>(items, n, in, out, D, st)
     LUVC_PAIR(0, 1); LUVC_PAIR(0, 2);
     LUVC_PAIR(1, 0); LUVC_PAIR(1, 1); LUVC_PAIR(1, 2);
     LUVC_PAIR(2, 0); LUVC_PAIR(2, 1); LUVC_PAIR(2, 2);

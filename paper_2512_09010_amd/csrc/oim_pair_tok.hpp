@@ -369,12 +369,12 @@ __device__ __forceinline__ void merge_tok(Tok<NQ, TW>& out, const Tok<NQ, TW>& B
 struct PairPlan { int segs, seg_out, waves; };
 
 // Cut the nd2 outputs of a line so that a workgroup needs at most `nw` wavefronts: its own rows,
-// two rows below (one more wavefront at most) and the single-row wavefront above.
-PairPlan plan_pair(int L2, int nw, int64_t lines)
+// two rows below (one more wavefront at most) and the single-row wavefront above.  A wavefront has `rows` of them, two or four.
+PairPlan plan_pair(int L2, int nw, int64_t lines, int rows = 4)
 {
-    const int nd2 = L2 / 2, uncut = (L2 + 3) / 4;
-    int cap = 2 * (nw - 1) - 1;                    // (2 * seg_out + 2 + 3) / 4 + 1 <= nw
-    if (cap & 1) --cap;                            // even: workgroups start on a multiple of four rows
+    const int nd2 = L2 / 2, uncut = (L2 + rows - 1) / rows;
+    int cap = (rows * (nw - 1) - 2) / 2;           // (2 * seg_out + 2 + rows - 1) / rows + 1 <= nw
+    if (cap & 1) --cap;                            // even: workgroups start on a multiple of `rows`
     if (cap < 2) cap = 2;
     // A grid with fewer line positions than the chip has CUs would leave most of it idle with one workgroup per position.
     // The best cut is the finest that leaves a CU one workgroup: 2 x 112 x 112 x 1280 bf16 in runs of 28 26.1 us (8: 30.2,
@@ -404,7 +404,7 @@ PairPlan plan_pair(int L2, int nw, int64_t lines)
     p.seg_out = (nd2 + p.segs - 1) / p.segs;
     if (p.seg_out & 1) ++p.seg_out;
     p.segs = (nd2 + p.seg_out - 1) / p.seg_out;
-    p.waves = p.segs == 1 ? uncut : (2 * p.seg_out + 2 + 3) / 4 + 1;
+    p.waves = p.segs == 1 ? uncut : (2 * p.seg_out + 2 + rows - 1) / rows + 1;
     if (p.waves > nw) p.waves = nw;
     return p;
 }

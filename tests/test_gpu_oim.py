@@ -140,6 +140,8 @@ def test_pair_close_calls(oracle):
     (1, 64, 6, 40), (3, 61, 10, 24), (1, 24, 24, 32), (1, 64, 64, 16),      # short runs, with a wavefront for the row above
     (4, 64, 64, 16), (2, 112, 112, 16), (6, 40, 72, 16),                    # as many runs as compute units, or one per line
     (5, 64, 104, 16), (33, 16, 16, 16), (1, 12, 80, 1032),                  # uncut lines of 16 and 4 wavefronts, wide tokens
+    (300, 9, 8, 16), (180, 7, 13, 16), (40, 33, 15, 24), (12, 131, 12, 16), (240, 3, 24, 8), (400, 2, 20, 8),      # four rows a wavefront
+    (112, 9, 14, 16), (128, 9, 14, 16), (13, 30, 37, 16), (14, 30, 37, 16), (2, 131, 26, 16), (1, 30, 2, 2040),      # two rows, also at the end of its range
 ])
 def test_pair_decisions_shared_by_wavefronts(oracle, dtype, B, H, W, D):
     """A source between two wavefronts is decided by both; where fp32 cannot tell they exchange fp64 sums.  Lines of which some
