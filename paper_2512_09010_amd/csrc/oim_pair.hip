@@ -24,10 +24,16 @@
 // decision may live in two wavefronts, which then both put theirs in LDS.  A source shared by
 // two workgroups is decided from the same bits by the same expressions in both.
 //
-// Bound: memory, while tokens come in (8 x 64 x 64 x 1280 bf16: 84 MB in 20 us), and then the wait for the last of them.  The
-// older wavefronts of a workgroup get their tokens first, the youngest as they come to 20 us.  A wavefront therefore
+// Bound: instructions.  Loads alone, in this order, take 14 us for 8 x 64 x 64 x 1280 bf16 (84 MB); a row of a wavefront is about 300
+// vector instructions beside its 15 loads (90 the products, 60 the totals and the verdicts, the rest the merge), and without the
+// products of the first pass a call takes 24 us of 29.  So all decisions of a row are worked out side by side, a sum per lane
+// (`wave_totals32`), rather than one after the other on values all lanes hold: 32 x 64 x 64 x 384 54.2 -> 49.4 us, 8 x 64 x 64 x 1280
+// 30.5 -> 29.2, 80 x 24 x 24 x 1024 35.0 -> 33.7, fp32 40 x 24 x 24 x 768 23.2 -> 22.4.  (The same totals by the matrix cores, nine
+// 16 x 16 x 4 products against unit columns, are fewer instructions and slower, 58: they take the vector unit's time.  The next
+// row's tokens asked for before a row is merged: 57, 31.3 and, for want of registers, 49.)
+// The older wavefronts of a workgroup get their tokens first, the youngest as they come to 20 us.  A wavefront therefore
 // waits only for its two neighbours (`stage`), not at barriers for all: the merges and stores of the older ones run
-// while the younger ones' tokens are on their way: a call of 34.5 us takes 30.5 (32 x 64 x 64 x 384 61.5 -> 54.8; 80 x 24 x 24 x
+// while the younger ones' tokens are on their way: a call of 34.5 us took 30.5 (32 x 64 x 64 x 384 61.5 -> 54.8; 80 x 24 x 24 x
 // 1024, workgroups of 6 wavefronts, 35.9 -> 34.7; 128 x 16 x 16 x 1152, of 4, the same).  Tokens of a few hundred bytes, which come in
 // together, pay for the words: 16 x 17 x 15 x 128 bf16 6.9 -> 7.4, 80 x 24 x 24 x 256 19.5 -> 20.1.
 //
@@ -159,16 +165,18 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         if (there) {
             // screening: every sum is formed lower position first, so the sum two workgroups share has the same bits
             // (tokens that are not there were loaded as zeros: their sums are zero and never looked at)
-            float sm[8] = {dot32_lane<T>(A, A), dot32_lane<T>(Bt, Bt), dot32_lane<T>(A, Bt), dot32_lane<T>(Lt, A),
-                           dot32_lane<T>(Lt, Lt), dot32_lane<T>(C, C), dot32_lane<T>(Bt, C), dot32_lane<T>(C, Rt)};
-            wave_total32x8(sm, lane);
-            const float ia = inv_norm32(sm[0]), ib = inv_norm32(sm[1]), dab = sm[2];
+            const float sm[9] = {dot32_lane<T>(Lt, Lt), dot32_lane<T>(A, A), dot32_lane<T>(Bt, Bt), dot32_lane<T>(C, C), dot32_lane<T>(Rt, Rt),
+                                 dot32_lane<T>(Lt, A), dot32_lane<T>(A, Bt), dot32_lane<T>(Bt, C), dot32_lane<T>(C, Rt)};
+            // lanes 0 .. 4: the squared norms, lanes 5 .. 8: the products of neighbours; lane i < 4 then works on token i and the next,
+            // of which the odd one is the source; lane 0 has the verdict on a, lane 2 the one on c
+            const float tot = wave_totals32(sm, lane);
+            const float inv = inv_norm32(tot), inv_next = from_lane_above<1>(inv);
+            const bool odd = lane & 1;
+            const float cosine = screen_cosine(from_lane_above<5>(tot), odd ? inv : inv_next, odd ? inv_next : inv);
+            const Verdicts sure = screen_verdicts(cosine, from_lane_above<1>(cosine), tau);
             int va = -1, vc = -1;
-            if (has_l) va = screen_source(true, true, ia, sm[3], inv_norm32(sm[4]), dab, ib, tau);
-            if (has_c) {
-                vc = 1;
-                if (has_r) vc = screen_source(true, true, inv_norm32(sm[5]), sm[6], ib, sm[7], inv_norm32(dot32<T>(Rt, Rt)), tau);
-            }
+            if (has_l) va = (int)(sure.left & 1u) - (int)(sure.right & 1u);
+            if (has_c) vc = has_r ? (int)(sure.left >> 2 & 1u) - (int)(sure.right >> 2 & 1u) : 1;
             bool a_left = va > 0, c_left = vc > 0;
             if (va == 0 || vc == 0) {                             // too close for fp32: the fp64 cosines decide
                 double n[5], d[4];
@@ -208,21 +216,20 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         zero_tok(Tx);
     }
     {
-        float sm[8];                                              // squared norms, products with the token below
+        float sm[8];                                              // squared norms (lanes 0 .. 3), products with the token below (lanes 4 .. 7)
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             sm[k] = k < R ? dot32_lane<T>(Tk[k < R ? k : 0], Tk[k < R ? k : 0]) : 0.f;
             sm[4 + k] = k < R ? dot32_lane<T>(Tk[k < R ? k : 0], k + 1 < R ? Tk[k + 1 < R ? k + 1 : 0] : Tx) : 0.f;
         }
-        wave_total32x8(sm, lane);
+        const float n2 = wave_totals32(sm, lane), dn = from_lane_above<4>(n2);
         if (lane < R) {
             const int k = lane, r = r0 + k;
             if (r >= row_lo && r <= row_end) {
-                float n2 = sm[0], dn = sm[4];
                 int sz = sk[0];
 #pragma unroll
                 for (int i = 1; i < R; ++i)
-                    if (k == i) { n2 = sm[i]; dn = sm[4 + i]; sz = sk[i]; }
+                    if (k == i) sz = sk[i];
                 inv32[rr0 + k] = inv_norm32(n2);
                 dt32[rr0 + k] = dn;
                 szl[rr0 + k] = sz;
@@ -233,13 +240,12 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     const bool e2 = R > 2 && is_main && r0 + 2 <= row_end, e4 = r0 + R <= row_end;
     if (above >= 0) wait_for(above, 2);
     if (e4) wait_for(below, 2);
-    // a source at intermediate row r (LDS index q) goes UP (to the lower position) unless the row below is strictly more similar
-    auto verdict32 = [&](int r, int q) -> int {
-        const bool has_up = r >= 1, has_dn = r + 1 < g.L2;
-        const int qm = q > 0 ? q - 1 : 0;
-        return screen_source(has_up, has_dn, inv32[q], dt32[qm], inv32[qm], dt32[q], inv32[q + 1], tau);
-    };
-    const int v0 = is_main ? verdict32(r0, rr0) : -1, v2 = e2 ? verdict32(r0 + 2, rr0 + 2) : -1, v4 = e4 ? verdict32(r0 + R, rr0 + R) : -1;
+    // a source at intermediate row r0 + lane (LDS index q) goes UP (to the lower position) unless the row below is strictly more similar
+    const int q = rr0 + (lane < R ? lane : R), qc = q > 0 ? q : 0, qm = q > 0 ? q - 1 : 0;        // (of the halo only the row after its last)
+    const float own = inv32[qc];
+    const Verdicts sure = screen_verdicts(screen_cosine(dt32[qm], own, inv32[qm]), screen_cosine(dt32[qc], own, inv32[qc + 1]), tau);
+    auto verdict = [&](int k) { return r0 + k < 1 ? -1 : r0 + k + 1 >= g.L2 ? 1 : (int)(sure.left >> k & 1u) - (int)(sure.right >> k & 1u); };
+    const int v0 = is_main ? verdict(0) : -1, v2 = e2 ? verdict(2) : -1, v4 = e4 ? verdict(R) : -1;
     bool up0 = v0 > 0, up2 = v2 > 0, up4 = v4 > 0;
     if (v0 == 0 || v2 == 0 || v4 == 0) {                          // too close for fp32: fp64 decides
         double n[R], d[R];

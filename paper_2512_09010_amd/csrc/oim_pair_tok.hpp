@@ -90,21 +90,6 @@ __device__ __forceinline__ void store_tok(void* p, int bytes, const Tok<NQ, TW>&
 }
 
 // ------------------------------------------------------------------ sums
-// wave64 sum without the LDS crossbar: DPP adds inside each row of 16 lanes, two row broadcasts,
-// and the total (held by lane 63) read back as a wave-uniform value.  One fixed order everywhere.
-__device__ __forceinline__ float wave_total32(float v)
-{
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, false));    // quad_perm [1,0,3,2]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, false));    // quad_perm [2,3,0,1]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false));   // row_half_mirror
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, false));   // row_mirror
-    // every lane of a row now holds the row's sum; lane 15 of row r is added into row r+1, then
-    // lane 31 into rows 2 and 3: lane 63 ends with all four
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x142, 0xa, 0xf, false));   // row_bcast:15 -> rows 1, 3
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x143, 0xc, 0xf, false));   // row_bcast:31 -> rows 2, 3
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-
 template <typename T> __device__ __forceinline__ float dot_word(float acc, uint32_t x, uint32_t y);
 template <> __device__ __forceinline__ float dot_word<bf16_t>(float acc, uint32_t x, uint32_t y)
 {
@@ -118,14 +103,15 @@ template <> __device__ __forceinline__ float dot_word<float>(float acc, uint32_t
     return fmaf(__uint_as_float(x), __uint_as_float(y), acc);
 }
 
-// Eight wave64 sums at once.  Three exchange steps inside a quad / half row keep, in every lane, only
-// the partial sum of value (lane & 7): each step halves the number of registers instead of adding every
-// value in every lane.  Then one add across the half rows, one across the two halves of the wave
-// and one across neighbouring rows (lane-swap instructions), and lane i holds the total of value i.
-// Six additions per term, like the one-value sum above.
-__device__ __forceinline__ void wave_total32x8(float (&v)[8], int lane)
+// Wave64 sums of eight or nine values at once.  Exchange steps inside a half row keep, in every lane, only the partial sum of value
+// lane & 7: each step halves the number of registers instead of adding every value in every lane; one more between the half rows
+// keeps the ninth in the upper ones.  Then an add across the two halves of the wavefront and one across neighbouring rows (lane-swap
+// instructions).  Lane i < 8 holds the total of value i, lane 8 that of value 8 (or of value 0).  Six additions per term.
+template <int M>
+__device__ __forceinline__ float wave_totals32(const float (&v)[M], int lane)
 {
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+    static_assert(M == 8 || M == 9, "");
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
     float p[4], q[2];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -139,13 +125,25 @@ __device__ __forceinline__ void wave_total32x8(float (&v)[8], int lane)
     }
     const float keep = b2 ? q[1] : q[0], send = b2 ? q[0] : q[1];
     float r = keep + dpp_get(dpp_get(send, 2), 3);                  // (lane ^ 7) ^ 3 = lane ^ 4
-    r += dpp_get(r, 4);
+    if constexpr (M == 9) {
+        float t = v[8] + dpp_get(v[8], 0);
+        t += dpp_get(t, 1);
+        t += dpp_get(dpp_get(t, 2), 3);
+        const float keep = b3 ? t : r, send = b3 ? r : t;
+        r = keep + dpp_get(send, 4);
+    } else {
+        r += dpp_get(r, 4);
+    }
     const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(r), __float_as_uint(r), false, false);
     r = __uint_as_float(h[0]) + __uint_as_float(h[1]);
     const auto g = __builtin_amdgcn_permlane16_swap(__float_as_uint(r), __float_as_uint(r), false, false);
-    r = __uint_as_float(g[0]) + __uint_as_float(g[1]);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), i));
+    return __uint_as_float(g[0]) + __uint_as_float(g[1]);
+}
+// the value of lane l + N of the row of 16 lanes, in lane l (zero past its end)
+template <int N>
+__device__ __forceinline__ float from_lane_above(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x100 + N, 0xf, 0xf, true));     // row_shl:N
 }
 
 // this lane's part of <x, y>
@@ -158,16 +156,6 @@ __device__ __forceinline__ float dot32_lane(const Tok<NQ, TW>& x, const Tok<NQ, 
     return acc;
 }
 
-// screening sum <x, y> in fp32 (wave-uniform result)
-template <typename T, int NQ, int TW>
-__device__ __forceinline__ float dot32(const Tok<NQ, TW>& x, const Tok<NQ, TW>& y)
-{
-    float acc = 0.f;
-#pragma unroll
-    for (int i = 0; i < Tok<NQ, TW>::N; ++i) acc = dot_word<T>(acc, x.w[i], y.w[i]);
-    return wave_total32(acc);
-}
-
 // element e of a word, widened
 template <typename T> __device__ __forceinline__ double elem64(uint32_t w, int e);
 template <> __device__ __forceinline__ double elem64<bf16_t>(uint32_t w, int e)
@@ -176,7 +164,8 @@ template <> __device__ __forceinline__ double elem64<bf16_t>(uint32_t w, int e)
 }
 template <> __device__ __forceinline__ double elem64<float>(uint32_t w, int) { return (double)__uint_as_float(w); }
 
-// wave64 sum of fp64 values, same DPP pattern as wave_total32 applied to both halves of the value
+// wave64 sum of fp64 values: DPP adds inside each row of 16 lanes, two row broadcasts, the total read back from lane 63; DPP moves
+// work on the halves of a value
 __device__ __forceinline__ double dpp_move64(double v, const int ctrl_sel)
 {
     const int lo = __double2loint(v), hi = __double2hiint(v);
@@ -258,21 +247,19 @@ __device__ __forceinline__ double inv_norm64(double n2)
     return 1.0 / (n < 1e-12 ? 1e-12 : n);
 }
 
-// Screening verdict for one source between its lower-position ("left") and higher-position
-// ("right") destination: +1 = left for certain, -1 = right for certain, 0 = too close to call.
-// Every operation rounds on its own: wherever this is inlined, the same sums give the same verdict.
-__device__ __forceinline__ int screen_source(bool has_left, bool has_right, float inv_src,
-                                             float dot_l, float inv_l, float dot_r, float inv_r, float tau)
+// Screening of sources between their lower-position ("left") and higher-position ("right") destinations: cosine on the left minus
+// cosine on the right, above tau = left for certain, below -tau = right for certain, else (NaN too) too close to call.
+__device__ __forceinline__ float screen_cosine(float dot, float inv_src, float inv_dst)
 {
 #pragma clang fp contract(off)
-    if (!has_left) return -1;
-    if (!has_right) return 1;
-    const float sl = (dot_l * inv_src) * inv_l;
-    const float sr = (dot_r * inv_src) * inv_r;
-    const float d = sl - sr;
-    if (d > tau) return 1;
-    if (d < -tau) return -1;
-    return 0;                                   // includes NaN
+    return (dot * inv_src) * inv_dst;
+}
+struct Verdicts { unsigned long long left, right; };                // a lane a source: certain verdicts
+__device__ __forceinline__ Verdicts screen_verdicts(float cos_left, float cos_right, float tau)
+{
+#pragma clang fp contract(off)
+    const float d = cos_left - cos_right;
+    return {__ballot(d > tau), __ballot(d < -tau)};
 }
 
 // The fp64 decision: cosines formed as (dot * 1/|src|) * 1/|dst|, the same expression on the same

@@ -36,7 +36,7 @@ __device__ __forceinline__ double add_far_lanes64(double r)
     return __hiloint2double((int)h16[0], (int)l16[0]) + __hiloint2double((int)h16[1], (int)l16[1]);
 }
 
-// Eight wave64 sums at once, the scheme of wave_total32x8: three exchange steps (lanes 1, 2, 4 apart) after which a
+// Eight wave64 sums at once, as in wave_totals32: three exchange steps (lanes 1, 2, 4 apart) after which a
 // lane keeps only the partial sum of value (lane & 7), then lanes 8, 32 and 16 apart.  Every step adds the partial sums
 // of two lane groups, so all eight values - and wave_total64b below - are summed over the same tree: a sum has the
 // same bits in whichever of these places it is formed, which two workgroups that look at one source rely on.
