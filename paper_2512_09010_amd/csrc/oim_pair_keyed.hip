@@ -9,34 +9,44 @@
 // all similarity sums are formed in fp64 straight away - there is no fp32 screening - and the features of tokens
 // that are only looked at for a decision (the two destinations beyond the sources of the first pass, the rows just
 // outside a workgroup's run) are never loaded.
+//
+// Bound: as in oim_halve_pair, the instructions of a row beside the tokens' way here (8 x 64 x 64 x 1280 bf16, keys of 128: 93 MB): fp64 sums
+// of the metric, reciprocal roots, the merges.  So the sums come one to a lane, which then forms the root, the cosine and the
+// verdict all lanes used to form one after the other; and a wavefront waits for its neighbours, not at barriers for all.  With
+// the value enhancement behind it a call takes 44.8 us (46.4 before).
 #include "oim_pair_tok.hpp"
 
 namespace luvc {
 
 namespace {
 
-// fp64 squared norms n[p] = <P_p, P_p> and neighbour products d[p] = <P_p, P_p+1> of five metric rows that follow
-// each other on a line; n[4], the ninth sum, only with FIVE
+// fp64 squared norms <P_p, P_p> and neighbour products <P_p, P_p+1> of five metric rows that follow each other on a line, a sum
+// per lane.  FIVE: the norms in lanes 0 .. 4, the products in 5 .. 8; else four norms in lanes 0 .. 3, the products in 4 .. 7
 template <typename T, bool FIVE, int MQ, int MW>
-__device__ __forceinline__ void metric_sums64(const Tok<MQ, MW>& P0, const Tok<MQ, MW>& P1, const Tok<MQ, MW>& P2, const Tok<MQ, MW>& P3,
-                                              const Tok<MQ, MW>& P4, double (&n)[5], double (&d)[4], int lane)
+__device__ __forceinline__ double metric_sums64(const Tok<MQ, MW>& P0, const Tok<MQ, MW>& P1, const Tok<MQ, MW>& P2, const Tok<MQ, MW>& P3,
+                                                const Tok<MQ, MW>& P4, int lane)
 {
-    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, t = 0.0;
+    constexpr int M = FIVE ? 9 : 8, F = FIVE ? 5 : 4;
+    double s[M] = {};
 #pragma unroll
     for (int i = 0; i < Tok<MQ, MW>::N; ++i) {
 #pragma unroll
         for (int e = 0; e < words<T>::per; ++e) {
-            const double p0 = elem64<T>(P0.w[i], e), p1 = elem64<T>(P1.w[i], e), p2 = elem64<T>(P2.w[i], e), p3 = elem64<T>(P3.w[i], e),
-                         p4 = elem64<T>(P4.w[i], e);
-            s[0] = fma(p0, p0, s[0]); s[1] = fma(p1, p1, s[1]); s[2] = fma(p2, p2, s[2]); s[3] = fma(p3, p3, s[3]);
-            s[4] = fma(p0, p1, s[4]); s[5] = fma(p1, p2, s[5]); s[6] = fma(p2, p3, s[6]); s[7] = fma(p3, p4, s[7]);
-            if (FIVE) t = fma(p4, p4, t);
+            const double p[5] = {elem64<T>(P0.w[i], e), elem64<T>(P1.w[i], e), elem64<T>(P2.w[i], e), elem64<T>(P3.w[i], e), elem64<T>(P4.w[i], e)};
+#pragma unroll
+            for (int k = 0; k < F; ++k) s[k] = fma(p[k], p[k], s[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s[F + k] = fma(p[k], p[k + 1], s[F + k]);
         }
     }
-    wave_total64x8(s, lane);
-    n[0] = s[0]; n[1] = s[1]; n[2] = s[2]; n[3] = s[3];
-    d[0] = s[4]; d[1] = s[5]; d[2] = s[6]; d[3] = s[7];
-    n[4] = FIVE ? wave_total64b(t) : 0.0;
+    return wave_totals64(s, lane);
+}
+
+// the value of lane l + N of the row of 16 lanes, in lane l
+template <int N>
+__device__ __forceinline__ double from_lane_above64(double v)
+{
+    return __hiloint2double(__float_as_int(from_lane_above<N>(__int_as_float(__double2hiint(v)))), __float_as_int(from_lane_above<N>(__int_as_float(__double2loint(v)))));
 }
 
 }  // namespace
@@ -55,6 +65,7 @@ oim_halve_pair_keyed(const T* __restrict__ x, const T* __restrict__ metric, cons
     uint32_t* lds_tok = reinterpret_cast<uint32_t*>(lds_raw);     // [live waves][NX + NM][64]: first token of each wave, features then metric
     __shared__ double inv64[kRows], dt64[kRows];                  // 1/|M[r]|, <M[r], M[r+1]> of the intermediate metric rows
     __shared__ int szl[kRows];
+    __shared__ int stage[NW];                                     // what a wavefront has written: 1 its first token, 2 inv64, dt64 and szl
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -75,6 +86,16 @@ oim_halve_pair_keyed(const T* __restrict__ x, const T* __restrict__ metric, cons
     const int r0 = is_halo ? row_base - 4 : row_base + 4 * w;
     const int rr0 = r0 - row_base + 1;                            // LDS index of row r0 (negative only for the halo wave's unused rows)
     const int x_bytes = g.D * (int)sizeof(T), m_bytes = Dm * (int)sizeof(T);
+    if (threadIdx.x < NW) stage[threadIdx.x] = 0;
+    auto reached = [&](int v) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0) __hip_atomic_store(stage + w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // every wavefront with rows gets to 1 without waiting and to 2 after a wait for a 1, and waits for no more than a 2: every wait ends
+    auto wait_for = [&](int other, int v) {
+        while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(stage + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < v) {}
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
 
     // ------------------------------------------------------------------ first pass: four intermediate tokens
     const int pa = 2 * j, pb = pa + 1, pc = pa + 2;
@@ -86,6 +107,9 @@ oim_halve_pair_keyed(const T* __restrict__ x, const T* __restrict__ metric, cons
     zero_tok(M0); zero_tok(M1); zero_tok(M2); zero_tok(M3);
     int s0 = 0, s1 = 0, s2 = 0, s3 = 0;
     unsigned took_a = 0, took_c = 0;                              // bit k: row k absorbed its a / its c
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();                                 // `stage` is cleared for everyone before it is used
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 #pragma unroll 4
     for (int k = 0; k < 4; ++k) {
         const int r = r0 + k;
@@ -114,12 +138,13 @@ oim_halve_pair_keyed(const T* __restrict__ x, const T* __restrict__ metric, cons
             const int sa_in = sizes_in ? sizes_in[ta] : 1;
             const int sc_in = (sizes_in && has_c) ? sizes_in[tc] : 1;
             // every sum is formed lower position first, so the sum two workgroups share has the same bits
-            // (tokens that are not there were loaded as zeros: their sums are zero and never looked at)
-            double n[5], d[4];
-            metric_sums64<T, true>(Ml, Ma, Mb, Mc, Mr, n, d, lane);
-            const double jb = inv_norm64(n[2]);
-            const bool a_left = has_l && source_goes_left(true, true, inv_norm64(n[1]), d[0], inv_norm64(n[0]), d[1], jb);
-            const bool c_left = has_c && (!has_r || source_goes_left(true, true, inv_norm64(n[3]), d[2], jb, d[3], inv_norm64(n[4])));
+            // (tokens that are not there were loaded as zeros: their sums are zero and never looked at).  Lane i < 4 works on
+            // tokens i and i + 1, of which the odd one is the source; lane 0 has the verdict on a, lane 2 the one on c
+            const double tot = metric_sums64<T, true>(Ml, Ma, Mb, Mc, Mr, lane), inv = inv_norm64(tot), inv_next = from_lane_above64<1>(inv);
+            const bool odd = lane & 1;
+            const double cosine = (from_lane_above64<5>(tot) * (odd ? inv : inv_next)) * (odd ? inv_next : inv);
+            const unsigned long long right = __ballot(from_lane_above64<1>(cosine) > cosine);
+            const bool a_left = has_l && !(right & 1u), c_left = has_c && !(has_r && (right & 4u));
             const bool take_a = !a_left, take_c = c_left;
             const int sa = take_a ? sa_in : 0, sc = take_c ? sc_in : 0;
             sn = sb + sa + sc;
@@ -138,6 +163,8 @@ oim_halve_pair_keyed(const T* __restrict__ x, const T* __restrict__ metric, cons
         s0 = s1; s1 = s2; s2 = s3; s3 = sn;
     }
 
+    if (!active) return;
+
     // ------------------------------------------------------------------ second pass: exchange
     if (is_main) {
 #pragma unroll
@@ -145,42 +172,41 @@ oim_halve_pair_keyed(const T* __restrict__ x, const T* __restrict__ metric, cons
 #pragma unroll
         for (int i = 0; i < NM; ++i) lds_tok[(w * NL + NX + i) * 64 + lane] = M0.w[i];
     }
-    __syncthreads();
+    reached(1);
+    const int above = is_halo ? -1 : w > 0 ? w - 1 : u0 > 0 ? nwm : -1, below = is_halo ? 0 : w + 1;
+    const bool e2 = r0 + 2 <= row_end, e4 = r0 + 4 <= row_end;
     TokX Tx;                                                      // the token after T3: first token of the next wavefront
     TokM Mx;
     zero_tok(Tx);
     zero_tok(Mx);
-    if (active && r0 + 4 <= row_end) {
-        const int nxt = is_halo ? 0 : w + 1;
+    if (e4) {
+        wait_for(below, 1);
 #pragma unroll
-        for (int i = 0; i < NX; ++i) Tx.w[i] = lds_tok[(nxt * NL + i) * 64 + lane];
+        for (int i = 0; i < NX; ++i) Tx.w[i] = lds_tok[(below * NL + i) * 64 + lane];
 #pragma unroll
-        for (int i = 0; i < NM; ++i) Mx.w[i] = lds_tok[(nxt * NL + NX + i) * 64 + lane];
+        for (int i = 0; i < NM; ++i) Mx.w[i] = lds_tok[(below * NL + NX + i) * 64 + lane];
     }
-    if (active) {
-        double n[5], d[4];
-        metric_sums64<T, false>(M0, M1, M2, M3, Mx, n, d, lane);
+    {
+        const double n2 = metric_sums64<T, false>(M0, M1, M2, M3, Mx, lane), dn = from_lane_above64<4>(n2), inv = inv_norm64(n2);
         if (lane < 4) {
             const int k = lane, r = r0 + k;
             if (r >= row_lo && r <= row_end) {
-                inv64[rr0 + k] = inv_norm64(k == 0 ? n[0] : k == 1 ? n[1] : k == 2 ? n[2] : n[3]);
-                dt64[rr0 + k] = k == 0 ? d[0] : k == 1 ? d[1] : k == 2 ? d[2] : d[3];
+                inv64[rr0 + k] = inv;
+                dt64[rr0 + k] = dn;
                 szl[rr0 + k] = k == 0 ? s0 : k == 1 ? s1 : k == 2 ? s2 : s3;
             }
         }
     }
-    __syncthreads();
-    if (!is_main) return;
-    // a source at intermediate row r (LDS index q) goes UP (to the lower position) unless the row below is strictly more similar
-    auto decide64 = [&](int r, int q) -> bool {
-        const bool has_up = r >= 1, has_dn = r + 1 < g.L2;
-        const int qm = q > 0 ? q - 1 : 0;
-        return source_goes_left(has_up, has_dn, inv64[q], dt64[qm], inv64[qm], dt64[q], inv64[q + 1]);
-    };
-    const bool e2 = r0 + 2 <= row_end, e4 = r0 + 4 <= row_end;
-    const bool up0 = decide64(r0, rr0);
-    const bool up2 = e2 && decide64(r0 + 2, rr0 + 2);
-    const bool up4 = e4 && decide64(r0 + 4, rr0 + 4);
+    reached(2);
+    if (is_halo) return;
+    if (above >= 0) wait_for(above, 2);
+    if (e4) wait_for(below, 2);
+    // a source at intermediate row r0 + lane (LDS index q) goes UP (to the lower position) unless the row below is strictly more similar
+    const int q = rr0 + (lane < 4 ? lane : 4), qm = q > 0 ? q - 1 : 0;
+    const double own = inv64[q];
+    const unsigned long long right = __ballot((dt64[q] * own) * inv64[q + 1] > (dt64[qm] * own) * inv64[qm]);
+    auto goes_up = [&](int k) { return r0 + k >= 1 && (r0 + k + 1 >= g.L2 || !(right >> k & 1u)); };
+    const bool up0 = goes_up(0), up2 = e2 && goes_up(2), up4 = e4 && goes_up(4);
 
     // ------------------------------------------------------------------ second pass: merge, write, maps
     const bool tail = (g.L2 & 1) && own_end == g.L2 - 1;          // the last source of an odd line belongs to this run

@@ -36,13 +36,15 @@ __device__ __forceinline__ double add_far_lanes64(double r)
     return __hiloint2double((int)h16[0], (int)l16[0]) + __hiloint2double((int)h16[1], (int)l16[1]);
 }
 
-// Eight wave64 sums at once, as in wave_totals32: three exchange steps (lanes 1, 2, 4 apart) after which a
-// lane keeps only the partial sum of value (lane & 7), then lanes 8, 32 and 16 apart.  Every step adds the partial sums
-// of two lane groups, so all eight values - and wave_total64b below - are summed over the same tree: a sum has the
-// same bits in whichever of these places it is formed, which two workgroups that look at one source rely on.
-__device__ __forceinline__ void wave_total64x8(double (&v)[8], int lane)
+// Eight or nine wave64 sums at once, that of v[i] in lane i: three exchange steps (lanes 1, 2, 4 apart) after which a
+// lane keeps only the partial sum of value (lane & 7), one between the half rows that keeps the ninth in the upper ones, then lanes
+// 32 and 16 apart.  Every step adds the partial sums of two lane groups, so all values are summed over the same tree: a sum has
+// the same bits in whichever of these places it is formed, which two workgroups that look at one source rely on.
+template <int M>
+__device__ __forceinline__ double wave_totals64(const double (&v)[M], int lane)
 {
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+    static_assert(M == 8 || M == 9, "");
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
     double p[4], q[2];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -56,22 +58,24 @@ __device__ __forceinline__ void wave_total64x8(double (&v)[8], int lane)
     }
     const double keep = b2 ? q[1] : q[0], send = b2 ? q[0] : q[1];
     double r = keep + dpp_get64(dpp_get64(send, 2), 3);             // (lane ^ 7) ^ 3 = lane ^ 4
-    r += dpp_get64(r, 4);
-    r = add_far_lanes64(r);
+    if constexpr (M == 9) {
+        double t = v[8] + dpp_get64(v[8], 0);
+        t += dpp_get64(t, 1);
+        t += dpp_get64(dpp_get64(t, 2), 3);
+        const double keep = b3 ? t : r, send = b3 ? r : t;
+        r = keep + dpp_get64(send, 4);
+    } else {
+        r += dpp_get64(r, 4);
+    }
+    return add_far_lanes64(r);
+}
+// all eight in every lane
+__device__ __forceinline__ void wave_total64x8(double (&v)[8], int lane)
+{
+    const double r = wave_totals64(v, lane);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
         v[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(r), i), __builtin_amdgcn_readlane(__double2loint(r), i));
-}
-
-// one sum over the same tree
-__device__ __forceinline__ double wave_total64b(double v)
-{
-    v += dpp_get64(v, 0);
-    v += dpp_get64(v, 1);
-    v += dpp_get64(dpp_get64(v, 2), 3);
-    v += dpp_get64(v, 4);
-    v = add_far_lanes64(v);
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 0), __builtin_amdgcn_readlane(__double2loint(v), 0));
 }
 
 // the largest value of the wavefront, in every lane (all 64 lanes take part, no NaN)
