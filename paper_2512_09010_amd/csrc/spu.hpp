@@ -11,6 +11,7 @@ enum class SpuPath {
     Circ,       // spu_circ: the filter as a circulant matrix on the matrix cores, short samples
     Fft,        // spu_fft16q: transform decomposition, N = 16 Q N2
     Mat,        // spu_mat: two transforms on the matrix cores, N = N1 N2 with a factor N1 in 9 .. 16
+    Fold,       // spu_fold: the same for wide pass bands and up to 4096 tokens
     Conv,       // spu_conv: M-point transforms in one workgroup, any N up to 8192
     Dense       // direct pass-band DFT through the workspace, any N
 };
@@ -69,6 +70,13 @@ luvc_status spu_score_mat(const void* x, const MatRun* runs, int n, const MatPla
 // a launch that several runs share: scratch, and the launch on it
 size_t spu_mat_bytes(const MatRun* runs, int n, int D);
 luvc_status spu_score_mat_runs(const void* x, const MatRun* runs, int n, int D, int64_t row_stride, int use_hamming, float* scores, void* workspace, hipStream_t st);
+
+// One launch of equal samples, up to 4096 tokens (spu_fold.hip); the workspace is that of spu_fold_tiles(D) tiles
+bool spu_fold_supported(int N, int sigma);
+int spu_fold_tiles(int D);
+double spu_fold_us(int B, int N, int D, int sigma);
+luvc_status spu_score_fold(const void* x, int B, int N, int D, int64_t row_stride, int sigma, int use_hamming,
+                           float* partial, float* gpartial, const TileSync& sy, float* scores, hipStream_t st);
 
 // Short samples on the matrix cores (spu_circ.hip), runs of equal samples in one launch
 constexpr int kCircMaxN = 1024, kCircMaxRuns = 64;

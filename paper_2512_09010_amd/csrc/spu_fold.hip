@@ -1,0 +1,491 @@
+// SPU score (paper Section 3.3, Eq. 4-8) for N = N1 N2 tokens with N1 in 9 .. 16, N2 <= 256 and a wide pass band: the products of
+// spu_mat.hip, with the multiples j and -j of N1 folded together and no table of operands.
+//
+// With C_j = sum_b cos(2 pi b j / N2) T[b], S_j likewise, of the real and the imaginary parts of T (see spu_mat.hip), the bins
+// c + N1 j and c - N1 j are
+//   Z[j] = (C_j Tr + S_j Ti) + i (C_j Ti - S_j Tr),      Z[-j] = (C_j Tr - S_j Ti) + i (C_j Ti + S_j Tr)
+// so products 2 have the rows (C_j, S_j), j >= 0, and Tr and Ti as two operands: half the products of one row per bin and part.  With
+// g+ = M[j] + M[-j], g- = M[j] - M[-j] the way back takes
+//   Vr = sum_j cos (g+ C_j Tr + g- S_j Ti) + sin (g+ S_j Tr - g- C_j Ti),      Vi = sum_j cos (g+ C_j Ti - g- S_j Tr) + sin (g- C_j Tr + g+ S_j Ti)
+// and a lane has all eight values of a j in its own registers.
+// The cosines and sines are those of N2 places on a circle.  A table of these places, each value two fp16 terms in a word, is
+// all there is in LDS (2 KB; operands as they enter the products would be 128 KB for 4096 tokens): a lane follows its own b j modulo
+// N2 and puts its operand together from what it reads, for the eight products of a row block that use it.
+// A workgroup owns 64 channels, a wavefront four pairs; tokens come as in spu_mat.hip.  Energies of four tiles at a time are added
+// over the wavefronts.
+// Bound: the instructions of two wavefronts per SIMD, whose products and vector instructions overlap little: 22 products of one block
+// of rows (spu_mat: 24 of two) and about 110 vector instructions per pair and 16 subsequences.  bf16, tokens that no cache holds:
+// 4x4096x3584, sigma = 100 112 -> 66 us against spu_fft16q, sigma = 240 93 -> 78 against spu_conv, 2x3328x5120 130 -> 61, 2x3000x3584 83 -> 57;
+// 4x2048x3584 42.7 -> 38.7 against spu_mat, 8x1600x3584 68 -> 64, 16x1536x1536, sigma = 153 69.5 -> 63.7.  Error against fp64 3.1 .. 3.6e-8 rms.
+// Three and four blocks of rows (4x4096x3584, sigma = 409) are slower than spu_conv, 95 us for 84.  Tried and not kept: wavefronts
+// of a SIMD half a tile apart, so that one has products while the other has vector instructions (no difference).
+#include <algorithm>
+#include <cstdlib>
+
+#include "spu_mat.hpp"
+
+namespace luvc {
+
+namespace {
+
+constexpr int kFoldWaves = 8, kFoldPairs = 4, kFoldWidth = 2 * kFoldWaves * kFoldPairs;
+constexpr int kFoldTiles = 16;                   // most tiles of 16 subsequences
+constexpr int kFoldRows = 2;                     // most blocks of 16 rows of the band, 8 multiples of N1 each
+constexpr int kFoldDirect = 32;                  // tiles of a sample whose energies are added in one go
+constexpr int kFoldTw = 18;                      // float2 per row of the twiddles: 16 and a pad for the banks
+constexpr int kFoldPast = 3 * (8 * kFoldRows - 1);            // places behind the circle that repeat its first ones
+
+// Where a place of the circle lies: steps of 4, 8, 16 or 32 places, which lengths with many factors of two take, fall in different banks
+__device__ __forceinline__ uint32_t ring_place(uint32_t i) { return i ^ i >> 5; }
+inline __host__ __device__ int ring_size(int N2) { return (N2 + kFoldPast + 15) / 16 * 16; }
+
+}  // namespace
+
+template <int RB /* blocks of 16 rows of the band */>
+__global__ void __launch_bounds__(64 * kFoldWaves, 2)
+spu_fold(const bf16_t* __restrict__ x, const MatShape sh, int D, int64_t row_stride, int use_hamming, int n_tiles /* workgroups per sample */,
+         float* __restrict__ partial /* [B, n_tiles, ld] */, float* __restrict__ gpartial, const TileSync sy, int ld, float* __restrict__ scores)
+{
+    constexpr int P = kFoldPairs, WAVES = kFoldWaves, THREADS = 64 * WAVES;
+    constexpr int KS = (RB + 1) / 2;             // steps of a product over the band
+    constexpr int kBuf = 256 * 8;                // 16-byte pieces of a buffer: 256 rows of 8, which are 64 channels
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int N = sh.N, N1 = sh.N1, N2 = sh.N2, NT = sh.NT, sigma = sh.sigma;
+    mat_u32x4* data = reinterpret_cast<mat_u32x4*>(smem);                       // [3][256 rows][8]
+    uint32_t* i2t = reinterpret_cast<uint32_t*>(data + 3 * kBuf);               // [2][2][64][4] last operand
+    float2* tw = reinterpret_cast<float2*>(i2t + 2 * 2 * 256);                  // [NT][16 c][kFoldTw]
+    uint2* ring = reinterpret_cast<uint2*>(tw + NT * 16 * kFoldTw);             // [ring_size]  cos, sin of 2 pi i / N2, each high | low
+    float* gm = reinterpret_cast<float*>(ring + ring_size(N2));                  // [sigma + 1]  M[f] / N
+    // where the third chunk comes
+    double2* root = reinterpret_cast<double2*>(data + 2 * kBuf);                // [16]  e^(2 pi i / N1)
+    uint32_t* f1t = reinterpret_cast<uint32_t*>(root + 16);                     // [2][3][64][4] first operand
+    float4* esum = reinterpret_cast<float4*>(data);                             // [2][4 tiles][WAVES][64] energies, on the way back
+    __shared__ uint32_t look[2][64];
+    __shared__ int is_last;
+    const int item = (int)xcd_contiguous(blockIdx.x, gridDim.x);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 15, g = lane >> 4;
+    const int b = item / n_tiles, tile = item - b * n_tiles, d0 = tile * kFoldWidth;
+    const bf16_t* xb = x + (int64_t)b * N * row_stride;
+
+    // ---- tokens: as in spu_mat
+    const uint32_t lds0 = lds_address(data);
+    const int s0 = tid / 8 & 15, piece = (tid & 7) ^ (s0 >> 1);
+    const uint32_t row_bytes = (uint32_t)row_stride * 2u;
+    const uint32_t off = (uint32_t)s0 * row_bytes + 16u * (uint32_t)(d0 + 8 * piece >= D ? 0 : piece);
+    const uint32_t over = 16 * NT - 16 + s0 < N2 ? 0u : (uint32_t)(16 * NT - 15 + s0 - N2) * row_bytes;       // in the last tile
+    auto issue = [&](int t) {                    // chunk t: subsequences 16 t .. + 15
+        const char* base = reinterpret_cast<const char*>(xb) + (int64_t)(16 * t) * row_bytes + 2 * d0;
+        const uint32_t less = t == NT - 1 ? over : 0u;
+#pragma unroll
+        for (int u = 0; u < 2 * P; ++u) {
+            int a = 2 * u + wave / 2;
+            a = a < N1 ? a : N1 - 1;
+            load_to_lds(base + (int64_t)(N2 * a) * row_bytes, off - less, lds0 + (uint32_t)((t % 3) * kBuf + u * (THREADS / 2) + wave * 64) * 16u);
+        }
+    };
+    auto landed = [&](bool newer) {              // all but the newest chunk asked for
+        if (newer) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * P) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    if (wave < WAVES / 2) {
+        issue(0);
+        if (NT > 1) issue(1);
+    }
+
+    // ---- tables
+    {
+        const int ntw = NT * 256, at_ring = ntw, at_gm = at_ring + N2, at_root = at_gm + sigma + 1, jobs = at_root + N1;
+        const double inv_N2 = sh.inv_N * (double)N1;
+#pragma clang loop unroll(disable)
+        for (int j = tid; j < jobs; j += THREADS) {
+            const int s = 16 * (j >> 8) + (j & 15), cc = (j >> 4) & 15;
+            int num = s < N2 && cc < N1 ? s * cc : 0, den = N;
+            double inv = sh.inv_N, sd, cd;
+            if (j >= at_root) { num = j - at_root; den = N1; inv = sh.inv_N1; }
+            else if (j >= at_gm) { num = j - at_gm; den = N - 1; inv = sh.inv_N_1; }
+            else if (j >= at_ring) { num = j - at_ring; den = N2; inv = inv_N2; }
+            circle(num, den, inv, &cd, &sd);
+            if (j >= at_root) root[num] = make_double2(cd, sd);
+            else if (j >= at_gm) gm[num] = (float)((use_hamming ? 0.54 + 0.46 * cd : 1.0) * sh.inv_N * sh.length);
+            else if (j >= at_ring) {
+                uint32_t h, l;
+                split16((float)cd, (float)sd, h, l);
+                const uint2 q = make_uint2((h & 0xffffu) | l << 16, h >> 16 | (l & 0xffff0000u));
+                for (int i = num; i < N2 + kFoldPast; i += N2) ring[ring_place(i)] = q;
+            } else
+                tw[(j >> 4) * kFoldTw + (j & 15)] = s < N2 && cc < N1 ? make_float2((float)cd, (float)sd) : make_float2(0.f, 0.f);
+        }
+    }
+    __syncthreads();
+    const float inv_n2 = 1.f / (float)N2, inv_n1 = 1.f / (float)N1;
+    auto rest = [](int v, int n, float inv) { return v - n * (int)(((float)v + 0.5f) * inv); };      // v mod n, 0 <= v < 2^20
+    // the operands on the side of the N1 places: [re, im of the result][terms]
+#pragma clang loop unroll(disable)
+    for (int j = tid; j < 512; j += THREADS) {
+        const int w = j & 3, l = j >> 2 & 63, o = j >> 8, u = l & 15, a = 4 * (l >> 4) + w;
+        double2 q = root[rest(a < N1 && u < N1 ? a * u : 0, N1, inv_n1)];
+        if (a >= N1 || u >= N1) q = make_double2(0.0, 0.0);
+        uint32_t t0, t1, t2;
+        split_bf16(o ? -q.y : q.x, o ? q.x : q.y, t0, t1, t2);
+        uint32_t* to = f1t + o * 768 + l * 4 + w;
+        to[0] = t0; to[256] = t1; to[512] = t2;
+        const int c0 = 4 * (l >> 4) + 2 * (w & 1);           // u is a place here, c0 and c0 + 1 are bins
+        const double2 q0 = root[rest(c0 < N1 && u < N1 ? c0 * u : 0, N1, inv_n1)], q1 = root[rest(c0 + 1 < N1 && u < N1 ? (c0 + 1) * u : 0, N1, inv_n1)];
+        const bool sine = (w >> 1) != o;
+        const float sign = sine && !o ? -1.f : 1.f;
+        const float v0 = c0 < N1 && u < N1 ? sign * (float)(sine ? q0.y : q0.x) : 0.f, v1 = c0 + 1 < N1 && u < N1 ? sign * (float)(sine ? q1.y : q1.x) : 0.f;
+        split16(v0, v1, t0, t1);
+        to = i2t + o * 512 + l * 4 + w;
+        to[0] = t0; to[256] = t1;
+    }
+    __syncthreads();
+    mat_u32x4 f1[2][3];
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) f1[o][k] = *reinterpret_cast<const mat_u32x4*>(f1t + (o * 3 + k) * 256 + lane * 4);
+    landed(NT > 1);
+    __syncthreads();
+
+    // ---- there
+    // this lane's words: places 4 g .. + 3 of subsequence c of a tile, channel pairs 4 wave .. + 3
+    const lds_word* words = (const lds_word*)reinterpret_cast<const uint32_t*>(data) + ((4 * g) * 16 + c) * 32 + (wave ^ (c >> 1)) * 4;
+    auto onward = [&](uint32_t& at, uint32_t by) {           // places modulo N2
+        const uint32_t n = at + by, less = n - (uint32_t)N2;
+        at = n < less ? n : less;
+    };
+    mat_f32x4 acc[P][RB][2];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int rt = 0; rt < RB; ++rt) acc[p][rt][0] = acc[p][rt][1] = mat_f32x4{0.f, 0.f, 0.f, 0.f};
+    int scale_e = 0;
+    float scale = 1.f;
+    {
+        // operand of block rt: row c, which is the cosine or the sine of multiple j, columns b = 16 t + 4 g .. + 3
+        uint32_t at[RB], one[RB], tile_step[RB];
+#pragma unroll
+        for (int rt = 0; rt < RB; ++rt) {
+            const int j = rt * 8 + (c >> 1);
+            at[rt] = (uint32_t)rest(4 * g * j, N2, inv_n2);
+            one[rt] = (uint32_t)rest(j, N2, inv_n2);
+            tile_step[rt] = (uint32_t)rest(16 * j, N2, inv_n2);
+        }
+        const uint32_t* mine = reinterpret_cast<const uint32_t*>(ring) + (c & 1);
+        bool unset = true;
+#pragma clang loop unroll(disable)
+        for (int t = 0; t < NT; ++t) {
+            const lds_word* buf = words + (t % 3) * (kBuf * 4);
+            float wc[4], ws[4];
+            {
+                const float4* twr = reinterpret_cast<const float4*>(tw + (t * 16 + c) * kFoldTw + 4 * g);
+                const float4 w01 = twr[0], w23 = twr[1];
+                wc[0] = w01.x; ws[0] = w01.y; wc[1] = w01.z; ws[1] = w01.w; wc[2] = w23.x; ws[2] = w23.y; wc[3] = w23.z; ws[3] = w23.w;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) { wc[v] *= scale; ws[v] *= scale; }
+            }
+            // places -> bins c of N1, and the twiddle; subsequence 4 g + v of the tile
+            mat_f32x4 T[P][2];
+            float m = 0.f;
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                mat_u32x4 xa;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) xa[i] = buf[i * 16 * 32 + p];
+                mat_f32x4 y[2];
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    y[o] = mac_bf16(mat_f32x4{0.f, 0.f, 0.f, 0.f}, xa, f1[o][2]);
+                    y[o] = mac_bf16(y[o], xa, f1[o][1]);
+                    y[o] = mac_bf16(y[o], xa, f1[o][0]);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    T[p][0][v] = fmaf(y[0][v], wc[v], y[1][v] * ws[v]);
+                    T[p][1][v] = fmaf(y[1][v], wc[v], -y[0][v] * ws[v]);
+                    m = fmaxf(fmaxf(m, fabsf(T[p][0][v])), fabsf(T[p][1][v]));
+                }
+            }
+            if (wave < WAVES / 2 && t + 2 < NT) issue(t + 2);
+            // The range of fp16: the first values that are not zero set the scale, 64 times larger ones change it.
+            if (__any(m > (unset ? 0.f : 32768.f))) {
+                const int to = clampi(scale_e + 9 - exponent(wave_max(m)), -120, 120), by = clampi(to - scale_e, -126, 126);
+                const float f = pow2(by);
+                scale_e += by;
+                scale *= f;
+                unset = false;
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int o = 0; o < 2; ++o) {
+                        T[p][o] *= f;
+#pragma unroll
+                        for (int rt = 0; rt < RB; ++rt) acc[p][rt][o] *= f;
+                    }
+            }
+            // high and low parts of four subsequences are the eight values of K: one product with the high parts of the constants
+            // twice, one with their low parts
+            mat_u32x4 tv[P][2];
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        uint32_t h, l;
+                        split16(T[p][o][2 * w], T[p][o][2 * w + 1], h, l);
+                        tv[p][o][w] = h; tv[p][o][2 + w] = l;
+                    }
+            // subsequences -> rows of the band
+#pragma unroll
+            for (int rt = 0; rt < RB; ++rt) {
+                uint32_t k[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) k[v] = mine[2 * ring_place(at[rt] + (uint32_t)v * one[rt])];
+                onward(at[rt], tile_step[rt]);
+                const uint32_t h0 = __builtin_amdgcn_perm(k[1], k[0], 0x05040100u), h1 = __builtin_amdgcn_perm(k[3], k[2], 0x05040100u);
+                const uint32_t l0 = __builtin_amdgcn_perm(k[1], k[0], 0x07060302u), l1 = __builtin_amdgcn_perm(k[3], k[2], 0x07060302u);
+                const mat_u32x4 ah{h0, h1, h0, h1}, al{l0, l1, l0, l1};
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) acc[p][rt][o] = mac_f16(acc[p][rt][o], al, tv[p][o]);
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) acc[p][rt][o] = mac_f16(acc[p][rt][o], ah, tv[p][o]);
+            }
+            landed(t + 2 < NT);
+            __syncthreads();
+        }
+    }
+    // ---- mask, scaled for the way back; row of the operands: bin c, K: (cosine, sine) of the multiples of a lane
+    mat_u32x4 gh[P][2][KS], gl[P][2][KS];
+    float back;
+    {
+        const bool live = d0 + 8 * wave < D;     // channels come in eights
+        float m = 0.f;
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int rt = 0; rt < RB; ++rt)
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(acc[p][rt][o][v]));
+        m = 4.f * wave_max(m) * (float)sh.inv_N; // no weight is larger than 1 / N, no value than four products with one
+        const int by = clampi(9 - exponent(m), -120, 120);
+        const float f = m > 0.f && live ? pow2(by) : 0.f;
+        back = pow2(clampi(-(scale_e + by), -126, 126));
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const int rt = 2 * ks + (w >> 1), e = 2 * (w & 1), j = rt * 8 + 2 * g + (w & 1);
+                if (rt >= RB) {
+#pragma unroll
+                    for (int p = 0; p < P; ++p)
+#pragma unroll
+                        for (int o = 0; o < 2; ++o) gh[p][o][ks][w] = gl[p][o][ks][w] = 0u;
+                    continue;
+                }
+                auto weight = [&](int k) {
+                    const int a = k < 0 ? -k : k;
+                    return c < N1 && a <= sigma && 2 * k != -N ? gm[a <= sigma ? a : 0] * f : 0.f;
+                };
+                const float up = weight(c + N1 * j), down = j ? weight(c - N1 * j) : 0.f;
+                const float gp = up + down, gn = j ? up - down : 0.f;
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    const mat_f32x4 &r = acc[p][rt < RB ? rt : 0][0], &i = acc[p][rt < RB ? rt : 0][1];
+                    uint32_t h, l;
+                    split16(fmaf(gp, r[e], gn * i[e + 1]), fmaf(gp, r[e + 1], -gn * i[e]), h, l);
+                    gh[p][0][ks][w] = h; gl[p][0][ks][w] = l;
+                    split16(fmaf(gp, i[e], -gn * r[e + 1]), fmaf(gn, r[e], gp * i[e + 1]), h, l);
+                    gh[p][1][ks][w] = h; gl[p][1][ks][w] = l;
+                }
+            }
+        if constexpr (RB == 1) {                 // high and low parts of eight values are the K of one product
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) gh[p][o][0][2 + w] = gl[p][o][0][w];
+        }
+    }
+    // the look at the arrival words, through LDS: see spu_mat
+    if (wave == 0) {
+        const tile_tag_t* w = tiles_word<kFoldDirect>(sy, b, tile, n_tiles);
+        if (w) {
+            load_word_to_lds(w, lds_address(look[0]));
+            load_word_to_lds((const uint32_t*)w + 1, lds_address(look[1]));
+        }
+    }
+    // ---- back
+    {
+        mat_u32x4 i2[2][2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) i2[o][k] = *reinterpret_cast<const mat_u32x4*>(i2t + (o * 2 + k) * 256 + lane * 4);
+        float* pout = partial + ((int64_t)b * n_tiles + tile) * ld;
+        // operand of block rt: column b = 16 t + c, multiples 8 rt + 2 g and the next
+        uint32_t at[RB][2], tile_step[RB][2];
+#pragma unroll
+        for (int rt = 0; rt < RB; ++rt)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int j = rt * 8 + 2 * g + e;
+                at[rt][e] = (uint32_t)rest(c * j, N2, inv_n2);
+                tile_step[rt][e] = (uint32_t)rest(16 * j, N2, inv_n2);
+            }
+#pragma clang loop unroll(disable)
+        for (int t = 0; t < NT; ++t) {
+            float wc[4], ws[4], sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) { const float2 q = tw[(t * 16 + 4 * g + v) * kFoldTw + c]; wc[v] = q.x; ws[v] = q.y; }
+            mat_u32x4 kh[KS], kl[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const int rt = 2 * ks + (w >> 1);
+                    if (rt >= RB) {
+                        kh[ks][w] = RB == 1 ? kh[ks][w & 1] : 0u;
+                        kl[ks][w] = RB == 1 ? kl[ks][w & 1] : 0u;
+                        continue;
+                    }
+                    uint32_t& a = at[rt < RB ? rt : 0][w & 1];
+                    const uint2 q = ring[ring_place(a)];
+                    onward(a, tile_step[rt < RB ? rt : 0][w & 1]);
+                    kh[ks][w] = __builtin_amdgcn_perm(q.y, q.x, 0x05040100u);
+                    kl[ks][w] = __builtin_amdgcn_perm(q.y, q.x, 0x07060302u);
+                }
+            mat_f32x4 z[P][2];
+#pragma unroll
+            for (int o = 0; o < 2; ++o)
+#pragma unroll
+                for (int p = 0; p < P; ++p) z[p][o] = mat_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if (RB > 1)
+#pragma unroll
+                    for (int o = 0; o < 2; ++o)
+#pragma unroll
+                        for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], gl[p][o][ks], kh[ks]);
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], gh[p][o][ks], kl[ks]);
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], gh[p][o][ks], kh[ks]);
+            }
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                float u[2][4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    u[0][v] = fmaf(z[p][0][v], wc[v], -z[p][1][v] * ws[v]);
+                    u[1][v] = fmaf(z[p][1][v], wc[v], z[p][0][v] * ws[v]);
+                }
+                mat_u32x4 uh, ul;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    uint32_t h, l;
+                    split16(u[w >> 1][2 * (w & 1)], u[w >> 1][2 * (w & 1) + 1], h, l);
+                    uh[w] = h; ul[w] = l;
+                }
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    mat_f32x4 y = mac_f16(mat_f32x4{0.f, 0.f, 0.f, 0.f}, i2[o][0], ul);
+                    y = mac_f16(y, i2[o][1], uh);
+                    y = mac_f16(y, i2[o][0], uh);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) sum[v] = fmaf(y[v], y[v], sum[v]);
+                }
+            }
+            esum[((t & 7) * WAVES + wave) * 64 + lane] = make_float4(sum[0] * back * back, sum[1] * back * back, sum[2] * back * back, sum[3] * back * back);
+            if ((t & 3) == 3 || t == NT - 1) {
+                // four tiles: the sums over the wavefronts; the next four go to the other half meanwhile
+                __syncthreads();
+                const int t0 = t & ~3;
+                for (int q = tid; q < (t - t0 + 1) * 256; q += THREADS) {
+                    const int s = 16 * (t0 + (q >> 8)) + (q & 15), a = (q >> 4) & 15;
+                    const float* e = reinterpret_cast<const float*>(esum + ((t0 & 7) + (q >> 8)) * WAVES * 64) + ((a >> 2) * 16 + (q & 15)) * 4 + (a & 3);
+                    double all = 0.0;
+#pragma unroll
+                    for (int w = 0; w < WAVES; ++w) all += (double)e[w * 256];
+                    if (a < N1 && s < N2) tile_store(pout + (N2 * a + s), (float)all);
+                }
+            }
+        }
+    }
+    if (wave == 0) {
+        landed(false);
+        tiles_claim<kFoldDirect>(sy, b, tile, n_tiles, (tile_tag_t)look[1][lane] << 32 | look[0][lane]);
+    }
+    tiles_to_scores<THREADS, kFoldDirect>(partial, gpartial, sy, scores, b, tile, n_tiles, N, ld, &is_last);
+}
+
+namespace {
+
+size_t fold_lds(const MatShape& sh)
+{
+    return (size_t)3 * 256 * (kFoldWidth * 2) + 4096 + (size_t)sh.NT * 16 * kFoldTw * 8 + (size_t)ring_size(sh.N2) * 8 + (size_t)(sh.sigma + 1) * 4;
+}
+// the largest N1: fewest tiles, fewest multiples
+bool fold_shape(int N, int sigma, MatShape* sh, int* rb)
+{
+    for (int N1 = 16; N1 >= 9; --N1) {
+        if (N % N1) continue;
+        const int N2 = N / N1, NT = (N2 + 15) / 16, dn = (sigma + N1 - 1) / N1, RB = (dn + 8) / 8;       // multiples 0 .. dn
+        if (NT > kFoldTiles || RB > kFoldRows || N2 < 2) continue;
+        *sh = MatShape{1.0 / N, 1.0 / (N - 1), 1.0 / N1, 1.0, N, N1, N2, NT, sigma, dn, dn + sigma / N1 + 1};
+        *rb = RB;
+        return true;
+    }
+    return false;
+}
+
+}  // namespace
+
+bool spu_fold_supported(int N, int sigma)
+{
+    MatShape sh;
+    int rb;
+    return fold_shape(N, sigma, &sh, &rb);
+}
+int spu_fold_tiles(int D) { return (D + kFoldWidth - 1) / kFoldWidth; }
+
+// us of one call, from measurements like those of spu_mat: rounds of workgroups, one per compute unit, each with its tables and its
+// hand-over.  bf16 4x1024x3584, sigma = 102: 25.9, 4x2048x3584, 102: 36.9 .. 38.7, 8x1600x3584, 100: 59.9 .. 64.4, 8x2048x3584, 204:
+// 72.3 .. 79.7, 16x1536x1536, 153: 59.1 .. 63.7, 16x720x4096, 54: 70 (spu_mat 48), 32x576x896, 57: 32 (spu_mat 28).
+double spu_fold_us(int B, int N, int D, int sigma)
+{
+    MatShape sh;
+    int rb;
+    fold_shape(N, sigma, &sh, &rb);
+    const int n_tiles = spu_fold_tiles(D);
+    return 4.5 + (n_tiles > kFoldDirect ? 2.0 : 0.0) + (double)(((int64_t)B * n_tiles + 255) / 256) * (4.5 + sh.NT * (2.45 + 0.47 * rb));
+}
+
+luvc_status spu_score_fold(const void* x, int B, int N, int D, int64_t row_stride, int sigma, int use_hamming,
+                           float* partial, float* gpartial, const TileSync& sy, float* scores, hipStream_t st)
+{
+    MatShape sh;
+    int rb;
+    if (!fold_shape(N, sigma, &sh, &rb)) { set_error("spu_fold: N = %d, sigma = %d", N, sigma); return LUVC_ERR_INVALID_ARG; }
+    sh.length = mat_length(sh, 0.5e-8);         // measured, 1024 to 4096 tokens, white and smooth
+    const int n_tiles = spu_fold_tiles(D), ld = (N + 3) / 4 * 4;
+#define LUVC_FOLD(RB) LUVC_LAUNCH("spu_fold", (spu_fold<RB>), dim3((unsigned)((int64_t)B * n_tiles)), dim3(64 * kFoldWaves), fold_lds(sh), st, (const bf16_t*)x, sh, D, \
+                                  row_stride, use_hamming, n_tiles, partial, gpartial, sy, ld, scores)
+    if (rb == 1) LUVC_FOLD(1);
+    else LUVC_FOLD(2);
+#undef LUVC_FOLD
+    return check_launch("spu score (fold)");
+}
+
+}  // namespace luvc

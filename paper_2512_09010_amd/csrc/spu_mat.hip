@@ -27,7 +27,7 @@
 // Bound: instructions issued by two wavefronts per SIMD.  Per pair and 16 subsequences 19 or 24 products (one holds the vector unit
 // up for 8 of its 16 cycles) and about 100 vector instructions of 4 cycles, 72 of which the method needs: twiddles 32, halves 32,
 // energies 8.  bf16, tokens that no cache holds: 8x1024x3584 40.2 -> 35.6 us against spu_fft16q, 16x720x4096 65 -> 46,
-// 4x2048x3584 45 -> 40, 2x2016x3584 45 -> 34, against spu_conv 16x390x1536 27 -> 19, against spu_circ 32x390x3584 102 -> 48.
+// against spu_conv 16x390x1536 27 -> 19, against spu_circ 32x390x3584 102 -> 48.
 // Tried and not kept: two wavefronts that fetch for the other eight (40 us for 38 at that time); two pairs per wavefront and
 // four wavefronts per SIMD (16x720x4096 71 for 51); products and vector instructions put in turns by hand; tokens through registers
 // (one chunk on its way: 42).
@@ -35,115 +35,12 @@
 #include <cmath>
 #include <cstdlib>
 #include <numeric>
-#include <type_traits>
 
-#include "common.hpp"
-#include "spu.hpp"
-#include "spu_tiles.hpp"
+#include "spu_mat.hpp"
 
 namespace luvc {
 
 namespace {
-
-typedef unsigned int mat_u32x4 __attribute__((__vector_size__(16)));
-typedef float mat_f32x4 __attribute__((ext_vector_type(4)));
-typedef float mat_f32x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 mat_f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 mat_f16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 mat_bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 mat_bf16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ mat_f32x4 mac_f16(mat_f32x4 acc, const mat_u32x4& a, const mat_u32x4& b)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(mat_f16x8, a), __builtin_bit_cast(mat_f16x8, b), acc, 0, 0, 0);
-}
-__device__ __forceinline__ mat_f32x4 mac_bf16(mat_f32x4 acc, const mat_u32x4& a, const mat_u32x4& b)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(mat_bf16x8, a), __builtin_bit_cast(mat_bf16x8, b), acc, 0, 0, 0);
-}
-
-// a, b = hi + lo, two fp16 values each (nearest): 2^-24 of the value, or 2^-25 for small ones
-__device__ __forceinline__ void split16(float a, float b, uint32_t& hi, uint32_t& lo)
-{
-    const mat_f16x2 h = __builtin_convertvector(mat_f32x2{a, b}, mat_f16x2);
-    hi = __builtin_bit_cast(uint32_t, h);
-    float one = 1.f;
-    asm("" : "+s"(one));                         // a factor that stays: with it the difference is one instruction, taking the half as it lies
-    const float ra = fmaf(-(float)h[0], one, a), rb = fmaf(-(float)h[1], one, b);
-    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(mat_f32x2{ra, rb}, mat_f16x2));
-}
-__device__ __forceinline__ uint32_t pk_bf16x2(float a, float b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(mat_f32x2{a, b}, mat_bf16x2));
-}
-// a, b as three bf16 values each
-__device__ __forceinline__ void split_bf16(double a, double b, uint32_t& t0, uint32_t& t1, uint32_t& t2)
-{
-    t0 = pk_bf16x2((float)a, (float)b);
-    a -= (double)__uint_as_float(t0 << 16);
-    b -= (double)__uint_as_float(t0 & 0xffff0000u);
-    t1 = pk_bf16x2((float)a, (float)b);
-    a -= (double)__uint_as_float(t1 << 16);
-    b -= (double)__uint_as_float(t1 & 0xffff0000u);
-    t2 = pk_bf16x2((float)a, (float)b);
-}
-
-typedef volatile __attribute__((address_space(3))) uint32_t lds_word;      // volatile: as one access for four pairs, it takes a move per word
-
-// the largest of the 64 lanes' values (none below zero), in every lane
-__device__ __forceinline__ float wave_max(float v)
-{
-    auto step = [&](auto ctrl, auto rows) { v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), decltype(ctrl)::value, decltype(rows)::value, 0xf, false))); };
-    using all = std::integral_constant<int, 0xf>;
-    step(std::integral_constant<int, 0xB1>{}, all{});            // quad_perm [1,0,3,2]
-    step(std::integral_constant<int, 0x4E>{}, all{});            // quad_perm [2,3,0,1]
-    step(std::integral_constant<int, 0x141>{}, all{});           // row_half_mirror
-    step(std::integral_constant<int, 0x140>{}, all{});           // row_mirror
-    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});      // row_bcast:15 -> rows 1, 3
-    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});      // row_bcast:31 -> rows 2, 3
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-// 16 (4) bytes per lane from memory to consecutive places in LDS, from the wavefront's first lane on; the caller waits for
-// vmcnt.  Written out, because behind the builtin every read of LDS waits for all such loads; the scalar write of m0 has to lie
-// a wait state before its use, one of the base by a vector instruction five.
-__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p; }
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void load_to_lds(const void* base /* the same in all lanes */, uint32_t offset, uint32_t to)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(to), "v"(offset), "s"(base) : "memory", "m0");
-}
-__device__ __forceinline__ void load_word_to_lds(const void* from, uint32_t to)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, off sc1" :: "s"(to), "v"(from) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-// cos and sin of 2 pi num / den, 0 <= num <= den, inv = 1 / den: the eighth of the circle it falls in, then the series of either
-// up to terms below 1e-15 of it.  (A third of the code of sincospi, which the first wavefronts of a compute unit fetch from
-// afar: 3 us of a launch.)
-__device__ __forceinline__ void circle(int num, int den, double inv, double* cosine, double* sine)
-{
-    int o = (int)(((float)(8 * num) + 0.5f) * (float)inv);       // exact: num <= 32768
-    int rem = 8 * num - o * den;
-    if (o & 1) rem = den - rem;
-    const double a = 0.78539816339744830962 * ((double)rem * inv), q = a * a;
-    double c = -1.0 / 87178291200.0, s = -1.0 / 1307674368000.0;             // 14!, 15!
-    c = fma(c, q, 1.0 / 479001600.0);    s = fma(s, q, 1.0 / 6227020800.0);
-    c = fma(c, q, -1.0 / 3628800.0);     s = fma(s, q, -1.0 / 39916800.0);
-    c = fma(c, q, 1.0 / 40320.0);        s = fma(s, q, 1.0 / 362880.0);
-    c = fma(c, q, -1.0 / 720.0);         s = fma(s, q, -1.0 / 5040.0);
-    c = fma(c, q, 1.0 / 24.0);           s = fma(s, q, 1.0 / 120.0);
-    c = fma(c, q, -0.5);                 s = fma(s, q, -1.0 / 6.0);
-    c = fma(c, q, 1.0);                  s = fma(s * q, a, a);
-    const bool swap = ((o + 1) & 2) != 0;
-    const double x = swap ? s : c, y = swap ? c : s;
-    *cosine = ((o + 2) & 4) ? -x : x;
-    *sine = (o & 4) ? -y : y;
-}
-__device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }     // -126 .. 127
-// e with 2^e <= m < 2^(e + 1)
-__device__ __forceinline__ int exponent(float m) { return (int)((__float_as_uint(m) >> 23) & 255u) - 127; }
-__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : v > hi ? hi : v; }
 
 constexpr int kMatWaves = 8, kMatPairs = 4;      // wavefronts of a workgroup, channel pairs of a wavefront
 constexpr int kMatWidth = 2 * kMatWaves * kMatPairs;
@@ -152,12 +49,6 @@ constexpr int kMatDirect = 32;                   // tiles of a sample whose ener
 constexpr int kTwRow = 18;                       // float2 per row of the twiddles: 16 and a pad for the banks
 
 }  // namespace
-
-struct MatShape {
-    double inv_N, inv_N_1, inv_N1;               // 1 / N, 1 / (N - 1), 1 / N1
-    double length;                               // what the weights give back (mat_length)
-    int N, N1, N2, NT /* tiles of 16 subsequences */, sigma, dn /* lowest multiple of N1 in the band, negated */, nb /* multiples */;
-};
 
 // runs of equal samples that share a launch
 struct MatLaunchRun {
@@ -559,7 +450,7 @@ constexpr size_t kMatLds = 160 * 1024 - 1024;
 
 // How much shorter than 1 the (cos, sin) of multiples of 2 pi / n are as the sum of two fp16 values, on the mean
 struct CircleLengths {
-    double of[129];
+    double of[257];
     CircleLengths()
     {
         auto two_halves = [](double v) {
@@ -573,7 +464,7 @@ struct CircleLengths {
             return h + half(f - h);
         };
         of[0] = 0.0;
-        for (int n = 1; n <= 128; ++n) {
+        for (int n = 1; n <= 256; ++n) {
             double sum = 0.0;
             for (int i = 0; i < n; ++i) {
                 const double a = 6.283185307179586 * i / n, c = std::cos(a), s = std::sin(a);
@@ -583,17 +474,21 @@ struct CircleLengths {
         }
     }
 };
+}  // namespace
+
 // The rounded constants make every score too small or too large by up to 5e-8, in a way that depends on N1 and N2 alone: the
 // rows of the band on the way there and back, and the N1 places.  The matrix cores' sums, which are cut off rather than
-// rounded, take another 2.4e-8 (measured, 576 to 2048 tokens, white and smooth).
-double mat_length(const MatShape& sh)
+// rounded, take another `sums`.
+double mat_length(const MatShape& sh, double sums)
 {
     static const CircleLengths circle;
     double band = 0.0, places = 0.0;
     for (int i = 0; i < sh.nb; ++i) band += circle.of[sh.N2 / std::gcd(sh.N2, std::abs(i - sh.dn))];
     for (int i = 0; i < sh.N1; ++i) places += circle.of[sh.N1 / std::gcd(sh.N1, i)];
-    return 1.0 - 2.0 * band / sh.nb - places / sh.N1 + 2.4e-8;
+    return 1.0 - 2.0 * band / sh.nb - places / sh.N1 + sums;
 }
+
+namespace {
 
 bool mat_shape(int N, int sigma, MatShape* sh, int* rb)
 {
@@ -690,7 +585,7 @@ static void mat_launch(const void* x, const MatRun* runs, int n, const MatPlan& 
     for (int i = 0; i < n; ++i) {
         int rb;
         mat_shape(runs[i].N, runs[i].sigma, &l.run[i].sh, &rb);
-        l.run[i].sh.length = mat_length(l.run[i].sh);
+        l.run[i].sh.length = mat_length(l.run[i].sh, 2.4e-8);       // measured, 576 to 2048 tokens, white and smooth
         l.run[i].wg0 = (int)(samples * p.n_tiles);
         l.run[i].sample0 = (int)samples;
         l.run[i].tok0 = runs[i].tok0;

@@ -193,8 +193,10 @@ static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, bool pie
         if (path == SpuPath::Dense || t < *us) { path = p; *us = t; }
     };
     if (pieces && spu_mat_supported(N, sigma)) offer(SpuPath::Mat, spu_mat_us(B, N, D, sigma));
+    if (pieces && spu_fold_supported(N, sigma)) offer(SpuPath::Fold, spu_fold_us(B, N, D, sigma));
     if (spu_fft_supported(N, sigma)) offer(SpuPath::Fft, spu_fft_us(B, N, D, sigma));
-    if (spu_conv_points(N, &half) != 0) offer(SpuPath::Conv, spu_conv_us(B, N, D, dt));
+    // spu_conv takes about five sixths of its estimate, which spu_fold, unlike the others, comes close to
+    if (spu_conv_points(N, &half) != 0) offer(SpuPath::Conv, spu_conv_us(B, N, D, dt) * (path == SpuPath::Fold ? 0.84 : 1.0));
     return path;
 }
 static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows)
@@ -236,9 +238,9 @@ SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows
         L.bytes = align_up(spu_circ_bytes(B, N, D));
         return L.bytes > most ? spu_layout(B, N, D, sigma, dt, SpuRows{CircRows::None, rows.pieces}, most) : L;
     }
-    if (L.path == SpuPath::Mat) {
+    if (L.path == SpuPath::Mat || L.path == SpuPath::Fold) {
         const MatRun run{N, sigma, B, 0};
-        L.n_tiles = spu_mat_plan(&run, 1, D).n_tiles;
+        L.n_tiles = L.path == SpuPath::Fold ? spu_fold_tiles(D) : spu_mat_plan(&run, 1, D).n_tiles;
         L.bytes = tile_bytes(B, L.n_tiles, (N + 3) / 4 * 4, &L, 0);
         return L.bytes > most ? spu_layout(B, N, D, sigma, dt, SpuRows{rows.circ, false}, most) : L;
     }
@@ -321,6 +323,7 @@ luvc_status spu_score_dense(const void* x, int B, int N, int D, int64_t row_stri
         const MatRun run{N, sigma, B, 0};
         return spu_score_mat(x, &run, 1, spu_mat_plan(&run, 1, D), D, row_stride, use_hamming, partial, gpartial, sy, scores, st);
     }
+    if (L.path == SpuPath::Fold) return spu_score_fold(x, B, N, D, row_stride, sigma, use_hamming, partial, gpartial, sy, scores, st);
     if (L.path == SpuPath::Conv)
         return spu_score_conv(x, B, N, D, row_stride, dt, sigma, use_hamming, (float*)(ws + L.spec), partial, gpartial, sy, L.n_tiles, scores, st);
     LUVC_LAUNCH("spu_tables", spu_tables, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, N, sigma, use_hamming, tw, gk, gm);

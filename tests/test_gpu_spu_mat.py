@@ -51,7 +51,7 @@ def test_score(oracle, B, N, D, sigma):
     x = rng.standard_normal((B, N, D)) * np.exp(rng.standard_normal((B, N, 1)))
     x = wl.cast_io(x.astype(np.float32), "bf16")
     xd, got, _ = score_case(oracle, x, "bf16", sigma, True, "mat")
-    assert kernels(lambda: lv.luvc_spu_score(xd, sigma, True)) == ["spu_mat"]
+    assert kernels(lambda: lv.luvc_spu_score(xd, sigma, True)) in (["spu_mat"], ["spu_fold"])
     for _ in range(2):                                           # same bits whichever workgroup adds up
         assert torch.equal(lv.luvc_spu_score(xd, sigma, True), got)
     if N < 1000:
