@@ -193,10 +193,13 @@ static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, bool pie
         if (path == SpuPath::Dense || t < *us) { path = p; *us = t; }
     };
     if (pieces && spu_mat_supported(N, sigma)) offer(SpuPath::Mat, spu_mat_us(B, N, D, sigma));
-    if (pieces && spu_fold_supported(N, sigma)) offer(SpuPath::Fold, spu_fold_us(B, N, D, sigma));
     if (spu_fft_supported(N, sigma)) offer(SpuPath::Fft, spu_fft_us(B, N, D, sigma));
+    if (spu_conv_points(N, &half) != 0) offer(SpuPath::Conv, spu_conv_us(B, N, D, dt));
     // spu_conv takes about five sixths of its estimate, which spu_fold, unlike the others, comes close to
-    if (spu_conv_points(N, &half) != 0) offer(SpuPath::Conv, spu_conv_us(B, N, D, dt) * (path == SpuPath::Fold ? 0.84 : 1.0));
+    if (pieces && path != SpuPath::Dense && spu_fold_supported(N, sigma)) {
+        const double f = spu_fold_us(B, N, D, sigma);
+        if (f < *us * (path == SpuPath::Conv ? 0.84 : 1.0)) { path = SpuPath::Fold; *us = f; }
+    }
     return path;
 }
 static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows)
