@@ -24,10 +24,13 @@
 // A workgroup owns 64 channels (a cache line of every token row) at a time, a wavefront four pairs.  Tokens come into LDS by 16
 // subsequences (32 KB) straight from memory, three chunks in turn, two on their way; every wavefront reads its own words.  On the way
 // back nothing is fetched but constants, and the next group's first chunks come in meanwhile.
-// Bound: instructions issued by two wavefronts per SIMD.  Per pair and 16 subsequences 19 or 24 products (one holds the vector unit
+// Bound: instructions issued by two wavefronts per SIMD.  Per pair and 16 subsequences 19, 20 or 24 products (one holds the vector unit
 // up for 8 of its 16 cycles) and about 100 vector instructions of 4 cycles, 72 of which the method needs: twiddles 32, halves 32,
-// energies 8.  bf16, tokens that no cache holds: 8x1024x3584 40.2 -> 35.6 us against spu_fft16q, 16x720x4096 65 -> 46,
+// energies 8.  bf16, tokens that no cache holds: 8x1024x3584 42 -> 36.4 us against spu_fft16q, 16x720x4096 65 -> 46,
 // against spu_conv 16x390x1536 27 -> 19, against spu_circ 32x390x3584 102 -> 48.
+// Bands of two blocks of rows whose multiples fit -7 .. 7 have their rows folded as in spu_fold.hip, 20 products for 24 and half the
+// tables, which leaves room for several groups of channels per workgroup: 8x1024x3584 41.0 -> 36.4, 8x1280x3584, sigma = 110 54.7 ->
+// 42.9, 8x1152x3584 53.7 -> 43.3, 16x1040x1536 51.3 -> 39.6; error 3.3 .. 3.8e-8 for 4.0 .. 4.5e-8 on the last.
 // Tried and not kept: two wavefronts that fetch for the other eight (40 us for 38 at that time); two pairs per wavefront and
 // four wavefronts per SIMD (16x720x4096 71 for 51); products and vector instructions put in turns by hand; tokens through registers
 // (one chunk on its way: 42).
@@ -58,7 +61,7 @@ struct MatLaunchRun {
 };
 template <int RUNS> struct MatLaunch { int n; MatLaunchRun run[RUNS]; };
 
-template <int RB /* blocks of 16 rows of the band */, int RUNS>
+template <int RB /* blocks of 16 rows of the band, 0: one of folded rows */, int RUNS>
 __global__ void __launch_bounds__(64 * kMatWaves, 2)
 spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t row_stride, int use_hamming, int gpw /* groups of channels per workgroup */,
         int n_tiles /* workgroups per sample */, float* __restrict__ partial /* [samples, n_tiles, ld] */, float* __restrict__ gpartial, const TileSync sy, int ld,
@@ -72,13 +75,16 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
     const MatLaunchRun& run = runs.run[at_run];
     const MatShape& sh = run.sh;
     constexpr int P = kMatPairs, WAVES = kMatWaves, THREADS = 64 * WAVES;
-    constexpr int KS = (RB + 1) / 2;             // steps of a product over the band
+    constexpr bool FOLD = RB == 0;
+    constexpr int KS = FOLD ? 1 : (RB + 1) / 2;  // steps of a product over the band
+    constexpr int NA = FOLD ? 2 : RB;            // results of the way there per pair: blocks, or the parts of the one
+    constexpr int kF2 = FOLD ? 64 : RB * 2 * 32; // 16-byte pieces of a tile's operands on the way there
     constexpr int kBuf = 256 * 8;                // 16-byte pieces of a buffer: 256 rows of 8, which are 64 channels
-    constexpr int kI1 = RB == 1 ? 1 : 2 * KS;    // 1 KB blocks of an inverse operand
+    constexpr int kI1 = RB <= 1 ? 1 : 2 * KS;    // 1 KB blocks of an inverse operand
     extern __shared__ __align__(16) unsigned char smem[];
     const int N = sh.N, N1 = sh.N1, N2 = sh.N2, NT = sh.NT, sigma = sh.sigma;
-    mat_u32x4* f2 = reinterpret_cast<mat_u32x4*>(smem);                         // [NT][RB][2][32]
-    mat_u32x4* i1 = f2 + NT * RB * 2 * 32;                                      // [NT][kI1][64]
+    mat_u32x4* f2 = reinterpret_cast<mat_u32x4*>(smem);                         // [NT][RB][2][32] or [NT][64]
+    mat_u32x4* i1 = f2 + NT * kF2;                                              // [NT][kI1][64]
     float2* tw = reinterpret_cast<float2*>(i1 + NT * kI1 * 64);                 // [NT][16 c][kTwRow]
     mat_u32x4* data = reinterpret_cast<mat_u32x4*>(tw + NT * 16 * kTwRow);      // [3][256 rows][8]
     // what the tables are made of, where the third chunk comes
@@ -148,9 +154,28 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
     auto rest = [](int v, int n, float inv) { return v - n * (int)(((float)v + 0.5f) * inv); };      // v mod n, 0 <= v < 2^20
     // Word by word, in loops that are not unrolled: the code runs once, and its size is what it costs.  Rows of the band:
     // 2 di, 2 di + 1 are the real and the imaginary part of multiple di - dn of N1.
+    if constexpr (FOLD) {
+        // way there: row r of lane l is the cosine (r even) or sine of multiple r / 2, subsequences 4 (l / 16) .. + 3 of a tile; way back: cosine
+        // and sine of multiples 2 (l / 16) and the next, subsequence l % 16; high parts, low parts
+#pragma clang loop unroll(disable)
+        for (int i = tid; i < NT * 64; i += THREADS) {
+            const int l = i & 63, r = l & 15, gg = l >> 4, t = i >> 6;
+            uint32_t th[2], tl[2], bh[2], bl[2];
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                const int s = 16 * t + 4 * gg + 2 * w, m = r >> 1;
+                const float2 q0 = cs[rest(s * m, N2, inv_n2) * N1], q1 = cs[rest((s + 1) * m, N2, inv_n2) * N1];
+                split16(r & 1 ? q0.y : q0.x, r & 1 ? q1.y : q1.x, th[w], tl[w]);
+                const float2 q = cs[rest((16 * t + r) * (2 * gg + w), N2, inv_n2) * N1];
+                split16(q.x, q.y, bh[w], bl[w]);
+            }
+            f2[i] = mat_u32x4{th[0], th[1], tl[0], tl[1]};
+            i1[i] = mat_u32x4{bh[0], bh[1], bl[0], bl[1]};
+        }
+    }
 #pragma clang loop unroll(disable)
     for (int j = tid; j < NT * RB * 128; j += THREADS) {
-        const int w = j & 3, i = j >> 2, gg = i & 3, di = (i >> 5) % RB * 8 + (i >> 2 & 7), s = 16 * ((i >> 5) / RB) + 4 * gg + 2 * (w & 1), m = di - sh.dn + N2;
+        const int w = j & 3, i = j >> 2, gg = i & 3, di = (i >> 5) % (RB ? RB : 1) * 8 + (i >> 2 & 7), s = 16 * ((i >> 5) / (RB ? RB : 1)) + 4 * gg + 2 * (w & 1), m = di - sh.dn + N2;
         const float2 q0 = cs[rest(s * m, N2, inv_n2) * N1], q1 = cs[rest((s + 1) * m, N2, inv_n2) * N1];
         uint32_t h, l;
         split16(di < sh.nb && s < N2 ? (w & 2 ? q0.y : q0.x) : 0.f, di < sh.nb && s + 1 < N2 ? (w & 2 ? q1.y : q1.x) : 0.f, h, l);
@@ -159,7 +184,7 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
         to[128] = l;
     }
 #pragma clang loop unroll(disable)
-    for (int j = tid; j < NT * KS * 256; j += THREADS) {
+    for (int j = tid; j < (FOLD ? 0 : NT * KS * 256); j += THREADS) {
         const int w = j & 3, l = j >> 2 & 63, ks = (j >> 8) % KS, t = (j >> 8) / KS, s = 16 * t + (l & 15), gg = l >> 4;
         const int di = (32 * ks + 16 * (w >> 1) + 4 * gg + 2 * (w & 1)) >> 1;        // rows 2 di, 2 di + 1
         const float2 q = cs[rest(s * (di - sh.dn + N2), N2, inv_n2) * N1];
@@ -198,7 +223,20 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
         to = i2t + o * 512 + l * 4 + w;
         to[0] = t0; to[256] = t1;
     }
-    float weight[RB][2];
+    float weight[NA][2];                         // FOLD: M[j] + M[-j], M[j] - M[-j] of a lane's two multiples
+    if constexpr (FOLD) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int j = 2 * g + e;
+            auto at = [&](int k) {
+                const int f = k < 0 ? -k : k;
+                return c < N1 && f <= sigma && 2 * k != -N ? gm[f <= sigma ? f : 0] : 0.f;
+            };
+            const float up = at(c + N1 * j), down = j ? at(c - N1 * j) : 0.f;
+            weight[0][e] = up + down;
+            weight[NA - 1][e] = j ? up - down : 0.f;
+        }
+    }
 #pragma unroll
     for (int rt = 0; rt < RB; ++rt)
 #pragma unroll
@@ -224,11 +262,11 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
     const uint32_t f2_sign = ro ? 0x80008000u : 0u;
     int ci = 0;
     for (int grp = 0; grp < groups; ++grp) {
-        mat_f32x4 acc[P][RB];
+        mat_f32x4 acc[P][NA];
 #pragma unroll
         for (int p = 0; p < P; ++p)
 #pragma unroll
-            for (int rt = 0; rt < RB; ++rt) acc[p][rt] = mat_f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int rt = 0; rt < NA; ++rt) acc[p][rt] = mat_f32x4{0.f, 0.f, 0.f, 0.f};
         int scale_e = 0;
         float scale = 1.f;
         bool unset = true;
@@ -277,8 +315,34 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
 #pragma unroll
                     for (int o = 0; o < 2; ++o) T[p][o] *= f;
 #pragma unroll
-                    for (int rt = 0; rt < RB; ++rt) acc[p][rt] *= f;
+                    for (int rt = 0; rt < NA; ++rt) acc[p][rt] *= f;
                 }
+            }
+            if constexpr (FOLD) {
+                // as in spu_fold: high and low parts of four subsequences are the eight values of K
+                mat_u32x4 tv[P][2];
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int o = 0; o < 2; ++o)
+#pragma unroll
+                        for (int w = 0; w < 2; ++w) {
+                            uint32_t h, l;
+                            split16(T[p][o][2 * w], T[p][o][2 * w + 1], h, l);
+                            tv[p][o][w] = h; tv[p][o][2 + w] = l;
+                        }
+                const mat_u32x4 k = f2[t * 64 + lane], ah{k[0], k[1], k[0], k[1]}, al{k[2], k[3], k[2], k[3]};
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) acc[p][o] = mac_f16(acc[p][o], al, tv[p][o]);
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) acc[p][o] = mac_f16(acc[p][o], ah, tv[p][o]);
+                landed(ci + 2 < chunks);
+                __syncthreads();
+                continue;
             }
             mat_u32x4 th[P], tl[P];
 #pragma unroll
@@ -310,7 +374,7 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
             __syncthreads();
         }
         // ---- mask, scaled for the way back
-        mat_u32x4 gh[P][KS], gl[P][KS];
+        mat_u32x4 gh[P][KS], gl[P][KS];          // FOLD: the real and the imaginary part's, high and low parts in one
         float back;
         {
             const bool live = (grp0 + grp) * kMatWidth + 8 * wave < D;          // channels come in eights
@@ -318,25 +382,40 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
 #pragma unroll
             for (int p = 0; p < P; ++p)
 #pragma unroll
-                for (int rt = 0; rt < RB; ++rt)
+                for (int rt = 0; rt < NA; ++rt)
 #pragma unroll
                     for (int e = 0; e < 2; ++e) m = fmaxf(fmaxf(m, fabsf(acc[p][rt][2 * e])), fabsf(acc[p][rt][2 * e + 1]));
-            m = wave_max(m) * (float)sh.inv_N;   // no weight is larger
+            m = wave_max(m) * (FOLD ? 4.f : 1.f) * (float)sh.inv_N;         // no weight is larger than 1 / N; folded values are of four
             const int by = clampi(9 - exponent(m), -120, 120);
             const float f = m > 0.f && live ? pow2(by) : 0.f;
             back = pow2(clampi(-(scale_e + by), -126, 126));
-            float wf[RB][2];
+            float wf[NA][2];
 #pragma unroll
-            for (int rt = 0; rt < RB; ++rt) { wf[rt][0] = weight[rt][0] * f; wf[rt][1] = weight[rt][1] * f; }
+            for (int rt = 0; rt < NA; ++rt) { wf[rt][0] = weight[rt][0] * f; wf[rt][1] = weight[rt][1] * f; }
+            if constexpr (FOLD) {
 #pragma unroll
-            for (int p = 0; p < P; ++p)
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        const mat_f32x4 &r = acc[p][0], &i = acc[p][NA - 1];
+                        const int e = 2 * w;
+                        const float gp = wf[0][w], gn = wf[NA - 1][w];
+                        uint32_t h, l;
+                        split16(fmaf(gp, r[e], gn * i[e + 1]), fmaf(gp, r[e + 1], -gn * i[e]), h, l);
+                        gh[p][0][w] = h; gh[p][0][2 + w] = l;
+                        split16(fmaf(gp, i[e], -gn * r[e + 1]), fmaf(gn, r[e], gp * i[e + 1]), h, l);
+                        gl[p][0][w] = h; gl[p][0][2 + w] = l;
+                    }
+            }
+#pragma unroll
+            for (int p = 0; p < (FOLD ? 0 : P); ++p)
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                     for (int w = 0; w < 4; ++w) {
                         const int rt = 2 * ks + (w >> 1), v = 2 * (w & 1);
                         uint32_t h = 0, l = 0;
-                        if (rt < RB) split16(acc[p][rt < RB ? rt : 0][v] * wf[rt < RB ? rt : 0][w & 1], acc[p][rt < RB ? rt : 0][v + 1] * wf[rt < RB ? rt : 0][w & 1], h, l);
+                        if (rt < RB) split16(acc[p][rt < NA ? rt : 0][v] * wf[rt < NA ? rt : 0][w & 1], acc[p][rt < NA ? rt : 0][v + 1] * wf[rt < NA ? rt : 0][w & 1], h, l);
                         gh[p][ks][w] = h; gl[p][ks][w] = l;
                     }
             if constexpr (RB == 1) {
@@ -372,7 +451,13 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
                     for (int w = 0; w < 4; ++w) r[w] = o ? __builtin_amdgcn_alignbit(k[w], k[w], 16) ^ 0x8000u : k[w];
                     return r;
                 };
-                if constexpr (RB == 1) {
+                if constexpr (FOLD) {
+                    const mat_u32x4 k = i1[t * 64 + lane], kh{k[0], k[1], k[0], k[1]}, kl{k[2], k[3], k[2], k[3]};
+#pragma unroll
+                    for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], o ? gl[p][0] : gh[p][0], kl);
+#pragma unroll
+                    for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], o ? gl[p][0] : gh[p][0], kh);
+                } else if constexpr (RB == 1) {
                     const mat_u32x4 k = turn(i1[t * 64 + lane]);
                     const mat_u32x4 kh{k[0], k[1], k[0], k[1]}, kl{k[2], k[3], 0u, 0u};
 #pragma unroll
@@ -509,8 +594,8 @@ bool mat_shape(int N, int sigma, MatShape* sh, int* rb)
 }
 size_t mat_lds(const MatShape& sh, int RB, int gpw)
 {
-    const int KS = (RB + 1) / 2, kI1 = RB == 1 ? 1 : 2 * KS;
-    return (size_t)3 * 256 * (kMatWidth * 2) + (size_t)sh.NT * (RB + kI1) * 1024 + (size_t)sh.NT * 16 * kTwRow * 8 + (gpw > 1 ? (size_t)kMatWaves * sh.NT * 1024 : 0);
+    const int KS = (RB + 1) / 2, kI1 = RB <= 1 ? 1 : 2 * KS;
+    return (size_t)3 * 256 * (kMatWidth * 2) + (size_t)sh.NT * ((RB ? RB : 1) + kI1) * 1024 + (size_t)sh.NT * 16 * kTwRow * 8 + (gpw > 1 ? (size_t)kMatWaves * sh.NT * 1024 : 0);
 }
 
 }  // namespace
@@ -530,14 +615,17 @@ MatPlan spu_mat_plan(const MatRun* runs, int n, int D)
 {
     MatPlan p{};
     int lds_groups = 0;
+    bool folds = true;                           // one block of folded rows holds the bands
     for (int i = 0; i < n; ++i) {
         MatShape sh;
         int rb;
         mat_shape(runs[i].N, runs[i].sigma, &sh, &rb);
         p.rb = std::max(p.rb, rb);
+        folds = folds && sh.dn <= 7;
         p.samples += runs[i].count;
         p.ld = std::max(p.ld, (runs[i].N + 3) / 4 * 4);
     }
+    if (p.rb == 2 && folds) p.rb = 0;            // 20 products for 24
     for (int i = 0; i < n; ++i) {
         MatShape sh;
         int rb;
@@ -554,7 +642,7 @@ MatPlan spu_mat_plan(const MatRun* runs, int n, int D)
 }
 
 // us of one call, from measurements: the rounds that the workgroups take on the chip, one per compute unit, each with its tables
-// and its hand-over.  bf16 8x1024x3584, sigma = 102: 35.6, 32x390x3584, 58: 48, 32x576x896, 57: 24, 16x1536x1536, 153: 61,
+// and its hand-over.  bf16 8x1024x3584, sigma = 102: 36.4, 32x390x3584, 58: 48, 32x576x896, 57: 24, 16x1536x1536, 153: 61,
 // 4x234x1536, 17: 13, 1x1280x896, 32: 21.
 static double mat_tile_us(const MatShape& sh, int rb) { return sh.NT * (2.5 + 0.5 * rb); }
 double spu_mat_us(int B, int N, int D, int sigma)
@@ -585,7 +673,7 @@ static void mat_launch(const void* x, const MatRun* runs, int n, const MatPlan& 
     for (int i = 0; i < n; ++i) {
         int rb;
         mat_shape(runs[i].N, runs[i].sigma, &l.run[i].sh, &rb);
-        l.run[i].sh.length = mat_length(l.run[i].sh, 2.4e-8);       // measured, 576 to 2048 tokens, white and smooth
+        l.run[i].sh.length = mat_length(l.run[i].sh, RB ? 2.4e-8 : 0.5e-8);         // measured, 576 to 2048 tokens, white and smooth
         l.run[i].wg0 = (int)(samples * p.n_tiles);
         l.run[i].sample0 = (int)samples;
         l.run[i].tok0 = runs[i].tok0;
@@ -600,9 +688,11 @@ luvc_status spu_score_mat(const void* x, const MatRun* runs, int n, const MatPla
 {
 #define LUVC_MAT(RB, RUNS) mat_launch<RB, RUNS>(x, runs, n, p, D, row_stride, use_hamming, partial, gpartial, sy, scores, st)
     if (n > 1) {
-        if (p.rb == 1) LUVC_MAT(1, kMatMaxRuns);
+        if (p.rb == 0) LUVC_MAT(0, kMatMaxRuns);
+        else if (p.rb == 1) LUVC_MAT(1, kMatMaxRuns);
         else LUVC_MAT(2, kMatMaxRuns);
     }
+    else if (p.rb == 0) LUVC_MAT(0, 1);
     else if (p.rb == 1) LUVC_MAT(1, 1);
     else if (p.rb == 2) LUVC_MAT(2, 1);
     else if (p.rb == 3) LUVC_MAT(3, 1);

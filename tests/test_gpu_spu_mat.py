@@ -41,6 +41,7 @@ SHAPES = [
     (8, 1904, 1032, 100),               # 16 119 8      2
     (8, 2048, 1032, 102),               # 16 128 8      2
     (8, 2016, 1032, 120),               # 16 126 8      2
+    (8, 1024, 3592, 112), (8, 1024, 3592, 113), (8, 1280, 3592, 110), (16, 1040, 1544, 100),    # folded rows up to their last multiple, one beyond, two groups
     (8, 1270, 1032, 11), (8, 1332, 1032, 11), (8, 1530, 1032, 30), (16, 909, 1032, 30),         # N1 = 10, 12, 15 and 9
 ]
 
