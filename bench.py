@@ -222,6 +222,7 @@ def run_config(cfg, args, lv, wl, torch, np):
         "oim_halve_pair": (oim_bytes, None, "hbm"), "oim_halve": (oim_bytes, None, "hbm"),
         "spu_fft16q": (score_bytes, fft_flops, "alu"),
         "spu_fwd_dense": (score_bytes, None, "hbm"), "spu_circ": (score_bytes, None, "hbm"),
+        "spu_mat": (score_bytes, None, "hbm"), "spu_fold": (score_bytes, None, "hbm"), "spu_conv": (score_bytes, None, "hbm"),
         "spu_gather": (prune_bytes, None, "hbm"), "spu_prune_fused": (prune_bytes, None, "hbm"),
     }
     try:
