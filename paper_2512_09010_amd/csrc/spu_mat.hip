@@ -267,56 +267,19 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
         for (int p = 0; p < P; ++p)
 #pragma unroll
             for (int rt = 0; rt < NA; ++rt) acc[p][rt] = mat_f32x4{0.f, 0.f, 0.f, 0.f};
-        int scale_e = 0;
-        float scale = 1.f;
-        bool unset = true;
+        MatScale scale;
         for (int t = 0; t < NT; ++t, ++ci) {
             const lds_word* buf = words + (ci % 3) * (kBuf * 4);
-            float wc[4], ws[4];
-            {
-                const float4* twr = reinterpret_cast<const float4*>(tw + (t * 16 + c) * kTwRow + 4 * g);
-                const float4 w01 = twr[0], w23 = twr[1];
-                wc[0] = w01.x; ws[0] = w01.y; wc[1] = w01.z; ws[1] = w01.w; wc[2] = w23.x; ws[2] = w23.y; wc[3] = w23.z; ws[3] = w23.w;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) { wc[v] *= scale; ws[v] *= scale; }
-            }
-            // places -> bins c of N1, and the twiddle; subsequence 4 g + v of the tile
-            mat_f32x4 T[P][2];
-            float m = 0.f;
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                mat_u32x4 xa;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) xa[i] = buf[i * 16 * 32 + p];
-                mat_f32x4 y[2];
-#pragma unroll
-                for (int o = 0; o < 2; ++o) {
-                    y[o] = mac_bf16(mat_f32x4{0.f, 0.f, 0.f, 0.f}, xa, f1[o][2]);
-                    y[o] = mac_bf16(y[o], xa, f1[o][1]);
-                    y[o] = mac_bf16(y[o], xa, f1[o][0]);
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    T[p][0][v] = fmaf(y[0][v], wc[v], y[1][v] * ws[v]);
-                    T[p][1][v] = fmaf(y[1][v], wc[v], -y[0][v] * ws[v]);
-                    m = fmaxf(fmaxf(m, fabsf(T[p][0][v])), fabsf(T[p][1][v]));
-                }
-            }
+            mat_f32x4 T[P][2];                   // subsequence 4 g + v of the tile
+            const float2* twiddles = tw + (t * 16 + c) * kTwRow + 4 * g;
+            const float m = places_to_bins(T, buf, f1, twiddles, scale.f);
             if (wave < WAVES / 2 && ci + 2 < chunks) issue(ci + 2);
-            // The range of fp16: the first values that are not zero set the scale, 64 times larger ones change it.
-            if (__any(m > (unset ? 0.f : 32768.f))) {
-                const int to = clampi(scale_e + 9 - exponent(wave_max(m)), -120, 120), by = clampi(to - scale_e, -126, 126);
-                const float f = pow2(by);
-                scale_e += by;
-                scale *= f;
-                unset = false;
+            if (__any(m > (scale.unset ? 0.f : 32768.f))) {
+                const float f = into_range(T, m, buf, f1, twiddles, scale);
 #pragma unroll
-                for (int p = 0; p < P; ++p) {
-#pragma unroll
-                    for (int o = 0; o < 2; ++o) T[p][o] *= f;
+                for (int p = 0; p < P; ++p)
 #pragma unroll
                     for (int rt = 0; rt < NA; ++rt) acc[p][rt] *= f;
-                }
             }
             if constexpr (FOLD) {
                 // as in spu_fold: high and low parts of four subsequences are the eight values of K
@@ -388,7 +351,7 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
             m = wave_max(m) * (FOLD ? 4.f : 1.f) * (float)sh.inv_N;         // no weight is larger than 1 / N; folded values are of four
             const int by = clampi(9 - exponent(m), -120, 120);
             const float f = m > 0.f && live ? pow2(by) : 0.f;
-            back = pow2(clampi(-(scale_e + by), -126, 126));
+            back = pow2(clampi(-(scale.e + by), -126, 126));
             float wf[NA][2];
 #pragma unroll
             for (int rt = 0; rt < NA; ++rt) { wf[rt][0] = weight[rt][0] * f; wf[rt][1] = weight[rt][1] * f; }

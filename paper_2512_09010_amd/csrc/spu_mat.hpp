@@ -110,6 +110,65 @@ __device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)
 __device__ __forceinline__ int exponent(float m) { return (int)((__float_as_uint(m) >> 23) & 255u) - 127; }
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : v > hi ? hi : v; }
 
+// The power of two that brings a wavefront's values into the range of fp16
+struct MatScale {
+    int e = 0;
+    float f = 1.f;                               // 2^e
+    bool unset = true;
+};
+// Places -> bins c of N1, and the twiddle, times `scale`: subsequences 4 g + v of a tile, P channel pairs.  The largest value of the lane.
+template <int P>
+__device__ __forceinline__ float places_to_bins(mat_f32x4 (&T)[P][2], const lds_word* buf, const mat_u32x4 (&f1)[2][3], const float2* twiddles, float scale)
+{
+    float wc[4], ws[4], m = 0.f;
+    const float4* twr = reinterpret_cast<const float4*>(twiddles);
+    const float4 w01 = twr[0], w23 = twr[1];
+    wc[0] = w01.x; ws[0] = w01.y; wc[1] = w01.z; ws[1] = w01.w; wc[2] = w23.x; ws[2] = w23.y; wc[3] = w23.z; ws[3] = w23.w;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) { wc[v] *= scale; ws[v] *= scale; }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        mat_u32x4 xa;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xa[i] = buf[i * 16 * 32 + p];
+        mat_f32x4 y[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            y[o] = mac_bf16(mat_f32x4{0.f, 0.f, 0.f, 0.f}, xa, f1[o][2]);
+            y[o] = mac_bf16(y[o], xa, f1[o][1]);
+            y[o] = mac_bf16(y[o], xa, f1[o][0]);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            T[p][0][v] = fmaf(y[0][v], wc[v], y[1][v] * ws[v]);
+            T[p][1][v] = fmaf(y[1][v], wc[v], -y[0][v] * ws[v]);
+            m = fmaxf(fmaxf(m, fabsf(T[p][0][v])), fabsf(T[p][1][v]));
+        }
+    }
+    return m;
+}
+// The range of fp16: the first values that are not zero set the scale, 64 times larger ones change it; what was added up so far follows
+// by the factor returned.  The scale they are met with may take them beyond fp32 (2^120 behind values of 1e-34): then they are formed
+// again without it.
+template <int P>
+__device__ __forceinline__ float into_range(mat_f32x4 (&T)[P][2], float m, const lds_word* buf, const mat_u32x4 (&f1)[2][3], const float2* twiddles, MatScale& scale)
+{
+    float top = wave_max(m);
+    int e = scale.e;
+    if (top > 3.4028234663852886e38f) {
+        top = wave_max(places_to_bins(T, buf, f1, twiddles, 1.f));
+        e = 0;
+    }
+    const int to = clampi(e + 9 - exponent(top), -120, 120);
+    const float f = pow2(clampi(to - e, -126, 126)), sums = pow2(clampi(to - scale.e, -126, 126));
+#pragma unroll
+    for (int p = 0; p < P; ++p) { T[p][0] *= f; T[p][1] *= f; }
+    scale.e = to;
+    scale.f = pow2(to);
+    scale.unset = false;
+    return sums;
+}
+
 }  // namespace
 
 struct MatShape {

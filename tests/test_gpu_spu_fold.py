@@ -9,7 +9,7 @@ from paper_2512_09010_amd import binding as lv
 from paper_2512_09010_amd import workloads as wl
 from gpu_util import to_dev
 from test_gpu_spu import score_case
-from test_gpu_spu_mat import kernels
+from test_gpu_spu_mat import GROWTHS, growth_case, kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -64,6 +64,13 @@ def test_values_out_of_the_range_of_fp16(oracle):
     got = lv.luvc_spu_score(to_dev(wl.cast_io(x.astype(np.float32), "bf16"), "bf16"), sigma, True)
     clean = lv.luvc_spu_score(to_dev(wl.cast_io(base.astype(np.float32), "bf16"), "bf16"), sigma, True)
     assert torch.equal(got[1:], clean[1:]) and not torch.isfinite(got[0]).any()
+
+
+@pytest.mark.parametrize("N,sigma,N2", [(2064, 112, 129), (2304, 150, 144)])
+@pytest.mark.parametrize("first,late", GROWTHS)
+def test_values_that_grow_beyond_the_first_scale(oracle, N, sigma, N2, first, late):
+    """As for spu_mat; one and two blocks of band rows."""
+    assert growth_case(oracle, 4, N, 1032, sigma, N2, first, late) == ["spu_fold"]
 
 
 @pytest.mark.parametrize("B,N,D,sigma", [(8, 2048, 1544, 102), (8, 4096, 1544, 200), (6, 3000, 1032, 150), (6, 2880, 1032, 140)])

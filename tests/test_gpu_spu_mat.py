@@ -80,6 +80,28 @@ def test_values_out_of_the_range_of_fp16(oracle):
     assert torch.equal(got[1:], clean[1:])                       # the other samples are not touched
 
 
+# the first subsequences hold `first`, those behind them `late`: the scale that `first` sets takes `late` beyond fp32 by itself
+GROWTHS = [(3e-34, 3e3), (1e-35, 1e4), (1e-38, 1e15), (1e-30, 1e10)]
+
+
+def growth_case(oracle, B, N, D, sigma, N2, first, late):
+    x = np.random.default_rng(N).standard_normal((1, N, D)) * np.where(np.arange(N) % N2 >= 16, late, first)[None, :, None]
+    x = wl.cast_io(x.astype(np.float32), "bf16")
+    print(f"[spu] growth {first} -> {late} {B}x{N}x{D} sigma={sigma}", flush=True)
+    ref = oracle.spu_score(wl.widen(x, "bf16"), sigma, True)
+    xd = to_dev(x, "bf16").expand(B, N, D).contiguous()
+    got = lv.luvc_spu_score(xd, sigma, True).cpu().numpy().astype(np.float64)
+    assert (np.abs(got - ref) <= SCORE_RTOL * ref + 1e-6 * ref.max()).all(), float(np.abs(got / ref - 1).max())
+    return kernels(lambda: lv.luvc_spu_score(xd, sigma, True))
+
+
+@pytest.mark.parametrize("B,N,D,sigma,N2", [(8, 1024, 1032, 60, 64), (8, 1024, 3592, 102, 64), (8, 1024, 3592, 113, 64), (4, 552, 5120, 96, 46), (16, 640, 3584, 250, 40)])
+@pytest.mark.parametrize("first,late", GROWTHS)
+def test_values_that_grow_beyond_the_first_scale(oracle, B, N, D, sigma, N2, first, late):
+    """One block of rows, folded rows, two, three and four blocks, one and several groups of channels per workgroup."""
+    growth_case(oracle, B, N, D, sigma, N2, first, late)
+
+
 @pytest.mark.parametrize("B,N,D,sigma", [(8, 1024, 1024, 102), (8, 720, 1024, 54), (4, 2048, 512, 102), (8, 576, 1024, 57), (4, 1248, 512, 62)])
 def test_error_against_fp64(oracle, B, N, D, sigma):
     """Rounding: the score's own (at most 2^-24 / sqrt(3), rms) and those behind a filtered value: six of 2^-24 at most per stage
