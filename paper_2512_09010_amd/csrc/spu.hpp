@@ -57,7 +57,7 @@ struct MatRun {
     int64_t tok0;                    // first token of the first sample
 };
 struct MatPlan {
-    int rb, gpw, n_tiles, ld;
+    int gpw, n_tiles, ld;
     int64_t samples;
     size_t lds;
 };
@@ -72,7 +72,7 @@ size_t spu_mat_bytes(const MatRun* runs, int n, int D);
 luvc_status spu_score_mat_runs(const void* x, const MatRun* runs, int n, int D, int64_t row_stride, int use_hamming, float* scores, void* workspace, hipStream_t st);
 
 // One launch of equal samples, up to 4096 tokens (spu_fold.hip); the workspace is that of spu_fold_tiles(D) tiles
-bool spu_fold_supported(int N, int sigma);
+int spu_fold_blocks(int N, int sigma);          // of 16 rows of the band; 0: not here
 int spu_fold_tiles(int D);
 double spu_fold_us(int B, int N, int D, int sigma);
 luvc_status spu_score_fold(const void* x, int B, int N, int D, int64_t row_stride, int sigma, int use_hamming,

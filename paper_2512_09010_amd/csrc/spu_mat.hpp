@@ -1,4 +1,4 @@
-// The matrix products of spu_mat.hip and spu_fold.hip: operands, values as sums of two fp16 values, circle points, loads to LDS.
+// The matrix products of spu_mat.hip and spu_fold.hip: operands, values as sums of fp16 values, circle points, tokens on their way to LDS.
 #pragma once
 #include <type_traits>
 
@@ -27,7 +27,8 @@ __device__ __forceinline__ mat_f32x4 mac_bf16(mat_f32x4 acc, const mat_u32x4& a,
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(mat_bf16x8, a), __builtin_bit_cast(mat_bf16x8, b), acc, 0, 0, 0);
 }
 
-// a, b = hi + lo, two fp16 values each (nearest): 2^-24 of the value, or 2^-25 for small ones
+// a, b = hi + lo, two fp16 values each (nearest): off by at most 2^-23 of the value (a quarter of all fp32 values have a last bit that
+// is lost), or by 2^-25 for small ones
 __device__ __forceinline__ void split16(float a, float b, uint32_t& hi, uint32_t& lo)
 {
     const mat_f16x2 h = __builtin_convertvector(mat_f32x2{a, b}, mat_f16x2);
@@ -36,6 +37,14 @@ __device__ __forceinline__ void split16(float a, float b, uint32_t& hi, uint32_t
     asm("" : "+s"(one));                         // a factor that stays: with it the difference is one instruction, taking the half as it lies
     const float ra = fmaf(-(float)h[0], one, a), rb = fmaf(-(float)h[1], one, b);
     lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(mat_f32x2{ra, rb}, mat_f16x2));
+}
+// and a third one, of what the two leave: 2^-33 of the value
+__device__ __forceinline__ void split16x3(double a, double b, uint32_t& hi, uint32_t& lo, uint32_t& least)
+{
+    split16((float)a, (float)b, hi, lo);
+    const mat_f16x2 h = __builtin_bit_cast(mat_f16x2, hi), l = __builtin_bit_cast(mat_f16x2, lo);
+    const float ra = (float)(a - (double)(float)h[0] - (double)(float)l[0]), rb = (float)(b - (double)(float)h[1] - (double)(float)l[1]);
+    least = __builtin_bit_cast(uint32_t, __builtin_convertvector(mat_f32x2{ra, rb}, mat_f16x2));
 }
 __device__ __forceinline__ uint32_t pk_bf16x2(float a, float b)
 {
@@ -110,19 +119,92 @@ __device__ __forceinline__ float pow2(int e) { return __uint_as_float((uint32_t)
 __device__ __forceinline__ int exponent(float m) { return (int)((__float_as_uint(m) >> 23) & 255u) - 127; }
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : v > hi ? hi : v; }
 
+// Constants of the band stand 2^10 above their values, so that their low and third fp16 terms are no subnormal ones; the twiddles
+// stand as much below theirs.
+constexpr int kMatBoost = 10;
+// Twiddles [row][16 columns] without a pad: the pieces of 16 bytes of a row in an order that puts those of 16 rows in different banks
+__device__ __forceinline__ int tw_place(int row, int col) { return row * 16 + (((col >> 1) ^ (row >> 1 & 7)) << 1 | (col & 1)); }
+
+// Tokens on their way to LDS, 16 subsequences (32 KB) at a time.  The older half of the wavefronts fetches: they come first where two
+// share a SIMD, and would wait for the younger ones.  A thread fetches eight pieces of a chunk, the same piece of the rows of one
+// subsequence s0 of a tile; places a >= N1, subsequences >= N2 and channels >= D are not used, but have to be numbers: others of
+// the same sample.  Row 16 a + s holds its pieces in an order that depends on s, so that the 16 subsequences' words of a channel pair
+// lie in 16 banks.
+constexpr int kMatWaves = 8, kMatPairs = 4;      // wavefronts of a workgroup, channel pairs of a wavefront
+constexpr int kMatThreads = 64 * kMatWaves, kMatWidth = 2 * kMatWaves * kMatPairs;
+constexpr int kMatBuf = 256 * 8;                 // 16-byte pieces of a buffer: 256 rows of 8, which are 64 channels
+struct MatTokens {
+    const char* base;                            // the sample's first token
+    uint32_t lds0, row_bytes, off, over;
+    int D, N1, N2, NT, piece, wave;
+    __device__ __forceinline__ MatTokens(const bf16_t* x, int64_t row_stride, int D_, int N1_, int N2_, int NT_, const void* data, int wave_)
+        : base(reinterpret_cast<const char*>(x)), lds0(lds_address(data)), row_bytes((uint32_t)row_stride * 2u), D(D_), N1(N1_), N2(N2_), NT(NT_), wave(wave_)
+    {
+        const int s0 = (int)threadIdx.x / 8 & 15;
+        piece = ((int)threadIdx.x & 7) ^ (s0 >> 1);
+        off = (uint32_t)s0 * row_bytes + 16u * (uint32_t)piece;
+        over = 16 * NT - 16 + s0 < N2 ? 0u : (uint32_t)(16 * NT - 15 + s0 - N2) * row_bytes;       // in the last tile
+    }
+    // chunk i: tile t of the channels from d on
+    __device__ __forceinline__ void issue(int i, int t, int d) const
+    {
+        const char* from = base + (int64_t)(16 * t) * row_bytes + 2 * d;
+        uint32_t less = t == NT - 1 ? over : 0u;
+        if (d + 8 * piece >= D) less += 16u * (uint32_t)piece;
+#pragma unroll
+        for (int u = 0; u < 2 * kMatPairs; ++u) {
+            int a = 2 * u + wave / 2;
+            a = a < N1 ? a : N1 - 1;
+            load_to_lds(from + (int64_t)(N2 * a) * row_bytes, off - less, lds0 + (uint32_t)((i % 3) * kMatBuf + u * (kMatThreads / 2) + wave * 64) * 16u);
+        }
+    }
+    // wait for all but the newest chunk asked for
+    __device__ __forceinline__ static void landed(bool newer)
+    {
+        if (newer) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * kMatPairs) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+};
+__device__ __forceinline__ int mat_rest(int v, int n, float inv) { return v - n * (int)(((float)v + 0.5f) * inv); }      // v mod n, 0 <= v < 2^20, inv = 1 / n
+
+// The operands on the side of the N1 places, [re, im of the result][terms][64][4]: f1t of the way there, i2t of the way back, whose
+// circle has the radius `scale` (mat_place_scale).  root: e^(2 pi i k / N1).
+__device__ __forceinline__ void place_operands(const double2* root, int N1, float inv_n1, double scale, uint32_t* f1t, uint32_t* i2t)
+{
+#pragma clang loop unroll(disable)
+    for (int j = threadIdx.x; j < 512; j += kMatThreads) {
+        const int w = j & 3, l = j >> 2 & 63, o = j >> 8, u = l & 15, a = 4 * (l >> 4) + w;
+        double2 q = root[mat_rest(a < N1 && u < N1 ? a * u : 0, N1, inv_n1)];
+        if (a >= N1 || u >= N1) q = make_double2(0.0, 0.0);
+        uint32_t t0, t1, t2;
+        split_bf16(o ? -q.y : q.x, o ? q.x : q.y, t0, t1, t2);
+        uint32_t* to = f1t + o * 768 + l * 4 + w;
+        to[0] = t0; to[256] = t1; to[512] = t2;
+        const int c0 = 4 * (l >> 4) + 2 * (w & 1);           // u is a place here, c0 and c0 + 1 are bins
+        const double2 q0 = root[mat_rest(c0 < N1 && u < N1 ? c0 * u : 0, N1, inv_n1)], q1 = root[mat_rest(c0 + 1 < N1 && u < N1 ? (c0 + 1) * u : 0, N1, inv_n1)];
+        const bool sine = (w >> 1) != o;
+        const double by = sine && !o ? -scale : scale;
+        const float v0 = c0 < N1 && u < N1 ? (float)(by * (sine ? q0.y : q0.x)) : 0.f, v1 = c0 + 1 < N1 && u < N1 ? (float)(by * (sine ? q1.y : q1.x)) : 0.f;
+        split16(v0, v1, t0, t1);
+        to = i2t + o * 512 + l * 4 + w;
+        to[0] = t0; to[256] = t1;
+    }
+}
+
 // The power of two that brings a wavefront's values into the range of fp16
 struct MatScale {
     int e = 0;
     float f = 1.f;                               // 2^e
     bool unset = true;
 };
-// Places -> bins c of N1, and the twiddle, times `scale`: subsequences 4 g + v of a tile, P channel pairs.  The largest value of the lane.
+// Places -> bins c of N1, and the twiddle (two pieces of its row: subsequences 4 g, 4 g + 1 and 4 g + 2, 4 g + 3), times `scale`:
+// subsequences 4 g + v of a tile, P channel pairs.  The largest value of the lane.
+struct MatTwiddles { const float2 *w01, *w23; };
 template <int P>
-__device__ __forceinline__ float places_to_bins(mat_f32x4 (&T)[P][2], const lds_word* buf, const mat_u32x4 (&f1)[2][3], const float2* twiddles, float scale)
+__device__ __forceinline__ float places_to_bins(mat_f32x4 (&T)[P][2], const lds_word* buf, const mat_u32x4 (&f1)[2][3], const MatTwiddles& twiddles, float scale)
 {
     float wc[4], ws[4], m = 0.f;
-    const float4* twr = reinterpret_cast<const float4*>(twiddles);
-    const float4 w01 = twr[0], w23 = twr[1];
+    const float4 w01 = *reinterpret_cast<const float4*>(twiddles.w01), w23 = *reinterpret_cast<const float4*>(twiddles.w23);
     wc[0] = w01.x; ws[0] = w01.y; wc[1] = w01.z; ws[1] = w01.w; wc[2] = w23.x; ws[2] = w23.y; wc[3] = w23.z; ws[3] = w23.w;
 #pragma unroll
     for (int v = 0; v < 4; ++v) { wc[v] *= scale; ws[v] *= scale; }
@@ -151,7 +233,7 @@ __device__ __forceinline__ float places_to_bins(mat_f32x4 (&T)[P][2], const lds_
 // by the factor returned.  The scale they are met with may take them beyond fp32 (2^120 behind values of 1e-34): then they are formed
 // again without it.
 template <int P>
-__device__ __forceinline__ float into_range(mat_f32x4 (&T)[P][2], float m, const lds_word* buf, const mat_u32x4 (&f1)[2][3], const float2* twiddles, MatScale& scale)
+__device__ __forceinline__ float into_range(mat_f32x4 (&T)[P][2], float m, const lds_word* buf, const mat_u32x4 (&f1)[2][3], const MatTwiddles& twiddles, MatScale& scale)
 {
     float top = wave_max(m);
     int e = scale.e;
@@ -173,9 +255,10 @@ __device__ __forceinline__ float into_range(mat_f32x4 (&T)[P][2], float m, const
 
 struct MatShape {
     double inv_N, inv_N_1, inv_N1;               // 1 / N, 1 / (N - 1), 1 / N1
-    double length;                               // what the weights give back (mat_length)
+    double place_scale, energy;                  // mat_scales
     int N, N1, N2, NT /* tiles of 16 subsequences */, sigma, dn /* lowest multiple of N1 in the band, negated */, nb /* multiples */;
+    int down;                                    // N = 2^down .. 2^(down + 1) - 1: energies are formed 2^(-2 down) of what they are without 1 / N
 };
-double mat_length(const MatShape& sh, double sums);
+void mat_scales(MatShape* sh, int ways);
 
 }  // namespace luvc
