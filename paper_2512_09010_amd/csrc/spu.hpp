@@ -46,6 +46,7 @@ luvc_status spu_score_call(const void* x, int B, int N, int D, int64_t row_strid
 // Fast path (spu_fft.hip): N = 16 * Q * N2 with Q in {16, 15, 9}, 2 * sigma + 1 <= 16 * Q, N <= 4096.
 bool spu_fft_supported(int N, int sigma);
 double spu_fft_us(int B, int N, int D, int sigma);
+double spu_fft_measured_us(int B, int N, int D, int sigma);
 struct TileSync;
 luvc_status spu_score_fft(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
                           float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st);
@@ -93,6 +94,7 @@ luvc_status spu_score_circ(const void* x, int64_t row_stride, int D, luvc_dtype 
 int spu_conv_points(int N, bool* half);
 int spu_conv_tiles(int B, int N, int D, int most = INT32_MAX);
 double spu_conv_us(int B, int N, int D, luvc_dtype dt);
+double spu_conv_measured_us(int B, int N, int D);
 size_t spu_conv_spec_bytes(int N);
 inline int spu_conv_ld(int N) { return (N + 3) / 4 * 4; }
 luvc_status spu_score_conv(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,

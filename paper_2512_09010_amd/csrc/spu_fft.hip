@@ -385,6 +385,14 @@ double spu_fft_us(int B, int N, int D, int sigma)
     return 5.0 + rounds * n2 * (Q == 16 ? 5.0 : Q == 15 ? 6.2 : 4.35);
 }
 
+// As measured on 18 shapes: short samples pay for the start of a workgroup too (19x256x4864: 51, the above 34; 11x240x4480: 28, 20.5;
+// 7x512x2432: 22.6, 20.2; from 3 or 4 subsequences on, 0.94 to 1.17 of it but for 4x4096x3584, sigma = 100: 110, 77)
+double spu_fft_measured_us(int B, int N, int D, int sigma)
+{
+    const int Q = fft_pick_q(N, sigma);
+    return spu_fft_us(B, N, D, sigma) + (N <= 2 * 16 * Q ? 3.0 * (double)((int64_t)B * ((D + 31) / 32)) / (Q == 16 ? 512.0 : 768.0) : 0.0);
+}
+
 luvc_status spu_score_fft(const void* x, int B, int N, int D, int64_t row_stride, luvc_dtype dt, int sigma, int use_hamming,
                           float* partial, float* gpartial, const TileSync& sy, int n_tiles, float* scores, hipStream_t st)
 {

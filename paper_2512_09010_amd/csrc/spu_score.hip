@@ -174,8 +174,8 @@ tile_tag_t spu_next_tag()
 }
 
 // ------------------------------------------------------------------ host side
-// Which kernel is quickest: measured times (us, one call) as functions of the sizes.  spu_circ: its products at 1.1e15 flop/s,
-// and a chain of steps that grows with N, which overlap in part (fitted to bf16 8x205x3584: 14, 1x729x3584: 20, 1x1000x1024: 16,
+// Which kernel serves a call, from times (us, one call) as functions of the sizes.  spu_circ: its products at 1.1e15 flop/s, and a
+// chain of steps that grows with N, which overlap in part (fitted to bf16 8x205x3584: 14, 1x729x3584: 20, 1x1000x1024: 16,
 // 4x861x1408: 34; fp32 1x300x2048: 13, 1x1000x1024: 29; channel by channel 8x205x3585: 16, 1x729x3585: 27; since its taps are ready
 // earlier it takes .5 to 2 us less); the others beside their launchers.
 double spu_circ_work_us(int64_t B, int N, int D, luvc_dtype dt) { return (dt == LUVC_F32 ? 12.0 : 6.0) * N * N * (double)D * (double)B / 1.1e9; }
@@ -184,33 +184,54 @@ static double circ_us(int64_t B, int N, int D, luvc_dtype dt, CircRows rows)
     const double work = 1.15 * spu_circ_work_us(B, N, D, dt), chain = (dt == LUVC_F32 ? 0.0218 : 0.0105) * N;
     return (dt == LUVC_F32 ? 6.3 : 5.5) + (rows == CircRows::Single ? 1.35 : 1.0) * std::sqrt(work * work + chain * chain);
 }
-static SpuPath long_path(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces, int blocks /* most of spu_fold */, double* us)
+// bf16, as measured since (101 shapes of 56 to 1024 tokens, 0.74 to 1.15 of it): large calls take three quarters of the above
+static double circ_measured_us(int64_t B, int N, int D)
+{
+    const double work = 0.94 * spu_circ_work_us(B, N, D, LUVC_BF16), chain = 0.01 * N;
+    return 6.5 + std::sqrt(work * work + chain * chain);
+}
+// The kernels for rows of any kind are weighed against each other with estimates that are those of their first forms; which of them
+// a call goes to has stayed as it was, its error with it.
+struct SpuChoice { SpuPath path; double us; };
+static SpuChoice long_path(int B, int N, int D, int sigma, luvc_dtype dt)
 {
     bool half;
-    SpuPath path = SpuPath::Dense;
-    *us = 0.0;
-    auto offer = [&](SpuPath p, double t) {
-        if (path == SpuPath::Dense || t < *us) { path = p; *us = t; }
-    };
-    if (pieces && spu_mat_supported(N, sigma)) offer(SpuPath::Mat, spu_mat_us(B, N, D, sigma));
-    if (spu_fft_supported(N, sigma)) offer(SpuPath::Fft, spu_fft_us(B, N, D, sigma));
-    if (spu_conv_points(N, &half) != 0) offer(SpuPath::Conv, spu_conv_us(B, N, D, dt));
-    // spu_conv takes about five sixths of its estimate, which spu_fold, unlike the others, comes close to
-    const int fold = pieces && path != SpuPath::Dense ? spu_fold_blocks(N, sigma) : 0;
-    if (fold && fold <= blocks) {
-        const double f = spu_fold_us(B, N, D, sigma);
-        if (f < *us * (path == SpuPath::Conv ? 0.84 : 1.0)) { path = SpuPath::Fold; *us = f; }
+    SpuChoice p{SpuPath::Dense, 0.0};
+    if (spu_fft_supported(N, sigma)) p = {SpuPath::Fft, spu_fft_us(B, N, D, sigma)};
+    if (spu_conv_points(N, &half) != 0) {
+        const double us = spu_conv_us(B, N, D, dt);
+        if (p.path == SpuPath::Dense || us < p.us) p = {SpuPath::Conv, us};
     }
-    return path;
+    return p;
 }
-static SpuPath spu_path(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows)
+static SpuChoice or_circ(const SpuChoice& p, int B, int N, int D, luvc_dtype dt, CircRows rows)
 {
-    double us;
-    auto circ = [&] { return rows.circ != CircRows::None && N <= kCircMaxN && circ_us(B, N, D, dt, rows.circ) <= us; };
-    // spu_fold with two blocks of rows takes no call from spu_circ, whose scores are the closer ones (rms error 2.9e-8 for 3.1e-8)
-    const SpuPath one = long_path(B, N, D, sigma, dt, rows.pieces, 1, &us);
-    if (circ()) return SpuPath::Circ;
-    return rows.pieces ? long_path(B, N, D, sigma, dt, true, 2, &us) : one;
+    if (rows == CircRows::None || N > kCircMaxN) return p;
+    const double us = circ_us(B, N, D, dt, rows);
+    return us <= p.us ? SpuChoice{SpuPath::Circ, us} : p;
+}
+// spu_mat and spu_fold take a call from the kernel that it would go to where they are quicker than that one measures.  On 158 shapes
+// of bf16 tokens with every kernel that takes them, drawn over 1 to 32 samples of 49 to 7549 tokens, they take 104 calls in 0.69 of
+// the time (one is slower: 4x637x1536, sigma = 35 20.2 for 19.3) and leave two that they would take in 0.95 of it; on 90 more with the two
+// sides within a quarter of each other, 42 in 0.85 of the time, none slower, and leave five at 0.91 to 0.97.  spu_fold with two
+// blocks of rows takes none from spu_circ, whose scores are the closer ones (rms error 2.9e-8 for 3.1e-8).
+static SpuChoice or_products(SpuChoice p, int B, int N, int D, int sigma)
+{
+    const int blocks = spu_fold_blocks(N, sigma);
+    const bool mat = spu_mat_supported(N, sigma), fold = blocks == 1 || (blocks == 2 && p.path != SpuPath::Circ);
+    if (p.path == SpuPath::Dense || !(mat || fold)) return p;
+    double limit = p.path == SpuPath::Fft ? spu_fft_measured_us(B, N, D, sigma) : p.path == SpuPath::Conv ? spu_conv_measured_us(B, N, D) : circ_measured_us(B, N, D);
+    auto offer = [&](SpuPath path, double us) {
+        if (us < limit) { p = {path, us}; limit = us; }
+    };
+    if (mat) offer(SpuPath::Mat, spu_mat_us(B, N, D, sigma));
+    if (fold) offer(SpuPath::Fold, spu_fold_us(B, N, D, sigma));
+    return p;
+}
+static SpuChoice spu_choice(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows)
+{
+    const SpuChoice p = or_circ(long_path(B, N, D, sigma, dt), B, N, D, dt, rows.circ);
+    return rows.pieces ? or_products(p, B, N, D, sigma) : p;
 }
 SpuRows spu_rows(const void* x, int D, int64_t row_stride, luvc_dtype dt)
 {
@@ -218,9 +239,7 @@ SpuRows spu_rows(const void* x, int D, int64_t row_stride, luvc_dtype dt)
 }
 double spu_alone_us(int B, int N, int D, int sigma, luvc_dtype dt, bool pieces)
 {
-    double us;
-    (void)long_path(B, N, D, sigma, dt, pieces, 2, &us);
-    return us;
+    return spu_choice(B, N, D, sigma, dt, SpuRows{CircRows::None, pieces}).us;
 }
 
 // Energies per tile and group of tiles, arrival words.  Up to kTileGroup tiles have no group level.
@@ -233,23 +252,22 @@ static size_t tile_bytes(int B, int n_tiles, size_t ld, SpuLayout* L, size_t off
     return off;
 }
 
-// most: scratch the call has to do with; a layout that needs more is returned where nothing smaller serves the call.  Short
-// samples then go to the kernels of long ones; spu_conv takes fewer workgroups per sample, down to one per 64 channels,
+// Of a path.  spu_conv takes fewer workgroups per sample where `most` bytes of scratch ask for it, down to one per 64 channels,
 // which is what the direct path's energies take (1 x 8192 x 2048: 256 of them want 8.9 MB, 205 want 7.2).
-SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows, size_t most)
+static SpuLayout layout_of(SpuPath path, int B, int N, int D, int sigma, size_t most)
 {
     SpuLayout L{};
-    L.path = spu_path(B, N, D, sigma, dt, rows);
+    L.path = path;
     if (L.path == SpuPath::Circ) {
         L.n_tiles = 1;
         L.bytes = align_up(spu_circ_bytes(B, N, D));
-        return L.bytes > most ? spu_layout(B, N, D, sigma, dt, SpuRows{CircRows::None, rows.pieces}, most) : L;
+        return L;
     }
     if (L.path == SpuPath::Mat || L.path == SpuPath::Fold) {
         const MatRun run{N, sigma, B, 0};
         L.n_tiles = L.path == SpuPath::Fold ? spu_fold_tiles(D) : spu_mat_plan(&run, 1, D).n_tiles;
         L.bytes = tile_bytes(B, L.n_tiles, (N + 3) / 4 * 4, &L, 0);
-        return L.bytes > most ? spu_layout(B, N, D, sigma, dt, SpuRows{rows.circ, false}, most) : L;
+        return L;
     }
     L.n_tiles = L.path == SpuPath::Fft ? (D + 31) / 32 : (D + 63) / 64;
     const bool dense = L.path == SpuPath::Dense;                     // the one path whose tables and spectra do not stay in LDS
@@ -275,14 +293,36 @@ SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows
     }
 }
 
-// What a call needs whichever way its rows lie: the long kernels' scratch, or spu_circ's words where those are more and it is
-// taken for rows in pairs (where it is taken for single rows, it is for pairs too).
+// most: scratch the call has to do with; a layout that needs more is returned where nothing smaller serves the call.  Short samples then
+// go to the kernels of long ones, and what spu_mat or spu_fold would take to the others.
+SpuLayout spu_layout(int B, int N, int D, int sigma, luvc_dtype dt, SpuRows rows, size_t most)
+{
+    const SpuLayout L = layout_of(spu_choice(B, N, D, sigma, dt, rows).path, B, N, D, sigma, most);
+    if (L.bytes <= most) return L;
+    if (L.path == SpuPath::Circ) return spu_layout(B, N, D, sigma, dt, SpuRows{CircRows::None, rows.pieces}, most);
+    if (L.path == SpuPath::Mat || L.path == SpuPath::Fold) return spu_layout(B, N, D, sigma, dt, SpuRows{rows.circ, false}, most);
+    return L;
+}
+
+// What a call needs whichever way its rows lie: the most of all paths that it may take (for single rows spu_circ is taken where it is
+// for pairs, or less)
 size_t spu_workspace(int B, int N, int D, int sigma, luvc_dtype dt, size_t most)
 {
-    size_t need = spu_layout(B, N, D, sigma, dt, SpuRows{CircRows::None, false}, most).bytes;
-    if (dt == LUVC_BF16) need = std::max(need, spu_layout(B, N, D, sigma, dt, SpuRows{CircRows::None, true}, most).bytes);
-    const size_t circ = N <= kCircMaxN ? align_up(spu_circ_bytes(B, N, D)) : 0;
-    return circ > need && circ <= most && spu_path(B, N, D, sigma, dt, SpuRows{CircRows::Paired, false}) == SpuPath::Circ ? circ : need;
+    const SpuChoice base = long_path(B, N, D, sigma, dt), circ = or_circ(base, B, N, D, dt, CircRows::Paired);
+    size_t need = layout_of(base.path, B, N, D, sigma, most).bytes;
+    SpuPath seen = base.path;
+    auto add = [&](SpuPath path) {
+        if (path == base.path || path == seen) return;
+        seen = path;
+        const size_t bytes = layout_of(path, B, N, D, sigma, most).bytes;
+        if (bytes <= most) need = std::max(need, bytes);
+    };
+    add(circ.path);
+    if (dt == LUVC_BF16) {
+        add(or_products(base, B, N, D, sigma).path);
+        if (circ.path != base.path) add(or_products(circ, B, N, D, sigma).path);
+    }
+    return need;
 }
 
 size_t spu_mat_bytes(const MatRun* runs, int n, int D)

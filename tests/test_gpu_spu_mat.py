@@ -50,6 +50,9 @@ SHAPES = [
     # a multiple more, shorter samples: other kernels
     (8, 1024, 3592, 113, "spu_fft16q"), (8, 2016, 1032, 120, "spu_fold"), (16, 910, 584, 150, "spu_fold"), (10, 1040, 968, 200, "spu_fold"),
     (10, 1280, 968, 150, "spu_fold"), (24, 594, 320, 90, "spu_circ"), (16, 390, 520, 40, "spu_circ"),
+    # either side of the line where one is quicker
+    (6, 351, 3456, 11, "spu_circ"), (14, 368, 1280, 36, "spu_circ"), (2, 576, 3840, 43, "spu_fft16q"), (11, 240, 4480, 6, "spu_mat"), (9, 1485, 1536, 75, "spu_mat"),
+    (8, 1600, 1032, 100, "spu_mat"), (3, 1632, 1280, 49, "spu_mat"),
 ]
 
 
