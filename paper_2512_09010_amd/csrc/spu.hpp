@@ -59,6 +59,7 @@ struct MatRun {
 };
 struct MatPlan {
     int gpw, n_tiles, ld;
+    bool fold;
     int64_t samples;
     size_t lds;
 };

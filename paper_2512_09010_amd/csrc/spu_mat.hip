@@ -12,8 +12,8 @@
 //   twiddle      U[c][b] = V[c][b] e^(2 pi i b c / N)
 //   products 4   z'[a][b] = sum_c e^(2 pi i a c / N1) U[c][b]               rows a, K = (c, re / im): constants x U
 //   energy       |z'|^2 / N^2 over the channel pairs
-// Products 2 and 3 take the multiples j and -j together, rows (cosine, sine) of j >= 0 and the real and the imaginary part of T as two
-// operands: see spu_fold.hip.  16 x 16 tiles with 32 values of K (v_mfma_f32_16x16x32): a lane's result holds four rows 4 g .. 4 g + 3
+// Up to eight multiples have two rows of products 2 and 3 each, real and imaginary part, and K = (b, re / im); of more, j and -j go
+// together, rows (cosine, sine) of j >= 0 and the real and the imaginary part of T as two operands: see spu_fold.hip.  16 x 16 tiles with 32 values of K (v_mfma_f32_16x16x32): a lane's result holds four rows 4 g .. 4 g + 3
 // of one column (g = lane / 16), an operand eight values of K of one row or column.  Each product contracts what were the rows of the
 // one before it, and the order of K is free, so a result, turned into fp16, is the next operand as it lies in the registers.
 //
@@ -32,14 +32,14 @@
 // subsequences (32 KB) straight from memory, three chunks in turn, two on their way; every wavefront reads its own words.  On the way
 // back nothing is fetched but constants, and the next group's first chunks come in meanwhile.
 // Bound: instructions issued by two wavefronts per SIMD.  Per pair and 16 subsequences 20 products (one holds the vector unit
-// up for 8 of its 16 cycles) and about 100 vector instructions of 4 cycles, 72 of which the method needs: twiddles 32, halves 32,
+// up for 8 of its 16 cycles; a row per multiple and part: 19) and about 100 vector instructions of 4 cycles, 72 of which the method needs: twiddles 32, halves 32,
 // energies 8.  us of a call, bf16 tokens that no cache holds, calls one after the other: 8x1024x3584, sigma = 102 33.0 (spu_fft16q 40.9),
-// 16x720x4096, 54 45.8 (58.1), 8x1280x3584, 110 42.0 (49.5), 4x2048x3584, 102 34.8 (42.9), 32x390x3584, 58 54.2 (spu_circ 105),
-// 32x576x896, 57 26.8 (spu_fft16q 32.6), 5x1352x3200, 91 31.6 (spu_conv 63.7).
+// 16x720x4096, 54 44.1 (58.1), 8x1280x3584, 110 42.0 (49.5), 4x2048x3584, 102 34.8 (42.9), 32x390x3584, 58 54.2 (spu_circ 105),
+// 32x576x896, 57 26.8 (spu_fft16q 32.6), 5x1352x3200, 91 31.6 (spu_conv 63.7).  Folded rows for all bands: 16x720x4096 45.8.
 // Tried and not kept: two wavefronts that fetch for the other eight (40 us for 38 at that time); two pairs per wavefront and
 // four wavefronts per SIMD (16x720x4096 71 for 51); products and vector instructions put in turns by hand; tokens through registers
 // (one chunk on its way: 42); bands of up to 32 multiples with a row per multiple and part, as two-term constants (24 products for
-// two blocks of rows; farther off than the general kernels and little quicker).
+// two blocks and more; farther off than the general kernels and little quicker).
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -53,6 +53,7 @@ namespace {
 
 constexpr int kMatTiles = 8;                     // most tiles of 16 subsequences
 constexpr int kMatMultiples = 7;                 // highest multiple of N1
+constexpr int kMatRows = 8;                      // most multiples of a band that has a row for each: 19 products for 20
 constexpr int kMatDirect = 32;                   // tiles of a sample whose energies are added in one go
 
 }  // namespace
@@ -65,7 +66,7 @@ struct MatLaunchRun {
 };
 template <int RUNS> struct MatLaunch { int n; MatLaunchRun run[RUNS]; };
 
-template <int RUNS>
+template <bool FOLD /* multiples j and -j together, or a row for each: up to 8 of them */, int RUNS>
 __global__ void __launch_bounds__(kMatThreads, 2)
 spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t row_stride, int use_hamming, int gpw /* groups of channels per workgroup */,
         int n_tiles /* workgroups per sample */, float* __restrict__ partial /* [samples, n_tiles, ld] */, float* __restrict__ gpartial, const TileSync sy, int ld,
@@ -79,6 +80,7 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
     const MatLaunchRun& run = runs.run[at_run];
     const MatShape& sh = run.sh;
     constexpr int P = kMatPairs, WAVES = kMatWaves, THREADS = kMatThreads;
+    constexpr int NA = FOLD ? 2 : 1;             // results of the way there per pair: of the two parts of T, or of both in one
     extern __shared__ __align__(16) unsigned char smem[];
     const int N = sh.N, N1 = sh.N1, N2 = sh.N2, NT = sh.NT, sigma = sh.sigma;
     mat_u32x4* f2 = reinterpret_cast<mat_u32x4*>(smem);                         // [NT][64] operands of the way there
@@ -135,22 +137,39 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
     if (wave < WAVES / 2 && chunks > 1) issue(1);
     const float inv_n2 = 1.f / (float)N2, inv_n1 = 1.f / (float)N1;
     // In loops that are not unrolled: the code runs once, and its size is what it costs.
-    // way there: row r of lane l is the cosine (r even) or sine of multiple r / 2, subsequences 4 (l / 16) .. + 3 of a tile; way back: cosine
-    // and sine of multiples 2 (l / 16) and the next, subsequence l % 16
+    // way there, FOLD: row r of lane l is the cosine (r even) or sine of multiple r / 2, subsequences 4 (l / 16) .. + 3 of a tile; else rows 2 di,
+    // 2 di + 1 are the real and the imaginary part of multiple di - dn, whose cosines and sines stand once.  Way back: cosine and sine of
+    // multiples 2 (l / 16) and the next, subsequence l % 16
     constexpr double kBoost = (double)(1 << kMatBoost);
+    if constexpr (!FOLD) {
+#pragma clang loop unroll(disable)
+        for (int j = tid; j < NT * 128; j += THREADS) {
+            const int w = j & 3, i = j >> 2, di = i >> 2 & 7, s = 16 * (i >> 5) + 4 * (i & 3) + 2 * (w & 1), m = di - sh.dn + N2;
+            const double2 q0 = ring[mat_rest(s * m, N2, inv_n2)], q1 = ring[mat_rest((s + 1) * m, N2, inv_n2)];
+            const double on = di < sh.nb ? kBoost : 0.0;
+            uint32_t h, l;
+            split16((float)(on * (w & 2 ? q0.y : q0.x)), (float)(on * (w & 2 ? q1.y : q1.x)), h, l);
+            uint32_t* to = reinterpret_cast<uint32_t*>(f2) + (i >> 5) * 256 + (j & 127);
+            to[0] = h;
+            to[128] = l;
+        }
+    }
 #pragma clang loop unroll(disable)
     for (int i = tid; i < NT * 64; i += THREADS) {
         const int l = i & 63, r = l & 15, gg = l >> 4, t = i >> 6;
         uint32_t th[2], tl[2], bh[2], bl[2], be[2];
 #pragma unroll
         for (int w = 0; w < 2; ++w) {
-            const int s = 16 * t + 4 * gg + 2 * w, m = r >> 1;
-            const double2 q0 = ring[mat_rest(s * m, N2, inv_n2)], q1 = ring[mat_rest((s + 1) * m, N2, inv_n2)];
-            split16((float)(kBoost * (r & 1 ? q0.y : q0.x)), (float)(kBoost * (r & 1 ? q1.y : q1.x)), th[w], tl[w]);
-            const double2 q = ring[mat_rest((16 * t + r) * (2 * gg + w), N2, inv_n2)];
-            split16x3(kBoost * q.x, kBoost * q.y, bh[w], bl[w], be[w]);
+            if constexpr (FOLD) {
+                const int s = 16 * t + 4 * gg + 2 * w, m = r >> 1;
+                const double2 q0 = ring[mat_rest(s * m, N2, inv_n2)], q1 = ring[mat_rest((s + 1) * m, N2, inv_n2)];
+                split16((float)(kBoost * (r & 1 ? q0.y : q0.x)), (float)(kBoost * (r & 1 ? q1.y : q1.x)), th[w], tl[w]);
+            }
+            const int m = FOLD ? 2 * gg + w : 2 * gg + w - sh.dn + N2;
+            const double2 q = ring[mat_rest((16 * t + r) * m, N2, inv_n2)];
+            split16x3(kBoost * q.x, (FOLD ? kBoost : -kBoost) * q.y, bh[w], bl[w], be[w]);
         }
-        f2[i] = mat_u32x4{th[0], th[1], tl[0], tl[1]};
+        if constexpr (FOLD) f2[i] = mat_u32x4{th[0], th[1], tl[0], tl[1]};
         i1[i] = mat_u32x4{bl[0], bl[1], bh[0], bh[1]};
         i1e[i] = make_uint2(be[0], be[1]);
     }
@@ -162,17 +181,24 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
         tw[tw_place(i >> 4, i & 15)] = make_float2(q.x * down, q.y * down);
     }
     place_operands(root, N1, inv_n1, sh.place_scale, f1t, i2t);
-    float weight[2][2];                          // M[j] + M[-j], M[j] - M[-j] of a lane's two multiples
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int j = 2 * g + e;
+    // of a lane's two multiples.  FOLD: M[j] + M[-j], M[j] - M[-j]
+    float weight[NA][2];
+    {
         auto at = [&](int k) {
             const int f = k < 0 ? -k : k;
             return c < N1 && f <= sigma && 2 * k != -N ? gm[f <= sigma ? f : 0] : 0.f;
         };
-        const float up = at(c + N1 * j), down = j ? at(c - N1 * j) : 0.f;
-        weight[0][e] = up + down;
-        weight[1][e] = j ? up - down : 0.f;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int j = 2 * g + e;
+            if constexpr (FOLD) {
+                const float up = at(c + N1 * j), down = j ? at(c - N1 * j) : 0.f;
+                weight[0][e] = up + down;
+                weight[NA - 1][e] = j ? up - down : 0.f;
+            } else {
+                weight[0][e] = j < sh.nb ? at(c + N1 * (j - sh.dn)) : 0.f;
+            }
+        }
     }
     __syncthreads();
     mat_u32x4 f1[2][3], i2[2][2];
@@ -188,15 +214,17 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
 
     // this lane's words: places 4 g .. + 3 of subsequence c of a tile, channel pairs 4 wave .. + 3 of a group
     const lds_word* words = (const lds_word*)reinterpret_cast<const uint32_t*>(data) + ((4 * g) * 16 + c) * 32 + (wave ^ (c >> 1)) * 4;
+    const int f2_at = ((c >> 1) * 4 + g) * 2, ro = c & 1;        // in 8-byte units: a row's cosines and sines, in either order
+    const uint32_t f2_sign = ro ? 0x80008000u : 0u;
     const int tw_there = tw_place(c, 4 * g), tw_there2 = tw_place(c, 4 * g + 2);
     int tw_back[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) tw_back[v] = tw_place(4 * g + v, c);
     int ci = 0;
     for (int grp = 0; grp < groups; ++grp) {
-        mat_f32x4 acc[P][2];
+        mat_f32x4 acc[P][NA];
 #pragma unroll
-        for (int p = 0; p < P; ++p) acc[p][0] = acc[p][1] = mat_f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int p = 0; p < P; ++p) acc[p][0] = acc[p][NA - 1] = mat_f32x4{0.f, 0.f, 0.f, 0.f};
         MatScale scale;
         for (int t = 0; t < NT; ++t, ++ci) {
             const lds_word* buf = words + (ci % 3) * (kMatBuf * 4);
@@ -207,35 +235,59 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
             if (__any(m > (scale.unset ? 0.f : 32768.f))) {
                 const float f = into_range(T, m, buf, f1, twiddles, scale);
 #pragma unroll
-                for (int p = 0; p < P; ++p) { acc[p][0] *= f; acc[p][1] *= f; }
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int o = 0; o < NA; ++o) acc[p][o] *= f;
             }
-            // subsequences -> rows of the band.  High and low parts of four subsequences are the eight values of K: one product with the
-            // high parts of the constants twice, one with their low parts
+            // subsequences -> rows of the band
             mat_u32x4 tv[P][2];
+            if constexpr (FOLD) {
+                // the real and the imaginary part; high and low parts of four subsequences are the eight values of K: one product with the
+                // high parts of the constants twice, one with their low parts
 #pragma unroll
-            for (int p = 0; p < P; ++p)
+                for (int p = 0; p < P; ++p)
 #pragma unroll
-                for (int o = 0; o < 2; ++o)
+                    for (int o = 0; o < 2; ++o)
 #pragma unroll
-                    for (int w = 0; w < 2; ++w) {
+                        for (int w = 0; w < 2; ++w) {
+                            uint32_t h, l;
+                            split16(T[p][o][2 * w], T[p][o][2 * w + 1], h, l);
+                            tv[p][o][w] = h; tv[p][o][2 + w] = l;
+                        }
+                const mat_u32x4 k = f2[t * 64 + lane], ah{k[0], k[1], k[0], k[1]}, al{k[2], k[3], k[2], k[3]};
+#pragma unroll
+                for (int o = 0; o < NA; ++o)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) acc[p][o] = mac_f16(acc[p][o], al, tv[p][o]);
+#pragma unroll
+                for (int o = 0; o < NA; ++o)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) acc[p][o] = mac_f16(acc[p][o], ah, tv[p][o]);
+            } else {
+                // high parts, low parts; real and imaginary parts of four subsequences are the eight values of K
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
                         uint32_t h, l;
-                        split16(T[p][o][2 * w], T[p][o][2 * w + 1], h, l);
-                        tv[p][o][w] = h; tv[p][o][2 + w] = l;
+                        split16(T[p][w >> 1][2 * (w & 1)], T[p][w >> 1][2 * (w & 1) + 1], h, l);
+                        tv[p][0][w] = h; tv[p][1][w] = l;
                     }
-            const mat_u32x4 k = f2[t * 64 + lane], ah{k[0], k[1], k[0], k[1]}, al{k[2], k[3], k[2], k[3]};
+                const uint2* at = reinterpret_cast<const uint2*>(f2 + t * 64) + f2_at;
+                const uint2 h0 = at[ro], h1 = at[1 - ro], l0 = at[64 + ro], l1 = at[65 - ro];
+                const mat_u32x4 ah{h0.x ^ f2_sign, h0.y ^ f2_sign, h1.x, h1.y}, al{l0.x ^ f2_sign, l0.y ^ f2_sign, l1.x, l1.y};
 #pragma unroll
-            for (int o = 0; o < 2; ++o)
+                for (int p = 0; p < P; ++p) acc[p][0] = mac_f16(acc[p][0], ah, tv[p][1]);
 #pragma unroll
-                for (int p = 0; p < P; ++p) acc[p][o] = mac_f16(acc[p][o], al, tv[p][o]);
+                for (int p = 0; p < P; ++p) acc[p][0] = mac_f16(acc[p][0], al, tv[p][0]);
 #pragma unroll
-            for (int o = 0; o < 2; ++o)
-#pragma unroll
-                for (int p = 0; p < P; ++p) acc[p][o] = mac_f16(acc[p][o], ah, tv[p][o]);
+                for (int p = 0; p < P; ++p) acc[p][0] = mac_f16(acc[p][0], ah, tv[p][0]);
+            }
             MatTokens::landed(ci + 2 < chunks);
             __syncthreads();
         }
-        // ---- mask, scaled for the way back: the real and the imaginary part's high parts twice, low and high parts
-        mat_u32x4 ghh[P][2], glh[P][2];
+        // ---- mask, scaled for the way back: high parts twice, low and high parts; FOLD: of the real and of the imaginary part
+        mat_u32x4 ghh[P][NA], glh[P][NA];
         float back;
         {
             const bool live = (grp0 + grp) * kMatWidth + 8 * wave < D;          // channels come in eights
@@ -243,28 +295,34 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
 #pragma unroll
             for (int p = 0; p < P; ++p)
 #pragma unroll
-                for (int o = 0; o < 2; ++o)
+                for (int o = 0; o < NA; ++o)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(acc[p][o][v]));
-            m = wave_max(m) * 4.f;               // no weight is larger than 1, folded values are of four
+            m = wave_max(m) * (FOLD ? 4.f : 1.f);           // no weight is larger than 1, folded values are of four
             const int by = clampi(9 - exponent(m), -120, 120);
             const float f = m > 0.f && live ? pow2(by) : 0.f;
             back = pow2(clampi(-(scale.e + by + sh.down), -126, 126));
-            float wf[2][2];
+            float wf[NA][2];
 #pragma unroll
-            for (int o = 0; o < 2; ++o) { wf[o][0] = weight[o][0] * f; wf[o][1] = weight[o][1] * f; }
+            for (int o = 0; o < NA; ++o) { wf[o][0] = weight[o][0] * f; wf[o][1] = weight[o][1] * f; }
 #pragma unroll
             for (int p = 0; p < P; ++p)
 #pragma unroll
                 for (int w = 0; w < 2; ++w) {
-                    const mat_f32x4 &r = acc[p][0], &i = acc[p][1];
                     const int e = 2 * w;
-                    const float gp = wf[0][w], gn = wf[1][w];
-                    uint32_t h, l;
-                    split16(fmaf(gp, r[e], gn * i[e + 1]), fmaf(gp, r[e + 1], -gn * i[e]), h, l);
-                    ghh[p][0][w] = ghh[p][0][2 + w] = glh[p][0][2 + w] = h; glh[p][0][w] = l;
-                    split16(fmaf(gp, i[e], -gn * r[e + 1]), fmaf(gn, r[e], gp * i[e + 1]), h, l);
-                    ghh[p][1][w] = ghh[p][1][2 + w] = glh[p][1][2 + w] = h; glh[p][1][w] = l;
+                    auto set = [&](int o, float a, float b) {
+                        uint32_t h, l;
+                        split16(a, b, h, l);
+                        ghh[p][o][w] = ghh[p][o][2 + w] = glh[p][o][2 + w] = h; glh[p][o][w] = l;
+                    };
+                    if constexpr (FOLD) {
+                        const mat_f32x4 &r = acc[p][0], &i = acc[p][NA - 1];
+                        const float gp = wf[0][w], gn = wf[NA - 1][w];
+                        set(0, fmaf(gp, r[e], gn * i[e + 1]), fmaf(gp, r[e + 1], -gn * i[e]));
+                        set(NA - 1, fmaf(gp, i[e], -gn * r[e + 1]), fmaf(gn, r[e], gp * i[e + 1]));
+                    } else {
+                        set(0, acc[p][0][e] * wf[0][w], acc[p][0][e + 1] * wf[0][w]);
+                    }
                 }
         }
         // The look at the arrival words goes to LDS as well: a result in registers would be waited for in front of every
@@ -285,16 +343,18 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
             for (int v = 0; v < 4; ++v) { const float2 q = tw[t * 256 + tw_back[v]]; wc[v] = q.x; ws[v] = q.y; }
             const mat_u32x4 klh = i1[t * 64 + lane];
             const uint2 ke = i1e[t * 64 + lane];
-            const mat_u32x4 khe{klh[2], klh[3], ke.x, ke.y};
             mat_f32x4 z[P][2];
 #pragma unroll
-            for (int o = 0; o < 2; ++o)
+            for (int o = 0; o < 2; ++o) {
+                // else the operand of the imaginary part: (cos, -sin) -> (sin, cos)
+                auto turn = [&](uint32_t k) { return FOLD || !o ? k : __builtin_amdgcn_alignbit(k, k, 16) ^ 0x8000u; };
+                const mat_u32x4 klo{turn(klh[0]), turn(klh[1]), turn(klh[2]), turn(klh[3])}, kho{klo[2], klo[3], turn(ke.x), turn(ke.y)};
+                const int go = FOLD ? o : 0;
 #pragma unroll
-                for (int p = 0; p < P; ++p) z[p][o] = mac_f16(mat_f32x4{0.f, 0.f, 0.f, 0.f}, glh[p][o], khe);
+                for (int p = 0; p < P; ++p) z[p][o] = mac_f16(mat_f32x4{0.f, 0.f, 0.f, 0.f}, glh[p][go], kho);
 #pragma unroll
-            for (int o = 0; o < 2; ++o)
-#pragma unroll
-                for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], ghh[p][o], klh);
+                for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], ghh[p][go], klo);
+            }
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 float u[2][4];
@@ -441,6 +501,7 @@ MatPlan spu_mat_plan(const MatRun* runs, int n, int D)
         p.ld = std::max(p.ld, (runs[i].N + 3) / 4 * 4);
         p.lds = std::max(p.lds, mat_lds(sh, 1));
         lds_groups = std::max(lds_groups, mat_lds(sh, 2));
+        p.fold = p.fold || sh.nb > kMatRows;
     }
     const int groups = mat_groups(D);
     p.gpw = (int)((p.samples * groups + 255) / 256);
@@ -470,7 +531,7 @@ double spu_mat_work_us(int B, int N, int D, int sigma)
     return (double)B * mat_groups(D) / 256.0 * mat_group_us(sh);
 }
 
-template <int RUNS>
+template <bool FOLD, int RUNS>
 static void mat_launch(const void* x, const MatRun* runs, int n, const MatPlan& p, int D, int64_t row_stride, int use_hamming,
                        float* partial, float* gpartial, const TileSync& sy, float* scores, hipStream_t st)
 {
@@ -485,15 +546,18 @@ static void mat_launch(const void* x, const MatRun* runs, int n, const MatPlan& 
         l.run[i].tok0 = runs[i].tok0;
         samples += runs[i].count;
     }
-    LUVC_LAUNCH("spu_mat", (spu_mat<RUNS>), dim3((unsigned)(samples * p.n_tiles)), dim3(kMatThreads), p.lds, st, (const bf16_t*)x, l, D, row_stride, use_hamming,
+    LUVC_LAUNCH("spu_mat", (spu_mat<FOLD, RUNS>), dim3((unsigned)(samples * p.n_tiles)), dim3(kMatThreads), p.lds, st, (const bf16_t*)x, l, D, row_stride, use_hamming,
                 p.gpw, p.n_tiles, partial, gpartial, sy, p.ld, scores);
 }
 
 luvc_status spu_score_mat(const void* x, const MatRun* runs, int n, const MatPlan& p, int D, int64_t row_stride, int use_hamming,
                           float* partial, float* gpartial, const TileSync& sy, float* scores, hipStream_t st)
 {
-    if (n > 1) mat_launch<kMatMaxRuns>(x, runs, n, p, D, row_stride, use_hamming, partial, gpartial, sy, scores, st);
-    else mat_launch<1>(x, runs, n, p, D, row_stride, use_hamming, partial, gpartial, sy, scores, st);
+#define LUVC_MAT(FOLD, RUNS) mat_launch<FOLD, RUNS>(x, runs, n, p, D, row_stride, use_hamming, partial, gpartial, sy, scores, st)
+    if (n > 1) { if (p.fold) LUVC_MAT(true, kMatMaxRuns); else LUVC_MAT(false, kMatMaxRuns); }
+    else if (p.fold) LUVC_MAT(true, 1);
+    else LUVC_MAT(false, 1);
+#undef LUVC_MAT
     return check_launch("spu score (mat)");
 }
 

@@ -139,15 +139,16 @@ def test_error_against_fp64(oracle, B, N, D, sigma, ham):
     assert error_case(oracle, B, N, D, sigma, ham) == ["spu_mat"]
 
 
-@pytest.mark.parametrize("lengths,D,names", [
-    ([520, 576, 576, 448, 312, 570, 392], 2056, ["spu_mat"]),                    # one launch; the last group of channels holds one piece
-    ([400 + 16 * i for i in range(18)] + [390, 390], 1032, ["spu_mat", "spu_mat"]),        # more runs than a launch takes
-    ([523, 576, 520, 448, 560, 570, 523, 40], 4104, ["spu_mat", "spu_circ"]),    # prime and short ones among them
+@pytest.mark.parametrize("lengths,D,names,share", [
+    ([520, 576, 576, 448, 312, 570, 392], 2056, ["spu_mat"], 10),                # one launch; the last group of channels holds one piece
+    ([520, 576, 576, 448, 312, 570, 392], 2056, ["spu_mat"], 30),                # a row per multiple
+    ([400 + 16 * i for i in range(18)] + [390, 390], 1032, ["spu_mat", "spu_mat"], 10),    # more runs than a launch takes
+    ([523, 576, 520, 448, 560, 570, 523, 40], 4104, ["spu_mat", "spu_circ"], 10),          # prime and short ones among them
 ])
-def test_ragged_samples_in_one_launch(oracle, lengths, D, names):
+def test_ragged_samples_in_one_launch(oracle, lengths, D, names, share):
     rng = np.random.default_rng(D)
     x = wl.cast_io((rng.standard_normal((sum(lengths), D)) * np.exp(rng.standard_normal((sum(lengths), 1)))).astype(np.float32), "bf16")
-    sigmas = [n // 10 for n in lengths]
+    sigmas = [n // share for n in lengths]
     print(f"[spu] ragged {lengths} D={D}", flush=True)
     xd, out = to_dev(x, "bf16"), {}
     got = kernels(lambda: out.update(lv.luvc_spu_stage_ragged(xd, lengths, sigmas, [max(1, n // 5) for n in lengths])))
