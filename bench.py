@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -43,6 +44,26 @@ def parse():
 
 HEADLINE = 2            # the largest of the four target workloads (46 080 tokens per step)
 TRAFFIC_FILE = os.path.join("profiles", "hbm_traffic.json")
+
+
+def mat_flops(N, sigma, fold):
+    """spu_mat, spu_fold: operations of the matrix instructions of a channel pair, 16 x 16 x 32 each, for 16 subsequences at a time, N = N1 N2
+    with N1 in 9 .. 16: 19 where the band meets up to eight multiples of N1, 20 up to the seventh on either side, 26 (spu_fold) beyond.
+    Tokens are exact operands in bf16; from the first transform on values and constants are sums of fp16 terms, two to three
+    instructions for one product in fp32."""
+    best = None
+    for n in range(16, 8, -1):
+        tiles, top = -(-N // n // 16), -(-sigma // n)
+        if N % n or tiles > (16 if fold else 8) or top > (15 if fold else 7) or (best and tiles >= best[0]):
+            continue
+        best = (tiles, 26 if top > 7 else 19 if not fold and top + sigma // n + 1 <= 8 else 20)
+    return best[0] * best[1] * 2 * 16 * 16 * 32 if best else 0
+
+
+def conv_flops(N):
+    """spu_conv: two transforms of M points of a channel pair."""
+    M = next((m for m in (1536, 2048, 3072, 4096, 6144, 8192, 12288, 16384) if 2 * N <= m or (N == m and m & (m - 1) == 0)), 0)
+    return 2 * 5 * M * math.log2(max(M, 2))
 
 
 def run_config(cfg, args, lv, wl, torch, np):
@@ -218,11 +239,13 @@ def run_config(cfg, args, lv, wl, torch, np):
         # This is the work of Eq. 4-8 as the transform decomposition states it; a kernel that reaches the same
         # scores with fewer operations is credited with these, not with its own count.
         fft_flops = w.spu_B * (w.spu_D / 2) * (2 * n2 * 5 * n1 * np.log2(n1) + 2 * 8 * n2 * L + 4 * w.spu_N)
+    pairs = w.spu_B * w.spu_D / 2
     work = {
         "oim_halve_pair": (oim_bytes, None, "hbm"), "oim_halve": (oim_bytes, None, "hbm"),
-        "spu_fft16q": (score_bytes, fft_flops, "alu"),
+        "spu_fft16q": (score_bytes, fft_flops, "alu"), "spu_conv": (score_bytes, pairs * conv_flops(w.spu_N), "alu"),
         "spu_fwd_dense": (score_bytes, None, "hbm"), "spu_circ": (score_bytes, None, "hbm"),
-        "spu_mat": (score_bytes, None, "hbm"), "spu_fold": (score_bytes, None, "hbm"), "spu_conv": (score_bytes, None, "hbm"),
+        "spu_mat": (score_bytes, pairs * mat_flops(w.spu_N, w.sigma, False), "matrix"),
+        "spu_fold": (score_bytes, pairs * mat_flops(w.spu_N, w.sigma, True), "matrix"),
         "spu_gather": (prune_bytes, None, "hbm"), "spu_prune_fused": (prune_bytes, None, "hbm"),
     }
     try:
@@ -243,7 +266,7 @@ def run_config(cfg, args, lv, wl, torch, np):
             k["hbm_GBps"] = round(by / per_step / (avg_ms * 1e-3) / 1e9, 1)
             k["hbm_frac"] = round(k["hbm_GBps"] / HBM_PEAK_GBS, 4)
             if fl:
-                k["algorithmic_flops_per_launch"] = int(fl / per_step)
+                k["matrix_flops_per_launch" if bound == "matrix" else "algorithmic_flops_per_launch"] = int(fl / per_step)
                 k["TFLOPs"] = round(fl / per_step / (avg_ms * 1e-3) / 1e12, 2)
         t = measured_traffic.get(name)
         if t:
@@ -251,11 +274,12 @@ def run_config(cfg, args, lv, wl, torch, np):
         kernels.append(k)
     kernels.sort(key=lambda k: -k["us_per_step"])
     dom = kernels[0]
-    if dom.get("bound") == "alu":
-        # fp32 vector peak of MI355X: 256 CUs x 4 SIMDs x 16 lanes x 2 (packed) x 2 flops x 2.4 GHz
-        roofline = {"bound": "alu", "kernel": dom["kernel"], "achieved": dom["TFLOPs"], "peak": 157.3, "unit": "TFLOP/s",
-                    "frac": round(dom["TFLOPs"] / 157.3, 4), "traffic": dom.get("traffic_bytes_per_launch"),
-                    "avg_us": dom["avg_us"], "algorithmic_flops": dom["algorithmic_flops_per_launch"],
+    if dom.get("bound") in ("alu", "matrix"):
+        # fp32 vector peak of MI355X: 256 CUs x 4 SIMDs x 16 lanes x 2 (packed) x 2 flops x 2.4 GHz; matrix cores: dense bf16 / fp16
+        peak, flops = (157.3, "algorithmic_flops") if dom["bound"] == "alu" else (2500.0, "matrix_flops")
+        roofline = {"bound": dom["bound"], "kernel": dom["kernel"], "achieved": dom["TFLOPs"], "peak": peak, "unit": "TFLOP/s",
+                    "frac": round(dom["TFLOPs"] / peak, 4), "traffic": dom.get("traffic_bytes_per_launch"),
+                    "avg_us": dom["avg_us"], flops: dom[flops + "_per_launch"],
                     "hbm_view": {"achieved": dom["hbm_GBps"], "peak": HBM_PEAK_GBS, "frac": dom["hbm_frac"],
                                  "algorithmic_bytes": dom["algorithmic_bytes_per_launch"]}}
     else:
