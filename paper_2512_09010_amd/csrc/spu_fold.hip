@@ -314,30 +314,7 @@ spu_fold(const bf16_t* __restrict__ x, const MatShape sh, int D, int64_t row_str
 #pragma unroll
                     for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], gh[p][o][ks], kh[ks]);
             }
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                float u[2][4];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    u[0][v] = fmaf(z[p][0][v], wc[v], -z[p][1][v] * ws[v]);
-                    u[1][v] = fmaf(z[p][1][v], wc[v], z[p][0][v] * ws[v]);
-                }
-                mat_u32x4 uh, ul;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    uint32_t h, l;
-                    split16(u[w >> 1][2 * (w & 1)], u[w >> 1][2 * (w & 1) + 1], h, l);
-                    uh[w] = h; ul[w] = l;
-                }
-#pragma unroll
-                for (int o = 0; o < 2; ++o) {
-                    mat_f32x4 y = mac_f16(mat_f32x4{0.f, 0.f, 0.f, 0.f}, i2[o][0], ul);
-                    y = mac_f16(y, i2[o][1], uh);
-                    y = mac_f16(y, i2[o][0], uh);
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) sum[v] = fmaf(y[v], y[v], sum[v]);
-                }
-            }
+            bins_to_energies(sum, z, wc, ws, i2);
             esum[((t & 7) * WAVES + wave) * 64 + lane] = make_float4(sum[0] * back * back, sum[1] * back * back, sum[2] * back * back, sum[3] * back * back);
             if ((t & 3) == 3 || t == NT - 1) {
                 // four tiles: the sums over the wavefronts; the next four go to the other half meanwhile

@@ -355,30 +355,7 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
 #pragma unroll
                 for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], ghh[p][go], klo);
             }
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                float u[2][4];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    u[0][v] = fmaf(z[p][0][v], wc[v], -z[p][1][v] * ws[v]);
-                    u[1][v] = fmaf(z[p][1][v], wc[v], z[p][0][v] * ws[v]);
-                }
-                mat_u32x4 uh, ul;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    uint32_t h, l;
-                    split16(u[w >> 1][2 * (w & 1)], u[w >> 1][2 * (w & 1) + 1], h, l);
-                    uh[w] = h; ul[w] = l;
-                }
-#pragma unroll
-                for (int o = 0; o < 2; ++o) {
-                    mat_f32x4 y = mac_f16(mat_f32x4{0.f, 0.f, 0.f, 0.f}, i2[o][0], ul);
-                    y = mac_f16(y, i2[o][1], uh);
-                    y = mac_f16(y, i2[o][0], uh);
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) sum[v] = fmaf(y[v], y[v], sum[v]);
-                }
-            }
+            bins_to_energies(sum, z, wc, ws, i2);
             float4* at = esum + (wave * NT + t) * 64 + lane;
             float4 q = grp ? *at : make_float4(0.f, 0.f, 0.f, 0.f);
             q.x = fmaf(sum[0] * back, back, q.x);

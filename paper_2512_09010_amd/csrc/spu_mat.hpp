@@ -250,6 +250,35 @@ __device__ __forceinline__ float into_range(mat_f32x4 (&T)[P][2], float m, const
     scale.unset = false;
     return sums;
 }
+// The twiddle (wc, ws) and bins c -> places, of a tile on the way back: energies of its subsequence c at places 4 g + v, added up over P pairs
+template <int P>
+__device__ __forceinline__ void bins_to_energies(float (&sum)[4], const mat_f32x4 (&z)[P][2], const float (&wc)[4], const float (&ws)[4], const mat_u32x4 (&i2)[2][2])
+{
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        float u[2][4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            u[0][v] = fmaf(z[p][0][v], wc[v], -z[p][1][v] * ws[v]);
+            u[1][v] = fmaf(z[p][1][v], wc[v], z[p][0][v] * ws[v]);
+        }
+        mat_u32x4 uh, ul;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            uint32_t h, l;
+            split16(u[w >> 1][2 * (w & 1)], u[w >> 1][2 * (w & 1) + 1], h, l);
+            uh[w] = h; ul[w] = l;
+        }
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            mat_f32x4 y = mac_f16(mat_f32x4{0.f, 0.f, 0.f, 0.f}, i2[o][0], ul);
+            y = mac_f16(y, i2[o][1], uh);
+            y = mac_f16(y, i2[o][0], uh);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sum[v] = fmaf(y[v], y[v], sum[v]);
+        }
+    }
+}
 
 }  // namespace
 
