@@ -430,7 +430,7 @@ void mat_scales(MatShape* sh, int ways)
     double band = 0.0;
     for (int i = 0; i < sh->nb; ++i) band += circle.of[sh->N2 / std::gcd(sh->N2, std::abs(i - sh->dn))];
     sh->place_scale = 1.0 + std::ldexp((double)kRadius[sh->N1 - 9], -20);
-    sh->down = std::ilogb((double)sh->N);
+    sh->down = (int)std::lround(std::log2(sh->N * sh->place_scale));
     const double one = std::ldexp(1.0 - ways * band / sh->nb + 0.2e-8, sh->down) / (sh->N * sh->place_scale);
     sh->energy = one * one;
 }

@@ -286,7 +286,7 @@ struct MatShape {
     double inv_N, inv_N_1, inv_N1;               // 1 / N, 1 / (N - 1), 1 / N1
     double place_scale, energy;                  // mat_scales
     int N, N1, N2, NT /* tiles of 16 subsequences */, sigma, dn /* lowest multiple of N1 in the band, negated */, nb /* multiples */;
-    int down;                                    // N = 2^down .. 2^(down + 1) - 1: energies are formed 2^(-2 down) of what they are without 1 / N
+    int down;                                    // the power of two next to N place_scale, which energies in fp32 are without: half to twice what they are
 };
 void mat_scales(MatShape* sh, int ways);
 

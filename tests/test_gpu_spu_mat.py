@@ -93,6 +93,17 @@ def test_values_out_of_the_range_of_fp16(oracle):
     assert torch.equal(got[1:], clean[1:]) and torch.isnan(got[0]).all()
 
 
+@pytest.mark.parametrize("B,N,D,sigma,name", [(8, 2016, 1032, 100, "spu_mat"), (8, 1024, 1032, 60, "spu_mat"), (4, 2044, 1032, 90, "spu_fold")])
+def test_largest_energies(oracle, B, N, D, sigma, name):
+    """All of a tile's 64 channels at 2.2e18 in every token: their energy, 3.1e38, is just below what fp32 holds."""
+    x = wl.cast_io(np.full((1, N, D), 2.2e18, np.float32), "bf16")
+    ref = oracle.spu_score(wl.widen(x, "bf16"), sigma, True)
+    xd = to_dev(x, "bf16").expand(B, N, D).contiguous()
+    got = lv.luvc_spu_score(xd, sigma, True).cpu().numpy().astype(np.float64)
+    assert (np.abs(got / ref - 1.0) <= SCORE_RTOL).all()
+    assert kernels(lambda: lv.luvc_spu_score(xd, sigma, True)) == [name]
+
+
 # the first subsequences hold `first`, those behind them `late`: the scale that `first` sets takes `late` beyond fp32 by itself
 GROWTHS = [(3e-34, 3e3), (1e-35, 1e4), (1e-38, 1e15), (1e-30, 1e10)]
 
