@@ -13,10 +13,10 @@
 // oim_wide_line, one workgroup per line (lines of at most 128 tokens).  The decisions are the fp64 decisions of the
 // method, reached in two steps:
 //   1. SCREENING.  The source x destination dot products of the line on the matrix cores in the storage precision
-//      (v_mfma_f32_32x32x16_bf16, or four v_mfma_f32_32x32x2_f32 for fp32 tokens): a 32 x 32 tile at a time, eight
+//      (v_mfma_f32_16x16x32_bf16, or four v_mfma_f32_16x16x4_f32 for fp32 tokens): a 32 x 32 tile at a time, eight
 //      wavefronts split the channels, every token byte is fetched once per tile.  The squared norms are summed in fp32
 //      on the way (in fp64, they took as long as everything else of the screening).  A screened cosine is taken to be
-//      within eps = (5 D / 32 + 48) 2^-23 of the fp64 cosine.  A wavefront contracts c <= D / 8 + 16 channels, which is
+//      within eps = (5 D / 32 + 53) 2^-23 of the fp64 cosine.  A wavefront contracts c <= D / 8 + 32 channels, which is
 //      at most c accumulation steps of 2^-23 each (relative to the sum of the magnitudes of the products, which is at
 //      most the product of the norms; the products of bf16 values are exact in fp32) - tests/test_gpu_oim_wide.py pins
 //      the contraction at that rate against fp64 on adversarial rows - and adding the eight parts is 4 more.  A squared
@@ -39,10 +39,15 @@
 //      rows to merge, the wavefronts share the channels of each.
 // All lines of a grid start together, so what follows the screening is serial time of the launch: no lists or
 // flags are handed through LDS where a ballot does, and each step after the screening is one barrier.
-// Bound: the screening, by the rate at which the tokens arrive (8 x 64 x 64 x 1280 bf16: 84 MB a pass), then latency
-// (three operations of merge number 2 on that grid, six passes and the last copy: 212 us; 185 with eight wavefronts per line
-// where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening; with the bound of step 1 and
-// the shared merges of step 4 168).
+// Bound: the screening, by the rate at which the tokens arrive (8 x 64 x 64 x 1280 bf16: 84 MB a pass), then latency.
+// Of a pass of that grid (20.4 us) the tokens of the last lines are there after 13.9 us, their screened cosines 1.5 us later, and the fp64
+// repeats (0 .. 4), the layout (1) and the merged rows (1.5) follow.  Six passes of merge number 2 and the last copy: 212 us;
+// 185 with eight wavefronts per line where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening; with
+// the bound of step 1 and the shared merges of step 4 168.  149 with the loads of 64 bytes a row (below; 10 us of the 19),
+// products added up in pieces of 16 bytes beside the norms (2.4 us a pass before), contenders from the m-th highest cosine
+// instead of a comparison with every source (2.1 to 2.8 us a pass before, 0.5) and the anchors fetched with the ids.
+// Lines of up to 32 tokens read half as much as a tile of 64: 12 x 32 x 32 x 1024, six passes, 97.3 -> 81.0 us, 8 x 24 x 24 x 1024
+// fp32, radius 2, four 63.7 -> 56.2, 1 x 16 x 16 x 768, six 57.2 -> 48.0.  Long ones: 4 x 100 x 100 x 1024, two 118 -> 97.
 #include <type_traits>
 
 #include "common.hpp"
@@ -55,8 +60,8 @@ namespace luvc {
 
 namespace {
 
-// floats between the rows of the screened matrix: the smallest value of at least n_dst that is 4 mod 32
-__host__ __device__ inline int lazy_row_stride(int n_dst) { return n_dst <= 4 ? 4 : 32 * ((n_dst - 4 + 31) / 32) + 4; }
+// floats between the rows (a destination each) of the screened matrix: whole tiles of sources, and 4 mod 32
+__host__ __device__ inline int lazy_row_stride(int n_src) { return 32 * ((n_src + 31) / 32) + 4; }
 
 }  // namespace
 
@@ -64,21 +69,20 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_lz __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4_lz __attribute__((ext_vector_type(4)));
 
 // What a lane feeds to the matrix cores per step of the screening contraction: 16 bytes of a token.  Lane l belongs
-// to row l % 32 of the tile (a source for the A side, a destination for the B side) and to half l / 32 of the
-// step's channels.
+// to row l % 16 of a 16 x 16 product (a source for the A side, a destination for the B side) and to quarter l / 16 of the
+// step's channels: 64 bytes of 16 rows to a load.
 template <typename T> struct screen;
 template <> struct screen<bf16_t> {
-    static constexpr int KS = 16, KL = 8;      // channels per step, per lane
-    static constexpr int LOADS = 5;            // steps in flight
-    __device__ static __forceinline__ f32x16 mac(f32x16 acc, const u32x4& a, const u32x4& c)
+    static constexpr int KS = 32, KL = 8;      // channels per step, per lane
+    __device__ static __forceinline__ f32x4_lz mac(f32x4_lz acc, const u32x4& a, const u32x4& c)
     {
         bf16x8_t va, vc;
         __builtin_memcpy(&va, &a, 16);
         __builtin_memcpy(&vc, &c, 16);
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, vc, acc, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, vc, acc, 0, 0, 0);
     }
     __device__ static __forceinline__ float sq(const u32x4& a, float acc)
     {
@@ -102,12 +106,12 @@ template <> struct screen<bf16_t> {
     }
 };
 template <> struct screen<float> {
-    static constexpr int KS = 8, KL = 4, LOADS = 4;
-    // instruction e contracts channels {e, 4 + e} of the step: the same pairing on both sides
-    __device__ static __forceinline__ f32x16 mac(f32x16 acc, const u32x4& a, const u32x4& c)
+    static constexpr int KS = 16, KL = 4;
+    // instruction e contracts channels {e, 4 + e, 8 + e, 12 + e} of the step: the same grouping on both sides
+    __device__ static __forceinline__ f32x4_lz mac(f32x4_lz acc, const u32x4& a, const u32x4& c)
     {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(c[e]), acc, 0, 0, 0);
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(c[e]), acc, 0, 0, 0);
         return acc;
     }
     __device__ static __forceinline__ float sq(const u32x4& a, float acc)
@@ -165,6 +169,28 @@ __device__ __forceinline__ void cos64_wave2(const T* a, const T* c1, const T* c2
     s2 = v[4] / (na * norm(v[2]));
 }
 
+// sum over the four quarters of the wavefront, in every lane
+__device__ __forceinline__ float quarters_total(float v)
+{
+    auto swapped = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(swapped[0]) + __uint_as_float(swapped[1]);
+    swapped = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(swapped[0]) + __uint_as_float(swapped[1]);
+}
+
+// largest value over the wavefront, in every lane
+__device__ __forceinline__ float wave_max32(float v)
+{
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true)));    // lane ^ 1
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true)));    // lane ^ 2
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true)));   // row_half_mirror
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, true)));   // row_mirror
+    auto swapped = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(swapped[0]), __uint_as_float(swapped[1]));
+    swapped = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(swapped[0]), __uint_as_float(swapped[1]));
+}
+
 // largest value over groups of eight lanes, in every lane
 __device__ __forceinline__ float oct_max(float v)
 {
@@ -188,18 +214,23 @@ __global__ void __launch_bounds__(64)
 selftest_screen_tile(const T* __restrict__ a, const T* __restrict__ c, int D, float* __restrict__ out)
 {
     using sc = screen<T>;
-    const int lane = threadIdx.x, r = lane & 31, kh = lane >> 5;
-    f32x16 acc;
+    const int lane = threadIdx.x, r = lane & 15, kq = lane >> 4;
+    f32x4_lz acc[2][2];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int q = 0; q < 4; ++q) acc[q >> 1][q & 1] = f32x4_lz{0.f, 0.f, 0.f, 0.f};
     for (int d = 0; d < D; d += sc::KS)         // the same trip count in every lane: the matrix instructions want the whole wavefront
-        acc = sc::mac(acc, piece(a + (int64_t)r * D, D, d + kh * sc::KL, true), piece(c + (int64_t)r * D, D, d + kh * sc::KL, true));
 #pragma unroll
-    for (int v = 0; v < 16; ++v) out[(8 * (v >> 2) + 4 * kh + (v & 3)) * 32 + r] = acc[v];
+        for (int q = 0; q < 4; ++q)
+            acc[q >> 1][q & 1] = sc::mac(acc[q >> 1][q & 1], piece(a + (int64_t)(16 * (q >> 1) + r) * D, D, d + kq * sc::KL, true),
+                                         piece(c + (int64_t)(16 * (q & 1) + r) * D, D, d + kq * sc::KL, true));
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[(16 * (q >> 1) + 4 * kq + v) * 32 + 16 * (q & 1) + r] = acc[q >> 1][q & 1][v];
 }
 
 constexpr int kScreenWaves = 8;                  // wavefronts that split its channels
-template <typename T>
+template <typename T, int TILE /* 1, 2: lines of up to 32, 64 tokens, which are one tile; 0: any */>
 __global__ void __launch_bounds__(1024)
 oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric [.., Dk] the decisions are taken on, or null: x */,
               T* ovk /* its overlay */, int Dk, const int32_t* __restrict__ idx_in /* null: identity */,
@@ -208,22 +239,24 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
               int32_t* __restrict__ pass_map /* or null */)
 {
     using sc = screen<T>;
+    constexpr bool ONE = TILE > 0;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int len = g.axis ? g.w : g.h, nlines = g.axis ? g.h : g.w;
     const int n_src = (len + 1) / 2, n_dst = len / 2;
     const int Wo = g.axis ? g.w - g.m : g.w, Ho = g.axis ? g.h : g.h - g.m;
     double* escore = reinterpret_cast<double*>(smem_raw);              // [64] fp64 cosine of a contender with its best destination
-    float* P = reinterpret_cast<float*>(escore + 64);    // [kScreenWaves][32 * 32] a tile, the part of each wavefront
-    // [n_src][sd] screened dot products, then cosines.  Rows are sd = 4 mod 32 floats apart: lanes on neighbouring sources
-    // fall into different banks
-    float* S = P + kScreenWaves * 1024;
-    const int sd = lazy_row_stride(n_dst);
-    float* pn = S + n_src * sd;                          // [kScreenWaves][len] squared norms, the part of each wavefront
+    // [kScreenWaves][32 destinations][8] a tile, the part of each wavefront: pieces of four sources, in an order that depends on the
+    // destination, so that 16-byte accesses of eight destinations fall into different banks
+    float4* P = reinterpret_cast<float4*>(escore + 64);
+    float* S = reinterpret_cast<float*>(P + kScreenWaves * 256);       // [n_dst][sd] screened dot products
+    const int sd = lazy_row_stride(n_src);
+    float* pn = S + n_dst * sd;                          // [kScreenWaves][len] squared norms, the part of each wavefront
     float* inv32 = pn + kScreenWaves * len;              // [len] 1 / norm
     float* b32 = inv32 + len;                            // [64] best screened cosine of a source
     int* rid = reinterpret_cast<int*>(b32 + 64);         // [len] row id of the token at position p
     int* sz = rid + len;                                 // [len] its size
-    int* ebest = sz + len;                               // [64] best destination of a contender
+    int* kept = sz + len;                                // [len] its anchor
+    int* ebest = kept + len;                             // [64] best destination of a contender
     int* wild = ebest + 64;                              // [1] a norm that fp32 does not hold
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), NW = blockDim.x >> 6;
@@ -237,126 +270,180 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     const T* dx = xk ? xk : x;
     const T* dov = xk ? ovk : ov;
     const int dD = xk ? Dk : g.D;
-    float tau = 2.f * (0.15625f * (float)dD + 48.f) * 1.1920929e-7f;  // 2 eps
+    float tau = 2.f * (0.15625f * (float)dD + 53.f) * 1.1920929e-7f;  // 2 eps
 
     for (int p = tid; p < len; p += blockDim.x) {
         const int f = in_flat(p);
         rid[p] = idx_in ? idx_in[img + f] : f;
         sz[p] = sizes_in ? sizes_in[img + f] : 1;
+        kept[p] = kept_in ? kept_in[img + f] : f;
     }
     if (tid == 0) *wild = 0;
     __syncthreads();
 
     // ------------------------------------------------------------------ 1. screening: dot products and squared norms
-    // Result layout of the 32 x 32 instructions: lane l, register v holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.
+    // Result layout of the 16 x 16 instructions: lane l, register v holds row 4 (l / 16) + v, column l % 16.
     {
-        constexpr int LOADS = sc::LOADS, STEP = kScreenWaves * sc::KS;
-        const int tiles_s = (n_src + 31) / 32, tiles_d = (n_dst + 31) / 32, tiles = tiles_s * tiles_d;
-        const int r = lane & 31, kh = lane >> 5;
+        constexpr int SUB = TILE == 1 ? 1 : 2;                                // 16 x 16 products along each side of a tile
+        constexpr bool BLOCKS = TILE == 2 && sizeof(T) == 2;
+        constexpr int LOADS = TILE == 1 ? 6 : BLOCKS ? 5 : 4;
+        const int tiles_s = ONE ? 1 : (n_src + 31) / 32, tiles_d = ONE ? n_dst > 0 : (n_dst + 31) / 32, tiles = tiles_s * tiles_d;
+        const int r = lane & 15, kq = lane >> 4;
         const bool screens = wave < kScreenWaves;
-        // Wavefront w takes steps w, w + kScreenWaves, ... of KS channels, a lane its half of each; the trip count is the
-        // same in every lane (the matrix instructions want the whole wavefront).  Rows and channels that are not there are
-        // read from where some are, without a branch - the compiler waits for everything in flight at a join - and
-        // such channels are masked.  LOADS steps stay in flight, across the tiles of a long line too.
-        const int first = wave * sc::KS + kh * sc::KL, steps = wave * sc::KS < dD ? (dD - wave * sc::KS + STEP - 1) / STEP : 0;
-        const T *tok_s = dx, *tok_d = dx;
-        u32x4 ra[LOADS], rc[LOADS];
-        auto fetch = [&](int u, int d) {
-            const int at = d < dD ? d : dD - sc::KL;
-            ra[u] = *reinterpret_cast<const u32x4*>(tok_s + at);
-            rc[u] = *reinterpret_cast<const u32x4*>(tok_d + at);
-        };
+        // A wavefront owns a run of steps of KS channels, a lane its quarter of each; the trip count is the same in every lane (the
+        // matrix instructions want the whole wavefront).  Rows that are not there, and steps beyond the last, are read from where some
+        // are, without a branch: the compiler waits for everything in flight at a join.  Channels that do not fill a step are the last
+        // wavefront's, at the end.
+        // LOADS steps stay in flight, across the tiles of a long line too, asked for row by row: the two halves of a cache line one
+        // after the other.  Reads of 8 x 64 x 64 x 1280 bf16 in this order, nothing done with them, 12.8 us from the shared cache
+        // and 15.5 from memory; 32 bytes of 32 rows to a load and the halves of a line with different wavefronts 15.4 and 21.2; step
+        // by step 13.7 and 18.7; in the order of memory 12.3 and 14.4.
+        const int all = dD / sc::KS, step0 = wave * all / kScreenWaves, steps = (wave + 1) * all / kScreenWaves - step0;
+        const int rest = wave == kScreenWaves - 1 ? dD - all * sc::KS : 0;
+        const T* tok[2 * SUB];                                                // sources r, 16 + r and destinations r, 16 + r of the tile
+        u32x4 raw[LOADS][2 * SUB];
+        auto fetch = [&](int u, int i, int step) { raw[u][i] = *reinterpret_cast<const u32x4*>(tok[i] + sc::KS * step); };
         auto begin_tile = [&](int t) {
-            const int js = t / tiles_d * 32 + r, jd = t % tiles_d * 32 + r;
-            tok_s = row_of<T>(dx, dov, b, rid[js < n_src ? 2 * js : 0], g, dD);
-            tok_d = row_of<T>(dx, dov, b, rid[jd < n_dst ? 2 * jd + 1 : 0], g, dD);
-            if (steps >= LOADS) {
+            const int js = (ONE ? 0 : t / tiles_d * 32) + r, jd = (ONE ? 0 : t % tiles_d * 32) + r;
 #pragma unroll
-                for (int u = 0; u < LOADS; ++u) fetch(u, first + STEP * u);
-            } else {
-#pragma unroll
-                for (int u = 0; u < LOADS; ++u)
-                    if (u < steps) fetch(u, first + STEP * u);
+            for (int i = 0; i < SUB; ++i) {
+                const int at = step0 * sc::KS + kq * sc::KL;
+                tok[i] = row_of<T>(dx, dov, b, rid[js + 16 * i < n_src ? 2 * (js + 16 * i) : 0], g, dD) + at;
+                tok[SUB + i] = row_of<T>(dx, dov, b, rid[jd + 16 * i < n_dst ? 2 * (jd + 16 * i) + 1 : 0], g, dD) + at;
             }
+            auto fetch_steps = [&](auto n) {
+#pragma unroll
+                for (int i = 0; i < 2 * SUB; ++i)
+#pragma unroll
+                    for (int u = 0; u < decltype(n)::value; ++u) fetch(u, i, u);
+            };
+            if (steps >= LOADS) fetch_steps(std::integral_constant<int, LOADS>{});
+            else if (!ONE) {                             // (few registers are left beside the next tile's)
+#pragma unroll
+                for (int u = 0; u < LOADS - 1; ++u)
+                    if (u < steps) {
+#pragma unroll
+                        for (int i = 0; i < 2 * SUB; ++i) fetch(u, i, u);
+                    }
+            }
+            else if (steps == 5) fetch_steps(std::integral_constant<int, LOADS < 5 ? 0 : 5>{});
+            else if (steps == 4) fetch_steps(std::integral_constant<int, LOADS < 4 ? 0 : 4>{});
+            else if (steps == 3) fetch_steps(std::integral_constant<int, 3>{});
+            else if (steps == 2) fetch_steps(std::integral_constant<int, 2>{});
+            else if (steps == 1) fetch_steps(std::integral_constant<int, 1>{});
         };
         if (screens && tiles > 0) begin_tile(0);
         for (int t = 0; t < tiles; ++t) {
-            const int ts = t / tiles_d, td = t % tiles_d;
+            const int ts = ONE ? 0 : t / tiles_d, td = ONE ? 0 : t % tiles_d;
             if (screens) {
-                f32x16 acc;
+                f32x4_lz acc[SUB][SUB];
+                float n2[2 * SUB];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-                float na = 0.f, nc = 0.f;
-                auto use = [&](int u, int d) {
-                    const uint32_t there = d < dD ? 0xffffffffu : 0u;
-                    const u32x4 a = ra[u] & there, c = rc[u] & there;
-                    acc = sc::mac(acc, a, c);
-                    na = sc::sq(a, na);
-                    nc = sc::sq(c, nc);
+                for (int i = 0; i < 2 * SUB; ++i) n2[i] = 0.f;
+#pragma unroll
+                for (int q = 0; q < SUB * SUB; ++q) acc[q / SUB][q % SUB] = f32x4_lz{0.f, 0.f, 0.f, 0.f};
+                auto use = [&](const u32x4 (&v)[2 * SUB]) {
+#pragma unroll
+                    for (int i = 0; i < 2 * SUB; ++i) n2[i] = sc::sq(v[i], n2[i]);
+#pragma unroll
+                    for (int q = 0; q < SUB * SUB; ++q) acc[q / SUB][q % SUB] = sc::mac(acc[q / SUB][q % SUB], v[q / SUB], v[SUB + q % SUB]);
                 };
-                int d = first, left = steps;
-                for (; left > LOADS; d += STEP * LOADS, left -= LOADS) {
+                int left = steps;
+                for (; left > LOADS; left -= LOADS) {
 #pragma unroll
                     for (int u = 0; u < LOADS; ++u) {
-                        use(u, d + STEP * u);
-                        fetch(u, d + STEP * (u + LOADS));
+                        use(raw[u]);
+                        if (BLOCKS) continue;
+                        const int step = min(u + LOADS, left - 1);
+#pragma unroll
+                        for (int i = 0; i < 2 * SUB; ++i) fetch(u, i, step);
                         __builtin_amdgcn_sched_barrier(0);
                     }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < 2 * SUB; ++i) tok[i] += sc::KS * LOADS;
+                    if (!BLOCKS) continue;
+#pragma unroll
+                    for (int i = 0; i < 2 * SUB; ++i)
+#pragma unroll
+                        for (int u = 0; u < LOADS; ++u) fetch(u, i, min(u, left - LOADS - 1));
                 }
 #pragma unroll
                 for (int u = 0; u < LOADS; ++u)
-                    if (u < left) use(u, d + STEP * u);
-                if (t + 1 < tiles) begin_tile(t + 1);
+                    if (u < left) use(raw[u]);
+                if (rest) {
+                    const bool there = kq * sc::KL < rest;
+                    u32x4 v[2 * SUB];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) P[wave * 1024 + (8 * (v >> 2) + 4 * kh + (v & 3)) * 32 + r] = acc[v];
-                na += __shfl_xor(na, 32, kWave);                              // the two channel halves of a step
-                nc += __shfl_xor(nc, 32, kWave);
+                    for (int i = 0; i < 2 * SUB; ++i) {
+                        v[i] = u32x4{0u, 0u, 0u, 0u};
+                        if (there) v[i] = *reinterpret_cast<const u32x4*>(tok[i] + sc::KS * left);
+                    }
+                    use(v);
+                }
+                if (!ONE && t + 1 < tiles) begin_tile(t + 1);
+#pragma unroll
+                for (int q = 0; q < SUB * SUB; ++q) {
+                    const int j = 16 * (q % SUB) + r, piece = 4 * (q / SUB) + kq;
+                    const f32x4_lz& y = acc[q / SUB][q % SUB];
+                    P[wave * 256 + j * 8 + (piece ^ (j & 7))] = make_float4(y[0], y[1], y[2], y[3]);
+                }
+#pragma unroll
+                for (int i = 0; i < 2 * SUB; ++i) n2[i] = quarters_total(n2[i]);
                 const int js = ts * 32 + r, jd = td * 32 + r;
-                if (kh == 0) {
-                    if (td == 0 && js < n_src) pn[wave * len + 2 * js] = na;
-                    if (ts == 0 && jd < n_dst) pn[wave * len + 2 * jd + 1] = nc;
+                if (kq == 0) {
+#pragma unroll
+                    for (int i = 0; i < SUB; ++i) {
+                        if (td == 0 && js + 16 * i < n_src) pn[wave * len + 2 * (js + 16 * i)] = n2[i];
+                        if (ts == 0 && jd + 16 * i < n_dst) pn[wave * len + 2 * (jd + 16 * i) + 1] = n2[SUB + i];
+                    }
                 }
             }
             __syncthreads();
-            for (int e = tid; e < 1024; e += blockDim.x) {
-                const int row = ts * 32 + (e >> 5), col = td * 32 + (e & 31);
-                float sum = P[e];
+            // half of the wavefronts add up the products, the other half the squared norms
+            if (tid < 256) {
+                const int j = tid >> 3, col = td * 32 + j, row = ts * 32 + 4 * ((tid & 7) ^ (j & 7));
+                float4 sum = P[tid];
 #pragma unroll
-                for (int w = 1; w < kScreenWaves; ++w) sum += P[w * 1024 + e];
-                if (row < n_src && col < n_dst) S[row * sd + col] = sum;
+                for (int w = 1; w < kScreenWaves; ++w) {
+                    const float4 p = P[w * 256 + tid];
+                    sum.x += p.x; sum.y += p.y; sum.z += p.z; sum.w += p.w;
+                }
+                if (col < n_dst) *reinterpret_cast<float4*>(S + col * sd + row) = sum;
             }
             if (t + 1 < tiles) __syncthreads();
         }
     }
-    if (n_dst > 0)                                       // a line of one token has no products and no decisions
-        for (int p = tid; p < len; p += blockDim.x) {
-            float v = pn[p];
+    const int p = tid - 256;
+    if (p >= 0 && p < len && n_dst > 0) {                // a line of one token has no products and no decisions
+        float v = pn[p];
 #pragma unroll
-            for (int w = 1; w < kScreenWaves; ++w) v += pn[w * len + p];
-            if (!(v <= 1.2676506e30f)) *wild = 1;
-            v = sqrtf(v);
-            inv32[p] = 1.0f / (v < 1e-12f ? 1e-12f : v);
-        }
+        for (int w = 1; w < kScreenWaves; ++w) v += pn[w * len + p];
+        if (!(v <= 1.2676506e30f)) *wild = 1;
+        v = sqrtf(v);
+        inv32[p] = 1.0f / (v < 1e-12f ? 1e-12f : v);
+    }
     __syncthreads();
     if (*wild) tau = INFINITY;
-    // screened cosines and the best of each source: eight lanes per source.  A cosine that is no number counts as the
-    // lowest, so that exactly m sources leave the line whatever the tokens hold.
+    // A screened cosine; outside the radius: never a candidate.  One that is no number counts as the lowest, so that exactly m sources
+    // leave the line whatever the tokens hold.
+    auto cosine = [&](int j, int k, float inv_src) {
+        const int c = 2 * k + 1, dist = abs(c - 2 * j);
+        float s = (S[k * sd + j] * inv_src) * inv32[c];
+        s = s >= -2.f ? s : -2.f;
+        return g.radius <= 0 || dist <= 2 * g.radius - 1 ? s : -INFINITY;
+    };
+    // the best of each source: eight lanes per source
     if (wave < 8) {
         const int j = tid >> 3, part = tid & 7;
         float mx = -INFINITY;
         if (j < n_src) {
-            const int a = 2 * j;
-            const float ia = inv32[a];
-            for (int k = part; k < n_dst; k += 8) {
-                const int c = 2 * k + 1;
-                const int dist = c > a ? c - a : a - c;
-                float s = -INFINITY;                     // outside the radius: never a candidate
-                if (g.radius <= 0 || dist <= 2 * g.radius - 1) {
-                    s = (S[j * sd + k] * ia) * inv32[c];
-                    s = s >= -2.f ? s : -2.f;
-                }
-                S[j * sd + k] = s;
-                mx = fmaxf(mx, s);
+            const float ia = inv32[2 * j];
+            if (ONE) {                                   // all at once; destinations that are not there are others again
+#pragma unroll
+                for (int i = 0; i < 2 * TILE; ++i) mx = n_dst > 0 ? fmaxf(mx, cosine(j, min(part + 8 * i, n_dst - 1), ia)) : mx;
+            } else {
+                for (int k = part; k < n_dst; k += 8) mx = fmaxf(mx, cosine(j, k, ia));
             }
         }
         mx = oct_max(mx);
@@ -368,10 +455,19 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     const bool is_src = lane < n_src;
     const float vbest = is_src ? b32[lane] : -INFINITY;
     bool contender = is_src && g.m > 0 && vbest > -INFINITY;
-    if (g.m < n_src) {
-        int above = 0;
-        for (int i = 0; i < n_src; ++i) above += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vbest), i)) > vbest + tau ? 1 : 0;
-        contender = contender && above < g.m;
+    if (g.m < n_src) {                                   // fewer than m above it: the m-th highest is not
+        if (g.m <= 4) {
+            float rest = vbest, top = -INFINITY;
+            for (int i = 0; i < g.m; ++i) {
+                top = wave_max32(rest);
+                if (lane == (int)__builtin_ctzll(__ballot(rest == top))) rest = -INFINITY;
+            }
+            contender = contender && !(top > vbest + tau);
+        } else {
+            int above = 0;
+            for (int i = 0; i < n_src; ++i) above += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vbest), i)) > vbest + tau ? 1 : 0;
+            contender = contender && above < g.m;
+        }
     }
     const unsigned long long con = __ballot(contender), below = (1ull << lane) - 1ull;
     const int n_con = __popcll(con);
@@ -382,7 +478,7 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
             if (q % NW != wave) continue;
             const int j = (int)__builtin_ctzll(left), a = 2 * j;
             const float bj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(vbest), j));
-            unsigned long long cand = __ballot(lane < n_dst && S[j * sd + (lane < n_dst ? lane : 0)] >= fmaxf(bj - tau, -3.f));
+            unsigned long long cand = __ballot(lane < n_dst && cosine(j, lane < n_dst ? lane : 0, inv32[a]) >= fmaxf(bj - tau, -3.f));
             double bs = -INFINITY;
             int bk = (int)__builtin_ctzll(cand);
             if (ranked || (cand & (cand - 1))) {
@@ -421,13 +517,13 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
 
     // ------------------------------------------------------------------ 3. layout of the next grid
     auto slot = [&](int p) { return out_flat(lazy_slot(ln, p)); };
-    if (wave == 0 && is_src) {                           // sources
+    if (wave == NW - 2 && is_src) {                      // sources
         const int p = 2 * lane, f = in_flat(p);
         if (!leaves) {
             const int of = slot(p);
             idx_out[img_out + of] = rid[p];
             sizes_out[img_out + of] = sz[p];
-            if (kept_out) kept_out[img_out + of] = kept_in ? kept_in[img + f] : f;
+            if (kept_out) kept_out[img_out + of] = kept[p];
             if (pass_map) pass_map[img + f] = of;
         } else if (pass_map) {
             pass_map[img + f] = slot(2 * bk + 1);        // a merged source lands in its destination's slot
@@ -444,7 +540,7 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
             const int p = 2 * lane + 1, f = in_flat(p), of = slot(p);
             idx_out[img_out + of] = ((ln.takes >> lane) & 1ull) ? g.n0 + g.ov_base + line * g.per_line + __popcll(ln.takes & below) : rid[p];
             sizes_out[img_out + of] = S1;
-            if (kept_out) kept_out[img_out + of] = kept_in ? kept_in[img + f] : f;
+            if (kept_out) kept_out[img_out + of] = kept[p];
             if (pass_map) pass_map[img + f] = of;
         }
     }
@@ -584,13 +680,15 @@ static luvc_status run_lazy_pass(const T* x, T* ov, const T* xk, T* ovk, int Dk,
     LazyGeom g;
     g.n0 = n0; g.h = h; g.w = w; g.D = D; g.axis = axis; g.m = m; g.radius = radius; g.cap = cap; g.ov_base = ov_base;
     g.per_line = m < n_dst ? m : n_dst;
-    const int sd = lazy_row_stride(n_dst);
-    const size_t lds = sizeof(double) * 64 + sizeof(float) * ((size_t)kScreenWaves * (1024 + len) + (size_t)n_src * sd + len + 64) + sizeof(int) * ((size_t)2 * len + 65);
+    const int sd = lazy_row_stride(n_src);
+    const size_t lds = sizeof(double) * 64 + sizeof(float) * ((size_t)kScreenWaves * (1024 + len) + (size_t)n_dst * sd + len + 64) + sizeof(int) * ((size_t)3 * len + 65);
     // eight wavefronts; sixteen where so many destinations are merged that eight would take several rounds and a compute
     // unit has no second line to work on
     const int waves = g.per_line * (xk ? 2 : 1) > 8 && B * nlines <= 256 ? 16 : 8;
-    LUVC_LAUNCH("oim_wide_line", (oim_wide_line<T>), dim3((unsigned)(B * nlines)), dim3(64 * waves), lds, st, x, ov, xk, ovk, Dk, idx_in, sizes_in, kept_in, g,
-                idx_out, sizes_out, kept_out, pass_map);
+#define LUVC_WIDE(TILE) LUVC_LAUNCH("oim_wide_line", (oim_wide_line<T, TILE>), dim3((unsigned)(B * nlines)), dim3(64 * waves), lds, st, x, ov, xk, ovk, Dk, \
+                                   idx_in, sizes_in, kept_in, g, idx_out, sizes_out, kept_out, pass_map)
+    if (len <= 32) LUVC_WIDE(1); else if (len <= 64) LUVC_WIDE(2); else LUVC_WIDE(0);
+#undef LUVC_WIDE
     return check_launch("oim pass (wide matching, one launch)");
 }
 

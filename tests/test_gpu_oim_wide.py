@@ -233,6 +233,17 @@ def test_wide_decisions_around_the_screening_bound(oracle, dtype, D, apart):
         run_wide(oracle, wl.cast_io(x.astype(np.float32), dtype), dtype, passes, radius, tag=f"{apart} apart")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,W,D", [(2, 31, 8), (2, 32, 40), (3, 33, 24), (2, 64, 264), (3, 65, 136), (2, 63, 1288), (2, 32, 1560), (2, 96, 1296), (5, 17, 1024)])
+def test_wide_lines_around_a_tile_and_rows_around_a_step(oracle, dtype, H, W, D):
+    """Lines at the edges of the tiles of 16 and 32 sources, rows that end within a step of the contraction or have more steps than stay
+    in flight, and merge numbers on either side of the one up to which sources are picked one by one."""
+    rng = np.random.default_rng(H * 1000 + W + D)
+    x = rng.standard_normal((2, H, W, D)).astype(np.float32)
+    for passes, radius in (([(W_AX, 1)], 0), ([(W_AX, 4), (H_AX, 1)], 0), ([(W_AX, 5)], 3)):
+        run_wide(oracle, wl.cast_io(x, dtype), dtype, passes, radius, tag=f"m={passes[0][1]}")
+
+
 def test_wide_determinism():
     rng = np.random.default_rng(43)
     x = to_dev(wl.cast_io(wl.smooth_field(rng, 2, 40, 36, 136, 2.0) + 0.05 * rng.standard_normal((2, 40, 36, 136)).astype(np.float32), "bf16"), "bf16")
