@@ -39,42 +39,62 @@ __device__ __forceinline__ void tile_store(float* p, float v)
     __hip_atomic_store(reinterpret_cast<unsigned int*>(p), __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// four consecutive floats with device scope: one 16-byte access, 16-byte aligned
+// consecutive floats with device scope: one access
 typedef unsigned int tile_u32x4 __attribute__((__vector_size__(16)));
-constexpr int kTileVec = 4;
+typedef unsigned int tile_u32x2 __attribute__((__vector_size__(8)));
 constexpr int kAuxSc1 = 16;                      // cache-policy bit of the buffer instructions: device scope
+template <int VEC> struct tile_vec;
+template <> struct tile_vec<4> {
+    typedef tile_u32x4 type;
+    __device__ static __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kAuxSc1); }
+    __device__ static __forceinline__ void store(const type& v, __amdgpu_buffer_rsrc_t r, uint32_t off) { __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, kAuxSc1); }
+};
+template <> struct tile_vec<2> {
+    typedef tile_u32x2 type;
+    __device__ static __forceinline__ type load(__amdgpu_buffer_rsrc_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kAuxSc1); }
+    __device__ static __forceinline__ void store(const type& v, __amdgpu_buffer_rsrc_t r, uint32_t off) { __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, kAuxSc1); }
+};
 
 // out[n] = sum over `count` rows (row stride ld floats, ld % 4 == 0) of in[row][n], n < N, added in row order in fp64; FIN: square
-// root.  Up to kTileGroup rows per trip, all loads of a trip in flight together (a short trip re-reads its last row).
-template <int THREADS, bool FIN>
-__device__ __forceinline__ void tile_rows_sum(const float* in, int count, int N, int ld, float* out)
+// root.  Up to ROWS rows per trip, all loads of a trip in flight together (a short trip re-reads its last row), VEC columns a thread.
+template <int THREADS, bool FIN, int ROWS, int VEC>
+__device__ __forceinline__ void tile_rows_sum_vec(const float* in, int count, int N, int ld, float* out)
 {
+    using vec = tile_vec<VEC>;
     const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in), 0, count * ld * 4, 0x00020000);
     const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out, 0, ld * 4, 0x00020000);
-    for (int i = threadIdx.x * kTileVec; i < N; i += THREADS * kTileVec) {
-        double e[kTileVec] = {0.0, 0.0, 0.0, 0.0};
-        for (int r0 = 0; r0 < count; r0 += kTileGroup) {
+    for (int i = threadIdx.x * VEC; i < N; i += THREADS * VEC) {
+        double e[VEC] = {};
+        for (int r0 = 0; r0 < count; r0 += ROWS) {
             const int left = count - r0;
-            tile_u32x4 p[kTileGroup];
+            typename vec::type p[ROWS];
 #pragma unroll
-            for (int r = 0; r < kTileGroup; ++r)
-                p[r] = __builtin_amdgcn_raw_buffer_load_b128(rin, (uint32_t)(((r0 + (r < left ? r : left - 1)) * ld + i) * 4), 0, kAuxSc1);
+            for (int r = 0; r < ROWS; ++r) p[r] = vec::load(rin, (uint32_t)(((r0 + (r < left ? r : left - 1)) * ld + i) * 4));
 #pragma unroll
-            for (int r = 0; r < kTileGroup; ++r)
+            for (int r = 0; r < ROWS; ++r)
 #pragma unroll
-                for (int c = 0; c < kTileVec; ++c) e[c] += r < left ? (double)__uint_as_float(p[r][c]) : 0.0;
+                for (int c = 0; c < VEC; ++c) e[c] += r < left ? (double)__uint_as_float(p[r][c]) : 0.0;
         }
-        tile_u32x4 o;
+        typename vec::type o;
 #pragma unroll
-        for (int c = 0; c < kTileVec; ++c) o[c] = __float_as_uint(FIN ? (float)sqrt(e[c]) : (float)e[c]);
+        for (int c = 0; c < VEC; ++c) o[c] = __float_as_uint(FIN ? (float)sqrt(e[c]) : (float)e[c]);
         if (FIN) {
 #pragma unroll
-            for (int c = 0; c < kTileVec; ++c)
+            for (int c = 0; c < VEC; ++c)
                 if (i + c < N) out[i + c] = __uint_as_float(o[c]);             // scores: ordinary stores, no alignment assumed
         } else {
-            __builtin_amdgcn_raw_buffer_store_b128(o, rout, (uint32_t)(i * 4), 0, kAuxSc1);
+            vec::store(o, rout, (uint32_t)(i * 4));
         }
     }
+}
+// More rows than a group has, where there is no group level, in one trip and over all threads if two columns to a thread are
+// enough: 28 rows of 1024 tokens, a launch of 8 x 1024 x 3584 40.2 us for 40.9 (4 columns to 256 of 512 threads, two trips).  With
+// fewer rows either costs .3 to .6 us more than it gives (7 rows of 576 tokens, 32 x 576 x 896).
+template <int THREADS, bool FIN, int MOST>
+__device__ __forceinline__ void tile_rows_sum(const float* in, int count, int N, int ld, float* out)
+{
+    if (MOST > kTileGroup && count > kTileGroup && N <= 2 * THREADS) tile_rows_sum_vec<THREADS, FIN, MOST, 2>(in, count, N, ld, out);
+    else tile_rows_sum_vec<THREADS, FIN, kTileGroup, 4>(in, count, N, ld, out);
 }
 
 // ------------------------------------------------------------------ arrival words
@@ -155,7 +175,7 @@ __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [
         if (tid == 0) *flag = tiles_arrive(cnt + 1 + grp, t_cnt);
         __syncthreads();
         if (!*flag) return;
-        tile_rows_sum<THREADS, false>(partial + ((int64_t)b * n_tiles + t_first) * ld, t_cnt, N, ld,
+        tile_rows_sum<THREADS, false, kTileGroup>(partial + ((int64_t)b * n_tiles + t_first) * ld, t_cnt, N, ld,
                                          gpartial + ((int64_t)b * n_groups + grp) * ld);
     }
     const int last_cnt = two_level ? n_groups : n_tiles;
@@ -165,9 +185,9 @@ __device__ __forceinline__ void tiles_to_scores(float* __restrict__ partial /* [
     __syncthreads();
     if (!*flag) return;
     if (two_level)
-        tile_rows_sum<THREADS, true>(gpartial + (int64_t)b * n_groups * ld, last_cnt, N, ld, scores + (int64_t)b * N);
+        tile_rows_sum<THREADS, true, kTileGroup>(gpartial + (int64_t)b * n_groups * ld, last_cnt, N, ld, scores + (int64_t)b * N);
     else
-        tile_rows_sum<THREADS, true>(partial + (int64_t)b * n_tiles * ld, last_cnt, N, ld, scores + (int64_t)b * N);
+        tile_rows_sum<THREADS, true, DIRECT>(partial + (int64_t)b * n_tiles * ld, last_cnt, N, ld, scores + (int64_t)b * N);
 }
 
 // Host side: 48-bit non-zero tag of the next launch (process-wide sequence, random start)
