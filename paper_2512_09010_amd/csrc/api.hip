@@ -384,8 +384,8 @@ static luvc_status oim_merge_impl(const void* x, const int32_t* sizes_in, int B,
             rc = oim_wide_pass(cur_x, cur_s, B, pl.h[i], pl.w[i], D, dtype, passes[i].axis, passes[i].m, radius, vec,
                                ox, os, pm, cur_k, ok, sc, (double*)(ws + L.gram), (int32_t*)(ws + L.srcdest), st);
         else if (steps[s].count == 2 || oim_halve_supported(pl.h[i], pl.w[i], D, dtype, passes[i].axis, passes[i].m, vec)) {
-            const OimStepItem item = {pl.h[i], pl.w[i], passes[i].axis, B, StepAt{0, 0, 0, pl.h[i] * pl.w[i], 0, 0, 0}};
-            const StepIn in = {cur_x, cur_s, cur_k};
+            const OimStepItem item = {pl.h[i], pl.w[i], passes[i].axis, B, StepAt{0, 0, 0, pl.h[i] * pl.w[i], 0, 0, 0, 0}};
+            const StepIns in = {{{cur_x, cur_s, cur_k}}};
             const StepOut out = {{ox, nullptr}, {os, nullptr}, {ok, nullptr}, {pm, nullptr}};
             rc = steps[s].count == 2 ? oim_pair_step(&item, 1, in, out, D, dtype, st) : oim_halve_step(&item, 1, in, out, D, dtype, st);
         } else

@@ -80,31 +80,38 @@ luvc_status value_enhance_run(const void* v, const int32_t* sizes, int64_t rows,
 
 // ---- Halving steps of one or several runs of equal images in one launch.  An item is a run: `count` images of H x W; axis is
 // that of the (first) pass.  Where its images lie: token offsets into the step's input and output, an offset and a stride per
-// image for its map; dst / map_dst choose one of two sets of outputs (a step that ends some images of a batch and not others).
+// image for its map; src, dst and map_dst choose among sets of inputs and outputs (runs of a batch meet in a launch at different
+// steps of theirs: some read the batch, some what their last step left; some end, some do not).
 constexpr int kOimMaxItems = 24;
 struct StepAt {
     int64_t in_off, out_off, map_off;
     int map_stride;
     unsigned wg0;                    // first workgroup (filled in by the launcher)
-    int dst, map_dst;
+    int src, dst, map_dst;
 };
 struct OimStepItem { int H, W, axis, count; StepAt at; };
 struct StepIn { const void* x; const int32_t *sizes, *kept; };               // sizes NULL: ones; kept NULL: identity
-struct StepOut { void* x[2]; int32_t *sizes[2], *kept[2], *map[2]; };        // kept, map: NULL = not wanted
-// the outputs of a launch of one item, as number 0
-inline StepOut step_out_of(const StepOut& o, const StepAt& at)
+struct StepIns { StepIn set[3]; };
+template <int MOST> struct StepMore { StepIn from[2]; };        // sets 1 and 2, in the argument of a launch of several items
+template <> struct StepMore<1> {};
+template <int SETS> struct StepOuts { void* x[SETS]; int32_t *sizes[SETS], *kept[SETS], *map[SETS > 1 ? 2 : 1]; };        // kept, map: NULL = not wanted
+using StepOut = StepOuts<3>;
+template <int MOST> using StepOutOf = StepOuts<(MOST > 1 ? 3 : 1)>;
+// the outputs as a launch of up to MOST items takes them: of one item, as number 0
+template <int MOST> StepOutOf<MOST> step_out_of(const StepOut& o, const StepAt& at)
 {
-    return StepOut{{o.x[at.dst], nullptr}, {o.sizes[at.dst], nullptr}, {o.kept[at.dst], nullptr}, {o.map[at.map_dst], nullptr}};
+    if constexpr (MOST > 1) return o;
+    else return StepOutOf<1>{{o.x[at.dst]}, {o.sizes[at.dst]}, {o.kept[at.dst]}, {o.map[at.map_dst]}};
 }
 
 // One pass with m = ceil(len/2) (oim_fast.hip); `vec` = rows are 16-byte aligned.
 bool oim_halve_supported(int H, int W, int D, luvc_dtype dt, int axis, int m, bool vec);
-luvc_status oim_halve_step(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st);
+luvc_status oim_halve_step(const OimStepItem* items, int n, const StepIns& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st);
 
 // Two consecutive halving passes on different axes (oim_pair.hip); the map sends an input flat index of the first pass
 // to an output slot of the second.
 bool oim_pair_supported(int H, int W, int D, luvc_dtype dt, int axis0, int m0, int axis1, int m1, bool vec);
-luvc_status oim_pair_step(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st);
+luvc_status oim_pair_step(const OimStepItem* items, int n, const StepIns& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st);
 
 // What a batch of runs leaves to the end (ragged.hip): images no pass touches are copied, the maps of images with several
 // steps composed (step s of a batch writes its maps at maps + s * map_level, an image its n0 entries at map_off + image * n0).

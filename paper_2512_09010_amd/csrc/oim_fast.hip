@@ -25,11 +25,11 @@
 namespace luvc {
 
 struct HalveItem { int H, W, axis, tiles, slots; StepAt at; };      // a line is cut into `tiles` runs of `slots` output slots
-template <int MOST> struct HalveTable { int n; HalveItem it[MOST]; };        // one item: a kernel of its own, as in oim_pair.hip (8 x 64 x 64 x 1280 bf16 36.7 -> 35.1 us)
+template <int MOST> struct HalveTable : StepMore<MOST> { int n; HalveItem it[MOST]; };        // one item: a kernel of its own, as in oim_pair.hip (8 x 64 x 64 x 1280 bf16 36.7 -> 35.1 us)
 
 template <typename T, int NCH, int MOST>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NCH <= 3 ? 4 : 2)))
-oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, int D, const StepOut out, const HalveTable<MOST> tab)
+oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, int D, const StepOutOf<MOST> out, const HalveTable<MOST> tab)
 {
     using tr = io_traits<T>;
     constexpr int V = tr::kVec;
@@ -48,6 +48,14 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const i
         for (int i = 1; i < tab.n; ++i)
             if (item >= tab.it[i].at.wg0) ent = i;
         it = tab.it[ent];
+    }
+    if constexpr (MOST > 1) {
+        if (it.at.src) {
+            const StepIn& from = tab.from[it.at.src - 1];
+            x = (const T*)from.x;
+            sizes_in = from.sizes;
+            kept_prev = from.kept;
+        }
     }
     const StepAt& at = it.at;
     const int H = it.H, W = it.W, axis = it.axis, tiles_per_line = it.tiles, slots_per_tile = it.slots;
@@ -239,7 +247,7 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const i
 }
 
 template <typename T, int NCH, int MOST>
-static void launch_halve(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
+static void launch_halve(const OimStepItem* items, int n, const StepIns& in, const StepOut& out, int D, hipStream_t st)
 {
     constexpr int cap = 4;                                 // wavefronts (= output slots) per workgroup
     HalveTable<MOST> tab;
@@ -258,11 +266,13 @@ static void launch_halve(const OimStepItem* items, int n, const StepIn& in, cons
         tab.it[i].at.wg0 = (unsigned)wgs;
         wgs += (int64_t)items[i].count * (axis ? H : W) * tab.it[i].tiles;
     }
-    LUVC_LAUNCH("oim_halve", (oim_halve<T, NCH, MOST>), dim3((unsigned)wgs), dim3(64 * waves), 0, st, (const T*)in.x, in.sizes, in.kept, D, MOST > 1 ? out : step_out_of(out, items[0].at), tab);
+    if constexpr (MOST > 1) { tab.from[0] = in.set[1]; tab.from[1] = in.set[2]; }
+    const StepIn& first = in.set[MOST > 1 ? 0 : items[0].at.src];
+    LUVC_LAUNCH("oim_halve", (oim_halve<T, NCH, MOST>), dim3((unsigned)wgs), dim3(64 * waves), 0, st, (const T*)first.x, first.sizes, first.kept, D, step_out_of<MOST>(out, items[0].at), tab);
 }
 
 template <typename T>
-static bool dispatch_halve(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
+static bool dispatch_halve(const OimStepItem* items, int n, const StepIns& in, const StepOut& out, int D, hipStream_t st)
 {
     const int per_wave = 64 * io_traits<T>::kVec;
     const int nch = (D + per_wave - 1) / per_wave;
@@ -288,7 +298,7 @@ bool oim_halve_supported(int H, int W, int D, luvc_dtype dt, int axis, int m, bo
     return vec && len >= 2 && m == (len + 1) / 2 && (D + per_wave - 1) / per_wave <= 8;
 }
 
-luvc_status oim_halve_step(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st)
+luvc_status oim_halve_step(const OimStepItem* items, int n, const StepIns& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st)
 {
     const bool ok = dt == LUVC_F32 ? dispatch_halve<float>(items, n, in, out, D, st) : dispatch_halve<bf16_t>(items, n, in, out, D, st);
     if (!ok) { set_error("oim halving pass: unsupported D"); return LUVC_ERR_UNSUPPORTED; }

@@ -51,7 +51,7 @@ namespace luvc {
 // 2 KB and costs a launch 0.3 .. 0.7 us (8 x 64 x 64 x 1280 bf16 34.7 -> 34.0, 2 x 112 x 112 x 1280 and its two smaller
 // grids 59.8 -> 58.3).
 template <int MOST>
-struct PairTable {
+struct PairTable : StepMore<MOST> {
     int n;
     struct { PairGeom g; StepAt at; } it[MOST];
 };
@@ -62,7 +62,7 @@ struct PairTable {
 // hint on wider tokens (96 instead of 103 registers) measured slower on every workload and is not given.
 template <typename T, int NQ, int TW, int NW, int R /* first-pass lines of a wavefront */, int MOST>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((4 * NQ + TW <= 8 && NW == 16) ? 6 : 1)))
-oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, const StepOut out, const PairTable<MOST> tab)
+oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const int32_t* __restrict__ kept_prev, const StepOutOf<MOST> out, const PairTable<MOST> tab)
 {
     using TokT = Tok<NQ, TW>;
     constexpr int N = TokT::N;
@@ -83,12 +83,18 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);
     PairGeom g = tab.it[0].g;
     StepAt at = tab.it[0].at;
-    if (MOST > 1) {
+    if constexpr (MOST > 1) {
         int ent = 0;
         for (int i = 1; i < tab.n; ++i)
             if (item >= tab.it[i].at.wg0) ent = i;
         g = tab.it[ent].g;
         at = tab.it[ent].at;
+        if (at.src) {
+            const StepIn& from = tab.from[at.src - 1];
+            x = (const T*)from.x;
+            sizes_in = from.sizes;
+            kept_prev = from.kept;
+        }
     }
     item -= at.wg0;
     const int j = item % g.nd1;
@@ -334,7 +340,7 @@ namespace {
 constexpr int pair_waves(int words) { return words <= 10 ? 16 : 8; }      // 16 wavefronts leave 128 registers per lane, 8 leave 256
 
 template <typename T, int NQ, int TW, int R, int MOST>
-luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, int64_t lines, hipStream_t st)
+luvc_status launch_pair(const OimStepItem* items, int n, const StepIns& in, const StepOut& out, int D, int64_t lines, hipStream_t st)
 {
     constexpr int N = 4 * NQ + TW, NW = pair_waves(N);
     PairTable<MOST> tab;
@@ -364,8 +370,10 @@ luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const
         wgs += (int64_t)items[i].count * g.segs * g.nd1;
     }
     const size_t lds = (size_t)waves * N * 64 * 4;             // at most 16 * 10 * 256 = 40 KiB
+    if constexpr (MOST > 1) { tab.from[0] = in.set[1]; tab.from[1] = in.set[2]; }
+    const StepIn& first = in.set[MOST > 1 ? 0 : items[0].at.src];
     LUVC_LAUNCH("oim_halve_pair", (oim_halve_pair<T, NQ, TW, NW, R, MOST>), dim3((unsigned)wgs), dim3(64 * waves), lds, st,
-                (const T*)in.x, in.sizes, in.kept, MOST > 1 ? out : step_out_of(out, items[0].at), tab);
+                (const T*)first.x, first.sizes, first.kept, step_out_of<MOST>(out, items[0].at), tab);
     return check_launch("oim halving pair");
 }
 
@@ -376,7 +384,7 @@ luvc_status launch_pair(const OimStepItem* items, int n, const StepIn& in, const
 // 18.4, 21.8 (5300), 2x112x112x1280 28, 38, 8x64x64x1280 29, 39.
 constexpr int64_t kTwoRowWaves = 3600;
 template <typename T, int NQ, int TW>
-luvc_status launch_pair_rows(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
+luvc_status launch_pair_rows(const OimStepItem* items, int n, const StepIns& in, const StepOut& out, int D, hipStream_t st)
 {
     int64_t lines = 0, waves2 = 0;
     for (int i = 0; i < n; ++i) lines += (int64_t)items[i].count * ((items[i].axis ? items[i].W : items[i].H) / 2);
@@ -391,7 +399,7 @@ luvc_status launch_pair_rows(const OimStepItem* items, int n, const StepIn& in, 
 }
 
 template <typename T>
-luvc_status dispatch_pair(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, hipStream_t st)
+luvc_status dispatch_pair(const OimStepItem* items, int n, const StepIns& in, const StepOut& out, int D, hipStream_t st)
 {
     // 16-byte pieces per lane, then a 4- or 8-byte tail piece if that covers what is left
     const int bytes = D * (int)sizeof(T);
@@ -421,7 +429,7 @@ bool oim_pair_supported(int H, int W, int D, luvc_dtype dt, int axis0, int m0, i
     return (int64_t)D * (dt == LUVC_F32 ? 4 : 2) <= 4096;
 }
 
-luvc_status oim_pair_step(const OimStepItem* items, int n, const StepIn& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st)
+luvc_status oim_pair_step(const OimStepItem* items, int n, const StepIns& in, const StepOut& out, int D, luvc_dtype dt, hipStream_t st)
 {
     return dt == LUVC_F32 ? dispatch_pair<float>(items, n, in, out, D, st) : dispatch_pair<bf16_t>(items, n, in, out, D, st);
 }

@@ -3,8 +3,8 @@
 // only: consecutive items of equal shape and schedule form a run; every item is validated before the first launch.
 //
 // Runs share launches wherever a kernel takes several of them.  OIM: images whose schedules consist of halvings advance
-// together, one launch per step and kind of step (a pair of passes, a single pass), then one for the images that stay as
-// they are and the maps of those with several steps.  SPU: the short samples are scored in one launch, all samples pruned
+// together, in as few launches of either kind of step (a pair of passes, a single pass) as their orders allow, then one for the images
+// that stay as they are and the maps of those with several steps.  SPU: the short samples are scored in one launch, all samples pruned
 // in one.  What does not fit these (other merge numbers, long samples, unaligned rows) is a batched call of the entry points
 // in api.hip per run.  A launch costs 4 to 12 us whatever it does: eight images of 24x24 to 56x56 tokens took
 // 30 launches and 398 us run by run, 95 us like this.
@@ -127,32 +127,62 @@ void batch_plan(const std::vector<OimRun>& runs, int D, luvc_dtype dt, bool vec,
     p->bytes = off;
 }
 
+// The kinds (2: a pair of passes, 1: a single one) of the launches that take all runs through their steps.  A run joins the first
+// launch of the kind it needs next; kind `first` comes as long as any run needs it, so that the others gather behind it (a schedule of
+// one pass goes along with the third pass of another), or the other way round where that takes fewer launches.
+std::vector<int> step_kinds(const std::vector<BatchRun>& runs)
+{
+    std::vector<int> best;
+    for (int first = 2; first >= 1; --first) {
+        std::vector<int> kinds, at(runs.size(), 0);
+        for (;;) {
+            bool wanted[3] = {false, false, false};
+            for (size_t i = 0; i < runs.size(); ++i)
+                if (at[i] < runs[i].n) wanted[runs[i].step[at[i]].passes] = true;
+            if (!wanted[1] && !wanted[2]) break;
+            kinds.push_back(wanted[first] ? first : 3 - first);
+            for (size_t i = 0; i < runs.size(); ++i)
+                if (at[i] < runs[i].n && runs[i].step[at[i]].passes == kinds.back()) ++at[i];
+        }
+        if (first == 2 || kinds.size() < best.size()) best = kinds;
+    }
+    return best;
+}
+
 luvc_status batch_run_all(const BatchPlan& p, const void* x, const int32_t* sizes_in, int D, luvc_dtype dt, void* x_out, int32_t* sizes_out,
                           int32_t* merged_map, int32_t* kept_map, char* ws, hipStream_t st)
 {
     int32_t* maps = (int32_t*)(ws + p.maps);
+    StepIns in = {{{x, sizes_in, nullptr}}};
+    StepOut out = {{x_out}, {sizes_out}, {kept_map}, {merged_map, merged_map ? maps : nullptr}};
+    for (int j = 0; j < 2; ++j) {
+        int32_t *sz = (int32_t*)(ws + p.sizes[j]), *kept = (int32_t*)(ws + p.kept[j]);
+        in.set[1 + j] = StepIn{ws + p.x[j], sz, kept};
+        out.x[1 + j] = ws + p.x[j];
+        out.sizes[1 + j] = sz;
+        out.kept[1 + j] = kept_map ? kept : nullptr;
+    }
     OimStepItem items[kOimMaxItems];
-    for (int s = 0; s < p.levels; ++s) {
-        const int i0 = (s + 1) & 1, o = s & 1;
-        const StepIn in = s == 0 ? StepIn{x, sizes_in, nullptr} : StepIn{ws + p.x[i0], (int32_t*)(ws + p.sizes[i0]), (int32_t*)(ws + p.kept[i0])};
-        const StepOut out = {{x_out, ws + p.x[o]}, {sizes_out, (int32_t*)(ws + p.sizes[o])}, {kept_map, kept_map ? (int32_t*)(ws + p.kept[o]) : nullptr},
-                             {merged_map, merged_map ? maps + s * p.map_level : nullptr}};
-        for (int passes = 2; passes >= 1; --passes) {
-            int n = 0;
-            for (size_t i = 0; i <= p.runs.size(); ++i) {
-                if (n == kOimMaxItems || (i == p.runs.size() && n)) {
-                    const luvc_status rc = passes == 2 ? oim_pair_step(items, n, in, out, D, dt, st) : oim_halve_step(items, n, in, out, D, dt, st);
-                    if (rc != LUVC_OK) return rc;
-                    n = 0;
-                }
-                if (i == p.runs.size()) break;
-                const BatchRun& b = p.runs[i];
-                if (s >= b.n || b.step[s].passes != passes) continue;
-                const bool last = s + 1 == b.n, single = b.n == 1;
-                items[n++] = OimStepItem{b.step[s].h, b.step[s].w, b.step[s].axis, b.run->count,
-                                         StepAt{s == 0 ? b.run->tok_in : b.between_off, last ? b.run->tok_out : b.between_off,
-                                                single ? b.run->tok_in : b.map_off, b.run->H * b.run->W, 0, last ? 0 : 1, single ? 0 : 1}};
+    std::vector<int> done(p.runs.size(), 0);
+    for (int passes : step_kinds(p.runs)) {
+        int n = 0;
+        for (size_t i = 0; i <= p.runs.size(); ++i) {
+            if (n == kOimMaxItems || (i == p.runs.size() && n)) {
+                const luvc_status rc = passes == 2 ? oim_pair_step(items, n, in, out, D, dt, st) : oim_halve_step(items, n, in, out, D, dt, st);
+                if (rc != LUVC_OK) return rc;
+                n = 0;
             }
+            if (i == p.runs.size()) break;
+            const BatchRun& b = p.runs[i];
+            const int s = done[i];
+            if (s >= b.n || b.step[s].passes != passes) continue;
+            ++done[i];
+            // step s leaves its tokens in number s & 1 of the two grids between steps
+            const bool last = s + 1 == b.n, single = b.n == 1;
+            items[n++] = OimStepItem{b.step[s].h, b.step[s].w, b.step[s].axis, b.run->count,
+                                     StepAt{s == 0 ? b.run->tok_in : b.between_off, last ? b.run->tok_out : b.between_off,
+                                            single ? b.run->tok_in : s * p.map_level + b.map_off, b.run->H * b.run->W, 0,
+                                            s == 0 ? 0 : 1 + ((s + 1) & 1), last ? 0 : 1 + (s & 1), single ? 0 : 1}};
         }
     }
     OimTailItem tail[kOimMaxItems];

@@ -12,11 +12,12 @@ from gpu_util import OIM_MARGIN, RTOL, SPU_MARGIN, assert_close, round_mode, to_
 pytestmark = pytest.mark.gpu
 
 
-def oim_ragged_case(oracle, shapes, D, dtype, max_tokens, seed, with_sizes):
+def oim_ragged_case(oracle, shapes, D, dtype, max_tokens, seed, with_sizes, schedules=None):
     rng = np.random.default_rng(seed)
-    schedules = [lv.luvc_oim_plan_anyres(h, w, max_tokens) for h, w in shapes]
-    for (h, w), sch in zip(shapes, schedules):
-        assert sch == oracle.plan_anyres(h, w, max_tokens), (h, w)
+    if schedules is None:
+        schedules = [lv.luvc_oim_plan_anyres(h, w, max_tokens) for h, w in shapes]
+        for (h, w), sch in zip(shapes, schedules):
+            assert sch == oracle.plan_anyres(h, w, max_tokens), (h, w)
     imgs = [wl.cast_io(wl.smooth_field(rng, 1, h, w, D, 2.0) + 0.1 * rng.standard_normal((1, h, w, D)).astype(np.float32), dtype)
             for h, w in shapes]
     sizes = [rng.integers(1, 5, (1, h, w)) for h, w in shapes] if with_sizes else None
@@ -158,6 +159,26 @@ def test_oim_more_runs_than_a_launch_takes(oracle, dtype):
     shapes = [(1 + i % 9, 3 + (5 * i) % 23) for i in range(40)] + [(31, 18), (18, 31), (26, 26)]
     oim_ragged_case(oracle, shapes, 40, dtype, 36, 11, with_sizes=True)
     oim_ragged_case(oracle, shapes[30:], 33, dtype, 36, 12, with_sizes=False)
+
+
+def halvings(h, w, axes):
+    out = []
+    for a in axes:
+        out.append((a, ((w if a else h) + 1) // 2))
+        h, w = (h, w - out[-1][1]) if a else (h - out[-1][1], w)
+    return out
+
+
+# pairs of passes and single ones in either order, so that runs meet in a launch at different steps of theirs; a single pass
+# comes first for all of the first batch, a pair for most of the others; one image keeps its tokens
+@pytest.mark.parametrize("axes", [["00", "001", "110", "0", "1", "0010"],
+                                  ["10", "1", "101", "0101", "0", "10011", "01", "", "01010"],
+                                  ["111", "10", "0110", "00", "1101"]])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_oim_runs_that_meet_at_different_steps(oracle, dtype, axes):
+    shapes = [(17 + 3 * i, 16 + 5 * i) for i in range(len(axes))]
+    schedules = [halvings(h, w, [int(a) for a in ax]) or [(0, 0)] for (h, w), ax in zip(shapes, axes)]
+    oim_ragged_case(oracle, shapes, 40, dtype, 0, 13, with_sizes=True, schedules=schedules)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
