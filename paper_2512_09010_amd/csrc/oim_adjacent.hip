@@ -13,7 +13,9 @@
 // Bound: latency.  A pass reads its tokens once, but a line is a chain of memory trips - ids, tokens, merged rows - with
 // the decisions between them; as many wavefronts as a line has groups of four tokens share it, so that each trip is made once.
 // 12 x 32 x 32 x 1024 bf16, three operations of (W,2),(H,2): 157 us as three launches per pass (norms and products,
-// decisions, a merge that rewrote the whole grid), 75 us as one, 68 with two pieces of a row per lane where a row has no more.
+// decisions, a merge that rewrote the whole grid), 75 us as one, 68 with two pieces of a row per lane where a row has no more, 62.4 with
+// the ids of a wavefront's tokens asked for together (one behind the other, each a branch and a wait, they were most of the 1.2 us
+// before its first token) and a merged row shared by two wavefronts.
 // Narrow rows were slower than the three launches while every row took three pieces: 32 x 64 x 64 x 384 bf16, (W,2): 92 us by
 // pass, 130, 78 then, of which the copy of the output rows went from 63 to 31.
 #include "common.hpp"
@@ -30,8 +32,8 @@ constexpr int kAdjTok = 4;                       // consecutive tokens of a wave
 // HOLD: a line has at most four tokens per wavefront, a row at most P pieces, and the decisions are taken on the tokens:
 // they stay in registers until the end of the pass, and a wavefront merges the two destinations among its own.  Taken where
 // the lines come in several rounds: 8 x 64 x 64 x 1280 bf16, merge number 2 three times, 167.2 us a call without, 163.0 with
-// (169.1 before m sources were picked by one wavefront); 32 x 64 x 64 x 384, once, 122.4, 118.7 (124.1).  A launch that
-// is one round long is no quicker for the trip it saves: 12 x 32 x 32 x 1024 68.1, 69.6; 1 x 100 x 24 x 1408 68.7, 70.7.
+// (158.1 now, with the ids asked for together); 32 x 64 x 64 x 384, once, 122.4, 118.7 (115.0 now).  A launch that
+// is one round long is no quicker for the trip it saves: 12 x 32 x 32 x 1024 68.1, 69.6 (71.1 for 66.9 now); 1 x 100 x 24 x 1408 68.7, 70.7.
 template <typename T, int P, int PM, bool HOLD>
 __global__ void __launch_bounds__(1024)
 oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric [.., Dk] the decisions are taken on, or null: x */,
@@ -42,7 +44,7 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
 {
     using io = lz_io<T>;
     constexpr int V = io::V;
-    __shared__ double nrm2[kLazyMaxLen + 4], dnx[kLazyMaxLen + 4];     // squared norm; product with the next token of the line
+    __shared__ double nrm2[kLazyMaxLen + 4], dnx[kLazyMaxLen + 4];     // squared norm, then norm; product with the next token of the line
     __shared__ double score[64];
     __shared__ int rid[kLazyMaxLen], sz[kLazyMaxLen];
     __shared__ int side[64];                     // best destination of a source: 0 the one before it, 1 the one after it, -1 none
@@ -61,20 +63,26 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
     const T* dov = xk ? ovk : ov;
     const int dD = xk ? Dk : g.D;
 
-    for (int p = tid; p < len; p += blockDim.x) {
-        const int f = in_flat(p);
-        rid[p] = idx_in ? idx_in[img + f] : f;
-        sz[p] = sizes_in ? sizes_in[img + f] : 1;
+    // What the line shares comes beside the tokens, one to a thread (there are 16 per token, or 1024), and is written to LDS behind the
+    // sums.  (The ids of a wavefront's tokens one to a lane as well, instead of by scalar loads: 12 x 32 x 32 x 1024 67.6 us for 65.5.)
+    int line_id = 0, line_size = 1;
+    if (tid < len) {
+        line_id = in_flat(tid);
+        if (sizes_in) line_size = sizes_in[img + line_id];
+        if (idx_in) line_id = idx_in[img + line_id];
     }
     // ---- squared norms and neighbour products
     lz_u32x4 tok[kAdjTok + 1][P];                // tokens p0 .. p0 + 4 of the line, P pieces of each
     for (int p0 = wave * kAdjTok; p0 < len; p0 += NW * kAdjTok) {
+        int id[kAdjTok + 1];                     // asked for together
+#pragma unroll
+        for (int i = 0; i <= kAdjTok; ++i) id[i] = in_flat(p0 + i < len ? p0 + i : len - 1);
+        if (idx_in)
+#pragma unroll
+            for (int i = 0; i <= kAdjTok; ++i) id[i] = idx_in[img + id[i]];
         __amdgpu_buffer_rsrc_t r[kAdjTok + 1];
 #pragma unroll
-        for (int i = 0; i <= kAdjTok; ++i) {
-            const int p = p0 + i < len ? p0 + i : len - 1, f = in_flat(p);
-            r[i] = lz_row(row_of<T>(dx, dov, b, idx_in ? idx_in[img + f] : f, g, dD), dD, p0 + i < len);
-        }
+        for (int i = 0; i <= kAdjTok; ++i) r[i] = lz_row(row_of<T>(dx, dov, b, id[i], g, dD), dD, p0 + i < len);
         double s[2 * kAdjTok];
 #pragma unroll
         for (int i = 0; i < 2 * kAdjTok; ++i) s[i] = 0.0;
@@ -97,11 +105,13 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
                     }
                 }
         }
-        wave_total64x8(s, lane);
-        if (lane == 0) {
-#pragma unroll
-            for (int i = 0; i < kAdjTok; ++i) { nrm2[p0 + i] = s[i]; dnx[p0 + i] = s[kAdjTok + i]; }
-        }
+        static_assert(kAdjTok == 4, "eight sums, one to a lane");
+        const double sum = wave_totals64(s, lane);
+        if (lane < 2 * kAdjTok) (lane < kAdjTok ? nrm2 : dnx)[p0 + (lane & (kAdjTok - 1))] = sum;
+    }
+    if (tid < len) {
+        rid[tid] = line_id;
+        sz[tid] = line_size;
     }
     __syncthreads();
     // ---- cosine of every source with its two neighbours (equal: the lower position)
@@ -112,9 +122,14 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
         const bool is_src = lane < n_src;
         const int a = is_src ? 2 * lane : 0;
         const bool hl = a >= 1, hr = a + 1 < len;
-        auto norm = [&](int p) { const double n = sqrt(nrm2[p]); return n < 1e-12 ? 1e-12 : n; };
-        const double na = norm(a);
-        const double sl = hl ? dnx[a - 1] / (na * norm(a - 1)) : 0.0, sr = hr ? dnx[a] / (na * norm(a + 1)) : 0.0;
+        for (int p = lane; p < len; p += 64) {               // a root per token: each is in the cosines of up to three sources
+            const double n = sqrt(nrm2[p]);
+            nrm2[p] = n < 1e-12 ? 1e-12 : n;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const double na = nrm2[a];
+        const double sl = hl ? dnx[a - 1] / (na * nrm2[a - 1]) : 0.0, sr = hr ? dnx[a] / (na * nrm2[a + 1]) : 0.0;
         const bool left = hl && (!hr || !(sr > sl));
         double best = left ? sl : sr;
         best = best == best ? best : -INFINITY;              // NaN: last, so that exactly m sources leave the line whatever the tokens hold
@@ -204,9 +219,14 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
             }
         }
     } else {
-        // ---- the same, a wavefront per destination and tensor
-        const int n_abs = __popcll(ln.takes);
-        for (int kk = wave; kk < (xk ? 2 : 1) * n_abs; kk += NW) {
+        // ---- the same, a wavefront per destination and tensor; one or two destinations: up to four per row, of a piece and more each.
+        // (us of a call without and with it, merge number 2: 12 x 32 x 32 x 1024 bf16 three times 71.1, 67.6; 2 x 64 x 64 x 1280 twice 51.0,
+        // 49.4.  Of three and more rows the shares stand in each other's way: m = 3 52.1, 53.4; 4 53.1, 53.5; 6 57.1, 57.8.)
+        const int n_abs = __popcll(ln.takes), n_rows = (xk ? 2 : 1) * n_abs;
+        int split = 0;                           // 2^split wavefronts
+        while ((64 * V << split) < g.D && (n_abs << (split + 1)) <= 4 && (n_rows << (split + 1)) <= NW) ++split;
+        for (int kp = wave; kp < n_rows << split; kp += NW) {
+            const int kk = kp >> split, part = kp - (kk << split);
             const bool on_metric = kk >= n_abs;
             const int at = on_metric ? kk - n_abs : kk;
             unsigned long long left = ln.takes;
@@ -215,7 +235,9 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
             const unsigned long long hits = ((from_prev >> k) & 1ull) << k | (((from_next >> k) & 1ull) << k) << 1;
             T* mov = on_metric ? ovk : ov;
             const int mD = on_metric ? Dk : g.D;
-            lazy_merge<T, PM>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, hits, mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane, 0, mD);
+            const int share = ((mD - 1) / (64 * V) >> split) + 1, from = part * share * 64 * V, to = from + share * 64 * V < mD ? from + share * 64 * V : mD;
+            if (from < to)
+                lazy_merge<T, PM>(on_metric ? xk : x, mov, g, mD, b, rid, sz, k, hits, mov + (b * g.cap + g.ov_base + line * g.per_line + at) * mD, lane, from, to);
         }
     }
 }

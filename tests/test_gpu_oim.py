@@ -365,6 +365,23 @@ def test_few_tokens_row_widths(oracle, dtype, B, H, W, D, passes):
     run_case(oracle, x, dtype, passes, sizes=rng.integers(1, 6, (B, H, W)), tag="widths")
 
 
+# one or two destinations of a line, rows of one piece to nine: one, two or four wavefronts to a row, with and without a last one
+# that has nothing of it, and (13 tokens) too few wavefronts for that
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m", [1, 2, 3])
+@pytest.mark.parametrize("W,D", [(24, 256), (24, 264), (24, 520), (24, 776), (13, 1032), (24, 1032), (40, 1288), (40, 1544), (40, 2056)])
+def test_few_tokens_merged_by_several_wavefronts(oracle, dtype, m, W, D):
+    rng = np.random.default_rng(1000 * m + W + D)
+    x = wl.cast_io((wl.smooth_field(rng, 2, 3, W, D, 1.5) + 0.5 * rng.standard_normal((2, 3, W, D))).astype(np.float32), dtype)
+    out, _ = run_case(oracle, x, dtype, [(W_AX, m), (H_AX, 1)], sizes=rng.integers(1, 6, (2, 3, W)), tag="shared rows")
+    xd = to_dev(x, dtype)
+    plain, keyed = lv.luvc_oim_merge(xd, [(W_AX, m), (H_AX, 1)]), lv.luvc_oim_merge_keyed(xd, xd.clone(), [(W_AX, m), (H_AX, 1)], 1)
+    torch.cuda.synchronize()
+    for k in ("x", "sizes", "merged_map", "kept_map"):
+        assert torch.equal(plain[k], keyed[k]), k
+    assert torch.equal(keyed["x"], keyed["metric"])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("B,H,W,D,passes", [
     (43, 25, 24, 16, [(W_AX, 2), (H_AX, 2)]),              # lines of 24 and of an odd 25, last wavefront with one token
