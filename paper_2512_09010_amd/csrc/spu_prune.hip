@@ -7,6 +7,8 @@
 //                then emits, in ascending index order, every token with key > T and the first of
 //                those with key == T (equal scores: the lower index wins).
 //   spu_gather   one wavefront per kept token copies the ORIGINAL row.
+#include <type_traits>
+
 #include "common.hpp"
 #include "spu.hpp"
 
@@ -164,6 +166,9 @@ spu_gather(const unsigned char* __restrict__ x, const int32_t* __restrict__ kept
 // its share of the kept rows: row q goes to wavefront q mod (4 G) of the sample.  Group 0 also writes
 // kept_idx.  Compared with a selection launch followed by a gather launch this saves a dispatch and the
 // wait between the two, which is most of the time at these sizes.
+// Bound: latency of the selection, then HBM.  us of a call with scores asked for one by one, an argument list for 64 runs, descriptors
+// made of vector registers and the indices ahead of the rows, and as it is: 8 x 1024 x 3584 bf16, 205 kept, 6.98, 6.77; 32 x 500 x 3584,
+// 100, 10.0, 9.6; 1 x 4096 x 1024, 1433, 7.87, 7.45; fp32 16 x 512 x 896, 150, 6.20, 5.87.
 // cache policy of the row copies (buffer aux bits): the copied rows are not read again by this kernel, so the stores
 // carry the non-temporal hint (2) and leave less dirty data in L2 for the end of the kernel (measured: -0.3 us)
 constexpr int kPruneLoadAux = 0, kPruneStoreAux = 2;
@@ -182,19 +187,22 @@ __host__ __device__ inline int prune_groups(int n_keep, int waves, bool gather)
     return G > 256 ? 256 : G;
 }
 
-template <int BYTES, int kFusedThreads, int kFusedKeys>
+// One run, the common case, has a kernel of its own: an argument list for 64 of them is 2 KB, and its run is fetched a trip later.
+template <int RUNS> struct PruneTable { int n; PruneRun run[RUNS]; };
+
+template <int BYTES, int kFusedThreads, int kFusedKeys, int RUNS>
 __global__ void __launch_bounds__(kFusedThreads)
-spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ scores, const PruneRuns runs,
+spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ scores, const PruneTable<RUNS> runs,
                 int64_t row_bytes_in, int64_t row_bytes_out, int32_t* __restrict__ kept_idx, unsigned char* __restrict__ x_out,
                 const int32_t* __restrict__ origin_in /* per token or null: identity */, int32_t* __restrict__ origin_out /* per kept token or null */)
 {
     __shared__ int32_t kept[kFusedThreads * kFusedKeys];
-    __shared__ int hist[4][256];                       // one histogram per digit pass: none has to be cleared in between
+    __shared__ __align__(16) int hist[4][256];         // one histogram per digit pass: none has to be cleared in between
     constexpr int WAVES = kFusedThreads / 64;
     __shared__ uint32_t wave_tot[WAVES], wave_hi[WAVES], wave_lo[WAVES];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    PruneRun run = runs.run[0];                        // fetched beside the count: one run is the common case
-    if (runs.n > 1) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    PruneRun run = runs.run[0];
+    if constexpr (RUNS > 1) {
         int r = 0;
         for (int i = 1; i < runs.n; ++i)
             if ((int)blockIdx.x >= runs.run[i].wg0) r = i;
@@ -207,10 +215,14 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
     // thread tid owns the K consecutive tokens tid * K .. tid * K + K - 1 and reads them straight from memory
     // (a wavefront covers 64 K consecutive scores; a few KB per sample, served by the caches)
     const int K = (N + kFusedThreads - 1) / kFusedThreads, n0 = tid * K;
+    // All asked for together: the descriptor keeps them in bounds, where a branch around each made one trip of every load.
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(s), 0, N * (int)sizeof(float), 0x00020000);
     uint32_t key[kFusedKeys];
 #pragma unroll
-    for (int i = 0; i < kFusedKeys; ++i) key[i] = (i < K && n0 + i < N) ? score_key(s[n0 + i]) : 0u;
-    for (int i = tid; i < 4 * 256; i += kFusedThreads) hist[i >> 8][i & 255] = 0;
+    for (int i = 0; i < kFusedKeys; ++i) key[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, (n0 + i) * (int)sizeof(float), 0, 0);
+    if (tid < 256) *reinterpret_cast<int4*>(&hist[0][0] + 4 * tid) = make_int4(0, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < kFusedKeys; ++i) key[i] = score_key(__uint_as_float(key[i]));
     // Largest and smallest key of the sample: the bits above the highest one in which they differ are common to all
     // keys and need no digit pass (scores of one sample share sign and most of the exponent, so the first of four
     // 8-bit passes would pile every key onto one or two counters - same-address LDS atomics, one after the other).
@@ -292,16 +304,8 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
         }
     }
     __syncthreads();
-    if (g == 0) {
-        for (int q = tid; q < n_keep; q += kFusedThreads) kept_idx[tok_out + q] = kept[q];
-        // position of every kept token before the first stage of a cascade
-        if (origin_out)
-            for (int q = tid; q < n_keep; q += kFusedThreads)
-                origin_out[tok_out + q] = origin_in ? origin_in[tok_in + kept[q]] : kept[q];
-    }
-    if (!x_out) return;
-    for (int q = g * WAVES + wave; q < n_keep; q += G * WAVES) {
-        int src = kept[q];
+    for (int q = x_out ? g * WAVES + wave : n_keep; q < n_keep; q += G * WAVES) {
+        int src = __builtin_amdgcn_readfirstlane(kept[q]);         // scalars: descriptors made of vectors are a loop around every access
         src = src < 0 ? 0 : (src >= N ? N - 1 : src);  // in bounds whatever the scores held
         const unsigned char* in = x + (tok_in + src) * row_bytes_in;
         unsigned char* o = x_out + (tok_out + q) * row_bytes_out;
@@ -326,6 +330,17 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
                 *reinterpret_cast<uint16_t*>(o + i) = *reinterpret_cast<const uint16_t*>(in + i);
         }
     }
+    if (g == G - 1)                                    // the last group, which may have fewer rows
+        for (int q = tid; q < n_keep; q += kFusedThreads) {
+            const int src = kept[q];
+            kept_idx[tok_out + q] = src;
+            // position before the first stage of a cascade
+            if (origin_out) {
+                int from = src;
+                if (origin_in) from = origin_in[tok_in + src];
+                origin_out[tok_out + q] = from;
+            }
+        }
 }
 
 static luvc_status prune_two_launches(const void* x, const float* scores, int B, int N, int D, int64_t row_stride, luvc_dtype dt,
@@ -375,14 +390,22 @@ luvc_status spu_prune_run(const void* x, const float* scores, int D, int64_t row
     if (fused == 0) return LUVC_OK;
     if (wgs >= ((int64_t)1 << 31)) { set_error("too many kept tokens in one call"); return LUVC_ERR_UNSUPPORTED; }
     runs.n = fused;
-#define LUVC_PRUNE_T(BYTES, THREADS, KEYS) LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<BYTES, THREADS, KEYS>), dim3((unsigned)wgs), dim3(THREADS), 0, st, (const unsigned char*)x, \
-                                                 scores, runs, rin, rout, kept_idx, (unsigned char*)x_out, origin_in, origin_out)
+    auto table = [&](auto runs_of) {
+        PruneTable<decltype(runs_of)::value> t;
+        t.n = runs.n;
+        for (int i = 0; i < runs.n; ++i) t.run[i] = runs.run[i];
+        return t;
+    };
+#define LUVC_PRUNE_R(BYTES, THREADS, KEYS, RUNS) LUVC_LAUNCH("spu_prune_fused", (spu_prune_fused<BYTES, THREADS, KEYS, RUNS>), dim3((unsigned)wgs), dim3(THREADS), 0, st, \
+                                                 (const unsigned char*)x, scores, table(std::integral_constant<int, RUNS>{}), rin, rout, kept_idx, (unsigned char*)x_out, origin_in, origin_out)
+#define LUVC_PRUNE_T(BYTES, THREADS, KEYS) do { if (runs.n == 1) LUVC_PRUNE_R(BYTES, THREADS, KEYS, 1); else LUVC_PRUNE_R(BYTES, THREADS, KEYS, kPruneMaxRuns); } while (0)
 #define LUVC_PRUNE(BYTES) do { if (longest > 4096) LUVC_PRUNE_T(BYTES, 1024, 8); else if (wide) LUVC_PRUNE_T(BYTES, 1024, 4); else LUVC_PRUNE_T(BYTES, 256, 4); } while (0)
     if (v16 || !x_out) LUVC_PRUNE(16);
     else if (es == 4)  LUVC_PRUNE(4);
     else               LUVC_PRUNE(2);
 #undef LUVC_PRUNE
 #undef LUVC_PRUNE_T
+#undef LUVC_PRUNE_R
     return check_launch("spu prune");
 }
 
