@@ -609,9 +609,7 @@ oim_lazy_finish_k(FinishArgs a)
     for (int q = 0; q < 2; ++q) {
         const FinishPart& f = a.part[q];
         if (blk < f.blocks) {
-            auto row_in = [&](int64_t row) {
-                const int64_t b = row / a.n_out_per;
-                int id = a.idx ? a.idx[row] : (int)(row - b * a.n_out_per);
+            auto row_in = [&](int64_t b, int id) {
                 id = id < 0 ? 0 : (id >= a.n0 + a.cap ? a.n0 + a.cap - 1 : id);        // ids come from the passes; stay in bounds regardless
                 return id < a.n0 ? f.x + (b * a.n0 + id) * (int64_t)f.row_bytes : f.ov + (b * a.cap + (id - a.n0)) * (int64_t)f.row_bytes;
             };
@@ -621,7 +619,8 @@ oim_lazy_finish_k(FinishArgs a)
                 const int64_t row = ((int64_t)blk * 4 + wave) * per_wave + lane / f.lanes;
                 if (row >= a.n_rows) return;
                 const int off = lane % f.lanes * 16;
-                const unsigned char* in = row_in(row);
+                const uint32_t b = (uint32_t)row / (uint32_t)a.n_out_per;
+                const unsigned char* in = row_in(b, a.idx ? a.idx[row] : (int)((uint32_t)row - b * (uint32_t)a.n_out_per));
                 unsigned char* o = f.out + row * (int64_t)f.row_bytes;
                 if (off < f.row_bytes) *reinterpret_cast<lazy_u32x4*>(o + off) = *reinterpret_cast<const lazy_u32x4*>(in + off);
                 return;
@@ -631,12 +630,25 @@ oim_lazy_finish_k(FinishArgs a)
                 constexpr int R = decltype(rows)::value, P = 8 / R;
                 const int64_t row0 = ((int64_t)blk * 4 + wave) * R;
                 if (row0 >= a.n_rows) return;
+                // image and place of each row, and the ids, asked for together (there are fewer than 2^31 rows)
+                uint32_t image[R];
+                int id[R];
+                uint32_t b = (uint32_t)row0 / (uint32_t)a.n_out_per, at = (uint32_t)row0 - b * (uint32_t)a.n_out_per;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    image[r] = b;
+                    id[r] = (int)at;
+                    if (++at == (uint32_t)a.n_out_per) { at = 0; ++b; }
+                }
+                if (a.idx)
+#pragma unroll
+                    for (int r = 0; r < R; ++r) id[r] = a.idx[row0 + r < a.n_rows ? row0 + r : row0];
                 __amdgpu_buffer_rsrc_t ri[R], ro[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const bool there = row0 + r < a.n_rows;
                     const int64_t row = there ? row0 + r : row0;
-                    ri[r] = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(row_in(row)), 0, there ? f.row_bytes : 0, 0x00020000);
+                    ri[r] = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(row_in(there ? image[r] : image[0], id[r])), 0, there ? f.row_bytes : 0, 0x00020000);
                     ro[r] = __builtin_amdgcn_make_buffer_rsrc(f.out + row * (int64_t)f.row_bytes, 0, there ? f.row_bytes : 0, 0x00020000);
                 }
                 for (int base = 0; base < f.row_bytes; base += P * 1024) {
