@@ -96,6 +96,21 @@ __device__ __forceinline__ unsigned xcd_contiguous(unsigned g, unsigned G)
     return k * q + (k < r ? k : r) + i;
 }
 
+// Which run of a launch a workgroup belongs to: the last of n (64 at most) whose first item, first(i), is not behind `item`.  A lane looks
+// at one, so that all are one trip to the argument list; one after the other, eight runs were half a microsecond in front of everything.
+template <typename F>
+__device__ __forceinline__ int run_of(int n, unsigned item, F first)
+{
+    const int lane = threadIdx.x & 63;
+    const unsigned w = first(lane < n ? lane : 0);
+    return __popcll(__ballot(lane < n && item >= w)) - 1;
+}
+
+// Words of an input for reads of one address by a whole wavefront.  The compiler makes scalar loads of those from a kernel argument; from
+// a pointer chosen among several it made vector loads, waited for one by one.
+using scalar_words = const __attribute__((address_space(4))) int32_t*;
+__device__ __forceinline__ scalar_words as_scalars(const int32_t* p) { return (scalar_words)(uintptr_t)p; }
+
 // ------------------------------------------------------------------ wave64 reductions (all lanes get the result)
 __device__ __forceinline__ double wave_sum(double v)
 {

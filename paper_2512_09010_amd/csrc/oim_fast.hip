@@ -44,10 +44,7 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const i
     unsigned item = xcd_contiguous(blockIdx.x, gridDim.x);         // tiles of a line stay on one XCD
     HalveItem it = tab.it[0];
     if (MOST > 1) {
-        int ent = 0;
-        for (int i = 1; i < tab.n; ++i)
-            if (item >= tab.it[i].at.wg0) ent = i;
-        it = tab.it[ent];
+        it = tab.it[run_of(tab.n, item, [&](int i) { return tab.it[i].at.wg0; })];
     }
     if constexpr (MOST > 1) {
         if (it.at.src) {
@@ -191,9 +188,10 @@ oim_halve(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, const i
     const bool take_a = !a_left, take_c = c_left;
 
     const int64_t ta = line0 + pa * step, tb = line0 + pb * step, tc = line0 + pc * step;
-    const int sb = sizes_in ? sizes_in[tb] : 1;
-    const int sa = take_a ? (sizes_in ? sizes_in[ta] : 1) : 0;
-    const int scz = take_c ? (sizes_in ? sizes_in[tc] : 1) : 0;
+    const scalar_words sizes = as_scalars(sizes_in);
+    const int sb = sizes_in ? sizes[tb] : 1;
+    const int sa = take_a ? (sizes_in ? sizes[ta] : 1) : 0;
+    const int scz = take_c ? (sizes_in ? sizes[tc] : 1) : 0;
     const int S = sb + sa + scz;
     const int64_t n_out_per = (int64_t)(axis ? H : nd) * Wo;
     const int out_in_img = axis ? line * Wo + j : j * Wo + line;
@@ -314,10 +312,7 @@ oim_batch_tail_k(const unsigned char* __restrict__ x, const int32_t* __restrict_
                  int32_t* __restrict__ sizes_out, int32_t* __restrict__ merged_map, int32_t* __restrict__ kept_map,
                  const int32_t* __restrict__ maps, int64_t map_level, const TailTable tab)
 {
-    int ent = 0;
-    for (int i = 1; i < tab.n; ++i)
-        if (blockIdx.x >= tab.it[i].blk0) ent = i;
-    const OimTailItem& a = tab.it[ent];
+    const OimTailItem& a = tab.it[run_of(tab.n, blockIdx.x, [&](int i) { return tab.it[i].blk0; })];
     const int64_t blk = blockIdx.x - a.blk0;
     if (a.copy) {
         const int lane = threadIdx.x & 63;

@@ -84,9 +84,7 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     PairGeom g = tab.it[0].g;
     StepAt at = tab.it[0].at;
     if constexpr (MOST > 1) {
-        int ent = 0;
-        for (int i = 1; i < tab.n; ++i)
-            if (item >= tab.it[i].at.wg0) ent = i;
+        const int ent = run_of(tab.n, item, [&](int i) { return tab.it[i].at.wg0; });
         g = tab.it[ent].g;
         at = tab.it[ent].at;
         if (at.src) {
@@ -139,6 +137,7 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     const int pa = 2 * j, pb = pa + 1, pc = pa + 2;
     const bool has_l = j > 0, has_c = pc < g.L1, has_r = pc + 1 < g.L1;
     const int64_t img_in = at.in_off + (int64_t)b * g.n_in;
+    const scalar_words sizes = as_scalars(sizes_in);
     TokT Tk[R];
     int sk[R];
     unsigned took_a = 0, took_c = 0;                              // bit k: row k absorbed its a / its c
@@ -159,9 +158,9 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
             load_tok(C, x + (has_c ? tc : tb) * g.D, tok_bytes, lane, has_c);
             load_tok(Lt, x + (has_l ? ta - g.sA : tb) * g.D, tok_bytes, lane, has_l);
             load_tok(Rt, x + (has_r ? tc + g.sA : tb) * g.D, tok_bytes, lane, has_r);
-            sb = sizes_in ? sizes_in[tb] : 1;
-            sa_in = sizes_in ? sizes_in[ta] : 1;
-            sc_in = (sizes_in && has_c) ? sizes_in[tc] : 1;
+            sb = sizes_in ? sizes[tb] : 1;
+            sa_in = sizes_in ? sizes[ta] : 1;
+            sc_in = (sizes_in && has_c) ? sizes[tc] : 1;
         }
         if (k == 0) {                                             // `stage` is cleared for everyone before it is used; the first tokens are on their way
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");

@@ -140,9 +140,11 @@ __host__ __device__ inline int circ_lds(int N, int RT) { return 24 * circ_stride
 }  // namespace
 
 // KS: wavefronts that share the steps of a product, each an equal run of them (RT = 1)
-template <typename T, int RT, int KS, bool PAIRED /* every channel pair is one aligned access */>
+// RUNS: one run, the common case, has a kernel of its own, without an argument list for 64 (1.5 KB)
+template <int RUNS> struct CircTable { int n; CircRun run[RUNS]; };
+template <typename T, int RT, int KS, bool PAIRED /* every channel pair is one aligned access */, int RUNS>
 __global__ void __launch_bounds__(256 * KS, KS == 1 || sizeof(T) == 4 ? 2 : 4)
-spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* workgroups across the channels */, int use_hamming, const CircRuns runs,
+spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* workgroups across the channels */, int use_hamming, const CircTable<RUNS> runs,
          unsigned long long* __restrict__ words /* [groups of 32 RT tokens][n_quads][32 RT] */, uint32_t tag, float* __restrict__ scores)
 {
     using raw_t = circ_raw<T, PAIRED>;
@@ -155,13 +157,8 @@ spu_circ(const T* __restrict__ x, int64_t row_stride, int D, int n_quads /* work
     __shared__ float red[4 * ROWS];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int item = (int)xcd_contiguous(blockIdx.x, gridDim.x);
-    CircRun run = runs.run[0];                   // fetched beside the count: one run is the common case
-    if (runs.n > 1) {
-        int q = 0;
-        for (int i = 1; i < runs.n; ++i)
-            if (item >= runs.run[i].group0 * n_quads) q = i;
-        run = runs.run[q];
-    }
+    CircRun run = runs.run[0];
+    if constexpr (RUNS > 1) run = runs.run[run_of(runs.n, (unsigned)item, [&](int i) { return (unsigned)(runs.run[i].group0 * n_quads); })];
     const int N = run.N, sigma = run.sigma, group0 = run.group0;
     const int n_groups = (N + ROWS - 1) / ROWS, local = item - group0 * n_quads;
     const int s = local / (n_quads * n_groups), rem = local - s * (n_quads * n_groups), quad = rem / n_groups, grp = rem - quad * n_groups;
@@ -432,7 +429,7 @@ static int circ_shares(const CircRuns& runs, int D, luvc_dtype dt)
     return wg <= 256 && longest >= (dt == LUVC_F32 ? 256 : 512) ? 2 : 1;
 }
 
-template <typename T, int RT, int KS, bool PAIRED>
+template <typename T, int RT, int KS, bool PAIRED, int RUNS>
 static void circ_launch(const T* x, int64_t row_stride, int D, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st)
 {
     int64_t groups = 0;
@@ -443,22 +440,27 @@ static void circ_launch(const T* x, int64_t row_stride, int D, int use_hamming, 
         const int b = circ_lds(runs.run[i].N, RT);
         lds = b > lds ? b : lds;
     }
-    LUVC_LAUNCH("spu_circ", (spu_circ<T, RT, KS, PAIRED>), dim3((unsigned)(groups * circ_quads(D))), dim3(256 * KS), (size_t)lds, st, x, row_stride, D, circ_quads(D), use_hamming,
-                runs, (unsigned long long*)words, (uint32_t)(spu_next_tag() % 0xffffffffull) + 1u, scores);
+    CircTable<RUNS> table;
+    table.n = runs.n;
+    for (int i = 0; i < runs.n; ++i) table.run[i] = runs.run[i];
+    LUVC_LAUNCH("spu_circ", (spu_circ<T, RT, KS, PAIRED, RUNS>), dim3((unsigned)(groups * circ_quads(D))), dim3(256 * KS), (size_t)lds, st, x, row_stride, D, circ_quads(D), use_hamming,
+                table, (unsigned long long*)words, (uint32_t)(spu_next_tag() % 0xffffffffull) + 1u, scores);
 }
 
 luvc_status spu_score_circ(const void* x, int64_t row_stride, int D, luvc_dtype dt, int use_hamming, CircRuns& runs, void* words, float* scores, hipStream_t st)
 {
     const int RT = circ_rt(runs, D), KS = RT == 1 ? circ_shares(runs, D, dt) : 1;
     const bool paired = spu_circ_rows(x, D, row_stride, dt) == CircRows::Paired;
-#define LUVC_CIRC(TT, R, K) do { \
-        if (paired) circ_launch<TT, R, K, true>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st); \
-        else circ_launch<TT, R, K, false>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st); \
+#define LUVC_CIRC_N(TT, R, K, PAIRED) do { \
+        if (runs.n == 1) circ_launch<TT, R, K, PAIRED, 1>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st); \
+        else circ_launch<TT, R, K, PAIRED, kCircMaxRuns>((const TT*)x, row_stride, D, use_hamming, runs, words, scores, st); \
     } while (0)
+#define LUVC_CIRC(TT, R, K) do { if (paired) LUVC_CIRC_N(TT, R, K, true); else LUVC_CIRC_N(TT, R, K, false); } while (0)
 #define LUVC_CIRC_T(TT) do { if (RT == 4) LUVC_CIRC(TT, 4, 1); else if (RT == 2) LUVC_CIRC(TT, 2, 1); else if (KS == 2) LUVC_CIRC(TT, 1, 2); else LUVC_CIRC(TT, 1, 1); } while (0)
     if (dt == LUVC_F32) LUVC_CIRC_T(float); else LUVC_CIRC_T(bf16_t);
 #undef LUVC_CIRC_T
 #undef LUVC_CIRC
+#undef LUVC_CIRC_N
     return check_launch("spu score (circulant)");
 }
 

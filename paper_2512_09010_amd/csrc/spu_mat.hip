@@ -74,9 +74,7 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
 {
     const int item = (int)xcd_contiguous(blockIdx.x, gridDim.x);
     int at_run = 0;
-    if (RUNS > 1)
-        for (int i = 1; i < runs.n; ++i)
-            if (item >= runs.run[i].wg0) at_run = i;
+    if (RUNS > 1) at_run = run_of(runs.n, (unsigned)item, [&](int i) { return (unsigned)runs.run[i].wg0; });
     const MatLaunchRun& run = runs.run[at_run];
     const MatShape& sh = run.sh;
     constexpr int P = kMatPairs, WAVES = kMatWaves, THREADS = kMatThreads;

@@ -203,10 +203,7 @@ spu_prune_fused(const unsigned char* __restrict__ x, const float* __restrict__ s
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     PruneRun run = runs.run[0];
     if constexpr (RUNS > 1) {
-        int r = 0;
-        for (int i = 1; i < runs.n; ++i)
-            if ((int)blockIdx.x >= runs.run[i].wg0) r = i;
-        run = runs.run[r];
+        run = runs.run[run_of(runs.n, blockIdx.x, [&](int i) { return (unsigned)runs.run[i].wg0; })];
     }
     const int N = run.N, n_keep = run.n_keep, G = prune_groups(n_keep, WAVES, x_out != nullptr);
     const int b = ((int)blockIdx.x - run.wg0) / G, g = (int)blockIdx.x - run.wg0 - b * G;
