@@ -336,6 +336,10 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
         // ---- back
 #pragma clang loop unroll(disable)
         for (int t = 0; t < NT; ++t) {
+            // The older wavefront of a SIMD would come first throughout and leave the other one alone at the end, where hardly anything
+            // overlaps: they take turns, tile by tile.  32x390x3584 48.9 -> 46.1 us, 16x720x4096 41.1 -> 40.4, 4x2048x3584 34.3 -> 34.0.
+            if ((t ^ (wave >> 2)) & 1) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
             float wc[4], ws[4], sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int v = 0; v < 4; ++v) { const float2 q = tw[t * 256 + tw_back[v]]; wc[v] = q.x; ws[v] = q.y; }
@@ -362,6 +366,7 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
             q.w = fmaf(sum[3] * back, back, q.w);
             *at = q;
         }
+        __builtin_amdgcn_s_setprio(0);
     }
     if (wave == 0) {
         MatTokens::landed(false);
