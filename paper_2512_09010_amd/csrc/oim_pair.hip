@@ -77,6 +77,13 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     // to 3 or beyond and waits for no more than a 2 before, so every wait ends, whatever the verdicts.
     __shared__ int stage[NW];
     constexpr int kSums = 3, kSettled = 16, kFirstUp = 4, kNextUp = 8;
+    // Of the wavefronts of a SIMD the oldest comes first, with merges of the second pass before younger ones that have tokens to ask for.
+    // The merges, which nobody waits for, come last instead; the exchange, which neighbours wait for, first; and of the first pass the
+    // earlier rows, as long as a compute unit has one workgroup: with four (tokens of up to 8 words) the later workgroups then hold up
+    // the older ones' ends.  us of the cases with the oldest first, merges last, all of it: 2 x 112 x 112 x 1280 three times, with the score, 61.6, 58.9,
+    // 58.5; 128 x 16 x 16 x 1152 69.1, 68.2, 67.3; 8 x 64 x 64 x 1280 68.0, 67.0, 66.8; 80 x 24 x 24 x 1024 (8 words) 81.0, 80.0, 82.5.
+    constexpr bool kRowsTakeTurns = N > 8;
+    __builtin_amdgcn_s_setprio(1);
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -147,6 +154,10 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     for (int k = 0; k < R; ++k) {
         const int r = r0 + k;
         TokT& Tn = Tk[k];
+        if constexpr (kRowsTakeTurns) {
+            if (k < R / 2) __builtin_amdgcn_s_setprio(2);
+            else __builtin_amdgcn_s_setprio(1);
+        }
         TokT A, Bt, C, Lt, Rt;
         int sn = 0, sa_in = 1, sb = 1, sc_in = 1;
         const bool there = active && r >= row_lo && r <= row_end;
@@ -206,6 +217,7 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     if (!active) return;
 
     // ------------------------------------------------------------------ second pass: exchange
+    __builtin_amdgcn_s_setprio(3);
     if (is_main) {
 #pragma unroll
         for (int i = 0; i < N; ++i) lds_tok[(w * N + i) * 64 + lane] = Tk[0].w[i];
@@ -282,6 +294,7 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     if (is_halo) return;
 
     // ------------------------------------------------------------------ second pass: merge, write, maps
+    __builtin_amdgcn_s_setprio(0);
     const int own_end = row_base + 2 * nseg;                      // rows below it belong to the next run ...
     const bool tail = (g.L2 & 1) && own_end == g.L2 - 1;          // ... except the last source of an odd line
     const int64_t img_out = at.out_off + (int64_t)b * g.n_out;

@@ -109,6 +109,9 @@ oim_halve_pair_keyed(const T* __restrict__ x, const T* __restrict__ metric, cons
     unsigned took_a = 0, took_c = 0;                              // bit k: row k absorbed its a / its c
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();                                 // `stage` is cleared for everyone before it is used
+    // The merges of the second pass, which nobody waits for, come behind everything else; the oldest wavefront's came first.  8 x 64 x 64 x
+    // 1280 bf16, keys of 128, with the value enhancement: 44.6 -> 43.4 us.
+    __builtin_amdgcn_s_setprio(1);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 #pragma unroll 4
     for (int k = 0; k < 4; ++k) {
@@ -209,6 +212,7 @@ oim_halve_pair_keyed(const T* __restrict__ x, const T* __restrict__ metric, cons
     const bool up0 = goes_up(0), up2 = e2 && goes_up(2), up4 = e4 && goes_up(4);
 
     // ------------------------------------------------------------------ second pass: merge, write, maps
+    __builtin_amdgcn_s_setprio(0);
     const bool tail = (g.L2 & 1) && own_end == g.L2 - 1;          // the last source of an odd line belongs to this run
     const int64_t img_out = (int64_t)b * g.n_out;
     const int uo = r0 >> 1;                                       // output slot (second axis) of destination r0 + 1
