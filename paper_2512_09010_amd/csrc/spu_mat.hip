@@ -336,10 +336,6 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
         // ---- back
 #pragma clang loop unroll(disable)
         for (int t = 0; t < NT; ++t) {
-            // The older wavefront of a SIMD would come first throughout and leave the other one alone at the end, where hardly anything
-            // overlaps: they take turns, tile by tile.  32x390x3584 48.9 -> 46.1 us, 16x720x4096 41.1 -> 40.4, 4x2048x3584 34.3 -> 34.0.
-            if ((t ^ (wave >> 2)) & 1) __builtin_amdgcn_s_setprio(1);
-            else __builtin_amdgcn_s_setprio(0);
             float wc[4], ws[4], sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int v = 0; v < 4; ++v) { const float2 q = tw[t * 256 + tw_back[v]]; wc[v] = q.x; ws[v] = q.y; }
@@ -357,7 +353,14 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
 #pragma unroll
                 for (int p = 0; p < P; ++p) z[p][o] = mac_f16(z[p][o], ghh[p][go], klo);
             }
+            // The older wavefront of a SIMD would come first throughout and leave the other one alone at the end, where hardly anything
+            // overlaps.  Whichever is in the second half of a tile, its vector instructions and short products, comes before one that
+            // asks for the long products of the first.  us of score and prune with turns tile by tile, which had taken 32x390x3584 from 48.9
+            // to 46.1 for the score alone, and so: 8x1024x3584 38.2, 37.2; 32x390x3584 54.5, 53.8; 16x720x4096 50.6, 49.9; 4x2048x3584 42.0, 41.0;
+            // 5x1352x3200 38.5, 37.6.
+            __builtin_amdgcn_s_setprio(1);
             bins_to_energies(sum, z, wc, ws, i2);
+            __builtin_amdgcn_s_setprio(0);
             float4* at = esum + (wave * NT + t) * 64 + lane;
             float4 q = grp ? *at : make_float4(0.f, 0.f, 0.f, 0.f);
             q.x = fmaf(sum[0] * back, back, q.x);
@@ -366,7 +369,6 @@ spu_mat(const bf16_t* __restrict__ x, const MatLaunch<RUNS> runs, int D, int64_t
             q.w = fmaf(sum[3] * back, back, q.w);
             *at = q;
         }
-        __builtin_amdgcn_s_setprio(0);
     }
     if (wave == 0) {
         MatTokens::landed(false);
