@@ -363,6 +363,13 @@ luvc_status luvc_selftest_fdot2(const void* x, const void* y, int rows, int word
  */
 luvc_status luvc_selftest_screen_tile(const void* a, const void* c, int D, luvc_dtype dtype, float* out, void* hip_stream);
 
+/*
+ * Self-test aid (not a step of the paper's method): for rows of D channels, the most channels that one wavefront of that
+ * screening contracts, and the distance from the fp64 cosine within which a screened one is taken to lie (the decisions
+ * of Section 3.2, Algorithm 1, rest on it).  Host only.
+ */
+luvc_status luvc_selftest_screen_bound(int D, luvc_dtype dtype, int* channels, float* eps);
+
 #ifdef __cplusplus
 }
 #endif

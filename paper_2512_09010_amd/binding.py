@@ -29,7 +29,8 @@ EXPORTS = ("luvc_version", "luvc_last_error", "luvc_oim_plan", "luvc_oim_workspa
            "luvc_spu_cascade_keeps", "luvc_spu_stage",
            "luvc_oim_plan_anyres", "luvc_oim_ragged_workspace_bytes", "luvc_oim_merge_ragged",
            "luvc_spu_ragged_workspace_bytes", "luvc_spu_stage_ragged",
-           "luvc_profile_start", "luvc_profile_stop", "luvc_profile_kernel", "luvc_selftest_fdot2", "luvc_selftest_screen_tile")
+           "luvc_profile_start", "luvc_profile_stop", "luvc_profile_kernel", "luvc_selftest_fdot2", "luvc_selftest_screen_tile",
+           "luvc_selftest_screen_bound")
 
 
 class LuvcPass(ctypes.Structure):
@@ -109,6 +110,8 @@ def lib() -> ctypes.CDLL:
     L.luvc_selftest_fdot2.restype = i
     L.luvc_selftest_screen_tile.argtypes = [vp, vp, i, i, vp, vp]
     L.luvc_selftest_screen_tile.restype = i
+    L.luvc_selftest_screen_bound.argtypes = [i, i, ctypes.POINTER(i), ctypes.POINTER(ctypes.c_float)]
+    L.luvc_selftest_screen_bound.restype = i
     _lib = L
     return L
 
@@ -618,3 +621,10 @@ def luvc_selftest_screen_tile(a, c, stream=None):
     out = torch.empty((32, 32), dtype=torch.float32, device=a.device)
     _check(lib().luvc_selftest_screen_tile(_ptr(a), _ptr(c), a.shape[1], _dtype_code(a), _ptr(out), _native().stream(stream)))
     return out
+
+
+def luvc_selftest_screen_bound(D, dtype):
+    """-> (channels, eps): the most channels a wavefront of the wide matching's screening contracts for rows of D, and what a screened cosine is taken to be within."""
+    c, eps = ctypes.c_int(), ctypes.c_float()
+    _check(lib().luvc_selftest_screen_bound(D, dtype, ctypes.byref(c), ctypes.byref(eps)))
+    return c.value, eps.value

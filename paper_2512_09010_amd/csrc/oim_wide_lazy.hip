@@ -16,17 +16,18 @@
 //      (v_mfma_f32_16x16x32_bf16, or four v_mfma_f32_16x16x4_f32 for fp32 tokens): a 32 x 32 tile at a time, eight
 //      wavefronts split the channels, every token byte is fetched once per tile.  The squared norms are summed in fp32
 //      on the way (in fp64, they took as long as everything else of the screening).  A screened cosine is taken to be
-//      within eps = (5 D / 32 + 53) 2^-23 of the fp64 cosine.  A wavefront contracts c <= D / 8 + 32 channels, which is
-//      at most c accumulation steps of 2^-23 each (relative to the sum of the magnitudes of the products, which is at
-//      most the product of the norms; the products of bf16 values are exact in fp32) - tests/test_gpu_oim_wide.py pins
-//      the contraction at that rate against fp64 on adversarial rows - and adding the eight parts is 4 more.  A squared
-//      norm is the sum of c / 2 roundings of 2^-24 in a lane and 8 behind it, halved by the root, twice; root,
-//      reciprocal and the two products of a cosine are 5: 5 c / 4 + 13 together.  The roundings count along the
-//      longest chain of additions, an eighth of the channels, not over all of them.  With (D + 24) 2^-22, ten times as
-//      much at 1280 channels, more sources and destinations had to be repeated in fp64, a memory trip behind the
-//      screening (8 x 64 x 64 x 1280 bf16, six passes of merge number 2: 185.7 us, 173.0 with this bound).  Sums of squares
-//      beyond 2^100 end the screening of their line: everything is repeated then.  Small values need no such care: what
-//      flushed products lose is below 2^-116, far below a norm of 1e-12, which is where the method clamps.
+//      within eps = (5 D / 32 + 53) 2^-23 of the fp64 cosine.  In units of 2^-23, for a wavefront that contracts c channels:
+//      the products are at most c accumulation steps of one unit each, relative to the sum of the magnitudes of the products,
+//      which is at most the product of the norms (the products of bf16 values are exact in fp32) - tests/test_gpu_oim_wide.py
+//      pins the contraction at that rate against fp64 on adversarial rows - and 3.5 for adding the eight parts.  A squared
+//      norm is c / 4 roundings of half a unit in a lane, which has a quarter of the channels, and 9 behind it, halved by the
+//      root, twice: c / 8 + 4.5.  Two roots, two reciprocals and the two products of a cosine are 3.  That is 9 c / 8 + 11
+//      together, and with c <= D / 8 + 28 at most 9 D / 64 + 42.5 (tests/test_abi.py holds the longest run of channels against eps
+//      for every width).  The roundings count along the longest chain of additions, an eighth of the channels, not over all
+//      of them.  With (D + 24) 2^-22, ten times as much at 1280 channels, more sources and destinations had to be repeated in fp64,
+//      a memory trip behind the screening (8 x 64 x 64 x 1280 bf16, six passes of merge number 2: 185.7 us, 173.0 with this bound).
+//      Sums of squares beyond 2^100 end the screening of their line: everything is repeated then.  Small values need no such
+//      care: what flushed products lose is below 2^-116, far below a norm of 1e-12, which is where the method clamps.
 //   2. EXACT.  A source may be among the m best of the line only if fewer than m screened best cosines exceed its own by
 //      more than 2 eps; for each such contender, the destinations within 2 eps of its best screened cosine may be its
 //      best destination, no other can.  Their dot products are repeated in fp64 (a wavefront per contender, two
@@ -127,6 +128,19 @@ template <> struct screen<float> {
         return acc;
     }
 };
+
+constexpr int kScreenWaves = 8;                  // wavefronts that split the channels of a tile
+
+// A wavefront's run of steps of KS channels, and the channels behind the last whole step, which go to the last wavefront: its run is never
+// the longest, so no wavefront contracts more than D / 8 + 28 channels.
+struct ScreenRun { int step0, steps, rest; };
+template <int KS> __host__ __device__ inline ScreenRun screen_run(int D, int wave)
+{
+    const int all = D / KS, step0 = (wave * all + kScreenWaves - 1) / kScreenWaves;
+    return {step0, ((wave + 1) * all + kScreenWaves - 1) / kScreenWaves - step0, wave == kScreenWaves - 1 ? D - all * KS : 0};
+}
+// what a screened cosine may be off by
+__host__ __device__ inline float screen_eps(int D) { return (0.15625f * (float)D + 53.f) * 1.1920929e-7f; }
 
 // 16 bytes of a token at channel d, zeros past its end or for a token that is not there (rows are multiples of 16 bytes)
 template <typename T>
@@ -229,7 +243,6 @@ selftest_screen_tile(const T* __restrict__ a, const T* __restrict__ c, int D, fl
         for (int v = 0; v < 4; ++v) out[(16 * (q >> 1) + 4 * kq + v) * 32 + 16 * (q & 1) + r] = acc[q >> 1][q & 1][v];
 }
 
-constexpr int kScreenWaves = 8;                  // wavefronts that split its channels
 template <typename T, int TILE /* 1, 2: lines of up to 32, 64 tokens, which are one tile; 0: any */>
 __global__ void __launch_bounds__(1024)
 oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric [.., Dk] the decisions are taken on, or null: x */,
@@ -270,7 +283,7 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     const T* dx = xk ? xk : x;
     const T* dov = xk ? ovk : ov;
     const int dD = xk ? Dk : g.D;
-    float tau = 2.f * (0.15625f * (float)dD + 53.f) * 1.1920929e-7f;  // 2 eps
+    float tau = 2.f * screen_eps(dD);
 
     // All asked for before any is waited for: six passes of 1 x 16 x 16 x 768 48.0 -> 44.8 us, of 8 x 64 x 64 x 1280 148.1 -> 145.8.
     if (tid < len) {
@@ -303,13 +316,13 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
         // A wavefront owns a run of steps of KS channels, a lane its quarter of each; the trip count is the same in every lane (the
         // matrix instructions want the whole wavefront).  Rows that are not there, and steps beyond the last, are read from where some
         // are, without a branch: the compiler waits for everything in flight at a join.  Channels that do not fill a step are the last
-        // wavefront's, at the end.
+        // wavefront's, at the end (it has the shortest run, see screen_run()).
         // LOADS steps stay in flight, across the tiles of a long line too, asked for row by row: the two halves of a cache line one
         // after the other.  Reads of 8 x 64 x 64 x 1280 bf16 in this order, nothing done with them, 12.8 us from the shared cache
         // and 15.5 from memory; 32 bytes of 32 rows to a load and the halves of a line with different wavefronts 15.4 and 21.2; step
         // by step 13.7 and 18.7; in the order of memory 12.3 and 14.4.
-        const int all = dD / sc::KS, step0 = wave * all / kScreenWaves, steps = (wave + 1) * all / kScreenWaves - step0;
-        const int rest = wave == kScreenWaves - 1 ? dD - all * sc::KS : 0;
+        const ScreenRun run = screen_run<sc::KS>(dD, wave);
+        const int first = run.step0, steps = run.steps, rest = run.rest;
         const T* tok[2 * SUB];                                                // sources r, 16 + r and destinations r, 16 + r of the tile
         u32x4 raw[LOADS][2 * SUB];
         auto fetch = [&](int u, int i, int step) { raw[u][i] = *reinterpret_cast<const u32x4*>(tok[i] + sc::KS * step); };
@@ -317,7 +330,7 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
             const int js = (ONE ? 0 : t / tiles_d * 32) + r, jd = (ONE ? 0 : t % tiles_d * 32) + r;
 #pragma unroll
             for (int i = 0; i < SUB; ++i) {
-                const int at = step0 * sc::KS + kq * sc::KL;
+                const int at = first * sc::KS + kq * sc::KL;
                 tok[i] = row_of<T>(dx, dov, b, rid[js + 16 * i < n_src ? 2 * (js + 16 * i) : 0], g, dD) + at;
                 tok[SUB + i] = row_of<T>(dx, dov, b, rid[jd + 16 * i < n_dst ? 2 * (jd + 16 * i) + 1 : 0], g, dD) + at;
             }
@@ -767,4 +780,22 @@ extern "C" luvc_status luvc_selftest_screen_tile(const void* a, const void* c, i
     if (dtype == LUVC_F32) LUVC_LAUNCH("selftest_screen_tile", (selftest_screen_tile<float>), dim3(1), dim3(64), 0, st, (const float*)a, (const float*)c, D, out);
     else                   LUVC_LAUNCH("selftest_screen_tile", (selftest_screen_tile<bf16_t>), dim3(1), dim3(64), 0, st, (const bf16_t*)a, (const bf16_t*)c, D, out);
     return check_launch("selftest screen tile");
+}
+
+extern "C" luvc_status luvc_selftest_screen_bound(int D, luvc_dtype dtype, int* channels, float* eps)
+{
+    using namespace luvc;
+    if ((dtype != LUVC_F32 && dtype != LUVC_BF16) || !channels || !eps || D < 1) {
+        set_error("luvc_selftest_screen_bound: unknown dtype, null pointer, or no channels");
+        return LUVC_ERR_INVALID_ARG;
+    }
+    *channels = 0;
+    for (int wave = 0; wave < kScreenWaves; ++wave) {
+        const bool f32 = dtype == LUVC_F32;
+        const ScreenRun run = f32 ? screen_run<screen<float>::KS>(D, wave) : screen_run<screen<bf16_t>::KS>(D, wave);
+        const int c = run.steps * (f32 ? screen<float>::KS : screen<bf16_t>::KS) + run.rest;
+        if (c > *channels) *channels = c;
+    }
+    *eps = screen_eps(D);
+    return LUVC_OK;
 }

@@ -203,6 +203,18 @@ def test_selftest_entry_points_reject_bad_arguments(L):
     assert rc == lv.LUVC_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("dtype,V", [(lv.LUVC_BF16, 8), (lv.LUVC_F32, 4)])
+def test_screening_bound_covers_the_longest_run_of_channels(L, dtype, V):
+    """What a screened cosine of the wide matching may be off by, in units of 2^-23, for a wavefront that contracts c channels: c for the
+    products and 3.5 for adding the parts of eight wavefronts; of each of the two squared norms c / 4 roundings of half a unit in a lane and
+    9 behind it, halved by the root; 3 for roots, reciprocals and the two products of a cosine."""
+    for D in range(V, 8193, V):
+        c, eps = lv.luvc_selftest_screen_bound(D, dtype)
+        assert -(-D // 8) <= c <= D / 8 + 28, (D, c)
+        assert eps * 2.0 ** 23 >= c + 3.5 + (c / 4 + 9) / 2 + 3, (D, c, eps * 2.0 ** 23)
+    assert L.luvc_selftest_screen_bound(0, dtype, None, None) == lv.LUVC_ERR_INVALID_ARG
+
+
 def test_anyres_plan_and_cascade_keeps_against_the_oracle(L, oracle):
     """Host arithmetic of the library against the oracle's separately written routines, over many shapes."""
     for H in (1, 2, 7, 16, 24, 37, 64, 112, 200):

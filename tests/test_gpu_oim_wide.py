@@ -223,7 +223,7 @@ def test_wide_decisions_the_screening_cannot_tell(oracle, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("D,apart", [(8, 2e-3), (136, 4e-3), (1280, 2e-3), (1280, 8e-3), (1408, 4e-3)])
+@pytest.mark.parametrize("D,apart", [(8, 2e-3), (56, 2e-3), (80, 3e-3), (88, 2e-3), (136, 4e-3), (312, 3e-3), (1280, 2e-3), (1280, 8e-3), (1408, 4e-3)])
 def test_wide_decisions_around_the_screening_bound(oracle, dtype, D, apart):
     """Cosines of a line about apart^2 = 4e-6 .. 6e-5 from each other, where the screening's allowance (6e-6 at 8 channels, 3e-5 at
     1408) takes some decisions and leaves others to fp64; long lines have several tiles."""
