@@ -181,6 +181,31 @@ def test_oim_runs_that_meet_at_different_steps(oracle, dtype, axes):
     oim_ragged_case(oracle, shapes, 40, dtype, 0, 13, with_sizes=True, schedules=schedules)
 
 
+@pytest.mark.parametrize("axes", [["1101", "10101"], ["0010", "10101", "1010"], ["110", "1010"], ["1", "10101", "001"]])
+def test_oim_runs_take_no_more_launches_than_step_by_step(oracle, axes):
+    """Runs that gather for one kind of step never cost more launches than a launch per step and kind."""
+    shapes = [(48 + 3 * i, 40 + 5 * i) for i in range(len(axes))]
+    schedules = [halvings(h, w, [int(a) for a in ax]) for (h, w), ax in zip(shapes, axes)]
+    kinds = []
+    for ax in axes:                                      # a pair is two passes on different axes
+        kinds.append([])
+        while ax:
+            kinds[-1].append(2 if len(ax) > 1 and ax[0] != ax[1] else 1)
+            ax = ax[kinds[-1][-1]:]
+    by_steps = sum(len({k[s] for k in kinds if s < len(k)}) for s in range(max(map(len, kinds))))
+    x = torch.randn((sum(h * w for h, w in shapes), 40), device="cuda").to(torch.bfloat16)
+    lv.luvc_oim_merge_ragged(x, shapes, schedules)
+    prof = lv.LaunchProfile(64)
+    prof.start()
+    lv.luvc_oim_merge_ragged(x, shapes, schedules)
+    prof.stop()
+    torch.cuda.synchronize()
+    launches = [name for name, _ in prof.results()]
+    prof.close()
+    assert 0 < sum(name.startswith("oim_halve") for name in launches) <= by_steps, (by_steps, launches)
+    oim_ragged_case(oracle, shapes, 40, "bf16", 0, 14, with_sizes=True, schedules=schedules)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_spu_more_runs_than_a_launch_takes(oracle, dtype):
     """More runs of short samples than one argument list holds, with samples of other kernels between them."""
