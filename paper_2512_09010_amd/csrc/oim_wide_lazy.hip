@@ -136,8 +136,8 @@ constexpr int kScreenWaves = 8;                  // wavefronts that split the ch
 struct ScreenRun { int step0, steps, rest; };
 template <int KS> __host__ __device__ inline ScreenRun screen_run(int D, int wave)
 {
-    const int all = D / KS, step0 = (wave * all + kScreenWaves - 1) / kScreenWaves;
-    return {step0, ((wave + 1) * all + kScreenWaves - 1) / kScreenWaves - step0, wave == kScreenWaves - 1 ? D - all * KS : 0};
+    const unsigned all = (unsigned)D / KS, upto = wave * all + kScreenWaves - 1, step0 = upto / kScreenWaves;
+    return {(int)step0, (int)((upto + all) / kScreenWaves - step0), wave == kScreenWaves - 1 ? (int)(D - all * KS) : 0};
 }
 // what a screened cosine may be off by
 __host__ __device__ inline float screen_eps(int D) { return (0.15625f * (float)D + 53.f) * 1.1920929e-7f; }
@@ -243,7 +243,7 @@ selftest_screen_tile(const T* __restrict__ a, const T* __restrict__ c, int D, fl
         for (int v = 0; v < 4; ++v) out[(16 * (q >> 1) + 4 * kq + v) * 32 + 16 * (q & 1) + r] = acc[q >> 1][q & 1][v];
 }
 
-template <typename T, int TILE /* 1, 2: lines of up to 32, 64 tokens, which are one tile; 0: any */>
+template <typename T, int TILE /* 1, 2: lines of up to 32, 64 tokens, which are one tile; 0: any */, int LOADS /* steps in flight */>
 __global__ void __launch_bounds__(1024)
 oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric [.., Dk] the decisions are taken on, or null: x */,
               T* ovk /* its overlay */, int Dk, const int32_t* __restrict__ idx_in /* null: identity */,
@@ -308,8 +308,7 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     // Result layout of the 16 x 16 instructions: lane l, register v holds row 4 (l / 16) + v, column l % 16.
     {
         constexpr int SUB = TILE == 1 ? 1 : 2;                                // 16 x 16 products along each side of a tile
-        constexpr bool BLOCKS = TILE == 2 && sizeof(T) == 2;
-        constexpr int LOADS = TILE == 1 ? 6 : BLOCKS ? 5 : 4;
+        constexpr bool BLOCKS = TILE == 2 && sizeof(T) == 2;                  // LOADS steps are used, then the next are asked for
         const int tiles_s = ONE ? 1 : (n_src + 31) / 32, tiles_d = ONE ? n_dst > 0 : (n_dst + 31) / 32, tiles = tiles_s * tiles_d;
         const int r = lane & 15, kq = lane >> 4;
         const bool screens = wave < kScreenWaves;
@@ -706,6 +705,21 @@ int oim_wide_lazy_rows(int h, int w, int axis, int m)
     return nlines * (m < n_dst ? m : n_dst);
 }
 
+// bf16 lines of 33 to 64 tokens are read in blocks of steps: of five where the wavefronts take fewer blocks of five than of four, else
+// of four.  us of a call, merge number 2 out of both axes of 4 x 64 x 64, in blocks of four and of five: 1152 channels (4 and 5 steps of a
+// wavefront) 42.1, 39.4; 1408 (5 and 6) 49.2, 47.8; 1536 (6) 50.4, 54.1; 1792 (7) 56.8, 60.5; 2048 (8) 60.3, 66.2; 2560 (10) 74.3, 71.2; 4096
+// (16) 110.0, 119.0; up to 1024 the same.  (8 x 64 x 64 x 1280, 5 steps: 77.0, 66.2.  Six in flight do not fit the registers.)
+static bool screen_by_fives(int D)
+{
+    int fours = 0, fives = 0;
+    for (int wave = 0; wave < kScreenWaves; ++wave) {
+        const int steps = screen_run<screen<bf16_t>::KS>(D, wave).steps;
+        fours += (steps + 3) / 4;
+        fives += (steps + 4) / 5;
+    }
+    return fives < fours;
+}
+
 template <typename T>
 static luvc_status run_lazy_pass(const T* x, T* ov, const T* xk, T* ovk, int Dk, const int32_t* idx_in, const int32_t* sizes_in, const int32_t* kept_in,
                                  int B, int n0, int h, int w, int D, int axis, int m, int radius, int cap, int ov_base,
@@ -721,9 +735,13 @@ static luvc_status run_lazy_pass(const T* x, T* ov, const T* xk, T* ovk, int Dk,
     // eight wavefronts; sixteen where so many destinations are merged that eight would take several rounds and a compute
     // unit has no second line to work on
     const int waves = g.per_line * (xk ? 2 : 1) > 8 && B * nlines <= 256 ? 16 : 8;
-#define LUVC_WIDE(TILE) LUVC_LAUNCH("oim_wide_line", (oim_wide_line<T, TILE>), dim3((unsigned)(B * nlines)), dim3(64 * waves), lds, st, x, ov, xk, ovk, Dk, \
+    constexpr int kMost = sizeof(T) == 2 ? 5 : 4;
+#define LUVC_WIDE(TILE, LOADS) LUVC_LAUNCH("oim_wide_line", (oim_wide_line<T, TILE, LOADS>), dim3((unsigned)(B * nlines)), dim3(64 * waves), lds, st, x, ov, xk, ovk, Dk, \
                                    idx_in, sizes_in, kept_in, g, idx_out, sizes_out, kept_out, pass_map)
-    if (len <= 32) LUVC_WIDE(1); else if (len <= 64) LUVC_WIDE(2); else LUVC_WIDE(0);
+    if (len <= 32) LUVC_WIDE(1, 6);
+    else if (len > 64) LUVC_WIDE(0, 4);
+    else if (sizeof(T) == 2 && screen_by_fives(xk ? Dk : D)) LUVC_WIDE(2, kMost);
+    else LUVC_WIDE(2, 4);
 #undef LUVC_WIDE
     return check_launch("oim pass (wide matching, one launch)");
 }

@@ -234,7 +234,7 @@ def test_wide_decisions_around_the_screening_bound(oracle, dtype, D, apart):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("H,W,D", [(2, 31, 8), (2, 32, 40), (3, 33, 24), (2, 64, 264), (3, 65, 136), (2, 63, 1288), (2, 32, 1560), (2, 96, 1296), (5, 17, 1024)])
+@pytest.mark.parametrize("H,W,D", [(2, 31, 8), (2, 32, 40), (3, 33, 24), (2, 64, 264), (3, 65, 136), (2, 63, 1288), (2, 32, 1560), (2, 96, 1296), (5, 17, 1024), (2, 48, 1560), (3, 41, 2312), (2, 64, 2560), (2, 33, 4096)])
 def test_wide_lines_around_a_tile_and_rows_around_a_step(oracle, dtype, H, W, D):
     """Lines at the edges of the tiles of 16 and 32 sources, rows that end within a step of the contraction or have more steps than stay
     in flight, and merge numbers on either side of the one up to which sources are picked one by one."""
