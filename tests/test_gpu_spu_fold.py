@@ -29,6 +29,7 @@ SHAPES = [
     (6, 2230, 1032, 150),               # 10 223 14     2
     (6, 2061, 1032, 135),               #  9 229 15     2
     (4, 2064, 1032, 112), (4, 2080, 1032, 1), (4, 2304, 1032, 230),      # 16 129, 16 130, 16 144
+    (10, 975, 2184, 140), (8, 1001, 3592, 150),         # odd numbers of up to 1024 tokens, 18 and 29 tiles: two columns to a thread in the last sum
     (30, 420, 2056, 28), (20, 648, 3080, 60), (6, 2736, 2312, 100),      # 15 28, 12 54 and 16 171 with more than 32 groups of channels
 ]
 
