@@ -12,10 +12,10 @@
 //
 // Bound: latency.  A pass reads its tokens once, but a line is a chain of memory trips - ids, tokens, merged rows - with
 // the decisions between them; as many wavefronts as a line has groups of four tokens share it, so that each trip is made once.
-// 12 x 32 x 32 x 1024 bf16, three operations of (W,2),(H,2): 157 us as three launches per pass (norms and products,
-// decisions, a merge that rewrote the whole grid), 75 us as one, 68 with two pieces of a row per lane where a row has no more, 62.4 with
-// the ids of a wavefront's tokens asked for together (one behind the other, each a branch and a wait, they were most of the 1.2 us
-// before its first token) and a merged row shared by two wavefronts.
+// 12 x 32 x 32 x 1024 bf16, three operations of (W,2),(H,2): 160 us as three launches per pass (norms and products,
+// decisions, a merge that rewrites the whole grid), 62 as one with two pieces of a row per lane where a row has no more, the ids of a
+// wavefront's tokens asked for together (one behind the other, each a branch and a wait, they were most of the 1.2 us before its first
+// token), a root per token (63.0 with one in every cosine) and a merged row shared by two wavefronts (66.4 without).
 // Narrow rows were slower than the three launches while every row took three pieces: 32 x 64 x 64 x 384 bf16, (W,2): 92 us by
 // pass, 130, 78 then, of which the copy of the output rows went from 63 to 31.
 #include "common.hpp"
@@ -31,9 +31,9 @@ constexpr int kAdjTok = 4;                       // consecutive tokens of a wave
 // costs its products all the same, and the registers of fewer pieces leave room for a second line on a compute unit.
 // HOLD: a line has at most four tokens per wavefront, a row at most P pieces, and the decisions are taken on the tokens:
 // they stay in registers until the end of the pass, and a wavefront merges the two destinations among its own.  Taken where
-// the lines come in several rounds: 8 x 64 x 64 x 1280 bf16, merge number 2 three times, 167.2 us a call without, 163.0 with
-// (158.1 now, with the ids asked for together); 32 x 64 x 64 x 384, once, 122.4, 118.7 (115.0 now).  A launch that
-// is one round long is no quicker for the trip it saves: 12 x 32 x 32 x 1024 68.1, 69.6 (71.1 for 66.9 now); 1 x 100 x 24 x 1408 68.7, 70.7.
+// the lines come in several rounds: 8 x 64 x 64 x 1280 bf16, merge number 2 three times, 158.1 us a call without, 153.3 with;
+// 32 x 64 x 64 x 384, once, 117.8, 112.8.  A launch that is one round long is no quicker for the trip it saves: 12 x 32 x 32 x 1024
+// three times 62.3, 67.8; 1 x 100 x 24 x 1408 64.9, 67.6.
 template <typename T, int P, int PM, bool HOLD>
 __global__ void __launch_bounds__(1024)
 oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric [.., Dk] the decisions are taken on, or null: x */,
@@ -120,7 +120,8 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
     __syncthreads();
     // ---- cosine of every source with its two neighbours (equal: the lower position)
     // Up to three sources are picked one by one by this wavefront; more are ranked by all, since every pick is a step behind the last:
-    // 32 x 64 x 64 x 384 bf16, m out of both axes, picked and ranked: m = 2 116.6 us, 119; 3 120.2, 122.0; 4 123.3, 122.8; 10 135.0, 122.5.
+    // 32 x 64 x 64 x 384 bf16, m out of both axes, picked and ranked, when the two were compared: m = 2 116.6 us, 119; 3 120.2, 122.0; 4 123.3,
+    // 122.8; 10 135.0, 122.5 (as it is taken, now 113, 116, 119, 119).
     const bool few = g.m <= 3;
     if (wave == 0) {
         const bool is_src = lane < n_src;
@@ -224,8 +225,8 @@ oim_adjacent_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* me
         }
     } else {
         // ---- the same, a wavefront per destination and tensor; one or two destinations: up to four per row, of a piece and more each.
-        // (us of a call without and with it, merge number 2: 12 x 32 x 32 x 1024 bf16 three times 71.1, 67.6; 2 x 64 x 64 x 1280 twice 51.0,
-        // 49.4.  Of three and more rows the shares stand in each other's way: m = 3 52.1, 53.4; 4 53.1, 53.5; 6 57.1, 57.8.)
+        // (us of a call without and with it, merge number 2: 12 x 32 x 32 x 1024 bf16 three times 66.4, 62.2; 2 x 64 x 64 x 1280 twice 49.1,
+        // 47.7.  When it came in, of three and more rows the shares stand in each other's way: m = 3 52.1, 53.4; 4 53.1, 53.5; 6 57.1, 57.8.)
         const int n_abs = __popcll(ln.takes), n_rows = (xk ? 2 : 1) * n_abs;
         int split = 0;                           // 2^split wavefronts
         while ((64 * V << split) < g.D && (n_abs << (split + 1)) <= 4 && (n_rows << (split + 1)) <= NW) ++split;
@@ -257,8 +258,11 @@ static int adjacent_waves(int len)
 // merge that moves the whole grid)?  us of either way, fitted to 190 schedules on twelve grids of 2 to 430 MB, one to six
 // passes of m = 2 up to every source (off by 15 %, rms).  What counts is bytes (MB of a grid) and, where the lines leave
 // compute units idle, the rounds in which the wavefronts of a line sum its tokens and merge its destinations.  Both ways
-// measured: 8x64x64x1280 bf16 (W,2),(H,2) three times 339 us pass by pass, 170 on ids; (W,31) 61, 59; 32x64x64x384 (W,2) 92, 78;
-// (W,32),(H,16) 112, 119; 2x30x120x1152 (W,2) 24, 22; (W,59) 26, 38; (W,60),(H,7) 40, 48; 1x12x100x640 (W,50),(H,3) 24, 31.
+// measured: 8x64x64x1280 bf16 (W,2),(H,2) three times 341 us pass by pass, 153 on ids; (W,31) 60, 59; 32x64x64x384 (W,2) 90, 72;
+// (W,32),(H,16) 114, 105; 2x30x120x1152 (W,2) 23, 20; (W,59) 25, 37; (W,60),(H,7) 37, 46; 1x12x100x640 (W,50),(H,3) 26, 30.
+// The fit is older than the kernels, which take up to 9 % less on ids since.  The line has not moved with them, since the fit's own
+// error is larger: with by_ids 5 % lower, 3 of 816 drawn schedules go to ids, at 0.82, 0.86 and 1.08 of the time; 10 % lower 7, at 0.82 to 1.08;
+// 6 % higher 21 leave them, at 0.81 to 1.28, most above 1.07.
 // Decided on keys, pass by pass is two more launches and ids always win: (W,31) 65 and 63, (W,32),(H,16) 109 and 80.
 bool oim_adjacent_pays(const int* h, const int* w, const luvc_oim_pass* passes, int n, int B, int D, luvc_dtype dt)
 {
@@ -298,7 +302,7 @@ static luvc_status run_adjacent(const T* x, T* ov, const T* xk, T* ovk, int Dk, 
                                       idx_in, sizes_in, kept_in, g, idx_out, sizes_out, kept_out, pass_map)
     // More wavefronts than 16 per compute unit: several rounds of lines.  bf16 rows of two or three pieces on lines of many wavefronts
     // only where a line merges one or two: the merges of a wavefront wait for one another there (64 tokens of 1280, m = 4 out of
-    // both axes of 8 x 64 x 64: 77.5 us held, 75 not; 640, 5 x 62 x 63, m = 8: 48.2, 46.7; but 48 of 1024, 15 x 48 x 48, m = 8: 64.8, 71).
+    // both axes of 8 x 64 x 64: 73.1 us held, 71.6 not; 640, 5 x 62 x 63, m = 8: 46.7, 45.0; but 48 of 1024, 15 x 48 x 48, m = 8: 63.2, 68.0).
     const bool merges_wait = sizeof(T) == 2 && p * waves > 24 && g.m > 2;
     if (!xk && len <= kAdjTok * waves && p <= 3 && (int64_t)B * nlines * waves > 4096 && !merges_wait) {
         if (p == 1) LUVC_ADJ(1, 1, true);

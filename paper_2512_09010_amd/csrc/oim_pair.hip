@@ -78,10 +78,14 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
     __shared__ int stage[NW];
     constexpr int kSums = 3, kSettled = 16, kFirstUp = 4, kNextUp = 8;
     // Of the wavefronts of a SIMD the oldest comes first, with merges of the second pass before younger ones that have tokens to ask for.
-    // The merges, which nobody waits for, come last instead; the exchange, which neighbours wait for, first; and of the first pass the
-    // earlier rows, as long as a compute unit has one workgroup: with four (tokens of up to 8 words) the later workgroups then hold up
-    // the older ones' ends.  us of the cases with the oldest first, merges last, all of it: 2 x 112 x 112 x 1280 three times, with the score, 61.6, 58.9,
-    // 58.5; 128 x 16 x 16 x 1152 69.1, 68.2, 67.3; 8 x 64 x 64 x 1280 68.0, 67.0, 66.8; 80 x 24 x 24 x 1024 (8 words) 81.0, 80.0, 82.5.
+    // The merges, which nobody waits for, come last instead; the exchange, which neighbours wait for, first.  us of the cases with the oldest
+    // first and so, with the score: 2 x 112 x 112 x 1280 three times 61.6, 58.9; 128 x 16 x 16 x 1152 69.1, 68.2; 8 x 64 x 64 x 1280 68.0, 67.0;
+    // 80 x 24 x 24 x 1024 81.0, 80.0.
+    // Of the first pass the earlier rows come first where a token has more than 8 words, which was never slower.  us of a merge without and
+    // with it: 8 x 64 x 64 x 1152 25.5, 24.9; x 1280 23.6, 23.4; x 1408 34.3, 34.2; 128 x 16 x 16 x 1152 24.8, 24.3; 80 x 24 x 24 x 1280 45.0,
+    // 44.5; 32 x 32 x 32 x 640 fp32 26.1, 25.5; 2 x 112 x 112 x 1280, 4 x 48 x 48 x 1408 fp32 the same.  Narrower tokens gain on some grids
+    // (128 x 16 x 16 x 384 13.8, 12.9; x 1024 22.6, 22.1; 8 x 64 x 64 x 384 13.9, 13.4) and lose on others (80 x 24 x 24 x 768 26.4, 26.9; x 1024
+    // 30.2, 30.8; 8 x 64 x 64 x 512 fp32 21.5, 21.8); what decides there is not known, and they go without.
     constexpr bool kRowsTakeTurns = N > 8;
     __builtin_amdgcn_s_setprio(1);
 
@@ -132,6 +136,8 @@ oim_halve_pair(const T* __restrict__ x, const int32_t* __restrict__ sizes_in, co
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         if (lane == 0) __hip_atomic_store(stage + w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
+    // A wavefront that waits has a high priority, yet cannot keep the one it waits for from running: each look is a trip to LDS that it
+    // stalls on, and the SIMD issues for the others meanwhile.
     auto wait_for = [&](int other, int v) {
         int word;
         do word = __builtin_amdgcn_readfirstlane(__hip_atomic_load(stage + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));

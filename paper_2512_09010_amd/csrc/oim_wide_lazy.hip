@@ -42,13 +42,12 @@
 // flags are handed through LDS where a ballot does, and each step after the screening is one barrier.
 // Bound: the screening, by the rate at which the tokens arrive (8 x 64 x 64 x 1280 bf16: 84 MB a pass), then latency.
 // Of a pass of that grid (20.4 us) the tokens of the last lines are there after 13.9 us, their screened cosines 1.5 us later, and the fp64
-// repeats (0 .. 4), the layout (1) and the merged rows (1.5) follow.  Six passes of merge number 2 and the last copy: 212 us;
-// 185 with eight wavefronts per line where it has a compute unit to itself, ballots in place of lists and fp32 norms in the screening; with
-// the bound of step 1 and the shared merges of step 4 168.  149 with the loads of 64 bytes a row (below; 10 us of the 19),
-// products added up in pieces of 16 bytes beside the norms (2.4 us a pass before), contenders from the m-th highest cosine
-// instead of a comparison with every source (2.1 to 2.8 us a pass before, 0.5) and the anchors fetched with the ids.
-// Lines of up to 32 tokens read half as much as a tile of 64: 12 x 32 x 32 x 1024, six passes, 97.3 -> 81.0 us, 8 x 24 x 24 x 1024
-// fp32, radius 2, four 63.7 -> 56.2, 1 x 16 x 16 x 768, six 57.2 -> 48.0.  Long ones: 4 x 100 x 100 x 1024, two 118 -> 97.
+// repeats (0 .. 4), the layout (1) and the merged rows (1.5) follow; six passes of merge number 2 and the last copy take 144 us.  What the
+// parts give, us with and without: contenders from the m-th highest cosine instead of a comparison with every source 144.1, 149.5, and
+// 8 x 48 x 48 x 768, six passes 84.7, 89.0; lines of up to 64 tokens as one tile, with the registers for a fifth step in flight 144.1, 177.7;
+// lines of up to 32 with half the loads of such a tile 12 x 32 x 32 x 1024, six passes 75.9, 83.5, 1 x 16 x 16 x 768, six 44.6, 50.0,
+// 8 x 24 x 24 x 1024 fp32, radius 2, four 54.6, 61.0.  fp32 on lines of 64 and 100 tokens: 4 x 64 x 64 x 1024, six passes 138.1,
+// 2 x 100 x 100 x 1024, two 107.8.
 #include <type_traits>
 
 #include "common.hpp"
@@ -308,7 +307,11 @@ oim_wide_line(const T* __restrict__ x, T* ov, const T* __restrict__ xk /* metric
     // Result layout of the 16 x 16 instructions: lane l, register v holds row 4 (l / 16) + v, column l % 16.
     {
         constexpr int SUB = TILE == 1 ? 1 : 2;                                // 16 x 16 products along each side of a tile
-        constexpr bool BLOCKS = TILE == 2 && sizeof(T) == 2;                  // LOADS steps are used, then the next are asked for
+        // Steps in flight are a ring, of which one is asked for when another has been used, or, on bf16 lines of one tile of 64, blocks: all
+        // used, then the next asked for.  A fifth step fits the registers in blocks only (as a ring 48 spill, 8 x 64 x 64 x 1280, six
+        // passes 144.9 -> 166.5 us).  In blocks fp32 is slower, 4 x 64 x 64 x 1024 138.1 -> 142.4, 2 x 100 x 100 x 1024 107.8 -> 116.2; bf16 on
+        // longer lines is not.
+        constexpr bool BLOCKS = TILE == 2 && sizeof(T) == 2;
         const int tiles_s = ONE ? 1 : (n_src + 31) / 32, tiles_d = ONE ? n_dst > 0 : (n_dst + 31) / 32, tiles = tiles_s * tiles_d;
         const int r = lane & 15, kq = lane >> 4;
         const bool screens = wave < kScreenWaves;
@@ -735,6 +738,10 @@ static luvc_status run_lazy_pass(const T* x, T* ov, const T* xk, T* ovk, int Dk,
     // eight wavefronts; sixteen where so many destinations are merged that eight would take several rounds and a compute
     // unit has no second line to work on
     const int waves = g.per_line * (xk ? 2 : 1) > 8 && B * nlines <= 256 ? 16 : 8;
+    // Steps in flight: six on lines of up to 32 tokens, four on others, or five (above).  us with other numbers: 12 x 32 x 32 x 1024 bf16, six
+    // passes 76.6 with four to six; 8 x 32 x 32 x 1408, four 49.9, 54.1 with four; x 2048 69.0, 62.1; fp32 8 x 24 x 24 x 1024, four 54.5, 49.6.
+    // fp32 lines of 33 to 64 with three: 4 x 64 x 64 x 1024 138.1, 142.1; 8 x 48 x 48 x 768 101.1, 95.3.  Longer lines with three: bf16
+    // 4 x 100 x 100 x 1024, two 94.2, 119.2, fp32 2 x 100 x 100 x 1024 107.8, 113.8; five do not fit the registers.
     constexpr int kMost = sizeof(T) == 2 ? 5 : 4;
 #define LUVC_WIDE(TILE, LOADS) LUVC_LAUNCH("oim_wide_line", (oim_wide_line<T, TILE, LOADS>), dim3((unsigned)(B * nlines)), dim3(64 * waves), lds, st, x, ov, xk, ovk, Dk, \
                                    idx_in, sizes_in, kept_in, g, idx_out, sizes_out, kept_out, pass_map)

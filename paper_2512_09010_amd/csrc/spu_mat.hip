@@ -495,7 +495,9 @@ MatPlan spu_mat_plan(const MatRun* runs, int n, int D)
 
 // us of one call: the rounds that the workgroups take on the chip, one per compute unit, each with its tables and its hand-over.
 // Fitted to 92 shapes of 56 to 2048 tokens, 0.91 to 1.15 of what was measured (two rounds of one tile 14.8
-// for 16; five groups and more 42 for 48).
+// for 16; five groups and more 42 for 48).  The kernel takes up to 6 % less since, and the line to the other kernels still lies well: with this
+// estimate and that of spu_fold 5 % lower, 5 of 768 drawn calls change kernel, at 0.81, 0.98, 1.09, 1.11 and 1.14 of the time; 6 % higher 5, at 0.98
+// to 1.34.
 static double mat_group_us(const MatShape& sh) { return 0.4 + sh.NT * 2.95; }
 double spu_mat_us(int B, int N, int D, int sigma)
 {

@@ -163,12 +163,13 @@ spu_gather(const unsigned char* __restrict__ x, const int32_t* __restrict__ kept
 // Workgroup g of sample b repeats the selection of the sample on its own (the scores of a sample
 // are a few KB, and the groups run side by side; samples of different lengths share a launch, the argument lists
 // runs of equal ones), keeps the list of kept tokens in LDS, and then copies
-// its share of the kept rows: row q goes to wavefront q mod (4 G) of the sample.  Group 0 also writes
-// kept_idx.  Compared with a selection launch followed by a gather launch this saves a dispatch and the
+// its share of the kept rows: row q goes to wavefront q mod (4 G) of the sample.  The last group, which may have
+// fewer rows, also writes kept_idx.  Compared with a selection launch followed by a gather launch this saves a dispatch and the
 // wait between the two, which is most of the time at these sizes.
 // Bound: latency of the selection, then HBM.  us of a call with scores asked for one by one, an argument list for 64 runs, descriptors
 // made of vector registers and the indices ahead of the rows, and as it is: 8 x 1024 x 3584 bf16, 205 kept, 6.98, 6.77; 32 x 500 x 3584,
-// 100, 10.0, 9.6; 1 x 4096 x 1024, 1433, 7.87, 7.45; fp32 16 x 512 x 896, 150, 6.20, 5.87.
+// 100, 10.0, 9.6; 1 x 4096 x 1024, 1433, 7.87, 7.45; fp32 16 x 512 x 896, 150, 6.20, 5.87.  One by one, three stages of 8 x 1024 x 3584
+// with their scores, 67.0: 68.4 without the kernel for one run, 67.7 with vector descriptors, 67.2 with scores one by one, 67.2 with the indices first.
 // cache policy of the row copies (buffer aux bits): the copied rows are not read again by this kernel, so the stores
 // carry the non-temporal hint (2) and leave less dirty data in L2 for the end of the kernel (measured: -0.3 us)
 constexpr int kPruneLoadAux = 0, kPruneStoreAux = 2;
