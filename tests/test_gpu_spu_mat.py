@@ -47,9 +47,9 @@ SHAPES = [
     (30, 224, 4872, 9, "spu_mat"),              # 16 14  1 10 1
     (8, 1024, 3592, 112, "spu_mat"), (8, 1280, 3592, 110, "spu_mat"), (16, 1040, 1544, 100, "spu_mat"),       # the highest multiple is 7; two groups
     (8, 1270, 1032, 11, "spu_mat"), (8, 1332, 1032, 11, "spu_mat"), (8, 1530, 1032, 30, "spu_mat"), (16, 909, 1032, 30, "spu_mat"),         # N1 = 10, 12, 15 and 9
-    # odd numbers of up to 1024 tokens and 17, 29 and 32 tiles, whose energies a sample's last workgroup adds two columns to a thread: the last
+    # odd numbers of up to 1024 tokens and 19, 29 and 32 tiles, whose energies a sample's last workgroup adds two columns to a thread: the last
     # has one, and the next sample's scores are behind it
-    (8, 909, 2056, 30, "spu_mat"), (8, 1023, 3592, 60, "spu_mat"), (8, 975, 4096, 45, "spu_mat"), (8, 455, 4096, 20, "spu_mat"),
+    (9, 909, 2312, 30, "spu_mat"), (8, 1023, 3592, 60, "spu_mat"), (8, 975, 4096, 45, "spu_mat"), (8, 455, 4096, 20, "spu_mat"),
     # a multiple more, shorter samples: other kernels
     (8, 1024, 3592, 113, "spu_fft16q"), (8, 2016, 1032, 120, "spu_fold"), (16, 910, 584, 150, "spu_fold"), (10, 1040, 968, 200, "spu_fold"),
     (10, 1280, 968, 150, "spu_fold"), (24, 594, 320, 90, "spu_circ"), (16, 390, 520, 40, "spu_circ"),
