@@ -3,7 +3,7 @@
 // only: consecutive items of equal shape and schedule form a run; every item is validated before the first launch.
 //
 // Runs share launches wherever a kernel takes several of them.  OIM: images whose schedules consist of halvings advance
-// together, in as few launches of either kind of step (a pair of passes, a single pass) as their orders allow, then one for the images
+// together, sharing launches of either kind of step (a pair of passes, a single pass) in the best of three orders, then one for the images
 // that stay as they are and the maps of those with several steps.  SPU: the short samples are scored in one launch, all samples pruned
 // in one.  What does not fit these (other merge numbers, long samples, unaligned rows) is a batched call of the entry points
 // in api.hip per run.  A launch costs 4 to 12 us whatever it does: eight images of 24x24 to 56x56 tokens took
