@@ -373,7 +373,7 @@ int spu_fold_blocks(int N, int sigma)
 int spu_fold_tiles(int D) { return (D + kMatWidth - 1) / kMatWidth; }
 
 // us of one call as that of spu_mat: rounds of workgroups, one per compute unit, each with its tables and its hand-over.  Fitted to 123
-// shapes of 56 to 4096 tokens, 0.87 to 1.12 of what was measured.
+// shapes of 56 to 4096 tokens, 0.87 to 1.12 of what was measured; the kernel takes 1 % less since (spu_mat_us has what a lower estimate would change).
 double spu_fold_us(int B, int N, int D, int sigma)
 {
     MatShape sh;
